@@ -209,6 +209,8 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *                    "1": wherever it applies (default: where it was measured shorter than two kernels)
  *   DG_ONEHOT_CODES_SPARSE "0": that kernel on the dense instruction only, "1": on the sparse one wherever the output's
  *                    channel axis is contiguous (the default)
+ *   DG_NIBBLES       "0": AUTO takes 3- and 4-bit tables whole even where they are the sum of two 2-bit lookups; "1": as
+ *                    such sums also while DG_ONEHOT_PLAN is set (which then forces the 2-bit kernel's shape)
  *   DG_PERM_PLAN     index of the permute kernel's tile shape
  */
 typedef enum {

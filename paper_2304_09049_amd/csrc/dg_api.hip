@@ -294,7 +294,7 @@ int64_t dg_conv_out_dim(int64_t in, int64_t k, int64_t stride, int64_t pad)
 
 namespace {
 
-enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Sparse4, Sparse2p, SparseWs, FewN, Unsupported };
+enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Unsupported };
 
 Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
 {
@@ -304,6 +304,7 @@ Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     if (lut->bits != 2) {
         if (variant == DG_KERNEL_LDS) return Pick::Lds;
         if (variant == DG_KERNEL_AUTO) {
+            if (dg_nibble_preferred(lut, p)) return Pick::Nibble;
             if (dg_sparse4_preferred(lut, p)) return Pick::Sparse4;
             return dg_onehot_supports(lut, p) ? Pick::OneHot : Pick::Lds;
         }
@@ -354,6 +355,7 @@ dg_status run(const dg_lut *lut, const DgProblem &p, dg_kernel variant, hipStrea
     case Pick::Lut65k: return dg_launch_lut65k(lut, p, stream);
     case Pick::OneHot: return dg_launch_onehot(lut, p, stream);
     case Pick::Sparse: return dg_launch_sparse(lut, p, stream);
+    case Pick::Nibble: return dg_launch_nibble(lut, p, stream);
     case Pick::Sparse4: return dg_launch_sparse4(lut, p, stream);
     case Pick::Sparse2p: return dg_launch_sparse2p(lut, p, stream);
     case Pick::SparseWs: return dg_launch_sparse_ws(lut, p, stream);
@@ -376,6 +378,7 @@ const char *pick_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Pick::Lut65k: return "lut65k";
     case Pick::OneHot: return dg_onehot_config_name(lut, p);
     case Pick::Sparse: return dg_sparse_config_name(lut, p);
+    case Pick::Nibble: return dg_nibble_config_name(lut, p);
     case Pick::Sparse4: return "onehot_smfmac4_64x128";
     case Pick::Sparse2p: return "onehot_smfmac_2p_32x128";
     case Pick::SparseWs: return "onehot_smfmac_ws_32xK";
@@ -718,6 +721,7 @@ dg_status dg_conv2d_lut_requant(const dg_lut *lut, const void *Wp_dev, const voi
     p.q_zero = q_zero;
     p.q_lo = lo;
     // the re-quantising epilogue lives in the one-hot matrix-core kernels (both instruction forms share it)
+    if (variant == DG_KERNEL_AUTO && dg_nibble_preferred(lut, p)) return dg_launch_nibble(lut, p, (hipStream_t)hip_stream);
     if ((variant == DG_KERNEL_ONEHOT_SMFMAC || variant == DG_KERNEL_AUTO) && dg_sparse_ws_preferred(lut, p))
         return dg_launch_sparse_ws(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_ONEHOT_SMFMAC && lut->bits == 2 && dg_sparse_supports(lut, p))

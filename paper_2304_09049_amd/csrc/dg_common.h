@@ -116,6 +116,9 @@ bool dg_sparse_supports(const dg_lut *lut, const DgProblem &p);
 bool dg_sparse_preferred(const dg_lut *lut, const DgProblem &p);     // AUTO's choice between the two one-hot kernels
 dg_status dg_launch_sparse(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p);
+bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p);      // 3- and 4-bit codes as two 2-bit ones each
+dg_status dg_launch_nibble(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+const char *dg_nibble_config_name(const dg_lut *lut, const DgProblem &p);
 bool dg_sparse4_supports(const dg_lut *lut, const DgProblem &p);      // 4-bit codes on the sparse instruction
 bool dg_sparse4_preferred(const dg_lut *lut, const DgProblem &p);
 dg_status dg_launch_sparse4(const dg_lut *lut, const DgProblem &p, hipStream_t stream);

@@ -41,6 +41,15 @@
 // and 2-bit fields j of its index register; byte j multiplies byte 16h + 4((j % 8) / 2) + field_j of the dense lane
 // (column, j / 8).  The accumulator layout is the dense instruction's.
 //
+// BITS = 24 is the same kernel for 3- and 4-bit codes whose table is a sum of two 2-bit lookups of the activation code,
+//   T[w][4 i + j] = low[w][j] + high[w][i],        i, j = 0..3
+// -- every table of products whose activation levels are spaced evenly (uniform quantisers), and any other table that
+// happens to split so (the host checks each entry).  A 4-bit slot then IS two 2-bit codes, j and i, and the layer a 2-bit
+// one with twice the positions: the packed words are index registers as they are, and only the dense operand differs -- a
+// position's pair of rows (low[w], high[w]) comes from the 16-entry table under the weight slot itself, where a 2-bit
+// layer's pair of rows comes from the same table under two weight codes.  Per position 8 bytes of dense operand instead
+// of the 16 of dg_sparse4_kernel.h, half its matrix work.
+//
 // Entries beyond int8 (2-bit codes only): the table is split into two int8 planes, T = 256 * hi + lo with
 // lo = ((T + 128) mod 256) - 128, each selected into an accumulator of its own (the two planes take the places of the
 // tile's two weight row blocks, so a tile covers 32 rows instead of 64), and the result is 256 * acc_hi + acc_lo.
@@ -55,7 +64,8 @@ typedef dg_v4i v4i;
 typedef dg_v16i v16i;
 
 // pool[v * (L/4) + q] = bytes T[4q .. 4q+3][v] (signed int8, as stored): column v of the table, 4 weight codes per word.
-// A second plane (two-plane tables, 2-bit codes) sits at word 32.
+// A second plane (two-plane tables, 2-bit codes) sits at word 32.  BITS = 20: word w = the row T[w][0..3]; BITS = 24: word w
+// = the row low[w][0..3], word 16 + w = the row high[w][0..3].
 struct Pools {
     uint32_t w[64];
 };
@@ -91,7 +101,8 @@ struct SplitArgs {
 template <int BITS>
 struct Fmt {
     static constexpr bool DECODE = BITS == 0;                   // the decode-and-multiply comparison (2-bit codes)
-    static constexpr bool SPARSE = BITS == 20;                  // 2-bit codes selected by the sparse MFMA's index
+    static constexpr bool NIB = BITS == 24;                     // 4-bit slots looked up as two 2-bit codes each
+    static constexpr bool SPARSE = BITS == 20 || NIB;           // 2-bit codes selected by the sparse MFMA's index
     static constexpr int SLOT = (BITS == 2 || DECODE || SPARSE) ? 2 : 4;  // bits per code slot in a packed byte
     static constexpr int PER_BYTE = 8 / SLOT;                  // codes per packed byte
     static constexpr int SELS = DECODE ? 1 : 8 / SLOT;         // selectors per 32-bit word (decode: the word itself)
@@ -243,14 +254,25 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 // Sparse-instruction form (BITS = 20).  Per wavefront, 16 entries of 8 bytes in LDS: entry (c0 | c1 << 2) holds the
 // table rows of weight codes c0 and c1, row w = bytes T[w][0..3] (pool words 0..3).  A wavefront writes and reads only
 // its own copy, so no barrier is involved (LDS operations of one wavefront execute in order).
+// (NIB, BITS = 24: the same 128 bytes hold the 16 rows low[w], then the 16 rows high[w] -- a position's two rows go to
+// registers that are not neighbours, so they are two 4-byte reads at one address, the second 64 bytes further.)
+template <bool NIB>
+__device__ __forceinline__ void sparse_fill_entry(uint2 *table, const Pools &pl, int i)
+{
+    if (NIB) {
+        ((uint32_t *)table)[i] = pl.w[i], ((uint32_t *)table)[16 + i] = pl.w[16 + i];
+        return;
+    }
+    const int c0 = i & 3, c1 = i >> 2;
+    const uint32_t r0 = c0 == 0 ? pl.w[0] : (c0 == 1 ? pl.w[1] : (c0 == 2 ? pl.w[2] : pl.w[3]));
+    const uint32_t r1 = c1 == 0 ? pl.w[0] : (c1 == 1 ? pl.w[1] : (c1 == 2 ? pl.w[2] : pl.w[3]));
+    table[i] = make_uint2(r0, r1);
+}
+
+template <bool NIB = false>
 __device__ __forceinline__ void sparse_fill_rows(uint2 *rows, const Pools &pl, int lane)
 {
-    if (lane < 16) {
-        const int c0 = lane & 3, c1 = lane >> 2;
-        const uint32_t r0 = c0 == 0 ? pl.w[0] : (c0 == 1 ? pl.w[1] : (c0 == 2 ? pl.w[2] : pl.w[3]));
-        const uint32_t r1 = c1 == 0 ? pl.w[0] : (c1 == 1 ? pl.w[1] : (c1 == 2 ? pl.w[2] : pl.w[3]));
-        rows[lane] = make_uint2(r0, r1);
-    }
+    if (lane < 16) sparse_fill_entry<NIB>(rows, pl, lane);
     __builtin_amdgcn_wave_barrier();
 }
 
@@ -266,48 +288,67 @@ __device__ __forceinline__ uint32_t sparse_pick(int half)
     return half ? 0x07060302u : 0x05040100u;                     // bytes 2,3 (or 0,1) of the lower source, then of the upper
 }
 
-__device__ __forceinline__ void sparse_dense_rows(const uint2 *rows, uint32_t w0, uint32_t w1, uint32_t pick, v8i &even, v8i &odd)
+// Table offsets (bytes) of a lane's codes `v`, a byte each: byte b of `e` leads to operand registers 2b and 2b+1 of the even
+// instruction, byte b of `o` to those of the odd one; NIB: to register 2b (2b+1) of both.
+template <bool NIB>
+__device__ __forceinline__ void sparse_row_offsets(uint32_t v, uint32_t &e, uint32_t &o)
 {
-    const uint32_t v = __builtin_amdgcn_perm(w1, w0, pick), t = v >> 2;
-    const uint32_t e = (v & 0x03030303u) | (t & 0x0C0C0C0Cu);    // byte b: codes 4b and 4b+2 of the 32 bits
-    const uint32_t o = (t & 0x03030303u) | ((v >> 4) & 0x0C0C0C0Cu);    // byte b: codes 4b+1 and 4b+3
+    if (NIB) {
+        e = (v & 0x0F0F0F0Fu) << 2;                              // byte b: 4 * slot 2b
+        o = (v & 0xF0F0F0F0u) >> 2;                              // byte b: 4 * slot 2b+1
+    } else {
+        const uint32_t t = v >> 2;
+        e = ((v & 0x03030303u) | (t & 0x0C0C0C0Cu)) << 3;        // byte b: 8 * (code 4b | code 4b+2 << 2)
+        o = ((t & 0x03030303u) | ((v >> 4) & 0x0C0C0C0Cu)) << 3; // byte b: 8 * (code 4b+1 | code 4b+3 << 2)
+    }
+}
+
+// Four (NIB: eight) pairs of rows read from the table into their places among the operands.
+template <bool NIB>
+__device__ __forceinline__ void sparse_read_rows(const uint2 *table, uint32_t e, uint32_t o, v8i &even, v8i &odd)
+{
+    const char *base = (const char *)table;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        const uint2 x = rows[(e >> (8 * b)) & 255u], y = rows[(o >> (8 * b)) & 255u];
-        even[2 * b] = (int)x.x, even[2 * b + 1] = (int)x.y;
-        odd[2 * b] = (int)y.x, odd[2 * b + 1] = (int)y.y;
+        const char *x = base + ((e >> (8 * b)) & 255u), *y = base + ((o >> (8 * b)) & 255u);
+        if (NIB) {
+            even[2 * b] = *(const int *)x, odd[2 * b] = *(const int *)(x + 64);
+            even[2 * b + 1] = *(const int *)y, odd[2 * b + 1] = *(const int *)(y + 64);
+        } else {
+            const uint2 p = *(const uint2 *)x, q = *(const uint2 *)y;
+            even[2 * b] = (int)p.x, even[2 * b + 1] = (int)p.y;
+            odd[2 * b] = (int)q.x, odd[2 * b + 1] = (int)q.y;
+        }
     }
+}
+
+template <bool NIB = false>
+__device__ __forceinline__ void sparse_dense_rows(const uint2 *rows, uint32_t w0, uint32_t w1, uint32_t pick, v8i &even, v8i &odd)
+{
+    uint32_t e, o;
+    sparse_row_offsets<NIB>(__builtin_amdgcn_perm(w1, w0, pick), e, o);
+    sparse_read_rows<NIB>(rows, e, o, even, odd);
 }
 
 // The same with ONE table for the whole workgroup, at a fixed LDS address: threads 0-15 fill it and the workgroup meets
 // at a barrier before the first read.  A read's address is then nothing but the 4-bit index times 8, and with the
 // indices kept pre-multiplied, a byte each, it is one bit-field extract per read (three instructions per read otherwise:
 // shift, mask, add the wavefront's table base).
+template <bool NIB = false>
 __device__ __forceinline__ void sparse_fill_table(uint2 *table, const Pools &pl, int tid)
 {
-    if (tid < 16) {
-        const int c0 = tid & 3, c1 = tid >> 2;
-        const uint32_t r0 = c0 == 0 ? pl.w[0] : (c0 == 1 ? pl.w[1] : (c0 == 2 ? pl.w[2] : pl.w[3]));
-        const uint32_t r1 = c1 == 0 ? pl.w[0] : (c1 == 1 ? pl.w[1] : (c1 == 2 ? pl.w[2] : pl.w[3]));
-        table[tid] = make_uint2(r0, r1);
-    }
+    if (tid < 16) sparse_fill_entry<NIB>(table, pl, tid);
 }
 
+template <bool NIB = false>
 __device__ __forceinline__ void sparse_dense_rows_shared(const uint2 *table, uint32_t w0, uint32_t w1, uint32_t pick, v8i &even, v8i &odd)
 {
-    const uint32_t v = __builtin_amdgcn_perm(w1, w0, pick), t = v >> 2;
-    uint32_t e = ((v & 0x03030303u) | (t & 0x0C0C0C0Cu)) << 3;          // byte b: 8 * (code 4b | code 4b+2 << 2)
-    uint32_t o = ((t & 0x03030303u) | ((v >> 4) & 0x0C0C0C0Cu)) << 3;   // byte b: 8 * (code 4b+1 | code 4b+3 << 2)
+    uint32_t e, o;
+    sparse_row_offsets<NIB>(__builtin_amdgcn_perm(w1, w0, pick), e, o);
     // (kept as they are: a byte of them IS an LDS offset; left to itself the compiler folds the multiplication into a
     // shift and a mask per read)
     asm volatile("" : "+v"(e), "+v"(o));
-    const char *base = (const char *)table;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const uint2 x = *(const uint2 *)(base + ((e >> (8 * b)) & 255u)), y = *(const uint2 *)(base + ((o >> (8 * b)) & 255u));
-        even[2 * b] = (int)x.x, even[2 * b + 1] = (int)x.y;
-        odd[2 * b] = (int)y.x, odd[2 * b + 1] = (int)y.y;
-    }
+    sparse_read_rows<NIB>(table, e, o, even, odd);
 }
 
 // Position bookkeeping shared by the two kernels: output column n -> image coordinates, and the filter tap of a chunk.
@@ -355,8 +396,8 @@ onehot_mfma_kernel(Args a)
     typedef Fmt<BITS> F;
     static_assert(!RAW || ((BITS == 2 || BITS == 20) && !TWO), "unpacked activations: 2-bit codes, one plane");
     static_assert(!TWO || (WM == 2 && BITS == 2), "two planes stand in for the two weight row blocks of 2-bit tiles");
-    static_assert(BITS == 0 || BITS == 2 || BITS == 3 || BITS == 4 || BITS == 20,
-                  "code widths 2, 3, 4; 0 = the decode comparison; 20 = 2-bit codes on the sparse instruction");
+    static_assert(BITS == 0 || BITS == 2 || BITS == 3 || BITS == 4 || BITS == 20 || BITS == 24,
+                  "code widths 2, 3, 4; 0 = the decode comparison; 20 = 2-bit codes on the sparse instruction, 24 = 4-bit slots as two");
     static_assert(!F::SPARSE || (TR && !TWO), "the sparse operand is the MFMA's row operand: activations on the rows");
     constexpr int RB = TWO ? 1 : WM;                       // weight row blocks of 32 rows
     constexpr int WRUNS = F::SPARSE ? 2 : 1;               // runs of CH words a weight lane reads: its half's, or both
@@ -370,7 +411,7 @@ onehot_mfma_kernel(Args a)
     const int64_t my_tile = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * TPW + tw;
     const bool active = my_tile < a.wave_tiles;
     if (F::SPARSE) {
-        sparse_fill_table(s_rows, a.pools, threadIdx.x);
+        sparse_fill_table<F::NIB>(s_rows, a.pools, threadIdx.x);
         __syncthreads();                                   // (every wavefront of the workgroup, also one without a tile)
     }
     if (SKW == 1 && !active) return;                       // whole waves leave; no barrier follows on this path
@@ -527,7 +568,7 @@ onehot_mfma_kernel(Args a)
             const uint32_t pick = sparse_pick(h);
             auto prepare = [&](int t, int u, int buf) {      // unit u < WM: a weight block; else an activation block
                 if (u < WM)
-                    sparse_dense_rows_shared(s_rows, ca[u].v[t], ca1[u].v[t], pick, dn[buf][u][0], dn[buf][u][1]);
+                    sparse_dense_rows_shared<F::NIB>(s_rows, ca[u].v[t], ca1[u].v[t], pick, dn[buf][u][0], dn[buf][u][1]);
                 else
                     odd_ix[buf][u - WM] = (int)(cb[u - WM].v[t] >> 2);
             };
@@ -676,7 +717,7 @@ onehot_splitk_kernel(SplitArgs a)
     if (F::SPARSE) wa1 = load_words<CH>(w_ptr + (int64_t)min(c0, a.chunks - 1) * (8 * CH) + 4 * CH);
     float sc = 0.0f;
     if (TR && p.scale) sc = p.scale[mw];
-    if (F::SPARSE) sparse_fill_rows(s_rows + 16 * ws, a.pools, lane);
+    if (F::SPARSE) sparse_fill_rows<F::NIB>(s_rows + 16 * ws, a.pools, lane);
     {
         constexpr int LANE_BYTE = RAW ? 16 * CH : 4 * CH;  // bytes a lane half reads per chunk
         const int bpp = RAW ? p.Cin : cq;                  // activation bytes per pixel
@@ -722,7 +763,7 @@ onehot_splitk_kernel(SplitArgs a)
 #pragma unroll
                 for (int word = 0; word < CH; ++word) {
                     v8i even, odd;
-                    sparse_dense_rows(s_rows + 16 * ws, ca.v[word], ca1.v[word], sparse_pick(h), even, odd);
+                    sparse_dense_rows<F::NIB>(s_rows + 16 * ws, ca.v[word], ca1.v[word], sparse_pick(h), even, odd);
                     acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones_even, even, acc, (int)cb.v[word], 0, 0);
                     acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones_odd, odd, acc, (int)cb.v[word], 0, 0);
                 }
@@ -810,7 +851,7 @@ void launch_ch(const Args &a, int ch, dim3 grid, hipStream_t stream)
     static_assert(lds <= 64 * 1024, "the host plans only shapes whose sums fit 64 KB of LDS");
     // (4-bit codes: the host never plans 4-word chunks -- 32 MFMA steps -- so they are not instantiated; nor for the
     // sparse instruction's 64 x 128 and shared tiles, which would spill with them)
-    if constexpr (BITS != 4 && !(BITS == 20 && (WN > 2 || SKW > 1))) {
+    if constexpr (BITS != 4 && !(Fmt<BITS>::SPARSE && (WN > 2 || SKW > 1))) {
         if (ch == 4) {
             hipLaunchKernelGGL((onehot_mfma_kernel<BITS, WM, WN, 4, TR, TWO, SKW>), grid, dim3(256), lds, stream, a);
             return;
@@ -846,7 +887,7 @@ void launch_main(const DgProblem &p, const Pools &pools, const Plan &q, int64_t 
         if constexpr (BITS == 0 && SKW == 1) launch_ch<0, 4, 4, TR, false, 1>(a, q.ch, grid, stream);
     } else if (q.wn == 7) {
         // (the sparse instruction's accumulators cannot live in the accumulation registers: 14 blocks do not fit)
-        if constexpr (SKW != 2 && BITS != 20) launch_ch<BITS, 2, 7, TR, TWO, SKW>(a, q.ch, grid, stream);
+        if constexpr (SKW != 2 && !Fmt<BITS>::SPARSE) launch_ch<BITS, 2, 7, TR, TWO, SKW>(a, q.ch, grid, stream);
     } else if (q.wn == 4) {
         launch_ch<BITS, 2, 4, TR, TWO, SKW>(a, q.ch, grid, stream);
     } else if (q.wn == 2) {
@@ -869,7 +910,7 @@ void launch_split(const DgProblem &p, const Pools &pools, const Plan &q, int64_t
     b.div_ow = make_div((uint32_t)p.OW), b.div_oh = make_div((uint32_t)p.OH);
     b.div_cin = make_div((uint32_t)p.Cin), b.div_kw = make_div((uint32_t)p.KW);
     const dim3 grid((unsigned)blocks11), block(64 * q.S);
-    if constexpr (BITS != 4 && BITS != 20 && !RAW) {        // (on unpacked codes the host plans 2-word chunks at most)
+    if constexpr (BITS != 4 && !Fmt<BITS>::SPARSE && !RAW) {        // (on unpacked codes the host plans 2-word chunks at most)
         if (q.ch == 4) {
             hipLaunchKernelGGL((onehot_splitk_kernel<BITS, 4, TR, TWO, RAW>), grid, block, 0, stream, b);
             return;
@@ -884,7 +925,8 @@ void launch_split(const DgProblem &p, const Pools &pools, const Plan &q, int64_t
 // One translation unit per (code width, output layout, K share) instantiates these (the kernels are many: 4 tiles x
 // 3 chunk sizes each).  TR: the output axis with stride 1 goes on the MFMA columns (see dg_mfma_tile.h).
 // Unit "bBtTkK" defines unit_main_bB_tT_kK, and for K = 1 also unit_split_bB_tT; B = 22 stands for 2-bit codes in two
-// planes, B = 0 for the decode-and-multiply comparison, B = 20 for 2-bit codes on the sparse instruction (T = 1 only).
+// planes, B = 0 for the decode-and-multiply comparison, B = 20 for 2-bit codes on the sparse instruction (T = 1 only), B = 24
+// for 3- and 4-bit codes as two 2-bit ones each on it.
 typedef void (*MainFn)(const DgProblem &, const Pools &, const Plan &, int64_t, hipStream_t);
 #define DGOH_UNIT(B, T, K) \
     void unit_main_b##B##_t##T##_k##K(const DgProblem &, const Pools &, const Plan &, int64_t, hipStream_t);
@@ -892,14 +934,18 @@ typedef void (*MainFn)(const DgProblem &, const Pools &, const Plan &, int64_t, 
     void unit_split_b##B##_t##T(const DgProblem &, const Pools &, const Plan &, int64_t, hipStream_t);
 DGOH_UNIT(2, 0, 1) DGOH_UNIT(2, 0, 2) DGOH_UNIT(2, 0, 4) DGOH_UNIT(2, 1, 1) DGOH_UNIT(2, 1, 2) DGOH_UNIT(2, 1, 4)
 DGOH_UNIT(3, 0, 1) DGOH_UNIT(3, 1, 1) DGOH_UNIT(4, 0, 1) DGOH_UNIT(4, 1, 1) DGOH_UNIT(22, 0, 1) DGOH_UNIT(22, 1, 1)
-DGOH_UNIT(20, 1, 1) DGOH_UNIT(20, 1, 2) DGOH_UNIT(20, 1, 4)
+DGOH_UNIT(20, 1, 1) DGOH_UNIT(20, 1, 2) DGOH_UNIT(20, 1, 4) DGOH_UNIT(24, 1, 1) DGOH_UNIT(24, 1, 2) DGOH_UNIT(24, 1, 4)
 DGOH_UNIT(0, 0, 1) DGOH_UNIT(0, 0, 2) DGOH_UNIT(0, 0, 4) DGOH_UNIT(0, 1, 1) DGOH_UNIT(0, 1, 2) DGOH_UNIT(0, 1, 4)
 DGOH_UNIT_SPLIT(2, 0) DGOH_UNIT_SPLIT(2, 1) DGOH_UNIT_SPLIT(3, 0) DGOH_UNIT_SPLIT(3, 1) DGOH_UNIT_SPLIT(4, 0)
 DGOH_UNIT_SPLIT(4, 1) DGOH_UNIT_SPLIT(22, 0) DGOH_UNIT_SPLIT(22, 1) DGOH_UNIT_SPLIT(0, 0) DGOH_UNIT_SPLIT(0, 1) DGOH_UNIT_SPLIT(20, 1)
+DGOH_UNIT_SPLIT(24, 1)
 void unit_sparse4(const DgProblem &, const uint32_t (&)[16][4], int, hipStream_t);      // dg_sparse4_kernel.h
 void unit_sparse2p(const DgProblem &, const uint32_t (&)[2][4], int, hipStream_t);      // dg_sparse2p_kernel.h
-void unit_sparse_ws(const DgProblem &, const uint32_t (&)[4], int, bool raw, hipStream_t);      // dg_sparse_ws_kernel.h
-void unit_sparse_staged(const DgProblem &, const Pools &, int32_t bias, const Plan &, int64_t, hipStream_t);      // dg_sparse_staged_kernel.h
+// dg_sparse_ws_kernel.h, dg_sparse_staged_kernel.h: 2-bit codes, and ("nib") 4-bit slots as two 2-bit codes each
+void unit_sparse_ws(const DgProblem &, const Pools &, int, bool raw, hipStream_t);
+void unit_sparse_ws_nib(const DgProblem &, const Pools &, int, hipStream_t);
+void unit_sparse_staged(const DgProblem &, const Pools &, int32_t bias, const Plan &, int64_t, hipStream_t);
+void unit_sparse_staged_nib(const DgProblem &, const Pools &, int32_t bias, const Plan &, int64_t, hipStream_t);
 // the split-K kernel on activations still one code per byte (one- and two-plane tables, either output layout)
 void unit_split_codes(const DgProblem &, const Pools &, const Plan &, bool two, bool tr, int64_t, hipStream_t);
 // the tiled kernel on unpacked codes: 64 x 32 and 64 x 64 tiles (q.wn = 1, 2), 2-word chunks, any sharing of K;

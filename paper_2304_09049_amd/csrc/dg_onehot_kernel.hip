@@ -362,25 +362,19 @@ const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p)
     return tile_names[q.skw == 4 ? 2 : (q.skw == 2 ? 1 : 0)][q.wn == 7 ? 0 : (q.wn == 4 ? 1 : (q.wn == 2 ? 2 : 3))];
 }
 
-dg_status dg_launch_sparse(const dg_lut *lut, const DgProblem &p0, hipStream_t stream)
+namespace {
+
+// `p`: the problem as the sparse kernel runs it (sparse_problem); `lo` ... `hi`: the range of the entries in `pools`.
+// NIB: 4-bit slots as two 2-bit codes each (p counts the latter).
+template <bool NIB>
+dg_status launch_sparse(const DgProblem &p, const Plan &q, dgoh::Pools pools, int lo, int hi, hipStream_t stream)
 {
-    const bool transposed = sparse_transposes(p0);
-    const DgProblem p = sparse_problem(p0);
-    const Plan q = sparse_plan(lut, p);
-    // pool word w = the table row of "weight" code w, bytes over the "activation" code (the transposed problem swaps them)
-    dgoh::Pools pools;
-    for (int i = 0; i < 64; ++i) pools.w[i] = 0;
-    for (int w = 0; w < 4; ++w)
-        for (int v = 0; v < 4; ++v) {
-            const int T = transposed ? lut->entry[(v << 2) | w] : lut->entry[(w << 2) | v];
-            pools.w[w] |= (uint32_t)(uint8_t)(int8_t)T << (8 * v);
-        }
     const int64_t blocks11 = tile_count(p, 1, 1), wave_tiles = tile_count(p, q.wm, q.wn);
     if ((q.split ? blocks11 : wave_tiles) > INT32_MAX)
         return dg_fail(DG_ERR_UNSUPPORTED, "sparse one-hot kernel: too many tiles for one grid");
     using namespace dgoh;
     if (q.split) {
-        unit_split_b20_t1(p, pools, q, blocks11, stream);
+        (NIB ? unit_split_b24_t1 : unit_split_b20_t1)(p, pools, q, blocks11, stream);
         return dg_check_launch("onehot_splitk_kernel<20>");
     }
     if (sparse_staged(p, q)) {
@@ -388,23 +382,44 @@ dg_status dg_launch_sparse(const dg_lut *lut, const DgProblem &p0, hipStream_t s
         // fit 32 bits (dg_sparse_staged_kernel.h: fewer toggling bits, a higher sustained clock) -- on problems large
         // enough to heat the chip; shorter kernels only pay the longer start.  DG_STAGED_BIAS: 0 keeps the table as it
         // is, 1 raises it whatever the size (tests, A/B measurement).
-        const int lo = lut->min_entry, hi = lut->max_entry;
         const bool fits = hi - lo <= 127 && (int64_t)(hi - lo > abs(lo) ? hi - lo : abs(lo)) * p.K <= INT32_MAX;
         bool raise = 2.0 * (double)p.M * (double)p.N * (double)p.K >= 2e10;
         if (const char *e = dg_override("DG_STAGED_BIAS")) raise = atoi(e) != 0;
         const int32_t bias = fits && raise ? -lo : 0;
         if (bias != 0)
-            for (int w = 0; w < 4; ++w) {
+            for (int w = 0; w < (NIB ? 32 : 4); ++w) {
                 uint32_t word = 0;
                 for (int v = 0; v < 4; ++v) word |= (uint32_t)(uint8_t)(int8_t)((int8_t)(pools.w[w] >> (8 * v)) + bias) << (8 * v);
                 pools.w[w] = word;
             }
-        unit_sparse_staged(p, pools, bias, q, wave_tiles, stream);
+        (NIB ? unit_sparse_staged_nib : unit_sparse_staged)(p, pools, bias, q, wave_tiles, stream);
         return dg_check_launch("smfmac_staged_kernel");
     }
-    static const MainFn main_units[3] = {unit_main_b20_t1_k1, unit_main_b20_t1_k2, unit_main_b20_t1_k4};
+    static const MainFn main_units[3] = {NIB ? unit_main_b24_t1_k1 : unit_main_b20_t1_k1, NIB ? unit_main_b24_t1_k2 : unit_main_b20_t1_k2,
+                                         NIB ? unit_main_b24_t1_k4 : unit_main_b20_t1_k4};
     main_units[q.skw == 4 ? 2 : (q.skw == 2 ? 1 : 0)](p, pools, q, wave_tiles, stream);
     return dg_check_launch("onehot_mfma_kernel<20>");
+}
+
+// pool word w = the table row of "weight" code w, bytes over the "activation" code (the transposed problem swaps them)
+dgoh::Pools sparse_pools(const dg_lut *lut, bool transposed)
+{
+    dgoh::Pools pools;
+    for (int i = 0; i < 64; ++i) pools.w[i] = 0;
+    for (int w = 0; w < 4; ++w)
+        for (int v = 0; v < 4; ++v) {
+            const int T = transposed ? lut->entry[(v << 2) | w] : lut->entry[(w << 2) | v];
+            pools.w[w] |= (uint32_t)(uint8_t)(int8_t)T << (8 * v);
+        }
+    return pools;
+}
+
+}   // namespace
+
+dg_status dg_launch_sparse(const dg_lut *lut, const DgProblem &p0, hipStream_t stream)
+{
+    const DgProblem p = sparse_problem(p0);
+    return launch_sparse<false>(p, sparse_plan(lut, p), sparse_pools(lut, sparse_transposes(p0)), lut->min_entry, lut->max_entry, stream);
 }
 
 // ---- weights stationary in registers on the sparse instruction (dg_sparse_ws_kernel.h): short reductions without filter window
@@ -475,17 +490,8 @@ namespace {
 
 dg_status launch_ws(const dg_lut *lut, const DgProblem &p0, bool raw, hipStream_t stream)
 {
-    const bool transposed = sparse_transposes(p0);
     const DgProblem p = sparse_problem(p0);
-    uint32_t rows[4];                                      // rows[w] = T[w][0..3] (the transposed problem swaps the codes)
-    for (int w = 0; w < 4; ++w) {
-        rows[w] = 0;
-        for (int v = 0; v < 4; ++v) {
-            const int T = transposed ? lut->entry[(v << 2) | w] : lut->entry[(w << 2) | v];
-            rows[w] |= (uint32_t)(uint8_t)(int8_t)T << (8 * v);
-        }
-    }
-    dgoh::unit_sparse_ws(p, rows, sparse_ws_streams(p, raw), raw, stream);
+    dgoh::unit_sparse_ws(p, sparse_pools(lut, sparse_transposes(p0)), sparse_ws_streams(p, raw), raw, stream);
     return dg_check_launch("smfmac_ws_kernel");
 }
 
@@ -501,6 +507,131 @@ bool dg_sparse_ws_codes_supports(const dg_lut *lut, const DgProblem &p)
 }
 
 dg_status dg_launch_sparse_ws_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream) { return launch_ws(lut, p, true, stream); }
+
+// ---- 3- and 4-bit codes as two 2-bit ones each on the sparse kernels above (dg_onehot_kernel.h, BITS = 24): tables that are
+// ---- the sum of two lookups, T[w][4 i + j] = low[w][j] + high[w][i], as every uniform quantiser's products are.
+// Bound by the matrix pipe (large layers) or latency (small ones) as the 2-bit layers of twice the positions are, whose plans
+// they run in: 8 bytes of dense operand per position instead of the 16 (dg_sparse4_kernel.h) or the 16 (4-bit) and 8 (3-bit)
+// at half the sparse instruction's rate (the dense instruction's kernels) of a table taken whole.  Measured, kernel alone in
+// graph replays, 4-bit codes: 28x28x128 -> 128 3x3 at batch 8 31.3 -> 8.8 us (dense split-K before), 56x56x256 -> 64 at batch
+// 4 10.5 -> 5.4, 14x14x128 -> 464 3x3 at batch 1 9.7 -> 5.3, 56x56x128 -> 128 3x3 at batch 16 64 -> 28.7 (sparse4_kernel
+// before), 56x56x256 -> 256 3x3 at batch 16 215 -> 95; 3-bit codes: 28x28x64 -> 128 at batch 8 4.1 -> 3.5.  No layer
+// measured was faster with the table whole, so the rule has no size in it.
+
+namespace {
+
+struct NibbleTable {
+    dgoh::Pools pools;           // word w: low[w][0..3], word 16 + w: high[w][0..3]
+    int lo, hi;                  // range of all their entries
+};
+
+// The split of a table, if it has one whose parts fit int8 (`transposed`: of the transposed table).  What T says about codes
+// beyond the table's width (3-bit codes in their 4-bit slots) does not matter: they read as the code without the bit.
+bool nibble_table(const dg_lut *lut, bool transposed, NibbleTable *out)
+{
+    if (lut->dtype == DG_LUT_F32 || (lut->bits != 3 && lut->bits != 4)) return false;
+    const int b = lut->bits, mask = (1 << b) - 1;
+    auto T = [&](int w, int a) -> int {
+        w &= mask, a &= mask;
+        return transposed ? lut->entry[(a << b) | w] : lut->entry[(w << b) | a];
+    };
+    out->lo = INT32_MAX, out->hi = INT32_MIN;
+    for (int i = 0; i < 64; ++i) out->pools.w[i] = 0;
+    for (int w = 0; w < 16; ++w) {
+        for (int a = 0; a < 16; ++a)
+            if (T(w, a) != T(w, a & 3) + T(w, a & ~3) - T(w, 0)) return false;
+        // a row's two parts may be moved against each other by any constant: the smaller shift that makes both int8
+        int low_min = INT32_MAX, low_max = INT32_MIN, high_min = INT32_MAX, high_max = INT32_MIN;
+        for (int i = 0; i < 4; ++i) {
+            const int l = T(w, i), h = T(w, 4 * i) - T(w, 0);
+            low_min = l < low_min ? l : low_min, low_max = l > low_max ? l : low_max;
+            high_min = h < high_min ? h : high_min, high_max = h > high_max ? h : high_max;
+        }
+        const int least = -128 - low_min > high_max - 127 ? -128 - low_min : high_max - 127;     // low + shift >= -128, high - shift <= 127
+        const int most = 127 - low_max < high_min + 128 ? 127 - low_max : high_min + 128;
+        if (least > most) return false;
+        const int shift = least > 0 ? least : (most < 0 ? most : 0);
+        for (int i = 0; i < 4; ++i) {
+            const int l = T(w, i) + shift, h = T(w, 4 * i) - T(w, 0) - shift;
+            out->pools.w[w] |= (uint32_t)(uint8_t)(int8_t)l << (8 * i);
+            out->pools.w[16 + w] |= (uint32_t)(uint8_t)(int8_t)h << (8 * i);
+        }
+        const int lo = low_min + shift < high_min - shift ? low_min + shift : high_min - shift;
+        const int hi = low_max + shift > high_max - shift ? low_max + shift : high_max - shift;
+        out->lo = lo < out->lo ? lo : out->lo, out->hi = hi > out->hi ? hi : out->hi;
+    }
+    return true;
+}
+
+// What the 2-bit planner needs to know of such a table: 2-bit codes, int8 entries.
+const dg_lut *two_bit_view()
+{
+    static const dg_lut view = [] {
+        dg_lut t;
+        memset(&t, 0, sizeof(t));
+        t.bits = 2, t.dtype = DG_LUT_I8, t.min_entry = -128, t.max_entry = 127, t.max_abs = 128;
+        return t;
+    }();
+    return &view;
+}
+
+DgProblem nibble_problem(const DgProblem &p)
+{
+    DgProblem t = p;
+    t.Cin = 2 * p.Cin, t.K = 2 * p.K;
+    return t;
+}
+
+}   // namespace
+
+// DG_NIBBLES: 0 never; 1 also while DG_ONEHOT_PLAN is set, which then forces the shape of the kernel (tests, A/B measurement).
+bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p)
+{
+    if (lut->bits != 3 && lut->bits != 4) return false;
+    const char *e = dg_override("DG_NIBBLES");
+    if (e ? atoi(e) == 0 : dg_override("DG_ONEHOT_PLAN") != nullptr) return false;
+    if (p.Cin % 16 != 0 || p.K >= (1 << 29)) return false;
+    NibbleTable t;
+    // (every sum of the split table is a sum of T, whose range the API has checked; partial sums wrap and wrap back)
+    return dg_sparse_supports(two_bit_view(), nibble_problem(p)) && nibble_table(lut, sparse_transposes(p), &t);
+}
+
+const char *dg_nibble_config_name(const dg_lut *, const DgProblem &p)
+{
+    const DgProblem n = nibble_problem(p), t = sparse_problem(n);
+    if (dg_sparse_ws_preferred(two_bit_view(), n)) return "onehot_mfma_4as2_ws_32xK";
+    const Plan q = sparse_plan(two_bit_view(), t);
+    static const char *const split_names[17] = {
+        "", "onehot_mfma_4as2_splitk_s1", "onehot_mfma_4as2_splitk_s2", "onehot_mfma_4as2_splitk_s3", "onehot_mfma_4as2_splitk_s4",
+        "onehot_mfma_4as2_splitk_s5", "onehot_mfma_4as2_splitk_s6", "onehot_mfma_4as2_splitk_s7", "onehot_mfma_4as2_splitk_s8",
+        "onehot_mfma_4as2_splitk_s9", "onehot_mfma_4as2_splitk_s10", "onehot_mfma_4as2_splitk_s11", "onehot_mfma_4as2_splitk_s12",
+        "onehot_mfma_4as2_splitk_s13", "onehot_mfma_4as2_splitk_s14", "onehot_mfma_4as2_splitk_s15", "onehot_mfma_4as2_splitk_s16"};
+    static const char *const tile_names[2][3][4] = {
+        {{"onehot_mfma_4as2_64x32", "onehot_mfma_4as2_64x64", "onehot_mfma_4as2_64x128", ""},
+         {"onehot_mfma_4as2_64x32_k2", "onehot_mfma_4as2_64x64_k2", "onehot_mfma_4as2_64x128_k2", ""},
+         {"onehot_mfma_4as2_64x32_k4", "onehot_mfma_4as2_64x64_k4", "onehot_mfma_4as2_64x128_k4", ""}},
+        {{"onehot_mfma_4as2_staged_32x64", "onehot_mfma_4as2_staged_32x128", "onehot_mfma_4as2_staged_32x192", "onehot_mfma_4as2_staged_32x224"},
+         {"onehot_mfma_4as2_staged_32x64_k2", "onehot_mfma_4as2_staged_32x128_k2", "", ""},
+         {"onehot_mfma_4as2_staged_32x64_k4", "onehot_mfma_4as2_staged_32x128_k4", "", ""}}};
+    if (q.split) return split_names[q.S];
+    if (q.staged && q.wm == 2) return "onehot_smfmac4_64x128";
+    const int k = q.skw == 4 ? 2 : (q.skw == 2 ? 1 : 0);
+    if (q.staged) return tile_names[1][k][q.wn == 2 ? 0 : (q.wn == 4 ? 1 : (q.wn == 6 ? 2 : 3))];
+    return tile_names[0][k][q.wn == 1 ? 0 : (q.wn == 2 ? 1 : 2)];
+}
+
+dg_status dg_launch_nibble(const dg_lut *lut, const DgProblem &p0, hipStream_t stream)
+{
+    NibbleTable t;
+    if (!nibble_table(lut, sparse_transposes(p0), &t))
+        return dg_fail(DG_ERR_UNSUPPORTED, "sparse one-hot kernel: the table is not the sum of two 2-bit lookups");
+    const DgProblem n = nibble_problem(p0), p = sparse_problem(n);
+    if (dg_sparse_ws_preferred(two_bit_view(), n)) {
+        dgoh::unit_sparse_ws_nib(p, t.pools, sparse_ws_streams(p, false), stream);
+        return dg_check_launch("smfmac_ws_kernel");
+    }
+    return launch_sparse<true>(p, sparse_plan(two_bit_view(), p), t.pools, t.lo, t.hi, stream);
+}
 
 // ---- 4-bit codes on the sparse instruction (dg_sparse4_kernel.h): 64 x 128 tiles only, so large layers only
 

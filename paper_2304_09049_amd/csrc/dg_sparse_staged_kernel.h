@@ -27,23 +27,16 @@ namespace dgoh {
 // The dense operands of all WM weight blocks for word `t` of `w` (as sparse_dense_rows_shared, but with the opaque
 // statement that keeps the indices pre-multiplied NOT volatile, so that the scheduler may move these instructions
 // between matrix instructions).
-template <int WM, class W>
+template <bool NIB, int WM, class W>
 __device__ __forceinline__ void dense_rows_movable(const uint2 *table, const W &w, int t, uint32_t pick, v8i (&out)[WM][2])
 {
 #pragma unroll
     for (int u = 0; u < WM; ++u) {
         const uint32_t w0 = t ? w.ca[u].y : w.ca[u].x, w1 = t ? w.ca1[u].y : w.ca1[u].x;
-        const uint32_t v = __builtin_amdgcn_perm(w1, w0, pick), s2 = v >> 2;
-        uint32_t e = ((v & 0x03030303u) | (s2 & 0x0C0C0C0Cu)) << 3;          // byte b: 8 * (code 4b | code 4b+2 << 2)
-        uint32_t o = ((s2 & 0x03030303u) | ((v >> 4) & 0x0C0C0C0Cu)) << 3;   // byte b: 8 * (code 4b+1 | code 4b+3 << 2)
+        uint32_t e, o;
+        sparse_row_offsets<NIB>(__builtin_amdgcn_perm(w1, w0, pick), e, o);
         asm("" : "+v"(e), "+v"(o));
-        const char *base = (const char *)table;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint2 x = *(const uint2 *)(base + ((e >> (8 * b)) & 255u)), y = *(const uint2 *)(base + ((o >> (8 * b)) & 255u));
-            out[u][0][2 * b] = (int)x.x, out[u][0][2 * b + 1] = (int)x.y;
-            out[u][1][2 * b] = (int)y.x, out[u][1][2 * b + 1] = (int)y.y;
-        }
+        sparse_read_rows<NIB>(table, e, o, out[u][0], out[u][1]);
     }
 }
 
@@ -55,7 +48,9 @@ __device__ __forceinline__ void dense_rows_movable(const uint2 *table, const W &
 // 64-position chunks, so the two chunks of a run may lie in different taps -- two different pixels for the loader's two
 // lanes of a row, two sets of kept bytes for the run's two halves -- and the last run of K may be half a run, whose
 // second chunk is fetched from the first's place and multiplied by kept bytes of zero.
-template <int WM, int WN, int SKW, bool TURNS, bool HALF>
+//
+// NIB: 3- and 4-bit codes as two 2-bit ones each (dg_onehot_kernel.h, BITS = 24); K and Cin count the 2-bit codes.
+template <int WM, int WN, int SKW, bool TURNS, bool HALF, bool NIB>
 __global__ void __launch_bounds__(256, 2)
 smfmac_staged_kernel(Args a)
 {
@@ -81,7 +76,7 @@ smfmac_staged_kernel(Args a)
     const int ks = w4 % SKW, tw = w4 / SKW;                 // this wavefront's share of K, and its tile within the workgroup
     const int64_t my_tile = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * TPW + tw;
     const bool active = my_tile < a.wave_tiles;
-    sparse_fill_table(s_rows, a.pools, threadIdx.x);
+    sparse_fill_table<NIB>(s_rows, a.pools, threadIdx.x);
     __syncthreads();                                       // (every wavefront of the workgroup, also one without a tile)
     if (SKW == 1 && !active) return;                       // whole wavefronts leave; no barrier follows on this path
     const int64_t wave_tile = active ? my_tile : 0;        // (an idle wavefront of a shared workgroup adds nothing)
@@ -240,7 +235,7 @@ smfmac_staged_kernel(Args a)
         constexpr int MN = WM * WN;
         // the next step's dense operands: written here, spread by the scheduling groups below a few instructions at a
         // time between this step's matrix instructions, in whose shadow they then issue
-        dense_rows_movable(s_rows, nw, nt, pick, next);
+        dense_rows_movable<NIB>(s_rows, nw, nt, pick, next);
         int odd_ix[SHIFT_ODD ? WN : 1];
         if constexpr (SHIFT_ODD) {
 #pragma unroll
@@ -287,7 +282,7 @@ smfmac_staged_kernel(Args a)
         dg_wait_for_loads();                                   // (both runs: the first is needed now)
         read_words(wa, TURNS ? 0 : g0 & 1, 0);
 #pragma unroll
-        for (int u = 0; u < WM; ++u) sparse_dense_rows_shared(s_rows, wa.ca[u].x, wa.ca1[u].x, pick, dn0[u][0], dn0[u][1]);
+        for (int u = 0; u < WM; ++u) sparse_dense_rows_shared<NIB>(s_rows, wa.ca[u].x, wa.ca1[u].x, pick, dn0[u][0], dn0[u][1]);
         if constexpr (HALF) {
             for (int g = 0; g < runs; ++g) {
                 kept_bytes((int)fdiv((uint32_t)(2 * g), a.div_cpt), true, ones, ones_odd);
@@ -369,7 +364,8 @@ smfmac_staged_kernel(Args a)
 // 8192-cube takes 550 us with an all-zero table, 640 us with entries 0 ... 9, 700 us with -6 ... 3 and 800 us with
 // -64 ... 64.  A table raised to 0 ... max - min keeps the high bits of the dense operand and of the growing sums
 // quiet; the kernel starts each sum at minus the bias times the pixel's positions of K, so the result is the same.
-inline void launch_sparse_staged(const DgProblem &p, const Pools &pools, int32_t bias, const Plan &q, int64_t wave_tiles, hipStream_t stream)
+template <bool NIB>
+void launch_sparse_staged(const DgProblem &p, const Pools &pools, int32_t bias, const Plan &q, int64_t wave_tiles, hipStream_t stream)
 {
     Args a;
     a.p = p;
@@ -392,9 +388,9 @@ inline void launch_sparse_staged(const DgProblem &p, const Pools &pools, int32_t
     const int tpw = 4 / q.skw;
     const dim3 grid((unsigned)((wave_tiles + tpw - 1) / tpw));
     const bool turns = p.KH * p.KW == 1;                   // (see the kernel: run by run without a filter window)
-#define DG_STAGED(WM, WN, SKW, TURNS) hipLaunchKernelGGL((smfmac_staged_kernel<WM, WN, SKW, TURNS, false>), grid, dim3(256), 0, stream, a)
-    if (half && q.wn == 4) hipLaunchKernelGGL((smfmac_staged_kernel<1, 4, 1, false, true>), grid, dim3(256), 0, stream, a);
-    else if (half) hipLaunchKernelGGL((smfmac_staged_kernel<1, 2, 1, false, true>), grid, dim3(256), 0, stream, a);
+#define DG_STAGED(WM, WN, SKW, TURNS) hipLaunchKernelGGL((smfmac_staged_kernel<WM, WN, SKW, TURNS, false, NIB>), grid, dim3(256), 0, stream, a)
+    if (half && q.wn == 4) hipLaunchKernelGGL((smfmac_staged_kernel<1, 4, 1, false, true, NIB>), grid, dim3(256), 0, stream, a);
+    else if (half) hipLaunchKernelGGL((smfmac_staged_kernel<1, 2, 1, false, true, NIB>), grid, dim3(256), 0, stream, a);
     else if (q.wm == 2) DG_STAGED(2, 4, 1, false);
     else if (q.wn == 7) DG_STAGED(1, 7, 1, false);
     else if (q.wn == 6) DG_STAGED(1, 6, 1, false);

@@ -24,7 +24,7 @@ namespace dgoh {
 
 struct WsArgs {
     DgProblem p;
-    uint32_t rows[4];            // rows[w] = bytes T[w][0..3]
+    uint32_t rows[32];           // rows[w] = bytes T[w][0..3]; NIB: low[w][0..3], and high[w][0..3] at 16 + w
     int32_t row_blocks;          // ceil(M / 32)
     int32_t streams;             // runs of pixel blocks; wavefronts = row_blocks * streams
     int32_t run, longer;         // the first `longer` runs have run + 1 pixel blocks, the others `run`
@@ -62,17 +62,21 @@ struct WsArgs {
 // wavefront counts them (9.5 -> 8.9 us on that layer; the same at batch 8: 5.2 -> 4.7 us).
 // STRIDED (packed activations): a 1x1 convolution with a stride and no padding -- output pixel (b, oh, ow) reads the
 // row of input pixel (b, oh * sh, ow * sw).
-template <int T, int G, bool RAW, bool STRIDED = false>
+// NIB: 3- and 4-bit codes as two 2-bit ones each (dg_onehot_kernel.h, BITS = 24); K counts the 2-bit codes.
+template <int T, int G, bool RAW, bool STRIDED = false, bool NIB = false>
 __global__ void __launch_bounds__(256, (!RAW && T * G > 32 ? 1 : 2))
 smfmac_ws_kernel(WsArgs a)
 {
     static_assert(T == 2 || T == 4 || T == 8 || (T == 16 && !RAW), "K = 64, 128 or 256; 512 on packed activations");
     static_assert(!(RAW && STRIDED), "the form that packs reads contiguous pixels");
+    static_assert(!(RAW && NIB), "the form that packs takes 2-bit codes");
     __shared__ uint2 s_rows[16];                            // the table of row pairs, one for the workgroup
     extern __shared__ uint4 s_codes[];                      // RAW: [wavefront][2][32 pixels x 2 T segments]
     const DgProblem &p = a.p;
     const int lane = threadIdx.x & 63, w4 = threadIdx.x >> 6;
-    {
+    if constexpr (NIB) {
+        if (threadIdx.x < 32) ((uint32_t *)s_rows)[threadIdx.x] = a.rows[threadIdx.x];
+    } else {
         Pools pl;
 #pragma unroll
         for (int i = 0; i < 4; ++i) pl.w[i] = a.rows[i];
@@ -168,7 +172,7 @@ smfmac_ws_kernel(WsArgs a)
         }
         const uint32_t pick = sparse_pick(h);
 #pragma unroll
-        for (int t = 0; t < T; ++t) sparse_dense_rows_shared(s_rows, ww[t], ww[T + t], pick, dn[t][0], dn[t][1]);
+        for (int t = 0; t < T; ++t) sparse_dense_rows_shared<NIB>(s_rows, ww[t], ww[T + t], pick, dn[t][0], dn[t][1]);
         // (the weight rows are in registers: their buffer takes the second block)
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (b0 + 1 < b1) stage(b0 + 1, 1);
@@ -181,7 +185,7 @@ smfmac_ws_kernel(WsArgs a)
         if (idle) return;
         const uint32_t pick = sparse_pick(h);
 #pragma unroll
-        for (int t = 0; t < T; ++t) sparse_dense_rows_shared(s_rows, w0.v[t], w1.v[t], pick, dn[t][0], dn[t][1]);
+        for (int t = 0; t < T; ++t) sparse_dense_rows_shared<NIB>(s_rows, w0.v[t], w1.v[t], pick, dn[t][0], dn[t][1]);
         dg_mfma_column_scales<1, true>(p, m0, lane, sc_cols);
     }
     // the kept bytes: (1, 0) per position with the even codes, (0, 1) with the odd; the index of both is the packed word
@@ -260,11 +264,12 @@ smfmac_ws_kernel(WsArgs a)
 }
 
 // `raw`: p.Xp holds codes one per byte
-inline void launch_sparse_ws(const DgProblem &p, const uint32_t (&rows)[4], int streams, bool raw, hipStream_t stream)
+template <bool NIB>
+void launch_sparse_ws(const DgProblem &p, const Pools &pools, int streams, bool raw, hipStream_t stream)
 {
     WsArgs a;
     a.p = p;
-    for (int w = 0; w < 4; ++w) a.rows[w] = rows[w];
+    for (int w = 0; w < 32; ++w) a.rows[w] = pools.w[w];
     a.row_blocks = (p.M + 31) / 32;
     const int pixel_blocks = (p.N + 31) / 32;
     a.streams = streams;
@@ -283,21 +288,22 @@ inline void launch_sparse_ws(const DgProblem &p, const uint32_t (&rows)[4], int 
     // (the staging buffers of the form that packs: 4 wavefronts x 2 blocks x 32 pixels x K bytes, up to 64 KB)
 #define DG_WS(T, G)                                                                                                   \
     do {                                                                                                              \
-        if (raw) {                                                                                                    \
+        if constexpr (!NIB) if (raw) {                                                                                \
             const int lds = 4 * 2 * 32 * 32 * T;                                                                      \
             (void)hipFuncSetAttribute((const void *)smfmac_ws_kernel<T, G, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); \
             hipLaunchKernelGGL((smfmac_ws_kernel<T, G, true>), grid, dim3(256), lds, stream, a);                      \
-        } else if (strided) {                                                                                         \
-            hipLaunchKernelGGL((smfmac_ws_kernel<T, G, false, true>), grid, dim3(256), 0, stream, a);                 \
-        } else {                                                                                                      \
-            hipLaunchKernelGGL((smfmac_ws_kernel<T, G, false>), grid, dim3(256), 0, stream, a);                       \
+            break;                                                                                                    \
         }                                                                                                             \
+        if (strided)                                                                                                  \
+            hipLaunchKernelGGL((smfmac_ws_kernel<T, G, false, true, NIB>), grid, dim3(256), 0, stream, a);            \
+        else                                                                                                          \
+            hipLaunchKernelGGL((smfmac_ws_kernel<T, G, false, false, NIB>), grid, dim3(256), 0, stream, a);                                                                                                             \
     } while (0)
     if (t == 16) {
         if (strided)
-            hipLaunchKernelGGL((smfmac_ws_kernel<16, 4, false, true>), grid, dim3(256), 0, stream, a);
+            hipLaunchKernelGGL((smfmac_ws_kernel<16, 4, false, true, NIB>), grid, dim3(256), 0, stream, a);
         else
-            hipLaunchKernelGGL((smfmac_ws_kernel<16, 4, false>), grid, dim3(256), 0, stream, a);
+            hipLaunchKernelGGL((smfmac_ws_kernel<16, 4, false, false, NIB>), grid, dim3(256), 0, stream, a);
     } else if (t == 8 && wide) DG_WS(8, 8);
     else if (t == 8) DG_WS(8, 4);
     else if (t == 4 && wide) DG_WS(4, 8);

@@ -1,0 +1,89 @@
+"""3- and 4-bit tables that are the sum of two 2-bit lookups, run as 2-bit layers of twice the positions: every kernel form
+that takes them, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2304_09049_amd import binding as dg
+from paper_2304_09049_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# evenly spaced levels; a split whose high part fits int8 only after a shift; unevenly spaced levels that still split
+TABLES = {(4, "uniform"): (list(range(-8, 8)), list(range(16))),
+          (4, "shifted"): ([1] * 8 + [-1, 0] * 4, [-120 + 16 * a for a in range(16)]),
+          (4, "uneven"): ([-3, 2, 1, 0, 5, -6, 4, 7, -7, 6, 3, -1, -2, -5, -4, 2], [g + f for g in (0, 9, -4, 3) for f in (1, 0, 5, 2)]),
+          (3, "uniform"): (list(range(-4, 4)), list(range(1, 9)))}
+# plan override, name's end, whether K must be whole runs of 64 four-bit codes (staged) or a power of two (stationary)
+PLANS = ["auto", "split", "1", "2", "4", "1k2", "2k4", "12", "12k2", "12k4", "14", "14k4", "16", "17", "24", "ws"]
+
+
+def _run(lut, bits, Wc, Xc, desc, scale=None):
+    B, H, W, Cin = Xc.shape
+    Cout = Wc.shape[0]
+    Wp = dg.dg_pack_codes_bits(torch.from_numpy(Wc).cuda(), Cout, Wc.size // Cout, bits)
+    Xp = dg.dg_pack_codes_bits(torch.from_numpy(Xc).cuda(), B * H * W, Cin, bits)
+    y = dg.dg_conv2d_lut(lut, Wp, Xp, desc, scale=scale)
+    torch.cuda.synchronize()
+    return y.cpu().numpy(), Wp, Xp
+
+
+@pytest.mark.parametrize("plan", PLANS)
+@pytest.mark.parametrize("table", list(TABLES))
+def test_nibble_tables(table, plan, monkeypatch):
+    bits, (lw, la) = table[0], TABLES[table]
+    lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I8)
+    monkeypatch.setenv("DG_NIBBLES", "1")
+    if plan != "auto":
+        monkeypatch.setenv("DG_ONEHOT_PLAN", plan)
+    rng = np.random.default_rng(len(plan) + bits)
+    nlev = 1 << bits
+    ran = 0
+    for (B, H, W, Cin, Cout, k, stride, pad) in [(2, 9, 7, 16, 12, 3, (2, 1), (1, 1)), (1, 13, 11, 64, 40, 3, (1, 1), (1, 1)),
+                                                 (2, 8, 9, 96, 68, 3, (1, 2), (1, 1)), (1, 17, 31, 128, 100, 1, (1, 1), (0, 0)),
+                                                 (1, 40, 31, 32, 36, 1, (1, 1), (0, 0)), (1, 6, 5, 256, 33, 5, (1, 1), (2, 2))]:
+        desc = dg.conv_desc(B, H, W, Cin, Cout, k, k, stride, pad)
+        name = dg.dg_conv_kernel_name(lut, desc)
+        assert "4as2" in name or name == "onehot_smfmac4_64x128", name
+        ran += plan == "auto" or plan == "split" or ("ws" in name) == (plan == "ws")
+        Wc, Xc = wl.draw_codes(rng, (Cout, k, k, Cin), nlev=nlev), wl.draw_codes(rng, (B, H, W, Cin), nlev=nlev)
+        want = oracle.conv2d(Wc, Xc, lw, la, stride=stride, pad=pad)
+        got, Wp, Xp = _run(lut, bits, Wc, Xc, desc)
+        assert np.array_equal(got, want), (name, B, H, W, Cin, Cout, k)
+        scale = rng.uniform(0.01, 0.1, size=Cout).astype(np.float32)
+        y = oracle.scale_epilogue_nhwc(want, scale)
+        got, Wp, Xp = _run(lut, bits, Wc, Xc, desc, torch.from_numpy(scale).cuda())
+        assert np.array_equal(got, y), (name, "scaled")
+        if Cout % 4 == 0:
+            qs = float(np.float32(3.0 / max(1e-6, float(np.percentile(np.abs(y), 90)))))
+            packed = dg.dg_conv2d_lut_requant(lut, Wp, Xp, desc, torch.from_numpy(scale).cuda(), qs, 0.5, 0)
+            torch.cuda.synchronize()
+            codes = oracle.quantize_codes(y, qs, 0.5, 0, 3)
+            assert np.array_equal(packed.cpu().numpy().reshape(-1, Cout // 4), oracle.pack_codes(codes.reshape(-1, Cout))), (name, "requant")
+    assert ran
+    for M, N, K in ((33, 130, 64), (70, 300, 256), (5, 1000, 96)):
+        Wc, Ac = wl.draw_codes(rng, (M, K), nlev=nlev), wl.draw_codes(rng, (N, K), nlev=nlev)
+        Wp = dg.dg_pack_codes_bits(torch.from_numpy(Wc).cuda(), M, K, bits)
+        Ap = dg.dg_pack_codes_bits(torch.from_numpy(Ac).cuda(), N, K, bits)
+        want = oracle.gemm(Wc, Ac, lw, la)
+        for strides, shape in (((1, M), (N, M)), ((N, 1), (M, N))):
+            out = torch.full(shape, -7, dtype=torch.int32, device="cuda")
+            dg.dg_gemm_lut(lut, Wp, Ap, M, N, K, out=out, strides=strides)      # (row-major only if the transposed table splits)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), want.T if strides[0] == 1 else want), (M, N, K, strides)
+
+
+def test_raised_nibble_table(monkeypatch):
+    """The staged kernel on the table raised to non-negative entries (its default on large problems only)."""
+    bits, (lw, la) = 4, TABLES[(4, "uniform")]
+    lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I8)
+    rng = np.random.default_rng(5)
+    monkeypatch.setenv("DG_NIBBLES", "1")
+    monkeypatch.setenv("DG_STAGED_BIAS", "1")
+    Wc, Xc = wl.draw_codes(rng, (70, 3, 3, 64), nlev=16), wl.draw_codes(rng, (2, 11, 10, 64), nlev=16)
+    want = oracle.conv2d(Wc, Xc, lw, la, stride=(1, 1), pad=(1, 1))
+    for plan in ("12k4", "14", "24", "17"):
+        monkeypatch.setenv("DG_ONEHOT_PLAN", plan)
+        got, _, _ = _run(lut, bits, Wc, Xc, dg.conv_desc(2, 11, 10, 64, 70, 3, 3, (1, 1), (1, 1)))
+        assert np.array_equal(got, want), plan
