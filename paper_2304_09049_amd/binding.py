@@ -1,8 +1,9 @@
-"""ctypes binding over the C ABI of ``libdeepgemm_hip.so`` (declared in ``include/deepgemm_hip.h``).
+"""Binding over the C ABI of ``libdeepgemm_hip.so`` (declared in ``include/deepgemm_hip.h``).
 
 Argument marshalling only: every step of the path runs in the library's HIP kernels.  torch is
-used for device memory and streams, nothing else.  There is no CPU fallback: if the library has
-not been built, loading fails with an explicit error.
+used for device memory and streams, nothing else.  The run-time calls go through ``_native.so``
+(``csrc/binding_native.cpp``: the same checks and the call, in C++), tables and sizes through ctypes.
+There is no CPU fallback: if either library has not been built, loading fails with an explicit error.
 """
 from __future__ import annotations
 
@@ -12,6 +13,7 @@ from typing import Optional, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdeepgemm_hip.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 DG_OK = 0
 STATUS_NAMES = ("DG_OK", "DG_ERR_NULL", "DG_ERR_SHAPE", "DG_ERR_RANGE", "DG_ERR_BUFFER",
@@ -112,6 +114,21 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+_native = None
+
+
+def _load_native():
+    """Load the native marshalling module (once).  Raises if it has not been built: there is no other path."""
+    global _native
+    lib()
+    import torch  # noqa: F401  (the module uses torch's libraries)
+    if not os.path.exists(NATIVE_PATH):
+        raise ImportError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2304_09049_amd.build`.")
+    from . import _native as module
+    _native = module
+    return module
+
+
 def _check(status: int) -> None:
     if status != DG_OK:
         raise DgError(status, lib().dg_last_error().decode())
@@ -128,37 +145,26 @@ def _stream_ptr(stream) -> ctypes.c_void_p:
     return ctypes.c_void_p(s.cuda_stream)
 
 
-def _dev_ptr(t, dtype=None, name="tensor") -> ctypes.c_void_p:
-    if t is None:
-        return ctypes.c_void_p(0)
-    if not t.is_cuda:
-        raise ValueError(f"{name} must live in device memory")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    if dtype is not None and t.dtype != dtype:
-        raise ValueError(f"{name} must have dtype {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
-
-
 class Lut:
     """Owner of a ``dg_lut`` built by ``dg_build_lut``."""
 
     def __init__(self, levels_w: Sequence[int], levels_a: Sequence[int], entry: int = DG_LUT_I8, bits: int = 2,
                  entries: Optional[Sequence[int]] = None):
         self._h = None
+        self._address = 0                             # the handle as a number, for the native module
         self.bits = bits
         self.is_f32 = entry == DG_LUT_F32
         handle = ctypes.c_void_p(0)
         if entries is not None:                       # a table given as such (any 16 integers)
             arr = (ctypes.c_int16 * 16)(*[int(v) for v in entries])
             _check(lib().dg_build_lut_entries(arr, int(entry), ctypes.byref(handle)))
-            self._h = handle
+            self._h, self._address = handle, handle.value
             return
         if self.is_f32:                               # binary32 products of floating-point levels
             lwf = (ctypes.c_float * 4)(*[float(v) for v in levels_w])
             laf = (ctypes.c_float * 4)(*[float(v) for v in levels_a])
             _check(lib().dg_build_lut_f32(lwf, laf, ctypes.byref(handle)))
-            self._h = handle
+            self._h, self._address = handle, handle.value
             return
         nlev = 1 << bits
         if len(levels_w) != nlev or len(levels_a) != nlev:
@@ -169,7 +175,7 @@ class Lut:
             _check(lib().dg_build_lut(lw, la, int(entry), ctypes.byref(handle)))
         else:
             _check(lib().dg_build_lut_bits(bits, lw, la, int(entry), ctypes.byref(handle)))
-        self._h = handle
+        self._h, self._address = handle, handle.value
 
     @property
     def handle(self) -> ctypes.c_void_p:
@@ -191,7 +197,7 @@ class Lut:
     def __del__(self):
         if getattr(self, "_h", None) is not None and _lib is not None:
             _lib.dg_lut_destroy(self._h)
-            self._h = None
+            self._h, self._address = None, 0
 
 
 def dg_build_lut(levels_w, levels_a, entry: int = DG_LUT_I8) -> Lut:
@@ -216,11 +222,12 @@ def dg_packed_bytes_bits(rows: int, K: int, bits: int) -> int:
 
 def dg_pack_codes_bits(codes, rows: int, K: int, bits: int, out=None, stream=None):
     """codes: uint8 device tensor with rows*K elements of `bits`-bit codes -> packed uint8 tensor (weights or activations)."""
-    import torch
     if out is None:
+        import torch
         out = torch.empty(dg_packed_bytes_bits(rows, K, bits), dtype=torch.uint8, device=codes.device)
-    _check(lib().dg_pack_codes_bits(_dev_ptr(codes, torch.uint8, "codes"), rows, K, bits,
-                                    _dev_ptr(out, torch.uint8, "packed"), out.numel(), _stream_ptr(stream)))
+    status = (_native or _load_native()).pack_codes_bits(codes, rows, K, bits, out, stream)
+    if status:
+        _check(status)
     return out
 
 
@@ -236,49 +243,54 @@ def dg_conv_out_dim(size: int, k: int, stride: int, pad: int) -> int:
     return int(lib().dg_conv_out_dim(size, k, stride, pad))
 
 
-def _pack(fn, size_fn, codes, rows: int, K: int, out, stream):
-    import torch
-    if out is None:
-        out = torch.empty(size_fn(rows, K), dtype=torch.uint8, device=codes.device)
-    _check(fn(_dev_ptr(codes, torch.uint8, "codes"), rows, K, _dev_ptr(out, torch.uint8, "packed"),
-              out.numel(), _stream_ptr(stream)))
-    return out
-
-
 def dg_pack_weights(codes, M: int, K: int, out=None, stream=None):
     """codes: uint8 device tensor with M*K elements ([M][K], or [Cout][KH][KW][Cin]) -> packed uint8 tensor."""
-    return _pack(lib().dg_pack_weights, dg_packed_weight_bytes, codes, M, K, out, stream)
+    if out is None:
+        import torch
+        out = torch.empty(dg_packed_weight_bytes(M, K), dtype=torch.uint8, device=codes.device)
+    status = (_native or _load_native()).pack_weights(codes, M, K, out, stream)
+    if status:
+        _check(status)
+    return out
 
 
 def dg_pack_activations(codes, N: int, K: int, out=None, stream=None):
     """codes: uint8 device tensor with N*K elements ([N][K], or NHWC with N = B*H*W, K = C) -> packed uint8 tensor."""
-    return _pack(lib().dg_pack_activations, dg_packed_activation_bytes, codes, N, K, out, stream)
+    if out is None:
+        import torch
+        out = torch.empty(dg_packed_activation_bytes(N, K), dtype=torch.uint8, device=codes.device)
+    status = (_native or _load_native()).pack_activations(codes, N, K, out, stream)
+    if status:
+        _check(status)
+    return out
 
 
 def dg_quantize_pack_activations(x, N: int, K: int, scale: float, zero_point: float, lo: int, out=None, stream=None):
     """x: float32 device tensor with N*K elements -> packed 2-bit codes of clip(rint(scale*x + zero_point), lo, lo+3) - lo."""
-    import torch
     if out is None:
+        import torch
         out = torch.empty(dg_packed_activation_bytes(N, K), dtype=torch.uint8, device=x.device)
-    _check(lib().dg_quantize_pack_activations(_dev_ptr(x, torch.float32, "x"), N, K, scale, zero_point, lo,
-                                              _dev_ptr(out, torch.uint8, "packed"), out.numel(), _stream_ptr(stream)))
+    status = (_native or _load_native()).quantize_pack_activations(x, N, K, scale, zero_point, lo, out, stream)
+    if status:
+        _check(status)
     return out
+
+
+def _empty(shape, lut: Lut, scale, device):
+    import torch
+    return torch.empty(shape, dtype=torch.float32 if scale is not None or lut.is_f32 else torch.int32, device=device)
 
 
 def dg_gemm_lut(lut: Lut, Wp, Ap, M: int, N: int, K: int, out=None, scale=None, variant="auto",
                 stream=None, strides: Optional[Sequence[int]] = None):
     """C[m][n] = sum_k LUT[4*Wc[m][k] + Ac[n][k]].  Returns int32 [M][N], or float32 when `scale` is given."""
-    import torch
-    as_float = scale is not None or lut.is_f32
-    dtype = torch.float32 if as_float else torch.int32
     if out is None:
-        out = torch.empty((M, N), dtype=dtype, device=Wp.device)
+        out = _empty((M, N), lut, scale, Wp.device)
     scm, scn = (N, 1) if strides is None else strides
-    c_int = _dev_ptr(out, torch.int32, "out") if not as_float else ctypes.c_void_p(0)
-    c_f32 = _dev_ptr(out, torch.float32, "out") if as_float else ctypes.c_void_p(0)
-    _check(lib().dg_gemm_lut(lut.handle, _dev_ptr(Wp, torch.uint8, "Wp"), _dev_ptr(Ap, torch.uint8, "Ap"),
-                             M, N, K, c_int, scm, scn, _dev_ptr(scale, torch.float32, "scale"), c_f32,
-                             _kernel(variant), _stream_ptr(stream)))
+    status = (_native or _load_native()).gemm_lut(lut._address, lut.is_f32, Wp, Ap, M, N, K, out, scm, scn, scale,
+                                                  _kernel(variant), stream)
+    if status:
+        _check(status)
     return out
 
 
@@ -286,18 +298,13 @@ def dg_gemm_lut_codes(lut: Lut, Wp, Ac, M: int, N: int, K: int, work=None, out=N
                       stream=None, strides: Optional[Sequence[int]] = None):
     """Packing stage + GEMM as one call, from codes one per byte (`Ac`: uint8 [N][K]).  `work` is the packed-activation
     buffer the library uses when it does not fuse the packing into the kernel (may be None)."""
-    import torch
-    as_float = scale is not None or lut.is_f32
-    dtype = torch.float32 if as_float else torch.int32
     if out is None:
-        out = torch.empty((M, N), dtype=dtype, device=Wp.device)
+        out = _empty((M, N), lut, scale, Wp.device)
     scm, scn = (N, 1) if strides is None else strides
-    c_int = _dev_ptr(out, torch.int32, "out") if not as_float else ctypes.c_void_p(0)
-    c_f32 = _dev_ptr(out, torch.float32, "out") if as_float else ctypes.c_void_p(0)
-    _check(lib().dg_gemm_lut_codes(lut.handle, _dev_ptr(Wp, torch.uint8, "Wp"), _dev_ptr(Ac, torch.uint8, "Ac"), M, N, K,
-                                   _dev_ptr(work, torch.uint8, "work"), 0 if work is None else work.numel(), c_int,
-                                   scm, scn, _dev_ptr(scale, torch.float32, "scale"), c_f32, _kernel(variant),
-                                   _stream_ptr(stream)))
+    status = (_native or _load_native()).gemm_lut_codes(lut._address, lut.is_f32, Wp, Ac, M, N, K, work, out, scm, scn, scale,
+                                                        _kernel(variant), stream)
+    if status:
+        _check(status)
     return out
 
 
@@ -309,39 +316,31 @@ def conv_desc(B, H, W, Cin, Cout, KH, KW, stride=(1, 1), pad=(0, 0)) -> ConvDesc
     return ConvDesc(B, H, W, Cin, Cout, KH, KW, stride[0], stride[1], pad[0], pad[1])
 
 
-def dg_conv2d_lut(lut: Lut, Wp, Xp, desc: ConvDesc, out=None, scale=None, variant="auto", stream=None):
-    """NHWC convolution by table lookup.  Returns [B][OH][OW][Cout], int32 or float32 (when `scale` is given)."""
-    import torch
+def _conv_shape(desc: ConvDesc):
     OH = dg_conv_out_dim(desc.H, desc.KH, desc.stride_h, desc.pad_h)
     OW = dg_conv_out_dim(desc.W, desc.KW, desc.stride_w, desc.pad_w)
-    as_float = scale is not None or lut.is_f32
-    dtype = torch.float32 if as_float else torch.int32
+    return desc.B, max(OH, 0), max(OW, 0), desc.Cout
+
+
+def dg_conv2d_lut(lut: Lut, Wp, Xp, desc: ConvDesc, out=None, scale=None, variant="auto", stream=None):
+    """NHWC convolution by table lookup.  Returns [B][OH][OW][Cout], int32 or float32 (when `scale` is given)."""
     if out is None:
-        out = torch.empty((desc.B, max(OH, 0), max(OW, 0), desc.Cout), dtype=dtype, device=Wp.device)
-    y_int = _dev_ptr(out, torch.int32, "out") if not as_float else ctypes.c_void_p(0)
-    y_f32 = _dev_ptr(out, torch.float32, "out") if as_float else ctypes.c_void_p(0)
-    _check(lib().dg_conv2d_lut(lut.handle, _dev_ptr(Wp, torch.uint8, "Wp"), _dev_ptr(Xp, torch.uint8, "Xp"),
-                               ctypes.byref(desc), y_int, _dev_ptr(scale, torch.float32, "scale"), y_f32,
-                               _kernel(variant), _stream_ptr(stream)))
+        out = _empty(_conv_shape(desc), lut, scale, Wp.device)
+    status = (_native or _load_native()).conv2d_lut(lut._address, lut.is_f32, Wp, Xp, desc, out, scale, _kernel(variant), stream)
+    if status:
+        _check(status)
     return out
 
 
 def dg_conv2d_lut_codes(lut: Lut, Wp, Xc, desc: ConvDesc, work=None, out=None, scale=None, variant="auto", stream=None):
     """Packing stage + NHWC convolution as one call, from codes one per byte (`Xc`: uint8 [B][H][W][Cin]).  `work` is
     the packed-activation buffer the library uses when it does not fuse the packing into the kernel (may be None)."""
-    import torch
-    OH = dg_conv_out_dim(desc.H, desc.KH, desc.stride_h, desc.pad_h)
-    OW = dg_conv_out_dim(desc.W, desc.KW, desc.stride_w, desc.pad_w)
-    as_float = scale is not None or lut.is_f32
-    dtype = torch.float32 if as_float else torch.int32
     if out is None:
-        out = torch.empty((desc.B, max(OH, 0), max(OW, 0), desc.Cout), dtype=dtype, device=Wp.device)
-    y_int = _dev_ptr(out, torch.int32, "out") if not as_float else ctypes.c_void_p(0)
-    y_f32 = _dev_ptr(out, torch.float32, "out") if as_float else ctypes.c_void_p(0)
-    work_bytes = 0 if work is None else work.numel()
-    _check(lib().dg_conv2d_lut_codes(lut.handle, _dev_ptr(Wp, torch.uint8, "Wp"), _dev_ptr(Xc, torch.uint8, "Xc"),
-                                     ctypes.byref(desc), _dev_ptr(work, torch.uint8, "work"), work_bytes, y_int,
-                                     _dev_ptr(scale, torch.float32, "scale"), y_f32, _kernel(variant), _stream_ptr(stream)))
+        out = _empty(_conv_shape(desc), lut, scale, Wp.device)
+    status = (_native or _load_native()).conv2d_lut_codes(lut._address, lut.is_f32, Wp, Xc, desc, work, out, scale,
+                                                          _kernel(variant), stream)
+    if status:
+        _check(status)
     return out
 
 
@@ -351,13 +350,10 @@ def dg_static_work_bytes() -> int:
 
 def dg_conv2d_lut_codes_static(lut: Lut, Wp, Xc, desc: ConvDesc, out, scale=None, variant="auto", stream=None):
     """dg_conv2d_lut_codes with the library's own staging buffer; `out` is required (the call allocates nothing)."""
-    import torch
-    as_float = scale is not None or lut.is_f32
-    y_int = _dev_ptr(out, torch.int32, "out") if not as_float else ctypes.c_void_p(0)
-    y_f32 = _dev_ptr(out, torch.float32, "out") if as_float else ctypes.c_void_p(0)
-    _check(lib().dg_conv2d_lut_codes_static(lut.handle, _dev_ptr(Wp, torch.uint8, "Wp"), _dev_ptr(Xc, torch.uint8, "Xc"),
-                                            ctypes.byref(desc), y_int, _dev_ptr(scale, torch.float32, "scale"), y_f32,
-                                            _kernel(variant), _stream_ptr(stream)))
+    status = (_native or _load_native()).conv2d_lut_codes_static(lut._address, lut.is_f32, Wp, Xc, desc, out, scale,
+                                                                 _kernel(variant), stream)
+    if status:
+        _check(status)
     return out
 
 
@@ -380,24 +376,24 @@ def dg_launch_empty(blocks: int, threads: int, stream=None) -> None:
 
 def dg_dequantize(acc, rows: int, C: int, scale, out=None, stream=None):
     """acc: int32 device tensor [rows][C]; scale: float32 [C] -> float32 [rows][C] = float(acc) * scale[c]."""
-    import torch
     if out is None:
+        import torch
         out = torch.empty(acc.shape, dtype=torch.float32, device=acc.device)
-    _check(lib().dg_dequantize(_dev_ptr(acc, torch.int32, "acc"), rows, C, _dev_ptr(scale, torch.float32, "scale"),
-                               _dev_ptr(out, torch.float32, "out"), _stream_ptr(stream)))
+    status = (_native or _load_native()).dequantize(acc, rows, C, scale, out, stream)
+    if status:
+        _check(status)
     return out
 
 
 def dg_conv2d_lut_requant(lut: Lut, Wp, Xp, desc: ConvDesc, scale, q_scale: float, q_zero: float, lo: int, out=None,
                           variant="auto", stream=None):
     """One fused layer: table convolution, per-channel scale, re-quantisation and packing -> packed uint8 [B*OH*OW][Cout/4]."""
-    import torch
-    OH = dg_conv_out_dim(desc.H, desc.KH, desc.stride_h, desc.pad_h)
-    OW = dg_conv_out_dim(desc.W, desc.KW, desc.stride_w, desc.pad_w)
     if out is None:
-        out = torch.empty(dg_packed_activation_bytes(desc.B * OH * OW, desc.Cout), dtype=torch.uint8, device=Wp.device)
-    _check(lib().dg_conv2d_lut_requant(lut.handle, _dev_ptr(Wp, torch.uint8, "Wp"), _dev_ptr(Xp, torch.uint8, "Xp"),
-                                       ctypes.byref(desc), _dev_ptr(scale, torch.float32, "scale"), q_scale, q_zero, lo,
-                                       _dev_ptr(out, torch.uint8, "packed"), out.numel(), _kernel(variant),
-                                       _stream_ptr(stream)))
+        import torch
+        B, OH, OW, Cout = _conv_shape(desc)
+        out = torch.empty(dg_packed_activation_bytes(B * OH * OW, Cout), dtype=torch.uint8, device=Wp.device)
+    status = (_native or _load_native()).conv2d_lut_requant(lut._address, Wp, Xp, desc, scale, q_scale, q_zero, lo, out,
+                                                            _kernel(variant), stream)
+    if status:
+        _check(status)
     return out

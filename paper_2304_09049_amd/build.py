@@ -1,4 +1,4 @@
-"""Build libdeepgemm_hip.so in-tree with hipcc for gfx950.
+"""Build libdeepgemm_hip.so in-tree with hipcc for gfx950, and _native.so, the Python module over it, with g++.
 
 Run as ``python -m paper_2304_09049_amd.build`` (or call ``build()``).  The library is placed next
 to this file so that it travels with the source tree; nothing is installed.
@@ -27,6 +27,27 @@ HIPCC_FLAGS = [
     "-ffp-contract=off",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
+
+
+NATIVE = os.path.join(HERE, "_native.so")
+
+
+def build_native(verbose: bool = True) -> str:
+    """Compile the native marshalling module (host code; it uses torch's tensor type and links the library)."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+           + [f for d in include_paths("cpu") for f in ("-isystem", d)]
+           + ["-isystem", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+              os.path.join(CSRC, "binding_native.cpp"), "-o", NATIVE, "-L", HERE, "-l:libdeepgemm_hip.so"]
+           + [f for d in library_paths("cpu") for f in ("-L", d)]
+           + ["-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"])
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return NATIVE
 
 
 def sources():
@@ -74,6 +95,7 @@ def build(verbose: bool = True, extra_flags=(), jobs: int = 8, incremental: bool
     if verbose:
         print(" ".join(link), flush=True)
     subprocess.run(link, check=True)
+    build_native(verbose)
     return LIB
 
 

@@ -35,14 +35,16 @@ dg_status dg_fail(dg_status s, const char *fmt, ...)
     return s;
 }
 
-const char *dg_override(const char *name)
+bool dg_overrides_enabled()
 {
     static const bool enabled = [] {
         const char *e = getenv("DG_TEST_OVERRIDES");
         return e != nullptr && e[0] == '1' && e[1] == 0;
     }();
-    return enabled ? getenv(name) : nullptr;
+    return enabled;
 }
+
+const char *dg_override(const char *name) { return dg_overrides_enabled() ? getenv(name) : nullptr; }
 
 int dg_simd_count()
 {

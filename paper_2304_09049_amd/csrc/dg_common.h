@@ -71,6 +71,7 @@ inline DgFastDiv dg_make_div(uint32_t d)
 // Value of a test / measurement override (an environment variable), or nullptr.  Overrides are looked at only when
 // DG_TEST_OVERRIDES=1 was set when the library was first called; otherwise this returns nullptr without reading anything.
 const char *dg_override(const char *name);
+bool dg_overrides_enabled();
 // Number of SIMD units of the current device (compute units x 4), asked from the runtime once.
 int dg_simd_count();
 // Record the calling thread's error detail and return `s`.

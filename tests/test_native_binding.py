@@ -1,0 +1,80 @@
+"""The native marshalling module's checks, and the planner's memo (neither needs a GPU)."""
+import os
+import subprocess
+import sys
+
+import pytest
+import torch
+
+from paper_2304_09049_amd import binding as dg
+
+SHAPES = """
+import random, sys
+from paper_2304_09049_amd import binding as dg
+lut = dg.dg_build_lut((-2, -1, 0, 1), (0, 1, 2, 3))
+wide = dg.dg_build_lut((-128, -1, 0, 1), (0, 1, 2, 127), dg.DG_LUT_I16)
+rng = random.Random(7)
+shapes = [(rng.choice((1, 8, 32)), s, s, 32 * rng.randint(1, 16), 8 * rng.randint(1, 64), k, k, (1, 1), (k // 2, k // 2))
+          for s in (7, 14, 28, 56) for k in (1, 3) for _ in range(20)]
+for _ in range(2):                                   # 160 shapes, so that the second time round finds some plans kept and most replaced
+    for s in shapes:
+        for t in (lut, wide):
+            d = dg.conv_desc(*s)
+            print(dg.dg_conv_kernel_name(t, d), dg.dg_conv_codes_kernel_name(t, d), dg.dg_conv_kernel_name(t, d, "onehot_mfma"))
+"""
+
+
+def _names(overrides):
+    env = {k: v for k, v in os.environ.items() if not k.startswith("DG_")}
+    env["DG_TEST_OVERRIDES"] = overrides             # "1": every plan is made anew
+    out = subprocess.run([sys.executable, "-c", SHAPES], env=env, capture_output=True, text=True, check=True,
+                         cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    return out.stdout.splitlines()
+
+
+def test_remembered_plans_are_the_plans():
+    fresh, kept = _names("1"), _names("0")
+    assert len(fresh) == 640 and fresh[:320] == fresh[320:]
+    assert kept == fresh
+
+
+def test_native_checks():
+    lut = dg.dg_build_lut((-2, -1, 0, 1), (0, 1, 2, 3))
+    host = torch.zeros(64, dtype=torch.uint8)
+    desc = dg.conv_desc(1, 2, 2, 16, 4, 1, 1)
+    for call in (lambda: dg.dg_pack_activations(host, 4, 16, out=host), lambda: dg.dg_pack_weights(host, 4, 16, out=host),
+                 lambda: dg.dg_pack_codes_bits(host, 4, 16, 3, out=host), lambda: dg.dg_dequantize(host, 4, 16, host, out=host),
+                 lambda: dg.dg_quantize_pack_activations(host, 4, 16, 1.0, 0.0, 0, out=host),
+                 lambda: dg.dg_gemm_lut(lut, host, host, 4, 4, 16, out=host),
+                 lambda: dg.dg_gemm_lut_codes(lut, host, host, 4, 4, 16, out=host),
+                 lambda: dg.dg_conv2d_lut(lut, host, host, desc, out=host),
+                 lambda: dg.dg_conv2d_lut_codes(lut, host, host, desc, out=host),
+                 lambda: dg.dg_conv2d_lut_codes_static(lut, host, host, desc, host),
+                 lambda: dg.dg_conv2d_lut_requant(lut, host, host, desc, host, 1.0, 0.0, 0, out=host)):
+        with pytest.raises(ValueError, match="must live in device memory"):
+            call()
+    with pytest.raises(TypeError, match="must be a tensor"):
+        dg.dg_pack_activations([1, 2], 4, 16, out=host)
+
+
+@pytest.mark.gpu
+def test_native_checks_on_device_tensors():
+    codes = torch.zeros(64, dtype=torch.uint8, device="cuda")
+    lut = dg.dg_build_lut((-2, -1, 0, 1), (0, 1, 2, 3))
+    with pytest.raises(ValueError, match="codes must have dtype torch.uint8, got torch.float16"):
+        dg.dg_pack_activations(codes.half(), 4, 16)
+    with pytest.raises(ValueError, match="codes must be contiguous"):
+        dg.dg_pack_activations(codes.reshape(8, 8).t(), 4, 16)
+    with pytest.raises(TypeError, match="ConvDesc"):
+        dg.dg_conv2d_lut(lut, codes, codes, b"1234", out=codes.to(torch.int32))
+    with pytest.raises(ValueError, match="out must have dtype torch.float32, got torch.int32"):
+        dg.dg_gemm_lut(lut, codes, codes, 4, 4, 16, out=torch.zeros(16, dtype=torch.int32, device="cuda"),
+                       scale=torch.ones(4, device="cuda"))
+    side = torch.cuda.Stream()                       # a stream of the caller's, and torch's current one
+    codes = torch.randint(0, 4, (64,), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    a = dg.dg_pack_activations(codes, 4, 16, stream=side)
+    with torch.cuda.stream(side):
+        b = dg.dg_pack_activations(codes, 4, 16)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b) and torch.equal(a, dg.dg_pack_activations(codes, 4, 16))
