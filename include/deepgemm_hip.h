@@ -209,6 +209,9 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *                    "1": wherever it applies (default: where it was measured shorter than two kernels)
  *   DG_ONEHOT_CODES_SPARSE "0": that kernel on the dense instruction only, "1": on the sparse one wherever the output's
  *                    channel axis is contiguous (the default)
+ *   DG_RAGGED        "0": AUTO never takes the sparse-instruction kernel for Cin % 32 != 0, "1": also on small problems
+ *   DG_RAGGED_PLAN   its tile, "11" (32 x 32), "21" (64 x 32) or "22" (64 x 64), optionally followed by "s<S>", the wavefronts sharing it
+ *   DG_RAGGED_CODES  "0": it never packs unpacked codes itself, "1": always
  *   DG_NIBBLES       "0": AUTO takes 3- and 4-bit tables whole even where they are the sum of two 2-bit lookups; "1": as
  *                    such sums also while DG_ONEHOT_PLAN is set (which then forces the 2-bit kernel's shape)
  *   DG_PERM_PLAN     index of the permute kernel's tile shape
@@ -279,7 +282,7 @@ dg_status dg_conv2d_lut(const dg_lut *lut, const void *Wp_dev, const void *Xp_de
  * where the output's channel axis is contiguous unless ONEHOT_MFMA is named -- up to about 2 * 10^9 table operations,
  * more where there is much to pack or Cin % 128 != 0); the layers of the stationary-weight
  * kernel (K = 64, 128, 256 without a filter window; AUTO or ONEHOT_SMFMAC); and the few-columns kernel (AUTO or
- * SMALLN).  Every other layer is packed into
+ * SMALLN); and layers with Cin % 32 != 0, Cin >= 16 and little enough to pack over (AUTO).  Every other layer is packed into
  * Xp_work_dev (device, work_bytes >= dg_packed_bytes_bits(B*H*W, Cin, bits), else DG_ERR_BUFFER; DG_ERR_NULL if it
  * is needed and NULL) by the packing kernel and then run as dg_conv2d_lut would run it, on the same stream (of a
  * 1x1 layer with a stride and no padding only the pixels it reads are packed, [B][OH][OW][Cin/4] at the start of the

@@ -296,7 +296,7 @@ int64_t dg_conv_out_dim(int64_t in, int64_t k, int64_t stride, int64_t pad)
 
 namespace {
 
-enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Unsupported };
+enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Ragged, Unsupported };
 
 Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
 {
@@ -340,6 +340,7 @@ Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
         if (dg_sparse_ws_preferred(lut, p)) return Pick::SparseWs;
         if (dg_onehot_supports(lut, p)) return dg_sparse_preferred(lut, p) ? Pick::Sparse : Pick::OneHot;
         if (p.N <= 32 && p.K >= 1024 && dg_smalln_supports(lut, p)) return Pick::SmallN;
+        if (dg_ragged_preferred(lut, p, false)) return Pick::Ragged;
         if (dg_perm_supports(lut, p)) return Pick::Perm;
         return Pick::Lds;
     }
@@ -362,6 +363,7 @@ dg_status run(const dg_lut *lut, const DgProblem &p, dg_kernel variant, hipStrea
     case Pick::Sparse2p: return dg_launch_sparse2p(lut, p, stream);
     case Pick::SparseWs: return dg_launch_sparse_ws(lut, p, stream);
     case Pick::FewN: return dg_launch_fewn(lut, p, stream);
+    case Pick::Ragged: return dg_launch_ragged(lut, p, false, stream);
     case Pick::Unsupported: break;
     }
     return dg_fail(DG_ERR_UNSUPPORTED,
@@ -385,6 +387,7 @@ const char *pick_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Pick::Sparse2p: return "onehot_smfmac_2p_32x128";
     case Pick::SparseWs: return "onehot_smfmac_ws_32xK";
     case Pick::FewN: return "onehot_smfmac_fewn_16";
+    case Pick::Ragged: return dg_ragged_config_name(lut, p, false);
     case Pick::Unsupported: break;
     }
     return "unsupported";
@@ -507,7 +510,7 @@ namespace {
 // The one-call entry points fuse the packing into the kernel where the library's own choice for the problem (or the
 // variant the caller names) is the one-hot split-K kernel or the few-columns kernel, i.e. on problems so small that a
 // second launch costs a good part of the whole.
-enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs };
+enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs, Ragged };
 
 Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel variant)
 {
@@ -536,6 +539,8 @@ Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel varian
     if ((variant == DG_KERNEL_AUTO || variant == DG_KERNEL_ONEHOT_SMFMAC) && dg_sparse_ws_codes_supports(lut, p_codes) &&
         pick_kernel(lut, p_codes, variant) == Pick::SparseWs)
         return Fuse::SparseWs;
+    if (variant == DG_KERNEL_AUTO && dg_ragged_preferred(lut, p_codes, true) && pick_kernel(lut, p_codes, variant) == Pick::Ragged)
+        return Fuse::Ragged;
     // (one column: on packed activations the few-columns sparse-instruction kernel is the faster by 6 %, which is less
     // than the packing launch it would need here)
     if (variant == DG_KERNEL_AUTO && p_codes.N == 1 && p_codes.K >= 1024 && dg_smalln_supports(lut, p_codes) &&
@@ -571,6 +576,7 @@ dg_status run_codes(const char *name, const dg_lut *lut, DgProblem &p, const uin
     case Fuse::OneHotSparse: return dg_launch_onehot_codes(lut, p, (hipStream_t)hip_stream, true);
     case Fuse::SmallN: return dg_launch_smalln_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::SparseWs: return dg_launch_sparse_ws_codes(lut, p, (hipStream_t)hip_stream);
+    case Fuse::Ragged: return dg_launch_ragged(lut, p, true, (hipStream_t)hip_stream);
     case Fuse::None: break;
     }
     if (packs_strided_pixels(lut, p)) {
@@ -598,6 +604,7 @@ const char *codes_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Fuse::OneHotSparse: return dg_onehot_codes_config_name(lut, p, true);
     case Fuse::SmallN: return "codes_smalln";
     case Fuse::SparseWs: return "codes_onehot_smfmac_ws_32xK";
+    case Fuse::Ragged: return dg_ragged_config_name(lut, p, true);
     case Fuse::None: break;
     }
     if (packs_strided_pixels(lut, p)) return pick_name(lut, without_stride(p), variant);

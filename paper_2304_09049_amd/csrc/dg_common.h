@@ -117,6 +117,9 @@ bool dg_sparse_supports(const dg_lut *lut, const DgProblem &p);
 bool dg_sparse_preferred(const dg_lut *lut, const DgProblem &p);     // AUTO's choice between the two one-hot kernels
 dg_status dg_launch_sparse(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p);
+bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes);      // taps of no whole 32-position groups; `codes`: p.Xp one per byte
+const char *dg_ragged_config_name(const dg_lut *lut, const DgProblem &p, bool codes);
+dg_status dg_launch_ragged(const dg_lut *lut, const DgProblem &p, bool codes, hipStream_t stream);
 bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p);      // 3- and 4-bit codes as two 2-bit ones each
 dg_status dg_launch_nibble(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 const char *dg_nibble_config_name(const dg_lut *lut, const DgProblem &p);

@@ -837,6 +837,15 @@ struct Plan {
     bool staged;     // sparse instruction: the kernel that stages its operands through LDS (dg_sparse_staged_kernel.h)
 };
 
+// What runs a layer whose taps are no whole 32-position groups (dg_sparse_ragged_kernel.h)
+struct RaggedPlan {
+    int wm, wn;                          // tile: 32 wm channels x 32 wn pixels
+    int S;                               // wavefronts sharing a tile
+    int ch;                              // words per window
+    int pair_taps, seg, base1, lead1;    // how the lane halves divide the taps (see the kernel)
+    int windows, chunks, cpw;            // windows per segment, in all, per wavefront
+};
+
 // dynamic LDS of the large-layer kernel: the shared tiles' sums
 template <int WM, int WN, bool TWO, int SKW>
 constexpr size_t main_lds_bytes()
@@ -946,6 +955,7 @@ void unit_sparse_ws(const DgProblem &, const Pools &, int, bool raw, hipStream_t
 void unit_sparse_ws_nib(const DgProblem &, const Pools &, int, hipStream_t);
 void unit_sparse_staged(const DgProblem &, const Pools &, int32_t bias, const Plan &, int64_t, hipStream_t);
 void unit_sparse_staged_nib(const DgProblem &, const Pools &, int32_t bias, const Plan &, int64_t, hipStream_t);
+void unit_sparse_ragged(const DgProblem &, const Pools &, const RaggedPlan &, bool scale_rows, bool n_first, bool raw, hipStream_t);
 // the split-K kernel on activations still one code per byte (one- and two-plane tables, either output layout)
 void unit_split_codes(const DgProblem &, const Pools &, const Plan &, bool two, bool tr, int64_t, hipStream_t);
 // the tiled kernel on unpacked codes: 64 x 32 and 64 x 64 tiles (q.wn = 1, 2), 2-word chunks, any sharing of K;

@@ -530,6 +530,116 @@ bool dg_sparse_ws_codes_supports(const dg_lut *lut, const DgProblem &p)
 
 dg_status dg_launch_sparse_ws_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream) { return launch_ws(lut, p, true, stream); }
 
+// ---- taps that are no whole 32-position groups (dg_sparse_ragged_kernel.h)
+
+namespace {
+
+// A GEMM whose n axis is the contiguous one is run transposed, with or without a scale.
+bool ragged_transposes(const DgProblem &p)
+{
+    return p.stride_cn == 1 && p.stride_cm != 1 && p.H == 1 && p.W == 1 && p.OH == 1 && p.OW == 1 && p.KH == 1 && p.KW == 1 &&
+           p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0;
+}
+
+DgProblem ragged_problem(const DgProblem &p)
+{
+    if (!ragged_transposes(p)) return p;
+    DgProblem t = p;
+    t.M = p.N, t.N = p.M;
+    t.Wp = p.Xp, t.Xp = p.Wp;
+    t.stride_cm = p.stride_cn, t.stride_cn = p.stride_cm;
+    return t;
+}
+
+// How the two lane halves divide a tap of L bytes (see the kernel), and the windows: the least number that hold a
+// segment four words at a time, evened out.
+//
+// Tile and sharing, measured on 20 layers (16 ... 528 channels, 1x1 to 5x5, 0.0005 to 3.2 GOP; graph replays): on packed
+// codes the smallest tile, shared among as many wavefronts as make 4096 in all while the tiles alone do not fill the chip
+// (8x29x27x48 -> 120 5x5: 8.4 us with 5 wavefronts a tile, 9.0 with 3; 14x14x208 -> 48 5x5 at batch 16: 9.2 with 12, 12.4 with
+// 4), unshared above one tile per SIMD (28x28x112 -> 224 3x3 at batch 16: 17.1 us, 26.7 on shared 64 x 64 tiles).  On unpacked
+// codes a taller tile packs less often: 64 x 64 where there is one for every second SIMD (that layer 18.9 against 20.3 us),
+// else 64 x 32 from 384 of them (the first layer 9.4 against 10.0), else the smallest.
+dgoh::RaggedPlan ragged_plan(const DgProblem &t, bool codes)
+{
+    dgoh::RaggedPlan q;
+    const int L = t.Cin / 4, taps = t.KH * t.KW, half = 4 * ((L + 7) / 8);
+    const int64_t words_pairs = (int64_t)((taps + 1) / 2) * ((L + 3) / 4), words_halves = (int64_t)taps * (half / 4);
+    q.pair_taps = words_pairs <= words_halves;
+    q.seg = q.pair_taps ? L : half;
+    q.base1 = q.pair_taps ? 0 : L - half, q.lead1 = q.pair_taps ? 0 : 2 * half - L;
+    const int words = (q.seg + 3) / 4, least = (words + 3) / 4, even = (words + least - 1) / least;
+    q.ch = even < q.seg / 4 ? even : q.seg / 4;
+    q.windows = (q.seg + 4 * q.ch - 1) / (4 * q.ch);
+    q.chunks = (q.pair_taps ? (taps + 1) / 2 : taps) * q.windows;
+    const int64_t simds = dg_simd_count();
+    q.wm = q.wn = 1;
+    int64_t waves = tile_count(t, 1, 1) > simds ? 1 : 4 * simds;
+    if (codes && tile_count(t, 2, 2) >= simds / 2) q.wm = q.wn = 2, waves = 1;
+    else if (codes && tile_count(t, 2, 1) >= simds * 3 / 8) q.wm = 2, waves = 2 * simds;
+    const char *force = dg_override("DG_RAGGED_PLAN");
+    if (force) q.wm = force[0] == '2' ? 2 : 1, q.wn = force[0] == '2' && force[1] == '2' ? 2 : 1;
+    const int64_t tiles = tile_count(t, q.wm, q.wn);
+    int S = (int)((waves + tiles - 1) / tiles);
+    if (force && strchr(force, 's')) S = atoi(strchr(force, 's') + 1);
+    const int most = q.wm == 1 ? 16 : 8;                    // (the kernel's launch bounds)
+    S = S < 1 ? 1 : (S > most ? most : S);
+    if (S > q.chunks) S = q.chunks;
+    q.cpw = (q.chunks + S - 1) / S;
+    q.S = (q.chunks + q.cpw - 1) / q.cpw;
+    return q;
+}
+
+// Packing while loading is done once per filter tap and tile row: it saves the packing kernel's launch, about 2 us, and
+// costs about 1 us per 8 million codes so packed (8x29x27x48 -> 120 5x5, 15.6 million: 10.3 against 10.6 us as two kernels;
+// 57x57x36 -> 128 3x3 at batch 4, 16.6 million: 11.6 against 10.8; 14x14x208 -> 48 5x5 at batch 16, 41 million: 11.9 against 11.4).
+bool ragged_codes_pay(const DgProblem &t, const dgoh::RaggedPlan &q)
+{
+    return 32.0 * q.chunks * q.ch * t.N * ((t.M + 32 * q.wm - 1) / (32 * q.wm)) <= 1.6e7;
+}
+
+// On unpacked codes a GEMM is not transposed (they are the kernel's pixels): its sums are stored n first instead.
+DgProblem ragged_problem(const DgProblem &p, bool codes) { return codes ? p : ragged_problem(p); }
+
+}   // namespace
+
+// AUTO, for tables of int8 entries: ahead of the permute kernel (Cin % 16 == 0) and of the plain LDS kernel (other Cin) on
+// every one of those 20 layers, by 1.06 (the smallest) to 15 times.  Below a million products those are as short as a launch.
+// Not for Cin < 16, a tap of less than one word.  DG_RAGGED: 0 never, 1 whatever the size; DG_RAGGED_CODES: 0 / 1.
+bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes)
+{
+    if (lut->dtype == DG_LUT_F32 || lut->bits != 2 || !fits_int8(lut)) return false;
+    if (p.Cin % 32 == 0 || p.Cin < 16 || p.Qp != nullptr) return false;
+    if (const char *e = dg_override("DG_RAGGED")) {
+        if (atoi(e) == 0) return false;
+    } else if ((double)p.M * p.N * p.K < 1e6) {
+        return false;
+    }
+    const DgProblem t = ragged_problem(p, codes);
+    if (!offsets_fit(t, codes ? 1 : 4) || tile_count(t, 1, 1) > INT32_MAX) return false;
+    if (!codes) return true;
+    if (const char *e = dg_override("DG_RAGGED_CODES")) return atoi(e) != 0;
+    return ragged_codes_pay(t, ragged_plan(t, true));
+}
+
+const char *dg_ragged_config_name(const dg_lut *, const DgProblem &p, bool codes)
+{
+    static const char *const names[2][3] = {{"onehot_smfmac_ragged_32x32", "onehot_smfmac_ragged_64x32", "onehot_smfmac_ragged_64x64"},
+                                            {"codes_onehot_smfmac_ragged_32x32", "codes_onehot_smfmac_ragged_64x32",
+                                             "codes_onehot_smfmac_ragged_64x64"}};
+    const dgoh::RaggedPlan q = ragged_plan(ragged_problem(p, codes), codes);
+    return names[codes][q.wm + q.wn - 2];
+}
+
+dg_status dg_launch_ragged(const dg_lut *lut, const DgProblem &p, bool codes, hipStream_t stream)
+{
+    const bool n_first = ragged_transposes(p), transposed = n_first && !codes;
+    const DgProblem t = ragged_problem(p, codes);
+    dgoh::unit_sparse_ragged(t, sparse_pools(lut, transposed), ragged_plan(t, codes), transposed && t.scale != nullptr, codes && n_first,
+                             codes, stream);
+    return dg_check_launch("smfmac_ragged_kernel");
+}
+
 // ---- 3- and 4-bit codes as two 2-bit ones each on the sparse kernels above (dg_onehot_kernel.h, BITS = 24): tables that are
 // ---- the sum of two lookups, T[w][4 i + j] = low[w][j] + high[w][i], as every uniform quantiser's products are.
 // Bound by the matrix pipe (large layers) or latency (small ones) as the 2-bit layers of twice the positions are, whose plans
