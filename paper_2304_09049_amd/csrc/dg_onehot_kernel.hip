@@ -723,6 +723,11 @@ bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p)
     const char *e = dg_override("DG_NIBBLES");
     if (e ? atoi(e) == 0 : dg_override("DG_ONEHOT_PLAN") != nullptr) return false;
     if (p.Cin % 16 != 0 || p.K >= (1 << 29)) return false;
+    // Where the 64 x 128 tiles of dg_sparse4_kernel.h fill the chip and the staged and stationary kernels do not take the layer
+    // (taps of no whole runs) the table stays whole.
+    const DgProblem n = nibble_problem(p);
+    if (!e && dg_sparse4_preferred(lut, p) && !dg_sparse_ws_preferred(two_bit_view(), n) && !sparse_plan(two_bit_view(), sparse_problem(n)).staged)
+        return false;
     NibbleTable t;
     // (every sum of the split table is a sum of T, whose range the API has checked; partial sums wrap and wrap back)
     return dg_sparse_supports(two_bit_view(), nibble_problem(p)) && nibble_table(lut, sparse_transposes(p), &t);
