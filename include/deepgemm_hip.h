@@ -209,6 +209,8 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *                    "1": wherever it applies (default: where it was measured shorter than two kernels)
  *   DG_ONEHOT_CODES_SPARSE "0": that kernel on the dense instruction only, "1": on the sparse one wherever the output's
  *                    channel axis is contiguous (the default)
+ *   DG_STAGED_2P     "0": AUTO never takes the staged kernel for entries beyond int8
+ *   DG_STAGED_2P_PLAN  its tile's width in blocks, 1, 2 or 4, optionally followed by "k2" or "k4" (whatever the size)
  *   DG_RAGGED        "0": AUTO never takes the sparse-instruction kernel for Cin % 32 != 0, "1": also on small problems
  *   DG_RAGGED_PLAN   its tile, "11" (32 x 32), "21" (64 x 32) or "22" (64 x 64), optionally followed by "s<S>", the wavefronts sharing it
  *   DG_RAGGED_CODES  "0": it never packs unpacked codes itself, "1": always

@@ -296,7 +296,7 @@ int64_t dg_conv_out_dim(int64_t in, int64_t k, int64_t stride, int64_t pad)
 
 namespace {
 
-enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Ragged, Unsupported };
+enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Ragged, Staged2p, Unsupported };
 
 Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
 {
@@ -335,6 +335,7 @@ Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
         // int8 tables: selecting entries with one-hot operands on the matrix cores outruns the permute loop at every
         // size measured (1.5x on a 0.2 GOP layer, 5x - 10x from 3 GOP upwards)
         // (large layers: the same selection on the sparse instruction, about half the matrix work)
+        if (dg_staged2p_preferred(lut, p)) return Pick::Staged2p;
         if (dg_sparse2p_preferred(lut, p)) return Pick::Sparse2p;
         // short reductions with many output blocks: the dense operand of the weights is built once per wavefront
         if (dg_sparse_ws_preferred(lut, p)) return Pick::SparseWs;
@@ -360,6 +361,7 @@ dg_status run(const dg_lut *lut, const DgProblem &p, dg_kernel variant, hipStrea
     case Pick::Sparse: return dg_launch_sparse(lut, p, stream);
     case Pick::Nibble: return dg_launch_nibble(lut, p, stream);
     case Pick::Sparse4: return dg_launch_sparse4(lut, p, stream);
+    case Pick::Staged2p: return dg_launch_staged2p(lut, p, stream);
     case Pick::Sparse2p: return dg_launch_sparse2p(lut, p, stream);
     case Pick::SparseWs: return dg_launch_sparse_ws(lut, p, stream);
     case Pick::FewN: return dg_launch_fewn(lut, p, stream);
@@ -384,6 +386,7 @@ const char *pick_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Pick::Sparse: return dg_sparse_config_name(lut, p);
     case Pick::Nibble: return dg_nibble_config_name(lut, p);
     case Pick::Sparse4: return "onehot_smfmac4_64x128";
+    case Pick::Staged2p: return dg_staged2p_config_name(lut, p);
     case Pick::Sparse2p: return "onehot_smfmac_2p_32x128";
     case Pick::SparseWs: return "onehot_smfmac_ws_32xK";
     case Pick::FewN: return "onehot_smfmac_fewn_16";
@@ -512,6 +515,16 @@ namespace {
 // second launch costs a good part of the whole.
 enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs, Ragged };
 
+// A 1x1 layer with a stride and no padding reads one input pixel in sh * sw: where the packing is not fused only those
+// are packed (2-bit codes in whole 16-code groups), and the layer then runs on them without a stride -- 56x56x256 -> 512
+// with stride 2 at batch 32 packs 6.4 MB of codes instead of 25.7 MB.
+bool packs_strided_pixels(const dg_lut *lut, const DgProblem &p_codes)
+{
+    return lut->bits == 2 && p_codes.KH == 1 && p_codes.KW == 1 && p_codes.ph == 0 && p_codes.pw == 0 &&
+           (p_codes.sh > 1 || p_codes.sw > 1) && p_codes.Cin % 16 == 0 && (uintptr_t)p_codes.Xp % 16 == 0 &&
+           (int64_t)p_codes.N * (p_codes.Cin / 16) < ((int64_t)1 << 31);
+}
+
 Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel variant)
 {
     // (the unpacked buffer's 16-byte alignment satisfies every kernel's test of the packed one)
@@ -539,7 +552,9 @@ Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel varian
     if ((variant == DG_KERNEL_AUTO || variant == DG_KERNEL_ONEHOT_SMFMAC) && dg_sparse_ws_codes_supports(lut, p_codes) &&
         pick_kernel(lut, p_codes, variant) == Pick::SparseWs)
         return Fuse::SparseWs;
-    if (variant == DG_KERNEL_AUTO && dg_ragged_preferred(lut, p_codes, true) && pick_kernel(lut, p_codes, variant) == Pick::Ragged)
+    // channels that are no whole groups of 32 (a 1x1 layer with a stride keeps the kernel that packs only the pixels it reads)
+    if (variant == DG_KERNEL_AUTO && dg_ragged_preferred(lut, p_codes, true) && !packs_strided_pixels(lut, p_codes) &&
+        pick_kernel(lut, p_codes, variant) == Pick::Ragged)
         return Fuse::Ragged;
     // (one column: on packed activations the few-columns sparse-instruction kernel is the faster by 6 %, which is less
     // than the packing launch it would need here)
@@ -547,16 +562,6 @@ Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel varian
         pick_kernel(lut, p_codes, variant) == Pick::FewN)
         return Fuse::SmallN;
     return Fuse::None;
-}
-
-// A 1x1 layer with a stride and no padding reads one input pixel in sh * sw: where the packing is not fused only those
-// are packed (2-bit codes in whole 16-code groups), and the layer then runs on them without a stride -- 56x56x256 -> 512
-// with stride 2 at batch 32 packs 6.4 MB of codes instead of 25.7 MB.
-bool packs_strided_pixels(const dg_lut *lut, const DgProblem &p_codes)
-{
-    return lut->bits == 2 && p_codes.KH == 1 && p_codes.KW == 1 && p_codes.ph == 0 && p_codes.pw == 0 &&
-           (p_codes.sh > 1 || p_codes.sw > 1) && p_codes.Cin % 16 == 0 && (uintptr_t)p_codes.Xp % 16 == 0 &&
-           (int64_t)p_codes.N * (p_codes.Cin / 16) < ((int64_t)1 << 31);
 }
 
 DgProblem without_stride(const DgProblem &p)
@@ -743,6 +748,7 @@ dg_status dg_conv2d_lut_requant(const dg_lut *lut, const void *Wp_dev, const voi
         !dg_onehot_supports(lut, p))
         return dg_fail(DG_ERR_UNSUPPORTED, "%s: needs the one-hot matrix-core kernel (variant %d, Cin=%d, table range %d..%d)",
                        name, (int)variant, p.Cin, lut->min_entry, lut->max_entry);
+    if (variant == DG_KERNEL_AUTO && dg_staged2p_preferred(lut, p)) return dg_launch_staged2p(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_AUTO && dg_sparse2p_preferred(lut, p)) return dg_launch_sparse2p(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_AUTO && dg_sparse4_preferred(lut, p)) return dg_launch_sparse4(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_AUTO && dg_sparse_preferred(lut, p)) return dg_launch_sparse(lut, p, (hipStream_t)hip_stream);

@@ -129,6 +129,9 @@ dg_status dg_launch_sparse4(const dg_lut *lut, const DgProblem &p, hipStream_t s
 bool dg_sparse2p_supports(const dg_lut *lut, const DgProblem &p);     // two-plane 2-bit tables on the sparse instruction
 bool dg_sparse2p_preferred(const dg_lut *lut, const DgProblem &p);
 dg_status dg_launch_sparse2p(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+bool dg_staged2p_preferred(const dg_lut *lut, const DgProblem &p);    // the same with staged operands, in any of their tiles
+dg_status dg_launch_staged2p(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+const char *dg_staged2p_config_name(const dg_lut *lut, const DgProblem &p);
 bool dg_sparse_ws_supports(const dg_lut *lut, const DgProblem &p);    // short K: weight operands stationary in registers
 bool dg_sparse_ws_preferred(const dg_lut *lut, const DgProblem &p);
 dg_status dg_launch_sparse_ws(const dg_lut *lut, const DgProblem &p, hipStream_t stream);

@@ -5,6 +5,6 @@
 namespace dgoh {
 void unit_sparse_staged_nib(const DgProblem &p, const Pools &pools, int32_t bias, const Plan &q, int64_t wave_tiles, hipStream_t stream)
 {
-    launch_sparse_staged<true>(p, pools, bias, q, wave_tiles, stream);
+    launch_sparse_staged<true, false>(p, pools, bias, q, wave_tiles, stream);
 }
 }   // namespace dgoh

@@ -269,6 +269,15 @@ __device__ __forceinline__ void sparse_fill_entry(uint2 *table, const Pools &pl,
     table[i] = make_uint2(r0, r1);
 }
 
+// Two-plane tables: the row pairs of the high plane, pool words 4 ... 7, behind the low plane's 16 entries.
+__device__ __forceinline__ void sparse_fill_high_entry(uint2 *table, const Pools &pl, int i)
+{
+    const int c0 = i & 3, c1 = i >> 2;
+    const uint32_t r0 = c0 == 0 ? pl.w[4] : (c0 == 1 ? pl.w[5] : (c0 == 2 ? pl.w[6] : pl.w[7]));
+    const uint32_t r1 = c1 == 0 ? pl.w[4] : (c1 == 1 ? pl.w[5] : (c1 == 2 ? pl.w[6] : pl.w[7]));
+    table[16 + i] = make_uint2(r0, r1);
+}
+
 template <bool NIB = false>
 __device__ __forceinline__ void sparse_fill_rows(uint2 *rows, const Pools &pl, int lane)
 {
@@ -954,6 +963,7 @@ void unit_sparse2p(const DgProblem &, const uint32_t (&)[2][4], int, hipStream_t
 void unit_sparse_ws(const DgProblem &, const Pools &, int, bool raw, hipStream_t);
 void unit_sparse_ws_nib(const DgProblem &, const Pools &, int, hipStream_t);
 void unit_sparse_staged(const DgProblem &, const Pools &, int32_t bias, const Plan &, int64_t, hipStream_t);
+void unit_sparse_staged_two(const DgProblem &, const Pools &, const Plan &, int64_t, hipStream_t);
 void unit_sparse_staged_nib(const DgProblem &, const Pools &, int32_t bias, const Plan &, int64_t, hipStream_t);
 void unit_sparse_ragged(const DgProblem &, const Pools &, const RaggedPlan &, bool scale_rows, bool n_first, bool raw, hipStream_t);
 // the split-K kernel on activations still one code per byte (one- and two-plane tables, either output layout)

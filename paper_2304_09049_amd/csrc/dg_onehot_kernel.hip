@@ -847,11 +847,11 @@ bool dg_sparse2p_preferred(const dg_lut *lut, const DgProblem &p)
            dg_override("DG_ONEHOT_PLAN") == nullptr;
 }
 
-dg_status dg_launch_sparse2p(const dg_lut *lut, const DgProblem &p0, hipStream_t stream)
+namespace {
+
+// rows[plane][w] = plane(T[w][0..3]) (transposed: codes swapped)
+void two_plane_rows(const dg_lut *lut, bool transposed, uint32_t (&rows)[2][4])
 {
-    const bool transposed = sparse_transposes(p0);
-    const DgProblem p = sparse_problem(p0);
-    uint32_t rows[2][4];                                   // rows[plane][w] = plane(T[w][0..3]) (transposed: codes swapped)
     for (int w = 0; w < 4; ++w) {
         rows[0][w] = rows[1][w] = 0;
         for (int v = 0; v < 4; ++v) {
@@ -861,8 +861,98 @@ dg_status dg_launch_sparse2p(const dg_lut *lut, const DgProblem &p0, hipStream_t
             rows[1][w] |= (uint32_t)(uint8_t)(int8_t)hi << (8 * v);
         }
     }
+}
+
+}   // namespace
+
+dg_status dg_launch_sparse2p(const dg_lut *lut, const DgProblem &p0, hipStream_t stream)
+{
+    const DgProblem p = sparse_problem(p0);
+    uint32_t rows[2][4];
+    two_plane_rows(lut, sparse_transposes(p0), rows);
     dgoh::unit_sparse2p(p, rows, sparse2p_ch(p), stream);
     return dg_check_launch("sparse2p_kernel");
+}
+
+// ---- the same planes with staged operands (dg_sparse_staged_kernel.h, TWO): any tile of its, where the taps are whole runs
+
+namespace {
+
+// Its tiles (32 channels in two planes x 32, 64 or 128 pixels) and which layers are its own.  What bounds it: every weight
+// word costs 16 table reads of LDS for both planes' dense operands, which only the 128-pixel tile spreads over enough matrix
+// instructions, so that tile comes first, its wavefronts sharing K where the tiles alone leave SIMDs idle.  Measured on 36
+// layers against the kernels that ran them before (dense instruction, sparse2p_kernel), packed codes, graph replays, us:
+//   32 x 128 from one per SIMD        56x56x256 -> 256 3x3 at batch 16 (3136 tiles) 114 -> 96.7
+//   32 x 128 shared by 2 / by 4       28x28x256 -> 256 3x3 at batch 16 (784) 42.8 -> 27.6; at batch 8 (392) 27.0 -> 17.7
+//   below 384 of those, 32 x 64 by 4  14x14x256 -> 256 3x3 at batch 8 (200) 12.1 -> 9.3; 14x14x512 -> 512 3x3 at batch 5 (256) 19.7 ->
+//                                     13.1; 7x7x2048 -> 512 at batch 16 (208) 10.8 -> 8.5 -- from 6e8 products on: less does not
+//                                     pay for the packing kernel that the split-K kernel's one-call form spares; below 192
+//                                     tiles split K is ahead (7x7x512 -> 512 3x3 at batch 8: 10.2 against 11.1)
+//   K = 512 ... 1023                  28x28x512 -> 256 at batch 16 (784 tiles of 32 x 128) 12.6 -> 10.7 unshared; with 392 8.3 against 8.5
+//   shorter K, up to 64 channels      56x56x256 -> 64 at batch 16 8.9 -> 7.7, 56x56x128 -> 64 6.9 -> 6.6; with more channels such a
+//                                     layer is its output's stores (28x28x128 -> 512 at batch 32: 16.4 against 17.6)
+//   half runs: 32 x 64, 7/8 per SIMD  56x56x64 -> 64 3x3 at batch 16 (1568) 15.7 -> 13.7, 28x28x192 -> 160 3x3 (980) 23.0 -> 22.0;
+//                                     with 784 tiles 10.2 against 10.9, with 490 22 against 32
+Plan staged2p_plan(const DgProblem &t)
+{
+    const int64_t simds = dg_simd_count(), t2 = tile_count(t, 1, 2), t4 = tile_count(t, 1, 4);
+    Plan q;
+    q.two = true, q.decode = false, q.split = false, q.wm = 2, q.wn = 4, q.skw = 1, q.ch = 2, q.S = 1, q.chunks = q.cpw = t.K / 64;
+    q.staged = true;
+    if (t.Cin % 128 != 0) {
+        q.wn = 2;                                            // (the tile built for taps of half runs)
+        q.staged = t.KH * t.KW > 1 && t2 >= simds * 7 / 8 && t4 < simds;
+    } else if (t.K < 512) {
+        q.wn = 2, q.staged = t2 >= simds && t.M <= 64;
+    } else if (t4 >= simds) {
+        q.skw = 1;
+    } else if (t.K < 1024) {
+        q.wn = 2, q.staged = t4 >= simds * 5 / 8;
+    } else if (t4 >= simds * 3 / 8) {
+        q.skw = t4 >= simds * 5 / 8 ? 2 : 4;
+    } else {
+        q.wn = 2, q.skw = 4, q.staged = t2 >= simds * 3 / 16 && (double)t.M * t.N * t.K >= 6e8;
+    }
+    if (const char *force = dg_override("DG_STAGED_2P_PLAN")) {
+        q.staged = true;
+        if (t.Cin % 128 == 0) q.wn = atoi(force), q.skw = strstr(force, "k4") ? 4 : (strstr(force, "k2") ? 2 : 1);
+    }
+    if (t.Cin % 64 != 0 || (uintptr_t)t.Wp % 16 != 0 || (uintptr_t)t.Xp % 16 != 0) q.staged = false;
+    return q;
+}
+
+}   // namespace
+
+bool dg_staged2p_preferred(const dg_lut *lut, const DgProblem &p)
+{
+    if (!dg_sparse2p_supports(lut, p) || dg_override("DG_ONEHOT_PLAN") != nullptr) return false;
+    if (const char *e = dg_override("DG_STAGED_2P")) if (atoi(e) == 0) return false;
+    const DgProblem t = sparse_problem(p);
+    if (t.M >= (1 << 30) || !offsets_fit(t, 4)) return false;
+    const Plan q = staged2p_plan(t);
+    return q.staged && tile_count(t, 1, q.wn) <= INT32_MAX;
+}
+
+const char *dg_staged2p_config_name(const dg_lut *, const DgProblem &p)
+{
+    static const char *const names[3][3] = {
+        {"onehot_mfma_2p_staged_32x32", "onehot_mfma_2p_staged_32x64", "onehot_smfmac_2p_32x128"},
+        {"onehot_mfma_2p_staged_32x32_k2", "onehot_mfma_2p_staged_32x64_k2", "onehot_mfma_2p_staged_32x128_k2"},
+        {"onehot_mfma_2p_staged_32x32_k4", "onehot_mfma_2p_staged_32x64_k4", "onehot_mfma_2p_staged_32x128_k4"}};
+    const Plan q = staged2p_plan(sparse_problem(p));
+    return names[q.skw == 4 ? 2 : (q.skw == 2 ? 1 : 0)][q.wn == 4 ? 2 : (q.wn == 2 ? 1 : 0)];
+}
+
+dg_status dg_launch_staged2p(const dg_lut *lut, const DgProblem &p0, hipStream_t stream)
+{
+    const DgProblem p = sparse_problem(p0);
+    const Plan q = staged2p_plan(p);
+    uint32_t rows[2][4];
+    two_plane_rows(lut, sparse_transposes(p0), rows);
+    dgoh::Pools pools;
+    for (int i = 0; i < 64; ++i) pools.w[i] = i < 8 ? rows[i / 4][i % 4] : 0;
+    dgoh::unit_sparse_staged_two(p, pools, q, tile_count(p, 1, q.wn), stream);
+    return dg_check_launch("smfmac_staged_kernel");
 }
 
 bool dg_decode_supports(const dg_lut *lut, const DgProblem &p)

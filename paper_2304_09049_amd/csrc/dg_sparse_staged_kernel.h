@@ -27,11 +27,19 @@ namespace dgoh {
 // The dense operands of all WM weight blocks for word `t` of `w` (as sparse_dense_rows_shared, but with the opaque
 // statement that keeps the indices pre-multiplied NOT volatile, so that the scheduler may move these instructions
 // between matrix instructions).
-template <bool NIB, int WM, class W>
+template <bool NIB, bool TWO, int WM, class W>
 __device__ __forceinline__ void dense_rows_movable(const uint2 *table, const W &w, int t, uint32_t pick, v8i (&out)[WM][2])
 {
+    if constexpr (TWO) {                                    // one row block, both planes
+        uint32_t e, o;
+        sparse_row_offsets<false>(__builtin_amdgcn_perm(t ? w.ca1[0].y : w.ca1[0].x, t ? w.ca[0].y : w.ca[0].x, pick), e, o);
+        asm("" : "+v"(e), "+v"(o));
 #pragma unroll
-    for (int u = 0; u < WM; ++u) {
+        for (int u = 0; u < 2; ++u) sparse_read_rows<false>(table + 16 * u, e, o, out[u][0], out[u][1]);
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < (TWO ? 0 : WM); ++u) {
         const uint32_t w0 = t ? w.ca[u].y : w.ca[u].x, w1 = t ? w.ca1[u].y : w.ca1[u].x;
         uint32_t e, o;
         sparse_row_offsets<NIB>(__builtin_amdgcn_perm(w1, w0, pick), e, o);
@@ -50,19 +58,25 @@ __device__ __forceinline__ void dense_rows_movable(const uint2 *table, const W &
 // second chunk is fetched from the first's place and multiplied by kept bytes of zero.
 //
 // NIB: 3- and 4-bit codes as two 2-bit ones each (dg_onehot_kernel.h, BITS = 24); K and Cin count the 2-bit codes.
-template <int WM, int WN, int SKW, bool TURNS, bool HALF, bool NIB>
+//
+// TWO: entries beyond int8, T = 256 * hi + lo (dg_onehot_kernel.h).  The planes take the places of two weight row blocks: a
+// tile is ONE block of 32 rows, whose words are staged once and whose table indices are worked out once for both planes'
+// dense operands (the second plane's rows lie 128 bytes behind the first's); pool words 4 ... 7 are the high plane's rows.
+template <int WM, int WN, int SKW, bool TURNS, bool HALF, bool NIB, bool TWO>
 __global__ void __launch_bounds__(256, 2)
 smfmac_staged_kernel(Args a)
 {
     static_assert(!HALF || SKW == 1, "taps of half runs: unshared tiles only");
-    constexpr int ROWS = (WM + WN) * 32;                    // staged rows of a wavefront: its weight rows, then its pixels
+    static_assert(!TWO || (WM == 2 && !NIB), "two planes stand in for two weight row blocks");
+    constexpr int RB = TWO ? 1 : WM;                       // weight row blocks of the tile
+    constexpr int ROWS = (RB + WN) * 32;                    // staged rows of a wavefront: its weight rows, then its pixels
     constexpr int BUF = ROWS * 32;                          // bytes of one wavefront's buffer
     constexpr int TPW = 4 / SKW;                           // tiles per workgroup
-    constexpr int NB = WM * WN;                            // 32x32 output blocks per tile
+    constexpr int NB = RB * WN;                            // 32x32 output blocks per tile
     // A block of 32 rows is 64 slots of 16 bytes, slot j = what loader lane j fetched: row j / 2, segment
     // (j % 2) ^ (j / 16 % 2) of the row's 32 bytes -- the exchange puts rows r and r + 8 of a segment on different
     // LDS banks, which leaves the consumers' reads (32 rows of one segment) two to a bank instead of four.
-    __shared__ uint2 s_rows[16];                            // the table of row pairs, one for the workgroup
+    __shared__ uint2 s_rows[TWO ? 32 : 16];                            // the table of row pairs, one for the workgroup
     // staging rows [wavefront][buffer][block * 64 + slot]; once the walk over K is over, the same memory holds the
     // shared tiles' sums [tile][block][sum register][lane]
     constexpr int STAGE_BYTES = 4 * 2 * BUF, SUM_BYTES = SKW > 1 ? TPW * NB * 4096 : 0;
@@ -77,6 +91,9 @@ smfmac_staged_kernel(Args a)
     const int64_t my_tile = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * TPW + tw;
     const bool active = my_tile < a.wave_tiles;
     sparse_fill_table<NIB>(s_rows, a.pools, threadIdx.x);
+    if constexpr (TWO) {
+        if (threadIdx.x >= 16 && threadIdx.x < 32) sparse_fill_high_entry(s_rows, a.pools, threadIdx.x - 16);
+    }
     __syncthreads();                                       // (every wavefront of the workgroup, also one without a tile)
     if (SKW == 1 && !active) return;                       // whole wavefronts leave; no barrier follows on this path
     const int64_t wave_tile = active ? my_tile : 0;        // (an idle wavefront of a shared workgroup adds nothing)
@@ -99,7 +116,7 @@ smfmac_staged_kernel(Args a)
         n_tile = first + (int)(g - mg * (uint32_t)width);
         m_tile = (int)((mg << a.m_log2) + mi);
     }
-    const int m0 = m_tile * (WM * 32), n0 = n_tile * (WN * 32);
+    const int m0 = m_tile * (RB * 32), n0 = n_tile * (WN * 32);
     const int cq = p.Cin / 4;                               // packed bytes per pixel
     // This wavefront's runs of K: g0, g0 + stride, ... below g1.  TURNS (layers without a filter window): wavefronts sharing
     // a tile take turns run by run (stride SKW), so that at any time the four of them read the four 32-byte runs of the SAME
@@ -118,9 +135,9 @@ smfmac_staged_kernel(Args a)
 
     // as a loader, this lane fetches 16-byte segment lseg of row lrow of every 32-row block
     const int lrow = lane >> 1, lseg = (lane & 1) ^ ((lane >> 4) & 1);
-    const uint8_t *w_ld[WM];
+    const uint8_t *w_ld[RB];
 #pragma unroll
-    for (int bm = 0; bm < WM; ++bm)
+    for (int bm = 0; bm < RB; ++bm)
         w_ld[bm] = p.Wp + (int64_t)min(m0 + bm * 32 + lrow, p.M - 1) * (p.K / 4) + (HALF ? 0 : lseg * 16);
     int32_t x_ld[WN];                                       // (32-bit offsets: the host sends inputs below 2^31 bytes)
 #pragma unroll
@@ -141,8 +158,8 @@ smfmac_staged_kernel(Args a)
         for (int bn = 0; bn < WN; ++bn)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[bm][bn][e] = 0;
-    float sc_cols[WM];
-    dg_mfma_column_scales<WM, true>(p, m0, lane, sc_cols);
+    float sc_cols[RB];
+    dg_mfma_column_scales<RB, true>(p, m0, lane, sc_cols);
 
     // ---- the loader's side: runs are fetched two ahead of the one being multiplied
     const char *stage = (const char *)s_mem + w4 * (2 * BUF);
@@ -162,21 +179,21 @@ smfmac_staged_kernel(Args a)
             const int32_t off0 = pixel_offset(c0), off1 = pixel_offset(c1);
             const int32_t w_off = (lseg ? c1 : c0) * 16, x_off = lseg ? off1 : off0;
 #pragma unroll
-            for (int bm = 0; bm < WM; ++bm) dg_load16_to_lds(w_ld[bm] + w_off, dst + bm * 1024);
+            for (int bm = 0; bm < RB; ++bm) dg_load16_to_lds(w_ld[bm] + w_off, dst + bm * 1024);
 #pragma unroll
-            for (int bn = 0; bn < WN; ++bn) dg_load16_to_lds(p.Xp, max(0, min(x_ld[bn] + x_off, x_last)), dst + (WM + bn) * 1024);
+            for (int bn = 0; bn < WN; ++bn) dg_load16_to_lds(p.Xp, max(0, min(x_ld[bn] + x_off, x_last)), dst + (RB + bn) * 1024);
             ++fetches, ++fetched;
             return;
         }
 #pragma unroll
-        for (int bm = 0; bm < WM; ++bm) dg_load16_to_lds(w_ld[bm] + g * 32, dst + bm * 1024);
+        for (int bm = 0; bm < RB; ++bm) dg_load16_to_lds(w_ld[bm] + g * 32, dst + bm * 1024);
         const int32_t tap_off = (kh * p.W + kw) * cq + cib;
 #pragma unroll
         for (int bn = 0; bn < WN; ++bn) {
             // (a tap outside the image or past the end: any address inside the tensor will do; the kept bytes of a
             // lane outside the image are zero)
             const int32_t off = max(0, min(x_ld[bn] + tap_off, x_last));
-            dg_load16_to_lds(p.Xp, off, dst + (WM + bn) * 1024);
+            dg_load16_to_lds(p.Xp, off, dst + (RB + bn) * 1024);
         }
         ++fetches;
         fetched += stride;
@@ -196,17 +213,17 @@ smfmac_staged_kernel(Args a)
     // own half's.  Lane offsets into a buffer, for the run's two chunks:
     const int w_at[2] = {slot0 * 16, (slot0 ^ 1) * 16}, x_at[2] = {slot0 * 16 + h * 8, (slot0 ^ 1) * 16 + h * 8};
     struct Words2 {
-        uint2 ca[WM], ca1[WM], cb[WN];
+        uint2 ca[RB], ca1[RB], cb[WN];
     };
     auto read_words = [&](Words2 &w, int buf, int s) {
         const char *src = stage + buf * BUF;
 #pragma unroll
-        for (int bm = 0; bm < WM; ++bm) {
+        for (int bm = 0; bm < RB; ++bm) {
             const uint4 q = *(const uint4 *)(src + bm * 1024 + w_at[s]);
             w.ca[bm] = make_uint2(q.x, q.y), w.ca1[bm] = make_uint2(q.z, q.w);
         }
 #pragma unroll
-        for (int bn = 0; bn < WN; ++bn) w.cb[bn] = *(const uint2 *)(src + (WM + bn) * 1024 + x_at[s]);
+        for (int bn = 0; bn < WN; ++bn) w.cb[bn] = *(const uint2 *)(src + (RB + bn) * 1024 + x_at[s]);
     };
     const uint32_t pick = sparse_pick(h);
     auto word = [](const uint2 &v, int t) { return t ? v.y : v.x; };
@@ -235,13 +252,13 @@ smfmac_staged_kernel(Args a)
         constexpr int MN = WM * WN;
         // the next step's dense operands: written here, spread by the scheduling groups below a few instructions at a
         // time between this step's matrix instructions, in whose shadow they then issue
-        dense_rows_movable<NIB>(s_rows, nw, nt, pick, next);
+        dense_rows_movable<NIB, TWO>(s_rows, nw, nt, pick, next);
         int odd_ix[SHIFT_ODD ? WN : 1];
         if constexpr (SHIFT_ODD) {
 #pragma unroll
             for (int bn = 0; bn < WN; ++bn) odd_ix[bn] = (int)(word(w.cb[bn], t) >> 2);
         }
-        constexpr int PER = (31 * WM + (SHIFT_ODD ? WN : 0) + 2 * MN - 1) / (2 * MN);      // other instructions per matrix instruction
+        constexpr int PER = ((TWO ? 39 : 31 * WM) + (SHIFT_ODD ? WN : 0) + 2 * MN - 1) / (2 * MN);      // other instructions per matrix instruction
 #pragma unroll
         for (int i = 0; i < 2 * MN; ++i) {
             const int par = i / MN, bm = (i % MN) / WN, bn = i % WN;
@@ -282,7 +299,8 @@ smfmac_staged_kernel(Args a)
         dg_wait_for_loads();                                   // (both runs: the first is needed now)
         read_words(wa, TURNS ? 0 : g0 & 1, 0);
 #pragma unroll
-        for (int u = 0; u < WM; ++u) sparse_dense_rows_shared<NIB>(s_rows, wa.ca[u].x, wa.ca1[u].x, pick, dn0[u][0], dn0[u][1]);
+        for (int u = 0; u < WM; ++u)
+            sparse_dense_rows_shared<NIB>(s_rows + (TWO ? 16 * u : 0), wa.ca[TWO ? 0 : u].x, wa.ca1[TWO ? 0 : u].x, pick, dn0[u][0], dn0[u][1]);
         if constexpr (HALF) {
             for (int g = 0; g < runs; ++g) {
                 kept_bytes((int)fdiv((uint32_t)(2 * g), a.div_cpt), true, ones, ones_odd);
@@ -322,8 +340,17 @@ smfmac_staged_kernel(Args a)
         }
         dg_wait_for_loads();                                   // (unused fetches past the end: their LDS writes end before the wavefront does)
     }
+    // the tile's blocks as they go to memory: two planes merge into one block row, 256 * hi + lo
+    v16i out[RB][WN];
+#pragma unroll
+    for (int bm = 0; bm < RB; ++bm)
+#pragma unroll
+        for (int bn = 0; bn < WN; ++bn)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                out[bm][bn][e] = TWO ? (int)((uint32_t)acc[0][bn][e] + ((uint32_t)acc[WM - 1][bn][e] << 8)) : acc[bm][bn][e];
     if (SKW == 1) {
-        dg_mfma_store_tile<WM, WN, true>(p, acc, m0, n0, lane, sc_cols);
+        dg_mfma_store_tile<RB, WN, true>(p, out, m0, n0, lane, sc_cols);
         return;
     }
     // The sums take the place of the staging rows: every wavefront is done with its rows (and its last loads have
@@ -334,7 +361,7 @@ smfmac_staged_kernel(Args a)
 #pragma unroll
         for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) sums[(i * 16 + e) * 64 + lane] = acc[i / WN][i % WN][e];
+            for (int e = 0; e < 16; ++e) sums[(i * 16 + e) * 64 + lane] = out[i / WN][i % WN][e];
     }
     __syncthreads();
     if (ks != 0 && g0 < g1) {
@@ -342,7 +369,7 @@ smfmac_staged_kernel(Args a)
         for (int i = 0; i < NB; ++i)
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                __hip_atomic_fetch_add(&sums[(i * 16 + e) * 64 + lane], acc[i / WN][i % WN][e], __ATOMIC_RELAXED,
+                __hip_atomic_fetch_add(&sums[(i * 16 + e) * 64 + lane], out[i / WN][i % WN][e], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __syncthreads();
@@ -364,14 +391,15 @@ smfmac_staged_kernel(Args a)
 // 8192-cube takes 550 us with an all-zero table, 640 us with entries 0 ... 9, 700 us with -6 ... 3 and 800 us with
 // -64 ... 64.  A table raised to 0 ... max - min keeps the high bits of the dense operand and of the growing sums
 // quiet; the kernel starts each sum at minus the bias times the pixel's positions of K, so the result is the same.
-template <bool NIB>
+template <bool NIB, bool TWO>
 void launch_sparse_staged(const DgProblem &p, const Pools &pools, int32_t bias, const Plan &q, int64_t wave_tiles, hipStream_t stream)
 {
     Args a;
     a.p = p;
     a.pools = pools;
     a.bias = bias;
-    a.tiles_m = (p.M + q.wm * 32 - 1) / (q.wm * 32);
+    const int rows = TWO ? 32 : q.wm * 32;                 // (two planes: q.wm = 2 blocks of the same 32 rows)
+    a.tiles_m = (p.M + rows - 1) / rows;
     a.wave_tiles = wave_tiles;
     a.div_ow = make_div((uint32_t)p.OW), a.div_oh = make_div((uint32_t)p.OH);
     a.div_cin = make_div((uint32_t)p.Cin), a.div_kw = make_div((uint32_t)p.KW);
@@ -388,22 +416,41 @@ void launch_sparse_staged(const DgProblem &p, const Pools &pools, int32_t bias, 
     const int tpw = 4 / q.skw;
     const dim3 grid((unsigned)((wave_tiles + tpw - 1) / tpw));
     const bool turns = p.KH * p.KW == 1;                   // (see the kernel: run by run without a filter window)
-#define DG_STAGED(WM, WN, SKW, TURNS) hipLaunchKernelGGL((smfmac_staged_kernel<WM, WN, SKW, TURNS, false, NIB>), grid, dim3(256), 0, stream, a)
-    if (half && q.wn == 4) hipLaunchKernelGGL((smfmac_staged_kernel<1, 4, 1, false, true, NIB>), grid, dim3(256), 0, stream, a);
-    else if (half) hipLaunchKernelGGL((smfmac_staged_kernel<1, 2, 1, false, true, NIB>), grid, dim3(256), 0, stream, a);
-    else if (q.wm == 2) DG_STAGED(2, 4, 1, false);
-    else if (q.wn == 7) DG_STAGED(1, 7, 1, false);
-    else if (q.wn == 6) DG_STAGED(1, 6, 1, false);
-    else if (q.wn == 4 && q.skw == 4 && turns) DG_STAGED(1, 4, 4, true);
-    else if (q.wn == 4 && q.skw == 4) DG_STAGED(1, 4, 4, false);
-    else if (q.wn == 4 && q.skw == 2 && turns) DG_STAGED(1, 4, 2, true);
-    else if (q.wn == 4 && q.skw == 2) DG_STAGED(1, 4, 2, false);
-    else if (q.wn == 4) DG_STAGED(1, 4, 1, false);
-    else if (q.skw == 4 && turns) DG_STAGED(1, 2, 4, true);
-    else if (q.skw == 4) DG_STAGED(1, 2, 4, false);
-    else if (q.skw == 2 && turns) DG_STAGED(1, 2, 2, true);
-    else if (q.skw == 2) DG_STAGED(1, 2, 2, false);
-    else DG_STAGED(1, 2, 1, false);
+#define DG_STAGED(WM, WN, SKW, TURNS) hipLaunchKernelGGL((smfmac_staged_kernel<WM, WN, SKW, TURNS, false, NIB, TWO>), grid, dim3(256), 0, stream, a)
+    if constexpr (TWO) {
+        if (half) hipLaunchKernelGGL((smfmac_staged_kernel<2, 2, 1, false, true, NIB, TWO>), grid, dim3(256), 0, stream, a);
+        else if (q.wn == 4 && q.skw == 1) DG_STAGED(2, 4, 1, false);
+        else if (q.wn == 4 && q.skw == 2 && turns) DG_STAGED(2, 4, 2, true);
+        else if (q.wn == 4 && q.skw == 2) DG_STAGED(2, 4, 2, false);
+        else if (q.wn == 4 && turns) DG_STAGED(2, 4, 4, true);
+        else if (q.wn == 4) DG_STAGED(2, 4, 4, false);
+        else if (q.wn == 2 && q.skw == 1) DG_STAGED(2, 2, 1, false);
+        else if (q.wn == 2 && q.skw == 2 && turns) DG_STAGED(2, 2, 2, true);
+        else if (q.wn == 2 && q.skw == 2) DG_STAGED(2, 2, 2, false);
+        else if (q.wn == 2 && turns) DG_STAGED(2, 2, 4, true);
+        else if (q.wn == 2) DG_STAGED(2, 2, 4, false);
+        else if (q.skw == 1) DG_STAGED(2, 1, 1, false);
+        else if (q.skw == 2 && turns) DG_STAGED(2, 1, 2, true);
+        else if (q.skw == 2) DG_STAGED(2, 1, 2, false);
+        else if (turns) DG_STAGED(2, 1, 4, true);
+        else DG_STAGED(2, 1, 4, false);
+    } else {
+        if (half && q.wn == 4) hipLaunchKernelGGL((smfmac_staged_kernel<1, 4, 1, false, true, NIB, false>), grid, dim3(256), 0, stream, a);
+        else if (half) hipLaunchKernelGGL((smfmac_staged_kernel<1, 2, 1, false, true, NIB, false>), grid, dim3(256), 0, stream, a);
+        else if (q.wm == 2) DG_STAGED(2, 4, 1, false);
+        else if (q.wn == 7) DG_STAGED(1, 7, 1, false);
+        else if (q.wn == 6) DG_STAGED(1, 6, 1, false);
+        else if (q.wn == 4 && q.skw == 4 && turns) DG_STAGED(1, 4, 4, true);
+        else if (q.wn == 4 && q.skw == 4) DG_STAGED(1, 4, 4, false);
+        else if (q.wn == 4 && q.skw == 2 && turns) DG_STAGED(1, 4, 2, true);
+        else if (q.wn == 4 && q.skw == 2) DG_STAGED(1, 4, 2, false);
+        else if (q.wn == 4) DG_STAGED(1, 4, 1, false);
+        else if (q.skw == 4 && turns) DG_STAGED(1, 2, 4, true);
+        else if (q.skw == 4) DG_STAGED(1, 2, 4, false);
+        else if (q.skw == 2 && turns) DG_STAGED(1, 2, 2, true);
+        else if (q.skw == 2) DG_STAGED(1, 2, 2, false);
+        else DG_STAGED(1, 2, 1, false);
+    }
 #undef DG_STAGED
 }
 
