@@ -27,7 +27,7 @@ namespace dgoh {
 // The dense operands of all WM weight blocks for word `t` of `w` (as sparse_dense_rows_shared, but with the opaque
 // statement that keeps the indices pre-multiplied NOT volatile, so that the scheduler may move these instructions
 // between matrix instructions).
-template <bool NIB, bool TWO, int WM, class W>
+template <bool NIB, bool TWO, int HIGH, int WM, class W>
 __device__ __forceinline__ void dense_rows_movable(const uint2 *table, const W &w, int t, uint32_t pick, v8i (&out)[WM][2])
 {
     if constexpr (TWO) {                                    // one row block, both planes
@@ -44,7 +44,7 @@ __device__ __forceinline__ void dense_rows_movable(const uint2 *table, const W &
         uint32_t e, o;
         sparse_row_offsets<NIB>(__builtin_amdgcn_perm(w1, w0, pick), e, o);
         asm("" : "+v"(e), "+v"(o));
-        sparse_read_rows<NIB>(table, e, o, out[u][0], out[u][1]);
+        sparse_read_rows<NIB, HIGH>(table, e, o, out[u][0], out[u][1]);
     }
 }
 
@@ -76,12 +76,14 @@ smfmac_staged_kernel(Args a)
     // A block of 32 rows is 64 slots of 16 bytes, slot j = what loader lane j fetched: row j / 2, segment
     // (j % 2) ^ (j / 16 % 2) of the row's 32 bytes -- the exchange puts rows r and r + 8 of a segment on different
     // LDS banks, which leaves the consumers' reads (32 rows of one segment) two to a bank instead of four.
-    __shared__ uint2 s_rows[TWO ? 32 : 16];                            // the table of row pairs, one for the workgroup
+    // the table of row pairs, one for the workgroup (NIB: the high rows HIGH bytes behind the low ones)
+    constexpr int HIGH = NIB ? 1040 : 64;
+    __shared__ uint2 s_rows[NIB ? (HIGH + 64) / 8 : (TWO ? 32 : 16)];
     // staging rows [wavefront][buffer][block * 64 + slot]; once the walk over K is over, the same memory holds the
     // shared tiles' sums [tile][block][sum register][lane]
     constexpr int STAGE_BYTES = 4 * 2 * BUF, SUM_BYTES = SKW > 1 ? TPW * NB * 4096 : 0;
     __shared__ uint4 s_mem[(STAGE_BYTES > SUM_BYTES ? STAGE_BYTES : SUM_BYTES) / 16];
-    static_assert(sizeof(s_mem) <= 80 * 1024 - 256, "two workgroups per compute unit (160 KB of LDS)");
+    static_assert(sizeof(s_mem) + sizeof(s_rows) <= 80 * 1024, "two workgroups per compute unit (160 KB of LDS)");
     int32_t *s_acc = (int32_t *)s_mem;
     // the narrower tiles have the registers for a second set of kept bytes, (0, 1), which spares the odd codes' shift
     constexpr bool SHIFT_ODD = WM * WN >= 7;
@@ -90,7 +92,7 @@ smfmac_staged_kernel(Args a)
     const int ks = w4 % SKW, tw = w4 / SKW;                 // this wavefront's share of K, and its tile within the workgroup
     const int64_t my_tile = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * TPW + tw;
     const bool active = my_tile < a.wave_tiles;
-    sparse_fill_table<NIB>(s_rows, a.pools, threadIdx.x);
+    sparse_fill_table<NIB, HIGH>(s_rows, a.pools, threadIdx.x);
     if constexpr (TWO) {
         if (threadIdx.x >= 16 && threadIdx.x < 32) sparse_fill_high_entry(s_rows, a.pools, threadIdx.x - 16);
     }
@@ -252,7 +254,7 @@ smfmac_staged_kernel(Args a)
         constexpr int MN = WM * WN;
         // the next step's dense operands: written here, spread by the scheduling groups below a few instructions at a
         // time between this step's matrix instructions, in whose shadow they then issue
-        dense_rows_movable<NIB, TWO>(s_rows, nw, nt, pick, next);
+        dense_rows_movable<NIB, TWO, HIGH>(s_rows, nw, nt, pick, next);
         int odd_ix[SHIFT_ODD ? WN : 1];
         if constexpr (SHIFT_ODD) {
 #pragma unroll
@@ -300,7 +302,7 @@ smfmac_staged_kernel(Args a)
         read_words(wa, TURNS ? 0 : g0 & 1, 0);
 #pragma unroll
         for (int u = 0; u < WM; ++u)
-            sparse_dense_rows_shared<NIB>(s_rows + (TWO ? 16 * u : 0), wa.ca[TWO ? 0 : u].x, wa.ca1[TWO ? 0 : u].x, pick, dn0[u][0], dn0[u][1]);
+            sparse_dense_rows_shared<NIB, HIGH>(s_rows + (TWO ? 16 * u : 0), wa.ca[TWO ? 0 : u].x, wa.ca1[TWO ? 0 : u].x, pick, dn0[u][0], dn0[u][1]);
         if constexpr (HALF) {
             for (int g = 0; g < runs; ++g) {
                 kept_bytes((int)fdiv((uint32_t)(2 * g), a.div_cpt), true, ones, ones_odd);
