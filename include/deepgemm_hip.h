@@ -84,7 +84,8 @@ dg_status dg_build_lut_entries(const int16_t entries[16], dg_lut_dtype entry, dg
  * dg_conv2d_lut write binary32 to Cf_dev / Yf_dev (required; the int32 pointer is ignored): the sum of the
  * fetched entries taken in binary32, one addition per reduction position in ascending k (for a convolution kh,
  * then kw, then ci; taps outside the image skipped), starting from +0; then, if a scale is given, one multiply by
- * scale[m].  Only the LDS kernel runs binary32 tables (AUTO selects it).
+ * scale[m].  The LDS kernel runs every such table; AUTO takes large layers (Cin >= 16, finite entries, none below 2^-100 but
+ * zero) to the matrix cores, with the same sums bit for bit.
  */
 dg_status dg_build_lut_f32(const float levels_w[4], const float levels_a[4], dg_lut **out);
 /* Copy the 16 binary32 entries of a DG_LUT_F32 table (DG_ERR_UNSUPPORTED for integer tables). */
@@ -209,6 +210,7 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *                    "1": wherever it applies (default: where it was measured shorter than two kernels)
  *   DG_ONEHOT_CODES_SPARSE "0": that kernel on the dense instruction only, "1": on the sparse one wherever the output's
  *                    channel axis is contiguous (the default)
+ *   DG_F32_MFMA      "0": AUTO never takes a binary32 table to the matrix cores, "1": whatever the layer's size
  *   DG_STAGED_2P     "0": AUTO never takes the staged kernel for entries beyond int8
  *   DG_STAGED_2P_PLAN  its tile's width in blocks, 1, 2 or 4, optionally followed by "k2" or "k4" (whatever the size)
  *   DG_RAGGED        "0": AUTO never takes the sparse-instruction kernel for Cin % 32 != 0, "1": also on small problems

@@ -296,11 +296,12 @@ int64_t dg_conv_out_dim(int64_t in, int64_t k, int64_t stride, int64_t pad)
 
 namespace {
 
-enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Ragged, Staged2p, Unsupported };
+enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Ragged, Staged2p, OneHotF32, Unsupported };
 
 Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
 {
-    // binary32 tables run on the plain LDS kernel only; 3- and 4-bit tables on the one-hot matrix-core kernel or the LDS kernel
+    // binary32 tables run on their own matrix-core kernel and on the plain LDS kernel; 3- and 4-bit tables on the one-hot matrix-core kernel or the LDS kernel
+    if (lut->dtype == DG_LUT_F32 && variant == DG_KERNEL_AUTO && dg_onehot_f32_preferred(lut, p)) return Pick::OneHotF32;
     if (lut->dtype == DG_LUT_F32)
         return (variant == DG_KERNEL_AUTO || variant == DG_KERNEL_LDS) ? Pick::LdsF32 : Pick::Unsupported;
     if (lut->bits != 2) {
@@ -354,6 +355,7 @@ dg_status run(const dg_lut *lut, const DgProblem &p, dg_kernel variant, hipStrea
     case Pick::Perm: return dg_launch_perm(lut, p, stream);
     case Pick::Lds: return dg_launch_lds(lut, p, stream);
     case Pick::LdsF32: return dg_launch_lds_f32(lut, p, stream);
+    case Pick::OneHotF32: return dg_launch_onehot_f32(lut, p, stream);
     case Pick::Mfma: return dg_launch_decode(lut, p, stream);
     case Pick::SmallN: return dg_launch_smalln(lut, p, stream);
     case Pick::Lut65k: return dg_launch_lut65k(lut, p, stream);
@@ -379,6 +381,7 @@ const char *pick_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Pick::Perm: return dg_perm_config_name(lut, p);
     case Pick::Lds: return "lds";
     case Pick::LdsF32: return "lds_f32";
+    case Pick::OneHotF32: return "onehot_mfma_f32";
     case Pick::Mfma: return dg_decode_config_name(lut, p);
     case Pick::SmallN: return "smalln";
     case Pick::Lut65k: return "lut65k";

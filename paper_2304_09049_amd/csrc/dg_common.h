@@ -92,6 +92,8 @@ dg_status dg_launch_dequantize(const int32_t *acc, int64_t rows, int64_t C, cons
                                hipStream_t stream);
 dg_status dg_launch_lds(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 dg_status dg_launch_lds_f32(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+bool dg_onehot_f32_preferred(const dg_lut *lut, const DgProblem &p);   // binary32 tables on the matrix cores
+dg_status dg_launch_onehot_f32(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 bool dg_perm_supports(const dg_lut *lut, const DgProblem &p);
 dg_status dg_launch_perm(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 const char *dg_perm_config_name(const dg_lut *lut, const DgProblem &p);

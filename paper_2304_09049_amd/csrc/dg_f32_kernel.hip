@@ -1,0 +1,231 @@
+// Binary32 tables on the matrix cores.  The sum is one binary32 addition per reduction position, in ascending k, from +0
+// (dg_lds_kernel.hip is the plain form); it cannot be split or reordered, so the parallel axis is the outputs alone.
+//
+//   acc[n][m] <- acc[n][m] + T[w(m,k)][a(n,k)]  =  fma chain over v = 0..3 of  [a(n,k) == v] * T[w(m,k)][v]
+//
+// v_mfma_f32_16x16x4_f32 does that for a 16 x 16 block and one position: its four products per output are the four codes v,
+// three of them by zero.  A product by zero is +-0 and leaves the sum as it is (a sum that starts at +0 never becomes -0), the
+// fourth is the entry itself, so whatever the order of the four, the result is the one rounded addition.  That needs finite
+// entries (0 * inf is not 0), and no subnormal numbers, which this kernel does not want to depend on: every entry 0 or at least
+// 2^-100, hence every partial sum a multiple of 2^-123 (the host checks; other tables stay with the plain kernel).
+//
+// Operands: lane (i = lane % 16, v = lane / 16) supplies [a(n0 + i, k) == v] and T[w(m0 + i, k)][v].  Two positions' worth comes from
+// one 8-byte LDS read at a 4-bit index, the two codes: 16 pairs per v, for either operand; a pixel whose tap lies outside the
+// image reads pairs of zeros instead.
+//
+// Bound by the matrix pipe and the instructions beside it: 32 cycles of the pipe per position and block of 256 outputs, a quarter
+// of it useful -- 8 table additions per SIMD and cycle at best -- and 2.5 other instructions, which a lone wavefront does not
+// overlap with its own matrix instructions (about 55 cycles per position; two blocks per wavefront, sharing the entries, 110: no
+// gain, and half the wavefronts).  So blocks are small and wavefronts many.  The plain kernel spends 5 vector instructions and an
+// LDS read per addition (3 additions per SIMD and cycle).  Measured against it: 28x28x128 -> 128 3x3 at batch 4 (1568 blocks) 63.4
+// -> 48.3 us, at batch 8 117 -> 88.8; 56x56x64 -> 64 at batch 8 21.1 -> 13.8; 14x14x36 -> 100 3x3 at batch 8 (686) 19.4 -> 13.5.
+// Reading the pairs one at a time, just before their instructions, instead of a word ahead: 57.1 us on the first.
+#include "dg_common.h"
+
+#include <cmath>
+#include <cstdlib>
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+struct F32Args {
+    DgProblem p;
+    float e[16];
+    DgFastDiv div_ow, div_oh;
+    int32_t tiles_m;
+    int64_t tiles;
+};
+
+template <int CHW>
+struct __attribute__((packed, aligned(1))) RawWords {
+    uint32_t v[CHW];
+};
+
+// CHW: words per load, 4 where a tap is whole 4-word groups.  WHOLE: Cin % 16 == 0, every
+// word of a tap is 16 codes; otherwise the last word of a tap is read so that it ends with the tap, and shifted.
+// One software pipeline over all of K: a word's pairs are read from LDS between the matrix instructions of the word before.
+template <int CHW, bool WHOLE>
+__global__ void __launch_bounds__(256)
+onehot_f32_kernel(F32Args a)
+{
+    static_assert(WHOLE || CHW == 1, "taps that are no whole words are loaded word by word");
+    constexpr int WN = 1;                                   // blocks of 16 pixels per wavefront
+    constexpr int RING = CHW == 4 ? 2 : 4;                  // loads in flight
+    __shared__ float s_table[2 * 4 * 32 + 32];              // pairs of entries [v][pair], pairs of one-hot values, pairs of zeros
+    const DgProblem &p = a.p;
+    for (int i = threadIdx.x; i < 2 * 4 * 32 + 32; i += 256) {
+        const int v = (i >> 5) & 3, code = (i & 1) ? (i >> 3) & 3 : (i >> 1) & 3;
+        s_table[i] = i < 128 ? a.e[4 * code + v] : (i < 256 && code == v ? 1.0f : 0.0f);
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, i16 = lane & 15, v = lane >> 4;
+    const int64_t tile = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (tile >= a.tiles) return;                            // (whole wavefronts; no barrier follows)
+    const int m0 = (int)(tile % a.tiles_m) * 16, n0 = (int)(tile / a.tiles_m) * (16 * WN);
+    const int L = p.Cin / 4, loads = (L + 4 * CHW - 1) / (4 * CHW), total = p.KH * p.KW * loads;
+
+    const uint8_t *w_next = p.Wp + (int64_t)min(m0 + i16, p.M - 1) * (p.K / 4);
+    int ih0[WN], iw0[WN], off0[WN];                          // (32-bit offsets: the host sends inputs below 2^31 bytes)
+    bool live[WN];
+#pragma unroll
+    for (int b = 0; b < WN; ++b) {
+        const int n = n0 + 16 * b + i16, nn = min(n, p.N - 1);
+        const int t = (int)dg_fdiv((uint32_t)nn, a.div_ow), ow = nn - t * p.OW;
+        const int img = (int)dg_fdiv((uint32_t)t, a.div_oh), oh = t - img * p.OH;
+        live[b] = n < p.N;
+        ih0[b] = oh * p.sh - p.ph, iw0[b] = ow * p.sw - p.pw;
+        off0[b] = ((img * p.H + ih0[b]) * p.W + iw0[b]) * L;
+    }
+
+    struct Load {
+        RawWords<CHW> w, x[WN];
+        uint32_t base[WN];                                  // where this pixel's pairs are read
+        int shift, codes;                                   // (the same in every lane)
+    };
+    const uint32_t w_base = 128 * v, x_base = 512 + 128 * v, zeros = 1024;
+    int kh = 0, kw = 0, j = 0, fetched = 0;
+    int32_t x_at[WN];                                       // the tap's bytes of each pixel (outside the image: the first pixel's)
+    uint32_t tap_base[WN];
+    auto enter_tap = [&]() {
+        const int32_t tap_off = (kh * p.W + kw) * L;
+#pragma unroll
+        for (int b = 0; b < WN; ++b) {
+            const bool ok = live[b] & ((uint32_t)(ih0[b] + kh) < (uint32_t)p.H) & ((uint32_t)(iw0[b] + kw) < (uint32_t)p.W);
+            x_at[b] = ok ? off0[b] + tap_off : 0;
+            tap_base[b] = ok ? x_base : zeros;
+        }
+    };
+    enter_tap();
+    auto fetch = [&](Load &t) {                              // past the end: the last words again, as pairs of zeros
+        const int start = WHOLE ? 4 * CHW * j : min(4 * j, L - 4);
+        t.shift = 8 * (4 * j - start);
+        t.codes = min(16, 4 * (L - 4 * j));
+        t.w = *(const RawWords<CHW> *)(w_next + start);
+#pragma unroll
+        for (int b = 0; b < WN; ++b) {
+            t.x[b] = *(const RawWords<CHW> *)(p.Xp + x_at[b] + start);
+            t.base[b] = fetched < total ? tap_base[b] : zeros;
+        }
+        if (++fetched < total && ++j == loads) {             // (uniform)
+            j = 0;
+            if (++kw == p.KW) kw = 0, ++kh;
+            w_next += L;
+            enter_tap();
+        }
+    };
+
+    f32x4 acc[WN];
+#pragma unroll
+    for (int b = 0; b < WN; ++b) acc[b] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    const char *table = (const char *)s_table;
+    struct Pairs {
+        float2 e[8], o[WN][8];
+    };
+    // Pair q = bits 4q ... 4q + 3 of the word, as a byte offset into a table of pairs: the even q in the bytes of one word, the odd
+    // ones in another's (kept as they are: a byte of them plus the base is one instruction).
+    auto read_pairs = [&](const Load &t, int c, Pairs &d) {
+        auto split = [&](uint32_t word, uint32_t (&s)[2]) {
+            if (!WHOLE) word >>= t.shift;
+            s[0] = (word & 0x0F0F0F0Fu) << 3, s[1] = (word >> 1) & 0x78787878u;
+            asm("" : "+v"(s[0]), "+v"(s[1]));
+        };
+        uint32_t w[2], x[WN][2];
+        split(t.w.v[c], w);
+#pragma unroll
+        for (int b = 0; b < WN; ++b) split(t.x[b].v[c], x[b]);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            d.e[q] = *(const float2 *)(table + (w_base + ((w[q & 1] >> (8 * (q / 2))) & 255u)));
+#pragma unroll
+            for (int b = 0; b < WN; ++b) d.o[b][q] = *(const float2 *)(table + (t.base[b] + ((x[b][q & 1] >> (8 * (q / 2))) & 255u)));
+        }
+    };
+    auto multiply = [&](const Pairs &d, int q0, int q1) {
+#pragma unroll
+        for (int q = q0; q < q1; ++q) {
+#pragma unroll
+            for (int b = 0; b < WN; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.o[b][q].x, d.e[q].x, acc[b], 0, 0, 0);
+#pragma unroll
+            for (int b = 0; b < WN; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.o[b][q].y, d.e[q].y, acc[b], 0, 0, 0);
+        }
+    };
+
+    Load ring[RING];
+    Pairs pairs[2];
+#pragma unroll
+    for (int i = 0; i < RING; ++i) fetch(ring[i]);
+    read_pairs(ring[0], 0, pairs[0]);
+    for (int done = 0; done < total; done += RING)
+#pragma unroll
+        for (int i = 0; i < RING; ++i) {
+            if (done + i >= total) break;                   // (uniform)
+            const int codes = ring[i].codes;
+#pragma unroll
+            for (int c = 0; c < CHW; ++c) {
+                const int cur = (i * CHW + c) & 1;
+                read_pairs(c + 1 < CHW ? ring[i] : ring[(i + 1) % RING], c + 1 < CHW ? c + 1 : 0, pairs[cur ^ 1]);
+                if constexpr (WHOLE) {
+                    multiply(pairs[cur], 0, 8);
+#pragma unroll
+                    for (int k = 0; k < 16 * WN; ++k) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x102, 3, 0);
+                    }
+                } else {
+                    multiply(pairs[cur], 0, 2);
+                    if (codes > 4) multiply(pairs[cur], 2, 4);       // (uniform)
+                    if (codes > 8) multiply(pairs[cur], 4, 6);
+                    if (codes > 12) multiply(pairs[cur], 6, 8);
+                }
+            }
+            fetch(ring[i]);
+        }
+
+    const int m = m0 + i16;
+    if (m >= p.M) return;
+    const float scale = p.scale ? p.scale[m] : 0.0f;
+#pragma unroll
+    for (int b = 0; b < WN; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int n = n0 + 16 * b + 4 * v + e;
+            if (n >= p.N) continue;
+            const int64_t o = (int64_t)m * p.stride_cm + (int64_t)n * p.stride_cn;
+            p.Cf[o] = p.scale ? __fmul_rn(acc[b][e], scale) : acc[b][e];
+        }
+}
+
+}   // namespace
+
+// AUTO takes it from 9/16 of a block per SIMD: 625 blocks were ahead (7x7x512 -> 400 at batch 8 18.7 -> 15.2 us), 400 behind
+// (14x14x256 -> 256 3x3 at batch 2 52.5 against 57.0: the plain kernel has four times the wavefronts), 196 and 128 further behind.
+// DG_F32_MFMA: 0 never, 1 whatever the size.
+bool dg_onehot_f32_preferred(const dg_lut *lut, const DgProblem &p)
+{
+    if (lut->dtype != DG_LUT_F32 || p.Cin < 16) return false;
+    for (int i = 0; i < 16; ++i) {
+        const float e = lut->fentry[i];
+        if (!std::isfinite(e) || (e != 0.0f && std::fabs(e) < 0x1p-100f)) return false;
+    }
+    const int64_t blocks = ((int64_t)(p.M + 15) / 16) * (((int64_t)p.N + 15) / 16);
+    if (blocks > INT32_MAX) return false;
+    if ((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4) >= ((int64_t)1 << 31)) return false;      // (32-bit byte offsets)
+    if (const char *f = dg_override("DG_F32_MFMA")) return atoi(f) != 0;
+    return blocks >= dg_simd_count() * 9 / 16;
+}
+
+dg_status dg_launch_onehot_f32(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
+{
+    F32Args a;
+    a.p = p;
+    for (int i = 0; i < 16; ++i) a.e[i] = lut->fentry[i];
+    a.div_ow = dg_make_div((uint32_t)p.OW), a.div_oh = dg_make_div((uint32_t)p.OH);
+    a.tiles_m = (p.M + 15) / 16;
+    a.tiles = (int64_t)a.tiles_m * (((int64_t)p.N + 15) / 16);
+    const dim3 grid((unsigned)((a.tiles + 3) / 4));
+    if (p.Cin % 64 == 0) hipLaunchKernelGGL((onehot_f32_kernel<4, true>), grid, dim3(256), 0, stream, a);
+    else if (p.Cin % 16 == 0) hipLaunchKernelGGL((onehot_f32_kernel<1, true>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((onehot_f32_kernel<1, false>), grid, dim3(256), 0, stream, a);
+    return dg_check_launch("onehot_f32_kernel");
+}
