@@ -142,16 +142,48 @@ pack_slots4_kernel(const uint8_t *__restrict__ codes, uint8_t *__restrict__ pack
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < pairs; g += stride)
         packed[g] = (uint8_t)((codes[2 * g] & mask) | ((codes[2 * g + 1] & mask) << 4));
 }
+
+// The same 16 codes to a lane (16-byte load, 8-byte store): in a dword of four codes the odd ones move down four bits beside the
+// even ones, and the two bytes that hold pairs are picked out of two such dwords at a time.  Bound by memory: a code per byte in,
+// half a byte out.  In graph replays, against a pair of codes per lane (above; now for what is left and for other
+// alignments): 3.2 M codes 4.14 -> 2.48 us, 12.8 M 6.77 -> 3.35, 0.8 M 2.54 -> 2.23 (a launch: 1.6).
+__device__ __forceinline__ uint32_t pack_slots8(uint32_t a, uint32_t b, uint32_t mask)
+{
+    a &= mask, b &= mask;
+    return __builtin_amdgcn_perm(b | (b >> 4), a | (a >> 4), 0x06040200u);
+}
+
+__global__ void __launch_bounds__(256)
+pack_slots4_vec16_kernel(const uint4 *__restrict__ codes, uint2 *__restrict__ packed, int64_t groups, uint32_t mask)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < groups; g += stride) {
+        const uint4 t = codes[g];
+        packed[g] = make_uint2(pack_slots8(t.x, t.y, mask), pack_slots8(t.z, t.w, mask));
+    }
+}
 }   // namespace
 
 dg_status dg_launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits, uint8_t *packed, hipStream_t stream)
 {
     if (bits != 2) {
-        const int64_t pairs = rows * K / 2;
+        const uint32_t mask = (1u << bits) - 1u;
+        const int64_t total = rows * K;                     // even
+        const int64_t groups = (uintptr_t)codes % 16 == 0 && (uintptr_t)packed % 8 == 0 ? total / 16 : 0;
+        if (groups > 0) {
+            int64_t blocks = (groups + 255) / 256;
+            if (blocks > 256 * 32) blocks = 256 * 32;
+            hipLaunchKernelGGL(pack_slots4_vec16_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint4 *)codes,
+                               (uint2 *)packed, groups, mask * 0x01010101u);
+            const dg_status s = dg_check_launch("pack_slots4_vec16_kernel");
+            if (s != DG_OK) return s;
+        }
+        const int64_t pairs = total / 2 - 8 * groups;
+        if (pairs == 0) return DG_OK;
         int64_t blocks = (pairs + 255) / 256;
         if (blocks > 256 * 32) blocks = 256 * 32;
-        hipLaunchKernelGGL(pack_slots4_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, codes, packed, pairs,
-                           (1u << bits) - 1u);
+        hipLaunchKernelGGL(pack_slots4_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, codes + 16 * groups, packed + 8 * groups,
+                           pairs, mask);
         return dg_check_launch("pack_slots4_kernel");
     }
     const int64_t total = rows * K;           // multiple of 4
