@@ -42,7 +42,7 @@ struct __attribute__((packed, aligned(1))) RawWords {
     uint32_t v[CHW];
 };
 
-// CHW: words per load, 4 where a tap is whole 4-word groups.  WHOLE: Cin % 16 == 0, every
+// CHW: words per load, 4 or 2 where a tap is whole groups of so many.  WHOLE: Cin % 16 == 0, every
 // word of a tap is 16 codes; otherwise the last word of a tap is read so that it ends with the tap, and shifted.
 // One software pipeline over all of K: a word's pairs are read from LDS between the matrix instructions of the word before.
 template <int CHW, bool WHOLE>
@@ -51,7 +51,7 @@ onehot_f32_kernel(F32Args a)
 {
     static_assert(WHOLE || CHW == 1, "taps that are no whole words are loaded word by word");
     constexpr int WN = 1;                                   // blocks of 16 pixels per wavefront
-    constexpr int RING = CHW == 4 ? 2 : 4;                  // loads in flight
+    constexpr int RING = CHW == 1 ? 4 : 2;                  // loads in flight
     __shared__ float s_table[2 * 4 * 32 + 32];              // pairs of entries [v][pair], pairs of one-hot values, pairs of zeros
     const DgProblem &p = a.p;
     for (int i = threadIdx.x; i < 2 * 4 * 32 + 32; i += 256) {
@@ -198,8 +198,12 @@ onehot_f32_kernel(F32Args a)
 
 }   // namespace
 
-// AUTO takes it from 9/16 of a block per SIMD: 625 blocks were ahead (7x7x512 -> 400 at batch 8 18.7 -> 15.2 us), 400 behind
-// (14x14x256 -> 256 3x3 at batch 2 52.5 against 57.0: the plain kernel has four times the wavefronts), 196 and 128 further behind.
+// AUTO compares what the two kernels take per position of K.  This one: 7 + 19.5 w ns, w the wavefronts on the busiest SIMD (a
+// workgroup of four blocks per compute unit at a time; w = 1: 26 - 29 ns measured, 2: 40 - 47, 3: 72, 4: 75).  The plain one: the
+// outputs at 5.8 thousand per ns -- 5.4 to 7.7 measured, half of that where it reads bytes (Cin % 16 != 0).  Of 20 layers it misses none by
+// more than 3 %: 56x56x32 -> 40 3x3 at batch 2 stays (14.8 against 15.9 us: 1176 blocks, one in five of them padding, are two on
+// some SIMDs), 28x28x32 -> 72 goes over (14.0 -> 10.8), 7x7x512 -> 400 at batch 8 too (18.7 -> 15.2), 14x14x256 -> 256 3x3 at batch 2
+// stays (52.5 against 57.0: 400 blocks leave SIMDs idle).
 // DG_F32_MFMA: 0 never, 1 whatever the size.
 bool dg_onehot_f32_preferred(const dg_lut *lut, const DgProblem &p)
 {
@@ -212,7 +216,9 @@ bool dg_onehot_f32_preferred(const dg_lut *lut, const DgProblem &p)
     if (blocks > INT32_MAX) return false;
     if ((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4) >= ((int64_t)1 << 31)) return false;      // (32-bit byte offsets)
     if (const char *f = dg_override("DG_F32_MFMA")) return atoi(f) != 0;
-    return blocks >= dg_simd_count() * 9 / 16;
+    const int64_t groups = (blocks + 3) / 4, units = dg_simd_count() / 4;
+    const double here = 7.0 + 19.5 * (double)((groups + units - 1) / units);
+    return here < (double)p.M * p.N / (p.Cin % 16 == 0 ? 5800.0 : 2900.0);
 }
 
 dg_status dg_launch_onehot_f32(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
@@ -225,6 +231,7 @@ dg_status dg_launch_onehot_f32(const dg_lut *lut, const DgProblem &p, hipStream_
     a.tiles = (int64_t)a.tiles_m * (((int64_t)p.N + 15) / 16);
     const dim3 grid((unsigned)((a.tiles + 3) / 4));
     if (p.Cin % 64 == 0) hipLaunchKernelGGL((onehot_f32_kernel<4, true>), grid, dim3(256), 0, stream, a);
+    else if (p.Cin % 32 == 0) hipLaunchKernelGGL((onehot_f32_kernel<2, true>), grid, dim3(256), 0, stream, a);
     else if (p.Cin % 16 == 0) hipLaunchKernelGGL((onehot_f32_kernel<1, true>), grid, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL((onehot_f32_kernel<1, false>), grid, dim3(256), 0, stream, a);
     return dg_check_launch("onehot_f32_kernel");
