@@ -728,6 +728,10 @@ bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p)
     const DgProblem n = nibble_problem(p);
     if (!e && dg_sparse4_preferred(lut, p) && !dg_sparse_ws_preferred(two_bit_view(), n) && !sparse_plan(two_bit_view(), sparse_problem(n)).staged)
         return false;
+    // The stationary-weight kernel gives a wavefront one row block for all its pixels, so where the last block is not whole those
+    // wavefronts store element by element throughout and the rest wait for them: 112x112x64 -> 112 at batch 15 (3-bit codes) took
+    // 60.8 us so, 32.9 with the table whole on the dense instruction's tiles, which share their edges out.
+    if (!e && dg_sparse_ws_preferred(two_bit_view(), n) && sparse_problem(n).M % 32 != 0) return false;
     NibbleTable t;
     // (every sum of the split table is a sum of T, whose range the API has checked; partial sums wrap and wrap back)
     return dg_sparse_supports(two_bit_view(), nibble_problem(p)) && nibble_table(lut, sparse_transposes(p), &t);
