@@ -97,7 +97,13 @@ dg_conv_desc geometry(PyObject *o)
     return d;
 }
 
-const dg_lut *table(PyObject *o) { return (const dg_lut *)PyLong_AsVoidPtr(o); }
+// The table's address, as binding.Lut holds it.
+const dg_lut *table(PyObject *o)
+{
+    const size_t address = PyLong_AsSize_t(o);
+    if (address == (size_t)-1 && PyErr_Occurred()) throw Failed();
+    return (const dg_lut *)address;
+}
 
 // Where the result goes: int32, or float32 with a scale or a binary32 table.
 struct Output {
@@ -128,23 +134,28 @@ PyObject *guarded(Py_ssize_t given, Py_ssize_t wanted, Call call)
     }
 }
 
+// The interpreter lock is away while one of these lives.
+struct Unlocked {
+    PyThreadState *const state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// EXPR: the library's call on values that are C's already, nothing of Python's.
 #define RUN(EXPR)            \
-    dg_status status;        \
-    Py_BEGIN_ALLOW_THREADS   \
-    status = EXPR;           \
-    Py_END_ALLOW_THREADS     \
-    return status
+    const Unlocked unlocked; \
+    return EXPR
 
 // (table, is_f32, Wp, Xp, desc, out, scale, variant, stream)
 PyObject *conv2d_lut(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 9, [&] {
+        const dg_lut *lut = table(a[0]);
         const void *w = device_ptr(a[2], at::kByte, "Wp"), *x = device_ptr(a[3], at::kByte, "Xp");
         const dg_conv_desc d = geometry(a[4]);
         const Output o(a[5], a[6], a[1]);
         const dg_kernel variant = (dg_kernel)integer(a[7]);
         void *s = stream_of(a[8]);
-        RUN(dg_conv2d_lut(table(a[0]), w, x, &d, o.i, o.scale, o.f, variant, s));
+        RUN(dg_conv2d_lut(lut, w, x, &d, o.i, o.scale, o.f, variant, s));
     });
 }
 
@@ -152,6 +163,7 @@ PyObject *conv2d_lut(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *conv2d_lut_codes(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 10, [&] {
+        const dg_lut *lut = table(a[0]);
         const void *w = device_ptr(a[2], at::kByte, "Wp");
         const uint8_t *x = (const uint8_t *)device_ptr(a[3], at::kByte, "Xc");
         const dg_conv_desc d = geometry(a[4]);
@@ -159,7 +171,8 @@ PyObject *conv2d_lut_codes(PyObject *, PyObject *const *a, Py_ssize_t n)
         const Output o(a[6], a[7], a[1]);
         const dg_kernel variant = (dg_kernel)integer(a[8]);
         void *s = stream_of(a[9]);
-        RUN(dg_conv2d_lut_codes(table(a[0]), w, x, &d, work, bytes_of(a[5]), o.i, o.scale, o.f, variant, s));
+        const size_t bytes = bytes_of(a[5]);
+        RUN(dg_conv2d_lut_codes(lut, w, x, &d, work, bytes, o.i, o.scale, o.f, variant, s));
     });
 }
 
@@ -167,13 +180,14 @@ PyObject *conv2d_lut_codes(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *conv2d_lut_codes_static(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 9, [&] {
+        const dg_lut *lut = table(a[0]);
         const void *w = device_ptr(a[2], at::kByte, "Wp");
         const uint8_t *x = (const uint8_t *)device_ptr(a[3], at::kByte, "Xc");
         const dg_conv_desc d = geometry(a[4]);
         const Output o(a[5], a[6], a[1]);
         const dg_kernel variant = (dg_kernel)integer(a[7]);
         void *s = stream_of(a[8]);
-        RUN(dg_conv2d_lut_codes_static(table(a[0]), w, x, &d, o.i, o.scale, o.f, variant, s));
+        RUN(dg_conv2d_lut_codes_static(lut, w, x, &d, o.i, o.scale, o.f, variant, s));
     });
 }
 
@@ -181,6 +195,7 @@ PyObject *conv2d_lut_codes_static(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *conv2d_lut_requant(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 11, [&] {
+        const dg_lut *lut = table(a[0]);
         const void *w = device_ptr(a[1], at::kByte, "Wp"), *x = device_ptr(a[2], at::kByte, "Xp");
         const dg_conv_desc d = geometry(a[3]);
         const float *scale = (const float *)device_ptr(a[4], at::kFloat, "scale");
@@ -189,7 +204,8 @@ PyObject *conv2d_lut_requant(PyObject *, PyObject *const *a, Py_ssize_t n)
         void *out = device_ptr(a[8], at::kByte, "packed");
         const dg_kernel variant = (dg_kernel)integer(a[9]);
         void *s = stream_of(a[10]);
-        RUN(dg_conv2d_lut_requant(table(a[0]), w, x, &d, scale, qs, qz, lo, out, bytes_of(a[8]), variant, s));
+        const size_t bytes = bytes_of(a[8]);
+        RUN(dg_conv2d_lut_requant(lut, w, x, &d, scale, qs, qz, lo, out, bytes, variant, s));
     });
 }
 
@@ -197,12 +213,13 @@ PyObject *conv2d_lut_requant(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *gemm_lut(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 13, [&] {
+        const dg_lut *lut = table(a[0]);
         const void *w = device_ptr(a[2], at::kByte, "Wp"), *x = device_ptr(a[3], at::kByte, "Ap");
         const int64_t M = integer(a[4]), N = integer(a[5]), K = integer(a[6]), sm = integer(a[8]), sn = integer(a[9]);
         const Output o(a[7], a[10], a[1]);
         const dg_kernel variant = (dg_kernel)integer(a[11]);
         void *s = stream_of(a[12]);
-        RUN(dg_gemm_lut(table(a[0]), w, x, M, N, K, o.i, sm, sn, o.scale, o.f, variant, s));
+        RUN(dg_gemm_lut(lut, w, x, M, N, K, o.i, sm, sn, o.scale, o.f, variant, s));
     });
 }
 
@@ -210,6 +227,7 @@ PyObject *gemm_lut(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *gemm_lut_codes(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 14, [&] {
+        const dg_lut *lut = table(a[0]);
         const void *w = device_ptr(a[2], at::kByte, "Wp");
         const uint8_t *x = (const uint8_t *)device_ptr(a[3], at::kByte, "Ac");
         const int64_t M = integer(a[4]), N = integer(a[5]), K = integer(a[6]), sm = integer(a[9]), sn = integer(a[10]);
@@ -217,7 +235,8 @@ PyObject *gemm_lut_codes(PyObject *, PyObject *const *a, Py_ssize_t n)
         const Output o(a[8], a[11], a[1]);
         const dg_kernel variant = (dg_kernel)integer(a[12]);
         void *s = stream_of(a[13]);
-        RUN(dg_gemm_lut_codes(table(a[0]), w, x, M, N, K, work, bytes_of(a[7]), o.i, sm, sn, o.scale, o.f, variant, s));
+        const size_t bytes = bytes_of(a[7]);
+        RUN(dg_gemm_lut_codes(lut, w, x, M, N, K, work, bytes, o.i, sm, sn, o.scale, o.f, variant, s));
     });
 }
 
@@ -230,7 +249,8 @@ PyObject *pack_codes_bits(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int32_t bits = (int32_t)integer(a[3]);
         void *out = device_ptr(a[4], at::kByte, "packed");
         void *s = stream_of(a[5]);
-        RUN(dg_pack_codes_bits(codes, rows, K, bits, out, bytes_of(a[4]), s));
+        const size_t bytes = bytes_of(a[4]);
+        RUN(dg_pack_codes_bits(codes, rows, K, bits, out, bytes, s));
     });
 }
 
@@ -243,7 +263,8 @@ PyObject *pack(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t rows = integer(a[1]), K = integer(a[2]);
         void *out = device_ptr(a[3], at::kByte, "packed");
         void *s = stream_of(a[4]);
-        RUN(FN(codes, rows, K, out, bytes_of(a[3]), s));
+        const size_t bytes = bytes_of(a[3]);
+        RUN(FN(codes, rows, K, out, bytes, s));
     });
 }
 
@@ -257,7 +278,8 @@ PyObject *quantize_pack_activations(PyObject *, PyObject *const *a, Py_ssize_t n
         const int32_t lo = (int32_t)integer(a[5]);
         void *out = device_ptr(a[6], at::kByte, "packed");
         void *s = stream_of(a[7]);
-        RUN(dg_quantize_pack_activations(x, N, K, scale, zero, lo, out, bytes_of(a[6]), s));
+        const size_t bytes = bytes_of(a[6]);
+        RUN(dg_quantize_pack_activations(x, N, K, scale, zero, lo, out, bytes, s));
     });
 }
 

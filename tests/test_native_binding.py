@@ -57,6 +57,34 @@ def test_native_checks():
         dg.dg_pack_activations([1, 2], 4, 16, out=host)
 
 
+BAD_TABLES = """
+from paper_2304_09049_amd import binding as dg
+native = dg._load_native()
+class Stream:
+    cuda_stream = 0
+for table, error in ((-1, OverflowError), (1 << 70, OverflowError), ("table", TypeError), (None, TypeError)):
+    for call in (lambda: native.gemm_lut(table, False, None, None, 1, 1, 16, None, 1, 1, None, 0, Stream),
+                 lambda: native.gemm_lut_codes(table, False, None, None, 1, 1, 16, None, None, 1, 1, None, 0, Stream),
+                 lambda: native.conv2d_lut(table, False, None, None, dg.conv_desc(1, 2, 2, 16, 4, 1, 1), None, None, 0, Stream),
+                 lambda: native.conv2d_lut_codes(table, False, None, None, dg.conv_desc(1, 2, 2, 16, 4, 1, 1), None, None, None, 0, Stream),
+                 lambda: native.conv2d_lut_codes_static(table, False, None, None, dg.conv_desc(1, 2, 2, 16, 4, 1, 1), None, None, 0, Stream),
+                 lambda: native.conv2d_lut_requant(table, None, None, dg.conv_desc(1, 2, 2, 16, 4, 1, 1), None, 1.0, 0.0, 0, None, 0, Stream)):
+        try:
+            call()
+        except error:
+            continue
+        raise SystemExit(f"{table!r} was taken for a table")
+print("refused")
+"""
+
+
+def test_bad_table_addresses_raise():
+    """A table that is no address is refused while the interpreter lock is held (in a process of its own: it ended there)."""
+    out = subprocess.run([sys.executable, "-c", BAD_TABLES], capture_output=True, text=True,
+                         cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert out.returncode == 0 and out.stdout == "refused\n", (out.returncode, out.stderr[-2000:])
+
+
 @pytest.mark.gpu
 def test_native_checks_on_device_tensors():
     codes = torch.zeros(64, dtype=torch.uint8, device="cuda")
