@@ -738,7 +738,10 @@ dg_status dg_conv2d_lut_requant(const dg_lut *lut, const void *Wp_dev, const voi
     p.q_zero = q_zero;
     p.q_lo = lo;
     // the re-quantising epilogue lives in the one-hot matrix-core kernels (both instruction forms share it)
-    if (variant == DG_KERNEL_AUTO && dg_nibble_preferred(lut, p)) return dg_launch_nibble(lut, p, (hipStream_t)hip_stream);
+    // (tables that split into two lookups, where the kernel named in the error below takes the table whole as well: not
+    // entries beyond int8, whose halves may fit, nor operands aligned for the halves alone)
+    if (variant == DG_KERNEL_AUTO && dg_onehot_supports(lut, p) && dg_nibble_preferred(lut, p))
+        return dg_launch_nibble(lut, p, (hipStream_t)hip_stream);
     if ((variant == DG_KERNEL_ONEHOT_SMFMAC || variant == DG_KERNEL_AUTO) && dg_sparse_ws_preferred(lut, p))
         return dg_launch_sparse_ws(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_ONEHOT_SMFMAC && lut->bits == 2 && dg_sparse_supports(lut, p))

@@ -262,6 +262,22 @@ def test_kernel_names_need_no_gpu():
     assert dg.dg_gemm_codes_kernel_name(lut, 8192, 8192, 8192) == "onehot_smfmac_staged_64x128"
 
 
+def test_requant_refuses_what_the_onehot_kernel_refuses():
+    """The fused layer with 3- and 4-bit tables: entries beyond int8 are refused also where the table is the sum of two 2-bit
+    lookups whose entries fit, and operands that are not aligned for the one-hot kernel also where the lookups' kernels would
+    take them.  (Nothing is launched: the addresses are made up.)"""
+    L = dg.lib()
+    at = ctypes.c_void_p
+    for bits, lw, la, wp, xp in ((4, range(-8, 8), range(0, 32, 2), 0x1000, 0x2000), (3, range(-40, 40, 10), range(8), 0x1000, 0x2000),
+                                 (3, range(-4, 4), range(8), 0x1008, 0x2000), (3, range(-4, 4), range(8), 0x1000, 0x2008)):
+        lut = dg.dg_build_lut_bits(bits, list(lw), list(la), dg.DG_LUT_I16)
+        for cin, k in ((64, 3), (128, 1)):
+            desc = dg.conv_desc(8, 28, 28, cin, 128, k, k, (1, 1), (k // 2, k // 2))
+            status = L.dg_conv2d_lut_requant(lut.handle, at(wp), at(xp), ctypes.byref(desc), at(0x3000), 1.0, 0.0, 0, at(0x4000),
+                                             8 * 28 * 28 * 32, dg.DG_KERNEL_AUTO, None)
+            assert status == 5, (bits, list(la), cin, status, L.dg_last_error())
+
+
 def test_dequantize_argument_errors():
     L = dg.lib()
     fake = ctypes.c_void_p(0x1000)
