@@ -125,6 +125,7 @@ def _load_native():
     if not os.path.exists(NATIVE_PATH):
         raise ImportError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2304_09049_amd.build`.")
     from . import _native as module
+    module.use_desc(ConvDesc)
     _native = module
     return module
 
@@ -287,7 +288,7 @@ def dg_gemm_lut(lut: Lut, Wp, Ap, M: int, N: int, K: int, out=None, scale=None, 
     if out is None:
         out = _empty((M, N), lut, scale, Wp.device)
     scm, scn = (N, 1) if strides is None else strides
-    status = (_native or _load_native()).gemm_lut(lut._address, lut.is_f32, Wp, Ap, M, N, K, out, scm, scn, scale,
+    status = (_native or _load_native()).gemm_lut(lut, lut.is_f32, Wp, Ap, M, N, K, out, scm, scn, scale,
                                                   _kernel(variant), stream)
     if status:
         _check(status)
@@ -301,7 +302,7 @@ def dg_gemm_lut_codes(lut: Lut, Wp, Ac, M: int, N: int, K: int, work=None, out=N
     if out is None:
         out = _empty((M, N), lut, scale, Wp.device)
     scm, scn = (N, 1) if strides is None else strides
-    status = (_native or _load_native()).gemm_lut_codes(lut._address, lut.is_f32, Wp, Ac, M, N, K, work, out, scm, scn, scale,
+    status = (_native or _load_native()).gemm_lut_codes(lut, lut.is_f32, Wp, Ac, M, N, K, work, out, scm, scn, scale,
                                                         _kernel(variant), stream)
     if status:
         _check(status)
@@ -326,7 +327,7 @@ def dg_conv2d_lut(lut: Lut, Wp, Xp, desc: ConvDesc, out=None, scale=None, varian
     """NHWC convolution by table lookup.  Returns [B][OH][OW][Cout], int32 or float32 (when `scale` is given)."""
     if out is None:
         out = _empty(_conv_shape(desc), lut, scale, Wp.device)
-    status = (_native or _load_native()).conv2d_lut(lut._address, lut.is_f32, Wp, Xp, desc, out, scale, _kernel(variant), stream)
+    status = (_native or _load_native()).conv2d_lut(lut, lut.is_f32, Wp, Xp, desc, out, scale, _kernel(variant), stream)
     if status:
         _check(status)
     return out
@@ -337,7 +338,7 @@ def dg_conv2d_lut_codes(lut: Lut, Wp, Xc, desc: ConvDesc, work=None, out=None, s
     the packed-activation buffer the library uses when it does not fuse the packing into the kernel (may be None)."""
     if out is None:
         out = _empty(_conv_shape(desc), lut, scale, Wp.device)
-    status = (_native or _load_native()).conv2d_lut_codes(lut._address, lut.is_f32, Wp, Xc, desc, work, out, scale,
+    status = (_native or _load_native()).conv2d_lut_codes(lut, lut.is_f32, Wp, Xc, desc, work, out, scale,
                                                           _kernel(variant), stream)
     if status:
         _check(status)
@@ -350,7 +351,7 @@ def dg_static_work_bytes() -> int:
 
 def dg_conv2d_lut_codes_static(lut: Lut, Wp, Xc, desc: ConvDesc, out, scale=None, variant="auto", stream=None):
     """dg_conv2d_lut_codes with the library's own staging buffer; `out` is required (the call allocates nothing)."""
-    status = (_native or _load_native()).conv2d_lut_codes_static(lut._address, lut.is_f32, Wp, Xc, desc, out, scale,
+    status = (_native or _load_native()).conv2d_lut_codes_static(lut, lut.is_f32, Wp, Xc, desc, out, scale,
                                                                  _kernel(variant), stream)
     if status:
         _check(status)
@@ -392,7 +393,7 @@ def dg_conv2d_lut_requant(lut: Lut, Wp, Xp, desc: ConvDesc, scale, q_scale: floa
         import torch
         B, OH, OW, Cout = _conv_shape(desc)
         out = torch.empty(dg_packed_activation_bytes(B * OH * OW, Cout), dtype=torch.uint8, device=Wp.device)
-    status = (_native or _load_native()).conv2d_lut_requant(lut._address, Wp, Xp, desc, scale, q_scale, q_zero, lo, out,
+    status = (_native or _load_native()).conv2d_lut_requant(lut, Wp, Xp, desc, scale, q_scale, q_zero, lo, out,
                                                             _kernel(variant), stream)
     if status:
         _check(status)

@@ -21,17 +21,63 @@ namespace {
 
 PyObject *g_raw_stream = nullptr;        // torch._C._cuda_getCurrentRawStream
 PyObject *g_stream_attr = nullptr;       // "cuda_stream"
+PyObject *g_address_attr = nullptr;      // "_address"
+PyTypeObject *g_desc_type = nullptr;     // binding.ConvDesc, from use_desc
 
 struct Failed {};                        // a Python error is set
+
+// One attribute of `o`, or of what it returns when called without arguments; a new reference.
+PyObject *attribute(PyObject *o, const char *name, bool call)
+{
+    PyObject *v = call ? PyObject_CallMethod(o, name, nullptr) : PyObject_GetAttrString(o, name);
+    if (!v) throw Failed();
+    return v;
+}
+
+bool is_true(PyObject *o)
+{
+    const int v = PyObject_IsTrue(o);
+    if (v < 0) throw Failed();
+    return v != 0;
+}
+
+// The same for an object that is no torch.Tensor but answers as one (is_cuda, is_contiguous(), dtype, data_ptr()).
+void *stand_in_ptr(PyObject *o, at::ScalarType type, const char *name)
+{
+    if (!PyObject_HasAttrString(o, "is_cuda")) {
+        PyErr_Format(PyExc_TypeError, "%s must be a tensor", name);
+        throw Failed();
+    }
+    const char *wrong = nullptr;
+    PyObject *v = attribute(o, "is_cuda", false);
+    if (!is_true(v)) wrong = "live in device memory";
+    Py_DECREF(v);
+    if (!wrong) {
+        v = attribute(o, "is_contiguous", true);
+        if (!is_true(v)) wrong = "be contiguous";
+        Py_DECREF(v);
+    }
+    if (wrong) {
+        PyErr_Format(PyExc_ValueError, "%s must %s", name, wrong);
+        throw Failed();
+    }
+    v = attribute(o, "dtype", false);
+    const int same = PyObject_RichCompareBool(v, (PyObject *)torch::getTHPDtype(type), Py_EQ);
+    if (same == 0) PyErr_Format(PyExc_ValueError, "%s must have dtype %S, got %S", name, (PyObject *)torch::getTHPDtype(type), v);
+    Py_DECREF(v);
+    if (same != 1) throw Failed();
+    v = attribute(o, "data_ptr", true);
+    void *ptr = PyLong_AsVoidPtr(v);
+    Py_DECREF(v);
+    if (!ptr && PyErr_Occurred()) throw Failed();
+    return ptr;
+}
 
 // The tensor's address; NULL for None.
 void *device_ptr(PyObject *o, at::ScalarType type, const char *name)
 {
     if (o == Py_None) return nullptr;
-    if (!THPVariable_Check(o)) {
-        PyErr_Format(PyExc_TypeError, "%s must be a tensor", name);
-        throw Failed();
-    }
+    if (!THPVariable_Check(o)) return stand_in_ptr(o, type, name);
     const at::Tensor &t = THPVariable_Unpack(o);
     const char *wrong = !t.is_cuda() ? "live in device memory" : (!t.is_contiguous() ? "be contiguous" : nullptr);
     if (wrong) {
@@ -46,13 +92,23 @@ void *device_ptr(PyObject *o, at::ScalarType type, const char *name)
     return t.data_ptr();
 }
 
-size_t bytes_of(PyObject *o) { return o == Py_None ? 0 : (size_t)THPVariable_Unpack(o).numel(); }
-
 int64_t integer(PyObject *o)
 {
     const int64_t v = PyLong_AsLongLong(o);
     if (v == -1 && PyErr_Occurred()) throw Failed();
     return v;
+}
+
+// Bytes of a buffer that device_ptr has checked.
+size_t bytes_of(PyObject *o)
+{
+    if (o == Py_None) return 0;
+    if (THPVariable_Check(o)) return (size_t)THPVariable_Unpack(o).numel();
+    PyObject *v = attribute(o, "numel", true);
+    const size_t n = PyLong_AsSize_t(v);
+    Py_DECREF(v);
+    if (n == (size_t)-1 && PyErr_Occurred()) throw Failed();
+    return n;
 }
 
 double real(PyObject *o)
@@ -84,10 +140,14 @@ void *stream_of(PyObject *o)
 // The convolution's geometry out of a binding.ConvDesc (a ctypes structure lends its memory as a buffer).
 dg_conv_desc geometry(PyObject *o)
 {
+    if (!g_desc_type || !PyObject_TypeCheck(o, g_desc_type)) {
+        PyErr_SetString(PyExc_TypeError, "desc must be a ConvDesc");
+        throw Failed();
+    }
     Py_buffer view;
     if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw Failed();
     dg_conv_desc d;
-    const bool fits = view.len == (Py_ssize_t)sizeof(d);
+    const bool fits = view.len >= (Py_ssize_t)sizeof(d);
     if (fits) memcpy(&d, view.buf, sizeof(d));
     PyBuffer_Release(&view);
     if (!fits) {
@@ -97,12 +157,36 @@ dg_conv_desc geometry(PyObject *o)
     return d;
 }
 
-// The table's address, as binding.Lut holds it.
+// The table's address: a number, or a binding.Lut's, or the handle of another object that owns a table (a number or a ctypes
+// pointer, whose value is None where it is NULL).
 const dg_lut *table(PyObject *o)
 {
-    const size_t address = PyLong_AsSize_t(o);
-    if (address == (size_t)-1 && PyErr_Occurred()) throw Failed();
-    return (const dg_lut *)address;
+    PyObject *address = nullptr;
+    if (PyLong_Check(o)) {
+        Py_INCREF(o);
+        address = o;
+    } else if (PyObject *own = PyObject_GetAttr(o, g_address_attr)) {
+        address = own;
+    } else {
+        if (!PyErr_ExceptionMatches(PyExc_AttributeError)) throw Failed();
+        PyErr_Clear();
+        PyObject *handle = PyObject_GetAttrString(o, "handle");
+        if (!handle) {
+            PyErr_Format(PyExc_TypeError, "lut must be a table, got %.100s", Py_TYPE(o)->tp_name);
+            throw Failed();
+        }
+        if (PyLong_Check(handle) || handle == Py_None) {
+            address = handle;
+        } else {
+            address = PyObject_GetAttrString(handle, "value");
+            Py_DECREF(handle);
+            if (!address) throw Failed();
+        }
+    }
+    const size_t value = address == Py_None ? 0 : PyLong_AsSize_t(address);
+    Py_DECREF(address);
+    if (value == (size_t)-1 && PyErr_Occurred()) throw Failed();
+    return (const dg_lut *)value;
 }
 
 // Where the result goes: int32, or float32 with a scale or a binary32 table.
@@ -112,7 +196,7 @@ struct Output {
     const float *scale = nullptr;
     Output(PyObject *out, PyObject *scale_o, PyObject *is_f32)
     {
-        if (scale_o != Py_None || is_f32 == Py_True)
+        if (scale_o != Py_None || is_true(is_f32))
             f = (float *)device_ptr(out, at::kFloat, "out");
         else
             i = (int32_t *)device_ptr(out, at::kInt, "out");
@@ -145,7 +229,7 @@ struct Unlocked {
     const Unlocked unlocked; \
     return EXPR
 
-// (table, is_f32, Wp, Xp, desc, out, scale, variant, stream)
+// (lut, is_f32, Wp, Xp, desc, out, scale, variant, stream)
 PyObject *conv2d_lut(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 9, [&] {
@@ -159,7 +243,7 @@ PyObject *conv2d_lut(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// (table, is_f32, Wp, Xc, desc, work, out, scale, variant, stream)
+// (lut, is_f32, Wp, Xc, desc, work, out, scale, variant, stream)
 PyObject *conv2d_lut_codes(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 10, [&] {
@@ -176,7 +260,7 @@ PyObject *conv2d_lut_codes(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// (table, is_f32, Wp, Xc, desc, out, scale, variant, stream)
+// (lut, is_f32, Wp, Xc, desc, out, scale, variant, stream)
 PyObject *conv2d_lut_codes_static(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 9, [&] {
@@ -191,7 +275,7 @@ PyObject *conv2d_lut_codes_static(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// (table, Wp, Xp, desc, scale, q_scale, q_zero, lo, out, variant, stream)
+// (lut, Wp, Xp, desc, scale, q_scale, q_zero, lo, out, variant, stream)
 PyObject *conv2d_lut_requant(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 11, [&] {
@@ -209,7 +293,7 @@ PyObject *conv2d_lut_requant(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// (table, is_f32, Wp, Ap, M, N, K, out, stride_m, stride_n, scale, variant, stream)
+// (lut, is_f32, Wp, Ap, M, N, K, out, stride_m, stride_n, scale, variant, stream)
 PyObject *gemm_lut(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 13, [&] {
@@ -223,7 +307,7 @@ PyObject *gemm_lut(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// (table, is_f32, Wp, Ac, M, N, K, work, out, stride_m, stride_n, scale, variant, stream)
+// (lut, is_f32, Wp, Ac, M, N, K, work, out, stride_m, stride_n, scale, variant, stream)
 PyObject *gemm_lut_codes(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 14, [&] {
@@ -296,6 +380,21 @@ PyObject *dequantize(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
+// (type): binding.ConvDesc, whose instances alone are taken for a geometry
+PyObject *use_desc(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 1, [&] {
+        if (!PyType_Check(a[0])) {
+            PyErr_SetString(PyExc_TypeError, "a type is needed");
+            throw Failed();
+        }
+        Py_INCREF(a[0]);
+        Py_XDECREF((PyObject *)g_desc_type);
+        g_desc_type = (PyTypeObject *)a[0];
+        return 0;
+    });
+}
+
 #define METHOD(NAME, FN) {NAME, (PyCFunction)(void (*)(void))(FN), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
     METHOD("conv2d_lut", conv2d_lut), METHOD("conv2d_lut_codes", conv2d_lut_codes),
@@ -303,6 +402,7 @@ PyMethodDef methods[] = {
     METHOD("gemm_lut", gemm_lut), METHOD("gemm_lut_codes", gemm_lut_codes), METHOD("pack_codes_bits", pack_codes_bits),
     METHOD("pack_weights", pack<dg_pack_weights>), METHOD("pack_activations", pack<dg_pack_activations>),
     METHOD("quantize_pack_activations", quantize_pack_activations), METHOD("dequantize", dequantize),
+    METHOD("use_desc", use_desc),
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_native", "Tensors in, the C ABI's status out.", -1, methods,
                           nullptr, nullptr, nullptr, nullptr};
@@ -316,6 +416,7 @@ PyMODINIT_FUNC PyInit__native()
     g_raw_stream = PyObject_GetAttrString(torch_c, "_cuda_getCurrentRawStream");
     Py_DECREF(torch_c);
     g_stream_attr = PyUnicode_InternFromString("cuda_stream");
-    if (!g_raw_stream || !g_stream_attr) return nullptr;
+    g_address_attr = PyUnicode_InternFromString("_address");
+    if (!g_raw_stream || !g_stream_attr || !g_address_attr) return nullptr;
     return PyModule_Create(&module_def);
 }

@@ -3,6 +3,7 @@ import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 import torch
 
@@ -83,6 +84,78 @@ def test_bad_table_addresses_raise():
     out = subprocess.run([sys.executable, "-c", BAD_TABLES], capture_output=True, text=True,
                          cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     assert out.returncode == 0 and out.stdout == "refused\n", (out.returncode, out.stderr[-2000:])
+
+
+class StandIn:
+    """No tensor, but it answers as a contiguous one on the GPU does.  (Its address is made up: nothing is launched.)"""
+
+    def __init__(self, dtype=torch.uint8, count=1 << 20, is_cuda=True, contiguous=True):
+        self.dtype, self.count, self.is_cuda, self.contiguous, self.device = dtype, count, is_cuda, contiguous, None
+
+    def is_contiguous(self):
+        return self.contiguous
+
+    def data_ptr(self):
+        return 0x1000
+
+    def numel(self):
+        return self.count
+
+
+class Stream:
+    cuda_stream = 0
+
+
+def _refused(call, status):
+    with pytest.raises(dg.DgError) as e:
+        call()
+    assert e.value.status == status
+
+
+def test_objects_that_answer_as_tensors_and_tables():
+    """Operands, tables and flags of other types than torch's and this package's own reach the library (which refuses these
+    calls by their shape, 2, or their buffer's size, 4)."""
+    x, f, i = StandIn(), StandIn(torch.float32), StandIn(torch.int32)
+    lut = dg.dg_build_lut((-2, -1, 0, 1), (0, 1, 2, 3))
+    desc = dg.conv_desc(1, 2, 2, 15, 4, 1, 1)
+    _refused(lambda: dg.dg_pack_activations(x, 4, 15, out=x, stream=Stream), 2)
+    _refused(lambda: dg.dg_pack_weights(x, 4, 16, out=StandIn(count=15), stream=Stream), 4)
+    _refused(lambda: dg.dg_pack_codes_bits(x, 4, 16, 3, out=StandIn(count=31), stream=Stream), 4)
+    _refused(lambda: dg.dg_quantize_pack_activations(f, 4, 16, 1.0, 0.0, 0, out=StandIn(count=15), stream=Stream), 4)
+    _refused(lambda: dg.dg_dequantize(i, 0, 4, f, out=f, stream=Stream), 2)
+
+    class Table:
+        is_f32 = False
+
+        def __init__(self, handle):
+            self.handle = handle
+
+    for table in (lut, Table(lut.handle), Table(lut.handle.value)):
+        _refused(lambda: dg.dg_gemm_lut(table, x, x, 4, 4, 15, out=i, stream=Stream), 2)
+        _refused(lambda: dg.dg_gemm_lut_codes(table, x, x, 4, 4, 15, work=x, out=i, stream=Stream), 2)
+        _refused(lambda: dg.dg_conv2d_lut(table, x, x, desc, out=f, scale=f, stream=Stream), 2)
+        _refused(lambda: dg.dg_conv2d_lut_codes(table, x, x, desc, work=x, out=i, stream=Stream), 2)
+        _refused(lambda: dg.dg_conv2d_lut_codes_static(table, x, x, dg.conv_desc(64, 1024, 1024, 16, 4, 1, 1), i, stream=Stream), 4)
+        _refused(lambda: dg.dg_conv2d_lut_requant(table, x, x, desc, f, 1.0, 0.0, 0, out=x, stream=Stream), 2)
+    _refused(lambda: dg.dg_gemm_lut(Table(None), x, x, 4, 4, 16, out=i, stream=Stream), 1)
+    binary32 = dg.Lut((-1.0, 0.5, 1.0, 2.0), (0.0, 1.0, 2.0, 3.0), entry=np.int64(dg.DG_LUT_F32))       # (its is_f32: numpy's True)
+    _refused(lambda: dg.dg_gemm_lut(binary32, x, x, 4, 4, 15, out=f, stream=Stream), 2)
+    with pytest.raises(ValueError, match="out must have dtype torch.float32, got torch.int32"):
+        dg.dg_gemm_lut(binary32, x, x, 4, 4, 15, out=i, stream=Stream)
+    for bad, match in ((StandIn(is_cuda=False), "live in device memory"), (StandIn(contiguous=False), "be contiguous"), (f, "have dtype")):
+        with pytest.raises(ValueError, match="codes must " + match):
+            dg.dg_pack_activations(bad, 4, 16, out=x, stream=Stream)
+    for no_table in ("table", object()):
+        with pytest.raises((TypeError, AttributeError)):
+            dg.dg_gemm_lut(no_table, x, x, 4, 4, 15, out=i, stream=Stream)
+
+    class Wider(dg.ConvDesc):
+        pass
+
+    _refused(lambda: dg.dg_conv2d_lut(lut, x, x, Wider(1, 2, 2, 15, 4, 1, 1, 1, 1, 0, 0), out=i, stream=Stream), 2)
+    for no_desc in (bytes(desc), bytearray(desc), np.zeros(11, np.int32), (1, 2, 2, 15, 4, 1, 1, 1, 1, 0, 0)):
+        with pytest.raises(TypeError, match="ConvDesc"):
+            dg.dg_conv2d_lut(lut, x, x, no_desc, out=i, stream=Stream)
 
 
 @pytest.mark.gpu
