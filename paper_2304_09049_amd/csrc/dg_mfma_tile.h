@@ -69,7 +69,18 @@ __device__ __forceinline__ void dg_mfma_requant_block(const DgProblem &p, const 
     }
 }
 
-template <bool TR>
+// Whether a block's rows all lie inside the output and its 32 x 32 footprint spans less than 2^30 elements (strides may be
+// negative): what the stores without a test per element need, besides the columns.
+__device__ __forceinline__ bool dg_mfma_rows_whole(int64_t row_stride, int64_t col_stride, int rowb, int row_limit)
+{
+    const int64_t span = 32 * ((row_stride < 0 ? -row_stride : row_stride) + (col_stride < 0 ? -col_stride : col_stride));
+    return rowb + 32 <= row_limit && span < ((int64_t)1 << 30);
+}
+
+// EDGE_COLUMNS: blocks whose columns are not all inside take the stores without a test per element too, the lanes of columns
+// beyond the last sitting them out (for kernels whose wavefronts keep one column block and would test every element of it
+// throughout, dg_sparse_ws_kernel.h).
+template <bool TR, bool EDGE_COLUMNS = false>
 __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg_v16i &acc, int mb, int nb, int lane,
                                                     float sc)
 {
@@ -82,12 +93,11 @@ __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg
     const int colb = __builtin_amdgcn_readfirstlane(TR ? mb : nb), rowb = __builtin_amdgcn_readfirstlane(TR ? nb : mb);
     const int col_limit = TR ? p.M : p.N, row_limit = TR ? p.N : p.M;
     const int64_t row_stride = TR ? p.stride_cn : p.stride_cm, col_stride = TR ? p.stride_cm : p.stride_cn;
-    // A block wholly inside the output whose 32 x 32 footprint spans less than 2^30 elements (strides may be negative):
-    // one uniform base address, a 32-bit offset per lane, then steps of the row stride -- no bounds test and no 64-bit
-    // arithmetic per element.  The stores are streaming (non-temporal) stores: the output is written once and read by
-    // a later kernel, it has no business in this one's caches.
-    const int64_t span = 32 * ((row_stride < 0 ? -row_stride : row_stride) + (col_stride < 0 ? -col_stride : col_stride));
-    if (colb + 32 <= col_limit && rowb + 32 <= row_limit && span < ((int64_t)1 << 30)) {
+    // A block wholly inside the output: one uniform base address, a 32-bit offset per lane, then steps of the row stride
+    // -- no bounds test and no 64-bit arithmetic per element.  The stores are streaming (non-temporal) stores: the output
+    // is written once and read by a later kernel, it has no business in this one's caches.
+    if ((EDGE_COLUMNS || colb + 32 <= col_limit) && dg_mfma_rows_whole(row_stride, col_stride, rowb, row_limit)) {
+        if (EDGE_COLUMNS && colb + r >= col_limit) return;
         const int64_t base = (int64_t)colb * col_stride + (int64_t)rowb * row_stride;
         const int rs = (int)row_stride, off0 = r * (int)col_stride + 4 * h * rs;
         if (p.scale) {

@@ -60,6 +60,12 @@ struct WsArgs {
 // behind two blocks of codes), the second block only after the dense operands are built (the address unit serves
 // every wavefront's first block first), and a wait for staged codes does not wait for the stores issued since: the
 // wavefront counts them (9.5 -> 8.9 us on that layer; the same at batch 8: 5.2 -> 4.7 us).
+// A wavefront keeps its 32 channels for all its pixel blocks, so where the last of them lie beyond M it would store element
+// by element throughout, and the others wait for it: its lanes of such channels sit the stores out instead
+// (dg_mfma_store_block, EDGE_COLUMNS).  Packed codes, graph replays, before -> after: 56x56x128 -> 100 at batch 16 14.1 -> 7.5 us
+// (the tiled kernels 11.7 - 13.4), 112x112x64 -> 112 at batch 15 25.9 -> 21.6 (20.5 - 27.4), 28x28x256 -> 1000 at batch 8 15.3 ->
+// 10.8, 56x56x256 -> 72 at batch 8 8.7 -> 5.9; the one-call steps of these four 15.6 -> 9.0, 32.9 -> 23.2, 12.9 -> 11.6, 9.0 -> 7.0;
+// layers of whole blocks the same (56x56x256 -> 64 at batch 8 5.26, 5.30).
 // STRIDED (packed activations): a 1x1 convolution with a stride and no padding -- output pixel (b, oh, ow) reads the
 // row of input pixel (b, oh * sh, ow * sw).
 // NIB: 3- and 4-bit codes as two 2-bit ones each (dg_onehot_kernel.h, BITS = 24); K counts the 2-bit codes.
@@ -196,13 +202,11 @@ smfmac_ws_kernel(WsArgs a)
         // next are issued as soon as the buffer's codes are in registers, ahead of this block's stores.
         // Waiting for a block's loads: the counter counts stores as well, and everything completes in issue order.
         // Issued after block blk's loads were: the stores of block blk - 2, the loads of block blk + 1, the stores of
-        // block blk - 1 -- all of which may still be under way.  The stores of a block wholly inside the output are 16
-        // instructions (dg_mfma_store_block: one per sum register); of any other block they count as none here, which
-        // only waits longer.
+        // block blk - 1 -- all of which may still be under way.  The stores of a block whose pixels all lie inside the output
+        // are 16 instructions (dg_mfma_store_block: one per sum register; some of its channels always do); of any other
+        // block they count as none here, which only waits longer.
         auto stores_of = [&](int64_t blk) -> int {
-            const int64_t span = 32 * ((p.stride_cn < 0 ? -p.stride_cn : p.stride_cn) + (p.stride_cm < 0 ? -p.stride_cm : p.stride_cm));
-            const bool whole = m0 + 32 <= p.M && (blk + 1) * 32 <= (int64_t)p.N && span < ((int64_t)1 << 30);
-            return a.count_stores && p.Qp == nullptr && whole ? 16 : 0;
+            return a.count_stores && p.Qp == nullptr && dg_mfma_rows_whole(p.stride_cn, p.stride_cm, (int)(blk * 32), p.N) ? 16 : 0;
         };
         int stores1 = 0, stores2 = 0;                       // of the last block, of the one before
         // (the body twice, with and without the loads of the block after next, so that each is straight-line code: the
@@ -232,7 +236,7 @@ smfmac_ws_kernel(WsArgs a)
 #pragma unroll
                 for (int par = 0; par < 2; ++par)
                     acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones[par], dn[t][par], acc, (int)xw.v[t], 0, 0);
-            dg_mfma_store_block<true>(p, acc, m0, (int)(blk * 32), lane, sc_cols[0]);
+            dg_mfma_store_block<true, true>(p, acc, m0, (int)(blk * 32), lane, sc_cols[0]);
             stores2 = stores1, stores1 = stores_of(blk);
         };
         int64_t blk = b0;
@@ -255,7 +259,7 @@ smfmac_ws_kernel(WsArgs a)
 #pragma unroll
                 for (int par = 0; par < 2; ++par)
                     acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones[par], dn[t][par], acc, (int)x[g].v[t], 0, 0);
-            dg_mfma_store_block<true>(p, acc, m0, (int)((blk + g) * 32), lane, sc_cols[0]);
+            dg_mfma_store_block<true, true>(p, acc, m0, (int)((blk + g) * 32), lane, sc_cols[0]);
         }
         // (only a run longer than one group comes here; these loads do queue behind the group's stores, which is why
         // the host sizes runs to one group where it can)

@@ -1180,3 +1180,33 @@ def test_few_columns_sparse_kernel(K, waves, monkeypatch):
     # K must be whole super-steps of 256 positions
     inp = wl.small_gemm(64, 4, 320, seed=2)
     assert GpuCase(inp, levels=(lw, la), entry=entry).kernel_name("onehot_smfmac") != "onehot_smfmac_fewn_16"
+
+
+@pytest.mark.parametrize("waves", [0, 5])
+@pytest.mark.parametrize("K", [64, 256, 512])
+def test_stationary_weight_kernel_partial_channel_blocks(K, waves, monkeypatch):
+    """A last block of 1, 8, 12, 31 or all of its 32 channels, in one row block and in several: the lanes of channels that do
+    not exist store nothing (the gap behind each pixel's channels keeps what it held), packed and from codes, int32 and scaled."""
+    monkeypatch.setenv("DG_ONEHOT_PLAN", "ws")
+    if waves:
+        monkeypatch.setenv("DG_WS_WAVES", str(waves))
+    lw, la, entry = LEVELS["nonuniform_i8"]
+    for (M, N, gap) in [(1, 70, 3), (8, 333, 60), (44, 1000, 1), (63, 257, 40), (97, 96, 33), (64, 100, 7)]:
+        inp = wl.small_gemm(M, N, K, seed=M + N + K)
+        case = GpuCase(inp, levels=(lw, la), entry=entry)
+        assert case.kernel_name("onehot_smfmac") == "onehot_smfmac_ws_32xK"
+        want = oracle.gemm(inp.Wc, inp.Ac, lw, la).T
+        scale = np.random.default_rng(M).uniform(0.01, 0.1, M).astype(np.float32)
+        codes, work = torch.from_numpy(inp.Ac).cuda(), torch.empty_like(case.Ap)
+        for s, w in ((None, want), (torch.from_numpy(scale).cuda(), want.astype(np.float32) * scale[None, :])):
+            for raw in (False, True):
+                out = torch.full((N, M + gap), -7, dtype=torch.int32 if s is None else torch.float32, device="cuda")
+                kw = dict(out=out, scale=s, variant="onehot_smfmac", strides=(1, M + gap))
+                if raw:
+                    dg.dg_gemm_lut_codes(case.lut, case.Wp, codes, M, N, K, work=work, **kw)
+                else:
+                    dg.dg_gemm_lut(case.lut, case.Wp, case.Ap, M, N, K, **kw)
+                torch.cuda.synchronize()
+                got = out.cpu().numpy()
+                _assert_same(got[:, :M].copy(), w, f"{(M, N, K)} {'codes' if raw else 'packed'}")
+                assert (got[:, M:] == -7).all(), f"{(M, N, K)}: stored beyond the last channel"
