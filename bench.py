@@ -391,9 +391,12 @@ def wide_code_kernels(torch, w, use_graph):
             ms = time_steady(torch, fn, use_graph)
             tops = w.ops / (ms * 1e-3) / 1e12
             # multiply-accumulates performed per effective operation: 2^bits when selecting with the dense instruction
-            # (8 for the two planes of 2-bit codes), half of that with the sparse one
+            # (8 for the two planes of 2-bit codes), half of that with the sparse one (3- and 4-bit codes as two 2-bit
+            # lookups: 2 for each)
             factor = None
-            if name.startswith("onehot_mfma"):
+            if name.startswith("onehot_smfmac_4as2"):
+                factor = 4
+            elif name.startswith("onehot_mfma"):
                 factor = 8 if bits == 2 else nlev
             elif name.startswith("onehot_smfmac"):
                 factor = 4 if bits == 2 else nlev // 2

@@ -740,22 +740,22 @@ bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p)
 const char *dg_nibble_config_name(const dg_lut *, const DgProblem &p)
 {
     const DgProblem n = nibble_problem(p), t = sparse_problem(n);
-    if (dg_sparse_ws_preferred(two_bit_view(), n)) return "onehot_mfma_4as2_ws_32xK";
+    if (dg_sparse_ws_preferred(two_bit_view(), n)) return "onehot_smfmac_4as2_ws_32xK";
     const Plan q = sparse_plan(two_bit_view(), t);
     static const char *const split_names[17] = {
-        "", "onehot_mfma_4as2_splitk_s1", "onehot_mfma_4as2_splitk_s2", "onehot_mfma_4as2_splitk_s3", "onehot_mfma_4as2_splitk_s4",
-        "onehot_mfma_4as2_splitk_s5", "onehot_mfma_4as2_splitk_s6", "onehot_mfma_4as2_splitk_s7", "onehot_mfma_4as2_splitk_s8",
-        "onehot_mfma_4as2_splitk_s9", "onehot_mfma_4as2_splitk_s10", "onehot_mfma_4as2_splitk_s11", "onehot_mfma_4as2_splitk_s12",
-        "onehot_mfma_4as2_splitk_s13", "onehot_mfma_4as2_splitk_s14", "onehot_mfma_4as2_splitk_s15", "onehot_mfma_4as2_splitk_s16"};
+        "", "onehot_smfmac_4as2_splitk_s1", "onehot_smfmac_4as2_splitk_s2", "onehot_smfmac_4as2_splitk_s3", "onehot_smfmac_4as2_splitk_s4",
+        "onehot_smfmac_4as2_splitk_s5", "onehot_smfmac_4as2_splitk_s6", "onehot_smfmac_4as2_splitk_s7", "onehot_smfmac_4as2_splitk_s8",
+        "onehot_smfmac_4as2_splitk_s9", "onehot_smfmac_4as2_splitk_s10", "onehot_smfmac_4as2_splitk_s11", "onehot_smfmac_4as2_splitk_s12",
+        "onehot_smfmac_4as2_splitk_s13", "onehot_smfmac_4as2_splitk_s14", "onehot_smfmac_4as2_splitk_s15", "onehot_smfmac_4as2_splitk_s16"};
     static const char *const tile_names[2][3][4] = {
-        {{"onehot_mfma_4as2_64x32", "onehot_mfma_4as2_64x64", "onehot_mfma_4as2_64x128", ""},
-         {"onehot_mfma_4as2_64x32_k2", "onehot_mfma_4as2_64x64_k2", "onehot_mfma_4as2_64x128_k2", ""},
-         {"onehot_mfma_4as2_64x32_k4", "onehot_mfma_4as2_64x64_k4", "onehot_mfma_4as2_64x128_k4", ""}},
-        {{"onehot_mfma_4as2_staged_32x64", "onehot_mfma_4as2_staged_32x128", "onehot_mfma_4as2_staged_32x192", "onehot_mfma_4as2_staged_32x224"},
-         {"onehot_mfma_4as2_staged_32x64_k2", "onehot_mfma_4as2_staged_32x128_k2", "", ""},
-         {"onehot_mfma_4as2_staged_32x64_k4", "onehot_mfma_4as2_staged_32x128_k4", "", ""}}};
+        {{"onehot_smfmac_4as2_64x32", "onehot_smfmac_4as2_64x64", "onehot_smfmac_4as2_64x128", ""},
+         {"onehot_smfmac_4as2_64x32_k2", "onehot_smfmac_4as2_64x64_k2", "onehot_smfmac_4as2_64x128_k2", ""},
+         {"onehot_smfmac_4as2_64x32_k4", "onehot_smfmac_4as2_64x64_k4", "onehot_smfmac_4as2_64x128_k4", ""}},
+        {{"onehot_smfmac_4as2_staged_32x64", "onehot_smfmac_4as2_staged_32x128", "onehot_smfmac_4as2_staged_32x192", "onehot_smfmac_4as2_staged_32x224"},
+         {"onehot_smfmac_4as2_staged_32x64_k2", "onehot_smfmac_4as2_staged_32x128_k2", "", ""},
+         {"onehot_smfmac_4as2_staged_32x64_k4", "onehot_smfmac_4as2_staged_32x128_k4", "", ""}}};
     if (q.split) return split_names[q.S];
-    if (q.staged && q.wm == 2) return "onehot_smfmac4_64x128";
+    if (q.staged && q.wm == 2) return "onehot_smfmac_4as2_staged_64x128";
     const int k = q.skw == 4 ? 2 : (q.skw == 2 ? 1 : 0);
     if (q.staged) return tile_names[1][k][q.wn == 2 ? 0 : (q.wn == 4 ? 1 : (q.wn == 6 ? 2 : 3))];
     return tile_names[0][k][q.wn == 1 ? 0 : (q.wn == 2 ? 1 : 2)];
@@ -940,9 +940,9 @@ bool dg_staged2p_preferred(const dg_lut *lut, const DgProblem &p)
 const char *dg_staged2p_config_name(const dg_lut *, const DgProblem &p)
 {
     static const char *const names[3][3] = {
-        {"onehot_mfma_2p_staged_32x32", "onehot_mfma_2p_staged_32x64", "onehot_smfmac_2p_32x128"},
-        {"onehot_mfma_2p_staged_32x32_k2", "onehot_mfma_2p_staged_32x64_k2", "onehot_mfma_2p_staged_32x128_k2"},
-        {"onehot_mfma_2p_staged_32x32_k4", "onehot_mfma_2p_staged_32x64_k4", "onehot_mfma_2p_staged_32x128_k4"}};
+        {"onehot_smfmac_2p_staged_32x32", "onehot_smfmac_2p_staged_32x64", "onehot_smfmac_2p_staged_32x128"},
+        {"onehot_smfmac_2p_staged_32x32_k2", "onehot_smfmac_2p_staged_32x64_k2", "onehot_smfmac_2p_staged_32x128_k2"},
+        {"onehot_smfmac_2p_staged_32x32_k4", "onehot_smfmac_2p_staged_32x64_k4", "onehot_smfmac_2p_staged_32x128_k4"}};
     const Plan q = staged2p_plan(sparse_problem(p));
     return names[q.skw == 4 ? 2 : (q.skw == 2 ? 1 : 0)][q.wn == 4 ? 2 : (q.wn == 2 ? 1 : 0)];
 }

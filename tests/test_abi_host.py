@@ -212,13 +212,20 @@ def test_kernel_names_need_no_gpu():
     assert dg.dg_gemm_kernel_name(lut, 64, 196, 576, "mfma_i8").startswith("mfma_i8_splitk_s")
     assert dg.dg_gemm_kernel_name(lut, 8192, 8192, 8192, "mfma_i8") == "mfma_i8_128x128"
     wide = dg.dg_build_lut((127, -128, 5, 0), (-128, 127, 1, 0), dg.DG_LUT_I16)
-    assert dg.dg_gemm_kernel_name(wide, 8192, 8192, 8192) == "onehot_smfmac_2p_32x128"   # large layers: the sparse instruction
+    assert dg.dg_gemm_kernel_name(wide, 8192, 8192, 8192) == "onehot_smfmac_2p_staged_32x128"   # large layers: the sparse instruction
+    assert dg.dg_gemm_kernel_name(wide, 8192, 8192, 8192 + 32) == "onehot_smfmac_2p_32x128"     # (taps of no whole runs: direct loads)
     assert dg.dg_gemm_kernel_name(wide, 8192, 8192, 8192, "onehot_mfma") == "onehot_mfma_2p_32x128"
-    assert dg.dg_gemm_kernel_name(wide, 256, 1568, 2304).startswith("onehot_mfma_2p_")
+    assert dg.dg_gemm_kernel_name(wide, 256, 1568, 2304) == "onehot_smfmac_2p_staged_32x64_k4"
+    assert dg.dg_gemm_kernel_name(wide, 256, 1568, 2304 + 32).startswith("onehot_mfma_2p_")
     t4 = dg.dg_build_lut_bits(4, list(range(-8, 8)), list(range(16)), dg.DG_LUT_I8)
-    assert dg.dg_gemm_kernel_name(t4, 256, 50176, 2304) == "onehot_smfmac4_64x128"      # large layers: the sparse instruction
+    # evenly spaced levels: the table is the sum of two 2-bit lookups; any other table is taken whole, large layers on the
+    # sparse instruction
+    assert dg.dg_gemm_kernel_name(t4, 256, 50176, 2304) == "onehot_smfmac_4as2_staged_64x128"
     assert dg.dg_gemm_kernel_name(t4, 256, 50176, 2304, "onehot_mfma").startswith("onehot_mfma_64x")
-    assert dg.dg_gemm_kernel_name(t4, 256, 1568, 2304).startswith("onehot_mfma_")
+    assert dg.dg_gemm_kernel_name(t4, 256, 1568, 2304) == "onehot_smfmac_4as2_staged_32x64_k4"
+    u4 = dg.dg_build_lut_bits(4, list(range(-8, 6)) + [7, 6], list(range(14)) + [15, 14], dg.DG_LUT_I8)
+    assert dg.dg_gemm_kernel_name(u4, 256, 50176, 2304) == "onehot_smfmac4_64x128"
+    assert dg.dg_gemm_kernel_name(u4, 256, 1568, 2304).startswith("onehot_mfma_")
     assert dg.dg_gemm_kernel_name(t4, 256, 50176, 2304, "perm") == "unsupported"
     # packing + convolution in one call: fused into the split-K kernel on small layers only
     small = dg.conv_desc(1, 56, 56, 64, 64, 3, 3, (1, 1), (1, 1))

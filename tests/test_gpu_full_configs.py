@@ -111,16 +111,27 @@ def test_sampled_output(name):
     assert np.array_equal(_one_call(case, inp).reshape(-1)[pos], want), f"{name}: packing + convolution / GEMM as one call"
 
 
-@pytest.mark.parametrize("name", ["vgg16_conv3x3_b16", "gemm_8192x8192x8192_i16"])
-def test_sampled_output_two_plane_table(name):
-    """The same full-size shapes under a table with entries beyond int8 (levels up to +-127, no zero activation
-    level): AUTO's sparse-instruction two-plane kernel and the dense-instruction one, against sampled oracle outputs."""
+TWO_PLANES = [("vgg16_conv3x3_b16", "onehot_smfmac_2p_staged_32x128"), ("gemm_8192x8192x8192_i16", "onehot_smfmac_2p_staged_32x128"),
+              ((16, 56, 96, 96, 3, 1), "onehot_smfmac_2p_32x128"),               # taps of no whole runs: direct loads
+              ((8, 28, 256, 256, 3, 1), "onehot_smfmac_2p_staged_32x128_k4"), ((16, 28, 256, 256, 3, 1), "onehot_smfmac_2p_staged_32x128_k2"),
+              ((8, 14, 256, 256, 3, 1), "onehot_smfmac_2p_staged_32x64_k4"), ((16, 56, 64, 64, 3, 1), "onehot_smfmac_2p_staged_32x64")]
+
+
+@pytest.mark.parametrize("name,kernel", TWO_PLANES)
+def test_sampled_output_two_plane_table(name, kernel):
+    """The same full-size shapes, and a network layer for each other form, under a table with entries beyond int8 (levels up
+    to +-127, no zero activation level): AUTO's sparse-instruction two-plane kernels and the dense-instruction one, against
+    sampled oracle outputs."""
     from paper_2304_09049_amd import binding as dg
-    w = wl.CONFIGS[name]
+    if isinstance(name, str):
+        w = wl.CONFIGS[name]
+    else:
+        B, H, Cin, Cout, k, s = name
+        w = wl._conv("layer", B, H, H, Cin, Cout, k, k, (s, s), (k // 2, k // 2))
     inp = wl.make_inputs(w)
     lw, la = (127, -128, 5, 3), (-128, 127, 1, 2)
     case = GpuCase(inp, levels=(lw, la), entry=dg.DG_LUT_I16)
-    assert case.kernel_name("auto") == "onehot_smfmac_2p_32x128"
+    assert case.kernel_name("auto") == kernel
     assert case.kernel_name("onehot_mfma").startswith("onehot_mfma_2p_")
     rng = np.random.default_rng(321)
     pos = _border_heavy_positions(w, rng, int(min(200000, 3e9 // w.K)))

@@ -15,8 +15,24 @@ TABLES = {(4, "uniform"): (list(range(-8, 8)), list(range(16))),
           (4, "shifted"): ([1] * 8 + [-1, 0] * 4, [-120 + 16 * a for a in range(16)]),
           (4, "uneven"): ([-3, 2, 1, 0, 5, -6, 4, 7, -7, 6, 3, -1, -2, -5, -4, 2], [g + f for g in (0, 9, -4, 3) for f in (1, 0, 5, 2)]),
           (3, "uniform"): (list(range(-4, 4)), list(range(1, 9)))}
-# plan override, name's end, whether K must be whole runs of 64 four-bit codes (staged) or a power of two (stationary)
 PLANS = ["auto", "split", "1", "2", "4", "1k2", "2k4", "12", "12k2", "12k4", "14", "14k4", "16", "17", "24", "ws"]
+STAGED = {"12": "32x64", "14": "32x128", "16": "32x192", "17": "32x224", "24": "64x128"}
+TILED = {"1": "64x32", "2": "64x64", "4": "64x128"}
+
+
+def _expected(plan, Cin, k, one_by_one):
+    """The name of a forced plan's kernel; None: any that neither stages nor keeps its weights, the planner's choice.  Staged tiles
+    need taps of whole 128-position runs of 2-bit codes (unshared 32 x 64 and 32 x 128: halves of one), stationary weights a
+    layer without a window and K = 64, 128, 256 or 512 of them; a tile is shared by no more wavefronts than K has chunks."""
+    c2, (tile, _, share) = 2 * Cin, plan.partition("k")
+    if plan == "ws":
+        return "ws_32xK" if one_by_one and c2 in (64, 128, 256, 512) else None
+    if tile in STAGED:
+        if c2 % 128 == 0 or (c2 % 64 == 0 and plan in ("12", "14")):
+            return "staged_" + STAGED[tile] + ("_k" + share if share else "")
+        return None
+    chunks = k * k * c2 // (64 if c2 % 64 == 0 else 32)
+    return TILED[tile] + ("_k" + share if share and int(share) <= chunks else "")
 
 
 def _run(lut, bits, Wc, Xc, desc, scale=None):
@@ -45,8 +61,17 @@ def test_nibble_tables(table, plan, monkeypatch):
                                                  (1, 40, 31, 32, 36, 1, (1, 1), (0, 0)), (1, 6, 5, 256, 33, 5, (1, 1), (2, 2))]:
         desc = dg.conv_desc(B, H, W, Cin, Cout, k, k, stride, pad)
         name = dg.dg_conv_kernel_name(lut, desc)
-        assert "4as2" in name or name == "onehot_smfmac4_64x128", name
-        ran += plan == "auto" or plan == "split" or ("ws" in name) == (plan == "ws")
+        if plan == "split":
+            assert name.startswith("onehot_smfmac_4as2_splitk_s") or (k == 1 and Cin == 32), name      # (one chunk is not split)
+            ran += "splitk" in name
+        elif plan == "auto":
+            assert name.startswith("onehot_smfmac_4as2_"), name
+            ran += 1
+        elif (want := _expected(plan, Cin, k, k == 1)) is not None:
+            assert name == "onehot_smfmac_4as2_" + want, (name, Cin, k)
+            ran += 1
+        else:
+            assert name.startswith("onehot_smfmac_4as2_") and "staged" not in name and "ws" not in name, (name, Cin, k)
         Wc, Xc = wl.draw_codes(rng, (Cout, k, k, Cin), nlev=nlev), wl.draw_codes(rng, (B, H, W, Cin), nlev=nlev)
         want = oracle.conv2d(Wc, Xc, lw, la, stride=stride, pad=pad)
         got, Wp, Xp = _run(lut, bits, Wc, Xc, desc)

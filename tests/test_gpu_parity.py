@@ -753,7 +753,8 @@ def test_wide_codes_gemm_and_conv(bits, plan, monkeypatch):
         if K % 16 != 0:
             assert name == ("lds" if variant in ("auto", "lds") else "unsupported")
         else:
-            assert name.startswith({"lds": "lds", "onehot_smfmac": "onehot_smfmac4"}.get(variant, "onehot_mfma"))
+            # (row-major, so run transposed: AUTO finds the evenly spaced weight levels and takes their table as two 2-bit ones)
+            assert name.startswith({"lds": "lds", "onehot_smfmac": "onehot_smfmac4_", "auto": "onehot_smfmac_4as2_"}.get(variant, "onehot_mfma"))
         if name == "unsupported":
             continue
         got = dg.dg_gemm_lut(lut, Wp, Ap, M, N, K, variant=variant)
