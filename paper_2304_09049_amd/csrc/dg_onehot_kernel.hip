@@ -647,8 +647,11 @@ dg_status dg_launch_ragged(const dg_lut *lut, const DgProblem &p, bool codes, hi
 // at half the sparse instruction's rate (the dense instruction's kernels) of a table taken whole.  Measured, kernel alone in
 // graph replays, 4-bit codes: 28x28x128 -> 128 3x3 at batch 8 31.3 -> 8.8 us (dense split-K before), 56x56x256 -> 64 at batch
 // 4 10.5 -> 5.4, 14x14x128 -> 464 3x3 at batch 1 9.7 -> 5.3, 56x56x128 -> 128 3x3 at batch 16 64 -> 28.7 (sparse4_kernel
-// before), 56x56x256 -> 256 3x3 at batch 16 215 -> 95; 3-bit codes: 28x28x64 -> 128 at batch 8 4.1 -> 3.5.  No layer
-// measured was faster with the table whole, so the rule has no size in it.
+// before), 56x56x256 -> 256 3x3 at batch 16 215 -> 95; 3-bit codes: 28x28x64 -> 128 at batch 8 4.1 -> 3.5.  Nor does it
+// take whole runs of K: of 16 layers with 512 and more tiles of sparse4_kernel and taps of no whole runs, whose direct-load
+// tiles the split then runs in, 56x56x32 -> 96 3x3 at batch 16 24.9 -> 16.7, 56x56x80 -> 128 49.8 -> 32.1, 56x56x288 -> 128
+// 22.4 -> 14.5, 112x112x16 -> 64 5x5 48.3 -> 30.9, the GEMMs 4096 x 4096 x 272 41.6 -> 35.5 (the least gain) and 4096 x
+// 4096 x 8208 943 -> 664.  No layer measured was faster with the table whole, so the rule has no size in it.
 
 namespace {
 
@@ -723,11 +726,7 @@ bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p)
     const char *e = dg_override("DG_NIBBLES");
     if (e ? atoi(e) == 0 : dg_override("DG_ONEHOT_PLAN") != nullptr) return false;
     if (p.Cin % 16 != 0 || p.K >= (1 << 29)) return false;
-    // Where the 64 x 128 tiles of dg_sparse4_kernel.h fill the chip and the staged and stationary kernels do not take the layer
-    // (taps of no whole runs) the table stays whole.
     const DgProblem n = nibble_problem(p);
-    if (!e && dg_sparse4_preferred(lut, p) && !dg_sparse_ws_preferred(two_bit_view(), n) && !sparse_plan(two_bit_view(), sparse_problem(n)).staged)
-        return false;
     // The stationary-weight kernel gives a wavefront one row block for all its pixels, so where the last block is not whole those
     // wavefronts store element by element throughout and the rest wait for them: 112x112x64 -> 112 at batch 15 (3-bit codes) took
     // 60.8 us so, 32.9 with the table whole on the dense instruction's tiles, which share their edges out.

@@ -223,8 +223,10 @@ def test_kernel_names_need_no_gpu():
     assert dg.dg_gemm_kernel_name(t4, 256, 50176, 2304) == "onehot_smfmac_4as2_staged_64x128"
     assert dg.dg_gemm_kernel_name(t4, 256, 50176, 2304, "onehot_mfma").startswith("onehot_mfma_64x")
     assert dg.dg_gemm_kernel_name(t4, 256, 1568, 2304) == "onehot_smfmac_4as2_staged_32x64_k4"
+    no_runs = dg.conv_desc(16, 56, 56, 32, 96, 3, 3, (1, 1), (1, 1))      # (also where the taps are no whole runs)
+    assert dg.dg_conv_kernel_name(t4, no_runs) == dg.dg_gemm_kernel_name(t4, 130, 32770, 272) == "onehot_smfmac_4as2_64x64"
     u4 = dg.dg_build_lut_bits(4, list(range(-8, 6)) + [7, 6], list(range(14)) + [15, 14], dg.DG_LUT_I8)
-    assert dg.dg_gemm_kernel_name(u4, 256, 50176, 2304) == "onehot_smfmac4_64x128"
+    assert dg.dg_gemm_kernel_name(u4, 256, 50176, 2304) == dg.dg_conv_kernel_name(u4, no_runs) == "onehot_smfmac4_64x128"
     assert dg.dg_gemm_kernel_name(u4, 256, 1568, 2304).startswith("onehot_mfma_")
     assert dg.dg_gemm_kernel_name(t4, 256, 50176, 2304, "perm") == "unsupported"
     # packing + convolution in one call: fused into the split-K kernel on small layers only

@@ -898,17 +898,19 @@ def test_graph_replays_equal_eager_launches():
             assert np.array_equal(y1.cpu().numpy(), want), f"replay {replay}: one-call path"
 
 
-def test_four_bit_auto_takes_the_sparse_kernel_on_large_layers():
-    """AUTO's choice for 4-bit tables from 512 tiles of 64 x 128 up is the sparse-instruction kernel: a GEMM and an NHWC
-    convolution of that size against the oracle (the forced-variant tests above only reach it on small shapes)."""
-    lw, la = WIDE[4]
+@pytest.mark.parametrize("lw,la,kernel", [(list(range(-8, 6)) + [7, 6], WIDE[4][1], "onehot_smfmac4_64x128"),
+                                          (list(range(-8, 8)), list(range(16)), "onehot_smfmac_4as2_64x64")])
+def test_four_bit_auto_takes_the_sparse_kernel_on_large_layers(lw, la, kernel):
+    """AUTO's choice for 4-bit tables from 512 tiles of 64 x 128 up is the sparse-instruction kernel, the one for tables that are
+    the sum of two 2-bit lookups (evenly spaced levels) or the one for any other (neither side's levels evenly spaced): a GEMM
+    and an NHWC convolution of that size against the oracle (the forced-variant tests above only reach them on small shapes)."""
     lut = dg.dg_build_lut_bits(4, lw, la, dg.DG_LUT_I8)
     rng = np.random.default_rng(77)
     M, N, K = 130, 32770, 272                               # ragged in M and N; 3 x 257 tiles; one-word chunks
     Wc, Ac = wl.draw_codes(rng, (M, K), nlev=16), wl.draw_codes(rng, (N, K), nlev=16)
     Wp = dg.dg_pack_codes_bits(torch.from_numpy(Wc).cuda(), M, K, 4)
     Ap = dg.dg_pack_codes_bits(torch.from_numpy(Ac).cuda(), N, K, 4)
-    assert dg.dg_gemm_kernel_name(lut, M, N, K) == "onehot_smfmac4_64x128"
+    assert dg.dg_gemm_kernel_name(lut, M, N, K) == kernel
     got = dg.dg_gemm_lut(lut, Wp, Ap, M, N, K)
     torch.cuda.synchronize()
     _assert_same(got.cpu().numpy(), oracle.gemm(Wc, Ac, lw, la), "4-bit gemm, AUTO")
@@ -918,7 +920,7 @@ def test_four_bit_auto_takes_the_sparse_kernel_on_large_layers():
     Wp = dg.dg_pack_codes_bits(torch.from_numpy(Wc).cuda(), Cout, 9 * Cin, 4)
     Xp = dg.dg_pack_codes_bits(torch.from_numpy(Xc).cuda(), B * H * W, Cin, 4)
     desc = dg.conv_desc(B, H, W, Cin, Cout, 3, 3, (1, 1), (1, 1))
-    assert dg.dg_conv_kernel_name(lut, desc) == "onehot_smfmac4_64x128"
+    assert dg.dg_conv_kernel_name(lut, desc) == kernel
     y = dg.dg_conv2d_lut(lut, Wp, Xp, desc)
     torch.cuda.synchronize()
     acc = oracle.conv2d(Wc, Xc, lw, la, stride=(1, 1), pad=(1, 1))
