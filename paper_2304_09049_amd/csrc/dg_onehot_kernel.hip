@@ -651,7 +651,11 @@ dg_status dg_launch_ragged(const dg_lut *lut, const DgProblem &p, bool codes, hi
 // take whole runs of K: of 16 layers with 512 and more tiles of sparse4_kernel and taps of no whole runs, whose direct-load
 // tiles the split then runs in, 56x56x32 -> 96 3x3 at batch 16 24.9 -> 16.7, 56x56x80 -> 128 49.8 -> 32.1, 56x56x288 -> 128
 // 22.4 -> 14.5, 112x112x16 -> 64 5x5 48.3 -> 30.9, the GEMMs 4096 x 4096 x 272 41.6 -> 35.5 (the least gain) and 4096 x
-// 4096 x 8208 943 -> 664.  No layer measured was faster with the table whole, so the rule has no size in it.
+// 4096 x 8208 943 -> 664; nor whole row blocks: of 13 layers whose last block of 32 channels is partial, on the stationary-weight
+// kernel, 56x56x128 -> 100 at batch 8 14.1 -> 7.0 (3-bit codes 8.2 -> 6.9), 28x28x128 -> 72 at batch 8 7.0 -> 4.8 (5.4 -> 4.8),
+// 112x112x64 -> 112 at batch 15 37 -> 20.6 (24.0 -> 20.8), 112x112x32 -> 112 26 -> 22.5 (3-bit codes 22.1, 22.2: the least gain).
+// The rule has no size in it: of all layers measured two were faster with the table whole, 3-bit codes on staged tiles with a
+// partial row block (28x28x256 -> 200 at batch 32 17.4, whole 16.2; 56x56x256 -> 72 27.4, 26.5), which store its edge element by element.
 
 namespace {
 
@@ -726,11 +730,6 @@ bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p)
     const char *e = dg_override("DG_NIBBLES");
     if (e ? atoi(e) == 0 : dg_override("DG_ONEHOT_PLAN") != nullptr) return false;
     if (p.Cin % 16 != 0 || p.K >= (1 << 29)) return false;
-    const DgProblem n = nibble_problem(p);
-    // The stationary-weight kernel gives a wavefront one row block for all its pixels, so where the last block is not whole those
-    // wavefronts store element by element throughout and the rest wait for them: 112x112x64 -> 112 at batch 15 (3-bit codes) took
-    // 60.8 us so, 32.9 with the table whole on the dense instruction's tiles, which share their edges out.
-    if (!e && dg_sparse_ws_preferred(two_bit_view(), n) && sparse_problem(n).M % 32 != 0) return false;
     NibbleTable t;
     // (every sum of the split table is a sum of T, whose range the API has checked; partial sums wrap and wrap back)
     return dg_sparse_supports(two_bit_view(), nibble_problem(p)) && nibble_table(lut, sparse_transposes(p), &t);

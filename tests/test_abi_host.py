@@ -225,6 +225,9 @@ def test_kernel_names_need_no_gpu():
     assert dg.dg_gemm_kernel_name(t4, 256, 1568, 2304) == "onehot_smfmac_4as2_staged_32x64_k4"
     no_runs = dg.conv_desc(16, 56, 56, 32, 96, 3, 3, (1, 1), (1, 1))      # (also where the taps are no whole runs)
     assert dg.dg_conv_kernel_name(t4, no_runs) == dg.dg_gemm_kernel_name(t4, 130, 32770, 272) == "onehot_smfmac_4as2_64x64"
+    for t, cout in ((t4, 100), (t4, 72), (dg.dg_build_lut_bits(3, list(range(-4, 4)), list(range(8)), dg.DG_LUT_I8), 112)):
+        partial = dg.conv_desc(8, 56, 56, 64, cout, 1, 1, (1, 1), (0, 0))         # (and where the last block of channels is partial)
+        assert dg.dg_conv_kernel_name(t, partial) == "onehot_smfmac_4as2_ws_32xK"
     u4 = dg.dg_build_lut_bits(4, list(range(-8, 6)) + [7, 6], list(range(14)) + [15, 14], dg.DG_LUT_I8)
     assert dg.dg_gemm_kernel_name(u4, 256, 50176, 2304) == dg.dg_conv_kernel_name(u4, no_runs) == "onehot_smfmac4_64x128"
     assert dg.dg_gemm_kernel_name(u4, 256, 1568, 2304).startswith("onehot_mfma_")

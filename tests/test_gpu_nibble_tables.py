@@ -99,6 +99,24 @@ def test_nibble_tables(table, plan, monkeypatch):
             assert np.array_equal(out.cpu().numpy(), want.T if strides[0] == 1 else want), (M, N, K, strides)
 
 
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("B,H,Cin,Cout,k,form", [(8, 56, 128, 100, 1, "ws_32xK"), (8, 28, 128, 72, 1, "ws_32xK"), (8, 28, 128, 128, 3, "staged_"),
+                                                 (8, 56, 32, 40, 1, "ws_32xK"), (2, 28, 48, 72, 3, "splitk_s")])
+def test_the_rule_takes_layers_with_partial_row_blocks(B, H, Cin, Cout, k, form, bits):
+    """AUTO by itself, no override, at network sizes: the two lookups wherever the table splits, also where the last block of 32
+    channels is partial."""
+    lw, la = TABLES[(bits, "uniform")]
+    lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I8)
+    desc = dg.conv_desc(B, H, H, Cin, Cout, k, k, (1, 1), (k // 2, k // 2))
+    assert dg.dg_conv_kernel_name(lut, desc).startswith("onehot_smfmac_4as2_" + form), dg.dg_conv_kernel_name(lut, desc)
+    rng = np.random.default_rng(Cout)
+    Wc, Xc = wl.draw_codes(rng, (Cout, k, k, Cin), nlev=1 << bits), wl.draw_codes(rng, (B, H, H, Cin), nlev=1 << bits)
+    got, _, _ = _run(lut, bits, Wc, Xc, desc)
+    pos = np.unique(np.concatenate([rng.integers(0, got.size, 20000), np.arange(4 * Cout), got.size - 1 - np.arange(4 * Cout)]))
+    want = oracle.conv2d_sampled(Wc, Xc, lw, la, pos, stride=(1, 1), pad=(k // 2, k // 2))
+    assert np.array_equal(got.reshape(-1)[pos], want)
+
+
 def test_raised_nibble_table(monkeypatch):
     """The staged kernel on the table raised to non-negative entries (its default on large problems only)."""
     bits, (lw, la) = 4, TABLES[(4, "uniform")]
