@@ -78,8 +78,10 @@ __device__ __forceinline__ bool dg_mfma_rows_whole(int64_t row_stride, int64_t c
 }
 
 // EDGE_COLUMNS: blocks whose columns are not all inside take the stores without a test per element too, the lanes of columns
-// beyond the last sitting them out (for kernels whose wavefronts keep one column block and would test every element of it
-// throughout, dg_sparse_ws_kernel.h).
+// beyond the last sitting them out.  For kernels whose wavefronts have one column block each, all of which would be stored
+// element by element where it is partial: dg_sparse_ws_kernel.h, and dg_sparse_staged_kernel.h, where (packed codes, graph
+// replays) 28x28x256 -> 200 at batch 32 went from 17.4 to 14.5 us with 3-bit codes, 56x56x256 -> 72 from 28.6 to 23.3, 56x56x128 ->
+// 72 3x3 at batch 16 from 21.7 to 17.9 with 2-bit ones, and layers of whole blocks stayed (56x56x128 -> 128 3x3 17.0, 17.2).
 template <bool TR, bool EDGE_COLUMNS = false>
 __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg_v16i &acc, int mb, int nb, int lane,
                                                     float sc)
@@ -136,7 +138,7 @@ __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg
 }
 
 // Store the (WM*32) x (WN*32) tile at (m0, n0).
-template <int WM, int WN, bool TR>
+template <int WM, int WN, bool TR, bool EDGE_COLUMNS = false>
 __device__ __forceinline__ void dg_mfma_store_tile(const DgProblem &p, const dg_v16i (&acc)[WM][WN], int m0, int n0,
                                                    int lane, const float (&sc_cols)[WM])
 {
@@ -144,5 +146,5 @@ __device__ __forceinline__ void dg_mfma_store_tile(const DgProblem &p, const dg_
     for (int bm = 0; bm < WM; ++bm)
 #pragma unroll
         for (int bn = 0; bn < WN; ++bn)
-            dg_mfma_store_block<TR>(p, acc[bm][bn], m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
+            dg_mfma_store_block<TR, EDGE_COLUMNS>(p, acc[bm][bn], m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
 }

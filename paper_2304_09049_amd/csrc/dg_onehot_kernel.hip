@@ -654,8 +654,8 @@ dg_status dg_launch_ragged(const dg_lut *lut, const DgProblem &p, bool codes, hi
 // 4096 x 8208 943 -> 664; nor whole row blocks: of 13 layers whose last block of 32 channels is partial, on the stationary-weight
 // kernel, 56x56x128 -> 100 at batch 8 14.1 -> 7.0 (3-bit codes 8.2 -> 6.9), 28x28x128 -> 72 at batch 8 7.0 -> 4.8 (5.4 -> 4.8),
 // 112x112x64 -> 112 at batch 15 37 -> 20.6 (24.0 -> 20.8), 112x112x32 -> 112 26 -> 22.5 (3-bit codes 22.1, 22.2: the least gain).
-// The rule has no size in it: of all layers measured two were faster with the table whole, 3-bit codes on staged tiles with a
-// partial row block (28x28x256 -> 200 at batch 32 17.4, whole 16.2; 56x56x256 -> 72 27.4, 26.5), which store its edge element by element.
+// The rule has no size in it: of all layers measured one was faster with the table whole (14x14x512 -> 72 at batch 32, 3-bit
+// codes: 7.15, whole 6.9).
 
 namespace {
 

@@ -352,7 +352,7 @@ smfmac_staged_kernel(Args a)
             for (int e = 0; e < 16; ++e)
                 out[bm][bn][e] = TWO ? (int)((uint32_t)acc[0][bn][e] + ((uint32_t)acc[WM - 1][bn][e] << 8)) : acc[bm][bn][e];
     if (SKW == 1) {
-        dg_mfma_store_tile<RB, WN, true>(p, out, m0, n0, lane, sc_cols);
+        dg_mfma_store_tile<RB, WN, true, true>(p, out, m0, n0, lane, sc_cols);
         return;
     }
     // The sums take the place of the staging rows: every wavefront is done with its rows (and its last loads have
@@ -382,7 +382,7 @@ smfmac_staged_kernel(Args a)
         v16i blk;
 #pragma unroll
         for (int e = 0; e < 16; ++e) blk[e] = sums[(i * 16 + e) * 64 + lane];
-        dg_mfma_store_block<true>(p, blk, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane, sc_cols[i / WN]);
+        dg_mfma_store_block<true, true>(p, blk, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane, sc_cols[i / WN]);
     }
 }
 

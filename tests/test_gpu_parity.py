@@ -1213,3 +1213,32 @@ def test_stationary_weight_kernel_partial_channel_blocks(K, waves, monkeypatch):
                 got = out.cpu().numpy()
                 _assert_same(got[:, :M].copy(), w, f"{(M, N, K)} {'codes' if raw else 'packed'}")
                 assert (got[:, M:] == -7).all(), f"{(M, N, K)}: stored beyond the last channel"
+
+
+@pytest.mark.parametrize("plan", ["12", "12k4", "14", "14k2", "16", "17", "24"])
+def test_staged_kernel_partial_channel_blocks(plan, monkeypatch):
+    """The same for the staged kernel's tiles, unshared and shared, on one and two planes' tables: a last block of 1, 8, 12 or 31
+    channels, the gap behind each pixel's channels untouched; in the row-major layout (run transposed) a last block of pixels."""
+    for levels in ("nonuniform_i8", "extreme_i16"):
+        lw, la, entry = LEVELS[levels]
+        monkeypatch.setenv("DG_ONEHOT_PLAN", plan)
+        kernel = "onehot_smfmac_staged_"
+        if levels == "extreme_i16":
+            if plan not in ("12", "12k4", "14", "14k2"):
+                continue
+            monkeypatch.delenv("DG_ONEHOT_PLAN")
+            monkeypatch.setenv("DG_STAGED_2P_PLAN", {"12": "2", "12k4": "2k4", "14": "4", "14k2": "4k2"}[plan])
+            kernel = "onehot_smfmac_2p_staged_"
+        variant = "onehot_smfmac" if levels == "nonuniform_i8" else "auto"
+        for (M, N, K, gap) in [(1, 70, 256, 3), (40, 333, 512, 60), (76, 1000, 1024, 1), (127, 257, 512, 40)]:
+            inp = wl.small_gemm(M, N, K, seed=M + N + K)
+            case = GpuCase(inp, levels=(lw, la), entry=entry)
+            assert case.kernel_name(variant).startswith(kernel), case.kernel_name(variant)
+            want = oracle.gemm(inp.Wc, inp.Ac, lw, la)
+            for shape, strides, w in (((N, M + gap), (1, M + gap), want.T), ((M, N + gap), (N + gap, 1), want)):
+                out = torch.full(shape, -7, dtype=torch.int32, device="cuda")
+                dg.dg_gemm_lut(case.lut, case.Wp, case.Ap, M, N, K, out=out, variant=variant, strides=strides)
+                torch.cuda.synchronize()
+                got = out.cpu().numpy()
+                _assert_same(got[:, :w.shape[1]].copy(), w.copy(), f"{levels} {(M, N, K)} {strides}")
+                assert (got[:, w.shape[1]:] == -7).all(), f"{levels} {(M, N, K)}: stored beyond the last channel"
