@@ -145,8 +145,9 @@ pack_slots4_kernel(const uint8_t *__restrict__ codes, uint8_t *__restrict__ pack
 
 // The same 16 codes to a lane (16-byte load, 8-byte store): in a dword of four codes the odd ones move down four bits beside the
 // even ones, and the two bytes that hold pairs are picked out of two such dwords at a time.  Bound by memory: a code per byte in,
-// half a byte out.  In graph replays, against a pair of codes per lane (above; now for what is left and for other
-// alignments): 3.2 M codes 4.14 -> 2.48 us, 12.8 M 6.77 -> 3.35, 0.8 M 2.54 -> 2.23 (a launch: 1.6).
+// half a byte out.  In graph replays, against a pair of codes per lane (above; now for other alignments and fewer than 16 codes): 3.2 M codes 4.14 -> 2.48 us, 12.8 M 6.77 -> 3.35, 0.8 M 2.54 -> 2.23 (a launch: 1.6).  The pairs behind the last whole
+// group go with the first block: a second launch for them made it 4.00 us for 3.1 M codes that are no multiple of 16 (now 2.46)
+// and 3.85 for 4290 (2.33), longer than a pair per lane takes.
 __device__ __forceinline__ uint32_t pack_slots8(uint32_t a, uint32_t b, uint32_t mask)
 {
     a &= mask, b &= mask;
@@ -154,9 +155,13 @@ __device__ __forceinline__ uint32_t pack_slots8(uint32_t a, uint32_t b, uint32_t
 }
 
 __global__ void __launch_bounds__(256)
-pack_slots4_vec16_kernel(const uint4 *__restrict__ codes, uint2 *__restrict__ packed, int64_t groups, uint32_t mask)
+pack_slots4_vec16_kernel(const uint4 *__restrict__ codes, uint2 *__restrict__ packed, int64_t groups, int32_t pairs, uint32_t mask)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    if (blockIdx.x == 0 && (int)threadIdx.x < pairs) {      // the up to 7 pairs behind the last whole group
+        const uint8_t *c = (const uint8_t *)(codes + groups) + 2 * threadIdx.x;
+        ((uint8_t *)(packed + groups))[threadIdx.x] = (uint8_t)((c[0] & mask & 255u) | ((c[1] & mask & 255u) << 4));
+    }
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < groups; g += stride) {
         const uint4 t = codes[g];
         packed[g] = make_uint2(pack_slots8(t.x, t.y, mask), pack_slots8(t.z, t.w, mask));
@@ -174,16 +179,13 @@ dg_status dg_launch_pack(const uint8_t *codes, int64_t rows, int64_t K, int bits
             int64_t blocks = (groups + 255) / 256;
             if (blocks > 256 * 32) blocks = 256 * 32;
             hipLaunchKernelGGL(pack_slots4_vec16_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint4 *)codes,
-                               (uint2 *)packed, groups, mask * 0x01010101u);
-            const dg_status s = dg_check_launch("pack_slots4_vec16_kernel");
-            if (s != DG_OK) return s;
+                               (uint2 *)packed, groups, (int32_t)(total / 2 - 8 * groups), mask * 0x01010101u);
+            return dg_check_launch("pack_slots4_vec16_kernel");
         }
-        const int64_t pairs = total / 2 - 8 * groups;
-        if (pairs == 0) return DG_OK;
+        const int64_t pairs = total / 2;
         int64_t blocks = (pairs + 255) / 256;
         if (blocks > 256 * 32) blocks = 256 * 32;
-        hipLaunchKernelGGL(pack_slots4_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, codes + 16 * groups, packed + 8 * groups,
-                           pairs, mask);
+        hipLaunchKernelGGL(pack_slots4_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, codes, packed, pairs, mask);
         return dg_check_launch("pack_slots4_kernel");
     }
     const int64_t total = rows * K;           // multiple of 4
