@@ -66,8 +66,8 @@ dg_status dg_build_lut(const int8_t levels_w[4], const int8_t levels_a[4], dg_lu
 /*
  * The same table for b-bit codes, b = 2, 3 or 4 (Sec. 3.3 and Table 2: index b + b bits, 2^(2b) = 16 / 64 / 256
  * entries; the paper describes this scaling without implementing it).  levels_w / levels_a hold 2^b levels each;
- * entry index = (w << b) | a.  Tables with b > 2 run on the one-hot matrix-core kernels (int8 entries, Cin % 16 == 0)
- * or on the LDS kernel.  bits outside 2..4 -> DG_ERR_UNSUPPORTED.  dg_build_lut is the b = 2 case.
+ * entry index = (w << b) | a.  Tables with b > 2 run on the one-hot matrix-core kernels (int8 entries, or wider ones that
+ * are the sum of two 2-bit lookups of int8 entries each, as evenly spaced levels give; Cin % 16 == 0) or on the LDS kernel.  bits outside 2..4 -> DG_ERR_UNSUPPORTED.  dg_build_lut is the b = 2 case.
  */
 dg_status dg_build_lut_bits(int32_t bits, const int8_t *levels_w, const int8_t *levels_a,
                             dg_lut_dtype entry, dg_lut **out);

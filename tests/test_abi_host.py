@@ -280,7 +280,7 @@ def test_requant_refuses_what_the_onehot_kernel_refuses():
     take them.  (Nothing is launched: the addresses are made up.)"""
     L = dg.lib()
     at = ctypes.c_void_p
-    for bits, lw, la, wp, xp in ((4, range(-8, 8), range(0, 32, 2), 0x1000, 0x2000), (3, range(-40, 40, 10), range(8), 0x1000, 0x2000),
+    for bits, lw, la, wp, xp in ((4, range(-8, 8), range(0, 32, 2), 0x1000, 0x2000), (3, range(-32, 32, 8), range(8), 0x1000, 0x2000),
                                  (3, range(-4, 4), range(8), 0x1008, 0x2000), (3, range(-4, 4), range(8), 0x1000, 0x2008)):
         lut = dg.dg_build_lut_bits(bits, list(lw), list(la), dg.DG_LUT_I16)
         for cin, k in ((64, 3), (128, 1)):

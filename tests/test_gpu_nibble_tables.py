@@ -14,7 +14,11 @@ pytestmark = pytest.mark.gpu
 TABLES = {(4, "uniform"): (list(range(-8, 8)), list(range(16))),
           (4, "shifted"): ([1] * 8 + [-1, 0] * 4, [-120 + 16 * a for a in range(16)]),
           (4, "uneven"): ([-3, 2, 1, 0, 5, -6, 4, 7, -7, 6, 3, -1, -2, -5, -4, 2], [g + f for g in (0, 9, -4, 3) for f in (1, 0, 5, 2)]),
-          (3, "uniform"): (list(range(-4, 4)), list(range(1, 9)))}
+          (3, "uniform"): (list(range(-4, 4)), list(range(1, 9))),
+          # entries beyond int8 whose two halves fit it: -240 ... 210, -224 ... 168
+          (4, "beyond"): (list(range(-8, 8)), list(range(0, 32, 2))),
+          (3, "beyond"): (list(range(-32, 32, 8)), list(range(8)))}
+ENTRY = {name: dg.DG_LUT_I16 if name[1] == "beyond" else dg.DG_LUT_I8 for name in TABLES}
 PLANS = ["auto", "split", "1", "2", "4", "1k2", "2k4", "12", "12k2", "12k4", "14", "14k4", "16", "17", "24", "ws"]
 STAGED = {"12": "32x64", "14": "32x128", "16": "32x192", "17": "32x224", "24": "64x128"}
 TILED = {"1": "64x32", "2": "64x64", "4": "64x128"}
@@ -49,7 +53,7 @@ def _run(lut, bits, Wc, Xc, desc, scale=None):
 @pytest.mark.parametrize("table", list(TABLES))
 def test_nibble_tables(table, plan, monkeypatch):
     bits, (lw, la) = table[0], TABLES[table]
-    lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I8)
+    lut = dg.dg_build_lut_bits(bits, lw, la, ENTRY[table])
     monkeypatch.setenv("DG_NIBBLES", "1")
     if plan != "auto":
         monkeypatch.setenv("DG_ONEHOT_PLAN", plan)
@@ -80,7 +84,11 @@ def test_nibble_tables(table, plan, monkeypatch):
         y = oracle.scale_epilogue_nhwc(want, scale)
         got, Wp, Xp = _run(lut, bits, Wc, Xc, desc, torch.from_numpy(scale).cuda())
         assert np.array_equal(got, y), (name, "scaled")
-        if Cout % 4 == 0:
+        if Cout % 4 == 0 and ENTRY[table] == dg.DG_LUT_I16:
+            with pytest.raises(dg.DgError) as e:             # (the fused layer takes tables of int8 entries)
+                dg.dg_conv2d_lut_requant(lut, Wp, Xp, desc, torch.from_numpy(scale).cuda(), 1.0, 0.5, 0)
+            assert e.value.status == 5
+        elif Cout % 4 == 0:
             qs = float(np.float32(3.0 / max(1e-6, float(np.percentile(np.abs(y), 90)))))
             packed = dg.dg_conv2d_lut_requant(lut, Wp, Xp, desc, torch.from_numpy(scale).cuda(), qs, 0.5, 0)
             torch.cuda.synchronize()
@@ -117,10 +125,29 @@ def test_the_rule_takes_layers_with_partial_row_blocks(B, H, Cin, Cout, k, form,
     assert np.array_equal(got.reshape(-1)[pos], want)
 
 
-def test_raised_nibble_table(monkeypatch):
+def test_wide_entries_that_do_not_split():
+    """Entries beyond int8 whose table is no sum of two lookups, or of none that fit int8, stay with the plain kernel."""
+    desc = dg.conv_desc(2, 14, 14, 64, 40, 3, 3, (1, 1), (1, 1))
+    for bits, lw, la in ((4, list(range(-8, 6)) + [7, 6], list(range(0, 28, 2)) + [30, 28]), (4, list(range(-128, 128, 16)), list(range(16))),
+                         (3, list(range(-4, 2)) + [3, 2], [100, 3, 5, 90, 1, 2, 127, 0])):
+        lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I16)
+        assert dg.dg_conv_kernel_name(lut, desc) == "lds"
+    # (activations 0 ... 15: the high parts of a weight level's row are up to 12 times the level apart, within int8 up to 21)
+    rng = np.random.default_rng(9)
+    for lw, la, name in ((list(range(-32, 32, 4)), list(range(16)), "lds"),
+                         (list(range(-16, 16, 2)), list(range(16)), "onehot_smfmac_4as2_splitk_s")):
+        lut = dg.dg_build_lut_bits(4, lw, la, dg.DG_LUT_I16)
+        assert dg.dg_conv_kernel_name(lut, desc).startswith(name), dg.dg_conv_kernel_name(lut, desc)
+        Wc, Xc = wl.draw_codes(rng, (40, 3, 3, 64), nlev=16), wl.draw_codes(rng, (2, 14, 14, 64), nlev=16)
+        got, _, _ = _run(lut, 4, Wc, Xc, desc)
+        assert np.array_equal(got, oracle.conv2d(Wc, Xc, lw, la, stride=(1, 1), pad=(1, 1)))
+
+
+@pytest.mark.parametrize("table", ["uniform", "beyond"])
+def test_raised_nibble_table(table, monkeypatch):
     """The staged kernel on the table raised to non-negative entries (its default on large problems only)."""
-    bits, (lw, la) = 4, TABLES[(4, "uniform")]
-    lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I8)
+    bits, (lw, la) = 4, TABLES[(4, table)]
+    lut = dg.dg_build_lut_bits(bits, lw, la, ENTRY[(4, table)])
     rng = np.random.default_rng(5)
     monkeypatch.setenv("DG_NIBBLES", "1")
     monkeypatch.setenv("DG_STAGED_BIAS", "1")
