@@ -124,6 +124,7 @@ dg_status dg_build_lut_bits(int32_t bits, const int8_t *levels_w, const int8_t *
             if (prod > t.max_entry) t.max_entry = prod;
         }
     t.max_abs = t.max_entry > -t.min_entry ? t.max_entry : -t.min_entry;
+    if (bits != 2) dg_find_two_lookups(&t);
     dg_lut *p = new (std::nothrow) dg_lut(t);
     if (!p) return dg_fail(DG_ERR_BUFFER, "dg_build_lut: out of host memory");
     *out = p;

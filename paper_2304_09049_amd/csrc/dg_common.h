@@ -7,6 +7,14 @@
 
 #include "deepgemm_hip.h"
 
+// A 3- or 4-bit table as the sum of two 2-bit lookups of the activation code, if it is one whose parts fit int8
+// (dg_onehot_kernel.hip): T[w][4 i + j] = low[w][j] + high[w][i], a row of four entries to a word.
+struct DgTwoLookups {
+    bool splits;
+    uint32_t low[16], high[16];
+    int32_t lo, hi;              // range of all their entries
+};
+
 // The opaque table object: levels, the 16 products, and what the kernels need to know about them.
 struct dg_lut {
     int32_t bits;        // code width: 2 (the paper's kernels), 3 or 4 (Sec. 3.3); 2^bits levels per side
@@ -19,6 +27,7 @@ struct dg_lut {
     int32_t min_entry;   // smallest product
     int32_t max_entry;   // largest product
     int32_t max_abs;     // max |product|
+    DgTwoLookups two[2]; // of the table, and of the transposed one (found when the table is built)
 };
 
 // 16 table entries passed to kernels by value (no device allocation is needed for a table).
@@ -122,6 +131,7 @@ const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p);
 bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes);      // taps of no whole 32-position groups; `codes`: p.Xp one per byte
 const char *dg_ragged_config_name(const dg_lut *lut, const DgProblem &p, bool codes);
 dg_status dg_launch_ragged(const dg_lut *lut, const DgProblem &p, bool codes, hipStream_t stream);
+void dg_find_two_lookups(dg_lut *lut);
 bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p);      // 3- and 4-bit codes as two 2-bit ones each
 dg_status dg_launch_nibble(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 const char *dg_nibble_config_name(const dg_lut *lut, const DgProblem &p);

@@ -659,26 +659,20 @@ dg_status dg_launch_ragged(const dg_lut *lut, const DgProblem &p, bool codes, hi
 
 namespace {
 
-struct NibbleTable {
-    dgoh::Pools pools;           // word w: low[w][0..3], word 16 + w: high[w][0..3]
-    int lo, hi;                  // range of all their entries
-};
-
 // The split of a table, if it has one whose parts fit int8 (`transposed`: of the transposed table).  What T says about codes
 // beyond the table's width (3-bit codes in their 4-bit slots) does not matter: they read as the code without the bit.
-bool nibble_table(const dg_lut *lut, bool transposed, NibbleTable *out)
+void find_two_lookups(const dg_lut *lut, bool transposed, DgTwoLookups *out)
 {
-    if (lut->dtype == DG_LUT_F32 || (lut->bits != 3 && lut->bits != 4)) return false;
+    memset(out, 0, sizeof(*out));
     const int b = lut->bits, mask = (1 << b) - 1;
     auto T = [&](int w, int a) -> int {
         w &= mask, a &= mask;
         return transposed ? lut->entry[(a << b) | w] : lut->entry[(w << b) | a];
     };
     out->lo = INT32_MAX, out->hi = INT32_MIN;
-    for (int i = 0; i < 64; ++i) out->pools.w[i] = 0;
     for (int w = 0; w < 16; ++w) {
         for (int a = 0; a < 16; ++a)
-            if (T(w, a) != T(w, a & 3) + T(w, a & ~3) - T(w, 0)) return false;
+            if (T(w, a) != T(w, a & 3) + T(w, a & ~3) - T(w, 0)) return;
         // a row's two parts may be moved against each other by any constant: the smaller shift that makes both int8
         int low_min = INT32_MAX, low_max = INT32_MIN, high_min = INT32_MAX, high_max = INT32_MIN;
         for (int i = 0; i < 4; ++i) {
@@ -688,18 +682,18 @@ bool nibble_table(const dg_lut *lut, bool transposed, NibbleTable *out)
         }
         const int least = -128 - low_min > high_max - 127 ? -128 - low_min : high_max - 127;     // low + shift >= -128, high - shift <= 127
         const int most = 127 - low_max < high_min + 128 ? 127 - low_max : high_min + 128;
-        if (least > most) return false;
+        if (least > most) return;
         const int shift = least > 0 ? least : (most < 0 ? most : 0);
         for (int i = 0; i < 4; ++i) {
             const int l = T(w, i) + shift, h = T(w, 4 * i) - T(w, 0) - shift;
-            out->pools.w[w] |= (uint32_t)(uint8_t)(int8_t)l << (8 * i);
-            out->pools.w[16 + w] |= (uint32_t)(uint8_t)(int8_t)h << (8 * i);
+            out->low[w] |= (uint32_t)(uint8_t)(int8_t)l << (8 * i);
+            out->high[w] |= (uint32_t)(uint8_t)(int8_t)h << (8 * i);
         }
         const int lo = low_min + shift < high_min - shift ? low_min + shift : high_min - shift;
         const int hi = low_max + shift > high_max - shift ? low_max + shift : high_max - shift;
         out->lo = lo < out->lo ? lo : out->lo, out->hi = hi > out->hi ? hi : out->hi;
     }
-    return true;
+    out->splits = true;
 }
 
 // What the 2-bit planner needs to know of such a table: 2-bit codes, int8 entries.
@@ -723,16 +717,23 @@ DgProblem nibble_problem(const DgProblem &p)
 
 }   // namespace
 
+// (once per table, 1.2 us for both: 256 entries, three lookups each; a call asks twice at least, and took 0.9 us each time
+// it worked it out anew -- the choice of a kernel 1.76 -> 0.82 us, of a 2-bit layer's 0.87)
+void dg_find_two_lookups(dg_lut *lut)
+{
+    find_two_lookups(lut, false, &lut->two[0]);
+    find_two_lookups(lut, true, &lut->two[1]);
+}
+
 // DG_NIBBLES: 0 never; 1 also while DG_ONEHOT_PLAN is set, which then forces the shape of the kernel (tests, A/B measurement).
 bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p)
 {
-    if (lut->bits != 3 && lut->bits != 4) return false;
+    if ((lut->bits != 3 && lut->bits != 4) || !lut->two[sparse_transposes(p)].splits) return false;
     const char *e = dg_override("DG_NIBBLES");
     if (e ? atoi(e) == 0 : dg_override("DG_ONEHOT_PLAN") != nullptr) return false;
     if (p.Cin % 16 != 0 || p.K >= (1 << 29)) return false;
-    NibbleTable t;
     // (every sum of the split table is a sum of T, whose range the API has checked; partial sums wrap and wrap back)
-    return dg_sparse_supports(two_bit_view(), nibble_problem(p)) && nibble_table(lut, sparse_transposes(p), &t);
+    return dg_sparse_supports(two_bit_view(), nibble_problem(p));
 }
 
 const char *dg_nibble_config_name(const dg_lut *, const DgProblem &p)
@@ -761,15 +762,16 @@ const char *dg_nibble_config_name(const dg_lut *, const DgProblem &p)
 
 dg_status dg_launch_nibble(const dg_lut *lut, const DgProblem &p0, hipStream_t stream)
 {
-    NibbleTable t;
-    if (!nibble_table(lut, sparse_transposes(p0), &t))
-        return dg_fail(DG_ERR_UNSUPPORTED, "sparse one-hot kernel: the table is not the sum of two 2-bit lookups");
+    const DgTwoLookups &t = lut->two[sparse_transposes(p0)];
+    if (!t.splits) return dg_fail(DG_ERR_UNSUPPORTED, "sparse one-hot kernel: the table is not the sum of two 2-bit lookups");
+    dgoh::Pools pools;                                     // word w: low[w][0..3], word 16 + w: high[w][0..3]
+    for (int i = 0; i < 64; ++i) pools.w[i] = i < 16 ? t.low[i] : (i < 32 ? t.high[i - 16] : 0);
     const DgProblem n = nibble_problem(p0), p = sparse_problem(n);
     if (dg_sparse_ws_preferred(two_bit_view(), n)) {
-        dgoh::unit_sparse_ws_nib(p, t.pools, sparse_ws_streams(p, false), stream);
+        dgoh::unit_sparse_ws_nib(p, pools, sparse_ws_streams(p, false), stream);
         return dg_check_launch("smfmac_ws_kernel");
     }
-    return launch_sparse<true>(p, sparse_plan(two_bit_view(), p), t.pools, t.lo, t.hi, stream);
+    return launch_sparse<true>(p, sparse_plan(two_bit_view(), p), pools, t.lo, t.hi, stream);
 }
 
 // ---- 4-bit codes on the sparse instruction (dg_sparse4_kernel.h): 64 x 128 tiles only, so large layers only
