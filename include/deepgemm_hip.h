@@ -212,7 +212,7 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *                    channel axis is contiguous (the default)
  *   DG_F32_MFMA      "0": AUTO never takes a binary32 table to the matrix cores, "1": whatever the layer's size
  *   DG_STAGED_2P     "0": AUTO never takes the staged kernel for entries beyond int8
- *   DG_STAGED_2P_PLAN  its tile's width in blocks, 1, 2 or 4, optionally followed by "k2" or "k4" (whatever the size)
+ *   DG_STAGED_2P_PLAN  its tile's width in blocks, 2 or 4, "2k4", "4k2" or "4k4": shared (whatever the size)
  *   DG_RAGGED        "0": AUTO never takes the sparse-instruction kernel for Cin % 32 != 0, "1": also on small problems
  *   DG_RAGGED_PLAN   its tile, "11" (32 x 32), "21" (64 x 32) or "22" (64 x 64), optionally followed by "s<S>", the wavefronts sharing it
  *   DG_RAGGED_CODES  "0": it never packs unpacked codes itself, "1": always

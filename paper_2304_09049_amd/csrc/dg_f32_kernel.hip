@@ -50,7 +50,6 @@ __global__ void __launch_bounds__(256)
 onehot_f32_kernel(F32Args a)
 {
     static_assert(WHOLE || CHW == 1, "taps that are no whole words are loaded word by word");
-    constexpr int WN = 1;                                   // blocks of 16 pixels per wavefront
     constexpr int RING = CHW == 1 ? 4 : 2;                  // loads in flight
     __shared__ float s_table[2 * 4 * 32 + 32];              // pairs of entries [v][pair], pairs of one-hot values, pairs of zeros
     const DgProblem &p = a.p;
@@ -62,39 +61,31 @@ onehot_f32_kernel(F32Args a)
     const int lane = threadIdx.x & 63, i16 = lane & 15, v = lane >> 4;
     const int64_t tile = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (tile >= a.tiles) return;                            // (whole wavefronts; no barrier follows)
-    const int m0 = (int)(tile % a.tiles_m) * 16, n0 = (int)(tile / a.tiles_m) * (16 * WN);
+    const int m0 = (int)(tile % a.tiles_m) * 16, n0 = (int)(tile / a.tiles_m) * 16;
     const int L = p.Cin / 4, loads = (L + 4 * CHW - 1) / (4 * CHW), total = p.KH * p.KW * loads;
 
     const uint8_t *w_next = p.Wp + (int64_t)min(m0 + i16, p.M - 1) * (p.K / 4);
-    int ih0[WN], iw0[WN], off0[WN];                          // (32-bit offsets: the host sends inputs below 2^31 bytes)
-    bool live[WN];
-#pragma unroll
-    for (int b = 0; b < WN; ++b) {
-        const int n = n0 + 16 * b + i16, nn = min(n, p.N - 1);
-        const int t = (int)dg_fdiv((uint32_t)nn, a.div_ow), ow = nn - t * p.OW;
-        const int img = (int)dg_fdiv((uint32_t)t, a.div_oh), oh = t - img * p.OH;
-        live[b] = n < p.N;
-        ih0[b] = oh * p.sh - p.ph, iw0[b] = ow * p.sw - p.pw;
-        off0[b] = ((img * p.H + ih0[b]) * p.W + iw0[b]) * L;
-    }
+    // this lane's pixel (32-bit offsets: the host sends inputs below 2^31 bytes)
+    const bool live = n0 + i16 < p.N;
+    const int nn = min(n0 + i16, p.N - 1);
+    const int line = (int)dg_fdiv((uint32_t)nn, a.div_ow), ow = nn - line * p.OW;
+    const int img = (int)dg_fdiv((uint32_t)line, a.div_oh), oh = line - img * p.OH;
+    const int ih0 = oh * p.sh - p.ph, iw0 = ow * p.sw - p.pw, off0 = ((img * p.H + ih0) * p.W + iw0) * L;
 
     struct Load {
-        RawWords<CHW> w, x[WN];
-        uint32_t base[WN];                                  // where this pixel's pairs are read
+        RawWords<CHW> w, x;
+        uint32_t base;                                      // where this pixel's pairs are read
         int shift, codes;                                   // (the same in every lane)
     };
     const uint32_t w_base = 128 * v, x_base = 512 + 128 * v, zeros = 1024;
     int kh = 0, kw = 0, j = 0, fetched = 0;
-    int32_t x_at[WN];                                       // the tap's bytes of each pixel (outside the image: the first pixel's)
-    uint32_t tap_base[WN];
+    int32_t x_at;                                           // the tap's bytes of the pixel (outside the image: the first pixel's)
+    uint32_t tap_base;
     auto enter_tap = [&]() {
         const int32_t tap_off = (kh * p.W + kw) * L;
-#pragma unroll
-        for (int b = 0; b < WN; ++b) {
-            const bool ok = live[b] & ((uint32_t)(ih0[b] + kh) < (uint32_t)p.H) & ((uint32_t)(iw0[b] + kw) < (uint32_t)p.W);
-            x_at[b] = ok ? off0[b] + tap_off : 0;
-            tap_base[b] = ok ? x_base : zeros;
-        }
+        const bool ok = live & ((uint32_t)(ih0 + kh) < (uint32_t)p.H) & ((uint32_t)(iw0 + kw) < (uint32_t)p.W);
+        x_at = ok ? off0 + tap_off : 0;
+        tap_base = ok ? x_base : zeros;
     };
     enter_tap();
     auto fetch = [&](Load &t) {                              // past the end: the last words again, as pairs of zeros
@@ -102,11 +93,8 @@ onehot_f32_kernel(F32Args a)
         t.shift = 8 * (4 * j - start);
         t.codes = min(16, 4 * (L - 4 * j));
         t.w = *(const RawWords<CHW> *)(w_next + start);
-#pragma unroll
-        for (int b = 0; b < WN; ++b) {
-            t.x[b] = *(const RawWords<CHW> *)(p.Xp + x_at[b] + start);
-            t.base[b] = fetched < total ? tap_base[b] : zeros;
-        }
+        t.x = *(const RawWords<CHW> *)(p.Xp + x_at + start);
+        t.base = fetched < total ? tap_base : zeros;
         if (++fetched < total && ++j == loads) {             // (uniform)
             j = 0;
             if (++kw == p.KW) kw = 0, ++kh;
@@ -115,12 +103,10 @@ onehot_f32_kernel(F32Args a)
         }
     };
 
-    f32x4 acc[WN];
-#pragma unroll
-    for (int b = 0; b < WN; ++b) acc[b] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     const char *table = (const char *)s_table;
     struct Pairs {
-        float2 e[8], o[WN][8];
+        float2 e[8], o[8];
     };
     // Pair q = bits 4q ... 4q + 3 of the word, as a byte offset into a table of pairs: the even q in the bytes of one word, the odd
     // ones in another's (kept as they are: a byte of them plus the base is one instruction).
@@ -130,24 +116,20 @@ onehot_f32_kernel(F32Args a)
             s[0] = (word & 0x0F0F0F0Fu) << 3, s[1] = (word >> 1) & 0x78787878u;
             asm("" : "+v"(s[0]), "+v"(s[1]));
         };
-        uint32_t w[2], x[WN][2];
+        uint32_t w[2], x[2];
         split(t.w.v[c], w);
-#pragma unroll
-        for (int b = 0; b < WN; ++b) split(t.x[b].v[c], x[b]);
+        split(t.x.v[c], x);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             d.e[q] = *(const float2 *)(table + (w_base + ((w[q & 1] >> (8 * (q / 2))) & 255u)));
-#pragma unroll
-            for (int b = 0; b < WN; ++b) d.o[b][q] = *(const float2 *)(table + (t.base[b] + ((x[b][q & 1] >> (8 * (q / 2))) & 255u)));
+            d.o[q] = *(const float2 *)(table + (t.base + ((x[q & 1] >> (8 * (q / 2))) & 255u)));
         }
     };
     auto multiply = [&](const Pairs &d, int q0, int q1) {
 #pragma unroll
         for (int q = q0; q < q1; ++q) {
-#pragma unroll
-            for (int b = 0; b < WN; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.o[b][q].x, d.e[q].x, acc[b], 0, 0, 0);
-#pragma unroll
-            for (int b = 0; b < WN; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.o[b][q].y, d.e[q].y, acc[b], 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d.o[q].x, d.e[q].x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d.o[q].y, d.e[q].y, acc, 0, 0, 0);
         }
     };
 
@@ -168,7 +150,7 @@ onehot_f32_kernel(F32Args a)
                 if constexpr (WHOLE) {
                     multiply(pairs[cur], 0, 8);
 #pragma unroll
-                    for (int k = 0; k < 16 * WN; ++k) {
+                    for (int k = 0; k < 16; ++k) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                         __builtin_amdgcn_sched_group_barrier(0x102, 3, 0);
                     }
@@ -186,14 +168,12 @@ onehot_f32_kernel(F32Args a)
     if (m >= p.M) return;
     const float scale = p.scale ? p.scale[m] : 0.0f;
 #pragma unroll
-    for (int b = 0; b < WN; ++b)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int n = n0 + 16 * b + 4 * v + e;
-            if (n >= p.N) continue;
-            const int64_t o = (int64_t)m * p.stride_cm + (int64_t)n * p.stride_cn;
-            p.Cf[o] = p.scale ? __fmul_rn(acc[b][e], scale) : acc[b][e];
-        }
+    for (int e = 0; e < 4; ++e) {
+        const int n = n0 + 4 * v + e;
+        if (n >= p.N) continue;
+        const int64_t o = (int64_t)m * p.stride_cm + (int64_t)n * p.stride_cn;
+        p.Cf[o] = p.scale ? __fmul_rn(acc[e], scale) : acc[e];
+    }
 }
 
 }   // namespace

@@ -882,7 +882,7 @@ dg_status dg_launch_sparse2p(const dg_lut *lut, const DgProblem &p0, hipStream_t
 
 namespace {
 
-// Its tiles (32 channels in two planes x 32, 64 or 128 pixels) and which layers are its own.  What bounds it: every weight
+// Its tiles (32 channels in two planes x 64 or 128 pixels) and which layers are its own.  What bounds it: every weight
 // word costs 16 table reads of LDS for both planes' dense operands, which only the 128-pixel tile spreads over enough matrix
 // instructions, so that tile comes first, its wavefronts sharing K where the tiles alone leave SIMDs idle.  Measured on 36
 // layers against the kernels that ran them before (dense instruction, sparse2p_kernel), packed codes, graph replays, us:
@@ -919,7 +919,7 @@ Plan staged2p_plan(const DgProblem &t)
     }
     if (const char *force = dg_override("DG_STAGED_2P_PLAN")) {
         q.staged = true;
-        if (t.Cin % 128 == 0) q.wn = atoi(force), q.skw = strstr(force, "k4") ? 4 : (strstr(force, "k2") ? 2 : 1);
+        if (t.Cin % 128 == 0) q.wn = atoi(force) == 4 ? 4 : 2, q.skw = strstr(force, "k4") ? 4 : (q.wn == 4 && strstr(force, "k2") ? 2 : 1);
     }
     if (t.Cin % 64 != 0 || (uintptr_t)t.Wp % 16 != 0 || (uintptr_t)t.Xp % 16 != 0) q.staged = false;
     return q;
@@ -939,12 +939,12 @@ bool dg_staged2p_preferred(const dg_lut *lut, const DgProblem &p)
 
 const char *dg_staged2p_config_name(const dg_lut *, const DgProblem &p)
 {
-    static const char *const names[3][3] = {
-        {"onehot_smfmac_2p_staged_32x32", "onehot_smfmac_2p_staged_32x64", "onehot_smfmac_2p_staged_32x128"},
-        {"onehot_smfmac_2p_staged_32x32_k2", "onehot_smfmac_2p_staged_32x64_k2", "onehot_smfmac_2p_staged_32x128_k2"},
-        {"onehot_smfmac_2p_staged_32x32_k4", "onehot_smfmac_2p_staged_32x64_k4", "onehot_smfmac_2p_staged_32x128_k4"}};
+    static const char *const names[3][2] = {
+        {"onehot_smfmac_2p_staged_32x64", "onehot_smfmac_2p_staged_32x128"},
+        {"", "onehot_smfmac_2p_staged_32x128_k2"},
+        {"onehot_smfmac_2p_staged_32x64_k4", "onehot_smfmac_2p_staged_32x128_k4"}};
     const Plan q = staged2p_plan(sparse_problem(p));
-    return names[q.skw == 4 ? 2 : (q.skw == 2 ? 1 : 0)][q.wn == 4 ? 2 : (q.wn == 2 ? 1 : 0)];
+    return names[q.skw == 4 ? 2 : (q.skw == 2 ? 1 : 0)][q.wn == 4];
 }
 
 dg_status dg_launch_staged2p(const dg_lut *lut, const DgProblem &p0, hipStream_t stream)

@@ -30,21 +30,14 @@ namespace dgoh {
 template <bool NIB, bool TWO, int HIGH, int WM, class W>
 __device__ __forceinline__ void dense_rows_movable(const uint2 *table, const W &w, int t, uint32_t pick, v8i (&out)[WM][2])
 {
-    if constexpr (TWO) {                                    // one row block, both planes
-        uint32_t e, o;
-        sparse_row_offsets<false>(__builtin_amdgcn_perm(t ? w.ca1[0].y : w.ca1[0].x, t ? w.ca[0].y : w.ca[0].x, pick), e, o);
-        asm("" : "+v"(e), "+v"(o));
 #pragma unroll
-        for (int u = 0; u < 2; ++u) sparse_read_rows<false>(table + 16 * u, e, o, out[u][0], out[u][1]);
-        return;
-    }
-#pragma unroll
-    for (int u = 0; u < (TWO ? 0 : WM); ++u) {
+    for (int u = 0; u < (TWO ? 1 : WM); ++u) {
         const uint32_t w0 = t ? w.ca[u].y : w.ca[u].x, w1 = t ? w.ca1[u].y : w.ca1[u].x;
         uint32_t e, o;
         sparse_row_offsets<NIB>(__builtin_amdgcn_perm(w1, w0, pick), e, o);
         asm("" : "+v"(e), "+v"(o));
         sparse_read_rows<NIB, HIGH>(table, e, o, out[u][0], out[u][1]);
+        if constexpr (TWO) sparse_read_rows<false>(table + 16, e, o, out[1][0], out[1][1]);      // (the same row block, the high plane)
     }
 }
 
@@ -426,16 +419,9 @@ void launch_sparse_staged(const DgProblem &p, const Pools &pools, int32_t bias, 
         else if (q.wn == 4 && q.skw == 2) DG_STAGED(2, 4, 2, false);
         else if (q.wn == 4 && turns) DG_STAGED(2, 4, 4, true);
         else if (q.wn == 4) DG_STAGED(2, 4, 4, false);
-        else if (q.wn == 2 && q.skw == 1) DG_STAGED(2, 2, 1, false);
-        else if (q.wn == 2 && q.skw == 2 && turns) DG_STAGED(2, 2, 2, true);
-        else if (q.wn == 2 && q.skw == 2) DG_STAGED(2, 2, 2, false);
-        else if (q.wn == 2 && turns) DG_STAGED(2, 2, 4, true);
-        else if (q.wn == 2) DG_STAGED(2, 2, 4, false);
-        else if (q.skw == 1) DG_STAGED(2, 1, 1, false);
-        else if (q.skw == 2 && turns) DG_STAGED(2, 1, 2, true);
-        else if (q.skw == 2) DG_STAGED(2, 1, 2, false);
-        else if (turns) DG_STAGED(2, 1, 4, true);
-        else DG_STAGED(2, 1, 4, false);
+        else if (q.skw == 1) DG_STAGED(2, 2, 1, false);
+        else if (turns) DG_STAGED(2, 2, 4, true);
+        else DG_STAGED(2, 2, 4, false);
     } else {
         if (half && q.wn == 4) hipLaunchKernelGGL((smfmac_staged_kernel<1, 4, 1, false, true, NIB, false>), grid, dim3(256), 0, stream, a);
         else if (half) hipLaunchKernelGGL((smfmac_staged_kernel<1, 2, 1, false, true, NIB, false>), grid, dim3(256), 0, stream, a);

@@ -13,11 +13,11 @@ pytestmark = pytest.mark.gpu
 LW, LA = (127, -128, 5, 3), (-128, 127, 1, 2)          # the widest entries; no zero activation level
 
 
-@pytest.mark.parametrize("plan", ["1", "1k2", "1k4", "2", "2k2", "2k4", "4", "4k2", "4k4"])
+@pytest.mark.parametrize("plan", ["2", "2k4", "4", "4k2", "4k4"])
 def test_two_plane_staged(plan, monkeypatch):
     monkeypatch.setenv("DG_STAGED_2P_PLAN", plan)
     lut = dg.dg_build_lut(LW, LA, dg.DG_LUT_I16)
-    name = {"1": "onehot_smfmac_2p_staged_32x32", "2": "onehot_smfmac_2p_staged_32x64", "4": "onehot_smfmac_2p_staged_32x128"}[plan[0]]
+    name = {"2": "onehot_smfmac_2p_staged_32x64", "4": "onehot_smfmac_2p_staged_32x128"}[plan[0]]
     name += "_" + plan[1:] if plan[1:] else ""
     for (B, H, W, Cin, Cout, k, stride, pad) in [(2, 13, 11, 128, 40, 3, (1, 1), (1, 1)), (1, 30, 30, 256, 68, 3, (2, 2), (1, 1)),
                                                  (3, 9, 10, 384, 33, 1, (1, 1), (0, 0)), (1, 8, 9, 128, 100, 5, (1, 2), (2, 2)),
