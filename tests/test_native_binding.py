@@ -17,11 +17,54 @@ wide = dg.dg_build_lut((-128, -1, 0, 1), (0, 1, 2, 127), dg.DG_LUT_I16)
 rng = random.Random(7)
 shapes = [(rng.choice((1, 8, 32)), s, s, 32 * rng.randint(1, 16), 8 * rng.randint(1, 64), k, k, (1, 1), (k // 2, k // 2))
           for s in (7, 14, 28, 56) for k in (1, 3) for _ in range(20)]
+t3, t4 = (dg.dg_build_lut_bits(b, list(range(-(1 << b) // 2, (1 << b) // 2)), list(range(1 << b))) for b in (3, 4))
+uneven = dg.dg_build_lut_bits(4, list(range(-8, 6)) + [7, 6], list(range(14)) + [15, 14])
 for _ in range(2):                                   # 160 shapes, so that the second time round finds some plans kept and most replaced
     for s in shapes:
-        for t in (lut, wide):
+        for t in (lut, wide, t3, t4, uneven):
             d = dg.conv_desc(*s)
-            print(dg.dg_conv_kernel_name(t, d), dg.dg_conv_codes_kernel_name(t, d), dg.dg_conv_kernel_name(t, d, "onehot_mfma"))
+            print(dg.dg_conv_kernel_name(t, d), dg.dg_conv_codes_kernel_name(t, d), dg.dg_conv_kernel_name(t, d, "onehot_mfma"),
+                  dg.dg_gemm_kernel_name(t, s[4], s[0] * s[1] * s[2], s[3]))
+"""
+
+# Small problems of every code width, one and two planes, GEMMs and convolutions, each three times in another order: most of their
+# plans are replaced between two of its calls.  The outputs of all three are the oracle's.
+PARITY = """
+import random, sys
+import numpy as np, torch
+import oracle
+from paper_2304_09049_amd import binding as dg
+from paper_2304_09049_amd import workloads as wl
+rng, gen = random.Random(11), np.random.default_rng(11)
+levels = {2: ((-2, -1, 0, 1), (0, 1, 2, 3)), 22: ((-128, -1, 5, 127), (1, -3, 127, 2)), 3: (list(range(-4, 4)), list(range(1, 9))),
+          4: (list(range(-8, 8)), list(range(16))), 44: (list(range(-8, 6)) + [7, 6], list(range(14)) + [15, 14])}
+tables = {k: dg.dg_build_lut_bits(k % 10, list(w), list(a), dg.DG_LUT_I16) for k, (w, a) in levels.items()}
+calls = []
+for i in range(150):
+    kind = rng.choice(list(levels))
+    bits, (lw, la), lut = kind % 10, levels[kind], tables[kind]
+    cin, cout = 32 * rng.randint(1, 8), rng.randint(1, 100)
+    if i % 3:
+        k, H, W, B = rng.choice((1, 3)), rng.randint(3, 12), rng.randint(3, 12), rng.randint(1, 3)
+        w, x = wl.draw_codes(gen, (cout, k, k, cin), nlev=1 << bits), wl.draw_codes(gen, (B, H, W, cin), nlev=1 << bits)
+        want = oracle.conv2d(w, x, lw, la, stride=(1, 1), pad=(k // 2, k // 2))
+        desc, rows, K = dg.conv_desc(B, H, W, cin, cout, k, k, (1, 1), (k // 2, k // 2)), B * H * W, k * k * cin
+    else:
+        rows, K = rng.randint(1, 300), cin
+        w, x = wl.draw_codes(gen, (cout, K), nlev=1 << bits), wl.draw_codes(gen, (rows, K), nlev=1 << bits)
+        want, desc = oracle.gemm(w, x, lw, la), None
+    pack = lambda c, r, n: dg.dg_pack_codes_bits(torch.from_numpy(c).cuda(), r, n, bits)
+    calls.append((lut, desc, pack(w, cout, K), pack(x, rows, cin), torch.from_numpy(x).cuda(), cout, rows, K, want))
+for time in range(3):
+    for (lut, desc, wp, xp, codes, cout, rows, K, want) in rng.sample(calls, len(calls)):
+        work = torch.empty_like(xp)
+        if desc is not None:
+            got = dg.dg_conv2d_lut(lut, wp, xp, desc), dg.dg_conv2d_lut_codes(lut, wp, codes, desc, work=work)
+        else:
+            got = dg.dg_gemm_lut(lut, wp, xp, cout, rows, K), dg.dg_gemm_lut_codes(lut, wp, codes, cout, rows, K, work=work)
+        for g in got:
+            assert np.array_equal(g.cpu().numpy(), want), (lut.bits, cout, rows, K)
+print("the oracle's")
 """
 
 
@@ -35,8 +78,17 @@ def _names(overrides):
 
 def test_remembered_plans_are_the_plans():
     fresh, kept = _names("1"), _names("0")
-    assert len(fresh) == 640 and fresh[:320] == fresh[320:]
+    assert len(fresh) == 1600 and fresh[:800] == fresh[800:]
     assert kept == fresh
+
+
+@pytest.mark.gpu
+def test_remembered_plans_give_the_oracles_outputs():
+    """(In a process of its own, as the other tests run with overrides, under which no plan is remembered.)"""
+    env = {k: v for k, v in os.environ.items() if not k.startswith("DG_")}
+    out = subprocess.run([sys.executable, "-c", PARITY], env=env, capture_output=True, text=True,
+                         cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), timeout=100)
+    assert out.returncode == 0 and out.stdout == "the oracle's\n", out.stderr[-2000:]
 
 
 def test_native_checks():
