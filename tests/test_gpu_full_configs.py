@@ -175,3 +175,83 @@ def test_sampled_output_network_layers(shape, kernel, step_kernel):
     assert np.array_equal(got, want), f"{shape} {kernel}: {np.count_nonzero(got != want)} sampled outputs differ"
     got = _one_call(case, inp).reshape(-1)[pos]
     assert np.array_equal(got, want), f"{shape} {step_kernel}: {np.count_nonzero(got != want)} sampled outputs differ (one call)"
+
+
+RAGGED_LAYERS = [
+    # (B, H, W, Cin, Cout, filter, stride), AUTO's kernel on packed codes, the one-call step's kernel
+    ((8, 29, 27, 48, 120, 5, 1), "onehot_smfmac_ragged_32x32", "codes_onehot_smfmac_ragged_64x32"),
+    ((16, 28, 28, 112, 224, 3, 1), "onehot_smfmac_ragged_32x32", "onehot_smfmac_ragged_32x32"),        # unshared tiles
+    ((16, 14, 14, 208, 48, 5, 1), "onehot_smfmac_ragged_32x32", "onehot_smfmac_ragged_32x32"),         # shared by 12
+    ((4, 57, 57, 36, 128, 3, 1), "onehot_smfmac_ragged_32x32", "onehot_smfmac_ragged_32x32"),
+    ((16, 56, 56, 20, 128, 1, 1), "onehot_smfmac_ragged_32x32", "codes_onehot_smfmac_ragged_64x64"),
+    ((1, 56, 56, 16, 32, 3, 1), "onehot_smfmac_ragged_32x32", "codes_onehot_smfmac_ragged_32x32"),
+    ((32, 28, 28, 80, 96, 1, 2), "onehot_smfmac_ragged_32x32", "onehot_smfmac_ragged_32x32"),          # strided; the step packs the pixels read
+]
+
+
+@pytest.mark.parametrize("shape,kernel,step_kernel", RAGGED_LAYERS)
+def test_sampled_output_ragged_channel_layers(shape, kernel, step_kernel):
+    """Channel counts that are no multiple of 32 at full size, in the plans AUTO makes by itself: packed and from codes, against
+    sampled oracle outputs (borders included)."""
+    from paper_2304_09049_amd import binding as dg
+    B, H, W, Cin, Cout, k, s = shape
+    w = wl._conv("layer", B, H, W, Cin, Cout, k, k, (s, s), (k // 2, k // 2))
+    inp = wl.make_inputs(w)
+    case = GpuCase(inp)
+    assert case.kernel_name("auto") == kernel
+    assert dg.dg_conv_codes_kernel_name(case.lut, case.desc, "auto") == step_kernel
+    rng = np.random.default_rng(B + H + Cin + Cout)
+    pos = _border_heavy_positions(w, rng, int(min(60000, 2e8 // w.K)))
+    want = oracle.conv2d_sampled(inp.Wc, inp.Ac, inp.levels_w, inp.levels_a, pos, stride=w.stride, pad=w.pad)
+    got = case.run("auto").cpu().numpy().reshape(-1)[pos]
+    assert np.array_equal(got, want), f"{shape} {kernel}: {np.count_nonzero(got != want)} sampled outputs differ"
+    got = _one_call(case, inp).reshape(-1)[pos]
+    assert np.array_equal(got, want), f"{shape} {step_kernel}: {np.count_nonzero(got != want)} sampled outputs differ (one call)"
+
+
+@pytest.mark.parametrize("shape", [(4, 28, 28, 128, 128, 3), (8, 56, 56, 64, 64, 1), (8, 14, 14, 36, 100, 3), (2, 56, 56, 96, 72, 1)])
+def test_full_output_binary32_table(shape):
+    """Binary32 tables on layers that AUTO takes to the matrix cores by itself: every output, scaled and not, bit for bit."""
+    import torch
+    from paper_2304_09049_amd import binding as dg
+    B, H, W, Cin, Cout, k = shape
+    lw, la = np.array([-1.27, -0.32, 0.3217, 1.19], np.float32), np.array([0.05, 0.451, 0.98, 1.78], np.float32)
+    lut, table = dg.dg_build_lut_f32(lw, la), oracle.build_lut_f32(lw, la)
+    c = wl.small_conv(B, H, W, Cin, Cout, k, k, (1, 1), (k // 2, k // 2), seed=Cin, scale=True)
+    desc = dg.conv_desc(B, H, W, Cin, Cout, k, k, (1, 1), (k // 2, k // 2))
+    assert dg.dg_conv_kernel_name(lut, desc) == "onehot_mfma_f32"
+    Xc, scale = torch.from_numpy(c.Ac).cuda(), torch.from_numpy(c.scale).cuda()
+    Wp = dg.dg_pack_weights(torch.from_numpy(c.Wc).cuda(), Cout, k * k * Cin)
+    Xp = dg.dg_pack_activations(Xc, B * H * W, Cin)
+    want = oracle.conv2d_table_f32(c.Wc, c.Ac, table, stride=(1, 1), pad=(k // 2, k // 2))
+    assert np.array_equal(dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy(), want)
+    got = dg.dg_conv2d_lut_codes(lut, Wp, Xc, desc, work=torch.empty_like(Xp), scale=scale).cpu().numpy()
+    assert np.array_equal(got, want * c.scale[None, None, None, :])
+
+
+@pytest.mark.parametrize("bits,shape,kernel", [(4, (8, 28, 128, 128, 3), "onehot_smfmac_4as2_staged_32x64_k4"),
+                                               (4, (16, 56, 256, 256, 3), "onehot_smfmac_4as2_staged_32x224"),
+                                               (3, (8, 28, 128, 512, 1), "onehot_smfmac_4as2_ws_32xK"),
+                                               (3, (2, 14, 128, 200, 3), "onehot_smfmac_4as2_splitk_s"),
+                                               (4, (16, 56, 80, 128, 3), "onehot_smfmac_4as2_64x64")])
+def test_sampled_output_two_lookups(bits, shape, kernel):
+    """3- and 4-bit codes as two 2-bit lookups at full size, in AUTO's plans: packed and from codes, against sampled outputs."""
+    import torch
+    from paper_2304_09049_amd import binding as dg
+    B, H, Cin, Cout, k = shape
+    lw, la = list(range(-(1 << bits) // 2, (1 << bits) // 2)), list(range(1, (1 << bits) + 1)) if bits == 3 else list(range(16))
+    lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I8)
+    desc = dg.conv_desc(B, H, H, Cin, Cout, k, k, (1, 1), (k // 2, k // 2))
+    name = dg.dg_conv_kernel_name(lut, desc)
+    assert name.startswith(kernel), name
+    rng = np.random.default_rng(Cin + Cout)
+    Wc, Xc = wl.draw_codes(rng, (Cout, k, k, Cin), nlev=1 << bits), wl.draw_codes(rng, (B, H, H, Cin), nlev=1 << bits)
+    w = wl._conv("layer", B, H, H, Cin, Cout, k, k, (1, 1), (k // 2, k // 2))
+    pos = _border_heavy_positions(w, rng, int(min(60000, 2e8 // w.K)))
+    want = oracle.conv2d_sampled(Wc, Xc, lw, la, pos, stride=(1, 1), pad=(k // 2, k // 2))
+    codes = torch.from_numpy(Xc).cuda()
+    Wp = dg.dg_pack_codes_bits(torch.from_numpy(Wc).cuda(), Cout, k * k * Cin, bits)
+    Xp = dg.dg_pack_codes_bits(codes, B * H * H, Cin, bits)
+    assert np.array_equal(dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy().reshape(-1)[pos], want)
+    got = dg.dg_conv2d_lut_codes(lut, Wp, codes, desc, work=torch.empty_like(Xp)).cpu().numpy()
+    assert np.array_equal(got.reshape(-1)[pos], want)
