@@ -559,7 +559,10 @@ DgProblem ragged_problem(const DgProblem &p)
 // (8x29x27x48 -> 120 5x5: 8.4 us with 5 wavefronts a tile, 9.0 with 3; 14x14x208 -> 48 5x5 at batch 16: 9.2 with 12, 12.4 with
 // 4), unshared above one tile per SIMD (28x28x112 -> 224 3x3 at batch 16: 17.1 us, 26.7 on shared 64 x 64 tiles).  On unpacked
 // codes a taller tile packs less often: 64 x 64 where there is one for every second SIMD (that layer 18.9 against 20.3 us),
-// else 64 x 32 from 384 of them (the first layer 9.4 against 10.0), else the smallest.
+// else 64 x 32 from 384 of them (the first layer 9.4 against 10.0), else the smallest.  The step with 64 x 32, smallest tiles: 344 of
+// the former (7x28x28x48 -> 120 5x5) 10.5, 9.6; 392 (batch 8) 10.7, 11.5; 442 10.6, 11.5; 28x28x80 -> 256 3x3 at batch 4 (392) 9.6,
+// 10.5; but with many pixels per channel the smallest are ahead above the line too (56x56x20 -> 32 3x3 at batch 8 8.6, 7.0;
+// 28x28x208 -> 256 at batch 4 9.0, 6.4, and 7.9 as two kernels).
 dgoh::RaggedPlan ragged_plan(const DgProblem &t, bool codes)
 {
     dgoh::RaggedPlan q;
@@ -892,6 +895,11 @@ namespace {
 //                                     13.1; 7x7x2048 -> 512 at batch 16 (208) 10.8 -> 8.5 -- from 6e8 products on: less does not
 //                                     pay for the packing kernel that the split-K kernel's one-call form spares; below 192
 //                                     tiles split K is ahead (7x7x512 -> 512 3x3 at batch 8: 10.2 against 11.1)
+//   where the lines lie               28x28x256 -> 224 ... 288 3x3 at batch 4 ... 7, 32 x 64 by 4 against 32 x 128 by 4: 200 tiles of
+//                                     the latter 13.7, 13.2; 259 19.0, 18.3; 344 19.1, 18.3; 387 21.9, 18.3 (the former's workgroups are
+//                                     more than three per compute unit); 1x1 with K = 1024: 300 tiles 9.7, 10.9; 400 12.5, 11.3.
+//                                     32 x 128 by 4 against by 2: 592 tiles 26.0, 27.2; 688 26.1, 27.5; 784 32.1, 27.9 (the line
+//                                     at 640 leaves up to 5 % there)
 //   K = 512 ... 1023                  28x28x512 -> 256 at batch 16 (784 tiles of 32 x 128) 12.6 -> 10.7 unshared; with 392 8.3 against 8.5
 //   shorter K, up to 64 channels      56x56x256 -> 64 at batch 16 8.9 -> 7.7, 56x56x128 -> 64 6.9 -> 6.6; with more channels such a
 //                                     layer is its output's stores (28x28x128 -> 512 at batch 32: 16.4 against 17.6)
