@@ -316,8 +316,8 @@ dg_status dg_conv2d_lut_codes_static(const dg_lut *lut, const void *Wp_dev, cons
                                      float *Yf_dev, dg_kernel variant, void *hip_stream);
 /*
  * The same for a GEMM: Ac_dev is device memory, [N][K] uint8 codes; Ap_work_dev (work_bytes >=
- * dg_packed_bytes_bits(N, K, bits)) is used when the packing is not fused (K % 32 != 0, a large problem, another
- * variant, 3- or 4-bit codes: the conditions above with Cin = K).  Outputs, strides, scale and the other errors as dg_gemm_lut.
+ * dg_packed_bytes_bits(N, K, bits)) is used when the packing is not fused (a large problem, K % 32 != 0 with K < 16 or
+ * much to pack over, another variant, 3- or 4-bit codes: the conditions above with Cin = K).  Outputs, strides, scale and the other errors as dg_gemm_lut.
  */
 dg_status dg_gemm_lut_codes(const dg_lut *lut, const void *Wp_dev, const uint8_t *Ac_dev, int64_t M, int64_t N,
                             int64_t K, void *Ap_work_dev, size_t work_bytes, int32_t *C_dev, int64_t stride_cm,

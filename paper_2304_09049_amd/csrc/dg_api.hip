@@ -514,9 +514,10 @@ dg_status dg_conv2d_lut(const dg_lut *lut, const void *Wp_dev, const void *Xp_de
 
 namespace {
 
-// The one-call entry points fuse the packing into the kernel where the library's own choice for the problem (or the
-// variant the caller names) is the one-hot split-K kernel or the few-columns kernel, i.e. on problems so small that a
-// second launch costs a good part of the whole.
+// The one-call entry points fuse the packing into the kernel where a second launch would cost a good part of the whole and
+// the library's own choice for the problem (or the variant the caller names) has such a form: the one-hot split-K kernel,
+// the tiled kernels in their narrow tiles (dense, and sparse), the kernel for one or two columns, the stationary-weight
+// kernel, and the one for channel counts that are no multiple of 32.
 enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs, Ragged };
 
 // A 1x1 layer with a stride and no padding reads one input pixel in sh * sw: where the packing is not fused only those

@@ -14,8 +14,8 @@
 // image reads pairs of zeros instead.
 //
 // Bound by the matrix pipe and the instructions beside it: 32 cycles of the pipe per position and block of 256 outputs, a quarter
-// of it useful -- 8 table additions per SIMD and cycle at best -- and 2.5 other instructions, which a lone wavefront does not
-// overlap with its own matrix instructions (about 55 cycles per position; two blocks per wavefront, sharing the entries, 110: no
+// of it useful -- 8 table additions per SIMD and cycle at best -- and 1.8 VALU, 1.0 LDS and 0.3 scalar instructions, which a lone
+// wavefront does not overlap with its own matrix instructions (about 55 cycles per position; two blocks per wavefront, sharing the entries, 110: no
 // gain, and half the wavefronts).  So blocks are small and wavefronts many.  The plain kernel spends 5 vector instructions and an
 // LDS read per addition (3 additions per SIMD and cycle).  Measured against it: 28x28x128 -> 128 3x3 at batch 4 (1568 blocks) 63.4
 // -> 48.3 us, at batch 8 117 -> 88.8; 56x56x64 -> 64 at batch 8 21.1 -> 13.8; 14x14x36 -> 100 3x3 at batch 8 (686) 19.4 -> 13.5.

@@ -885,9 +885,11 @@ dg_status dg_launch_sparse2p(const dg_lut *lut, const DgProblem &p0, hipStream_t
 
 namespace {
 
-// Its tiles (32 channels in two planes x 64 or 128 pixels) and which layers are its own.  What bounds it: every weight
-// word costs 16 table reads of LDS for both planes' dense operands, which only the 128-pixel tile spreads over enough matrix
-// instructions, so that tile comes first, its wavefronts sharing K where the tiles alone leave SIMDs idle.  Measured on 36
+// Its tiles (32 channels in two planes x 64 or 128 pixels) and which layers are its own.  What bounds it: the
+// instructions beside the matrix ones.  Every weight word costs 16 table reads for both planes' dense operands and the offsets
+// for them, which only the 128-pixel tile spreads over enough matrix instructions (28x28x256 -> 256 3x3 at batch 8: 6.1 VALU and
+// 0.9 LDS instructions per matrix instruction, the pipe busy 0.33 of the cycles at 1.2 wavefronts per SIMD), so that tile
+// comes first, its wavefronts sharing K where the tiles alone leave SIMDs idle.  Measured on 36
 // layers against the kernels that ran them before (dense instruction, sparse2p_kernel), packed codes, graph replays, us:
 //   32 x 128 from one per SIMD        56x56x256 -> 256 3x3 at batch 16 (3136 tiles) 114 -> 96.7
 //   32 x 128 shared by 2 / by 4       28x28x256 -> 256 3x3 at batch 16 (784) 42.8 -> 27.6; at batch 8 (392) 27.0 -> 17.7

@@ -13,7 +13,8 @@
 // whichever takes fewer words.  (Words that are masked in both halves are multiplied all the same: a branch around them cost
 // more than the words, since it kept the loads of the next window from being issued between this one's instructions.)
 //
-// Bound by the latency of its loads and by issue slots, not by the matrix pipe: these layers are small.  So S wavefronts
+// Bound by issue slots and by how few wavefronts such small layers have, not by the matrix pipe (8x29x27x48 -> 120 5x5 from codes:
+// 36 VALU instructions per matrix instruction, VALU issue 0.35 of the cycles, the pipe 0.08, 1.4 wavefronts per SIMD).  So S wavefronts
 // of a workgroup share one tile and split the windows of K among them, their sums meeting in LDS (exact in any order).
 // Measured against the permute kernel (Cin % 16 == 0) and the LDS kernel that ran these layers, packed codes, graph replays:
 // 8x29x27x48 -> 120 5x5 43.1 -> 8.6 us (0.2 of the rate at which the instruction can select: 1.8 us), 28x28x112 -> 224 3x3 at batch
