@@ -65,12 +65,14 @@ onehot_f32_kernel(F32Args a)
     const int L = p.Cin / 4, loads = (L + 4 * CHW - 1) / (4 * CHW), total = p.KH * p.KW * loads;
 
     const uint8_t *w_next = p.Wp + (int64_t)min(m0 + i16, p.M - 1) * (p.K / 4);
-    // this lane's pixel (32-bit offsets: the host sends inputs below 2^31 bytes)
+    // this lane's pixel (32-bit offsets: the host sends inputs below 2^31 bytes; unsigned, as what a pixel's and a tap's offset
+    // are by themselves may be more where the padding is large, and their sum is the one of a byte inside)
     const bool live = n0 + i16 < p.N;
     const int nn = min(n0 + i16, p.N - 1);
     const int line = (int)dg_fdiv((uint32_t)nn, a.div_ow), ow = nn - line * p.OW;
     const int img = (int)dg_fdiv((uint32_t)line, a.div_oh), oh = line - img * p.OH;
-    const int ih0 = oh * p.sh - p.ph, iw0 = ow * p.sw - p.pw, off0 = ((img * p.H + ih0) * p.W + iw0) * L;
+    const int ih0 = oh * p.sh - p.ph, iw0 = ow * p.sw - p.pw;
+    const uint32_t off0 = ((uint32_t)(img * p.H + ih0) * (uint32_t)p.W + (uint32_t)iw0) * (uint32_t)L;
 
     struct Load {
         RawWords<CHW> w, x;
@@ -79,12 +81,12 @@ onehot_f32_kernel(F32Args a)
     };
     const uint32_t w_base = 128 * v, x_base = 512 + 128 * v, zeros = 1024;
     int kh = 0, kw = 0, j = 0, fetched = 0;
-    int32_t x_at;                                           // the tap's bytes of the pixel (outside the image: the first pixel's)
+    uint32_t x_at;                                          // the tap's bytes of the pixel (outside the image: the first pixel's)
     uint32_t tap_base;
     auto enter_tap = [&]() {
-        const int32_t tap_off = (kh * p.W + kw) * L;
+        const uint32_t tap_off = ((uint32_t)kh * (uint32_t)p.W + (uint32_t)kw) * (uint32_t)L;
         const bool ok = live & ((uint32_t)(ih0 + kh) < (uint32_t)p.H) & ((uint32_t)(iw0 + kw) < (uint32_t)p.W);
-        x_at = ok ? off0 + tap_off : 0;
+        x_at = ok ? off0 + tap_off : 0u;
         tap_base = ok ? x_base : zeros;
     };
     enter_tap();

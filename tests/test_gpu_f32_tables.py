@@ -45,6 +45,27 @@ def test_f32_tables(table, monkeypatch):
                 assert np.array_equal(got, want.T if strides[0] == 1 else want, equal_nan=True), (table, M, N, K, strides)
 
 
+def test_f32_tables_large_padding():
+    """One image row of 65536 pixels under a filter of 16385 rows with 16384 rows of padding: a pixel's own offset and a tap's are
+    2^32 bytes and more, of either sign; only one row of the filter meets the image for each output row."""
+    W, Cin, Cout, reach = 1 << 16, 16, 16, 1 << 14
+    lw, la = (np.array(x, np.float32) for x in TABLES["normal"])
+    lut, entries = dg.dg_build_lut_f32(lw, la), oracle.build_lut_f32(lw, la).reshape(4, 4)
+    desc = dg.conv_desc(1, 1, W, Cin, Cout, reach + 1, 1, (reach, 1), (reach, 0))
+    assert dg.dg_conv_kernel_name(lut, desc) == "onehot_mfma_f32"
+    rng = np.random.default_rng(3)
+    Wc, Xc = wl.draw_codes(rng, (Cout, reach + 1, 1, Cin)), wl.draw_codes(rng, (1, 1, W, Cin))
+    Wp = dg.dg_pack_weights(torch.from_numpy(Wc).cuda(), Cout, (reach + 1) * Cin)
+    Xp = dg.dg_pack_activations(torch.from_numpy(Xc).cuda(), W, Cin)
+    got = dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy()
+    assert got.shape == (1, 2, W, Cout)
+    for oh, kh in ((0, reach), (1, 0)):
+        want = np.zeros((W, Cout), np.float32)
+        for ci in range(Cin):
+            want = want + entries[Wc[:, kh, 0, ci][None, :], Xc[0, 0, :, ci][:, None]]
+        assert np.array_equal(got[0, oh], want), oh
+
+
 def test_f32_tables_rule():
     big, small = dg.conv_desc(4, 28, 28, 128, 128, 3, 3, (1, 1), (1, 1)), dg.conv_desc(1, 5, 5, 16, 8, 3, 3, (1, 1), (1, 1))
     good = dg.dg_build_lut_f32([-1.0, 0.3, 2.0, 0.0], [0.1, 0.2, 0.0, 4.0])
