@@ -77,6 +77,25 @@ inline DgFastDiv dg_make_div(uint32_t d)
     return f;
 }
 
+// The kernel's arguments, BYTES of them, asked for at once: one word of every 64-byte line, all before the first is waited for.  A
+// line's first reader waits 0.2 - 0.4 us for it (500 - 900 cycles measured, launches with new arguments), and a structure of 300 to
+// 550 bytes read where its fields are needed pays for that two or three times in a row before a kernel's first load.  The staged kernel
+// with it: 28x28x128 -> 128 3x3 at batch 8 with 4-bit codes (packing kernel included) 11.4 -> 10.9 us, 28x28x256 -> 256 in two planes
+// 20.8 -> 20.4.  The split-K, stationary-weight, few-columns and ragged kernels, whose argument loads the compiler puts together by
+// itself, gained nothing.
+template <size_t BYTES>
+__device__ __forceinline__ void dg_fetch_arguments()
+{
+    constexpr int LINES = (int)((BYTES + 63) / 64);
+    static_assert(LINES <= 10, "one operand of the statement below per line");
+    typedef const uint32_t __attribute__((address_space(4))) *Segment;
+    const Segment s = (Segment)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t v[10];
+#pragma unroll
+    for (int i = 0; i < 10; ++i) v[i] = s[16 * (i < LINES ? i : LINES - 1)];
+    asm volatile("" ::"s"(v[0]), "s"(v[1]), "s"(v[2]), "s"(v[3]), "s"(v[4]), "s"(v[5]), "s"(v[6]), "s"(v[7]), "s"(v[8]), "s"(v[9]));
+}
+
 // Value of a test / measurement override (an environment variable), or nullptr.  Overrides are looked at only when
 // DG_TEST_OVERRIDES=1 was set when the library was first called; otherwise this returns nullptr without reading anything.
 const char *dg_override(const char *name);

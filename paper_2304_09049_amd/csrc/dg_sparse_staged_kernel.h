@@ -81,6 +81,7 @@ smfmac_staged_kernel(Args a)
     // the narrower tiles have the registers for a second set of kept bytes, (0, 1), which spares the odd codes' shift
     constexpr bool SHIFT_ODD = WM * WN >= 7;
     const DgProblem &p = a.p;
+    dg_fetch_arguments<sizeof(a)>();
     const int lane = threadIdx.x & 63, w4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ks = w4 % SKW, tw = w4 / SKW;                 // this wavefront's share of K, and its tile within the workgroup
     const int64_t my_tile = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * TPW + tw;
