@@ -55,25 +55,24 @@ struct DgProblem {
 };
 
 // n / d for 0 <= n < 2^31 by multiply-high and shift, d fixed per launch and prepared on the host:
-// n / d == umulhi(n, mul) >> shift for d >= 2 with L = ceil(log2 d), mul = ceil(2^(31+L) / d) < 2^32 and shift = L - 1
-// (the error mul * d - 2^(31+L) is below d <= 2^L = 2^((31+L) - 31)); d = 1 is passed through.
+// n / d == umulhi(2 n, mul) >> shift with shift = ceil(log2 d) and mul = ceil(2^(31+shift) / d) < 2^32
+// (the error mul * d - 2^(31+shift) is below d <= 2^shift = 2^((31+shift) - 31)).  d = 1 is no case of its own (mul = 2^31, shift = 0):
+// a branch around it cost a kernel's start, which works out four to eight pixels' places, 10 to 30 instructions.
 struct DgFastDiv {
     uint32_t mul, shift, d;
 };
 
 __device__ __forceinline__ uint32_t dg_fdiv(uint32_t n, const DgFastDiv &f)
 {
-    return f.d == 1 ? n : __umulhi(n, f.mul) >> f.shift;
+    return __umulhi(2u * n, f.mul) >> f.shift;
 }
 
 inline DgFastDiv dg_make_div(uint32_t d)
 {
-    DgFastDiv f = {0u, 0u, d};
+    DgFastDiv f = {0x80000000u, 0u, d};
     if (d < 2) return f;
-    uint32_t L = 0;
-    while ((1ull << L) < d) ++L;
-    f.mul = (uint32_t)(((1ull << (31 + L)) + d - 1) / d);
-    f.shift = L - 1;
+    while ((1ull << f.shift) < d) ++f.shift;
+    f.mul = (uint32_t)(((1ull << (31 + f.shift)) + d - 1) / d);
     return f;
 }
 
