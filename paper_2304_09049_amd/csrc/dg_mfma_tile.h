@@ -48,25 +48,27 @@ __device__ __forceinline__ uint32_t dg_quad_or(uint32_t v)
 // a lane places its four codes in the four bytes of a word, at the bit position of its channel within the packed byte;
 // one OR across the quad (two DPP permutes) completes the four packed bytes in every lane, and lane i of the quad
 // stores the byte of pixel i -- so all lanes store.  Call with all 64 lanes active.
-__device__ __forceinline__ void dg_mfma_requant_block(const DgProblem &p, const dg_v16i &acc, int mb, int nb, int lane,
-                                                      float sc)
+__device__ __forceinline__ void dg_mfma_requant_quad(const DgProblem &p, const dg_v4i &acc, int e4, int mb, int nb, int lane, float sc)
 {
     const int r = lane & 31, h = lane >> 5, q = r & 3;
     const bool live = mb + r < p.M;                       // (M % 4 == 0: a quad is inside M or outside as a whole)
     const float lo_f = (float)p.q_lo, hi_f = (float)(p.q_lo + 3);
-    const int64_t row_bytes = p.M / 4;
+    uint32_t word = 0;
 #pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) {
-        uint32_t word = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float y = __fmul_rn((float)acc[4 * e4 + i], sc);
-            word |= dg_quantize_code_clamped(y, p.q_scale, p.q_zero, lo_f, hi_f) << (8 * i);
-        }
-        word = dg_quad_or(live ? word << (2 * q) : 0u);   // byte i = the packed byte of pixel i
-        const int n = nb + 8 * e4 + 4 * h + q;            // the pixel whose byte this lane stores
-        if (live && n < p.N) p.Qp[(int64_t)n * row_bytes + (mb + r) / 4] = (uint8_t)(word >> (8 * q));
+    for (int i = 0; i < 4; ++i) {
+        const float y = __fmul_rn((float)acc[i], sc);
+        word |= dg_quantize_code_clamped(y, p.q_scale, p.q_zero, lo_f, hi_f) << (8 * i);
     }
+    word = dg_quad_or(live ? word << (2 * q) : 0u);       // byte i = the packed byte of pixel i
+    const int n = nb + 8 * e4 + 4 * h + q;                // the pixel whose byte this lane stores
+    if (live && n < p.N) p.Qp[(int64_t)n * (p.M / 4) + (mb + r) / 4] = (uint8_t)(word >> (8 * q));
+}
+__device__ __forceinline__ void dg_mfma_requant_block(const DgProblem &p, const dg_v16i &acc, int mb, int nb, int lane,
+                                                      float sc)
+{
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4)
+        dg_mfma_requant_quad(p, (dg_v4i){acc[4 * e4], acc[4 * e4 + 1], acc[4 * e4 + 2], acc[4 * e4 + 3]}, e4, mb, nb, lane, sc);
 }
 
 // Whether a block's rows all lie inside the output and its 32 x 32 footprint spans less than 2^30 elements (strides may be
@@ -134,6 +136,44 @@ __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg
             __builtin_nontemporal_store((float)acc[e] * (TR ? sc : p.scale[row0 + k]), p.Cf + o);
         else
             __builtin_nontemporal_store(acc[e], p.C + o);
+    }
+}
+
+// Store NQ groups of four registers of a block, the first one group q0 (TR layout; a partial last block of channels as with EDGE_COLUMNS
+// above).
+template <int NQ>
+__device__ __forceinline__ void dg_mfma_store_quads(const DgProblem &p, const dg_v4i (&acc)[NQ], int q0, int mb, int nb, int lane, float sc)
+{
+    if (p.Qp) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) dg_mfma_requant_quad(p, acc[q], q0 + q, mb, nb, lane, sc);
+        return;
+    }
+    const int r = lane & 31, h = lane >> 5;
+    const int colb = __builtin_amdgcn_readfirstlane(mb), rowb = __builtin_amdgcn_readfirstlane(nb), row0 = rowb + 8 * q0;
+    if (colb + r >= p.M) return;                          // (group q: rows 8 q + 4 h ... + 3 of the block, this lane's)
+    if (dg_mfma_rows_whole(p.stride_cn, p.stride_cm, rowb, p.N)) {
+        const int64_t base = (int64_t)colb * p.stride_cm + (int64_t)row0 * p.stride_cn;
+        const int rs = (int)p.stride_cn, off0 = r * (int)p.stride_cm + 4 * h * rs;
+        if (p.scale) {
+            float *out = p.Cf + base;
+#pragma unroll
+            for (int e = 0; e < 4 * NQ; ++e) __builtin_nontemporal_store((float)acc[e / 4][e % 4] * sc, out + (off0 + (8 * (e / 4) + e % 4) * rs));
+        } else {
+            int32_t *out = p.C + base;
+#pragma unroll
+            for (int e = 0; e < 4 * NQ; ++e) __builtin_nontemporal_store(acc[e / 4][e % 4], out + (off0 + (8 * (e / 4) + e % 4) * rs));
+        }
+        return;
+    }
+    const int64_t first = (int64_t)(colb + r) * p.stride_cm + (int64_t)(row0 + 4 * h) * p.stride_cn;
+#pragma unroll
+    for (int e = 0; e < 4 * NQ; ++e) {
+        const int k = 8 * (e / 4) + e % 4;
+        if (row0 + 4 * h + k >= p.N) continue;
+        const int64_t o = first + k * p.stride_cn;
+        if (p.scale) __builtin_nontemporal_store((float)acc[e / 4][e % 4] * sc, p.Cf + o);
+        else __builtin_nontemporal_store(acc[e / 4][e % 4], p.C + o);
     }
 }
 

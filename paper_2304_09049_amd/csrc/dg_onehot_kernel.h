@@ -87,6 +87,7 @@ struct Args {
     uint32_t band_tiles;
     // dg_sparse_staged_kernel.h: what was added to every table entry (the sums start at minus this per position of K)
     int32_t bias;
+    uint32_t x_bytes;        // and the size of the packed activations
 };
 
 struct SplitArgs {
@@ -256,31 +257,17 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 // its own copy, so no barrier is involved (LDS operations of one wavefront execute in order).
 // (NIB, BITS = 24: the same 128 bytes hold the 16 rows low[w], then the 16 rows high[w] -- a position's two rows go to
 // registers that are not neighbours, so they are two 4-byte reads at one address, the second 64 bytes further.)
-// HIGH: where the rows high[w] begin, in bytes.  More than 1020 and no multiple of 256 keeps the compiler from reading a
-// position's two rows with one instruction, whose two registers then have to be moved to their places -- 8 to 12 moves per
-// step, each waiting for its read.  The staged kernel measured with its table laid out so (4-bit codes, both sides on one card):
-// 14x14x256 -> 256 3x3 at batch 8 10.3 -> 9.8 us, 7x7x512 -> 512 3x3 at batch 32 19.9 -> 19.1, 28x28x512 -> 128 at batch 16 9.1 ->
-// 8.8, the large layers bound by the matrix pipe the same (56x56x256 -> 256 3x3 at batch 16 95.9, 95.2).
-template <bool NIB, int HIGH = 64>
+template <bool NIB>
 __device__ __forceinline__ void sparse_fill_entry(uint2 *table, const Pools &pl, int i)
 {
     if (NIB) {
-        ((uint32_t *)table)[i] = pl.w[i], ((uint32_t *)table)[HIGH / 4 + i] = pl.w[16 + i];
+        ((uint32_t *)table)[i] = pl.w[i], ((uint32_t *)table)[16 + i] = pl.w[16 + i];
         return;
     }
     const int c0 = i & 3, c1 = i >> 2;
     const uint32_t r0 = c0 == 0 ? pl.w[0] : (c0 == 1 ? pl.w[1] : (c0 == 2 ? pl.w[2] : pl.w[3]));
     const uint32_t r1 = c1 == 0 ? pl.w[0] : (c1 == 1 ? pl.w[1] : (c1 == 2 ? pl.w[2] : pl.w[3]));
     table[i] = make_uint2(r0, r1);
-}
-
-// Two-plane tables: the row pairs of the high plane, pool words 4 ... 7, behind the low plane's 16 entries.
-__device__ __forceinline__ void sparse_fill_high_entry(uint2 *table, const Pools &pl, int i)
-{
-    const int c0 = i & 3, c1 = i >> 2;
-    const uint32_t r0 = c0 == 0 ? pl.w[4] : (c0 == 1 ? pl.w[5] : (c0 == 2 ? pl.w[6] : pl.w[7]));
-    const uint32_t r1 = c1 == 0 ? pl.w[4] : (c1 == 1 ? pl.w[5] : (c1 == 2 ? pl.w[6] : pl.w[7]));
-    table[16 + i] = make_uint2(r0, r1);
 }
 
 template <bool NIB = false>
@@ -318,6 +305,11 @@ __device__ __forceinline__ void sparse_row_offsets(uint32_t v, uint32_t &e, uint
 }
 
 // Four (NIB: eight) pairs of rows read from the table into their places among the operands.
+// HIGH: where the rows high[w] begin, in bytes.  More than 1020 and no multiple of 256 keeps the compiler from reading a
+// position's two rows with one instruction, whose two registers then have to be moved to their places -- 8 to 12 moves per
+// step, each waiting for its read.  The staged kernel measured with its table laid out so (4-bit codes, both sides on one card):
+// 14x14x256 -> 256 3x3 at batch 8 10.3 -> 9.8 us, 7x7x512 -> 512 3x3 at batch 32 19.9 -> 19.1, 28x28x512 -> 128 at batch 16 9.1 ->
+// 8.8, the large layers bound by the matrix pipe the same (56x56x256 -> 256 3x3 at batch 16 95.9, 95.2).
 template <bool NIB, int HIGH = 64>
 __device__ __forceinline__ void sparse_read_rows(const uint2 *table, uint32_t e, uint32_t o, v8i &even, v8i &odd)
 {
@@ -348,13 +340,13 @@ __device__ __forceinline__ void sparse_dense_rows(const uint2 *rows, uint32_t w0
 // at a barrier before the first read.  A read's address is then nothing but the 4-bit index times 8, and with the
 // indices kept pre-multiplied, a byte each, it is one bit-field extract per read (three instructions per read otherwise:
 // shift, mask, add the wavefront's table base).
-template <bool NIB = false, int HIGH = 64>
+template <bool NIB = false>
 __device__ __forceinline__ void sparse_fill_table(uint2 *table, const Pools &pl, int tid)
 {
-    if (tid < 16) sparse_fill_entry<NIB, HIGH>(table, pl, tid);
+    if (tid < 16) sparse_fill_entry<NIB>(table, pl, tid);
 }
 
-template <bool NIB = false, int HIGH = 64>
+template <bool NIB = false>
 __device__ __forceinline__ void sparse_dense_rows_shared(const uint2 *table, uint32_t w0, uint32_t w1, uint32_t pick, v8i &even, v8i &odd)
 {
     uint32_t e, o;
@@ -362,7 +354,7 @@ __device__ __forceinline__ void sparse_dense_rows_shared(const uint2 *table, uin
     // (kept as they are: a byte of them IS an LDS offset; left to itself the compiler folds the multiplication into a
     // shift and a mask per read)
     asm volatile("" : "+v"(e), "+v"(o));
-    sparse_read_rows<NIB, HIGH>(table, e, o, even, odd);
+    sparse_read_rows<NIB>(table, e, o, even, odd);
 }
 
 // Position bookkeeping shared by the two kernels: output column n -> image coordinates, and the filter tap of a chunk.

@@ -11,39 +11,172 @@
 // (lane l's 16 bytes land at the instruction's LDS base + 16 l; no registers are held while they are in flight), into
 // staging rows of the wavefront's own, from which lane (r, half) reads its 8 bytes per 64 positions of K.  Staging
 // rows belong to one wavefront, so no barrier is involved: a wavefront waits for its own loads (vmcnt) before it reads
-// a run, and runs alternate between two buffers, fetched two ahead.
+// a run, and runs go round in two or three buffers.
 // The multiplication is one software pipeline over all of K: the dense operands of a step are made between the matrix
-// instructions of the step before, across chunks, runs and filter taps alike.
+// instructions of the step before (or the one before that), and the words they are made from are read from LDS a step or more earlier still, across
+// chunks, runs and filter taps alike.
 //
-// A run is 128 positions of K inside one filter tap (Cin % 128 == 0; Cin % 128 == 64: HALF below).  A tap outside the image is fetched from a
-// clamped address and contributes nothing because the kept bytes of its lanes are zero.
+// A run is 128 positions of K inside one filter tap (Cin % 128 == 0; Cin % 128 == 64: HALF below).  A tap outside the image is fetched from
+// wherever it would lie (outside the tensor: as zeros) and contributes nothing because the kept bytes of its lanes are zero.
+//
+// Where the time goes (timestamps per wavefront at 100 MHz, us; before: the words read a step later, every operand from pairs, the table
+// filled before the first load, sums met by atomic additions, two wavefronts of four storing):
+//   28x28x256 -> 256 3x3 at batch 8, two planes, 32 x 128 by four   start to first words 3.0 -> 2.4, the walk over K 10.3 -> 9.1,
+//                                                                   the end 2.3 -> 2.3; kernel 17.7 -> 15.4, the call 20.2 -> 18.2
+//   8192 x 256 x 8192, 32 x 128 by four                             the walk 34.0 -> 29.7 thousand cycles of the 32.8 thousand its
+//                                                                   matrix instructions take two wavefronts: at 1.7 GHz, what the power allows
+// The walk is bound by the matrix pipe where two wavefronts share a SIMD and the operands serve four pixel blocks or more; a lone wavefront, whose other
+// instructions do not all hide behind its own matrix instructions, spends about 0.48 us per run beside them.
 #pragma once
 
 #include "dg_lds_dma.h"
 #include "dg_onehot_kernel.h"
 
+#include <type_traits>
+
 namespace dgoh {
 
-// The dense operands of all WM weight blocks for word `t` of `w` (as sparse_dense_rows_shared, but with the opaque
-// statement that keeps the indices pre-multiplied NOT volatile, so that the scheduler may move these instructions
-// between matrix instructions).
-template <bool NIB, bool TWO, int HIGH, int WM, class W>
-__device__ __forceinline__ void dense_rows_movable(const uint2 *table, const W &w, int t, uint32_t pick, v8i (&out)[WM][2])
-{
-#pragma unroll
-    for (int u = 0; u < (TWO ? 1 : WM); ++u) {
-        const uint32_t w0 = t ? w.ca[u].y : w.ca[u].x, w1 = t ? w.ca1[u].y : w.ca1[u].x;
+// The table of rows in LDS, one for the workgroup, in one of two forms.
+//
+// PairTable: 16 entries of two rows (NIB: 16 low rows, 16 high rows), as in dg_onehot_kernel.h.  A step's operands are 16 vector instructions
+// (NIB 13) and 8 reads (16) at 4-bit indices, without bank conflicts: little for LDS, much for the vector units.
+template <bool NIB, bool TWO>
+struct PairTable {
+    static constexpr int HIGH = NIB ? 1040 : 128;           // the high rows (the high plane's pairs) begin here
+    static constexpr int BYTES = NIB ? HIGH + 64 + 16 : (TWO ? 256 : 128);
+    // entry i as thread i of 16 reads it from the kernel's arguments (vector loads, asked for at the kernel's start), and as it writes it
+    struct Entry {
+        uint32_t q[4];
+    };
+    static __device__ __forceinline__ Entry load(const Pools &pl, int i)
+    {
+        Entry e;
+        i &= 15;
+        e.q[0] = pl.w[NIB ? i : i & 3], e.q[1] = pl.w[NIB ? 16 + i : i >> 2];
+        e.q[2] = TWO ? pl.w[4 + (i & 3)] : 0, e.q[3] = TWO ? pl.w[4 + (i >> 2)] : 0;
+        return e;
+    }
+    static __device__ __forceinline__ void wait(Entry &e) { asm volatile("" : "+v"(e.q[0]), "+v"(e.q[1]), "+v"(e.q[2]), "+v"(e.q[3])); }
+    static __device__ __forceinline__ void store(char *table, const Entry &e, int i)
+    {
+        if (i >= 16) return;
+        if constexpr (NIB) {
+            *(uint32_t *)(table + 4 * i) = e.q[0], *(uint32_t *)(table + HIGH + 4 * i) = e.q[1];
+        } else {
+            *(uint2 *)(table + 8 * i) = make_uint2(e.q[0], e.q[1]);
+            if (TWO) *(uint2 *)(table + HIGH + 8 * i) = make_uint2(e.q[2], e.q[3]);
+        }
+    }
+    static __device__ __forceinline__ uint32_t copy(int) { return 0; }
+    static __device__ __forceinline__ void read(const char *table, uint32_t, uint32_t w0, uint32_t w1, uint32_t pick, v8i (&lo)[2], v8i (&hi)[2])
+    {
         uint32_t e, o;
         sparse_row_offsets<NIB>(__builtin_amdgcn_perm(w1, w0, pick), e, o);
-        asm("" : "+v"(e), "+v"(o));
-        sparse_read_rows<NIB, HIGH>(table, e, o, out[u][0], out[u][1]);
-        if constexpr (TWO) sparse_read_rows<false>(table + 16, e, o, out[1][0], out[1][1]);      // (the same row block, the high plane)
+        asm("" : "+v"(e), "+v"(o));                         // (kept pre-multiplied, a byte each, and movable between matrix instructions)
+        sparse_read_rows<NIB, HIGH>((const uint2 *)table, e, o, lo[0], lo[1]);
+        if constexpr (TWO) sparse_read_rows<false>((const uint2 *)(table + HIGH), e, o, hi[0], hi[1]);
     }
-}
+    static constexpr int BESIDE = NIB ? 30 : (TWO ? 34 : 26);      // instructions of a step's operands
+};
+
+// QuadTable: 256 entries.  2-bit codes: entry i, 16 bytes, holds the rows of FOUR codes -- those of bits 0-1,
+// 4-5, 2-3, 6-7 of i -- so that one 16-byte read fills half an operand; TWO: the high plane's entries PLANE bytes behind.  NIB: entry
+// i, 8 bytes, the low rows of two 4-bit slots (a packed byte), their high rows PLANE bytes behind.  A step's operands are 12 vector
+// instructions (NIB 9) and 4 reads (8): beside a matrix instruction (32 cycles) four vector instructions are free, six make it 36.5
+// and eight 44, with any number of wavefronts (measured, registers only).  The reads' indices are random, so an entry is held COPIES times, lane l
+// reading copy l % COPIES: 16 lanes are served at a time, and with one copy the fullest of the 16 places in the banks gets three of them
+// on average, with four two.
+template <bool NIB, bool TWO, int COPIES>
+struct QuadTable {
+    static constexpr int ENTRY = NIB ? 8 : 16;
+    static constexpr int SHIFT = (NIB ? 3 : 4) + (COPIES == 8 ? 3 : (COPIES == 4 ? 2 : (COPIES == 2 ? 1 : 0)));      // log2 of an entry's copies
+    static constexpr int PLANE = 256 << SHIFT;
+    static constexpr int BYTES = PLANE * (NIB || TWO ? 2 : 1);
+    static_assert((ENTRY * COPIES) == (1 << SHIFT), "COPIES: 1, 2, 4 or 8");
+
+    // Entry i as thread i of 256 reads it from the kernel's arguments (vector loads: asked for at the kernel's start, they come with the
+    // other arguments; `wait` before any load that is not waited for by the compiler), and as it writes it.
+    struct Entry {
+        uint32_t q[NIB || TWO ? 2 : 1][4];
+    };
+    static __device__ __forceinline__ Entry load(const Pools &pl, int i)
+    {
+        Entry e;
+#pragma unroll
+        for (int plane = 0; plane < (NIB || TWO ? 2 : 1); ++plane) {
+            if constexpr (NIB) {
+                e.q[plane][0] = pl.w[16 * plane + (i & 15)], e.q[plane][1] = pl.w[16 * plane + (i >> 4)];
+                e.q[plane][2] = e.q[plane][3] = 0;
+            } else {
+                e.q[plane][0] = pl.w[4 * plane + (i & 3)], e.q[plane][1] = pl.w[4 * plane + ((i >> 4) & 3)];
+                e.q[plane][2] = pl.w[4 * plane + ((i >> 2) & 3)], e.q[plane][3] = pl.w[4 * plane + (i >> 6)];
+            }
+        }
+        return e;
+    }
+    static __device__ __forceinline__ void wait(Entry &e)
+    {
+#pragma unroll
+        for (int plane = 0; plane < (NIB || TWO ? 2 : 1); ++plane)
+            asm volatile("" : "+v"(e.q[plane][0]), "+v"(e.q[plane][1]), "+v"(e.q[plane][2]), "+v"(e.q[plane][3]));
+    }
+    static __device__ __forceinline__ void store(char *table, const Entry &e, int i)
+    {
+        const int turn = (i & 63) / (NIB ? 32 / COPIES : 16 / COPIES);        // (neighbouring threads on different banks)
+#pragma unroll
+        for (int plane = 0; plane < (NIB || TWO ? 2 : 1); ++plane) {
+            char *entry = table + plane * PLANE + (i << SHIFT);
+#pragma unroll
+            for (int c = 0; c < COPIES; ++c) {
+                if constexpr (NIB) *(uint2 *)(entry + ((c + turn) & (COPIES - 1)) * 8) = make_uint2(e.q[plane][0], e.q[plane][1]);
+                else *(uint4 *)(entry + ((c + turn) & (COPIES - 1)) * 16) = make_uint4(e.q[plane][0], e.q[plane][1], e.q[plane][2], e.q[plane][3]);
+            }
+        }
+    }
+
+    static __device__ __forceinline__ uint32_t shifted(uint32_t v, int by) { return by >= 0 ? v << by : v >> -by; }
+
+    // The dense operands of the two instructions that consume one packed word per lane half (w0, w1, pick: sparse_dense_rows in
+    // dg_onehot_kernel.h); `copy`: this lane's copy, as a byte offset.
+    static __device__ __forceinline__ void read(const char *table, uint32_t copy, uint32_t w0, uint32_t w1, uint32_t pick, v8i (&lo)[2], v8i (&hi)[2])
+    {
+        constexpr uint32_t INDEX = 255u << SHIFT;
+        const uint32_t v = __builtin_amdgcn_perm(w1, w0, pick);
+        if constexpr (NIB) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const char *x = table + ((shifted(v, SHIFT - 8 * b) & INDEX) | copy);
+                const uint2 l = *(const uint2 *)x, h = *(const uint2 *)(x + PLANE);
+                lo[0][2 * b] = (int)l.x, lo[0][2 * b + 1] = (int)l.y;
+                lo[1][2 * b] = (int)h.x, lo[1][2 * b + 1] = (int)h.y;
+            }
+        } else {
+            // the even (odd) codes of a lane's two 16-bit halves, each half's four brought together as an index: codes 0, 2 (1, 3) stay
+            // 4 bits apart and codes 4, 6 (5, 7) go between them
+            constexpr uint32_t M = (uint32_t)(0x33333333ull << SHIFT);
+            uint32_t e = (shifted(v, SHIFT) & M) | (shifted(v, SHIFT - 6) & ~M);
+            uint32_t o = (shifted(v, SHIFT - 2) & M) | (shifted(v, SHIFT - 8) & ~M);
+            asm("" : "+v"(e), "+v"(o));                     // (kept as they are: an index in its place, for both halves)
+            const uint32_t at[4] = {(e & INDEX) | copy, ((e >> 16) & INDEX) | copy, (o & INDEX) | copy, ((o >> 16) & INDEX) | copy};
+#pragma unroll
+            for (int plane = 0; plane < (TWO ? 2 : 1); ++plane) {
+                v8i(&out)[2] = plane ? hi : lo;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint4 q = *(const uint4 *)(table + at[i] + plane * PLANE);
+                    const int d = 4 * (i & 1);
+                    out[i / 2][d] = (int)q.x, out[i / 2][d + 1] = (int)q.y, out[i / 2][d + 2] = (int)q.z, out[i / 2][d + 3] = (int)q.w;
+                }
+            }
+        }
+    }
+    static __device__ __forceinline__ uint32_t copy(int lane) { return (lane & (COPIES - 1)) * ENTRY; }
+    static constexpr int BESIDE = NIB ? 17 : (TWO ? 20 : 16);      // instructions of a step's operands
+};
 
 // SKW = 1: a wavefront walks all of K.  SKW = 2 or 4 (layers whose tiles alone would leave SIMDs idle): SKW wavefronts
-// of the workgroup share a tile and split K between them (run by run, or in contiguous shares); their sums meet in LDS by integer atomics
-// (exact in any order) and each of them stores a share of the tile's blocks, as in dg_onehot_kernel.h.
+// of the workgroup share a tile and split K between them (run by run, or in contiguous shares); their sums meet in LDS and each of them
+// adds up and stores a share of the tile.
 //
 // HALF (unshared tiles, Cin % 128 == 64): a filter tap is an odd number of
 // 64-position chunks, so the two chunks of a run may lie in different taps -- two different pixels for the loader's two
@@ -54,7 +187,17 @@ __device__ __forceinline__ void dense_rows_movable(const uint2 *table, const W &
 //
 // TWO: entries beyond int8, T = 256 * hi + lo (dg_onehot_kernel.h).  The planes take the places of two weight row blocks: a
 // tile is ONE block of 32 rows, whose words are staged once and whose table indices are worked out once for both planes'
-// dense operands (the second plane's rows lie 128 bytes behind the first's); pool words 4 ... 7 are the high plane's rows.
+// dense operands; pool words 4 ... 7 are the high plane's rows.
+// f(0), f(1), ... f(N - 1), each argument a constant
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void dg_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        dg_for<N, I + 1>(f);
+    }
+}
+
 template <int WM, int WN, int SKW, bool TURNS, bool HALF, bool NIB, bool TWO>
 __global__ void __launch_bounds__(256, 2)
 smfmac_staged_kernel(Args a)
@@ -66,33 +209,38 @@ smfmac_staged_kernel(Args a)
     constexpr int BUF = ROWS * 32;                          // bytes of one wavefront's buffer
     constexpr int TPW = 4 / SKW;                           // tiles per workgroup
     constexpr int NB = RB * WN;                            // 32x32 output blocks per tile
+    constexpr int MN = WM * WN;                            // matrix instructions per parity of a step
+    // how many steps ahead the dense operands are made, and how many buffers the runs go round in (three on the wider tiles too: 1 % slower)
+    constexpr int AHEAD = MN <= 2 ? 2 : 1, SETS = AHEAD == 2 ? 4 : 2;
+    constexpr int BUFS = WN <= 2 ? 3 : 2;
+    constexpr bool LATE = WM == 2 && !TWO;                   // (that tile has no registers for a chunk's words beside the next one's)
+    // Which table: on narrow tiles, whose operands serve few pixels, its random reads keep LDS busier than the vector instructions they
+    // spare are worth (28x28x128 -> 128 3x3 at batch 8, 4-bit codes, 32 x 64 by four: 9.9 us with quads, 9.2 with pairs); with 4-bit slots on
+    // the shared and the 64-row tiles too (28x28x256 -> 256 3x3 at batch 8, 32 x 128 by four: 21.5, 19.5).  On the others quads are ahead:
+    // 8192-cube 740 us with pairs, 706 with quads; 56x56x256 -> 256 3x3 at batch 16, 4-bit, 32 x 224: 98.2, 96.8.
+    constexpr bool QUADS = WN >= 4 && !(NIB && (SKW > 1 || WM == 2));
+    constexpr int LOADS = RB + WN;                          // a run's loads
+    constexpr int REGION = SKW > 1 && NB * 4096 > BUFS * BUF ? NB * 4096 : BUFS * BUF;      // a wavefront's: its buffers, then its sums
+    typedef std::conditional_t<QUADS, QuadTable<NIB, TWO, (TWO && SKW > 1 ? 2 : 4)>, PairTable<NIB, TWO>> Table;
+    // A wavefront's staging rows [buffer][block * 64 + slot] which the sums of a
+    // wavefront that shares its tile replace, [block][group of four sum registers][lane]; then the table of rows.
     // A block of 32 rows is 64 slots of 16 bytes, slot j = what loader lane j fetched: row j / 2, segment
     // (j % 2) ^ (j / 16 % 2) of the row's 32 bytes -- the exchange puts rows r and r + 8 of a segment on different
     // LDS banks, which leaves the consumers' reads (32 rows of one segment) two to a bank instead of four.
-    // the table of row pairs, one for the workgroup (NIB: the high rows HIGH bytes behind the low ones)
-    constexpr int HIGH = NIB ? 1040 : 64;
-    __shared__ uint2 s_rows[NIB ? (HIGH + 64) / 8 : (TWO ? 32 : 16)];
-    // staging rows [wavefront][buffer][block * 64 + slot]; once the walk over K is over, the same memory holds the
-    // shared tiles' sums [tile][block][sum register][lane]
-    constexpr int STAGE_BYTES = 4 * 2 * BUF, SUM_BYTES = SKW > 1 ? TPW * NB * 4096 : 0;
-    __shared__ uint4 s_mem[(STAGE_BYTES > SUM_BYTES ? STAGE_BYTES : SUM_BYTES) / 16];
-    static_assert(sizeof(s_mem) + sizeof(s_rows) <= 80 * 1024, "two workgroups per compute unit (160 KB of LDS)");
-    int32_t *s_acc = (int32_t *)s_mem;
+    static_assert(4 * REGION + Table::BYTES <= 80 * 1024, "two workgroups per compute unit (160 KB of LDS)");
+    __shared__ uint4 s_mem[(4 * REGION + Table::BYTES) / 16];
+    char *s_table = (char *)s_mem + 4 * REGION;
     // the narrower tiles have the registers for a second set of kept bytes, (0, 1), which spares the odd codes' shift
-    constexpr bool SHIFT_ODD = WM * WN >= 7;
+    constexpr bool SHIFT_ODD = MN >= 7;
     const DgProblem &p = a.p;
+    typename Table::Entry entry = Table::load(a.pools, threadIdx.x);
     dg_fetch_arguments<sizeof(a)>();
+    Table::wait(entry);
     const int lane = threadIdx.x & 63, w4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ks = w4 % SKW, tw = w4 / SKW;                 // this wavefront's share of K, and its tile within the workgroup
     const int64_t my_tile = (int64_t)xcd_contiguous(blockIdx.x, gridDim.x) * TPW + tw;
-    const bool active = my_tile < a.wave_tiles;
-    sparse_fill_table<NIB, HIGH>(s_rows, a.pools, threadIdx.x);
-    if constexpr (TWO) {
-        if (threadIdx.x >= 16 && threadIdx.x < 32) sparse_fill_high_entry(s_rows, a.pools, threadIdx.x - 16);
-    }
-    __syncthreads();                                       // (every wavefront of the workgroup, also one without a tile)
-    if (SKW == 1 && !active) return;                       // whole wavefronts leave; no barrier follows on this path
-    const int64_t wave_tile = active ? my_tile : 0;        // (an idle wavefront of a shared workgroup adds nothing)
+    const bool active = my_tile < a.wave_tiles;             // (a wavefront without a tile only joins the barriers)
+    const int64_t wave_tile = active ? my_tile : 0;
     const int r = lane & 31, h = lane >> 5;
     // Tiles are numbered in bands of 2^band_log2 pixel tiles; inside a band groups of 2^m_log2 channel tiles (the four
     // wavefronts of a workgroup, which then share their pixels' loads) follow each other along the pixels first.  The
@@ -123,75 +271,54 @@ smfmac_staged_kernel(Args a)
     // cache gives (3x3 layers 7 - 14 % slower).
     static_assert(!TURNS || SKW > 1, "taking turns is for wavefronts that share a tile");
     constexpr int stride = TURNS ? SKW : 1;
-    const int runs = HALF ? (p.K + 127) / 128 : p.K / 128, share = (runs + SKW - 1) / SKW;
+    const int runs = HALF ? (p.K + 127) / 128 : p.K / 128;
     const int chunks = p.K / 64, cpt = p.Cin / 64;          // HALF: 64-position chunks in all, and per filter tap
-    const int g0 = min(TURNS ? ks : ks * share, runs), g1 = !active ? g0 : (TURNS ? runs : min(g0 + share, runs));
+    const int g0 = TURNS ? min(ks, runs) : runs * ks / SKW, g1 = !active ? g0 : (TURNS ? runs : runs * (ks + 1) / SKW);
     const int runs_per_tap = cq / 32;
     const int tap0 = (int)fdiv((uint32_t)g0, a.div_runs), rt0 = g0 - tap0 * runs_per_tap;
 
-    // as a loader, this lane fetches 16-byte segment lseg of row lrow of every 32-row block
+    // ---- the loader's side: as a loader, this lane fetches 16-byte segment lseg of row lrow of every 32-row block.  Both operands are
+    // read as buffers, whose bounds the hardware checks: rows beyond M, a tap outside the tensor and runs past the end read as zeros
+    // without a clamp (a tap outside its image, but inside the tensor, reads whatever lies there: its kept bytes are zero).
     const int lrow = lane >> 1, lseg = (lane & 1) ^ ((lane >> 4) & 1);
-    const uint8_t *w_ld[RB];
+    const uint32_t row_bytes = (uint32_t)p.K / 4;
+    const v4i w_buffer = dg_buffer(p.Wp + (int64_t)m0 * row_bytes, (uint32_t)min(p.M - m0, RB * 32) * row_bytes);
+    const v4i x_buffer = dg_buffer(p.Xp, a.x_bytes);        // (the host sends inputs below 2^31 bytes)
+    uint32_t w_ld[RB], x_ld[WN];
 #pragma unroll
-    for (int bm = 0; bm < RB; ++bm)
-        w_ld[bm] = p.Wp + (int64_t)min(m0 + bm * 32 + lrow, p.M - 1) * (p.K / 4) + (HALF ? 0 : lseg * 16);
-    int32_t x_ld[WN];                                       // (32-bit offsets: the host sends inputs below 2^31 bytes)
+    for (int bm = 0; bm < RB; ++bm) w_ld[bm] = (uint32_t)(bm * 32 + lrow) * row_bytes + (HALF ? 0 : lseg * 16);
 #pragma unroll
     for (int bn = 0; bn < WN; ++bn)
-        x_ld[bn] = (int32_t)make_column(p, a.div_ow, a.div_oh, n0 + bn * 32 + lrow, cq, HALF ? 0 : lseg * 16).off0;
-    const int images = (int)fdiv(fdiv((uint32_t)p.N, a.div_ow), a.div_oh);
-    const int32_t x_last = images * p.H * p.W * cq - 16;    // the last 16 bytes of the packed activations
-    // as a consumer, it is row / pixel r (lane half h) of every block: its slot of segment s is slot0 ^ s
-    const int slot0 = 2 * r + ((r >> 3) & 1);
-    Column col[WN];
-#pragma unroll
-    for (int bn = 0; bn < WN; ++bn) col[bn] = make_column(p, a.div_ow, a.div_oh, n0 + bn * 32 + r, cq, 0);
-
-    v16i acc[WM][WN];
-#pragma unroll
-    for (int bm = 0; bm < WM; ++bm)
-#pragma unroll
-        for (int bn = 0; bn < WN; ++bn)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[bm][bn][e] = 0;
-    float sc_cols[RB];
-    dg_mfma_column_scales<RB, true>(p, m0, lane, sc_cols);
-
-    // ---- the loader's side: runs are fetched two ahead of the one being multiplied
-    const char *stage = (const char *)s_mem + w4 * (2 * BUF);
-    const uint32_t stage_lds = dg_lds_address(s_mem) + w4 * (2 * BUF);
-    // filter tap and byte within the pixel of the run fetched next
-    int kh = (int)fdiv((uint32_t)tap0, a.div_kw), kw = tap0 - kh * p.KW, cib = rt0 * 32, fetched = g0, fetches = 0;
-    auto fetch = [&]() {                                    // this wavefront's next run, into the buffer of its parity
-        const int g = min(fetched, runs - 1);               // (past the end: a run inside the tensors, unused)
-        const uint32_t dst = stage_lds + ((TURNS ? fetches : fetched) & 1) * BUF;
+        x_ld[bn] = (uint32_t)make_column(p, a.div_ow, a.div_oh, n0 + bn * 32 + lrow, cq, HALF ? 0 : lseg * 16).off0;
+    const char *stage = (const char *)s_mem + w4 * REGION;
+    const uint32_t stage_lds = dg_lds_address(s_mem) + w4 * REGION;
+    // filter tap and byte within the pixel of the run fetched next, and its buffer
+    int kh = (int)fdiv((uint32_t)tap0, a.div_kw), kw = tap0 - kh * p.KW, cib = rt0 * 32, fetched = g0;
+    uint32_t fetch_to = 0;
+    auto next_buffer = [](uint32_t b) { return BUFS == 2 ? BUF - b : (b == (BUFS - 1) * BUF ? 0u : b + BUF); };
+    auto fetch = [&]() {                                    // this wavefront's next run, into the buffer whose turn it is
+        const uint32_t dst = stage_lds + fetch_to;
+        fetch_to = next_buffer(fetch_to);
+        const bool live = fetched < g1;                     // (uniform; past the end: outside both buffers)
         if constexpr (HALF) {
             // this lane's chunk of the run: 2 g + lseg (past the end of K: the chunk before), its tap and place in it
-            const int c0 = 2 * g, c1 = min(2 * g + 1, chunks - 1);
+            const int c0 = 2 * fetched, c1 = min(2 * fetched + 1, chunks - 1);
             auto pixel_offset = [&](int c) {
                 const int tap = (int)fdiv((uint32_t)c, a.div_cpt), th = (int)fdiv((uint32_t)tap, a.div_kw);
-                return (int32_t)((th * p.W + (tap - th * p.KW)) * cq + (c - tap * cpt) * 16);
+                return live ? (uint32_t)((th * p.W + (tap - th * p.KW)) * cq + (c - tap * cpt) * 16) : 0x80000000u;
             };
-            const int32_t off0 = pixel_offset(c0), off1 = pixel_offset(c1);
-            const int32_t w_off = (lseg ? c1 : c0) * 16, x_off = lseg ? off1 : off0;
-#pragma unroll
-            for (int bm = 0; bm < RB; ++bm) dg_load16_to_lds(w_ld[bm] + w_off, dst + bm * 1024);
-#pragma unroll
-            for (int bn = 0; bn < WN; ++bn) dg_load16_to_lds(p.Xp, max(0, min(x_ld[bn] + x_off, x_last)), dst + (RB + bn) * 1024);
-            ++fetches, ++fetched;
+            const uint32_t off0 = pixel_offset(c0), off1 = pixel_offset(c1);
+            const uint32_t w_off = live ? (uint32_t)(lseg ? c1 : c0) * 16 : 0x80000000u, x_off = lseg ? off1 : off0;
+            dg_for<RB>([&](auto bm) { dg_load16_to_lds<bm * 1024>(w_buffer, w_ld[bm] + w_off, 0u, dst); });
+            dg_for<WN>([&](auto bn) { dg_load16_to_lds<(RB + bn) * 1024>(x_buffer, x_ld[bn] + x_off, 0u, dst); });
+            ++fetched;
             return;
         }
-#pragma unroll
-        for (int bm = 0; bm < RB; ++bm) dg_load16_to_lds(w_ld[bm] + g * 32, dst + bm * 1024);
-        const int32_t tap_off = (kh * p.W + kw) * cq + cib;
-#pragma unroll
-        for (int bn = 0; bn < WN; ++bn) {
-            // (a tap outside the image or past the end: any address inside the tensor will do; the kept bytes of a
-            // lane outside the image are zero)
-            const int32_t off = max(0, min(x_ld[bn] + tap_off, x_last));
-            dg_load16_to_lds(p.Xp, off, dst + (RB + bn) * 1024);
-        }
-        ++fetches;
+        const uint32_t w_off = live ? (uint32_t)fetched * 32 : 0x80000000u;
+        dg_for<RB>([&](auto bm) { dg_load16_to_lds<bm * 1024>(w_buffer, w_ld[bm], w_off, dst); });
+        const uint32_t tap_off = live ? (uint32_t)((kh * p.W + kw) * cq + cib) : 0x80000000u;
+        // (the whole offset in the register that is checked: a tap above the first image is "negative")
+        dg_for<WN>([&](auto bn) { dg_load16_to_lds<(RB + bn) * 1024>(x_buffer, x_ld[bn] + tap_off, 0u, dst); });
         fetched += stride;
         cib += 32 * stride;
         if constexpr (TURNS) {
@@ -204,84 +331,122 @@ smfmac_staged_kernel(Args a)
             }
         }
     };
+    if (g0 < g1) {                                          // (uniform; the first runs are asked for before anything else is made ready)
+        fetch();
+        fetch();
+    }
+    Table::store(s_table, entry, threadIdx.x);
+    if (BUFS > 2 && g0 < g1) {                              // (uniform)
+#pragma unroll
+        for (int i = 2; i < BUFS; ++i) fetch();
+    }
 
-    // ---- the consumer's side.  Words of a chunk (64 positions): of weight row r both halves' 8 bytes, of pixel r its
-    // own half's.  Lane offsets into a buffer, for the run's two chunks:
+    // ---- the consumer's side: row / pixel r (lane half h) of every block; its slot of segment s is slot0 ^ s
+    const int slot0 = 2 * r + ((r >> 3) & 1);
+    const uint32_t copy = Table::copy(lane);
+    // which rows (bits 0 ... 15) and columns (16 ... 31) of the filter window lie inside the image for pixel r of a block (none beyond N)
+    uint32_t window[WN];
+    int taps_in[WN];
+#pragma unroll
+    for (int bn = 0; bn < WN; ++bn) {
+        const Column c = make_column(p, a.div_ow, a.div_oh, n0 + bn * 32 + r, cq, 0);
+        const int h0 = min(max(0, -c.ih0), 15), h1 = c.ok ? max(h0, min(p.KH, p.H - c.ih0)) : h0;
+        const int w0 = min(max(0, -c.iw0), 15), w1 = max(w0, min(p.KW, p.W - c.iw0));
+        window[bn] = (((1u << (h1 - h0)) - 1u) << h0) | (((1u << (w1 - w0)) - 1u) << (16 + w0));
+        taps_in[bn] = (h1 - h0) * (w1 - w0);
+    }
+
+    v16i acc[WM][WN];
+#pragma unroll
+    for (int bm = 0; bm < WM; ++bm)
+#pragma unroll
+        for (int bn = 0; bn < WN; ++bn)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[bm][bn][e] = 0;
+    float sc_cols[RB];
+    dg_mfma_column_scales<RB, true>(p, m0, lane, sc_cols);
+
+    // Words of a chunk (64 positions): of weight row r both halves' 8 bytes, of pixel r its own half's.  Lane offsets into a buffer,
+    // for the run's two chunks:
     const int w_at[2] = {slot0 * 16, (slot0 ^ 1) * 16}, x_at[2] = {slot0 * 16 + h * 8, (slot0 ^ 1) * 16 + h * 8};
-    struct Words2 {
-        uint2 ca[RB], ca1[RB], cb[WN];
+    struct Weights {
+        uint2 ca[RB], ca1[RB];
     };
-    auto read_words = [&](Words2 &w, int buf, int s) {
-        const char *src = stage + buf * BUF;
+    struct Pixels {
+        uint2 cb[WN];
+    };
+    auto read_weights = [&](Weights &w, uint32_t buf, int s) {
+        const char *src = stage + buf;
 #pragma unroll
         for (int bm = 0; bm < RB; ++bm) {
             const uint4 q = *(const uint4 *)(src + bm * 1024 + w_at[s]);
             w.ca[bm] = make_uint2(q.x, q.y), w.ca1[bm] = make_uint2(q.z, q.w);
         }
+    };
+    auto read_pixels = [&](Pixels &x, uint32_t buf, int s) {
+        const char *src = stage + buf;
 #pragma unroll
-        for (int bn = 0; bn < WN; ++bn) w.cb[bn] = *(const uint2 *)(src + (RB + bn) * 1024 + x_at[s]);
+        for (int bn = 0; bn < WN; ++bn) x.cb[bn] = *(const uint2 *)(src + (RB + bn) * 1024 + x_at[s]);
     };
     const uint32_t pick = sparse_pick(h);
     auto word = [](const uint2 &v, int t) { return t ? v.y : v.x; };
-    // One step = one word of the chunk: two instructions (even codes, odd codes) per block of the tile, with the dense
-    // operands `next` of the following step -- per weight block a unit of table reads -- made between them.
-    // (see dg_onehot_kernel.h for the index register and the kept bytes)
+    // the dense operands of all weight blocks (TWO: of both planes) for word t
+    auto dense_rows = [&](v8i (&out)[WM][2], const Weights &w, int t) {
+#pragma unroll
+        for (int u = 0; u < RB; ++u) Table::read(s_table, copy, word(w.ca[u], t), word(w.ca1[u], t), pick, out[u], out[TWO ? 1 : u]);
+    };
     v4i ones[WN], ones_odd[SHIFT_ODD ? 1 : WN];
     // which of this lane's pixels see a filter tap: the kept bytes, (1, 0) per position (and (0, 1) for the odd codes),
     // or zeros outside the image (or for a chunk past the end of K)
-    auto kept_bytes = [&](int tap, bool live, v4i (&on)[WN], v4i (&on_odd)[SHIFT_ODD ? 1 : WN]) {
+    auto kept_bytes = [&](int tap, bool live) {
         const int khc = (int)fdiv((uint32_t)tap, a.div_kw), kwc = tap - khc * p.KW;
 #pragma unroll
         for (int bn = 0; bn < WN; ++bn) {
-            const int ih = col[bn].ih0 + khc, iw = col[bn].iw0 + kwc;
-            const bool v = live & col[bn].ok & ((uint32_t)ih < (uint32_t)p.H) & ((uint32_t)iw < (uint32_t)p.W);
-            const int x = v ? 0x00010001 : 0;
-            on[bn] = (v4i){x, x, x, x};
+            const uint32_t v = live ? (window[bn] >> khc) & (window[bn] >> (16 + kwc)) & 1u : 0u;
+            const int x = (int)(v * 0x00010001u);
+            ones[bn] = (v4i){x, x, x, x};
             if constexpr (!SHIFT_ODD) {
-                const int y = v ? 0x01000100 : 0;
-                on_odd[bn] = (v4i){y, y, y, y};
+                const int y = x << 8;
+                ones_odd[bn] = (v4i){y, y, y, y};
             }
         }
     };
-    auto step = [&](const v8i (&dn)[WM][2], const Words2 &w, int t, v8i (&next)[WM][2], const Words2 &nw, int nt,
-                    const v4i (&ones)[WN], const v4i (&ones_odd)[SHIFT_ODD ? 1 : WN]) {
-        constexpr int MN = WM * WN;
-        // the next step's dense operands: written here, spread by the scheduling groups below a few instructions at a
-        // time between this step's matrix instructions, in whose shadow they then issue
-        dense_rows_movable<NIB, TWO, HIGH>(s_rows, nw, nt, pick, next);
+    // One step = one word of the chunk: two instructions (even codes, odd codes) per block of the tile, with the dense operands of
+    // the next step (or the one after) and the reads of later words -- `beside` -- made between them.
+    // (see dg_onehot_kernel.h for the index register and the kept bytes)
+    auto step = [&](const v8i (&dn)[WM][2], const Pixels &x, int t, auto &&beside) {
+        beside();
         int odd_ix[SHIFT_ODD ? WN : 1];
         if constexpr (SHIFT_ODD) {
 #pragma unroll
-            for (int bn = 0; bn < WN; ++bn) odd_ix[bn] = (int)(word(w.cb[bn], t) >> 2);
+            for (int bn = 0; bn < WN; ++bn) odd_ix[bn] = (int)(word(x.cb[bn], t) >> 2);
         }
-        constexpr int PER = ((TWO ? 39 : 31 * WM) + (SHIFT_ODD ? WN : 0) + 2 * MN - 1) / (2 * MN);      // other instructions per matrix instruction
+        constexpr int OTHERS = Table::BESIDE * RB + (SHIFT_ODD ? WN : 0) + (WN + 3) / 2;
+        constexpr int PER = (OTHERS + 2 * MN - 1) / (2 * MN);      // other instructions per matrix instruction
 #pragma unroll
         for (int i = 0; i < 2 * MN; ++i) {
             const int par = i / MN, bm = (i % MN) / WN, bn = i % WN;
             if (par && !SHIFT_ODD)
-                acc[bm][bn] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones_odd[SHIFT_ODD ? 0 : bn], dn[bm][1], acc[bm][bn], (int)word(w.cb[bn], t), 0, 0);
+                acc[bm][bn] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones_odd[SHIFT_ODD ? 0 : bn], dn[bm][1], acc[bm][bn], (int)word(x.cb[bn], t), 0, 0);
             else
                 acc[bm][bn] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones[bn], dn[bm][par], acc[bm][bn],
-                                                                      par ? odd_ix[SHIFT_ODD ? bn : 0] : (int)word(w.cb[bn], t), 0, 0);
+                                                                      par ? odd_ix[SHIFT_ODD ? bn : 0] : (int)word(x.cb[bn], t), 0, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x102, PER, 0);
         }
     };
+    __syncthreads();                                       // (the table)
 
-    if (g0 < g1) {                                          // (uniform; a wavefront without a share of K only joins the barrier)
-        fetch();
-        fetch();
+    if (g0 < g1) {                                          // (uniform; a wavefront without a share of K only joins the barriers)
         // The sums start at zero, or -- the table's entries having been raised by a.bias to make them all small and
         // non-negative (launch_sparse_staged says why) -- at minus the bias for every position of K the pixel really
         // sees: Cin per filter tap inside the image.  Lane (r, .) works that out for pixel r of a block; sum register
         // e of a lane belongs to pixel 8 (e / 4) + 4 h + e % 4 and takes it from that lane.  Of the wavefronts sharing
-        // a tile the first one does this (it always has a share of K).  Done here, while the first runs are on their way.
-        if (a.bias != 0 && ks == 0) {                       // (uniform)
+        // a tile one that surely has a share of K does this.  Done here, while the first runs are on their way.
+        if (a.bias != 0 && ks == (TURNS ? 0 : SKW - 1)) {                       // (uniform)
 #pragma unroll
             for (int bn = 0; bn < WN; ++bn) {
-                const int ih0 = col[bn].ih0, iw0 = col[bn].iw0;
-                const int taps_h = max(0, min(p.KH, p.H - ih0) - max(0, -ih0)), taps_w = max(0, min(p.KW, p.W - iw0) - max(0, -iw0));
-                const int start = col[bn].ok ? -a.bias * p.Cin * taps_h * taps_w : 0;
+                const int start = -a.bias * p.Cin * taps_in[bn];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int v = __builtin_amdgcn_ds_bpermute(4 * (8 * (e / 4) + 4 * h + e % 4), start);
@@ -290,52 +455,82 @@ smfmac_staged_kernel(Args a)
                 }
             }
         }
-        Words2 wa, wb;
-        v8i dn0[WM][2], dn1[WM][2];
-        dg_wait_for_loads();                                   // (both runs: the first is needed now)
-        read_words(wa, TURNS ? 0 : g0 & 1, 0);
-#pragma unroll
-        for (int u = 0; u < WM; ++u)
-            sparse_dense_rows_shared<NIB, HIGH>(s_rows + (TWO ? 16 * u : 0), wa.ca[TWO ? 0 : u].x, wa.ca1[TWO ? 0 : u].x, pick, dn0[u][0], dn0[u][1]);
-        if constexpr (HALF) {
-            for (int g = 0; g < runs; ++g) {
-                kept_bytes((int)fdiv((uint32_t)(2 * g), a.div_cpt), true, ones, ones_odd);
-                step(dn0, wa, 0, dn1, wa, 1, ones, ones_odd);
-                read_words(wb, g & 1, 1);
-                step(dn1, wa, 1, dn0, wb, 0, ones, ones_odd);
-                // (the second chunk's kept bytes take the first's registers)
-                kept_bytes((int)fdiv((uint32_t)min(2 * g + 1, chunks - 1), a.div_cpt), 2 * g + 1 < chunks, ones, ones_odd);
-                step(dn0, wb, 0, dn1, wb, 1, ones, ones_odd);
-                dg_wait_for_loads();
-                fetch();
-                read_words(wa, (g + 1) & 1, 0);
-                step(dn1, wb, 1, dn0, wa, 0, ones, ones_odd);
-            }
-        }
-        int g = HALF ? g1 : g0, rt = rt0, n = 0;            // the run, its place in its tap, runs done
-        for (int tap = tap0; g < g1;) {
-            kept_bytes(tap, true, ones, ones_odd);
-            for (; rt < runs_per_tap && g < g1; rt += stride, g += stride, ++n) {
-                // run g, in the buffer of its parity (of its count where wavefronts take turns): wa holds its first chunk's words, dn0 the dense operands of that chunk's word 0
-                step(dn0, wa, 0, dn1, wa, 1, ones, ones_odd);
-                read_words(wb, (TURNS ? n : g) & 1, 1);
-                step(dn1, wa, 1, dn0, wb, 0, ones, ones_odd);
-                step(dn0, wb, 0, dn1, wb, 1, ones, ones_odd);
-                // every read of run g has been issued: its buffer takes the wavefront's run after next, once its next
-                // run is known to be in (one counter serves all loads, and they complete in order)
-                dg_wait_for_loads();
-                fetch();
-                read_words(wa, ((TURNS ? n : g) + 1) & 1, 0);
-                step(dn1, wb, 1, dn0, wa, 0, ones, ones_odd);
-            }
-            if constexpr (TURNS) {
-                while (rt >= runs_per_tap) rt -= runs_per_tap;      // (uniform; no filter window: the tap stays)
+        Weights w0, w1;                                     // of the run's first and second chunk
+        Pixels x0, x1;
+        v8i dn[SETS][WM][2];
+        uint32_t cur = 0, nxt = BUFS > 1 ? BUF : 0;         // the buffers of this run and the next
+        dg_wait_for_loads<(BUFS - 1) * LOADS>();
+        read_weights(w0, cur, 0);
+        if constexpr (AHEAD == 2) read_weights(w1, cur, 1);
+        read_pixels(x0, cur, 0);
+        dense_rows(dn[0], w0, 0);
+        if constexpr (AHEAD == 2) dense_rows(dn[1], w0, 1);
+        // run g, whose first chunk's words and operands (both steps' where they are made two ahead) are at hand
+        auto run = [&](int g) {
+            if constexpr (AHEAD == 2) {
+                step(dn[0], x0, 0, [&]() { read_pixels(x1, cur, 1), dense_rows(dn[2], w1, 0); });
+                dg_wait_for_loads<(BUFS - 2) * LOADS>();       // the next run is in
+                step(dn[1], x0, 1, [&]() { read_weights(w0, nxt, 0), dense_rows(dn[SETS - 1], w1, 1); });
             } else {
-                rt = 0, ++tap;
+                step(dn[0], x0, 0, [&]() {
+                    if (LATE) dense_rows(dn[1], w0, 1);
+                    read_weights(w1, cur, 1);
+                    if (!LATE) read_pixels(x1, cur, 1), dense_rows(dn[1], w0, 1);
+                });
+                step(dn[1], x0, 1, [&]() {
+                    dense_rows(dn[0], w1, 0);
+                    if (LATE) read_pixels(x1, cur, 1);
+                });
+                dg_wait_for_loads<(BUFS - 2) * LOADS>();
+            }
+            // (the second chunk's kept bytes take the first's registers)
+            if constexpr (HALF) kept_bytes((int)fdiv((uint32_t)min(2 * g + 1, chunks - 1), a.div_cpt), 2 * g + 1 < chunks);
+            if constexpr (AHEAD == 2)
+                step(dn[SETS - 2], x1, 0, [&]() { read_pixels(x0, nxt, 0), read_weights(w1, nxt, 1), dense_rows(dn[0], w0, 0); });
+            else
+                step(dn[0], x1, 0, [&]() {
+                    if (LATE) dense_rows(dn[1], w1, 1);
+                    read_weights(w0, nxt, 0);
+                    if (!LATE) read_pixels(x0, nxt, 0), dense_rows(dn[1], w1, 1);
+                });
+            // This run's words have all been read and used: its buffer takes the run BUFS after it.
+#pragma unroll
+            for (int bn = 0; bn < WN; ++bn) asm volatile("" ::"v"(x1.cb[bn].x), "v"(x1.cb[bn].y));
+            if constexpr (AHEAD == 1 && !LATE) {             // (LATE: those words' operands are made first of all in the step above)
+#pragma unroll
+                for (int bm = 0; bm < RB; ++bm) asm volatile("" ::"v"(w1.ca[bm].x), "v"(w1.ca1[bm].y));
+            }
+            fetch();
+            step(dn[SETS - 1], x1, 1, [&]() {
+                dense_rows(dn[AHEAD - 1], w0, AHEAD - 1);
+                if (LATE) read_pixels(x0, nxt, 0);
+            });
+            cur = nxt;
+            nxt = next_buffer(nxt);
+        };
+        if constexpr (HALF) {
+            for (int g = g0; g < g1; ++g) {
+                kept_bytes((int)fdiv((uint32_t)(2 * g), a.div_cpt), true);
+                run(g);
+            }
+        } else if constexpr (TURNS) {
+            kept_bytes(tap0, true);
+            for (int g = g0; g < g1; g += stride) run(g);
+        } else {
+            int g = g0, first = rt0;
+            for (int tap = tap0; g < g1; ++tap, first = 0) {
+                kept_bytes(tap, true);
+                const int end = min(g + runs_per_tap - first, g1);
+                for (; g < end; ++g) run(g);
             }
         }
         dg_wait_for_loads();                                   // (unused fetches past the end: their LDS writes end before the wavefront does)
     }
+    if (SKW == 1 && !active) return;                       // (whole wavefronts; no barrier follows on this path)
+    // (The scales are in: said here, or the compiler, which cannot tell across the stores' branches, waits for them -- and with them for
+    // every store before -- again at each group of stores.)
+#pragma unroll
+    for (int bm = 0; bm < RB; ++bm) asm volatile("" : "+v"(sc_cols[bm]));
     // the tile's blocks as they go to memory: two planes merge into one block row, 256 * hi + lo
     v16i out[RB][WN];
 #pragma unroll
@@ -349,34 +544,36 @@ smfmac_staged_kernel(Args a)
         dg_mfma_store_tile<RB, WN, true, true>(p, out, m0, n0, lane, sc_cols);
         return;
     }
-    // The sums take the place of the staging rows: every wavefront is done with its rows (and its last loads have
-    // landed) at the first barrier; the tile's first wavefront writes its sums, the others add theirs.
-    int32_t *sums = s_acc + tw * (NB * 1024);
-    __syncthreads();
-    if (ks == 0) {
+    // Every wavefront's sums take the place of its own staging rows (its last loads have landed), 16 bytes per lane and group of four
+    // sum registers; once all are there, each wavefront of the tile adds up and stores a share of the groups: 8 rows of
+    // 32 channels each.  (The sums met by atomic additions before, with two barriers more, and with two blocks two of four wavefronts stored.)
+    uint4 *const mine = s_mem + w4 * (REGION / 16) + lane;
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) sums[(i * 16 + e) * 64 + lane] = out[i / WN][i % WN][e];
-    }
-    __syncthreads();
-    if (ks != 0 && g0 < g1) {
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                __hip_atomic_fetch_add(&sums[(i * 16 + e) * 64 + lane], out[i / WN][i % WN][e], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
+        for (int q = 0; q < 4; ++q) {
+            const v16i &b = out[i / WN][i % WN];
+            mine[(4 * i + q) * 64] = make_uint4(b[4 * q], b[4 * q + 1], b[4 * q + 2], b[4 * q + 3]);
+        }
     __syncthreads();
     if (!active) return;
+    const uint4 *const theirs = s_mem + (w4 - ks) * (REGION / 16) + lane;
+    static_assert(SKW == 1 || RB == 1, "a share's blocks are one row of blocks");
+    constexpr int GROUPS = NB * 4 / SKW, NQ = GROUPS < 4 ? GROUPS : 4;        // this wavefront's, and those of a block among them
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        if (i % SKW != ks) continue;                        // each wavefront of the tile stores a share of its blocks
-        v16i blk;
+    for (int j = 0; j < GROUPS / NQ; ++j) {
+        const int first = ks * GROUPS + j * NQ, i = first / 4, q0 = first % 4;
+        v4i sum[NQ];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) blk[e] = sums[(i * 16 + e) * 64 + lane];
-        dg_mfma_store_block<true, true>(p, blk, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane, sc_cols[i / WN]);
+        for (int q = 0; q < NQ; ++q) {
+            sum[q] = (v4i){0, 0, 0, 0};
+#pragma unroll
+            for (int w = 0; w < SKW; ++w) {
+                const uint4 t = theirs[w * (REGION / 16) + (first + q) * 64];
+                sum[q] += (v4i){(int)t.x, (int)t.y, (int)t.z, (int)t.w};
+            }
+        }
+        dg_mfma_store_quads<NQ>(p, sum, q0, m0, n0 + i * 32, lane, sc_cols[0]);
     }
 }
 
@@ -394,6 +591,7 @@ void launch_sparse_staged(const DgProblem &p, const Pools &pools, int32_t bias, 
     a.p = p;
     a.pools = pools;
     a.bias = bias;
+    a.x_bytes = (uint32_t)((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4));
     const int rows = TWO ? 32 : q.wm * 32;                 // (two planes: q.wm = 2 blocks of the same 32 rows)
     a.tiles_m = (p.M + rows - 1) / rows;
     a.wave_tiles = wave_tiles;
