@@ -13,12 +13,14 @@
 // one 8-byte LDS read at a 4-bit index, the two codes: 16 pairs per v, for either operand; a pixel whose tap lies outside the
 // image reads pairs of zeros instead.
 //
-// Bound by the matrix pipe and the instructions beside it: 32 cycles of the pipe per position and block of 256 outputs, a quarter
-// of it useful -- 8 table additions per SIMD and cycle at best -- and 1.8 VALU, 1.0 LDS and 0.3 scalar instructions, which a lone
-// wavefront does not overlap with its own matrix instructions (about 55 cycles per position; two blocks per wavefront, sharing the entries, 110: no
-// gain, and half the wavefronts).  So blocks are small and wavefronts many.  The plain kernel spends 5 vector instructions and an
-// LDS read per addition (3 additions per SIMD and cycle).  Measured against it: 28x28x128 -> 128 3x3 at batch 4 (1568 blocks) 63.4
-// -> 48.3 us, at batch 8 117 -> 88.8; 56x56x64 -> 64 at batch 8 21.1 -> 13.8; 14x14x36 -> 100 3x3 at batch 8 (686) 19.4 -> 13.5.
+// Bound by the matrix pipe: 32 cycles of it per position and block of 256 outputs, a quarter of it useful -- 8 table additions per SIMD and
+// cycle at best.  Binary32 matrix instructions do not overlap with vector instructions at all, whosever they are: a group of n between two of
+// them costs 4.4 + 2 n cycles at two wavefronts per SIMD (measured, registers only), while LDS reads between them are free.  So a word's 16
+// matrix instructions are issued in one piece, only the next word's table reads between them, and the next word's 28 vector
+// instructions before or behind them in another: 40 cycles per position instead of 51 with the vector instructions
+// spread three at a time.  A sum cannot be split along K, so blocks are small and wavefronts many.  The plain kernel spends 5 vector instructions
+// and an LDS read per addition (3 additions per SIMD and cycle).  Measured against it: 28x28x128 -> 128 3x3 at batch 4 (1568 blocks) 68.7
+// -> 45.5 us (spread: 50), at batch 8 120 -> 81 (89); 56x56x64 -> 64 at batch 8 113 -> 73; 14x14x36 -> 100 3x3 at batch 8 (686) 19.8 -> 14.3.
 // Reading the pairs one at a time, just before their instructions, instead of a word ahead: 57.1 us on the first.
 #include "dg_common.h"
 
@@ -151,10 +153,11 @@ onehot_f32_kernel(F32Args a)
                 read_pairs(c + 1 < CHW ? ring[i] : ring[(i + 1) % RING], c + 1 < CHW ? c + 1 : 0, pairs[cur ^ 1]);
                 if constexpr (WHOLE) {
                     multiply(pairs[cur], 0, 8);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 64, 0);      // (all the vector instructions there are, then none)
 #pragma unroll
                     for (int k = 0; k < 16; ++k) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x102, 3, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                     }
                 } else {
                     multiply(pairs[cur], 0, 2);
@@ -180,12 +183,13 @@ onehot_f32_kernel(F32Args a)
 
 }   // namespace
 
-// AUTO compares what the two kernels take per position of K.  This one: 7 + 19.5 w ns, w the wavefronts on the busiest SIMD (a
-// workgroup of four blocks per compute unit at a time; w = 1: 26 - 29 ns measured, 2: 40 - 47, 3: 72, 4: 75).  The plain one: the
-// outputs at 5.8 thousand per ns -- 5.4 to 7.7 measured, half of that where it reads bytes (Cin % 16 != 0).  Of 20 layers it misses none by
-// more than 3 %: 56x56x32 -> 40 3x3 at batch 2 stays (14.8 against 15.9 us: 1176 blocks, one in five of them padding, are two on
-// some SIMDs), 28x28x32 -> 72 goes over (14.0 -> 10.8), 7x7x512 -> 400 at batch 8 too (18.7 -> 15.2), 14x14x256 -> 256 3x3 at batch 2
-// stays (52.5 against 57.0: 400 blocks leave SIMDs idle).
+// AUTO compares what the two kernels take per position of K.  This one: 2 + 16.7 w ns, w the wavefronts on the busiest SIMD (a
+// workgroup of four blocks per compute unit at a time; w = 1: 17.5 - 21 ns measured, 2: 37, 3: 52, 4: 68).  The plain one: the
+// outputs at 5.8 thousand per ns -- 5.4 to 7.9 measured, half of that where it reads bytes (Cin % 16 != 0) -- and 21 at least, below which
+// its own chain of additions does not get (50 to 100 thousand outputs: 21.2 - 22.6).  Of 39 layers it misses none by more than 4 %:
+// 14x14x256 -> 256 3x3 at batch 2 (400 blocks) goes over (54.0 -> 44.1 us), 28x28x32 -> 72 too (10.9 -> 9.8), 56x56x32 -> 40 at batch 2 (1176
+// blocks) 15.5 -> 14.7; with fewer than 256 blocks or shorter K the two are within 4 % of each other or the plain one is ahead
+// (28x28x64 -> 64 1x1 5.1 against 6.3).
 // DG_F32_MFMA: 0 never, 1 whatever the size.
 bool dg_onehot_f32_preferred(const dg_lut *lut, const DgProblem &p)
 {
@@ -199,8 +203,9 @@ bool dg_onehot_f32_preferred(const dg_lut *lut, const DgProblem &p)
     if ((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4) >= ((int64_t)1 << 31)) return false;      // (32-bit byte offsets)
     if (const char *f = dg_override("DG_F32_MFMA")) return atoi(f) != 0;
     const int64_t groups = (blocks + 3) / 4, units = dg_simd_count() / 4;
-    const double here = 7.0 + 19.5 * (double)((groups + units - 1) / units);
-    return here < (double)p.M * p.N / (p.Cin % 16 == 0 ? 5800.0 : 2900.0);
+    const double here = 2.0 + 16.7 * (double)((groups + units - 1) / units), chain = blocks >= 256 && p.K >= 256 ? 21.0 : 0.0;
+    const double plain = (double)p.M * p.N / (p.Cin % 16 == 0 ? 5800.0 : 2900.0);
+    return here < (plain > chain ? plain : chain);
 }
 
 dg_status dg_launch_onehot_f32(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
