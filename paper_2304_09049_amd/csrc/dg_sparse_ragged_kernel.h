@@ -13,10 +13,15 @@
 // whichever takes fewer words.  (Words that are masked in both halves are multiplied all the same: a branch around them cost
 // more than the words, since it kept the loads of the next window from being issued between this one's instructions.)
 //
-// Bound by issue slots and by how few wavefronts such small layers have, not by the matrix pipe (8x29x27x48 -> 120 5x5 from codes:
-// 36 VALU instructions per matrix instruction, VALU issue 0.35 of the cycles, the pipe 0.08, 1.4 wavefronts per SIMD).  So S wavefronts
-// of a workgroup share one tile and split the windows of K among them, their sums meeting in LDS (exact in any order).
-// Measured against the permute kernel (Cin % 16 == 0) and the LDS kernel that ran these layers, packed codes, graph replays:
+// Bound by issue slots and by how few wavefronts such small layers have, not by the matrix pipe.  So S wavefronts
+// of a workgroup share one tile and split the windows of K among them, their sums meeting in LDS (exact in any order).  Registers are
+// kept to 128: with 134 the second workgroup of a compute unit, of five wavefronts, did not fit beside the first and ran after it (11.6 us
+// for the 9.3 below).  29x27x48 -> 120 5x5 at batch 8 from codes, timestamps: start to first loads 1.1 us, the windows 3.0 (3.6 packed as they
+// were loaded), the end 0.9 (2.0 with a bounds test, an address and a load of the scale for every element).  With the last window fetching no other
+// (it made a tile's wavefronts, of three windows or so each, wait for loads that nobody used): 28x28x48 -> 120 11.7 -> 10.2, 28x28x208 -> 256 1x1 at
+// batch 4 10.1 -> 6.6, 14x14x100 -> 100 3x3 at batch 8 packed 6.4 -> 5.8, 56x56x20 -> 128 at batch 4 10.6 -> 8.1, 7x7x500 -> 200 at batch 16 12.1 -> 10.5
+// (unshared tiles with many windows, 57x57x36 -> 128 at batch 4: 9.8 -> 10.2).
+// Measured against the permute kernel (Cin % 16 == 0) and the LDS kernel that ran these layers before, packed codes, graph replays:
 // 8x29x27x48 -> 120 5x5 43.1 -> 8.6 us (0.2 of the rate at which the instruction can select: 1.8 us), 28x28x112 -> 224 3x3 at batch
 // 16 76.5 -> 16.3, 57x57x36 -> 128 3x3 at batch 4 142 -> 8.9, 56x56x16 -> 32 for one image 6.2 -> 3.8 (a launch: 1.6).
 // RAW: the activations are codes one per byte and are packed in registers as they are loaded, which spares the packing
@@ -24,6 +29,8 @@
 #pragma once
 
 #include "dg_onehot_kernel.h"
+
+#include <type_traits>
 
 namespace dgoh {
 
@@ -57,7 +64,7 @@ __device__ __forceinline__ Words<CH> load_unaligned(const uint8_t *ptr)
 }
 
 template <int WM, int WN, int CH, bool RAW>
-__global__ void __launch_bounds__(WM * WN == 1 ? 1024 : 512, WM * WN == 1 ? 4 : 2)
+__global__ void __launch_bounds__(WM * WN == 1 ? 1024 : 512, WM * WN <= 2 ? 4 : 2)
 smfmac_ragged_kernel(RaggedArgs a)
 {
     constexpr int NB = WM * WN, XB = RAW ? 4 : 1;           // activation bytes per packed byte
@@ -65,6 +72,8 @@ smfmac_ragged_kernel(RaggedArgs a)
     __shared__ int32_t s_sum[NB * 1024];                    // [block][accumulator register][lane]
     const DgProblem &p = a.p;
     const int lane = threadIdx.x & 63, ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), S = blockDim.x >> 6;
+    // the table's entry that this thread writes, asked for with the arguments
+    const uint2 entry = make_uint2(a.pools.w[threadIdx.x & 3], a.pools.w[(threadIdx.x >> 2) & 3]);
     const int r = lane & 31, h = lane >> 5;
     const int tile = (int)xcd_contiguous(blockIdx.x, gridDim.x);
     const int m0 = (tile % a.tiles_m) * (WM * 32), n0 = (tile / a.tiles_m) * (WN * 32);
@@ -73,42 +82,39 @@ smfmac_ragged_kernel(RaggedArgs a)
     const int c0 = ws * a.cpw, c1 = max(c0, min(c0 + a.cpw, a.chunks));
     const bool through_lds = S > 1 || a.scale_rows || a.n_first;
 
-    sparse_fill_table(s_rows, a.pools, threadIdx.x);
-    if (through_lds)
-        for (int i = threadIdx.x; i < NB * 1024; i += blockDim.x) s_sum[i] = 0;
+    float sc_cols[WM];
+#pragma unroll
+    for (int bm = 0; bm < WM; ++bm) sc_cols[bm] = 0.0f;
+    if (!a.scale_rows) dg_mfma_column_scales<WM, true>(p, m0, lane, sc_cols);
     const uint8_t *w_ptr[WM];
 #pragma unroll
     for (int bm = 0; bm < WM; ++bm) w_ptr[bm] = p.Wp + (int64_t)min(m0 + bm * 32 + r, p.M - 1) * (p.K / 4);
     Column col[WN];
 #pragma unroll
     for (int bn = 0; bn < WN; ++bn) col[bn] = make_column(p, a.div_ow, a.div_oh, n0 + bn * 32 + r, L * XB, 0);
-    float sc_cols[WM];
-#pragma unroll
-    for (int bm = 0; bm < WM; ++bm) sc_cols[bm] = 0.0f;
-    if (!a.scale_rows) dg_mfma_column_scales<WM, true>(p, m0, lane, sc_cols);
-
-    v16i acc[WM][WN];
-#pragma unroll
-    for (int bm = 0; bm < WM; ++bm)
-#pragma unroll
-        for (int bn = 0; bn < WN; ++bn)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[bm][bn][e] = 0;
 
     const int base = h ? a.base1 : 0, lead = h ? a.lead1 : 0;
     // the window fetched next
     int pair = (int)fdiv((uint32_t)min(c0, a.chunks - 1), a.div_win), win = min(c0, a.chunks - 1) - pair * a.windows;
-    Words<CH> wa[WM][2], wb[WN];
-    bool vb[WN];
-    auto fetch = [&]() {
-        const int start = min(4 * CH * win, a.seg - 4 * CH);
+    // A window as it is loaded -- codes one per byte are packed when their turn comes, not before: packed at once, as they
+    // were, every window waited for the next one's loads in the middle of its own matrix instructions.  (Two windows in flight: slower, the
+    // compiler moves them between registers at the loop's end and waits for them there.)
+    struct Window {
+        Words<CH> wa[WM][2];
+        Words<RAW ? 4 : CH> x[WN][RAW ? CH : 1];
+        bool vb[WN];
+        int dead;                                           // bytes, from its start, that an earlier window or the other half counts
+    };
+    auto fetch = [&](Window &w) {
+        const int start = min(4 * CH * win, a.seg - 4 * CH), overlap = 4 * CH * win - start;
+        w.dead = max(overlap, lead - (4 * CH * win - overlap));
         // weights: both halves' words; (an odd tap count: the last pair's second tap is any tap, its kept bytes are zero)
         const int tap0 = a.pair_taps ? 2 * pair : pair, tap1 = a.pair_taps ? min(tap0 + 1, taps - 1) : tap0;
         const int w0 = tap0 * L + start, w1 = tap1 * L + a.base1 + start;
 #pragma unroll
         for (int bm = 0; bm < WM; ++bm) {
-            wa[bm][0] = load_unaligned<CH>(w_ptr[bm] + w0);
-            wa[bm][1] = load_unaligned<CH>(w_ptr[bm] + w1);
+            w.wa[bm][0] = load_unaligned<CH>(w_ptr[bm] + w0);
+            w.wa[bm][1] = load_unaligned<CH>(w_ptr[bm] + w1);
         }
         const int tap = a.pair_taps ? 2 * pair + h : pair;
         const int kh = (int)fdiv((uint32_t)tap, a.div_kw), kw = tap - kh * p.KW;
@@ -117,61 +123,78 @@ smfmac_ragged_kernel(RaggedArgs a)
 #pragma unroll
         for (int bn = 0; bn < WN; ++bn) {
             const int ih = col[bn].ih0 + kh, iw = col[bn].iw0 + kw;
-            vb[bn] = col[bn].ok & (tap < taps) & ((uint32_t)ih < (uint32_t)p.H) & ((uint32_t)iw < (uint32_t)p.W);
+            w.vb[bn] = col[bn].ok & (tap < taps) & ((uint32_t)ih < (uint32_t)p.H) & ((uint32_t)iw < (uint32_t)p.W);
             // (outside the image: the same bytes of the first pixel, multiplied by kept bytes of zero)
-            const uint8_t *ptr = vb[bn] ? p.Xp + col[bn].off0 + tap_off * XB : p.Xp + inside * XB;
-            if constexpr (RAW) {
+            const uint8_t *ptr = w.vb[bn] ? p.Xp + col[bn].off0 + tap_off * XB : p.Xp + inside * XB;
 #pragma unroll
-                for (int i = 0; i < CH; ++i) {
-                    const Words<4> t = load_unaligned<4>(ptr + 16 * i);
-                    wb[bn].v[i] = dg_pack_codes16(make_uint4(t.v[0], t.v[1], t.v[2], t.v[3]));
-                }
-            } else {
-                wb[bn] = load_unaligned<CH>(ptr);
-            }
+            for (int i = 0; i < (RAW ? CH : 1); ++i) w.x[bn][i] = load_unaligned<RAW ? 4 : CH>(ptr + 16 * i);
         }
+        if (++win == a.windows) win = 0, ++pair;            // (uniform)
     };
 
-    fetch();
-    // the table and every wavefront's zeroes are in LDS; the loads above stay in flight across this barrier
+    Window w;
+    fetch(w);
+    // the table and every wavefront's zeroes go to LDS while the loads are on their way
+    if (threadIdx.x < 16) s_rows[threadIdx.x] = entry;
+    if (through_lds)
+        for (int i = threadIdx.x; i < NB * 1024; i += blockDim.x) s_sum[i] = 0;
+    v16i acc[WM][WN];
+#pragma unroll
+    for (int bm = 0; bm < WM; ++bm)
+#pragma unroll
+        for (int bn = 0; bn < WN; ++bn)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[bm][bn][e] = 0;
+    // (the scales, asked for first, are in: said once, or they are waited for, and every store before with them, at each group of stores)
+#pragma unroll
+    for (int bm = 0; bm < WM; ++bm) asm volatile("" : "+v"(sc_cols[bm]));
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const uint32_t pick = sparse_pick(h);
-    for (int c = c0; c < c1; ++c) {
+    // (the last window by itself: it has none to fetch, which a branch in the loop would keep from being fetched among the matrix instructions)
+    auto window = [&](auto more) {
         Words<CH> ca[WM][2], cb[WN];
         bool valid[WN];
+        const int dead = w.dead;
 #pragma unroll
-        for (int bm = 0; bm < WM; ++bm) ca[bm][0] = wa[bm][0], ca[bm][1] = wa[bm][1];
+        for (int bm = 0; bm < WM; ++bm) ca[bm][0] = w.wa[bm][0], ca[bm][1] = w.wa[bm][1];
 #pragma unroll
-        for (int bn = 0; bn < WN; ++bn) cb[bn] = wb[bn], valid[bn] = vb[bn];
-        // bytes of this window, from its start, that an earlier window or the other half counts
-        const int overlap = 4 * CH * win - min(4 * CH * win, a.seg - 4 * CH);
-        const int dead = max(overlap, lead - (4 * CH * win - overlap));
-        if (c + 1 < c1) {                                    // (uniform; the last one re-reads in bounds and is unused)
-            if (++win == a.windows) win = 0, ++pair;
+        for (int bn = 0; bn < WN; ++bn) {
+            valid[bn] = w.vb[bn];
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                if constexpr (RAW) {
+                    const Words<4> &t = w.x[bn][i];
+                    cb[bn].v[i] = dg_pack_codes16(make_uint4(t.v[0], t.v[1], t.v[2], t.v[3]));
+                } else {
+                    cb[bn].v[i] = w.x[bn][0].v[i];
+                }
+            }
         }
-        fetch();
+        if constexpr (more) fetch(w);
 #pragma unroll
         for (int t = 0; t < CH; ++t) {
-            v8i dn[WM][2];
-#pragma unroll
-            for (int bm = 0; bm < WM; ++bm)
-                sparse_dense_rows_shared(s_rows, ca[bm][0].v[t], ca[bm][1].v[t], pick, dn[bm][0], dn[bm][1]);
-            v4i kept;
+            v4i kept, ones[WN];
 #pragma unroll
             for (int b = 0; b < 4; ++b) kept[b] = 4 * t + b >= dead ? 0x00010001 : 0;
 #pragma unroll
-            for (int bn = 0; bn < WN; ++bn) {
-                v4i ones;
+            for (int bn = 0; bn < WN; ++bn)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) ones[b] = valid[bn] ? kept[b] : 0;
-                const int even = (int)cb[bn].v[t], odd = (int)(cb[bn].v[t] >> 2);
+                for (int b = 0; b < 4; ++b) ones[bn][b] = valid[bn] ? kept[b] : 0;
+            // (one block of channels after the other: the operands of both at once are registers that a fourth wavefront per SIMD needs)
 #pragma unroll
-                for (int bm = 0; bm < WM; ++bm) acc[bm][bn] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones, dn[bm][0], acc[bm][bn], even, 0, 0);
+            for (int bm = 0; bm < WM; ++bm) {
+                v8i dn[2];
+                sparse_dense_rows_shared(s_rows, ca[bm][0].v[t], ca[bm][1].v[t], pick, dn[0], dn[1]);
 #pragma unroll
-                for (int bm = 0; bm < WM; ++bm) acc[bm][bn] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones, dn[bm][1], acc[bm][bn], odd, 0, 0);
+                for (int bn = 0; bn < WN; ++bn) {
+                    acc[bm][bn] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones[bn], dn[0], acc[bm][bn], (int)cb[bn].v[t], 0, 0);
+                    acc[bm][bn] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones[bn], dn[1], acc[bm][bn], (int)(cb[bn].v[t] >> 2), 0, 0);
+                }
             }
         }
-    }
+    };
+    for (int c = c0; c + 1 < c1; ++c) window(std::true_type());
+    if (c0 < c1) window(std::false_type());
 
     if (!through_lds) {
         dg_mfma_store_tile<WM, WN, true>(p, acc, m0, n0, lane, sc_cols);
@@ -183,6 +206,27 @@ smfmac_ragged_kernel(RaggedArgs a)
         for (int e = 0; e < 16; ++e)
             __hip_atomic_fetch_add(&s_sum[(i * 16 + e) * 64 + lane], acc[i / WN][i % WN][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __syncthreads();
+    if (!a.n_first && !a.scale_rows && p.stride_cm == 1) {  // (uniform: the channels contiguous, their scales at hand)
+        if (S <= NB * 4) {
+            for (int u = ws; u < NB * 4; u += S) {          // groups of four registers: 8 pixels x 32 channels each
+                const int i = u >> 2;
+                v4i sum[1];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[0][e] = s_sum[(4 * u + e) * 64 + lane];
+                dg_mfma_store_quads<1>(p, sum, u & 3, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane, WM == 1 || i / WN == 0 ? sc_cols[0] : sc_cols[WM - 1]);
+            }
+            return;
+        }
+        for (int u = ws; u < NB * 16; u += S) {             // more wavefronts than groups: a register at a time
+            const int i = u >> 4, e = u & 15, m = m0 + (i / WN) * 32 + r, n = n0 + (i % WN) * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+            if (m >= p.M || n >= p.N) continue;
+            const int32_t sum = s_sum[u * 64 + lane];
+            const int64_t o = m + (int64_t)n * p.stride_cn;
+            if (p.scale) p.Cf[o] = (float)sum * (WM == 1 || i / WN == 0 ? sc_cols[0] : sc_cols[WM - 1]);
+            else p.C[o] = sum;
+        }
+        return;
+    }
     for (int idx = threadIdx.x; idx < NB * 1024; idx += blockDim.x) {
         const int i = idx >> 10;
         int e = (idx >> 6) & 15, l = idx & 63;
