@@ -58,6 +58,8 @@
 #include "dg_codes.h"
 #include "dg_mfma_tile.h"
 
+#include <type_traits>
+
 namespace dgoh {
 
 typedef dg_v4i v4i;
@@ -755,13 +757,16 @@ onehot_splitk_kernel(SplitArgs a)
         // every wavefront's zeroes are in LDS before any wavefront adds to them; the global loads issued above stay in
         // flight across this barrier (it waits for LDS only), so the wavefronts' staggered starts cost nothing here
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        for (int c = c0; c < c1; ++c) {
+        // (the last chunk by itself: it has none to fetch.  Most wavefronts have one or two chunks, and fetching one more that nobody used
+        // made the kernel wait for its loads.)
+        auto chunk = [&](int c, auto more) {
             const Words<CH> ca = wa, ca1 = wa1, cb = wb;
             const bool valid = vb;
-            // unconditional prefetch (the last one re-reads in bounds and is unused)
-            wa = load_words<CH>(w_ptr + (int64_t)(c + 1 < c1 ? c + 1 : c) * (8 * CH));
-            if (F::SPARSE) wa1 = load_words<CH>(w_ptr + (int64_t)(c + 1 < c1 ? c + 1 : c) * (8 * CH) + 4 * CH);
-            fetch_x();
+            if constexpr (more) {
+                wa = load_words<CH>(w_ptr + (int64_t)(c + 1) * (8 * CH));
+                if (F::SPARSE) wa1 = load_words<CH>(w_ptr + (int64_t)(c + 1) * (8 * CH) + 4 * CH);
+                fetch_x();
+            }
             if constexpr (F::SPARSE) {
                 // (kept bytes (1, 0) with the even codes, (0, 1) with the odd; the packed word is the index of both)
                 const int x = valid ? 0x00010001 : 0, y = valid ? 0x01000100 : 0;
@@ -773,7 +778,7 @@ onehot_splitk_kernel(SplitArgs a)
                     acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones_even, even, acc, (int)cb.v[word], 0, 0);
                     acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones_odd, odd, acc, (int)cb.v[word], 0, 0);
                 }
-                continue;
+                return;
             }
 #pragma unroll
             for (int word = 0; word < CH; ++word)
@@ -787,7 +792,9 @@ onehot_splitk_kernel(SplitArgs a)
                         if (TWO) acc_hi = dg_mfma_step<TR>(weight_operand<BITS>(a.pools, sa, g, 1), fb, acc_hi);
                     }
                 }
-        }
+        };
+        for (int c = c0; c + 1 < c1; ++c) chunk(c, std::true_type());
+        if (c0 < c1) chunk(c1 - 1, std::false_type());
     }
     if (TWO) {
 #pragma unroll
