@@ -216,9 +216,10 @@ smfmac_staged_kernel(Args a)
     constexpr bool LATE = WM == 2 && !TWO;                   // (that tile has no registers for a chunk's words beside the next one's)
     // Which table: on narrow tiles, whose operands serve few pixels, its random reads keep LDS busier than the vector instructions they
     // spare are worth (28x28x128 -> 128 3x3 at batch 8, 4-bit codes, 32 x 64 by four: 9.9 us with quads, 9.2 with pairs); with 4-bit slots on
-    // the shared and the 64-row tiles too (28x28x256 -> 256 3x3 at batch 8, 32 x 128 by four: 21.5, 19.5).  On the others quads are ahead:
-    // 8192-cube 740 us with pairs, 706 with quads; 56x56x256 -> 256 3x3 at batch 16, 4-bit, 32 x 224: 98.2, 96.8.
-    constexpr bool QUADS = WN >= 4 && !(NIB && (SKW > 1 || WM == 2));
+    // the 32 x 128 and 64 x 128 tiles too (28x28x256 -> 256 3x3 at batch 8, 32 x 128 by four: 21.5, 19.5; 28x28x512 -> 256 1x1 at batch 32, unshared:
+    // 22.0, 19.3).  On the others quads are ahead: 8192-cube 740 us with pairs, 706 with quads; 56x56x256 -> 256 3x3 at batch 16, 4-bit,
+    // 32 x 224: 98.2, 96.8.
+    constexpr bool QUADS = WN >= 4 && !(NIB && WN == 4);
     constexpr int LOADS = RB + WN;                          // a run's loads
     constexpr int REGION = SKW > 1 && NB * 4096 > BUFS * BUF ? NB * 4096 : BUFS * BUF;      // a wavefront's: its buffers, then its sums
     typedef std::conditional_t<QUADS, QuadTable<NIB, TWO, (TWO && SKW > 1 ? 2 : 4)>, PairTable<NIB, TWO>> Table;
