@@ -542,7 +542,8 @@ onehot_mfma_kernel(Args a)
     // this barrier (it waits for LDS only)
     if (SKW > 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     v4i ones[F::SPARSE ? WN : 1];                            // sparse form: the kept bytes of the one-hot operand
-    for (int c = c0; c < c1; ++c) {
+    // (wavefronts that share a tile have few chunks each: their last one stands by itself and fetches no other)
+    auto multiply = [&](int c, auto more) {
         Words<CH> ca[RB], ca1[RB], cb[WN];
         bool valid[WN];
 #pragma unroll
@@ -554,7 +555,7 @@ onehot_mfma_kernel(Args a)
         }
         const bool new_tap = starts_tap;                    // of the chunk about to be computed
         if constexpr (STEPPED) advance();
-        fetch(c + 1 < c1 ? c + 1 : c);                      // unconditional (the last one re-reads in bounds and is unused)
+        if constexpr (more) fetch(c + 1 < c1 ? c + 1 : c);  // unconditional (unshared: the last one re-reads in bounds and is unused)
         if constexpr (F::SPARSE) {
             // The kept bytes: (1, 0) per position, or zeros for a tap outside the image; they change with the tap only.
             // The index register is the packed word as it is for the even codes and shifted by one code for the odd
@@ -606,7 +607,7 @@ onehot_mfma_kernel(Args a)
                     }
                 }
             }
-            continue;
+            return;
         }
         // Step t = one MFMA per block of the tile: word t / STEPS, selector j of it, value group g.  The operands of
         // step t+1 are built between the MFMAs of step t so that the matrix unit and the VALU of a single wavefront
@@ -650,8 +651,17 @@ onehot_mfma_kernel(Args a)
                 }
             }
         }
+    };
+    if constexpr (SKW > 1) {
+        for (int c = c0; c + 1 < c1; ++c) multiply(c, std::true_type());
+        if (c0 < c1) multiply(c1 - 1, std::false_type());
+    } else {
+        for (int c = c0; c < c1; ++c) multiply(c, std::true_type());
     }
 
+    // (the scales are in: said once, or they are waited for, and every store before with them, at each group of stores)
+#pragma unroll
+    for (int bm = 0; bm < RB; ++bm) asm volatile("" : "+v"(sc_cols[bm]));
     // the tile's blocks as they go to memory: two planes merge into one block row, 256 * hi + lo
     v16i out[RB][WN];
 #pragma unroll
