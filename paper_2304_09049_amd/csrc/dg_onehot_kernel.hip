@@ -893,17 +893,18 @@ namespace {
 // 0.9 LDS instructions per matrix instruction, the pipe busy 0.33 of the cycles at 1.2 wavefronts per SIMD), so that tile
 // comes first, its wavefronts sharing K where the tiles alone leave SIMDs idle.  Measured on 36
 // layers against the kernels that ran them before (dense instruction, sparse2p_kernel), packed codes, graph replays, us:
-//   32 x 128 from one per SIMD        56x56x256 -> 256 3x3 at batch 16 (3136 tiles) 114 -> 96.7
+//   32 x 128, from 11/8 per SIMD      56x56x256 -> 256 3x3 at batch 16 (3136 tiles) 114 -> 96.7
 //   32 x 128 shared by 2 / by 4       28x28x256 -> 256 3x3 at batch 16 (784) 42.8 -> 27.6; at batch 8 (392) 27.0 -> 17.7
-//   below 384 of those, 32 x 64 by 4  14x14x256 -> 256 3x3 at batch 8 (200) 12.1 -> 9.3; 14x14x512 -> 512 3x3 at batch 5 (256) 19.7 ->
+//   below 192 of those, 32 x 64 by 4  14x14x256 -> 256 3x3 at batch 8 (104) 12.1 -> 9.3; 14x14x512 -> 512 3x3 at batch 5 (128) 19.7 ->
 //                                     13.1; 7x7x2048 -> 512 at batch 16 (208) 10.8 -> 8.5 -- from 6e8 products on: less does not
 //                                     pay for the packing kernel that the split-K kernel's one-call form spares; below 192
 //                                     tiles split K is ahead (7x7x512 -> 512 3x3 at batch 8: 10.2 against 11.1)
-//   where the lines lie               28x28x256 -> 224 ... 288 3x3 at batch 4 ... 7, 32 x 64 by 4 against 32 x 128 by 4: 200 tiles of
-//                                     the latter 13.7, 13.2; 259 19.0, 18.3; 344 19.1, 18.3; 387 21.9, 18.3 (the former's workgroups are
-//                                     more than three per compute unit); 1x1 with K = 1024: 300 tiles 9.7, 10.9; 400 12.5, 11.3.
-//                                     32 x 128 by 4 against by 2: 592 tiles 26.0, 27.2; 688 26.1, 27.5; 784 32.1, 27.9 (the line
-//                                     at 640 leaves up to 5 % there)
+//   where the lines lie               3x3 layers, 32 x 64 by 4 against 32 x 128 by 4: 200 tiles of the latter 12.6, 12.2; 208 17.5, 16.4; 296
+//                                     17.7, 16.6; 343 13.1, 12.1; 344 17.4, 16.6; 1x1 with K = 1024: 200 tiles 7.9, 8.0; 300 9.7, 10.9 (measured
+//                                     on the kernel before); 400 13.3, 11.0.
+//                                     32 x 128 by 4 against by 2: 592 tiles 24.2, 26.8; 784 30.1, 27.7.  Unshared, by 2, by 4:
+//                                     1032 tiles 44.5, 40.6, 37.6; 1176 45.8, 41.2, 37.8; 1280 45.9, 41.2, 39.2; 1376 46.1, 41.1, 44.3; 1568
+//                                     46.4, 52.3, 50.9 (a second tile on a few SIMDs takes as long as one on all)
 //   K = 512 ... 1023                  28x28x512 -> 256 at batch 16 (784 tiles of 32 x 128) 12.6 -> 10.7 unshared; with 392 8.3 against 8.5
 //   shorter K, up to 64 channels      56x56x256 -> 64 at batch 16 8.9 -> 7.7, 56x56x128 -> 64 6.9 -> 6.6; with more channels such a
 //                                     layer is its output's stores (28x28x128 -> 512 at batch 32: 16.4 against 17.6)
@@ -921,10 +922,10 @@ Plan staged2p_plan(const DgProblem &t)
     } else if (t.K < 512) {
         q.wn = 2, q.staged = t2 >= simds && t.M <= 64;
     } else if (t4 >= simds) {
-        q.skw = 1;
+        q.skw = t.K < 1024 || t4 > simds * 11 / 8 ? 1 : (t4 > simds * 5 / 4 ? 2 : 4);
     } else if (t.K < 1024) {
         q.wn = 2, q.staged = t4 >= simds * 5 / 8;
-    } else if (t4 >= simds * 3 / 8) {
+    } else if (t4 >= simds * 3 / (t.KH * t.KW > 1 ? 16 : 8)) {
         q.skw = t4 >= simds * 5 / 8 ? 2 : 4;
     } else {
         q.wn = 2, q.skw = 4, q.staged = t2 >= simds * 3 / 16 && (double)t.M * t.N * t.K >= 6e8;
