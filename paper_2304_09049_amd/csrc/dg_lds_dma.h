@@ -27,8 +27,9 @@ __device__ __forceinline__ void dg_load16_to_lds(const uint8_t *address, uint32_
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                  :: "v"(address), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
 }
-// The same from a buffer: `offset` bytes into it, and `scalar` more (the same in every lane).  The hardware compares the lane's
-// offset with the buffer's size: a load from outside reads as zeros and touches no memory.
+// The same from a buffer: `offset` bytes into it.  The hardware compares the lane's offset with the buffer's size: a load from outside
+// reads as zeros and touches no memory.  There is no scalar offset (soffset is 0): it is not part of what is compared -- it comes off the
+// size, in 32 bits -- and one beyond the size would make the difference wrap and every lane's offset count as inside.
 __device__ __forceinline__ dg_v4i dg_buffer(const uint8_t *base, uint32_t bytes)
 {
     const uint64_t b = (uint64_t)base;
@@ -36,10 +37,10 @@ __device__ __forceinline__ dg_v4i dg_buffer(const uint8_t *base, uint32_t bytes)
                     __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
 }
 template <int MORE = 0>      // (added to `lds`)
-__device__ __forceinline__ void dg_load16_to_lds(const dg_v4i &buffer, uint32_t offset, uint32_t scalar, uint32_t lds)
+__device__ __forceinline__ void dg_load16_to_lds(const dg_v4i &buffer, uint32_t offset, uint32_t lds)
 {
-    asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :: "v"(offset), "s"(buffer), "s"(scalar), "s"(__builtin_amdgcn_readfirstlane(lds)), "n"(MORE) : "memory", "m0", "scc");
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+                 :: "v"(offset), "s"(buffer), "s"(__builtin_amdgcn_readfirstlane(lds)), "n"(MORE) : "memory", "m0", "scc");
 }
 template <int OUTSTANDING = 0>
 __device__ __forceinline__ void dg_wait_for_loads()

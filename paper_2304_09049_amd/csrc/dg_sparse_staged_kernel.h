@@ -310,16 +310,16 @@ smfmac_staged_kernel(Args a)
             };
             const uint32_t off0 = pixel_offset(c0), off1 = pixel_offset(c1);
             const uint32_t w_off = live ? (uint32_t)(lseg ? c1 : c0) * 16 : 0x80000000u, x_off = lseg ? off1 : off0;
-            dg_for<RB>([&](auto bm) { dg_load16_to_lds<bm * 1024>(w_buffer, w_ld[bm] + w_off, 0u, dst); });
-            dg_for<WN>([&](auto bn) { dg_load16_to_lds<(RB + bn) * 1024>(x_buffer, x_ld[bn] + x_off, 0u, dst); });
+            dg_for<RB>([&](auto bm) { dg_load16_to_lds<bm * 1024>(w_buffer, w_ld[bm] + w_off, dst); });
+            dg_for<WN>([&](auto bn) { dg_load16_to_lds<(RB + bn) * 1024>(x_buffer, x_ld[bn] + x_off, dst); });
             ++fetched;
             return;
         }
         const uint32_t w_off = live ? (uint32_t)fetched * 32 : 0x80000000u;
-        dg_for<RB>([&](auto bm) { dg_load16_to_lds<bm * 1024>(w_buffer, w_ld[bm], w_off, dst); });
+        dg_for<RB>([&](auto bm) { dg_load16_to_lds<bm * 1024>(w_buffer, w_ld[bm] + w_off, dst); });
         const uint32_t tap_off = live ? (uint32_t)((kh * p.W + kw) * cq + cib) : 0x80000000u;
-        // (the whole offset in the register that is checked: a tap above the first image is "negative")
-        dg_for<WN>([&](auto bn) { dg_load16_to_lds<(RB + bn) * 1024>(x_buffer, x_ld[bn] + tap_off, 0u, dst); });
+        // (a tap above the first image is "negative": beyond the buffer's size like what lies past its end)
+        dg_for<WN>([&](auto bn) { dg_load16_to_lds<(RB + bn) * 1024>(x_buffer, x_ld[bn] + tap_off, dst); });
         fetched += stride;
         cib += 32 * stride;
         if constexpr (TURNS) {
