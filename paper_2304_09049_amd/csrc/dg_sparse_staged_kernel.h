@@ -198,8 +198,12 @@ __device__ __forceinline__ void dg_for(F &&f)
     }
 }
 
+// Registers: the narrow tiles are held to 128 (with two planes and wavefronts taking turns to 168), so that four (three) wavefronts share a SIMD
+// and up to 1024 (768) shared tiles are all resident at once.  At 132 - 136 (180) they ran in two rounds: 56x56x128 -> 160 3x3 at batch 4 (980
+// tiles) 10.6 us against 9.2, 28x28x1024 -> 160 1x1 at batch 16 8.3 against 7.6, two planes 28x28x1024 -> 256 1x1 at batch 6 (592) 10.1 against
+// 8.5.  A spill is no way there: its scratch memory alone costs a launch 0.3 us.
 template <int WM, int WN, int SKW, bool TURNS, bool HALF, bool NIB, bool TWO>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, WN > 2 ? 2 : (TWO ? (TURNS ? 3 : 2) : 4))
 smfmac_staged_kernel(Args a)
 {
     static_assert(!HALF || SKW == 1, "taps of half runs: unshared tiles only");
@@ -231,8 +235,9 @@ smfmac_staged_kernel(Args a)
     static_assert(4 * REGION + Table::BYTES <= 80 * 1024, "two workgroups per compute unit (160 KB of LDS)");
     __shared__ uint4 s_mem[(4 * REGION + Table::BYTES) / 16];
     char *s_table = (char *)s_mem + 4 * REGION;
-    // the narrower tiles have the registers for a second set of kept bytes, (0, 1), which spares the odd codes' shift
-    constexpr bool SHIFT_ODD = MN >= 7;
+    // the narrower tiles have the registers for a second set of kept bytes, (0, 1), which spares the odd codes' shift (with two planes: where
+    // two wavefronts per SIMD are enough)
+    constexpr bool SHIFT_ODD = MN >= 7 || (TWO && WN <= 2 && TURNS);
     const DgProblem &p = a.p;
     typename Table::Entry entry = Table::load(a.pools, threadIdx.x);
     dg_fetch_arguments<sizeof(a)>();
@@ -291,7 +296,6 @@ smfmac_staged_kernel(Args a)
 #pragma unroll
     for (int bn = 0; bn < WN; ++bn)
         x_ld[bn] = (uint32_t)make_column(p, a.div_ow, a.div_oh, n0 + bn * 32 + lrow, cq, HALF ? 0 : lseg * 16).off0;
-    const char *stage = (const char *)s_mem + w4 * REGION;
     const uint32_t stage_lds = dg_lds_address(s_mem) + w4 * REGION;
     // filter tap and byte within the pixel of the run fetched next, and its buffer
     int kh = (int)fdiv((uint32_t)tap0, a.div_kw), kw = tap0 - kh * p.KW, cib = rt0 * 32, fetched = g0;
@@ -367,9 +371,17 @@ smfmac_staged_kernel(Args a)
     float sc_cols[RB];
     dg_mfma_column_scales<RB, true>(p, m0, lane, sc_cols);
 
-    // Words of a chunk (64 positions): of weight row r both halves' 8 bytes, of pixel r its own half's.  Lane offsets into a buffer,
-    // for the run's two chunks:
-    const int w_at[2] = {slot0 * 16, (slot0 ^ 1) * 16}, x_at[2] = {slot0 * 16 + h * 8, (slot0 ^ 1) * 16 + h * 8};
+    // Words of a chunk (64 positions): of weight row r both halves' 8 bytes, of pixel r its own half's.  Lane offsets into a buffer
+    // for a run's first chunk; its second chunk's differ in bit 4 (worked out with the buffer's place in one instruction: kept beside
+    // the first's, which the compiler would do, they are registers that the narrow tiles do not have).
+    const uint32_t w_at = slot0 * 16, x_at = slot0 * 16 + h * 8;
+    auto place = [&](uint32_t at, uint32_t buf, int s) -> const char * {
+        const uint32_t base = w4 * REGION + buf;            // (a multiple of 1024)
+        if (s == 0) return (const char *)s_mem + (at + base);
+        uint32_t second;
+        asm("v_xad_u32 %0, %1, 16, %2" : "=v"(second) : "v"(at), "s"(base));
+        return (const char *)s_mem + second;
+    };
     struct Weights {
         uint2 ca[RB], ca1[RB];
     };
@@ -377,17 +389,17 @@ smfmac_staged_kernel(Args a)
         uint2 cb[WN];
     };
     auto read_weights = [&](Weights &w, uint32_t buf, int s) {
-        const char *src = stage + buf;
+        const char *src = place(w_at, buf, s);
 #pragma unroll
         for (int bm = 0; bm < RB; ++bm) {
-            const uint4 q = *(const uint4 *)(src + bm * 1024 + w_at[s]);
+            const uint4 q = *(const uint4 *)(src + bm * 1024);
             w.ca[bm] = make_uint2(q.x, q.y), w.ca1[bm] = make_uint2(q.z, q.w);
         }
     };
     auto read_pixels = [&](Pixels &x, uint32_t buf, int s) {
-        const char *src = stage + buf;
+        const char *src = place(x_at, buf, s);
 #pragma unroll
-        for (int bn = 0; bn < WN; ++bn) x.cb[bn] = *(const uint2 *)(src + (RB + bn) * 1024 + x_at[s]);
+        for (int bn = 0; bn < WN; ++bn) x.cb[bn] = *(const uint2 *)(src + (RB + bn) * 1024);
     };
     const uint32_t pick = sparse_pick(h);
     auto word = [](const uint2 &v, int t) { return t ? v.y : v.x; };
@@ -528,6 +540,8 @@ smfmac_staged_kernel(Args a)
         dg_wait_for_loads();                                   // (unused fetches past the end: their LDS writes end before the wavefront does)
     }
     if (SKW == 1 && !active) return;                       // (whole wavefronts; no barrier follows on this path)
+    // (this lane's number once more, which takes no register of the walk's)
+    const int lane_out = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     // (The scales are in: said here, or the compiler, which cannot tell across the stores' branches, waits for them -- and with them for
     // every store before -- again at each group of stores.)
 #pragma unroll
@@ -542,13 +556,13 @@ smfmac_staged_kernel(Args a)
             for (int e = 0; e < 16; ++e)
                 out[bm][bn][e] = TWO ? (int)((uint32_t)acc[0][bn][e] + ((uint32_t)acc[WM - 1][bn][e] << 8)) : acc[bm][bn][e];
     if (SKW == 1) {
-        dg_mfma_store_tile<RB, WN, true, true>(p, out, m0, n0, lane, sc_cols);
+        dg_mfma_store_tile<RB, WN, true, true>(p, out, m0, n0, lane_out, sc_cols);
         return;
     }
     // Every wavefront's sums take the place of its own staging rows (its last loads have landed), 16 bytes per lane and group of four
     // sum registers; once all are there, each wavefront of the tile adds up and stores a share of the groups: 8 rows of
     // 32 channels each.  (The sums met by atomic additions before, with two barriers more, and with two blocks two of four wavefronts stored.)
-    uint4 *const mine = s_mem + w4 * (REGION / 16) + lane;
+    uint4 *const mine = s_mem + w4 * (REGION / 16) + lane_out;
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -558,7 +572,7 @@ smfmac_staged_kernel(Args a)
         }
     __syncthreads();
     if (!active) return;
-    const uint4 *const theirs = s_mem + (w4 - ks) * (REGION / 16) + lane;
+    const uint4 *const theirs = s_mem + (w4 - ks) * (REGION / 16) + lane_out;
     static_assert(SKW == 1 || RB == 1, "a share's blocks are one row of blocks");
     constexpr int GROUPS = NB * 4 / SKW, NQ = GROUPS < 4 ? GROUPS : 4;        // this wavefront's, and those of a block among them
 #pragma unroll
@@ -574,7 +588,7 @@ smfmac_staged_kernel(Args a)
                 sum[q] += (v4i){(int)t.x, (int)t.y, (int)t.z, (int)t.w};
             }
         }
-        dg_mfma_store_quads<NQ>(p, sum, q0, m0, n0 + i * 32, lane, sc_cols[0]);
+        dg_mfma_store_quads<NQ>(p, sum, q0, m0, n0 + i * 32, lane_out, sc_cols[0]);
     }
 }
 

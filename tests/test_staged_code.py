@@ -1,0 +1,43 @@
+"""The staged kernel's machine code, compiled here: what its loads rely on, and the registers that its narrow tiles may take."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2304_09049_amd.build import HIPCC_FLAGS
+
+
+def compile_forms(tmp_path, forms, *flags):
+    """The listing of the kernel's instantiations <WM, WN, SKW, TURNS, HALF, NIB, TWO>."""
+    source, listing = tmp_path / "forms.hip", tmp_path / "forms.s"
+    source.write_text('#include "dg_sparse_staged_kernel.h"\n' +
+                      "".join(f"template __global__ void dgoh::smfmac_staged_kernel<{f}>(dgoh::Args);\n" for f in forms))
+    common = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *common, *flags, "--cuda-device-only", "-S", str(source), "-o", str(listing)],
+                   check=True, stderr=subprocess.DEVNULL)
+    return listing.read_text()
+
+
+def test_no_staged_load_has_a_scalar_offset(tmp_path):
+    """The hardware holds a buffer load's LANE offset against the buffer's size, and takes a scalar offset off that size in 32 bits, so
+    a load that is switched off (past the end of K) through its scalar offset is not outside at all."""
+    text = compile_forms(tmp_path, ["1, 2, 4, false, false, false, false", "1, 2, 1, false, true, false, false",       # whole runs, half runs
+                                    "1, 4, 4, true, false, true, false", "2, 4, 2, false, false, false, true"],        # 4-bit slots, two planes
+                         "-O1")
+    offsets = re.findall(r"buffer_load_dwordx4 v\d+, s\[\d+:\d+\], (\S+) offen lds", text)
+    assert len(offsets) >= 4 * 3 * 2 and set(offsets) == {"0"}, set(offsets)
+
+
+# (512 registers per SIMD lane, handed out by eights: 128 for four wavefronts, 168 for three)
+@pytest.mark.parametrize("most,forms", [(128, [f"1, 2, {s}, {nib}, false" for s in ("1, false, false", "1, false, true", "2, false, false", "2, true, false",
+                                                                                     "4, false, false", "4, true, false") for nib in ("false", "true")]),
+                                        (168, ["2, 2, 4, true, false, false, true"])])
+def test_narrow_tiles_leave_room_for_the_next_workgroups(tmp_path, most, forms):
+    """Layers of up to 1024 narrow tiles that four wavefronts share are all resident at once -- if a SIMD holds four of them (two planes without a
+    filter window: three) -- and run in two rounds otherwise."""
+    text = compile_forms(tmp_path, forms)
+    registers = [int(n) for n in re.findall(r"\.vgpr_count:\s+(\d+)", text)]
+    assert len(registers) == len(forms) and max(registers) <= most, registers
+    assert set(re.findall(r"\.private_segment_fixed_size:\s+(\d+)", text)) == {"0"}
+    assert max(int(n) for n in re.findall(r"\.group_segment_fixed_size:\s+(\d+)", text)) * (512 // most) <= 160 * 1024
