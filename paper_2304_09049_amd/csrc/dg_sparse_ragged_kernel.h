@@ -20,7 +20,7 @@
 // were loaded), the end 0.9 (2.0 with a bounds test, an address and a load of the scale for every element).  With the last window fetching no other
 // (it made a tile's wavefronts, of three windows or so each, wait for loads that nobody used): 28x28x48 -> 120 11.7 -> 10.2, 28x28x208 -> 256 1x1 at
 // batch 4 10.1 -> 6.6, 14x14x100 -> 100 3x3 at batch 8 packed 6.4 -> 5.8, 56x56x20 -> 128 at batch 4 10.6 -> 8.1, 7x7x500 -> 200 at batch 16 12.1 -> 10.5
-// (unshared tiles with many windows, 57x57x36 -> 128 at batch 4: 9.8 -> 10.2).
+// (unshared tiles with many windows, 57x57x36 -> 128 at batch 4: 8.65 -> 8.75; one loop for them, the last window fetching another, 9.15).
 // Measured against the permute kernel (Cin % 16 == 0) and the LDS kernel that ran these layers before, packed codes, graph replays:
 // 8x29x27x48 -> 120 5x5 43.1 -> 8.6 us (0.2 of the rate at which the instruction can select: 1.8 us), 28x28x112 -> 224 3x3 at batch
 // 16 76.5 -> 16.3, 57x57x36 -> 128 3x3 at batch 4 142 -> 8.9, 56x56x16 -> 32 for one image 6.2 -> 3.8 (a launch: 1.6).
@@ -72,8 +72,6 @@ smfmac_ragged_kernel(RaggedArgs a)
     __shared__ int32_t s_sum[NB * 1024];                    // [block][accumulator register][lane]
     const DgProblem &p = a.p;
     const int lane = threadIdx.x & 63, ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), S = blockDim.x >> 6;
-    // the table's entry that this thread writes, asked for with the arguments
-    const uint2 entry = make_uint2(a.pools.w[threadIdx.x & 3], a.pools.w[(threadIdx.x >> 2) & 3]);
     const int r = lane & 31, h = lane >> 5;
     const int tile = (int)xcd_contiguous(blockIdx.x, gridDim.x);
     const int m0 = (tile % a.tiles_m) * (WM * 32), n0 = (tile / a.tiles_m) * (WN * 32);
@@ -132,10 +130,13 @@ smfmac_ragged_kernel(RaggedArgs a)
         if (++win == a.windows) win = 0, ++pair;            // (uniform)
     };
 
+    // The table's rows come with the other scalar arguments, before the first loads: as two loads per lane at the kernel's start, written
+    // while the first window's were on their way, they made 59 of 105 layers 2 - 15 % slower (31x28x88 -> 316 1x1 at batch 7 5.6 ->
+    // 6.5 us, 14x14x100 -> 100 3x3 at batch 8 4.4 -> 4.6), and none faster by more than 2 %.
+    sparse_fill_table(s_rows, a.pools, threadIdx.x);
     Window w;
     fetch(w);
-    // the table and every wavefront's zeroes go to LDS while the loads are on their way
-    if (threadIdx.x < 16) s_rows[threadIdx.x] = entry;
+    // every wavefront's zeroes go to LDS while the loads are on their way
     if (through_lds)
         for (int i = threadIdx.x; i < NB * 1024; i += blockDim.x) s_sum[i] = 0;
     v16i acc[WM][WN];

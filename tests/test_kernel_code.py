@@ -1,4 +1,5 @@
-"""The staged kernel's machine code, compiled here: what its loads rely on, and the registers that its narrow tiles may take."""
+"""Kernels' machine code, compiled here: what the staged kernel's loads rely on, the registers that its narrow tiles may take, and how the kernel
+for ragged channel counts reads its table."""
 import os
 import re
 import subprocess
@@ -8,11 +9,11 @@ import pytest
 from paper_2304_09049_amd.build import HIPCC_FLAGS
 
 
-def compile_forms(tmp_path, forms, *flags):
-    """The listing of the kernel's instantiations <WM, WN, SKW, TURNS, HALF, NIB, TWO>."""
+def compile_forms(tmp_path, forms, *flags, header="dg_sparse_staged_kernel.h", kernel="smfmac_staged_kernel", arguments="Args"):
+    """The listing of a kernel's instantiations (the staged kernel's: <WM, WN, SKW, TURNS, HALF, NIB, TWO>)."""
     source, listing = tmp_path / "forms.hip", tmp_path / "forms.s"
-    source.write_text('#include "dg_sparse_staged_kernel.h"\n' +
-                      "".join(f"template __global__ void dgoh::smfmac_staged_kernel<{f}>(dgoh::Args);\n" for f in forms))
+    source.write_text(f'#include "{header}"\n' +
+                      "".join(f"template __global__ void dgoh::{kernel}<{f}>(dgoh::{arguments});\n" for f in forms))
     common = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *common, *flags, "--cuda-device-only", "-S", str(source), "-o", str(listing)],
                    check=True, stderr=subprocess.DEVNULL)
@@ -41,3 +42,14 @@ def test_narrow_tiles_leave_room_for_the_next_workgroups(tmp_path, most, forms):
     assert len(registers) == len(forms) and max(registers) <= most, registers
     assert set(re.findall(r"\.private_segment_fixed_size:\s+(\d+)", text)) == {"0"}
     assert max(int(n) for n in re.findall(r"\.group_segment_fixed_size:\s+(\d+)", text)) * (512 // most) <= 160 * 1024
+
+
+def test_ragged_table_comes_with_the_scalar_arguments(tmp_path):
+    """Read from the arguments lane by lane, the table's rows were two vector loads that every launch waited for."""
+    text = compile_forms(tmp_path, [], header="dg_sparse_ragged_kernel.h")        # (its launches instantiate every form)
+    kernels = re.findall(r"^(_ZN4dgoh20smfmac_ragged_kernelILi(\d)ELi(\d)ELi(\d)\S+):(.*?)s_barrier", text, re.M | re.S)
+    assert len(kernels) == 3 * 4 * 2
+    for name, wm, wn, ch, start in kernels:
+        # single words before the barrier: a scale per block of channels, and operands of one word (packed activations too)
+        words = int(wm) + (2 * int(wm) + int(wn) if ch == "1" else 0)
+        assert len(re.findall(r"global_load_dword ", start)) <= words, name
