@@ -244,13 +244,15 @@ int sparse_tile_hint(const dg_lut *lut, const DgProblem &t)
     return dense.wn > 4 ? 4 : dense.wn;
 }
 
+// The staged kernel keeps a byte per bound of the filter window, and counts a tile's weight bytes in 31 bits.
+bool staged_counts(const DgProblem &t) { return t.KH <= 127 && t.KW <= 127 && t.K < 1 << 26; }
+
 // The tiled kernel with operands staged through LDS (dg_sparse_staged_kernel.h) takes the unshared tiles of layers
 // whose filter taps are whole 32-byte runs of packed codes, or -- its two narrow tiles, unshared -- whole 16-byte chunks.
 // DG_ONEHOT_STAGED=0 keeps the direct loads (A/B measurement).
-// (The kernel keeps a bit per row and per column of the filter window, and counts a tile's weight bytes in 31 bits.)
 bool staged_takes(const DgProblem &t)
 {
-    if (t.KH > 15 || t.KW > 15 || t.K >= 1 << 26) return false;
+    if (!staged_counts(t)) return false;
     if (t.Cin % 64 != 0 || (uintptr_t)t.Wp % 16 != 0 || (uintptr_t)t.Xp % 16 != 0) return false;
     if (const char *e = dg_override("DG_ONEHOT_STAGED")) return atoi(e) != 0;
     return true;
@@ -935,7 +937,7 @@ Plan staged2p_plan(const DgProblem &t)
         if (t.Cin % 128 == 0) q.wn = atoi(force) == 4 ? 4 : 2, q.skw = strstr(force, "k4") ? 4 : (q.wn == 4 && strstr(force, "k2") ? 2 : 1);
     }
     if (t.Cin % 64 != 0 || (uintptr_t)t.Wp % 16 != 0 || (uintptr_t)t.Xp % 16 != 0) q.staged = false;
-    if (t.KH > 15 || t.KW > 15 || t.K >= 1 << 26) q.staged = false;       // (staged_takes)
+    if (!staged_counts(t)) q.staged = false;
     return q;
 }
 

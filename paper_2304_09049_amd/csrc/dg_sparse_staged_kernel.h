@@ -349,15 +349,16 @@ smfmac_staged_kernel(Args a)
     // ---- the consumer's side: row / pixel r (lane half h) of every block; its slot of segment s is slot0 ^ s
     const int slot0 = 2 * r + ((r >> 3) & 1);
     const uint32_t copy = Table::copy(lane);
-    // which rows (bits 0 ... 15) and columns (16 ... 31) of the filter window lie inside the image for pixel r of a block (none beyond N)
+    // Which rows h0 ... h1 - 1 and columns w0 ... w1 - 1 of the filter window lie inside the image for pixel r of a block (beyond N: none,
+    // h1 = h0), as the bytes h0, 128 - h1, w0, 128 - w1: kept_bytes asks for all four bounds with one subtraction.
     uint32_t window[WN];
     int taps_in[WN];
 #pragma unroll
     for (int bn = 0; bn < WN; ++bn) {
         const Column c = make_column(p, a.div_ow, a.div_oh, n0 + bn * 32 + r, cq, 0);
-        const int h0 = min(max(0, -c.ih0), 15), h1 = c.ok ? max(h0, min(p.KH, p.H - c.ih0)) : h0;
-        const int w0 = min(max(0, -c.iw0), 15), w1 = max(w0, min(p.KW, p.W - c.iw0));
-        window[bn] = (((1u << (h1 - h0)) - 1u) << h0) | (((1u << (w1 - w0)) - 1u) << (16 + w0));
+        const int h0 = min(max(0, -c.ih0), 127), h1 = c.ok ? max(h0, min(p.KH, p.H - c.ih0)) : h0;
+        const int w0 = min(max(0, -c.iw0), 127), w1 = max(w0, min(p.KW, p.W - c.iw0));
+        window[bn] = 0x80008000u + (uint32_t)(h0 - (h1 << 8)) + ((uint32_t)(w0 - (w1 << 8)) << 16);
         taps_in[bn] = (h1 - h0) * (w1 - w0);
     }
 
@@ -413,10 +414,11 @@ smfmac_staged_kernel(Args a)
     // or zeros outside the image (or for a chunk past the end of K)
     auto kept_bytes = [&](int tap, bool live) {
         const int khc = (int)fdiv((uint32_t)tap, a.div_kw), kwc = tap - khc * p.KW;
+        // bytes 128 + khc, 255 - khc, 128 + kwc, 255 - kwc: none borrows from the next, and 128 stays of each whose bound holds
+        const uint32_t at = 0xFF80FF80u + (uint32_t)khc * 0xFFFFFF01u + ((uint32_t)kwc << 16) - ((uint32_t)kwc << 24);
 #pragma unroll
         for (int bn = 0; bn < WN; ++bn) {
-            const uint32_t v = live ? (window[bn] >> khc) & (window[bn] >> (16 + kwc)) & 1u : 0u;
-            const int x = (int)(v * 0x00010001u);
+            const int x = live && ((at - window[bn]) & 0x80808080u) == 0x80808080u ? 0x00010001 : 0;
             ones[bn] = (v4i){x, x, x, x};
             if constexpr (!SHIFT_ODD) {
                 const int y = x << 8;
