@@ -184,12 +184,14 @@ onehot_f32_kernel(F32Args a)
 }   // namespace
 
 // AUTO compares what the two kernels take per position of K.  This one: 2 + 16.7 w ns, w the wavefronts on the busiest SIMD (a
-// workgroup of four blocks per compute unit at a time; w = 1: 17.5 - 21 ns measured, 2: 37, 3: 52, 4: 68).  The plain one: the
-// outputs at 5.8 thousand per ns -- 5.4 to 7.9 measured, half of that where it reads bytes (Cin % 16 != 0) -- and 21 at least, below which
-// its own chain of additions does not get (50 to 100 thousand outputs: 21.2 - 22.6).  Of 39 layers it misses none by more than 4 %:
-// 14x14x256 -> 256 3x3 at batch 2 (400 blocks) goes over (54.0 -> 44.1 us), 28x28x32 -> 72 too (10.9 -> 9.8), 56x56x32 -> 40 at batch 2 (1176
-// blocks) 15.5 -> 14.7; with fewer than 256 blocks or shorter K the two are within 4 % of each other or the plain one is ahead
-// (28x28x64 -> 64 1x1 5.1 against 6.3).
+// workgroup of four blocks per compute unit at a time; w = 1: 17.5 - 21 ns measured, 2: 37, 3: 52, 4: 68), and a start 0.2 us longer than the
+// plain one's; with few positions, or a second word per tap that is mostly empty (Cin = 20 ... 28), 7 + 19.5 w in all.  The plain one: the
+// outputs at 5.8 thousand per ns -- 5.4 to 7.9 measured, half of that where it reads bytes (Cin % 16 != 0) -- and 21 at least where K is long, below
+// which its own chain of additions does not get (50 to 100 thousand outputs: 21.2 - 22.6; one word per load here, Cin % 32 == 16, is no
+// faster).  Of 215 layers of 40 to 400 thousand outputs the choice costs 1.1 % over the better one on average, 4 % at most against 7 + 19.5 w for all
+// and no chain, 5 % less than it on average: 14x14x256 -> 256 3x3 at batch 2 (400 blocks) goes over (52.1 -> 43.8 us), 28x28x32 -> 72 3x3 at
+// batch 2 9.4 -> 8.4, 28x28x100 -> 48 3x3 at batch 2 40.5 -> 28.0; 7x7x16 -> 576 1x1 at batch 4 stays (2.9 against 3.1), 28x28x20 -> 16 1x1 at
+// batch 5 (2.9 against 3.5), 14x14x48 -> 320 5x5 (28.8 against 30.4) and 28x28x32 -> 72 1x1 at batch 2 (3.2 against 3.3) too.
 // DG_F32_MFMA: 0 never, 1 whatever the size.
 bool dg_onehot_f32_preferred(const dg_lut *lut, const DgProblem &p)
 {
@@ -203,8 +205,10 @@ bool dg_onehot_f32_preferred(const dg_lut *lut, const DgProblem &p)
     if ((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4) >= ((int64_t)1 << 31)) return false;      // (32-bit byte offsets)
     if (const char *f = dg_override("DG_F32_MFMA")) return atoi(f) != 0;
     const int64_t groups = (blocks + 3) / 4, units = dg_simd_count() / 4;
-    const double here = 2.0 + 16.7 * (double)((groups + units - 1) / units), chain = blocks >= 256 && p.K >= 256 ? 21.0 : 0.0;
+    const double w = (double)((groups + units - 1) / units), few = 5.0 + 2.8 * w, start = 200.0 / p.K;
+    const double here = 2.0 + 16.7 * w + (few < start || (p.Cin < 32 && p.Cin % 16 != 0) ? few : start);
     const double plain = (double)p.M * p.N / (p.Cin % 16 == 0 ? 5800.0 : 2900.0);
+    const double chain = blocks >= 256 && p.K > 256 && p.Cin % 32 == 0 ? 21.0 : 0.0;
     return here < (plain > chain ? plain : chain);
 }
 

@@ -191,6 +191,19 @@ def test_empty_launch_rejects_bad_grids_before_launching():
     assert L.dg_launch_empty(1 << 40, 64, None) == 2
 
 
+@pytest.mark.parametrize("layer,name", [((4, 7, 7, 16, 576, 1), "lds_f32"), ((2, 14, 14, 16, 320, 1), "lds_f32"), ((5, 28, 28, 20, 16, 1), "lds_f32"),
+                                        ((2, 28, 28, 32, 72, 1), "lds_f32"), ((23, 7, 7, 48, 96, 3), "lds_f32"),
+                                        ((1, 14, 14, 256, 320, 1), "lds_f32"),          # a start that few positions do not pay for, half words
+                                        ((13, 7, 7, 32, 256, 1), "onehot_mfma_f32"), ((3, 56, 56, 16, 32, 1), "onehot_mfma_f32"),
+                                        ((2, 28, 28, 32, 72, 3), "onehot_mfma_f32"), ((2, 14, 14, 256, 256, 3), "onehot_mfma_f32"),
+                                        ((2, 28, 28, 100, 48, 3), "onehot_mfma_f32"), ((6, 7, 7, 200, 192, 3), "onehot_mfma_f32")])
+def test_binary32_rule(layer, name):
+    """Which kernel a layer's binary32 table runs on, where the two measured apart (256 compute units)."""
+    B, H, W, Cin, Cout, k = layer
+    lut = dg.dg_build_lut_f32((-1.27, -0.32, 0.32, 1.27), (0.05, 0.45, 0.98, 1.78))
+    assert dg.dg_conv_kernel_name(lut, dg.conv_desc(B, H, W, Cin, Cout, k, k, (1, 1), (k // 2, k // 2))) == name
+
+
 def test_kernel_names_need_no_gpu():
     # the plan functions are host code: small layers split K, large ones get a wave tile, wide entries two planes
     lut = dg.dg_build_lut((-2, -1, 0, 1), (0, 1, 2, 3))
