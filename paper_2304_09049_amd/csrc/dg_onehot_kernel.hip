@@ -902,11 +902,14 @@ namespace {
 //                                     pay for the packing kernel that the split-K kernel's one-call form spares; below 192
 //                                     tiles split K is ahead (7x7x512 -> 512 3x3 at batch 8: 10.2 against 11.1)
 //   where the lines lie               3x3 layers, 32 x 64 by 4 against 32 x 128 by 4: 200 tiles of the latter 12.6, 12.2; 208 17.5, 16.4; 296
-//                                     17.7, 16.6; 343 13.1, 12.1; 344 17.4, 16.6; 1x1 with K = 1024: 200 tiles 7.9, 8.0; 300 9.7, 10.9 (measured
-//                                     on the kernel before); 400 13.3, 11.0.
+//                                     17.7, 16.6; 343 13.1, 12.1; 344 17.4, 16.6; 1x1 with K = 1024: 200 tiles 6.8, 6.9; 300 8.5, 9.5; 400
+//                                     10.6, 9.4; with K = 2048 9.4, 9.0; 12.6, 14.0; 16.2, 14.3.
 //                                     32 x 128 by 4 against by 2: 592 tiles 24.2, 26.8; 784 30.1, 27.7.  Unshared, by 2, by 4:
 //                                     1032 tiles 44.5, 40.6, 37.6; 1176 45.8, 41.2, 37.8; 1280 45.9, 41.2, 39.2; 1376 46.1, 41.1, 44.3; 1568
-//                                     46.4, 52.3, 50.9 (a second tile on a few SIMDs takes as long as one on all)
+//                                     46.4, 52.3, 50.9 (a second tile on a few SIMDs takes as long as one on all); one for
+//                                     every SIMD, 1024, 27.7, 30.1, 32.3 (other layers).  1x1, K = 1024: 1024 tiles 15.3, 16.0, 18.3; 1028
+//                                     23.9, 21.1, 22.0; 1280 23.7, 21.8, 22.2; 1344 24.0, 22.1, 25.8; K = 2048: 1024 25.1, 26.4, 28.8; 1028
+//                                     39.7, 35.0, 33.5; 1280 40.5, 36.6, 35.5; 1344 40.7, 38.4, 39.9
 //   K = 512 ... 1023                  28x28x512 -> 256 at batch 16 (784 tiles of 32 x 128) 12.6 -> 10.7 unshared; with 392 8.3 against 8.5
 //   shorter K, up to 64 channels      56x56x256 -> 64 at batch 16 8.9 -> 7.7, 56x56x128 -> 64 6.9 -> 6.6; with more channels such a
 //                                     layer is its output's stores (28x28x128 -> 512 at batch 32: 16.4 against 17.6)
@@ -924,7 +927,7 @@ Plan staged2p_plan(const DgProblem &t)
     } else if (t.K < 512) {
         q.wn = 2, q.staged = t2 >= simds && t.M <= 64;
     } else if (t4 >= simds) {
-        q.skw = t.K < 1024 || t4 > simds * 11 / 8 ? 1 : (t4 > simds * 5 / 4 ? 2 : 4);
+        q.skw = t.K < 1024 || t4 == simds || t4 > simds * 11 / 8 ? 1 : (t4 > simds * 5 / 4 ? 2 : 4);
     } else if (t.K < 1024) {
         q.wn = 2, q.staged = t4 >= simds * 5 / 8;
     } else if (t4 >= simds * 3 / (t.KH * t.KW > 1 ? 16 : 8)) {

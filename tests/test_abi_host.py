@@ -204,6 +204,16 @@ def test_binary32_rule(layer, name):
     assert dg.dg_conv_kernel_name(lut, dg.conv_desc(B, H, W, Cin, Cout, k, k, (1, 1), (k // 2, k // 2))) == name
 
 
+def test_two_plane_sharing_rule():
+    """32 x 128 tiles of entries beyond int8: shared by four or two wavefronts where a second round of them would be short, and not
+    where there is one tile for every SIMD (256 compute units)."""
+    wide = dg.dg_build_lut((127, -128, 5, 0), (-128, 127, 1, 0), dg.DG_LUT_I16)
+    for k, Cin in ((1, 1024), (3, 256)):
+        for tiles, share in ((1020, "_k2"), (1024, ""), (1028, "_k4"), (1280, "_k4"), (1284, "_k2"), (1408, "_k2"), (1412, "")):
+            desc = dg.conv_desc(tiles // 2, 8, 8, Cin, 128, k, k, (1, 1), (k // 2, k // 2))
+            assert dg.dg_conv_kernel_name(wide, desc) == "onehot_smfmac_2p_staged_32x128" + share, (tiles, k)
+
+
 def test_kernel_names_need_no_gpu():
     # the plan functions are host code: small layers split K, large ones get a wave tile, wide entries two planes
     lut = dg.dg_build_lut((-2, -1, 0, 1), (0, 1, 2, 3))
