@@ -221,9 +221,13 @@ smfmac_staged_kernel(Args a)
     // Which table: on narrow tiles, whose operands serve few pixels, its random reads keep LDS busier than the vector instructions they
     // spare are worth (28x28x128 -> 128 3x3 at batch 8, 4-bit codes, 32 x 64 by four: 9.9 us with quads, 9.2 with pairs); with 4-bit slots on
     // the 32 x 128 and 64 x 128 tiles too (28x28x256 -> 256 3x3 at batch 8, 32 x 128 by four: 21.5, 19.5; 28x28x512 -> 256 1x1 at batch 32, unshared:
-    // 22.0, 19.3).  On the others quads are ahead: 8192-cube 740 us with pairs, 706 with quads; 56x56x256 -> 256 3x3 at batch 16, 4-bit,
-    // 32 x 224: 98.2, 96.8.
-    constexpr bool QUADS = WN >= 4 && !(NIB && WN == 4);
+    // 22.0, 19.3).  Unshared 32 x 128 tiles, whose K is short, pay for filling 16 KB of quads, and beside these a compute unit has room for
+    // two workgroups instead of three (56x56x128 -> 128 3x3 at batch 16 16.6 us with quads, 16.2 with pairs; 128x96000x512 17.5, 16.1;
+    // 8192x4096x384 41.5, 38.3; 2048x4080x640, whose output's rows are no whole cache lines, 15.6, 16.4; pairs with room for two workgroups only,
+    // 1024x12032x384 17.3, three 14.8; half runs, with a longer K, 2 % the other way).  On the others quads are ahead: 8192-cube 740 us with pairs,
+    // 706 with quads; 56x56x256 ->
+    // 256 3x3 at batch 16, 4-bit, 32 x 224: 98.2, 96.8.
+    constexpr bool QUADS = WN >= 4 && !(WN == 4 && (NIB || (WM == 1 && SKW == 1 && !HALF)));
     constexpr int LOADS = RB + WN;                          // a run's loads
     constexpr int REGION = SKW > 1 && NB * 4096 > BUFS * BUF ? NB * 4096 : BUFS * BUF;      // a wavefront's: its buffers, then its sums
     typedef std::conditional_t<QUADS, QuadTable<NIB, TWO, (TWO && SKW > 1 ? 2 : 4)>, PairTable<NIB, TWO>> Table;
