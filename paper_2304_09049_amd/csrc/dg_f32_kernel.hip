@@ -19,9 +19,11 @@
 // matrix instructions are issued in one piece, only the next word's table reads between them, and the next word's 28 vector
 // instructions before or behind them in another: 40 cycles per position instead of 51 with the vector instructions
 // spread three at a time.  A sum cannot be split along K, so blocks are small and wavefronts many.  The plain kernel spends 5 vector instructions
-// and an LDS read per addition (3 additions per SIMD and cycle).  Measured against it: 28x28x128 -> 128 3x3 at batch 4 (1568 blocks) 68.7
-// -> 45.5 us (spread: 50), at batch 8 120 -> 81 (89); 56x56x64 -> 64 at batch 8 113 -> 73; 14x14x36 -> 100 3x3 at batch 8 (686) 19.8 -> 14.3.
-// Reading the pairs one at a time, just before their instructions, instead of a word ahead: 57.1 us on the first.
+// and an LDS read per addition (3 additions per SIMD and cycle).  Packed codes, graph replays, the plain kernel, this one: 28x28x128 -> 128 3x3
+// at batch 4 (1568 blocks) 61.1, 42.3 us (spread: 48.8), at batch 8 118.7, 81.2; 56x56x64 -> 64 3x3 at batch 8 109.2, 72.7; 14x14x36 -> 100 3x3 at
+// batch 8 (686) 18.4, 13.1.  Layers of one load per pixel, K = 32, with ten or more blocks per SIMD were 2 - 4 % shorter spread (56x56x32 -> 152 1x1
+// at batch 6 13.7, 14.0), other two-word loads 2 - 30 % longer.
+// Reading the pairs one at a time, just before their instructions, instead of a word ahead: 57.1 us on the first, 48.3 then.
 #include "dg_common.h"
 
 #include <cmath>

@@ -890,17 +890,17 @@ dg_status dg_launch_sparse2p(const dg_lut *lut, const DgProblem &p0, hipStream_t
 namespace {
 
 // Its tiles (32 channels in two planes x 64 or 128 pixels) and which layers are its own.  What bounds it: the
-// instructions beside the matrix ones.  Every weight word costs 16 table reads for both planes' dense operands and the offsets
-// for them, which only the 128-pixel tile spreads over enough matrix instructions (28x28x256 -> 256 3x3 at batch 8: 6.1 VALU and
-// 0.9 LDS instructions per matrix instruction, the pipe busy 0.33 of the cycles at 1.2 wavefronts per SIMD), so that tile
+// instructions beside the matrix ones.  Every weight word costs 8 table reads of four rows (16 of two on the 64-pixel tile) for both planes'
+// dense operands and the offsets for them, which only the 128-pixel tile spreads over enough matrix instructions (28x28x256 -> 256 3x3 at
+// batch 8: 5.0 VALU and 0.8 LDS instructions per matrix instruction, the pipe busy 0.38 of the cycles at 1.2 wavefronts per SIMD), so that tile
 // comes first, its wavefronts sharing K where the tiles alone leave SIMDs idle.  Measured on 36
-// layers against the kernels that ran them before (dense instruction, sparse2p_kernel), packed codes, graph replays, us:
+// layers against the kernels that ran them before (dense instruction, sparse2p_kernel), packed codes, graph replays, us (tiles: of 32 x 128):
 //   32 x 128, from 11/8 per SIMD      56x56x256 -> 256 3x3 at batch 16 (3136 tiles) 114 -> 96.7
 //   32 x 128 shared by 2 / by 4       28x28x256 -> 256 3x3 at batch 16 (784) 42.8 -> 27.6; at batch 8 (392) 27.0 -> 17.7
 //   below 192 of those, 32 x 64 by 4  14x14x256 -> 256 3x3 at batch 8 (104) 12.1 -> 9.3; 14x14x512 -> 512 3x3 at batch 5 (128) 19.7 ->
-//                                     13.1; 7x7x2048 -> 512 at batch 16 (208) 10.8 -> 8.5 -- from 6e8 products on: less does not
+//                                     13.1; 7x7x2048 -> 512 at batch 16 (112) 10.8 -> 8.5 -- from 6e8 products on: less does not
 //                                     pay for the packing kernel that the split-K kernel's one-call form spares; below 192
-//                                     tiles split K is ahead (7x7x512 -> 512 3x3 at batch 8: 10.2 against 11.1)
+//                                     tiles of 32 x 64 split K is ahead (7x7x512 -> 512 3x3 at batch 8: 10.2 against 11.1)
 //   where the lines lie               3x3 layers, 32 x 64 by 4 against 32 x 128 by 4: 200 tiles of the latter 12.6, 12.2; 208 17.5, 16.4; 296
 //                                     17.7, 16.6; 343 13.1, 12.1; 344 17.4, 16.6; 1x1 with K = 1024: 200 tiles 6.8, 6.9; 300 8.5, 9.5; 400
 //                                     10.6, 9.4; with K = 2048 9.4, 9.0; 12.6, 14.0; 16.2, 14.3.
@@ -913,8 +913,8 @@ namespace {
 //   K = 512 ... 1023                  28x28x512 -> 256 at batch 16 (784 tiles of 32 x 128) 12.6 -> 10.7 unshared; with 392 8.3 against 8.5
 //   shorter K, up to 64 channels      56x56x256 -> 64 at batch 16 8.9 -> 7.7, 56x56x128 -> 64 6.9 -> 6.6; with more channels such a
 //                                     layer is its output's stores (28x28x128 -> 512 at batch 32: 16.4 against 17.6)
-//   half runs: 32 x 64, 7/8 per SIMD  56x56x64 -> 64 3x3 at batch 16 (1568) 15.7 -> 13.7, 28x28x192 -> 160 3x3 (980) 23.0 -> 22.0;
-//                                     with 784 tiles 10.2 against 10.9, with 490 22 against 32
+//   half runs: 32 x 64, 7/8 per SIMD  56x56x64 -> 64 3x3 at batch 16 (1568 of those) 15.7 -> 13.7, 28x28x192 -> 160 3x3 (980) 23.0 ->
+//                                     22.0; with 784 tiles 10.2 against 10.9, with 490 22 against 32
 Plan staged2p_plan(const DgProblem &t)
 {
     const int64_t simds = dg_simd_count(), t2 = tile_count(t, 1, 2), t4 = tile_count(t, 1, 4);

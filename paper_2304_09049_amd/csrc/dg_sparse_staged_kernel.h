@@ -22,11 +22,11 @@
 // Where the time goes (timestamps per wavefront at 100 MHz, us; before: the words read a step later, every operand from pairs, the table
 // filled before the first load, sums met by atomic additions, two wavefronts of four storing):
 //   28x28x256 -> 256 3x3 at batch 8, two planes, 32 x 128 by four   start to first words 3.0 -> 2.4, the walk over K 10.3 -> 9.1,
-//                                                                   the end 2.3 -> 2.3; kernel 17.7 -> 15.4, the call 20.2 -> 18.2
-//   8192 x 256 x 8192, 32 x 128 by four                             the walk 34.0 -> 29.7 thousand cycles of the 32.8 thousand its
-//                                                                   matrix instructions take two wavefronts: at 1.7 GHz, what the power allows
-// The walk is bound by the matrix pipe where two wavefronts share a SIMD and the operands serve four pixel blocks or more; a lone wavefront, whose other
-// instructions do not all hide behind its own matrix instructions, spends about 0.48 us per run beside them.
+//                                                                   the end 2.3 -> 2.3; kernel 18.1 -> 16.1, the call 20.9 -> 18.4
+//   8192 x 256 x 8192, 32 x 128 by four                             the walk 20.0 -> 17.5; kernel 27.8 -> 25.9 - 26.8
+// The second's matrix instructions are 32.8 thousand cycles per SIMD, 16.8 us at the 1.95 GHz that the kernel runs at (50.4 thousand cycles in
+// 25.9 us): its walk is the matrix pipe's, and the pipe is busy 0.65 of the kernel.  A lone wavefront, whose other instructions do not all hide
+// behind its own matrix instructions, spends about 0.48 us per run beside them.
 #pragma once
 
 #include "dg_lds_dma.h"
