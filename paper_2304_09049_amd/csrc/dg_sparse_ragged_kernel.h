@@ -71,10 +71,14 @@ smfmac_ragged_kernel(RaggedArgs a)
     __shared__ uint2 s_rows[16];
     __shared__ int32_t s_sum[NB * 1024];                    // [block][accumulator register][lane]
     const DgProblem &p = a.p;
-    const int lane = threadIdx.x & 63, ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), S = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, S = blockDim.x >> 6;
+    int ws = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, h = lane >> 5;
     const int tile = (int)xcd_contiguous(blockIdx.x, gridDim.x);
-    const int m0 = (tile % a.tiles_m) * (WM * 32), n0 = (tile / a.tiles_m) * (WN * 32);
+    int m0 = (tile % a.tiles_m) * (WM * 32), n0 = (tile / a.tiles_m) * (WN * 32);
+    // (these as they are: the compiler keeps what they were made from beside them, and with more than 80 scalar registers a SIMD holds seven
+    // wavefronts instead of eight: 29x29x24 -> 64 5x5 at batch 6, 316 tiles of 13 wavefronts, 6.8 us at 82, 5.4 at 79)
+    asm("" : "+s"(ws), "+s"(m0), "+s"(n0));
     const int L = p.Cin / 4, taps = p.KH * p.KW;
     // this wavefront's windows (the host leaves none without one; the max only keeps an odd launch harmless)
     const int c0 = ws * a.cpw, c1 = max(c0, min(c0 + a.cpw, a.chunks));
@@ -197,15 +201,20 @@ smfmac_ragged_kernel(RaggedArgs a)
     for (int c = c0; c + 1 < c1; ++c) window(std::true_type());
     if (c0 < c1) window(std::false_type());
 
+    // (Every load is in: said once.  A wavefront without windows has its first one's under way, and the compiler would wait for them -- and
+    // with them for the stores -- wherever a store's address takes one of their registers.)
+    __builtin_amdgcn_s_waitcnt(0x0F70);                     // vmcnt(0)
+    // (this lane's number once more, which takes no register of the walk's)
+    const int lane_out = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), r_out = lane_out & 31, h_out = lane_out >> 5;
     if (!through_lds) {
-        dg_mfma_store_tile<WM, WN, true>(p, acc, m0, n0, lane, sc_cols);
+        dg_mfma_store_tile<WM, WN, true>(p, acc, m0, n0, lane_out, sc_cols);
         return;
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            __hip_atomic_fetch_add(&s_sum[(i * 16 + e) * 64 + lane], acc[i / WN][i % WN][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_add(&s_sum[(i * 16 + e) * 64 + lane_out], acc[i / WN][i % WN][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __syncthreads();
     if (!a.n_first && !a.scale_rows && p.stride_cm == 1) {  // (uniform: the channels contiguous, their scales at hand)
         if (S <= NB * 4) {
@@ -213,15 +222,15 @@ smfmac_ragged_kernel(RaggedArgs a)
                 const int i = u >> 2;
                 v4i sum[1];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sum[0][e] = s_sum[(4 * u + e) * 64 + lane];
-                dg_mfma_store_quads<1>(p, sum, u & 3, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane, WM == 1 || i / WN == 0 ? sc_cols[0] : sc_cols[WM - 1]);
+                for (int e = 0; e < 4; ++e) sum[0][e] = s_sum[(4 * u + e) * 64 + lane_out];
+                dg_mfma_store_quads<1>(p, sum, u & 3, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane_out, WM == 1 || i / WN == 0 ? sc_cols[0] : sc_cols[WM - 1]);
             }
             return;
         }
         for (int u = ws; u < NB * 16; u += S) {             // more wavefronts than groups: a register at a time
-            const int i = u >> 4, e = u & 15, m = m0 + (i / WN) * 32 + r, n = n0 + (i % WN) * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+            const int i = u >> 4, e = u & 15, m = m0 + (i / WN) * 32 + r_out, n = n0 + (i % WN) * 32 + 8 * (e >> 2) + 4 * h_out + (e & 3);
             if (m >= p.M || n >= p.N) continue;
-            const int32_t sum = s_sum[u * 64 + lane];
+            const int32_t sum = s_sum[u * 64 + lane_out];
             const int64_t o = m + (int64_t)n * p.stride_cn;
             if (p.scale) p.Cf[o] = (float)sum * (WM == 1 || i / WN == 0 ? sc_cols[0] : sc_cols[WM - 1]);
             else p.C[o] = sum;

@@ -44,12 +44,34 @@ def test_tiles_leave_room_for_the_next_workgroups(tmp_path, most, forms):
     assert max(int(n) for n in re.findall(r"\.group_segment_fixed_size:\s+(\d+)", text)) * (512 // most) <= 160 * 1024
 
 
-def test_ragged_table_comes_with_the_scalar_arguments(tmp_path):
+@pytest.fixture(scope="module")
+def ragged_listing(tmp_path_factory):
+    return compile_forms(tmp_path_factory.mktemp("ragged"), [], header="dg_sparse_ragged_kernel.h")        # (its launches instantiate every form)
+
+
+def test_ragged_table_comes_with_the_scalar_arguments(ragged_listing):
     """Read from the arguments lane by lane, the table's rows were two vector loads that every launch waited for."""
-    text = compile_forms(tmp_path, [], header="dg_sparse_ragged_kernel.h")        # (its launches instantiate every form)
+    text = ragged_listing
     kernels = re.findall(r"^(_ZN4dgoh20smfmac_ragged_kernelILi(\d)ELi(\d)ELi(\d)\S+):(.*?)s_barrier", text, re.M | re.S)
     assert len(kernels) == 3 * 4 * 2
     for name, wm, wn, ch, start in kernels:
         # single words before the barrier: a scale per block of channels, and operands of one word (packed activations too)
         words = int(wm) + (2 * int(wm) + int(wn) if ch == "1" else 0)
         assert len(re.findall(r"global_load_dword ", start)) <= words, name
+
+
+def test_ragged_wavefronts_eight_to_a_simd(ragged_listing):
+    """A workgroup of 13 to 16 wavefronts has a second one beside it on a compute unit only if a SIMD holds eight of them: 64 vector registers, and
+    80 scalar ones (of 800, handed out by sixteens; measured: at 82 the second workgroup waits for the first).  No form spills, and none waits for loads
+    between its stores (a wait for one that was never used is a wait for every store before)."""
+    text = ragged_listing
+    kernels = re.findall(r"^(_ZN4dgoh20smfmac_ragged_kernelILi(\d)ELi(\d)ELi(\d)ELb(\d)\S+):(.*?)^\.Lfunc_end", text, re.M | re.S)
+    notes = {name: (int(scalars), int(vectors), int(scratch)) for scratch, scalars, name, vectors in re.findall(
+        r"\.private_segment_fixed_size: (\d+)\s+\.sgpr_count:\s+(\d+).*?\.symbol:\s+(\S+)\.kd.*?\.vgpr_count:\s+(\d+)", text, re.S)}
+    assert len(kernels) == len(notes) == 3 * 4 * 2
+    for name, wm, wn, ch, raw, code in kernels:
+        scalars, vectors, scratch = notes[name]
+        assert scratch == 0, name
+        if wm == wn == "1":
+            assert scalars <= 80 and vectors <= (64 if ch == "1" else 512), (name, scalars, vectors)
+        assert code.count("vmcnt(") <= 16, (name, code.count("vmcnt("))
