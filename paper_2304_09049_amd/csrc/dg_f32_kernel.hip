@@ -187,7 +187,7 @@ onehot_f32_kernel(F32Args a)
 
 // AUTO compares what the two kernels take per position of K.  This one: 2 + 16.7 w ns, w the wavefronts on the busiest SIMD (a
 // workgroup of four blocks per compute unit at a time; w = 1: 17.5 - 21 ns measured, 2: 37, 3: 52, 4: 68), and a start 0.2 us longer than the
-// plain one's; with few positions, or a second word per tap that is mostly empty (Cin = 20 ... 28), 7 + 19.5 w in all.  The plain one: the
+// plain one's; with less than 64 positions, or a second word per tap that is mostly empty (Cin = 20 ... 28), 7 + 19.5 w in all.  The plain one: the
 // outputs at 5.8 thousand per ns -- 5.4 to 7.9 measured, half of that where it reads bytes (Cin % 16 != 0) -- and 21 at least where K is long, below
 // which its own chain of additions does not get (50 to 100 thousand outputs: 21.2 - 22.6; one word per load here, Cin % 32 == 16, is no
 // faster).  Of 215 layers of 40 to 400 thousand outputs the choice costs 1.1 % over the better one on average, 4 % at most against 7 + 19.5 w for all
@@ -208,7 +208,7 @@ bool dg_onehot_f32_preferred(const dg_lut *lut, const DgProblem &p)
     if (const char *f = dg_override("DG_F32_MFMA")) return atoi(f) != 0;
     const int64_t groups = (blocks + 3) / 4, units = dg_simd_count() / 4;
     const double w = (double)((groups + units - 1) / units), few = 5.0 + 2.8 * w, start = 200.0 / p.K;
-    const double here = 2.0 + 16.7 * w + (few < start || (p.Cin < 32 && p.Cin % 16 != 0) ? few : start);
+    const double here = 2.0 + 16.7 * w + (p.K < 64 || (p.Cin < 32 && p.Cin % 16 != 0) ? few : start);
     const double plain = (double)p.M * p.N / (p.Cin % 16 == 0 ? 5800.0 : 2900.0);
     const double chain = blocks >= 256 && p.K > 256 && p.Cin % 32 == 0 ? 21.0 : 0.0;
     return here < (plain > chain ? plain : chain);

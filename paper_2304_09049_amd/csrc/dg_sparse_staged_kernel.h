@@ -202,11 +202,12 @@ __device__ __forceinline__ void dg_for(F &&f)
 // and up to 1024 (768) shared tiles are all resident at once.  At 132 - 136 (180) they ran in two rounds: 56x56x128 -> 160 3x3 at batch 4 (980
 // tiles) 10.6 us against 9.2, 28x28x1024 -> 160 1x1 at batch 16 8.3 against 7.6, two planes 28x28x1024 -> 256 1x1 at batch 6 (592) 10.1 against
 // 8.5.  A spill is no way there: its scratch memory alone costs a launch 0.3 us.
-template <int WM, int WN, int SKW, bool TURNS, bool HALF, bool NIB, bool TWO>
+template <int WM, int WN, int SKW, bool TURNS, bool HALF, bool NIB, bool TWO, bool SHORT = false>
 __global__ void __launch_bounds__(256, WN > 2 ? 2 : (TWO ? (TURNS ? 3 : 2) : 4))
 smfmac_staged_kernel(Args a)
 {
     static_assert(!HALF || SKW == 1, "taps of half runs: unshared tiles only");
+    static_assert(!SHORT || (WM == 1 && WN == 4 && SKW == 1), "a form of its own for short K: the unshared 32 x 128 tile");
     static_assert(!TWO || (WM == 2 && !NIB), "two planes stand in for two weight row blocks");
     constexpr int RB = TWO ? 1 : WM;                       // weight row blocks of the tile
     constexpr int ROWS = (RB + WN) * 32;                    // staged rows of a wavefront: its weight rows, then its pixels
@@ -221,13 +222,11 @@ smfmac_staged_kernel(Args a)
     // Which table: on narrow tiles, whose operands serve few pixels, its random reads keep LDS busier than the vector instructions they
     // spare are worth (28x28x128 -> 128 3x3 at batch 8, 4-bit codes, 32 x 64 by four: 9.9 us with quads, 9.2 with pairs); with 4-bit slots on
     // the 32 x 128 and 64 x 128 tiles too (28x28x256 -> 256 3x3 at batch 8, 32 x 128 by four: 21.5, 19.5; 28x28x512 -> 256 1x1 at batch 32, unshared:
-    // 22.0, 19.3).  Unshared 32 x 128 tiles, whose K is short, pay for filling 16 KB of quads, and beside these a compute unit has room for
-    // two workgroups instead of three (56x56x128 -> 128 3x3 at batch 16 16.6 us with quads, 16.2 with pairs; 128x96000x512 17.5, 16.1;
-    // 8192x4096x384 41.5, 38.3; 2048x4080x640, whose output's rows are no whole cache lines, 15.6, 16.4; pairs with room for two workgroups only,
-    // 1024x12032x384 17.3, three 14.8; half runs, with a longer K, 2 % the other way).  On the others quads are ahead: 8192-cube 740 us with pairs,
+    // 22.0, 19.3).  SHORT: unshared 32 x 128 tiles where K is short (launch_sparse_staged) pay for filling 16 KB of quads, and beside these a
+    // compute unit has room for two workgroups instead of three.  On the others quads are ahead: 8192-cube 740 us with pairs,
     // 706 with quads; 56x56x256 ->
     // 256 3x3 at batch 16, 4-bit, 32 x 224: 98.2, 96.8.
-    constexpr bool QUADS = WN >= 4 && !(WN == 4 && (NIB || (WM == 1 && SKW == 1 && !HALF)));
+    constexpr bool QUADS = WN >= 4 && !(WN == 4 && NIB) && !SHORT;
     constexpr int LOADS = RB + WN;                          // a run's loads
     constexpr int REGION = SKW > 1 && NB * 4096 > BUFS * BUF ? NB * 4096 : BUFS * BUF;      // a wavefront's: its buffers, then its sums
     typedef std::conditional_t<QUADS, QuadTable<NIB, TWO, (TWO && SKW > 1 ? 2 : 4)>, PairTable<NIB, TWO>> Table;
@@ -652,8 +651,15 @@ void launch_sparse_staged(const DgProblem &p, const Pools &pools, int32_t bias, 
         else if (q.wn == 4 && q.skw == 4) DG_STAGED(1, 4, 4, false);
         else if (q.wn == 4 && q.skw == 2 && turns) DG_STAGED(1, 4, 2, true);
         else if (q.wn == 4 && q.skw == 2) DG_STAGED(1, 4, 2, false);
-        else if (q.wn == 4) DG_STAGED(1, 4, 1, false);
-        else if (q.skw == 4 && turns) DG_STAGED(1, 2, 4, true);
+        else if (q.wn == 4) {
+            // K below 2304 and output rows of whole cache lines: the table of pairs (the kernel's SHORT form).  With quads, with pairs: 56x56x128 -> 128
+            // 3x3 at batch 16 16.6 us, 16.2; 128x96000x512 17.5, 16.1; 8192x4096x384 41.5, 38.3; 1920x5856x640 19.7, 18.3; 96x43936x1152 16.0, 15.4.
+            // Other rows: 1919x5832x640 26.4, 27.4, 56x56x128 -> 100 3x3 at batch 20 20.4, 21.6, eight more within 1 %.  K from 2304 up:
+            // 1611x4573x2816 43.3, 45.6; 14x14x512 -> 512 3x3 at batch 50 34.7, 35.3; 1536x4480x4096 44.7, 44.9.
+            if (!NIB && p.K < 2304 && p.stride_cn % 32 == 0)
+                hipLaunchKernelGGL((smfmac_staged_kernel<1, 4, 1, false, false, NIB, false, !NIB>), grid, dim3(256), 0, stream, a);
+            else DG_STAGED(1, 4, 1, false);
+        } else if (q.skw == 4 && turns) DG_STAGED(1, 2, 4, true);
         else if (q.skw == 4) DG_STAGED(1, 2, 4, false);
         else if (q.skw == 2 && turns) DG_STAGED(1, 2, 2, true);
         else if (q.skw == 2) DG_STAGED(1, 2, 2, false);

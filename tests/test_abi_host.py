@@ -193,7 +193,7 @@ def test_empty_launch_rejects_bad_grids_before_launching():
 
 @pytest.mark.parametrize("layer,name", [((4, 7, 7, 16, 576, 1), "lds_f32"), ((2, 14, 14, 16, 320, 1), "lds_f32"), ((5, 28, 28, 20, 16, 1), "lds_f32"),
                                         ((2, 28, 28, 32, 72, 1), "lds_f32"), ((23, 7, 7, 48, 96, 3), "lds_f32"),
-                                        ((1, 14, 14, 256, 320, 1), "lds_f32"),          # a start that few positions do not pay for, half words
+                                        ((1, 14, 14, 256, 320, 1), "lds_f32"), ((2, 14, 14, 56, 192, 1), "lds_f32"),          # a start that few positions do not pay for, half words
                                         ((13, 7, 7, 32, 256, 1), "onehot_mfma_f32"), ((3, 56, 56, 16, 32, 1), "onehot_mfma_f32"),
                                         ((2, 28, 28, 32, 72, 3), "onehot_mfma_f32"), ((2, 14, 14, 256, 256, 3), "onehot_mfma_f32"),
                                         ((2, 28, 28, 100, 48, 3), "onehot_mfma_f32"), ((6, 7, 7, 200, 192, 3), "onehot_mfma_f32")])

@@ -15,11 +15,12 @@ SHAPES = [(1, 9, 6, 128, 40, 15, 1, (14, 0)), (1, 5, 9, 128, 36, 1, 15, (0, 7)),
           (1, 16, 3, 128, 32, 16, 1, (0, 0)), (2, 1, 1, 128, 4, 3, 3, (1, 1)), (1, 1, 1, 256, 1, 1, 1, (0, 0)),
           (1, 3, 40, 128, 20, 1, 16, (0, 15)), (1, 6, 7, 128, 9, 17, 18, (8, 9)), (1, 2, 70, 128, 5, 1, 127, (0, 126)),
           (2, 70, 1, 128, 5, 127, 1, (63, 0)), (1, 66, 1, 128, 4, 128, 1, (64, 0)), (1, 1, 66, 128, 4, 1, 128, (0, 64)),
-          (1, 5, 5, 128, 8, 3, 3, (130, 1)), (1, 5, 5, 128, 8, 3, 3, (1, 140))]
+          (1, 5, 5, 128, 8, 3, 3, (130, 1)), (1, 5, 5, 128, 8, 3, 3, (1, 140)),
+          (2, 9, 8, 256, 36, 3, 3, (1, 1)), (1, 7, 19, 2176, 33, 1, 1, (0, 0))]      # K = 2304 and 2176: either table of the 32 x 128 tile
 
 
 @pytest.mark.parametrize("bias", ["0", "1"])
-@pytest.mark.parametrize("plan", ["12", "12k4", "14k2", "14k4", "17", "24"])
+@pytest.mark.parametrize("plan", ["12", "12k4", "14", "14k2", "14k4", "16", "17", "24"])
 def test_staged_windows_and_shares(plan, bias, monkeypatch):
     monkeypatch.setenv("DG_ONEHOT_PLAN", plan)
     monkeypatch.setenv("DG_STAGED_BIAS", bias)

@@ -10,7 +10,7 @@ from paper_2304_09049_amd.build import HIPCC_FLAGS
 
 
 def compile_forms(tmp_path, forms, *flags, header="dg_sparse_staged_kernel.h", kernel="smfmac_staged_kernel", arguments="Args"):
-    """The listing of a kernel's instantiations (the staged kernel's: <WM, WN, SKW, TURNS, HALF, NIB, TWO>)."""
+    """The listing of a kernel's instantiations (the staged kernel's: <WM, WN, SKW, TURNS, HALF, NIB, TWO, SHORT>)."""
     source, listing = tmp_path / "forms.hip", tmp_path / "forms.s"
     source.write_text(f'#include "{header}"\n' +
                       "".join(f"template __global__ void dgoh::{kernel}<{f}>(dgoh::{arguments});\n" for f in forms))
@@ -33,7 +33,7 @@ def test_no_staged_load_has_a_scalar_offset(tmp_path):
 # (512 registers per SIMD lane, handed out by eights: 128 for four wavefronts, 168 for three)
 @pytest.mark.parametrize("most,forms", [(128, [f"1, 2, {s}, {nib}, false" for s in ("1, false, false", "1, false, true", "2, false, false", "2, true, false",
                                                                                      "4, false, false", "4, true, false") for nib in ("false", "true")]),
-                                        (168, ["2, 2, 4, true, false, false, true", "1, 4, 1, false, false, false, false"])])
+                                        (168, ["2, 2, 4, true, false, false, true", "1, 4, 1, false, false, false, false, true"])])
 def test_tiles_leave_room_for_the_next_workgroups(tmp_path, most, forms):
     """Layers of up to 1024 narrow tiles that four wavefronts share are all resident at once -- if a SIMD holds four of them (two planes without a
     filter window, and unshared 32 x 128 tiles: three) -- and run in two rounds otherwise."""
