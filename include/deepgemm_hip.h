@@ -218,6 +218,8 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *   DG_RAGGED_CODES  "0": it never packs unpacked codes itself, "1": always
  *   DG_NIBBLES       "0": AUTO takes 3- and 4-bit tables whole even where they are the sum of two 2-bit lookups; "1": as
  *                    such sums also while DG_ONEHOT_PLAN is set (which then forces the 2-bit kernel's shape)
+ *   DG_ONEBIT        "0": AUTO never takes tables that are two one-bit lookups to the FP4 instruction; "1", "2", "4": whatever the size, in
+ *                    tiles of 64 x 128, 256 or 512, "12": 64 x 128 with K shared by two
  *   DG_PERM_PLAN     index of the permute kernel's tile shape
  */
 typedef enum {
@@ -348,7 +350,9 @@ dg_status dg_conv2d_lut_requant(const dg_lut *lut, const void *Wp_dev, const voi
 dg_status dg_launch_empty(int64_t blocks, int32_t threads, void *hip_stream);
 
 /* Name of the kernel that AUTO would pick (or that `variant` maps to) for this GEMM / convolution
- * shape; static storage.  For reports only. */
+ * shape; static storage.  For reports only: it names AUTO's plan for the shape.  A "onehot_smfmac_<tile>" or "onehot_mfma_<tile>"
+ * plan of AUTO's runs tables that are two one-bit lookups (2-bit activation levels 0, d, 2d, 3d) on the FP4 matrix instruction, in
+ * tiles of its own, where there are many; the results are the same. */
 const char *dg_gemm_kernel_name(const dg_lut *lut, int64_t M, int64_t N, int64_t K,
                                 dg_kernel variant);
 const char *dg_conv_kernel_name(const dg_lut *lut, const dg_conv_desc *desc, dg_kernel variant);

@@ -352,7 +352,11 @@ Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
 
 dg_status run(const dg_lut *lut, const DgProblem &p, dg_kernel variant, hipStream_t stream)
 {
-    switch (pick_kernel(lut, p, variant)) {
+    const Pick pick = pick_kernel(lut, p, variant);
+    // (AUTO's plans on the one-hot kernels: tables of a narrower form run on a kernel of their own, whatever the plan's name says)
+    if (variant == DG_KERNEL_AUTO && (pick == Pick::Sparse || pick == Pick::OneHot) && dg_onebit_preferred(lut, p, dg_sparse_is_staged(lut, p)))
+        return dg_launch_onebit(lut, p, stream);
+    switch (pick) {
     case Pick::Perm: return dg_launch_perm(lut, p, stream);
     case Pick::Lds: return dg_launch_lds(lut, p, stream);
     case Pick::LdsF32: return dg_launch_lds_f32(lut, p, stream);
@@ -759,6 +763,7 @@ dg_status dg_conv2d_lut_requant(const dg_lut *lut, const void *Wp_dev, const voi
     if (variant == DG_KERNEL_AUTO && dg_staged2p_preferred(lut, p)) return dg_launch_staged2p(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_AUTO && dg_sparse2p_preferred(lut, p)) return dg_launch_sparse2p(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_AUTO && dg_sparse4_preferred(lut, p)) return dg_launch_sparse4(lut, p, (hipStream_t)hip_stream);
+    if (variant == DG_KERNEL_AUTO && dg_onebit_preferred(lut, p, dg_sparse_is_staged(lut, p))) return dg_launch_onebit(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_AUTO && dg_sparse_preferred(lut, p)) return dg_launch_sparse(lut, p, (hipStream_t)hip_stream);
     return dg_launch_onehot(lut, p, (hipStream_t)hip_stream);
 }

@@ -145,7 +145,10 @@ bool dg_onehot_codes_tiled_pays(const dg_lut *lut, const DgProblem &p, bool spar
 bool dg_sparse_supports(const dg_lut *lut, const DgProblem &p);
 bool dg_sparse_preferred(const dg_lut *lut, const DgProblem &p);     // AUTO's choice between the two one-hot kernels
 dg_status dg_launch_sparse(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+bool dg_sparse_is_staged(const dg_lut *lut, const DgProblem &p);     // AUTO would run it on the staged kernel
 const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p);
+bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p, bool staged);        // tables that are two one-bit lookups, on the FP4 instruction
+dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes);      // taps of no whole 32-position groups; `codes`: p.Xp one per byte
 const char *dg_ragged_config_name(const dg_lut *lut, const DgProblem &p, bool codes);
 dg_status dg_launch_ragged(const dg_lut *lut, const DgProblem &p, bool codes, hipStream_t stream);

@@ -79,12 +79,19 @@ __device__ __forceinline__ bool dg_mfma_rows_whole(int64_t row_stride, int64_t c
     return rowb + 32 <= row_limit && span < ((int64_t)1 << 30);
 }
 
+template <bool STREAM, class T>
+__device__ __forceinline__ void dg_put(T v, T *to)
+{
+    if constexpr (STREAM) __builtin_nontemporal_store(v, to);
+    else *to = v;
+}
+
 // EDGE_COLUMNS: blocks whose columns are not all inside take the stores without a test per element too, the lanes of columns
 // beyond the last sitting them out.  For kernels whose wavefronts have one column block each, all of which would be stored
 // element by element where it is partial: dg_sparse_ws_kernel.h, and dg_sparse_staged_kernel.h, where (packed codes, graph
 // replays) 28x28x256 -> 200 at batch 32 went from 17.4 to 14.5 us with 3-bit codes, 56x56x256 -> 72 from 28.6 to 23.3, 56x56x128 ->
 // 72 3x3 at batch 16 from 21.7 to 17.9 with 2-bit ones, and layers of whole blocks stayed (56x56x128 -> 128 3x3 17.0, 17.2).
-template <bool TR, bool EDGE_COLUMNS = false>
+template <bool TR, bool EDGE_COLUMNS = false, bool STREAM = true>
 __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg_v16i &acc, int mb, int nb, int lane,
                                                     float sc)
 {
@@ -110,14 +117,14 @@ __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int k = 8 * (e / 4) + (e % 4);
-                __builtin_nontemporal_store((float)acc[e] * (TR ? sc : scale_rows[k]), out + (off0 + k * rs));
+                dg_put<STREAM>((float)acc[e] * (TR ? sc : scale_rows[k]), out + (off0 + k * rs));
             }
         } else {
             int32_t *out = p.C + base;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int k = 8 * (e / 4) + (e % 4);
-                __builtin_nontemporal_store(acc[e], out + (off0 + k * rs));
+                dg_put<STREAM>(acc[e], out + (off0 + k * rs));
             }
         }
         return;
@@ -133,15 +140,15 @@ __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg
         if (row0 + k >= row_limit) continue;
         const int64_t o = first + k * row_stride;
         if (p.scale)
-            __builtin_nontemporal_store((float)acc[e] * (TR ? sc : p.scale[row0 + k]), p.Cf + o);
+            dg_put<STREAM>((float)acc[e] * (TR ? sc : p.scale[row0 + k]), p.Cf + o);
         else
-            __builtin_nontemporal_store(acc[e], p.C + o);
+            dg_put<STREAM>(acc[e], p.C + o);
     }
 }
 
 // Store NQ groups of four registers of a block, the first one group q0 (TR layout; a partial last block of channels as with EDGE_COLUMNS
 // above).
-template <int NQ>
+template <int NQ, bool STREAM = true>
 __device__ __forceinline__ void dg_mfma_store_quads(const DgProblem &p, const dg_v4i (&acc)[NQ], int q0, int mb, int nb, int lane, float sc)
 {
     if (p.Qp) {
@@ -158,11 +165,11 @@ __device__ __forceinline__ void dg_mfma_store_quads(const DgProblem &p, const dg
         if (p.scale) {
             float *out = p.Cf + base;
 #pragma unroll
-            for (int e = 0; e < 4 * NQ; ++e) __builtin_nontemporal_store((float)acc[e / 4][e % 4] * sc, out + (off0 + (8 * (e / 4) + e % 4) * rs));
+            for (int e = 0; e < 4 * NQ; ++e) dg_put<STREAM>((float)acc[e / 4][e % 4] * sc, out + (off0 + (8 * (e / 4) + e % 4) * rs));
         } else {
             int32_t *out = p.C + base;
 #pragma unroll
-            for (int e = 0; e < 4 * NQ; ++e) __builtin_nontemporal_store(acc[e / 4][e % 4], out + (off0 + (8 * (e / 4) + e % 4) * rs));
+            for (int e = 0; e < 4 * NQ; ++e) dg_put<STREAM>(acc[e / 4][e % 4], out + (off0 + (8 * (e / 4) + e % 4) * rs));
         }
         return;
     }
@@ -172,8 +179,8 @@ __device__ __forceinline__ void dg_mfma_store_quads(const DgProblem &p, const dg
         const int k = 8 * (e / 4) + e % 4;
         if (row0 + 4 * h + k >= p.N) continue;
         const int64_t o = first + k * p.stride_cn;
-        if (p.scale) __builtin_nontemporal_store((float)acc[e / 4][e % 4] * sc, p.Cf + o);
-        else __builtin_nontemporal_store(acc[e / 4][e % 4], p.C + o);
+        if (p.scale) dg_put<STREAM>((float)acc[e / 4][e % 4] * sc, p.Cf + o);
+        else dg_put<STREAM>(acc[e / 4][e % 4], p.C + o);
     }
 }
 

@@ -1,0 +1,372 @@
+// 2-bit tables that are two ONE-BIT lookups, on the FP4 matrix instruction.  Where
+//
+//   T[w][0] = 0,  T[w][2] = 2 T[w][1],  T[w][3] = T[w][1] + T[w][2]       (evenly spaced activation levels from zero, any weight levels)
+//
+// a position adds the entry T[w][1] if bit 0 of its activation code is set, and the entry T[w][2] if bit 1 is.  As a contraction that is
+// two places of the reduction per position, the entries on one side and single bits on the other, where the one-hot form of any table
+// needs four (dg_onehot_kernel.h); and v_mfma_f32_32x32x64_f8f6f4 takes 64 places of 4-bit numbers in the 32 cycles in which the sparse int8
+// instruction takes 16 positions of four.  So the matrix work is half of that kernel's, and no row of a table is read per position.
+//
+// Numbers: FP4 (E2M1) is 0, 0.5, 1, 1.5, 2, 3, 4, 6 and their negatives.  A code's bits are masked out where they lie in the packed word:
+// the low bit at the bottom of a 4-bit place is 0.5, the high bit next to it is 1, of even codes as loaded, of odd ones after a shift by
+// two -- five vector instructions for the operands of two instructions.  Weight code w is the number N[w] = T[w][1] / (2 f), the same for
+// both bits, f the entries' common factor.  All products and sums are multiples of 1/4 below 2^22, hence exact in binary32 in any order
+// (the host checks; find_numbers), and 4 f times the sum is the integer result.
+//
+// A workgroup's four wavefronts share 64 channels, each with 32 WN pixels of its own.  A run is 256 positions of K, 64 bytes of a row: four
+// neighbouring lanes fetch a row's, the pixels' straight to LDS (dg_lds_dma.h), one run ahead.  A 16-byte segment lies in one filter tap
+// (Cin % 64 == 0); each lane works out its own segment's, and fetches zeros where the tap lies outside the image: nothing is masked later.
+// The weights' 4-bit numbers are made once for the four wavefronts, 13 vector instructions per word of 16 codes, 16 bytes a thread, and
+// handed over in LDS: one barrier per run.
+//
+// Bound by the matrix pipe at the clock it runs at on large layers (8192-cube: 22 ns per instruction and SIMD, where registers alone with
+// random operands take 18.4 at 1.77 GHz, constant ones 13.5 at 2.4), by the start, the end and lone wavefronts' issue slots on those of a few
+// microseconds: a run of the 64 x 128 tile takes 0.5 us then.  The staged sparse kernel, this one (packed codes, graph replays, us):
+//   8192-cube 648, 356          56x56x256 -> 256 3x3 at batch 16 47.1, 30.6          28x28x512 -> 512 3x3 at batch 16 46.1, 29.9
+//   28x28x128 -> 128 3x3 at batch 32 12.2, 8.6          28x28x256 -> 256 3x3 at batch 8 10.9, 8.4          3569 x 7478 x 704 81.5, 28.3
+// (the last by its stores too: see STREAM).
+#include "dg_lds_dma.h"
+#include "dg_onehot_kernel.h"
+
+#include <cstdlib>
+#include <numeric>
+
+namespace {
+
+using namespace dgoh;
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
+struct OneBitArgs {
+    DgProblem p;
+    uint32_t numbers;        // byte w: N[w] as FP4
+    int32_t factor;          // f
+    FastDiv div_ow, div_oh, div_kw, div_cpt, div_band, div_last;    // (div_cpt: by the 64-position segments of a filter tap)
+    int32_t tiles_m, tiles_n, band_log2;
+    uint32_t band_tiles, x_bytes;
+};
+
+__device__ __forceinline__ f32x16 fp4_step(const v4i &a, const v4i &b, f32x16 c)
+{
+    const i32x8 x = {a[0], a[1], a[2], a[3], 0, 0, 0, 0}, y = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, c, 4, 4, 0, 0, 0, 0);
+}
+
+// KS = 2: eight wavefronts, two to a tile, each with half of K; their sums meet in LDS.  TAPS: a filter window.  TR: channels on the
+// matrix instruction's columns (dg_mfma_tile.h).  STREAM: the output bypasses the caches, which is best where its rows are whole 64-byte
+// pieces; where they are not, a line's parts come from different wavefronts and tiles and are brought together in L2 instead of being
+// written one by one (same tile, us, streaming and not: 3569 x 7478 x 704 55.1, 28.3; 112x112x128 -> 120 3x3 at batch 25 77.5, 54.7; whole
+// pieces: 112x112x64 -> 96 3x3 at batch 12 20.4, 22.5).
+template <int WN, int KS, bool TAPS, bool TR, bool STREAM>
+__global__ void __launch_bounds__(256 * KS, 2)
+onebit_kernel(OneBitArgs a)
+{
+    constexpr int WEIGHTS = 8192;                           // bytes of a run's weight operands: 64 rows, 256 positions
+    constexpr int PIXELS = WN * 2048;                       // bytes of a wavefront's pixels of a run
+    constexpr int LOADS = 2 * WN;                           // loads of 16 rows each
+    constexpr int BESIDE = WN > 1 ? 6 : 0;                  // other instructions between two matrix instructions (8192-cube 372 -> 356 us; 0: the compiler's order)
+    constexpr int SHARE = 2 * WEIGHTS + 8 * PIXELS;         // bytes of the four wavefronts that walk one share of K
+    __shared__ uint4 s_mem[KS * SHARE / 16];
+    const DgProblem &p = a.p;
+    dg_fetch_arguments<sizeof(a)>();
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 31, h = lane >> 5;
+    const int w4 = wave & 3, ks = KS == 1 ? 0 : wave >> 2;
+    int m_tile, n_tile;                                     // numbered in bands of 2^band_log2 pixel tiles, as in dg_sparse_staged_kernel.h
+    {
+        const uint32_t t = xcd_contiguous(blockIdx.x, gridDim.x), band = fdiv(t, a.div_band), t_in = t - band * a.band_tiles;
+        const int first = (int)band << a.band_log2, width = min(1 << a.band_log2, a.tiles_n - first);
+        m_tile = (int)(width == 1 << a.band_log2 ? t_in >> a.band_log2 : fdiv(t_in, a.div_last));
+        n_tile = first + (int)t_in - m_tile * width;
+    }
+    const int m0 = m_tile * 64, n0 = (n_tile * 4 + w4) * (WN * 32);
+    const int cq = p.Cin / 4, all_runs = (p.K + 255) / 256;
+    // this share's runs g0 ... g1 - 1 of K and its chunks (64 positions); the shares walk equally many runs, past their ends as zeros
+    const int g0 = KS == 1 ? 0 : all_runs * ks / KS, g1 = KS == 1 ? all_runs : all_runs * (ks + 1) / KS;
+    const int runs = (all_runs + KS - 1) / KS, chunks = min(p.K / 64, 4 * g1);
+    char *const mem = (char *)s_mem + ks * SHARE;
+
+    // ---- weights: thread t of a share loads segment t % 4 of a run of row t / 4 (rows beyond M, bytes past the last row: zeros; past the end of
+    // K: the next row's, which meet pixels of zero)
+    const uint32_t row_bytes = (uint32_t)p.K / 4;
+    const __amdgpu_buffer_rsrc_t w_buffer =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(p.Wp + (int64_t)m0 * row_bytes), 0, (int)(min(p.M - m0, 64) * row_bytes), 0x00020000);
+    const int w_row = (threadIdx.x >> 2) & 63, w_seg = threadIdx.x & 3;
+    const uint32_t w_ld = w_row * row_bytes + w_seg * 16;
+    auto load_weights = [&](int g) { return (v4i)__builtin_amdgcn_raw_buffer_load_b128(w_buffer, w_ld + g * 64, 0, 0); };
+    const uint32_t low = a.numbers, high = a.numbers << 4;
+    // segment s of rows 32 b ... as [s][b][lane], lane (r, half) with its two words' numbers of even and odd codes; lanes exchanged so that a
+    // thread's neighbours, which write the other segments, are on other banks
+    char *const w_to = mem + ((2 * w_seg + (w_row >> 5)) * 64 + ((w_row & 31) ^ (2 * w_seg))) * 16;
+    auto expand = [&](uint32_t word, int &even, int &odd) {
+        even = (int)(__builtin_amdgcn_perm(0u, low, word & 0x03030303u) | __builtin_amdgcn_perm(0u, high, (word >> 4) & 0x03030303u));
+        odd = (int)(__builtin_amdgcn_perm(0u, low, (word >> 2) & 0x03030303u) | __builtin_amdgcn_perm(0u, high, (word >> 6) & 0x03030303u));
+    };
+    auto expand_half = [&](const v4i &raw, int half, uint32_t buf) {
+        v4i o;
+        int e0, o0, e1, o1;
+        expand((uint32_t)raw[2 * half], e0, o0);
+        expand((uint32_t)raw[2 * half + 1], e1, o1);
+        o[0] = e0, o[1] = o0, o[2] = e1, o[3] = o1;
+        *(v4i *)(w_to + buf + half * 512) = o;
+    };
+
+    // ---- pixels: lane l of a load fetches segment (l % 4) ^ (row / 4 % 4) of row l / 4 of 16: a segment's 16 rows lie on 16 places of the banks
+    const v4i x_buffer = dg_buffer(p.Xp, a.x_bytes);
+    const int l_row = lane >> 2, l_seg = (lane & 3) ^ (lane >> 4);
+    uint32_t off0[LOADS], outside[TAPS ? LOADS : 1];       // outside: bit t, filter tap t lies outside the image
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const Column c = make_column(p, a.div_ow, a.div_oh, n0 + 16 * i + l_row, cq, 0);
+        off0[i] = (uint32_t)c.off0;
+        asm("" : "+v"(off0[i]));                            // (kept, not worked out again for each load)
+        const int h0 = max(0, -c.ih0), h1 = c.ok ? min(p.KH, p.H - c.ih0) : 0, c0 = max(0, -c.iw0), c1 = min(p.KW, p.W - c.iw0);
+        const uint32_t columns = c1 > c0 ? (~0u >> (32 - (c1 - c0))) << c0 : 0u;
+        if constexpr (TAPS) {
+            uint32_t in = 0;
+            for (int kh = 0; kh < p.KH; ++kh) in |= kh >= h0 && kh < h1 ? columns << (kh * p.KW) : 0u;
+            outside[i] = ~in;
+        } else {
+            off0[i] |= h1 > h0 && c1 > c0 ? 0u : 0x80000000u;
+        }
+    }
+    const uint32_t x_lds = dg_lds_address(mem) + 2 * WEIGHTS + w4 * 2 * PIXELS;
+    auto fetch = [&](int g, int odd) {
+        const uint32_t dst = x_lds + odd * PIXELS;
+        const int c = 4 * g + l_seg;
+        const uint32_t dead = c < chunks ? 0u : 0x80000000u;
+        if constexpr (TAPS) {
+            const int tap = (int)fdiv((uint32_t)c, a.div_cpt), kh = (int)fdiv((uint32_t)tap, a.div_kw), kw = tap - kh * p.KW;
+            const uint32_t tap_off = (uint32_t)((kh * p.W + kw) * cq + (c - tap * (cq >> 4)) * 16);
+            dg_for<LOADS>([&](auto i) {
+                const uint32_t out = (outside[i] << ((31 - tap) & 31)) | dead;
+                dg_load16_to_lds<i * 1024>(x_buffer, (off0[i] + tap_off) | (out & 0x80000000u), dst);
+            });
+        } else {
+            dg_for<LOADS>([&](auto i) { dg_load16_to_lds<i * 1024>(x_buffer, (off0[i] + c * 16) | dead, dst); });
+        }
+    };
+
+    v4i raw = load_weights(g0);
+    fetch(g0, 0);
+    expand_half(raw, 0, 0), expand_half(raw, 1, 0);
+    raw = load_weights(g0 + 1);
+    float sc_cols[2];
+    dg_mfma_column_scales<2, TR>(p, m0, lane, sc_cols);
+
+    f32x16 acc[2][WN];
+#pragma unroll
+    for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+        for (int bn = 0; bn < WN; ++bn)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[bm][bn][e] = 0.0f;
+
+    struct Words {
+        v4i w[2];
+        uint2 x[WN];
+    };
+    const char *const x_from = mem + 2 * WEIGHTS + w4 * 2 * PIXELS + (r >> 4) * 1024 + (r & 15) * 64 + 8 * h;
+    const int x_swap = (r >> 2) & 3;
+    auto read = [&](Words &t, int odd, int s) {
+        const char *w = mem + odd * WEIGHTS + (lane ^ (2 * s)) * 16, *x = x_from + odd * PIXELS + (s ^ x_swap) * 16;
+#pragma unroll
+        for (int bm = 0; bm < 2; ++bm) t.w[bm] = *(const v4i *)(w + (2 * s + bm) * 1024);
+#pragma unroll
+        for (int bn = 0; bn < WN; ++bn) t.x[bn] = *(const uint2 *)(x + bn * 2048);
+    };
+    auto multiply = [&](const Words &t) {
+#pragma unroll
+        for (int bn = 0; bn < WN; ++bn) {
+            const uint32_t x0 = t.x[bn].x, x1 = t.x[bn].y, y0 = x0 >> 2, y1 = x1 >> 2;
+#pragma unroll
+            for (int bit = 0; bit < 2; ++bit) {
+                const uint32_t M = bit ? 0x22222222u : 0x11111111u;
+                const v4i x = {(int)(x0 & M), (int)(y0 & M), (int)(x1 & M), (int)(y1 & M)};
+#pragma unroll
+                for (int bm = 0; bm < 2; ++bm) {
+                    acc[bm][bn] = TR ? fp4_step(x, t.w[bm], acc[bm][bn]) : fp4_step(t.w[bm], x, acc[bm][bn]);
+                    if constexpr (BESIDE > 0) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x302, BESIDE, 0);
+                    }
+                }
+            }
+        }
+    };
+
+    for (int i = 0; i < runs; ++i) {
+        const int odd = i & 1, g = g0 + i;
+        dg_wait_for_loads<0>();                             // (this run's pixels, the next one's weights)
+        asm volatile("" : "+v"(raw));
+        const v4i next = raw;
+        __syncthreads();
+        fetch(g + 1, odd ^ 1);
+        raw = load_weights(g + 2);
+        const uint32_t to = (odd ^ 1) * WEIGHTS;
+        Words t[2];
+        read(t[0], odd, 0);
+        read(t[1], odd, 1);
+        multiply(t[0]);
+        read(t[0], odd, 2);
+        expand_half(next, 0, to);
+        multiply(t[1]);
+        read(t[1], odd, 3);
+        expand_half(next, 1, to);
+        multiply(t[0]);
+        multiply(t[1]);
+    }
+    auto result = [&](float sum) { return (int)(sum * 4.0f) * a.factor; };
+    dg_wait_for_loads();                                    // (fetches past the end: their LDS writes end before the wavefront does)
+
+    if constexpr (KS > 1) {
+        static_assert(KS == 2 && WN == 1, "a wavefront's sums take the place of its share of LDS");
+        // [share][wavefront][block][group of four sums][lane]; then each wavefront of a pair adds up and stores one of their two blocks
+        __syncthreads();
+        float4 *const mine = (float4 *)s_mem + wave * 512 + lane;
+#pragma unroll
+        for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                mine[(4 * bm + q) * 64] = make_float4(acc[bm][0][4 * q], acc[bm][0][4 * q + 1], acc[bm][0][4 * q + 2], acc[bm][0][4 * q + 3]);
+        __syncthreads();
+        const float4 *const theirs = (const float4 *)s_mem + w4 * 512 + ks * 256 + lane;
+        v16i out;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 x = theirs[q * 64], y = theirs[2048 + q * 64];
+            out[4 * q] = result(x.x + y.x), out[4 * q + 1] = result(x.y + y.y);
+            out[4 * q + 2] = result(x.z + y.z), out[4 * q + 3] = result(x.w + y.w);
+        }
+        dg_mfma_store_block<TR, true, STREAM>(p, out, m0 + ks * 32, n0, lane, ks ? sc_cols[1] : sc_cols[0]);
+        return;
+    }
+#pragma unroll
+    for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+        for (int bn = 0; bn < WN; ++bn) {
+            v16i out;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) out[e] = result(acc[bm][bn][e]);
+            dg_mfma_store_block<TR, true, STREAM>(p, out, m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
+        }
+}
+
+// N[w] and f of a table of the form above, if its N are FP4 numbers; *largest: the largest |T[w][1]| / f.
+bool find_numbers(const dg_lut *lut, uint32_t *numbers, int32_t *factor, int32_t *largest)
+{
+    if (lut->bits != 2 || lut->dtype == DG_LUT_F32) return false;
+    int f = 0;
+    for (int w = 0; w < 4; ++w) {
+        const int16_t *row = lut->entry + 4 * w;
+        if (row[0] != 0 || row[2] != 2 * row[1] || row[3] != row[1] + row[2]) return false;
+        f = std::gcd(f, (int)row[1]);
+    }
+    if (f == 0) f = 1;
+    *numbers = 0, *factor = f, *largest = 0;
+    for (int w = 0; w < 4; ++w) {
+        static const int doubled[8] = {0, 1, 2, 3, 4, 6, 8, 12};
+        const int t = lut->entry[4 * w + 1] / f, magnitude = abs(t);
+        int code = 0;
+        while (code < 8 && doubled[code] != magnitude) ++code;
+        if (code == 8) return false;
+        *numbers |= (uint32_t)(code | (t < 0 ? 8 : 0)) << (8 * w);
+        if (magnitude > *largest) *largest = magnitude;
+    }
+    return true;
+}
+
+bool takes(const dg_lut *lut, const DgProblem &p)
+{
+    uint32_t numbers;
+    int32_t factor, largest;
+    if (!find_numbers(lut, &numbers, &factor, &largest)) return false;
+    if ((int64_t)p.K * 3 * largest >= 1 << 24) return false;           // (multiples of 1/4 below 2^22)
+    if (p.Cin % 64 != 0 || p.KH * p.KW > 32 || (uintptr_t)p.Wp % 16 != 0 || (uintptr_t)p.Xp % 16 != 0) return false;
+    if ((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4) >= (int64_t)1 << 31) return false;      // (32-bit byte offsets)
+    return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 127) / 128) <= INT32_MAX;
+}
+
+struct OneBitPlan {
+    int wn, ks;
+};
+
+int64_t tiles_of(const DgProblem &p, int wn) { return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 128 * wn - 1) / (128 * wn)); }
+
+// DG_ONEBIT: 0 never, 1, 2, 4 this kernel with WN so large, 12 with WN = 1 and KS = 2, whatever the size.
+OneBitPlan onebit_plan(const DgProblem &p)
+{
+    if (const char *f = dg_override("DG_ONEBIT")) return OneBitPlan{atoi(f) == 12 ? 1 : atoi(f), atoi(f) == 12 ? 2 : 1};
+    // A tile twice (four times) as wide costs 1.82 (3.55) times as much per run on a busy compute unit, so the plan is the one that
+    // leaves the busiest the least: 112x112x128 -> 128 3x3 at batch 10 (1960, 980, 490 tiles) 24.2, 22.7, 25.0 us; 56x56x128 -> 112 3x3 at batch 26
+    // (1274, 638) 16.7, 18.1; 56x56x256 -> 112 3x3 at batch 28 (1372, 686) 28.3, 25.2.  Few runs do not pay for a wide tile's longer end:
+    // 6648 x 2359 x 832 22.1, 25.2; the widest wants nine: 1986 x 7254 x 6272 83.7, 78.3, 74.9, 8192-cube 402, 367, 356, 112x112x128 -> 120 3x3 at
+    // batch 25 60.2, 54.7, 59.4.
+    const int64_t units = dg_simd_count() / 4, runs = ((int64_t)p.K + 255) / 256, t1 = tiles_of(p, 1);
+    auto rounds = [&](int wn) { return (double)((tiles_of(p, wn) + units - 1) / units); };
+    if (t1 <= units) return OneBitPlan{1, runs >= 8 ? 2 : 1};
+    OneBitPlan q = {1, 1};
+    double best = rounds(1);
+    if (t1 > 2 * units && (runs >= 5 || t1 >= 13 * units)) {
+        if (1.82 * rounds(2) < best) q.wn = 2, best = 1.82 * rounds(2);
+        if (runs >= 9 && 3.55 * rounds(4) < best) q.wn = 4;
+    }
+    return q;
+}
+
+}   // namespace
+
+// AUTO takes such tables here where the tiles are many enough, instead of to the one-hot kernels (`staged`: the staged one).  Of 210 layers and
+// GEMMs of 1.5 to 200 GOP those with 130 tiles of 64 x 128 and more were all shorter here, by 38 % on average; with fewer, long K is walked by too
+// few wavefronts: 28x28x256 -> 64 3x3 at batch 8 (98 tiles, 9 runs) 8.3 against 7.9, 14x14x256 -> 744 3x3 at batch 7 (132) 11.4 against 9.2,
+// 7x7x1152 -> 1680 3x3 at batch 10 (108 tiles, 41 runs) 18.5 against 20.8; the direct-load kernels from 35: 738 x 360 x 5568 (36) 15.3 against 12.2.
+bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p, bool staged)
+{
+    if (!takes(lut, p)) return false;
+    if (const char *f = dg_override("DG_ONEBIT")) return atoi(f) != 0;
+    if (dg_override("DG_ONEHOT_PLAN") != nullptr || dg_override("DG_ONEHOT_WAVES") != nullptr) return false;
+    const int64_t t1 = tiles_of(p, 1), runs = ((int64_t)p.K + 255) / 256;
+    return t1 >= (staged ? (runs <= 7 ? 80 : 130) : 35);
+}
+
+dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
+{
+    OneBitArgs a;
+    int32_t largest;
+    a.p = p;
+    find_numbers(lut, &a.numbers, &a.factor, &largest);
+    const OneBitPlan q = onebit_plan(p);
+    a.div_ow = make_div((uint32_t)p.OW), a.div_oh = make_div((uint32_t)p.OH), a.div_kw = make_div((uint32_t)p.KW);
+    a.div_cpt = make_div((uint32_t)(p.Cin / 64));
+    a.tiles_m = (p.M + 63) / 64, a.tiles_n = (p.N + 128 * q.wn - 1) / (128 * q.wn);
+    a.band_log2 = 2;
+    a.band_tiles = (uint32_t)a.tiles_m << a.band_log2;
+    a.div_band = make_div(a.band_tiles);
+    const int last = a.tiles_n & ((1 << a.band_log2) - 1);
+    a.div_last = make_div((uint32_t)(last ? last : 1));
+    a.x_bytes = (uint32_t)((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4));
+    const dim3 grid((unsigned)((int64_t)a.tiles_m * a.tiles_n));
+    const bool taps = p.KH * p.KW > 1;
+    const bool rows_m = p.stride_cn == 1 && p.stride_cm != 1 && !taps && !p.Qp;      // (the output's rows are channels: a GEMM with n contiguous)
+    const int64_t row = rows_m ? p.stride_cm : p.stride_cn;
+    const uintptr_t out = p.scale ? (uintptr_t)p.Cf : (uintptr_t)p.C;
+    const bool stream_out = row % 16 == 0 && out % 64 == 0;
+#define DG_ONEBIT_FORM(WN, KS, TAPS, TR) \
+    do { \
+        if (stream_out) hipLaunchKernelGGL((onebit_kernel<WN, KS, TAPS, TR, true>), grid, dim3(256 * KS), 0, stream, a); \
+        else hipLaunchKernelGGL((onebit_kernel<WN, KS, TAPS, TR, false>), grid, dim3(256 * KS), 0, stream, a); \
+    } while (0)
+#define DG_ONEBIT(WN, KS) \
+    do { \
+        if (rows_m) DG_ONEBIT_FORM(WN, KS, false, false); \
+        else if (taps) DG_ONEBIT_FORM(WN, KS, true, true); \
+        else DG_ONEBIT_FORM(WN, KS, false, true); \
+    } while (0)
+    if (q.wn == 4) DG_ONEBIT(4, 1);
+    else if (q.wn == 2) DG_ONEBIT(2, 1);
+    else if (q.ks == 2) DG_ONEBIT(1, 2);
+    else DG_ONEBIT(1, 1);
+#undef DG_ONEBIT
+#undef DG_ONEBIT_FORM
+    return dg_check_launch("onebit_kernel");
+}

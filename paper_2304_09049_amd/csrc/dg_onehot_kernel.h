@@ -359,6 +359,16 @@ __device__ __forceinline__ void sparse_dense_rows_shared(const uint2 *table, uin
     sparse_read_rows<NIB>(table, e, o, even, odd);
 }
 
+// f(0), f(1), ... f(N - 1), each argument a constant
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void dg_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        dg_for<N, I + 1>(f);
+    }
+}
+
 // Position bookkeeping shared by the two kernels: output column n -> image coordinates, and the filter tap of a chunk.
 // Workgroups are dealt to the 8 XCDs, each with an L2 of its own, round-robin.  Renumbered this way each XCD works on a
 // contiguous run of tiles, so that neighbouring pixels' filter windows and a tile row's weights meet in one L2

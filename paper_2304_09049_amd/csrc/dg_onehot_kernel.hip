@@ -349,6 +349,11 @@ bool dg_sparse_preferred(const dg_lut *lut, const DgProblem &p)
            tile_count(t, 2, 1) > dg_simd_count();
 }
 
+bool dg_sparse_is_staged(const dg_lut *lut, const DgProblem &p)
+{
+    return dg_sparse_supports(lut, p) && sparse_plan(lut, sparse_problem(p)).staged;
+}
+
 bool dg_sparse_supports(const dg_lut *lut, const DgProblem &p)
 {
     if (lut->dtype == DG_LUT_F32 || lut->bits != 2 || !fits_int8(lut)) return false;

@@ -188,16 +188,6 @@ struct QuadTable {
 // TWO: entries beyond int8, T = 256 * hi + lo (dg_onehot_kernel.h).  The planes take the places of two weight row blocks: a
 // tile is ONE block of 32 rows, whose words are staged once and whose table indices are worked out once for both planes'
 // dense operands; pool words 4 ... 7 are the high plane's rows.
-// f(0), f(1), ... f(N - 1), each argument a constant
-template <int N, int I = 0, class F>
-__device__ __forceinline__ void dg_for(F &&f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>());
-        dg_for<N, I + 1>(f);
-    }
-}
-
 // Registers: the narrow tiles are held to 128 (with two planes and wavefronts taking turns to 168), so that four (three) wavefronts share a SIMD
 // and up to 1024 (768) shared tiles are all resident at once.  At 132 - 136 (180) they ran in two rounds: 56x56x128 -> 160 3x3 at batch 4 (980
 // tiles) 10.6 us against 9.2, 28x28x1024 -> 160 1x1 at batch 16 8.3 against 7.6, two planes 28x28x1024 -> 256 1x1 at batch 6 (592) 10.1 against

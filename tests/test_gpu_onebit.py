@@ -1,0 +1,73 @@
+"""Tables that are two one-bit lookups of the activation code, on the FP4 matrix instruction: every tile, with and without a filter
+window, K of whole and of broken runs, every way to the output, against the oracle; and sums at the end of the range that is taken."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2304_09049_amd import binding as dg
+from paper_2304_09049_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+TABLES = [((-2, -1, 0, 1), (0, 1, 2, 3)), ((12, -8, 3, -6), (0, 1, 2, 3)), ((-10, 5, 0, 15), (0, -2, -4, -6)), ((0, 0, 0, 0), (0, 1, 2, 3))]
+CONVS = [  # B, H, W, Cin, Cout, KH, KW, stride, pad: 1 to 25 taps, tiles and runs whole and not, taps outside on every side, padding without a window
+    (1, 9, 11, 64, 36, 3, 3, (1, 1), (1, 1)), (2, 20, 13, 64, 132, 5, 5, (1, 1), (2, 2)), (1, 17, 19, 192, 64, 3, 2, (2, 1), (2, 0)),
+    (3, 14, 14, 256, 200, 1, 1, (1, 1), (0, 0)), (2, 15, 14, 320, 68, 1, 1, (2, 2), (1, 1)), (1, 8, 40, 128, 100, 1, 4, (1, 3), (0, 3)),
+    (1, 28, 28, 576, 4, 3, 3, (1, 1), (1, 1)), (2, 3, 3, 64, 64, 3, 3, (1, 1), (2, 2))]
+GEMMS = [(70, 300, 64), (64, 1025, 320), (300, 65, 2304), (129, 513, 1088), (1, 3, 128)]
+
+
+@pytest.mark.parametrize("plan", ["1", "2", "4", "12"])
+def test_onebit_kernel(plan, monkeypatch):
+    monkeypatch.setenv("DG_ONEBIT", plan)
+    for i, (B, H, W, Cin, Cout, KH, KW, stride, pad) in enumerate(CONVS):
+        lw, la = TABLES[i % len(TABLES)]
+        lut = dg.dg_build_lut(lw, la, dg.DG_LUT_I16)
+        c = wl.small_conv(B, H, W, Cin, Cout, KH, KW, stride, pad, seed=H + Cin, scale=True)
+        desc = dg.conv_desc(B, H, W, Cin, Cout, KH, KW, stride, pad)
+        scale = torch.from_numpy(c.scale).cuda()
+        Wp = dg.dg_pack_weights(torch.from_numpy(c.Wc).cuda(), Cout, KH * KW * Cin)
+        Xp = dg.dg_pack_activations(torch.from_numpy(c.Ac).cuda(), B * H * W, Cin)
+        want = oracle.conv2d(c.Wc, c.Ac, lw, la, stride=stride, pad=pad)
+        wants = oracle.scale_epilogue_nhwc(want, c.scale)
+        assert np.array_equal(dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy(), want), (i, "int32")
+        assert np.array_equal(dg.dg_conv2d_lut(lut, Wp, Xp, desc, scale=scale).cpu().numpy(), wants), (i, "scaled")
+        got = dg.dg_conv2d_lut_requant(lut, Wp, Xp, desc, scale, 1.5, 0.5, 0).cpu().numpy()
+        codes = np.clip(np.rint(np.float32(1.5) * wants + np.float32(0.5)), 0, 3).astype(np.uint8).reshape(-1, Cout // 4, 4)
+        assert np.array_equal(got, (codes << np.array([0, 2, 4, 6], dtype=np.uint8)).sum(-1).astype(np.uint8).reshape(-1)), (i, "requantised")
+    for i, (M, N, K) in enumerate(GEMMS):
+        lw, la = TABLES[i % len(TABLES)]
+        lut = dg.dg_build_lut(lw, la, dg.DG_LUT_I16)
+        g = wl.small_gemm(M, N, K, seed=M)
+        Wp, Ap = dg.dg_pack_weights(torch.from_numpy(g.Wc).cuda(), M, K), dg.dg_pack_activations(torch.from_numpy(g.Ac).cuda(), N, K)
+        scale = torch.from_numpy(np.random.default_rng(K).uniform(0.01, 0.1, M).astype(np.float32)).cuda()
+        want = oracle.gemm(g.Wc, g.Ac, lw, la)
+        wants = want.astype(np.float32) * scale.cpu().numpy()[:, None]
+        # column-major, row-major, rows of whole 64-byte pieces, neither axis contiguous
+        wide = (N + 15) // 16 * 16
+        for strides, shape, view in (((1, M), (N, M), lambda o: o.T), ((N, 1), (M, N), lambda o: o), ((wide, 1), (M, wide), lambda o: o[:, :N]),
+                                     ((3, 3 * M + 1), (N, 3 * M + 1), lambda o: o[:, : 3 * M : 3].T)):
+            for s, w in ((None, want), (scale, wants)):
+                out = torch.zeros(shape, dtype=torch.int32 if s is None else torch.float32, device="cuda")
+                dg.dg_gemm_lut(lut, Wp, Ap, M, N, K, out=out, strides=strides, scale=s)
+                assert np.array_equal(view(out.cpu().numpy()), w), ((M, N, K), strides, s is not None)
+
+
+def test_sums_to_the_end_of_the_range(monkeypatch):
+    """Sums of every magnitude up to the largest that is taken, 3 * 4 * K just below 2^24, in steps of the smallest entry: exact."""
+    M, N, K = 64, 40, 1398016
+    lw, la = (-4, 1, 3, 4), (0, 1, 2, 3)
+    rng = np.random.default_rng(5)
+    Wc, Ac = rng.integers(0, 4, (M, K), dtype=np.uint8), rng.integers(0, 4, (N, K), dtype=np.uint8)
+    for m in range(0, M, 2):                                # rows that climb to ever larger sums, on columns of the largest code
+        Wc[m, : K * (m + 2) // M] = 3
+    Ac[: N // 2] = 3
+    Wc[1], Ac[1, ::7] = 0, 0
+    lut = dg.dg_build_lut(lw, la)
+    Wp, Ap = dg.dg_pack_weights(torch.from_numpy(Wc).cuda(), M, K), dg.dg_pack_activations(torch.from_numpy(Ac).cuda(), N, K)
+    want = np.rint(np.asarray(lw, np.float64)[Wc] @ np.asarray(la, np.float64)[Ac].T).astype(np.int64)      # (below 2^53: exact)
+    assert 2 ** 24 - 2 ** 10 <= np.abs(want).max() < 2 ** 24
+    for plan in ("1", "12"):
+        monkeypatch.setenv("DG_ONEBIT", plan)
+        assert np.array_equal(dg.dg_gemm_lut(lut, Wp, Ap, M, N, K).cpu().numpy(), want), plan
