@@ -219,7 +219,7 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *   DG_NIBBLES       "0": AUTO takes 3- and 4-bit tables whole even where they are the sum of two 2-bit lookups; "1": as
  *                    such sums also while DG_ONEHOT_PLAN is set (which then forces the 2-bit kernel's shape)
  *   DG_ONEBIT        "0": AUTO never takes tables that are two one-bit lookups to the FP4 instruction; "1", "2", "4": whatever the size, in
- *                    tiles of 64 x 128, 256 or 512, "12": 64 x 128 with K shared by two
+ *                    tiles of 64 x 128, 256 or 512, "12": 64 x 128 with K shared by two; "21", "41": wide tiles for half of the pixels
  *   DG_PERM_PLAN     index of the permute kernel's tile shape
  */
 typedef enum {

@@ -42,9 +42,13 @@ struct OneBitArgs {
     DgProblem p;
     uint32_t numbers;        // byte w: N[w] as FP4
     int32_t factor;          // f
-    FastDiv div_ow, div_oh, div_kw, div_cpt, div_band, div_last;    // (div_cpt: by the 64-position segments of a filter tap)
-    int32_t tiles_m, tiles_n, band_log2;
+    FastDiv div_ow, div_oh, div_kw, div_cpt, div_band;      // (div_cpt: by the 64-position segments of a filter tap)
+    int32_t band_log2;
     uint32_t band_tiles, x_bytes;
+    // the pixels before n_narrow in tiles of the kernel's width, `wide` workgroups, the rest in narrow ones
+    uint32_t wide;
+    int32_t tiles_n[2], n_narrow;
+    FastDiv div_last[2];
 };
 
 __device__ __forceinline__ f32x16 fp4_step(const v4i &a, const v4i &b, f32x16 c)
@@ -53,33 +57,32 @@ __device__ __forceinline__ f32x16 fp4_step(const v4i &a, const v4i &b, f32x16 c)
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, c, 4, 4, 0, 0, 0, 0);
 }
 
+// One tile: 64 channels, 4 x 32 WN pixels.
+//
 // KS = 2: eight wavefronts, two to a tile, each with half of K; their sums meet in LDS.  TAPS: a filter window.  TR: channels on the
 // matrix instruction's columns (dg_mfma_tile.h).  STREAM: the output bypasses the caches, which is best where its rows are whole 64-byte
 // pieces; where they are not, a line's parts come from different wavefronts and tiles and are brought together in L2 instead of being
 // written one by one (same tile, us, streaming and not: 3569 x 7478 x 704 55.1, 28.3; 112x112x128 -> 120 3x3 at batch 25 77.5, 54.7; whole
 // pieces: 112x112x64 -> 96 3x3 at batch 12 20.4, 22.5).
 template <int WN, int KS, bool TAPS, bool TR, bool STREAM>
-__global__ void __launch_bounds__(256 * KS, 2)
-onebit_kernel(OneBitArgs a)
+__device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, uint32_t block, uint32_t blocks, int part)
 {
     constexpr int WEIGHTS = 8192;                           // bytes of a run's weight operands: 64 rows, 256 positions
     constexpr int PIXELS = WN * 2048;                       // bytes of a wavefront's pixels of a run
     constexpr int LOADS = 2 * WN;                           // loads of 16 rows each
     constexpr int BESIDE = WN > 1 ? 6 : 0;                  // other instructions between two matrix instructions (8192-cube 372 -> 356 us; 0: the compiler's order)
     constexpr int SHARE = 2 * WEIGHTS + 8 * PIXELS;         // bytes of the four wavefronts that walk one share of K
-    __shared__ uint4 s_mem[KS * SHARE / 16];
     const DgProblem &p = a.p;
-    dg_fetch_arguments<sizeof(a)>();
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 31, h = lane >> 5;
     const int w4 = wave & 3, ks = KS == 1 ? 0 : wave >> 2;
     int m_tile, n_tile;                                     // numbered in bands of 2^band_log2 pixel tiles, as in dg_sparse_staged_kernel.h
     {
-        const uint32_t t = xcd_contiguous(blockIdx.x, gridDim.x), band = fdiv(t, a.div_band), t_in = t - band * a.band_tiles;
-        const int first = (int)band << a.band_log2, width = min(1 << a.band_log2, a.tiles_n - first);
-        m_tile = (int)(width == 1 << a.band_log2 ? t_in >> a.band_log2 : fdiv(t_in, a.div_last));
+        const uint32_t t = xcd_contiguous(block, blocks), band = fdiv(t, a.div_band), t_in = t - band * a.band_tiles;
+        const int first = (int)band << a.band_log2, width = min(1 << a.band_log2, a.tiles_n[part] - first);
+        m_tile = (int)(width == 1 << a.band_log2 ? t_in >> a.band_log2 : fdiv(t_in, a.div_last[part]));
         n_tile = first + (int)t_in - m_tile * width;
     }
-    const int m0 = m_tile * 64, n0 = (n_tile * 4 + w4) * (WN * 32);
+    const int m0 = m_tile * 64, n0 = (part ? a.n_narrow : 0) + (n_tile * 4 + w4) * (WN * 32);
     const int cq = p.Cin / 4, all_runs = (p.K + 255) / 256;
     // this share's runs g0 ... g1 - 1 of K and its chunks (64 positions); the shares walk equally many runs, past their ends as zeros
     const int g0 = KS == 1 ? 0 : all_runs * ks / KS, g1 = KS == 1 ? all_runs : all_runs * (ks + 1) / KS;
@@ -252,6 +255,17 @@ onebit_kernel(OneBitArgs a)
         }
 }
 
+// WN > 1: the last workgroups take narrow tiles (onebit_plan).
+template <int WN, int KS, bool TAPS, bool TR, bool STREAM>
+__global__ void __launch_bounds__(256 * KS, 2)
+onebit_kernel(OneBitArgs a)
+{
+    __shared__ uint4 s_mem[KS * (16384 + WN * 16384) / 16];
+    dg_fetch_arguments<sizeof(a)>();
+    if (WN > 1 && blockIdx.x >= a.wide) onebit_tile<1, 1, TAPS, TR, STREAM>(a, s_mem, blockIdx.x - a.wide, gridDim.x - a.wide, 1);
+    else onebit_tile<WN, KS, TAPS, TR, STREAM>(a, s_mem, blockIdx.x, WN > 1 ? a.wide : gridDim.x, 0);
+}
+
 // N[w] and f of a table of the form above, if its N are FP4 numbers; *largest: the largest |T[w][1]| / f.
 bool find_numbers(const dg_lut *lut, uint32_t *numbers, int32_t *factor, int32_t *largest)
 {
@@ -289,27 +303,44 @@ bool takes(const dg_lut *lut, const DgProblem &p)
 
 struct OneBitPlan {
     int wn, ks;
+    int64_t columns;         // of wide tiles, the pixel tiles; what is left takes narrow ones
 };
 
 int64_t tiles_of(const DgProblem &p, int wn) { return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 128 * wn - 1) / (128 * wn)); }
 
-// DG_ONEBIT: 0 never, 1, 2, 4 this kernel with WN so large, 12 with WN = 1 and KS = 2, whatever the size.
+// DG_ONEBIT: 0 never, 1, 2, 4 this kernel with WN so large, 12 with WN = 1 and KS = 2, 21 and 41 half of the pixels in narrow tiles, whatever the size.
 OneBitPlan onebit_plan(const DgProblem &p)
 {
-    if (const char *f = dg_override("DG_ONEBIT")) return OneBitPlan{atoi(f) == 12 ? 1 : atoi(f), atoi(f) == 12 ? 2 : 1};
+    const int64_t units = dg_simd_count() / 4, runs = ((int64_t)p.K + 255) / 256, t1 = tiles_of(p, 1), tm = ((int64_t)p.M + 63) / 64;
+    auto columns = [&](int wn) { return ((int64_t)p.N + 128 * wn - 1) / (128 * wn); };
+    if (const char *f = dg_override("DG_ONEBIT")) {
+        const int v = atoi(f);
+        if (v > 20) return OneBitPlan{v / 10, 1, columns(v / 10) / 2};
+        return OneBitPlan{v == 12 ? 1 : v, v == 12 ? 2 : 1, columns(v == 12 ? 1 : v)};
+    }
     // A tile twice (four times) as wide costs 1.82 (3.55) times as much per run on a busy compute unit, so the plan is the one that
     // leaves the busiest the least: 112x112x128 -> 128 3x3 at batch 10 (1960, 980, 490 tiles) 24.2, 22.7, 25.0 us; 56x56x128 -> 112 3x3 at batch 26
     // (1274, 638) 16.7, 18.1; 56x56x256 -> 112 3x3 at batch 28 (1372, 686) 28.3, 25.2.  Few runs do not pay for a wide tile's longer end:
     // 6648 x 2359 x 832 22.1, 25.2; the widest wants nine: 1986 x 7254 x 6272 83.7, 78.3, 74.9, 8192-cube 402, 367, 356, 112x112x128 -> 120 3x3 at
-    // batch 25 60.2, 54.7, 59.4.
-    const int64_t units = dg_simd_count() / 4, runs = ((int64_t)p.K + 255) / 256, t1 = tiles_of(p, 1);
-    auto rounds = [&](int wn) { return (double)((tiles_of(p, wn) + units - 1) / units); };
-    if (t1 <= units) return OneBitPlan{1, runs >= 8 ? 2 : 1};
-    OneBitPlan q = {1, 1};
-    double best = rounds(1);
+    // batch 25 60.2, 54.7, 59.4.  Rounds of wide tiles that would leave compute units idle in the last one end in narrow tiles: 56x56x256 -> 256
+    // 3x3 at batch 16 (392 tiles of 512 pixels on 256 compute units) 32.4, as 256 and 544 of 128 pixels 30.8; 112x112x128 -> 112 3x3 at batch 18
+    // 42.4, 39.4; 3200 x 6400 x 2304 42.9, 40.4.
+    if (t1 <= units) return OneBitPlan{1, runs >= 8 ? 2 : 1, columns(1)};
+    OneBitPlan q = {1, 1, columns(1)};
+    double best = (double)((t1 + units - 1) / units);
+    auto consider = [&](int wn, double cost) {
+        const int64_t all = tm * columns(wn), whole = all / units * units / tm;          // columns that fill whole rounds
+        const double c = all <= units ? 4.1 : cost * ((all + units - 1) / units);          // (a lone wavefront per SIMD is slower: WN = 4)
+        if (c < best) best = c, q = OneBitPlan{wn, 1, columns(wn)};
+        const int64_t rest = p.N - whole * 128 * wn;
+        if (whole > 0 && rest > 0) {
+            const double mixed = cost * (all / units) + (double)((tm * ((rest + 127) / 128) + units - 1) / units);
+            if (mixed < best) best = mixed, q = OneBitPlan{wn, 1, whole};
+        }
+    };
     if (t1 > 2 * units && (runs >= 5 || t1 >= 13 * units)) {
-        if (1.82 * rounds(2) < best) q.wn = 2, best = 1.82 * rounds(2);
-        if (runs >= 9 && 3.55 * rounds(4) < best) q.wn = 4;
+        consider(2, 1.82);
+        if (runs >= 9) consider(4, 3.55);
     }
     return q;
 }
@@ -319,14 +350,15 @@ OneBitPlan onebit_plan(const DgProblem &p)
 // AUTO takes such tables here where the tiles are many enough, instead of to the one-hot kernels (`staged`: the staged one).  Of 210 layers and
 // GEMMs of 1.5 to 200 GOP those with 130 tiles of 64 x 128 and more were all shorter here, by 38 % on average; with fewer, long K is walked by too
 // few wavefronts: 28x28x256 -> 64 3x3 at batch 8 (98 tiles, 9 runs) 8.3 against 7.9, 14x14x256 -> 744 3x3 at batch 7 (132) 11.4 against 9.2,
-// 7x7x1152 -> 1680 3x3 at batch 10 (108 tiles, 41 runs) 18.5 against 20.8; the direct-load kernels from 35: 738 x 360 x 5568 (36) 15.3 against 12.2.
+// 7x7x1152 -> 1680 3x3 at batch 10 (108 tiles, 41 runs) 18.5 against 20.8, and short K is level: 28x28x128 -> 128 3x3 at batch 8 (98, 5 runs) 6.1 against
+// 6.2, re-quantising between other layers 0.4 us longer here; the direct-load kernels from 35: 738 x 360 x 5568 (36) 15.3 against 12.2.
 bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p, bool staged)
 {
     if (!takes(lut, p)) return false;
     if (const char *f = dg_override("DG_ONEBIT")) return atoi(f) != 0;
     if (dg_override("DG_ONEHOT_PLAN") != nullptr || dg_override("DG_ONEHOT_WAVES") != nullptr) return false;
-    const int64_t t1 = tiles_of(p, 1), runs = ((int64_t)p.K + 255) / 256;
-    return t1 >= (staged ? (runs <= 7 ? 80 : 130) : 35);
+    const int64_t t1 = tiles_of(p, 1);
+    return t1 >= (staged ? 130 : 35);
 }
 
 dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
@@ -338,14 +370,19 @@ dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t st
     const OneBitPlan q = onebit_plan(p);
     a.div_ow = make_div((uint32_t)p.OW), a.div_oh = make_div((uint32_t)p.OH), a.div_kw = make_div((uint32_t)p.KW);
     a.div_cpt = make_div((uint32_t)(p.Cin / 64));
-    a.tiles_m = (p.M + 63) / 64, a.tiles_n = (p.N + 128 * q.wn - 1) / (128 * q.wn);
+    const int64_t tiles_m = ((int64_t)p.M + 63) / 64, rest = p.N - q.columns * 128 * q.wn;
+    a.n_narrow = (int32_t)(rest > 0 ? q.columns * 128 * q.wn : 0);
+    a.tiles_n[0] = (int32_t)q.columns, a.tiles_n[1] = (int32_t)(rest > 0 ? (rest + 127) / 128 : 0);
+    a.wide = (uint32_t)(tiles_m * a.tiles_n[0]);
     a.band_log2 = 2;
-    a.band_tiles = (uint32_t)a.tiles_m << a.band_log2;
+    a.band_tiles = (uint32_t)tiles_m << a.band_log2;
     a.div_band = make_div(a.band_tiles);
-    const int last = a.tiles_n & ((1 << a.band_log2) - 1);
-    a.div_last = make_div((uint32_t)(last ? last : 1));
+    for (int i = 0; i < 2; ++i) {
+        const int last = a.tiles_n[i] & ((1 << a.band_log2) - 1);
+        a.div_last[i] = make_div((uint32_t)(last ? last : 1));
+    }
     a.x_bytes = (uint32_t)((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4));
-    const dim3 grid((unsigned)((int64_t)a.tiles_m * a.tiles_n));
+    const dim3 grid((unsigned)(tiles_m * (a.tiles_n[0] + a.tiles_n[1])));
     const bool taps = p.KH * p.KW > 1;
     const bool rows_m = p.stride_cn == 1 && p.stride_cm != 1 && !taps && !p.Qp;      // (the output's rows are channels: a GEMM with n contiguous)
     const int64_t row = rows_m ? p.stride_cm : p.stride_cn;
