@@ -52,7 +52,20 @@ struct DgProblem {
     uint8_t *Qp;          // [N][M/4]; requires scale, M % 4 == 0 and the NHWC output order (stride_cm == 1)
     float q_scale, q_zero;
     int32_t q_lo;
+    int32_t cached;       // the output goes through the caches (dg_output_cached; set by the kernels' launchers)
 };
+
+// Whether an output is better written through the caches than past them: a tile's rows are 128-byte pieces of the output's, and where those
+// are no whole multiples of 64 bytes a memory line's parts come from different wavefronts and tiles; streamed they are written one by
+// one, through L2 together.  Same kernels, us, streamed and through the caches: 5942 x 6830 x 320 (direct-load tiles) 108, 51; 3648 x 7425 x 256
+// (stationary weights) 52.8, 29.7; 1986 x 7254 x 1280 (staged) 56.5, 42.2; 28x28x512 -> 264 at batch 32 15.5, 14.1; 28x28x128 -> 104 3x3 at batch
+// 16, 4-bit, 12.6, 12.0; 1000 x 1001 x 2048 8.1, 8.0; and one-bit tables (dg_onebit_kernel.hip) 3569 x 7478 x 704 55, 28.  Whole pieces: 56x56x256 -> 64 at
+// batch 32 8.6, 9.9; one-bit tables 112x112x64 -> 96 3x3 at batch 12 20.4, 22.5.
+inline int32_t dg_output_cached(const DgProblem &p)
+{
+    const int64_t row = p.stride_cm == 1 ? p.stride_cn : p.stride_cm;
+    return row % 16 != 0 || (p.scale ? (uintptr_t)p.Cf : (uintptr_t)p.C) % 64 != 0;
+}
 
 // n / d for 0 <= n < 2^31 by multiply-high and shift, d fixed per launch and prepared on the host:
 // n / d == umulhi(2 n, mul) >> shift with shift = ceil(log2 d) and mul = ceil(2^(31+shift) / d) < 2^32

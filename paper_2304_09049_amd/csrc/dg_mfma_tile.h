@@ -79,10 +79,13 @@ __device__ __forceinline__ bool dg_mfma_rows_whole(int64_t row_stride, int64_t c
     return rowb + 32 <= row_limit && span < ((int64_t)1 << 30);
 }
 
-template <bool STREAM, class T>
+// How a block's stores go: past the caches, through them, or as the problem says (DgProblem::cached: dg_output_cached).
+enum DgOut { DG_OUT_STREAM, DG_OUT_CACHED, DG_OUT_BY_PROBLEM };
+template <DgOut OUT, class T>
 __device__ __forceinline__ void dg_put(T v, T *to)
 {
-    if constexpr (STREAM) __builtin_nontemporal_store(v, to);
+    static_assert(OUT != DG_OUT_BY_PROBLEM, "decided before");
+    if constexpr (OUT == DG_OUT_STREAM) __builtin_nontemporal_store(v, to);
     else *to = v;
 }
 
@@ -91,22 +94,17 @@ __device__ __forceinline__ void dg_put(T v, T *to)
 // element by element where it is partial: dg_sparse_ws_kernel.h, and dg_sparse_staged_kernel.h, where (packed codes, graph
 // replays) 28x28x256 -> 200 at batch 32 went from 17.4 to 14.5 us with 3-bit codes, 56x56x256 -> 72 from 28.6 to 23.3, 56x56x128 ->
 // 72 3x3 at batch 16 from 21.7 to 17.9 with 2-bit ones, and layers of whole blocks stayed (56x56x128 -> 128 3x3 17.0, 17.2).
-template <bool TR, bool EDGE_COLUMNS = false, bool STREAM = true>
-__device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg_v16i &acc, int mb, int nb, int lane,
-                                                    float sc)
+template <bool TR, bool EDGE_COLUMNS, DgOut OUT>
+__device__ __forceinline__ void dg_mfma_store_sums(const DgProblem &p, const dg_v16i &acc, int mb, int nb, int lane, float sc)
 {
-    if (TR && p.Qp) {
-        dg_mfma_requant_block(p, acc, mb, nb, lane, sc);
-        return;
-    }
     const int r = lane & 31, h = lane >> 5;
     // (mb and nb are the same in every lane of the wavefront: say so, and the block's base address is scalar arithmetic)
     const int colb = __builtin_amdgcn_readfirstlane(TR ? mb : nb), rowb = __builtin_amdgcn_readfirstlane(TR ? nb : mb);
     const int col_limit = TR ? p.M : p.N, row_limit = TR ? p.N : p.M;
     const int64_t row_stride = TR ? p.stride_cn : p.stride_cm, col_stride = TR ? p.stride_cm : p.stride_cn;
     // A block wholly inside the output: one uniform base address, a 32-bit offset per lane, then steps of the row stride
-    // -- no bounds test and no 64-bit arithmetic per element.  The stores are streaming (non-temporal) stores: the output
-    // is written once and read by a later kernel, it has no business in this one's caches.
+    // -- no bounds test and no 64-bit arithmetic per element.  The stores are streaming (non-temporal) stores, the output
+    // being written once and read by a later kernel, where its rows are whole 64-byte pieces (dg_output_cached).
     if ((EDGE_COLUMNS || colb + 32 <= col_limit) && dg_mfma_rows_whole(row_stride, col_stride, rowb, row_limit)) {
         if (EDGE_COLUMNS && colb + r >= col_limit) return;
         const int64_t base = (int64_t)colb * col_stride + (int64_t)rowb * row_stride;
@@ -117,14 +115,14 @@ __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int k = 8 * (e / 4) + (e % 4);
-                dg_put<STREAM>((float)acc[e] * (TR ? sc : scale_rows[k]), out + (off0 + k * rs));
+                dg_put<OUT>((float)acc[e] * (TR ? sc : scale_rows[k]), out + (off0 + k * rs));
             }
         } else {
             int32_t *out = p.C + base;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int k = 8 * (e / 4) + (e % 4);
-                dg_put<STREAM>(acc[e], out + (off0 + k * rs));
+                dg_put<OUT>(acc[e], out + (off0 + k * rs));
             }
         }
         return;
@@ -140,15 +138,24 @@ __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg
         if (row0 + k >= row_limit) continue;
         const int64_t o = first + k * row_stride;
         if (p.scale)
-            dg_put<STREAM>((float)acc[e] * (TR ? sc : p.scale[row0 + k]), p.Cf + o);
+            dg_put<OUT>((float)acc[e] * (TR ? sc : p.scale[row0 + k]), p.Cf + o);
         else
-            dg_put<STREAM>(acc[e], p.C + o);
+            dg_put<OUT>(acc[e], p.C + o);
     }
+}
+template <bool TR, bool EDGE_COLUMNS = false, DgOut OUT = DG_OUT_STREAM>
+__device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg_v16i &acc, int mb, int nb, int lane,
+                                                    float sc)
+{
+    if (TR && p.Qp) dg_mfma_requant_block(p, acc, mb, nb, lane, sc);
+    else if (OUT == DG_OUT_CACHED || (OUT == DG_OUT_BY_PROBLEM && p.cached))           // (uniform)
+        dg_mfma_store_sums<TR, EDGE_COLUMNS, DG_OUT_CACHED>(p, acc, mb, nb, lane, sc);
+    else dg_mfma_store_sums<TR, EDGE_COLUMNS, DG_OUT_STREAM>(p, acc, mb, nb, lane, sc);
 }
 
 // Store NQ groups of four registers of a block, the first one group q0 (TR layout; a partial last block of channels as with EDGE_COLUMNS
-// above).
-template <int NQ, bool STREAM = true>
+// above; always past the caches: shared tiles belong to layers of a few microseconds, whose outputs gain 4 % at most the other way).
+template <int NQ>
 __device__ __forceinline__ void dg_mfma_store_quads(const DgProblem &p, const dg_v4i (&acc)[NQ], int q0, int mb, int nb, int lane, float sc)
 {
     if (p.Qp) {
@@ -165,11 +172,11 @@ __device__ __forceinline__ void dg_mfma_store_quads(const DgProblem &p, const dg
         if (p.scale) {
             float *out = p.Cf + base;
 #pragma unroll
-            for (int e = 0; e < 4 * NQ; ++e) dg_put<STREAM>((float)acc[e / 4][e % 4] * sc, out + (off0 + (8 * (e / 4) + e % 4) * rs));
+            for (int e = 0; e < 4 * NQ; ++e) dg_put<DG_OUT_STREAM>((float)acc[e / 4][e % 4] * sc, out + (off0 + (8 * (e / 4) + e % 4) * rs));
         } else {
             int32_t *out = p.C + base;
 #pragma unroll
-            for (int e = 0; e < 4 * NQ; ++e) dg_put<STREAM>(acc[e / 4][e % 4], out + (off0 + (8 * (e / 4) + e % 4) * rs));
+            for (int e = 0; e < 4 * NQ; ++e) dg_put<DG_OUT_STREAM>(acc[e / 4][e % 4], out + (off0 + (8 * (e / 4) + e % 4) * rs));
         }
         return;
     }
@@ -179,13 +186,13 @@ __device__ __forceinline__ void dg_mfma_store_quads(const DgProblem &p, const dg
         const int k = 8 * (e / 4) + e % 4;
         if (row0 + 4 * h + k >= p.N) continue;
         const int64_t o = first + k * p.stride_cn;
-        if (p.scale) dg_put<STREAM>((float)acc[e / 4][e % 4] * sc, p.Cf + o);
-        else dg_put<STREAM>(acc[e / 4][e % 4], p.C + o);
+        if (p.scale) dg_put<DG_OUT_STREAM>((float)acc[e / 4][e % 4] * sc, p.Cf + o);
+        else dg_put<DG_OUT_STREAM>(acc[e / 4][e % 4], p.C + o);
     }
 }
 
 // Store the (WM*32) x (WN*32) tile at (m0, n0).
-template <int WM, int WN, bool TR, bool EDGE_COLUMNS = false>
+template <int WM, int WN, bool TR, bool EDGE_COLUMNS = false, DgOut OUT = DG_OUT_STREAM>
 __device__ __forceinline__ void dg_mfma_store_tile(const DgProblem &p, const dg_v16i (&acc)[WM][WN], int m0, int n0,
                                                    int lane, const float (&sc_cols)[WM])
 {
@@ -193,5 +200,5 @@ __device__ __forceinline__ void dg_mfma_store_tile(const DgProblem &p, const dg_
     for (int bm = 0; bm < WM; ++bm)
 #pragma unroll
         for (int bn = 0; bn < WN; ++bn)
-            dg_mfma_store_block<TR, EDGE_COLUMNS>(p, acc[bm][bn], m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
+            dg_mfma_store_block<TR, EDGE_COLUMNS, OUT>(p, acc[bm][bn], m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
 }

@@ -24,7 +24,7 @@
 // microseconds: a run of the 64 x 128 tile takes 0.5 us then.  The staged sparse kernel, this one (packed codes, graph replays, us):
 //   8192-cube 648, 356          56x56x256 -> 256 3x3 at batch 16 47.1, 30.6          28x28x512 -> 512 3x3 at batch 16 46.1, 29.9
 //   28x28x128 -> 128 3x3 at batch 32 12.2, 8.6          28x28x256 -> 256 3x3 at batch 8 10.9, 8.4          3569 x 7478 x 704 81.5, 28.3
-// (the last by its stores too: see STREAM).
+// (the last by its stores too: dg_output_cached).
 #include "dg_lds_dma.h"
 #include "dg_onehot_kernel.h"
 
@@ -60,11 +60,8 @@ __device__ __forceinline__ f32x16 fp4_step(const v4i &a, const v4i &b, f32x16 c)
 // One tile: 64 channels, 4 x 32 WN pixels.
 //
 // KS = 2: eight wavefronts, two to a tile, each with half of K; their sums meet in LDS.  TAPS: a filter window.  TR: channels on the
-// matrix instruction's columns (dg_mfma_tile.h).  STREAM: the output bypasses the caches, which is best where its rows are whole 64-byte
-// pieces; where they are not, a line's parts come from different wavefronts and tiles and are brought together in L2 instead of being
-// written one by one (same tile, us, streaming and not: 3569 x 7478 x 704 55.1, 28.3; 112x112x128 -> 120 3x3 at batch 25 77.5, 54.7; whole
-// pieces: 112x112x64 -> 96 3x3 at batch 12 20.4, 22.5).
-template <int WN, int KS, bool TAPS, bool TR, bool STREAM>
+// matrix instruction's columns (dg_mfma_tile.h).
+template <int WN, int KS, bool TAPS, bool TR>
 __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, uint32_t block, uint32_t blocks, int part)
 {
     constexpr int WEIGHTS = 8192;                           // bytes of a run's weight operands: 64 rows, 256 positions
@@ -241,7 +238,7 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
             out[4 * q] = result(x.x + y.x), out[4 * q + 1] = result(x.y + y.y);
             out[4 * q + 2] = result(x.z + y.z), out[4 * q + 3] = result(x.w + y.w);
         }
-        dg_mfma_store_block<TR, true, STREAM>(p, out, m0 + ks * 32, n0, lane, ks ? sc_cols[1] : sc_cols[0]);
+        dg_mfma_store_block<TR, true, DG_OUT_BY_PROBLEM>(p, out, m0 + ks * 32, n0, lane, ks ? sc_cols[1] : sc_cols[0]);
         return;
     }
 #pragma unroll
@@ -251,19 +248,19 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
             v16i out;
 #pragma unroll
             for (int e = 0; e < 16; ++e) out[e] = result(acc[bm][bn][e]);
-            dg_mfma_store_block<TR, true, STREAM>(p, out, m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
+            dg_mfma_store_block<TR, true, DG_OUT_BY_PROBLEM>(p, out, m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
         }
 }
 
 // WN > 1: the last workgroups take narrow tiles (onebit_plan).
-template <int WN, int KS, bool TAPS, bool TR, bool STREAM>
+template <int WN, int KS, bool TAPS, bool TR>
 __global__ void __launch_bounds__(256 * KS, 2)
 onebit_kernel(OneBitArgs a)
 {
     __shared__ uint4 s_mem[KS * (16384 + WN * 16384) / 16];
     dg_fetch_arguments<sizeof(a)>();
-    if (WN > 1 && blockIdx.x >= a.wide) onebit_tile<1, 1, TAPS, TR, STREAM>(a, s_mem, blockIdx.x - a.wide, gridDim.x - a.wide, 1);
-    else onebit_tile<WN, KS, TAPS, TR, STREAM>(a, s_mem, blockIdx.x, WN > 1 ? a.wide : gridDim.x, 0);
+    if (WN > 1 && blockIdx.x >= a.wide) onebit_tile<1, 1, TAPS, TR>(a, s_mem, blockIdx.x - a.wide, gridDim.x - a.wide, 1);
+    else onebit_tile<WN, KS, TAPS, TR>(a, s_mem, blockIdx.x, WN > 1 ? a.wide : gridDim.x, 0);
 }
 
 // N[w] and f of a table of the form above, if its N are FP4 numbers; *largest: the largest |T[w][1]| / f.
@@ -385,14 +382,8 @@ dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t st
     const dim3 grid((unsigned)(tiles_m * (a.tiles_n[0] + a.tiles_n[1])));
     const bool taps = p.KH * p.KW > 1;
     const bool rows_m = p.stride_cn == 1 && p.stride_cm != 1 && !taps && !p.Qp;      // (the output's rows are channels: a GEMM with n contiguous)
-    const int64_t row = rows_m ? p.stride_cm : p.stride_cn;
-    const uintptr_t out = p.scale ? (uintptr_t)p.Cf : (uintptr_t)p.C;
-    const bool stream_out = row % 16 == 0 && out % 64 == 0;
-#define DG_ONEBIT_FORM(WN, KS, TAPS, TR) \
-    do { \
-        if (stream_out) hipLaunchKernelGGL((onebit_kernel<WN, KS, TAPS, TR, true>), grid, dim3(256 * KS), 0, stream, a); \
-        else hipLaunchKernelGGL((onebit_kernel<WN, KS, TAPS, TR, false>), grid, dim3(256 * KS), 0, stream, a); \
-    } while (0)
+    a.p.cached = dg_output_cached(p);
+#define DG_ONEBIT_FORM(WN, KS, TAPS, TR) hipLaunchKernelGGL((onebit_kernel<WN, KS, TAPS, TR>), grid, dim3(256 * KS), 0, stream, a)
 #define DG_ONEBIT(WN, KS) \
     do { \
         if (rows_m) DG_ONEBIT_FORM(WN, KS, false, false); \

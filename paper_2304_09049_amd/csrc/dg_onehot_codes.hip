@@ -49,6 +49,7 @@ void unit_main_codes(const DgProblem &p, const Pools &pools, const Plan &q, bool
 {
     Args a{};
     a.p = p;
+    a.p.cached = dg_output_cached(p);
     a.pools = pools;
     a.tiles_m = (p.M + 63) / 64;
     a.wave_tiles = wave_tiles;

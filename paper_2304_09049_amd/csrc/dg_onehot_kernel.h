@@ -682,7 +682,7 @@ onehot_mfma_kernel(Args a)
             for (int e = 0; e < 16; ++e)
                 out[bm][bn][e] = TWO ? (int)((uint32_t)acc[0][bn][e] + ((uint32_t)acc[WM - 1][bn][e] << 8)) : acc[bm][bn][e];
     if (SKW == 1) {
-        dg_mfma_store_tile<RB, WN, TR>(p, out, m0, n0, lane, sc_cols);
+        dg_mfma_store_tile<RB, WN, TR, false, DG_OUT_BY_PROBLEM>(p, out, m0, n0, lane, sc_cols);
         return;
     }
     int32_t *sums = s_acc + tw * (NB * 1024);
@@ -700,7 +700,7 @@ onehot_mfma_kernel(Args a)
         v16i blk;
 #pragma unroll
         for (int e = 0; e < 16; ++e) blk[e] = sums[(i * 16 + e) * 64 + lane];
-        dg_mfma_store_block<TR>(p, blk, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane, sc_cols[i / WN]);
+        dg_mfma_store_block<TR, false, DG_OUT_BY_PROBLEM>(p, blk, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane, sc_cols[i / WN]);
     }
 }
 
@@ -916,6 +916,7 @@ void launch_main(const DgProblem &p, const Pools &pools, const Plan &q, int64_t 
 {
     Args a;
     a.p = p;
+    a.p.cached = dg_output_cached(p);
     a.pools = pools;
     a.tiles_m = (p.M + q.wm * 32 - 1) / (q.wm * 32);
     a.wave_tiles = wave_tiles;

@@ -121,13 +121,14 @@ sparse2p_kernel(Sparse2pArgs a)
     for (int bn = 0; bn < WN; ++bn)
 #pragma unroll
         for (int e = 0; e < 16; ++e) out[0][bn][e] = (int)((uint32_t)acc[0][bn][e] + ((uint32_t)acc[1][bn][e] << 8));
-    dg_mfma_store_tile<1, WN, true>(p, out, m0, n0, lane, sc_cols);
+    dg_mfma_store_tile<1, WN, true, false, DG_OUT_BY_PROBLEM>(p, out, m0, n0, lane, sc_cols);
 }
 
 inline void launch_sparse2p(const DgProblem &p, const uint32_t (&rows)[2][4], int ch, hipStream_t stream)
 {
     Sparse2pArgs a;
     a.p = p;
+    a.p.cached = dg_output_cached(p);
     for (int pl = 0; pl < 2; ++pl)
         for (int w = 0; w < 4; ++w) a.rows[pl][w] = rows[pl][w];
     a.tiles_m = (p.M + 31) / 32;

@@ -125,13 +125,14 @@ sparse4_kernel(Sparse4Args a)
                 }
             }
     }
-    dg_mfma_store_tile<WM, WN, true>(p, acc, m0, n0, lane, sc_cols);
+    dg_mfma_store_tile<WM, WN, true, false, DG_OUT_BY_PROBLEM>(p, acc, m0, n0, lane, sc_cols);
 }
 
 inline void launch_sparse4(const DgProblem &p, const uint32_t (&rows)[16][4], int ch, hipStream_t stream)
 {
     Sparse4Args a;
     a.p = p;
+    a.p.cached = dg_output_cached(p);
     for (int w = 0; w < 16; ++w)
         for (int i = 0; i < 4; ++i) a.rows[w][i] = rows[w][i];
     a.tiles_m = (p.M + 63) / 64;

@@ -551,7 +551,7 @@ smfmac_staged_kernel(Args a)
             for (int e = 0; e < 16; ++e)
                 out[bm][bn][e] = TWO ? (int)((uint32_t)acc[0][bn][e] + ((uint32_t)acc[WM - 1][bn][e] << 8)) : acc[bm][bn][e];
     if (SKW == 1) {
-        dg_mfma_store_tile<RB, WN, true, true>(p, out, m0, n0, lane_out, sc_cols);
+        dg_mfma_store_tile<RB, WN, true, true, DG_OUT_BY_PROBLEM>(p, out, m0, n0, lane_out, sc_cols);
         return;
     }
     // Every wavefront's sums take the place of its own staging rows (its last loads have landed), 16 bytes per lane and group of four
@@ -599,6 +599,7 @@ void launch_sparse_staged(const DgProblem &p, const Pools &pools, int32_t bias, 
 {
     Args a;
     a.p = p;
+    a.p.cached = dg_output_cached(p);
     a.pools = pools;
     a.bias = bias;
     a.x_bytes = (uint32_t)((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4));

@@ -69,7 +69,7 @@ struct WsArgs {
 // STRIDED (packed activations): a 1x1 convolution with a stride and no padding -- output pixel (b, oh, ow) reads the
 // row of input pixel (b, oh * sh, ow * sw).
 // NIB: 3- and 4-bit codes as two 2-bit ones each (dg_onehot_kernel.h, BITS = 24); K counts the 2-bit codes.
-template <int T, int G, bool RAW, bool STRIDED = false, bool NIB = false>
+template <int T, int G, bool RAW, bool STRIDED, bool NIB, bool CACHED>
 __global__ void __launch_bounds__(256, (!RAW && T * G > 32 ? 1 : 2))
 smfmac_ws_kernel(WsArgs a)
 {
@@ -236,7 +236,7 @@ smfmac_ws_kernel(WsArgs a)
 #pragma unroll
                 for (int par = 0; par < 2; ++par)
                     acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones[par], dn[t][par], acc, (int)xw.v[t], 0, 0);
-            dg_mfma_store_block<true, true>(p, acc, m0, (int)(blk * 32), lane, sc_cols[0]);
+            dg_mfma_store_block<true, true, CACHED ? DG_OUT_CACHED : DG_OUT_STREAM>(p, acc, m0, (int)(blk * 32), lane, sc_cols[0]);
             stores2 = stores1, stores1 = stores_of(blk);
         };
         int64_t blk = b0;
@@ -259,7 +259,7 @@ smfmac_ws_kernel(WsArgs a)
 #pragma unroll
                 for (int par = 0; par < 2; ++par)
                     acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(ones[par], dn[t][par], acc, (int)x[g].v[t], 0, 0);
-            dg_mfma_store_block<true, true>(p, acc, m0, (int)((blk + g) * 32), lane, sc_cols[0]);
+            dg_mfma_store_block<true, true, CACHED ? DG_OUT_CACHED : DG_OUT_STREAM>(p, acc, m0, (int)((blk + g) * 32), lane, sc_cols[0]);
         }
         // (only a run longer than one group comes here; these loads do queue behind the group's stores, which is why
         // the host sizes runs to one group where it can)
@@ -273,6 +273,9 @@ void launch_sparse_ws(const DgProblem &p, const Pools &pools, int streams, bool 
 {
     WsArgs a;
     a.p = p;
+    // (outputs that fit L2 beside the rest stay streamed, us: 56x56x128 -> 100 at batch 16, 20 MB, 7.6, through the caches 8.0; 112x112x64 -> 40 at batch 8,
+    // 16 MB, 6.0, 6.7; 56x56x128 -> 72 at batch 27, 24 MB, 9.5, 8.8; 56x56x64 -> 120 at batch 32, 48 MB, 18.2, 11.4)
+    const bool cached = dg_output_cached(p) && 4.0 * (double)p.M * (double)p.N >= 22e6;
     for (int w = 0; w < 32; ++w) a.rows[w] = pools.w[w];
     a.row_blocks = (p.M + 31) / 32;
     const int pixel_blocks = (p.N + 31) / 32;
@@ -290,24 +293,27 @@ void launch_sparse_ws(const DgProblem &p, const Pools &pools, int streams, bool 
     const int t = p.K / 32;
     const bool wide = a.run + (a.longer ? 1 : 0) > 4;
     // (the staging buffers of the form that packs: 4 wavefronts x 2 blocks x 32 pixels x K bytes, up to 64 KB)
+#define DG_WS_FORM(T, G, RAW, STRIDED, LDS)                                                                            \
+    do {                                                                                                              \
+        if (cached) hipLaunchKernelGGL((smfmac_ws_kernel<T, G, RAW, STRIDED, NIB, true>), grid, dim3(256), LDS, stream, a);  \
+        else hipLaunchKernelGGL((smfmac_ws_kernel<T, G, RAW, STRIDED, NIB, false>), grid, dim3(256), LDS, stream, a); \
+    } while (0)
 #define DG_WS(T, G)                                                                                                   \
     do {                                                                                                              \
         if constexpr (!NIB) if (raw) {                                                                                \
             const int lds = 4 * 2 * 32 * 32 * T;                                                                      \
-            (void)hipFuncSetAttribute((const void *)smfmac_ws_kernel<T, G, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); \
-            hipLaunchKernelGGL((smfmac_ws_kernel<T, G, true>), grid, dim3(256), lds, stream, a);                      \
+            (void)hipFuncSetAttribute(cached ? (const void *)smfmac_ws_kernel<T, G, true, false, false, true>         \
+                                             : (const void *)smfmac_ws_kernel<T, G, true, false, false, false>,       \
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);                               \
+            DG_WS_FORM(T, G, true, false, lds);                                                                       \
             break;                                                                                                    \
         }                                                                                                             \
-        if (strided)                                                                                                  \
-            hipLaunchKernelGGL((smfmac_ws_kernel<T, G, false, true, NIB>), grid, dim3(256), 0, stream, a);            \
-        else                                                                                                          \
-            hipLaunchKernelGGL((smfmac_ws_kernel<T, G, false, false, NIB>), grid, dim3(256), 0, stream, a);                                                                                                             \
+        if (strided) DG_WS_FORM(T, G, false, true, 0);                                                                \
+        else DG_WS_FORM(T, G, false, false, 0);                                                                       \
     } while (0)
     if (t == 16) {
-        if (strided)
-            hipLaunchKernelGGL((smfmac_ws_kernel<16, 4, false, true, NIB>), grid, dim3(256), 0, stream, a);
-        else
-            hipLaunchKernelGGL((smfmac_ws_kernel<16, 4, false, false, NIB>), grid, dim3(256), 0, stream, a);
+        if (strided) DG_WS_FORM(16, 4, false, true, 0);
+        else DG_WS_FORM(16, 4, false, false, 0);
     } else if (t == 8 && wide) DG_WS(8, 8);
     else if (t == 8) DG_WS(8, 4);
     else if (t == 4 && wide) DG_WS(4, 8);
@@ -315,6 +321,7 @@ void launch_sparse_ws(const DgProblem &p, const Pools &pools, int streams, bool 
     else if (wide) DG_WS(2, 8);
     else DG_WS(2, 4);
 #undef DG_WS
+#undef DG_WS_FORM
 }
 
 }   // namespace dgoh
