@@ -354,7 +354,7 @@ dg_status run(const dg_lut *lut, const DgProblem &p, dg_kernel variant, hipStrea
 {
     const Pick pick = pick_kernel(lut, p, variant);
     // (AUTO's plans on the one-hot kernels: tables of a narrower form run on a kernel of their own, whatever the plan's name says)
-    if (variant == DG_KERNEL_AUTO && (pick == Pick::Sparse || pick == Pick::OneHot) && dg_onebit_preferred(lut, p, dg_sparse_is_staged(lut, p)))
+    if (variant == DG_KERNEL_AUTO && (pick == Pick::Sparse || pick == Pick::OneHot) && dg_onebit_preferred(lut, p))
         return dg_launch_onebit(lut, p, stream);
     switch (pick) {
     case Pick::Perm: return dg_launch_perm(lut, p, stream);
@@ -585,7 +585,11 @@ dg_status run_codes(const char *name, const dg_lut *lut, DgProblem &p, const uin
                     void *work, size_t work_bytes, dg_kernel variant, void *hip_stream)
 {
     p.Xp = codes;
-    switch (fuses_packing(lut, p, variant)) {
+    const Fuse fuse = fuses_packing(lut, p, variant);
+    if (variant == DG_KERNEL_AUTO && (fuse == Fuse::OneHot || fuse == Fuse::OneHotSparse || fuse == Fuse::SparseWs) &&
+        dg_onebit_codes_preferred(lut, p, fuse == Fuse::SparseWs))
+        return dg_launch_onebit_codes(lut, p, (hipStream_t)hip_stream);
+    switch (fuse) {
     case Fuse::OneHot: return dg_launch_onehot_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::OneHotSparse: return dg_launch_onehot_codes(lut, p, (hipStream_t)hip_stream, true);
     case Fuse::SmallN: return dg_launch_smalln_codes(lut, p, (hipStream_t)hip_stream);
@@ -763,7 +767,7 @@ dg_status dg_conv2d_lut_requant(const dg_lut *lut, const void *Wp_dev, const voi
     if (variant == DG_KERNEL_AUTO && dg_staged2p_preferred(lut, p)) return dg_launch_staged2p(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_AUTO && dg_sparse2p_preferred(lut, p)) return dg_launch_sparse2p(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_AUTO && dg_sparse4_preferred(lut, p)) return dg_launch_sparse4(lut, p, (hipStream_t)hip_stream);
-    if (variant == DG_KERNEL_AUTO && dg_onebit_preferred(lut, p, dg_sparse_is_staged(lut, p))) return dg_launch_onebit(lut, p, (hipStream_t)hip_stream);
+    if (variant == DG_KERNEL_AUTO && dg_onebit_preferred(lut, p)) return dg_launch_onebit(lut, p, (hipStream_t)hip_stream);
     if (variant == DG_KERNEL_AUTO && dg_sparse_preferred(lut, p)) return dg_launch_sparse(lut, p, (hipStream_t)hip_stream);
     return dg_launch_onehot(lut, p, (hipStream_t)hip_stream);
 }

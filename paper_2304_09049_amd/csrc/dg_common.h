@@ -160,8 +160,10 @@ bool dg_sparse_preferred(const dg_lut *lut, const DgProblem &p);     // AUTO's c
 dg_status dg_launch_sparse(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 bool dg_sparse_is_staged(const dg_lut *lut, const DgProblem &p);     // AUTO would run it on the staged kernel
 const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p);
-bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p, bool staged);        // tables that are two one-bit lookups, on the FP4 instruction
+bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p);       // tables that are two one-bit lookups, on the FP4 instruction
 dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stationary);    // p.Xp: codes one per byte
+dg_status dg_launch_onebit_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes);      // taps of no whole 32-position groups; `codes`: p.Xp one per byte
 const char *dg_ragged_config_name(const dg_lut *lut, const DgProblem &p, bool codes);
 dg_status dg_launch_ragged(const dg_lut *lut, const DgProblem &p, bool codes, hipStream_t stream);

@@ -263,6 +263,143 @@ onebit_kernel(OneBitArgs a)
     else onebit_tile<WN, KS, TAPS, TR>(a, s_mem, blockIdx.x, WN > 1 ? a.wide : gridDim.x, 0);
 }
 
+// The same from activations that are still one code per byte (p.Xp = those bytes): 64 channels x 4 x 32 pixels, runs of 128 positions.  Nothing is
+// packed: eight codes' bytes become an operand's word of 4-bit places by one shift and one bit-field insert, position i of the first
+// four at the bottom of byte i, of the second four at its top, and the weights' numbers are made in that order.  Bound by its start and by
+// lone wavefronts' issue slots, as the narrow tile on packed codes is: 112x112x64 -> 48 3x3 at batch 7 17.1 (sparse instruction, codes packed in
+// registers) -> 10.8 us, 22 MB of codes and sums in 9 us.
+template <bool TAPS>
+__global__ void __launch_bounds__(256, 4)
+onebit_codes_kernel(OneBitArgs a)
+{
+    constexpr int WEIGHTS = 4096, PIXELS = 4096;            // bytes of a run: the weights' numbers, a wavefront's pixels
+    __shared__ uint4 s_mem[(2 * WEIGHTS + 8 * PIXELS) / 16];
+    const DgProblem &p = a.p;
+    dg_fetch_arguments<sizeof(a)>();
+    const int lane = threadIdx.x & 63, w4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 31, h = lane >> 5;
+    int m_tile, n_tile;
+    {
+        const uint32_t t = xcd_contiguous(blockIdx.x, gridDim.x), band = fdiv(t, a.div_band), t_in = t - band * a.band_tiles;
+        const int first = (int)band << a.band_log2, width = min(1 << a.band_log2, a.tiles_n[0] - first);
+        m_tile = (int)(width == 1 << a.band_log2 ? t_in >> a.band_log2 : fdiv(t_in, a.div_last[0]));
+        n_tile = first + (int)t_in - m_tile * width;
+    }
+    const int m0 = m_tile * 64, n0 = (n_tile * 4 + w4) * 32;
+    const int runs = (p.K + 127) / 128, pieces = p.K / 16;  // (a piece: 16 positions, a lane's 16 bytes)
+
+    // ---- weights: thread t loads quarter t % 4 of a run's 32 bytes of row t / 4: word pair `half` of segment `seg`
+    const uint32_t row_bytes = (uint32_t)p.K / 4;
+    const __amdgpu_buffer_rsrc_t w_buffer =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(p.Wp + (int64_t)m0 * row_bytes), 0, (int)(min(p.M - m0, 64) * row_bytes), 0x00020000);
+    const int w_row = threadIdx.x >> 2, w_quarter = threadIdx.x & 3;
+    const uint32_t w_ld = w_row * row_bytes + w_quarter * 8;
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    auto load_weights = [&](int g) { return (v2i)__builtin_amdgcn_raw_buffer_load_b64(w_buffer, w_ld + g * 32, 0, 0); };
+    const uint32_t low = a.numbers, high = a.numbers << 4;
+    char *const w_to = (char *)s_mem + (((w_quarter >> 1) * 2 + (w_row >> 5)) * 64 + (w_quarter & 1) * 32 + ((w_row & 31) ^ (2 * w_quarter))) * 16;
+    auto spread = [](uint32_t word, int byte) {             // its four codes, one to a byte
+        const uint32_t pairs = (((word >> (8 * byte)) & 255u) * 0x1001u) & 0x000F000Fu;
+        return (pairs << 6 | pairs) & 0x03030303u;
+    };
+    auto expand = [&](const v2i &raw, uint32_t buf) {
+        v4i o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t word = (uint32_t)raw[q / 2];
+            o[q] = (int)(__builtin_amdgcn_perm(0u, low, spread(word, 2 * (q & 1))) | __builtin_amdgcn_perm(0u, high, spread(word, 2 * (q & 1) + 1)));
+        }
+        *(v4i *)(w_to + buf) = o;
+    };
+
+    // ---- pixels: lane l of a load fetches piece (l % 8) ^ (row % 8) of row l / 8 of eight
+    const v4i x_buffer = dg_buffer(p.Xp, a.x_bytes);
+    const int l_row = lane >> 3, l_piece = (lane & 7) ^ l_row;
+    uint32_t off0[4], outside[TAPS ? 4 : 1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const Column c = make_column(p, a.div_ow, a.div_oh, n0 + 8 * i + l_row, p.Cin, 0);
+        off0[i] = (uint32_t)c.off0;
+        asm("" : "+v"(off0[i]));
+        const int h0 = max(0, -c.ih0), h1 = c.ok ? min(p.KH, p.H - c.ih0) : 0, c0 = max(0, -c.iw0), c1 = min(p.KW, p.W - c.iw0);
+        const uint32_t columns = c1 > c0 ? (~0u >> (32 - (c1 - c0))) << c0 : 0u;
+        if constexpr (TAPS) {
+            uint32_t in = 0;
+            for (int kh = 0; kh < p.KH; ++kh) in |= kh >= h0 && kh < h1 ? columns << (kh * p.KW) : 0u;
+            outside[i] = ~in;
+        } else {
+            off0[i] |= h1 > h0 && c1 > c0 ? 0u : 0x80000000u;
+        }
+    }
+    const uint32_t x_lds = dg_lds_address(s_mem) + 2 * WEIGHTS + w4 * 2 * PIXELS;
+    auto fetch = [&](int g, int odd) {
+        const uint32_t dst = x_lds + odd * PIXELS;
+        const int c = 8 * g + l_piece;
+        const uint32_t dead = c < pieces ? 0u : 0x80000000u;
+        if constexpr (TAPS) {
+            const int tap = (int)fdiv((uint32_t)c, a.div_cpt), kh = (int)fdiv((uint32_t)tap, a.div_kw), kw = tap - kh * p.KW;
+            const uint32_t tap_off = (uint32_t)((kh * p.W + kw) * p.Cin + (c - tap * (p.Cin >> 4)) * 16);
+            dg_for<4>([&](auto i) {
+                const uint32_t out = (outside[i] << ((31 - tap) & 31)) | dead;
+                dg_load16_to_lds<i * 1024>(x_buffer, (off0[i] + tap_off) | (out & 0x80000000u), dst);
+            });
+        } else {
+            dg_for<4>([&](auto i) { dg_load16_to_lds<i * 1024>(x_buffer, (off0[i] + c * 16) | dead, dst); });
+        }
+    };
+
+    v2i raw = load_weights(0);
+    fetch(0, 0);
+    expand(raw, 0);
+    raw = load_weights(1);
+    float sc_cols[2];
+    dg_mfma_column_scales<2, true>(p, m0, lane, sc_cols);
+    f32x16 acc[2];
+#pragma unroll
+    for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[bm][e] = 0.0f;
+
+    const char *const x_from = (const char *)s_mem + 2 * WEIGHTS + w4 * 2 * PIXELS + r * 128;
+    for (int g = 0; g < runs; ++g) {
+        const int odd = g & 1;
+        dg_wait_for_loads<0>();                             // (this run's pixels, the next one's weights)
+        asm volatile("" : "+v"(raw));
+        const v2i next = raw;
+        __syncthreads();
+        fetch(g + 1, odd ^ 1);
+        raw = load_weights(g + 2);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            v4i w[2];
+            uint4 x[2];
+#pragma unroll
+            for (int bm = 0; bm < 2; ++bm)
+                w[bm] = *(const v4i *)((const char *)s_mem + odd * WEIGHTS + ((2 * s + bm) * 64 + h * 32 + (r ^ (2 * (2 * s + h)))) * 16);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) x[e] = *(const uint4 *)(x_from + odd * PIXELS + ((4 * s + 2 * h + e) ^ (r & 7)) * 16);
+            uint32_t t[4];
+            auto merge = [](uint32_t first, uint32_t second) { return (first & 0x0F0F0F0Fu) | ((second << 4) & 0xF0F0F0F0u); };
+            t[0] = merge(x[0].x, x[0].y), t[1] = merge(x[0].z, x[0].w), t[2] = merge(x[1].x, x[1].y), t[3] = merge(x[1].z, x[1].w);
+#pragma unroll
+            for (int bit = 0; bit < 2; ++bit) {
+                const uint32_t M = bit ? 0x22222222u : 0x11111111u;
+                const v4i o = {(int)(t[0] & M), (int)(t[1] & M), (int)(t[2] & M), (int)(t[3] & M)};
+#pragma unroll
+                for (int bm = 0; bm < 2; ++bm) acc[bm] = fp4_step(o, w[bm], acc[bm]);
+            }
+            if (s == 0) expand(next, (odd ^ 1) * WEIGHTS);
+        }
+    }
+    dg_wait_for_loads();                                    // (fetches past the end: their LDS writes end before the wavefront does)
+#pragma unroll
+    for (int bm = 0; bm < 2; ++bm) {
+        v16i out;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) out[e] = (int)(acc[bm][e] * 4.0f) * a.factor;
+        dg_mfma_store_block<true, true, DG_OUT_BY_PROBLEM>(p, out, m0 + bm * 32, n0, lane, sc_cols[bm]);
+    }
+}
+
 // N[w] and f of a table of the form above, if its N are FP4 numbers; *largest: the largest |T[w][1]| / f.
 bool find_numbers(const dg_lut *lut, uint32_t *numbers, int32_t *factor, int32_t *largest)
 {
@@ -344,27 +481,31 @@ OneBitPlan onebit_plan(const DgProblem &p)
 
 }   // namespace
 
-// AUTO takes such tables here where the tiles are many enough, instead of to the one-hot kernels (`staged`: the staged one).  Of 210 layers and
+// AUTO takes such tables here where the tiles are many enough, instead of to the one-hot kernels.  Of 210 layers and
 // GEMMs of 1.5 to 200 GOP those with 130 tiles of 64 x 128 and more were all shorter here, by 38 % on average; with fewer, long K is walked by too
 // few wavefronts: 28x28x256 -> 64 3x3 at batch 8 (98 tiles, 9 runs) 8.3 against 7.9, 14x14x256 -> 744 3x3 at batch 7 (132) 11.4 against 9.2,
 // 7x7x1152 -> 1680 3x3 at batch 10 (108 tiles, 41 runs) 18.5 against 20.8, and short K is level: 28x28x128 -> 128 3x3 at batch 8 (98, 5 runs) 6.1 against
 // 6.2, re-quantising between other layers 0.4 us longer here; the direct-load kernels from 35: 738 x 360 x 5568 (36) 15.3 against 12.2.
-bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p, bool staged)
+bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p)
 {
-    if (!takes(lut, p)) return false;
-    if (const char *f = dg_override("DG_ONEBIT")) return atoi(f) != 0;
-    if (dg_override("DG_ONEHOT_PLAN") != nullptr || dg_override("DG_ONEHOT_WAVES") != nullptr) return false;
+    const char *f = dg_override("DG_ONEBIT");
     const int64_t t1 = tiles_of(p, 1);
-    return t1 >= (staged ? 130 : 35);
+    if (f ? atoi(f) == 0 : t1 < 35) return false;
+    if (!takes(lut, p)) return false;
+    if (f) return true;
+    if (dg_override("DG_ONEHOT_PLAN") || dg_override("DG_ONEHOT_WAVES")) return false;
+    return t1 >= 130 || !dg_sparse_is_staged(lut, p);
 }
 
-dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
+namespace {
+
+void fill(const dg_lut *lut, const DgProblem &p, const OneBitPlan &q, OneBitArgs *args)
 {
-    OneBitArgs a;
+    OneBitArgs &a = *args;
     int32_t largest;
     a.p = p;
+    a.p.cached = dg_output_cached(p);
     find_numbers(lut, &a.numbers, &a.factor, &largest);
-    const OneBitPlan q = onebit_plan(p);
     a.div_ow = make_div((uint32_t)p.OW), a.div_oh = make_div((uint32_t)p.OH), a.div_kw = make_div((uint32_t)p.KW);
     a.div_cpt = make_div((uint32_t)(p.Cin / 64));
     const int64_t tiles_m = ((int64_t)p.M + 63) / 64, rest = p.N - q.columns * 128 * q.wn;
@@ -379,10 +520,18 @@ dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t st
         a.div_last[i] = make_div((uint32_t)(last ? last : 1));
     }
     a.x_bytes = (uint32_t)((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4));
-    const dim3 grid((unsigned)(tiles_m * (a.tiles_n[0] + a.tiles_n[1])));
+}
+
+}   // namespace
+
+dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
+{
+    const OneBitPlan q = onebit_plan(p);
+    OneBitArgs a;
+    fill(lut, p, q, &a);
+    const dim3 grid(a.wide + (unsigned)((((int64_t)p.M + 63) / 64) * a.tiles_n[1]));
     const bool taps = p.KH * p.KW > 1;
     const bool rows_m = p.stride_cn == 1 && p.stride_cm != 1 && !taps && !p.Qp;      // (the output's rows are channels: a GEMM with n contiguous)
-    a.p.cached = dg_output_cached(p);
 #define DG_ONEBIT_FORM(WN, KS, TAPS, TR) hipLaunchKernelGGL((onebit_kernel<WN, KS, TAPS, TR>), grid, dim3(256 * KS), 0, stream, a)
 #define DG_ONEBIT(WN, KS) \
     do { \
@@ -397,4 +546,31 @@ dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t st
 #undef DG_ONEBIT
 #undef DG_ONEBIT_FORM
     return dg_check_launch("onebit_kernel");
+}
+
+// p.Xp: codes one per byte.  AUTO, where it would run a one-hot kernel that packs while loading: from 140 tiles of 64 x 128 up, of 60 such layers, us,
+// that kernel, this one (inputs changing from pass to pass): 56x56x64 -> 40 3x3 stride 2 at batch 25 (154 tiles) 10.8, 8.7; 112x112x64 -> 48 3x3 at
+// batch 7 (686) 17.1, 10.8; 14x14x192 -> 280 3x3 at batch 23 (180) 14.6, 13.5; below, 112x112x128 -> 64 3x3 (98) 8.3, 9.3; 28x28x320 -> 88 3x3 stride 2
+// at batch 31 (96) 15.2, 17.9.  Not in place of the one with stationary weights, whose loads run ahead of its stores: 56x56x256 -> 64 at
+// batch 32 8.6, 8.2 with the input in L2, but 9.4, 10.4 from the last-level cache.
+// DG_ONEBIT_CODES: 0 never, 1 wherever a kernel packs while loading.
+bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stationary)
+{
+    const char *f = dg_override("DG_ONEBIT_CODES");
+    if (f ? atoi(f) == 0 : stationary || tiles_of(p, 1) < 140) return false;
+    if (!f && (dg_override("DG_ONEHOT_PLAN") || dg_override("DG_ONEHOT_WAVES") || dg_override("DG_ONEHOT_CODES_TILED"))) return false;
+    if (!takes(lut, p) || p.stride_cm != 1 || p.Qp) return false;
+    return (int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * p.Cin < (int64_t)1 << 31;                   // (32-bit byte offsets)
+}
+
+dg_status dg_launch_onebit_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
+{
+    OneBitArgs a;
+    fill(lut, p, OneBitPlan{1, 1, ((int64_t)p.N + 127) / 128}, &a);
+    a.div_cpt = make_div((uint32_t)(p.Cin / 16));
+    a.x_bytes = (uint32_t)((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * p.Cin);
+    const dim3 grid(a.wide);
+    if (p.KH * p.KW > 1) hipLaunchKernelGGL((onebit_codes_kernel<true>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((onebit_codes_kernel<false>), grid, dim3(256), 0, stream, a);
+    return dg_check_launch("onebit_codes_kernel");
 }

@@ -54,6 +54,30 @@ def test_onebit_kernel(plan, monkeypatch):
                 assert np.array_equal(view(out.cpu().numpy()), w), ((M, N, K), strides, s is not None)
 
 
+def test_onebit_kernel_on_unpacked_codes(monkeypatch):
+    """The same from codes one per byte, whose higher bits count for nothing; the work buffer is left alone."""
+    monkeypatch.setenv("DG_ONEBIT_CODES", "1")
+    for i, (B, H, W, Cin, Cout, KH, KW, stride, pad) in enumerate(CONVS + [(1, 12, 30, 256, 70, 1, 1, (1, 1), (0, 0)), (1, 12, 30, 64, 64, 1, 1, (1, 1), (0, 0)),
+                                                                           (16, 56, 56, 256, 72, 1, 1, (1, 1), (0, 0)), (8, 28, 28, 512, 96, 1, 1, (1, 1), (0, 0))]):
+        if KH * KW * Cin > 3072:                            # (two kernels)
+            continue
+        lw, la = TABLES[i % len(TABLES)]
+        lut = dg.dg_build_lut(lw, la, dg.DG_LUT_I16)
+        c = wl.small_conv(B, H, W, Cin, Cout, KH, KW, stride, pad, seed=H + Cin, scale=True)
+        desc = dg.conv_desc(B, H, W, Cin, Cout, KH, KW, stride, pad)
+        assert dg.dg_conv_codes_kernel_name(lut, desc).startswith("codes_onehot"), i
+        scale = torch.from_numpy(c.scale).cuda()
+        high = torch.randint(0, 64, (c.Ac.size,), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(i)) * 4
+        X = torch.from_numpy(c.Ac).cuda().reshape(-1) + high
+        Wp = dg.dg_pack_weights(torch.from_numpy(c.Wc).cuda(), Cout, KH * KW * Cin)
+        work = torch.full((B * H * W * Cin // 4,), 77, dtype=torch.uint8, device="cuda")
+        want = oracle.conv2d(c.Wc, c.Ac, lw, la, stride=stride, pad=pad)
+        assert np.array_equal(dg.dg_conv2d_lut_codes(lut, Wp, X, desc, work=work).cpu().numpy(), want), (i, "int32")
+        got = dg.dg_conv2d_lut_codes(lut, Wp, X, desc, work=work, scale=scale).cpu().numpy()
+        assert np.array_equal(got, oracle.scale_epilogue_nhwc(want, c.scale)), (i, "scaled")
+        assert bool((work == 77).all()), i
+
+
 def test_sums_to_the_end_of_the_range(monkeypatch):
     """Sums of every magnitude up to the largest that is taken, 3 * 4 * K just below 2^24, in steps of the smallest entry: exact."""
     M, N, K = 64, 40, 1398016
