@@ -38,6 +38,19 @@ using namespace dgoh;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
+// Sums to results: 4 f times a sum, which is whole once it is four times as large.
+__device__ __forceinline__ v16i results(const f32x16 &sums, int32_t factor)
+{
+    v16i out;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) out[e] = (int)(sums[e] * 4.0f);
+    if (factor != 1) {                                      // (uniform; a 32-bit product is 16 cycles)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) out[e] *= factor;
+    }
+    return out;
+}
+
 struct OneBitArgs {
     DgProblem p;
     uint32_t numbers;        // byte w: N[w] as FP4
@@ -216,7 +229,6 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
         multiply(t[0]);
         multiply(t[1]);
     }
-    auto result = [&](float sum) { return (int)(sum * 4.0f) * a.factor; };
     dg_wait_for_loads();                                    // (fetches past the end: their LDS writes end before the wavefront does)
 
     if constexpr (KS > 1) {
@@ -231,13 +243,13 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
                 mine[(4 * bm + q) * 64] = make_float4(acc[bm][0][4 * q], acc[bm][0][4 * q + 1], acc[bm][0][4 * q + 2], acc[bm][0][4 * q + 3]);
         __syncthreads();
         const float4 *const theirs = (const float4 *)s_mem + w4 * 512 + ks * 256 + lane;
-        v16i out;
+        f32x16 sums;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const float4 x = theirs[q * 64], y = theirs[2048 + q * 64];
-            out[4 * q] = result(x.x + y.x), out[4 * q + 1] = result(x.y + y.y);
-            out[4 * q + 2] = result(x.z + y.z), out[4 * q + 3] = result(x.w + y.w);
+            sums[4 * q] = x.x + y.x, sums[4 * q + 1] = x.y + y.y, sums[4 * q + 2] = x.z + y.z, sums[4 * q + 3] = x.w + y.w;
         }
+        const v16i out = results(sums, a.factor);
         dg_mfma_store_block<TR, true, DG_OUT_BY_PROBLEM>(p, out, m0 + ks * 32, n0, lane, ks ? sc_cols[1] : sc_cols[0]);
         return;
     }
@@ -245,9 +257,7 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
     for (int bm = 0; bm < 2; ++bm)
 #pragma unroll
         for (int bn = 0; bn < WN; ++bn) {
-            v16i out;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) out[e] = result(acc[bm][bn][e]);
+            const v16i out = results(acc[bm][bn], a.factor);
             dg_mfma_store_block<TR, true, DG_OUT_BY_PROBLEM>(p, out, m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
         }
 }
@@ -393,9 +403,7 @@ onebit_codes_kernel(OneBitArgs a)
     dg_wait_for_loads();                                    // (fetches past the end: their LDS writes end before the wavefront does)
 #pragma unroll
     for (int bm = 0; bm < 2; ++bm) {
-        v16i out;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) out[e] = (int)(acc[bm][e] * 4.0f) * a.factor;
+        const v16i out = results(acc[bm], a.factor);
         dg_mfma_store_block<true, true, DG_OUT_BY_PROBLEM>(p, out, m0 + bm * 32, n0, lane, sc_cols[bm]);
     }
 }
