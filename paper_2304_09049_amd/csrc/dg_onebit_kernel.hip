@@ -262,15 +262,15 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
         }
 }
 
-// WN > 1: the last workgroups take narrow tiles (onebit_plan).
+// WN = 2: the last workgroups may take narrow tiles (onebit_plan).
 template <int WN, int KS, bool TAPS, bool TR>
 __global__ void __launch_bounds__(256 * KS, 2)
 onebit_kernel(OneBitArgs a)
 {
     __shared__ uint4 s_mem[KS * (16384 + WN * 16384) / 16];
     dg_fetch_arguments<sizeof(a)>();
-    if (WN > 1 && blockIdx.x >= a.wide) onebit_tile<1, 1, TAPS, TR>(a, s_mem, blockIdx.x - a.wide, gridDim.x - a.wide, 1);
-    else onebit_tile<WN, KS, TAPS, TR>(a, s_mem, blockIdx.x, WN > 1 ? a.wide : gridDim.x, 0);
+    if (WN == 2 && blockIdx.x >= a.wide) onebit_tile<1, 1, TAPS, TR>(a, s_mem, blockIdx.x - a.wide, gridDim.x - a.wide, 1);
+    else onebit_tile<WN, KS, TAPS, TR>(a, s_mem, blockIdx.x, WN == 2 ? a.wide : gridDim.x, 0);
 }
 
 // The same from activations that are still one code per byte (p.Xp = those bytes): 64 channels x 4 x 32 pixels, runs of 128 positions.  Nothing is
@@ -450,14 +450,15 @@ struct OneBitPlan {
 
 int64_t tiles_of(const DgProblem &p, int wn) { return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 128 * wn - 1) / (128 * wn)); }
 
-// DG_ONEBIT: 0 never, 1, 2, 4 this kernel with WN so large, 12 with WN = 1 and KS = 2, 21 and 41 half of the pixels in narrow tiles, whatever the size.
+// DG_ONEBIT: 0 never, 1, 2, 4 this kernel with WN so large, 12 with WN = 1 and KS = 2, 21 with WN = 2 and half of the pixels in narrow tiles, whatever the
+// size.
 OneBitPlan onebit_plan(const DgProblem &p)
 {
     const int64_t units = dg_simd_count() / 4, runs = ((int64_t)p.K + 255) / 256, t1 = tiles_of(p, 1), tm = ((int64_t)p.M + 63) / 64;
     auto columns = [&](int wn) { return ((int64_t)p.N + 128 * wn - 1) / (128 * wn); };
     if (const char *f = dg_override("DG_ONEBIT")) {
         const int v = atoi(f);
-        if (v > 20) return OneBitPlan{v / 10, 1, columns(v / 10) / 2};
+        if (v == 21) return OneBitPlan{2, 1, columns(2) / 2};
         return OneBitPlan{v == 12 ? 1 : v, v == 12 ? 2 : 1, columns(v == 12 ? 1 : v)};
     }
     // A tile twice (four times) as wide costs 1.82 (3.55) times as much per run on a busy compute unit, so the plan is the one that
@@ -465,8 +466,8 @@ OneBitPlan onebit_plan(const DgProblem &p)
     // (1274, 638) 16.7, 18.1; 56x56x256 -> 112 3x3 at batch 28 (1372, 686) 28.3, 25.2.  Few runs do not pay for a wide tile's longer end:
     // 6648 x 2359 x 832 22.1, 25.2; the widest wants nine: 1986 x 7254 x 6272 83.7, 78.3, 74.9, 8192-cube 402, 367, 356, 112x112x128 -> 120 3x3 at
     // batch 25 60.2, 54.7, 59.4.  Rounds of wide tiles that would leave compute units idle in the last one end in narrow tiles: 56x56x256 -> 256
-    // 3x3 at batch 16 (392 tiles of 512 pixels on 256 compute units) 32.4, as 256 and 544 of 128 pixels 30.8; 112x112x128 -> 112 3x3 at batch 18
-    // 42.4, 39.4; 3200 x 6400 x 2304 42.9, 40.4.
+    // 3x3 at batch 16 (784 tiles on 256 compute units) 35.1, as 768 and 32 narrow ones 31.1; 112x112x128 -> 112 3x3 at batch 18 42.4, 39.4; 3200 x 6400 x
+    // 2304 42.9, 40.4.  Not the widest: the first as 256 of 512 pixels and 544 narrow ones was 3 us longer than that.
     if (t1 <= units) return OneBitPlan{1, runs >= 8 ? 2 : 1, columns(1)};
     OneBitPlan q = {1, 1, columns(1)};
     double best = (double)((t1 + units - 1) / units);
@@ -475,7 +476,7 @@ OneBitPlan onebit_plan(const DgProblem &p)
         const double c = all <= units ? 4.1 : cost * ((all + units - 1) / units);          // (a lone wavefront per SIMD is slower: WN = 4)
         if (c < best) best = c, q = OneBitPlan{wn, 1, columns(wn)};
         const int64_t rest = p.N - whole * 128 * wn;
-        if (whole > 0 && rest > 0) {
+        if (wn == 2 && whole > 0 && rest > 0) {
             const double mixed = cost * (all / units) + (double)((tm * ((rest + 127) / 128) + units - 1) / units);
             if (mixed < best) best = mixed, q = OneBitPlan{wn, 1, whole};
         }
