@@ -63,6 +63,7 @@ struct DgProblem {
 // batch 32 8.6, 9.9; one-bit tables 112x112x64 -> 96 3x3 at batch 12 20.4, 22.5.
 inline int32_t dg_output_cached(const DgProblem &p)
 {
+    if (p.Qp) return 0;                                     // (packed codes, bytes)
     const int64_t row = p.stride_cm == 1 ? p.stride_cn : p.stride_cm;
     return row % 16 != 0 || (p.scale ? (uintptr_t)p.Cf : (uintptr_t)p.C) % 64 != 0;
 }

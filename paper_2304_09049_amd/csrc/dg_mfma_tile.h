@@ -191,14 +191,23 @@ __device__ __forceinline__ void dg_mfma_store_quads(const DgProblem &p, const dg
     }
 }
 
-// Store the (WM*32) x (WN*32) tile at (m0, n0).
+// Store the (WM*32) x (WN*32) tile at (m0, n0).  (How, decided once for the tile: a branch in each of 14 blocks is more than the compiler unrolls.)
 template <int WM, int WN, bool TR, bool EDGE_COLUMNS = false, DgOut OUT = DG_OUT_STREAM>
 __device__ __forceinline__ void dg_mfma_store_tile(const DgProblem &p, const dg_v16i (&acc)[WM][WN], int m0, int n0,
                                                    int lane, const float (&sc_cols)[WM])
 {
+    if (OUT == DG_OUT_BY_PROBLEM && p.cached) {             // (uniform)
+#pragma unroll
+        for (int bm = 0; bm < WM; ++bm)
+#pragma unroll
+            for (int bn = 0; bn < WN; ++bn)
+                dg_mfma_store_sums<TR, EDGE_COLUMNS, DG_OUT_CACHED>(p, acc[bm][bn], m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
+        return;
+    }
 #pragma unroll
     for (int bm = 0; bm < WM; ++bm)
 #pragma unroll
         for (int bn = 0; bn < WN; ++bn)
-            dg_mfma_store_block<TR, EDGE_COLUMNS, OUT>(p, acc[bm][bn], m0 + bm * 32, n0 + bn * 32, lane, sc_cols[bm]);
+            dg_mfma_store_block<TR, EDGE_COLUMNS, OUT == DG_OUT_CACHED ? DG_OUT_CACHED : DG_OUT_STREAM>(p, acc[bm][bn], m0 + bm * 32, n0 + bn * 32,
+                                                                                                          lane, sc_cols[bm]);
 }

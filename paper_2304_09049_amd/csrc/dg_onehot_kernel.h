@@ -418,6 +418,7 @@ onehot_mfma_kernel(Args a)
                   "code widths 2, 3, 4; 0 = the decode comparison; 20 = 2-bit codes on the sparse instruction, 24 = 4-bit slots as two");
     static_assert(!F::SPARSE || (TR && !TWO), "the sparse operand is the MFMA's row operand: activations on the rows");
     constexpr int RB = TWO ? 1 : WM;                       // weight row blocks of 32 rows
+    constexpr DgOut HOW = F::DECODE ? DG_OUT_STREAM : DG_OUT_BY_PROBLEM;      // (the comparison's 128 x 128 tile has no registers for the choice)
     constexpr int WRUNS = F::SPARSE ? 2 : 1;               // runs of CH words a weight lane reads: its half's, or both
     __shared__ uint2 s_rows[F::SPARSE ? 16 : 1];            // the sparse form's table of row pairs, one for the workgroup
     constexpr int TPW = 4 / SKW;                           // tiles per workgroup
@@ -682,7 +683,7 @@ onehot_mfma_kernel(Args a)
             for (int e = 0; e < 16; ++e)
                 out[bm][bn][e] = TWO ? (int)((uint32_t)acc[0][bn][e] + ((uint32_t)acc[WM - 1][bn][e] << 8)) : acc[bm][bn][e];
     if (SKW == 1) {
-        dg_mfma_store_tile<RB, WN, TR, false, DG_OUT_BY_PROBLEM>(p, out, m0, n0, lane, sc_cols);
+        dg_mfma_store_tile<RB, WN, TR, false, HOW>(p, out, m0, n0, lane, sc_cols);
         return;
     }
     int32_t *sums = s_acc + tw * (NB * 1024);
@@ -700,7 +701,7 @@ onehot_mfma_kernel(Args a)
         v16i blk;
 #pragma unroll
         for (int e = 0; e < 16; ++e) blk[e] = sums[(i * 16 + e) * 64 + lane];
-        dg_mfma_store_block<TR, false, DG_OUT_BY_PROBLEM>(p, blk, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane, sc_cols[i / WN]);
+        dg_mfma_store_block<TR, false, HOW>(p, blk, m0 + (i / WN) * 32, n0 + (i % WN) * 32, lane, sc_cols[i / WN]);
     }
 }
 

@@ -78,6 +78,24 @@ def test_onebit_kernel_on_unpacked_codes(monkeypatch):
         assert bool((work == 77).all()), i
 
 
+def test_tables_of_other_forms_stay_with_the_general_kernels(monkeypatch):
+    """A level that FP4 does not have, activation levels that are not evenly spaced from zero: taken whole, with the kernel above forced;
+    and a table given entry by entry that is of its form."""
+    monkeypatch.setenv("DG_ONEBIT", "1")
+    B, H, W, Cin, Cout = 1, 15, 17, 128, 68
+    c = wl.small_conv(B, H, W, Cin, Cout, 3, 3, (1, 1), (1, 1), seed=3)
+    desc = dg.conv_desc(B, H, W, Cin, Cout, 3, 3, (1, 1), (1, 1))
+    Wp = dg.dg_pack_weights(torch.from_numpy(c.Wc).cuda(), Cout, 9 * Cin)
+    Xp = dg.dg_pack_activations(torch.from_numpy(c.Ac).cuda(), B * H * W, Cin)
+    for lw, la in (((-2, 5, 0, 1), (0, 1, 2, 3)), ((-2, -1, 0, 1), (1, 2, 3, 4)), ((-2, -1, 0, 1), (0, 1, 2, 4)), ((-2, -1, 0, 1), (0, 1, 3, 4)),
+                   ((-2, -1, 0, 1), (0, 2, 1, 3)), ((-7, 7, 14, 1), (0, 1, 2, 3))):
+        got = dg.dg_conv2d_lut(dg.dg_build_lut(lw, la), Wp, Xp, desc).cpu().numpy()
+        assert np.array_equal(got, oracle.conv2d(c.Wc, c.Ac, lw, la, stride=(1, 1), pad=(1, 1))), (lw, la)
+    lw, la = (-3, -1, 1, 3), (0, 1, 2, 3)
+    lut = dg.dg_build_lut_entries([w * a for w in lw for a in la])
+    assert np.array_equal(dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy(), oracle.conv2d(c.Wc, c.Ac, lw, la, stride=(1, 1), pad=(1, 1)))
+
+
 def test_sums_to_the_end_of_the_range(monkeypatch):
     """Sums of every magnitude up to the largest that is taken, 3 * 4 * K just below 2^24, in steps of the smallest entry: exact."""
     M, N, K = 64, 40, 1398016
