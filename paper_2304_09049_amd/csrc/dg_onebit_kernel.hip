@@ -499,7 +499,7 @@ bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p)
 {
     const char *f = dg_override("DG_ONEBIT");
     const int64_t t1 = tiles_of(p, 1);
-    if (f ? atoi(f) == 0 : t1 < 35) return false;
+    if (f ? atoi(f) == 0 : t1 < 35 || 2.0 * (double)p.M * (double)p.N * (double)p.K < 1.5e9) return false;       // (smaller ones: not measured ahead)
     if (!takes(lut, p)) return false;
     if (f) return true;
     if (dg_override("DG_ONEHOT_PLAN") || dg_override("DG_ONEHOT_WAVES")) return false;
