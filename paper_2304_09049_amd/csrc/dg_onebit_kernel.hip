@@ -70,6 +70,27 @@ __device__ __forceinline__ f32x16 fp4_step(const v4i &a, const v4i &b, f32x16 c)
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, c, 4, 4, 0, 0, 0, 0);
 }
 
+// Where pixel n's row of bytes begins, and, with a filter window, which of its taps lie outside the image (bit t, tap t).  Without a window a
+// pixel outside begins at byte 2^31, beyond any buffer taken here and still beyond it a row of K on.  (Its own offset with the top bit set is not:
+// from just under 2^31 such a row wraps to the buffer's first bytes.)
+template <bool TAPS>
+__device__ __forceinline__ void place_pixel(const OneBitArgs &a, int n, int bytes_per_pixel, uint32_t &off0, uint32_t &outside)
+{
+    const DgProblem &p = a.p;
+    const Column c = make_column(p, a.div_ow, a.div_oh, n, bytes_per_pixel, 0);
+    const int h0 = max(0, -c.ih0), h1 = c.ok ? min(p.KH, p.H - c.ih0) : 0, c0 = max(0, -c.iw0), c1 = min(p.KW, p.W - c.iw0);
+    off0 = (uint32_t)c.off0;
+    if constexpr (TAPS) {
+        const uint32_t columns = c1 > c0 ? (~0u >> (32 - (c1 - c0))) << c0 : 0u;
+        uint32_t in = 0;
+        for (int kh = 0; kh < p.KH; ++kh) in |= kh >= h0 && kh < h1 ? columns << (kh * p.KW) : 0u;
+        outside = ~in;
+    } else if (!(h1 > h0 && c1 > c0)) {
+        off0 = 0x80000000u;
+    }
+    asm("" : "+v"(off0));                                   // (kept, not worked out again for each load)
+}
+
 // One tile: 64 channels, 4 x 32 WN pixels.
 //
 // KS = 2: eight wavefronts, two to a tile, each with half of K; their sums meet in LDS.  TAPS: a filter window.  TR: channels on the
@@ -127,22 +148,9 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
     // ---- pixels: lane l of a load fetches segment (l % 4) ^ (row / 4 % 4) of row l / 4 of 16: a segment's 16 rows lie on 16 places of the banks
     const v4i x_buffer = dg_buffer(p.Xp, a.x_bytes);
     const int l_row = lane >> 2, l_seg = (lane & 3) ^ (lane >> 4);
-    uint32_t off0[LOADS], outside[TAPS ? LOADS : 1];       // outside: bit t, filter tap t lies outside the image
+    uint32_t off0[LOADS], outside[TAPS ? LOADS : 1];       // (place_pixel)
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-        const Column c = make_column(p, a.div_ow, a.div_oh, n0 + 16 * i + l_row, cq, 0);
-        off0[i] = (uint32_t)c.off0;
-        asm("" : "+v"(off0[i]));                            // (kept, not worked out again for each load)
-        const int h0 = max(0, -c.ih0), h1 = c.ok ? min(p.KH, p.H - c.ih0) : 0, c0 = max(0, -c.iw0), c1 = min(p.KW, p.W - c.iw0);
-        const uint32_t columns = c1 > c0 ? (~0u >> (32 - (c1 - c0))) << c0 : 0u;
-        if constexpr (TAPS) {
-            uint32_t in = 0;
-            for (int kh = 0; kh < p.KH; ++kh) in |= kh >= h0 && kh < h1 ? columns << (kh * p.KW) : 0u;
-            outside[i] = ~in;
-        } else {
-            off0[i] |= h1 > h0 && c1 > c0 ? 0u : 0x80000000u;
-        }
-    }
+    for (int i = 0; i < LOADS; ++i) place_pixel<TAPS>(a, n0 + 16 * i + l_row, cq, off0[i], outside[TAPS ? i : 0]);
     const uint32_t x_lds = dg_lds_address(mem) + 2 * WEIGHTS + w4 * 2 * PIXELS;
     auto fetch = [&](int g, int odd) {
         const uint32_t dst = x_lds + odd * PIXELS;
@@ -326,20 +334,7 @@ onebit_codes_kernel(OneBitArgs a)
     const int l_row = lane >> 3, l_piece = (lane & 7) ^ l_row;
     uint32_t off0[4], outside[TAPS ? 4 : 1];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const Column c = make_column(p, a.div_ow, a.div_oh, n0 + 8 * i + l_row, p.Cin, 0);
-        off0[i] = (uint32_t)c.off0;
-        asm("" : "+v"(off0[i]));
-        const int h0 = max(0, -c.ih0), h1 = c.ok ? min(p.KH, p.H - c.ih0) : 0, c0 = max(0, -c.iw0), c1 = min(p.KW, p.W - c.iw0);
-        const uint32_t columns = c1 > c0 ? (~0u >> (32 - (c1 - c0))) << c0 : 0u;
-        if constexpr (TAPS) {
-            uint32_t in = 0;
-            for (int kh = 0; kh < p.KH; ++kh) in |= kh >= h0 && kh < h1 ? columns << (kh * p.KW) : 0u;
-            outside[i] = ~in;
-        } else {
-            off0[i] |= h1 > h0 && c1 > c0 ? 0u : 0x80000000u;
-        }
-    }
+    for (int i = 0; i < 4; ++i) place_pixel<TAPS>(a, n0 + 8 * i + l_row, p.Cin, off0[i], outside[TAPS ? i : 0]);
     const uint32_t x_lds = dg_lds_address(s_mem) + 2 * WEIGHTS + w4 * 2 * PIXELS;
     auto fetch = [&](int g, int odd) {
         const uint32_t dst = x_lds + odd * PIXELS;

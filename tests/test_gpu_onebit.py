@@ -113,3 +113,22 @@ def test_sums_to_the_end_of_the_range(monkeypatch):
     for plan in ("1", "12"):
         monkeypatch.setenv("DG_ONEBIT", plan)
         assert np.array_equal(dg.dg_gemm_lut(lut, Wp, Ap, M, N, K).cpu().numpy(), want), plan
+
+
+@pytest.mark.parametrize("codes", [False, True])
+def test_padding_pixel_at_the_end_of_the_32_bit_offsets(codes, monkeypatch):
+    """A padded 1x1 layer whose pixels below the image would lie just under byte 2^31: every output is padding, hence zero, wherever in the
+    pixel's row the piece of K lies."""
+    monkeypatch.setenv("DG_ONEBIT_CODES" if codes else "DG_ONEBIT", "1")
+    Cin, Cout, W = 192, 64, 5592405 if codes else 22369621
+    used = 2 * W * (Cin if codes else Cin // 4)
+    assert 2 ** 31 - Cin < used < 2 ** 31
+    lut = dg.dg_build_lut((-2, -1, 0, 1), (0, 1, 2, 3))
+    desc = dg.conv_desc(1, 2, W, Cin, Cout, 1, 1, (3, W), (1, 0))           # rows -1 and 2 of two, column 0
+    Wp = torch.zeros(Cout * Cin // 4, dtype=torch.uint8, device="cuda")
+    X = torch.full((used,), 255, dtype=torch.uint8, device="cuda")
+    if codes:
+        got = dg.dg_conv2d_lut_codes(lut, Wp, X, desc, work=torch.empty(used // 4, dtype=torch.uint8, device="cuda"))
+    else:
+        got = dg.dg_conv2d_lut(lut, Wp, X, desc)
+    assert got.shape == (1, 2, 1, Cout) and not got.any()
