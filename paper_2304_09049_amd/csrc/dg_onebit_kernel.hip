@@ -29,6 +29,7 @@
 #include "dg_onehot_kernel.h"
 
 #include <cstdlib>
+#include <cstring>
 #include <numeric>
 
 namespace {
@@ -446,16 +447,24 @@ struct OneBitPlan {
 int64_t tiles_of(const DgProblem &p, int wn) { return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 128 * wn - 1) / (128 * wn)); }
 
 // DG_ONEBIT: 0 never, 1, 2, 4 this kernel with WN so large, 12 with WN = 1 and KS = 2, 21 with WN = 2 and half of the pixels in narrow tiles, whatever the
-// size.
+// size; -1 where it is not set, or to anything else.
+int onebit_override()
+{
+    static const char *const names[] = {"0", "1", "2", "4", "12", "21"};
+    if (const char *f = dg_override("DG_ONEBIT"))
+        for (const char *name : names)
+            if (strcmp(f, name) == 0) return atoi(name);
+    return -1;
+}
+
 OneBitPlan onebit_plan(const DgProblem &p)
 {
     const int64_t units = dg_simd_count() / 4, runs = ((int64_t)p.K + 255) / 256, t1 = tiles_of(p, 1), tm = ((int64_t)p.M + 63) / 64;
     auto columns = [&](int wn) { return ((int64_t)p.N + 128 * wn - 1) / (128 * wn); };
-    if (const char *f = dg_override("DG_ONEBIT")) {
-        const int v = atoi(f);
-        if (v == 21) return OneBitPlan{2, 1, columns(2) / 2};
-        return OneBitPlan{v == 12 ? 1 : v, v == 12 ? 2 : 1, columns(v == 12 ? 1 : v)};
-    }
+    const int forced = onebit_override();
+    if (forced == 21) return OneBitPlan{2, 1, columns(2) / 2};
+    if (forced == 12) return OneBitPlan{1, 2, columns(1)};
+    if (forced > 0) return OneBitPlan{forced, 1, columns(forced)};
     // A tile twice (four times) as wide costs 1.82 (3.55) times as much per run on a busy compute unit, so the plan is the one that
     // leaves the busiest the least: 112x112x128 -> 128 3x3 at batch 10 (1960, 980, 490 tiles) 24.2, 22.7, 25.0 us; 56x56x128 -> 112 3x3 at batch 26
     // (1274, 638) 16.7, 18.1; 56x56x256 -> 112 3x3 at batch 28 (1372, 686) 28.3, 25.2.  Few runs do not pay for a wide tile's longer end:
@@ -492,11 +501,11 @@ OneBitPlan onebit_plan(const DgProblem &p)
 // 6.2, re-quantising between other layers 0.4 us longer here; the direct-load kernels from 35: 738 x 360 x 5568 (36) 15.3 against 12.2.
 bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p)
 {
-    const char *f = dg_override("DG_ONEBIT");
+    const int forced = onebit_override();
     const int64_t t1 = tiles_of(p, 1);
-    if (f ? atoi(f) == 0 : t1 < 35 || 2.0 * (double)p.M * (double)p.N * (double)p.K < 1.5e9) return false;       // (smaller ones: not measured ahead)
+    if (forced >= 0 ? forced == 0 : t1 < 35 || 2.0 * (double)p.M * (double)p.N * (double)p.K < 1.5e9) return false;       // (smaller ones: not measured ahead)
     if (!takes(lut, p)) return false;
-    if (f) return true;
+    if (forced > 0) return true;
     if (dg_override("DG_ONEHOT_PLAN") || dg_override("DG_ONEHOT_WAVES")) return false;
     return t1 >= 130 || !dg_sparse_is_staged(lut, p);
 }

@@ -132,3 +132,17 @@ def test_padding_pixel_at_the_end_of_the_32_bit_offsets(codes, monkeypatch):
     else:
         got = dg.dg_conv2d_lut(lut, Wp, X, desc)
     assert got.shape == (1, 2, 1, Cout) and not got.any()
+
+
+@pytest.mark.parametrize("value", ["3", "8", "-1", "", "1x"])
+def test_override_values_that_are_none(value, monkeypatch):
+    """Values that DG_ONEBIT does not have count as not set: the whole output is written."""
+    monkeypatch.setenv("DG_ONEBIT", value)
+    lw, la = TABLES[0]
+    c = wl.small_conv(2, 20, 13, 64, 132, 3, 3, (1, 1), (1, 1), seed=7)
+    desc = dg.conv_desc(2, 20, 13, 64, 132, 3, 3, (1, 1), (1, 1))
+    Wp = dg.dg_pack_weights(torch.from_numpy(c.Wc).cuda(), 132, 9 * 64)
+    Xp = dg.dg_pack_activations(torch.from_numpy(c.Ac).cuda(), 2 * 20 * 13, 64)
+    out = torch.full((2, 20, 13, 132), 1 << 30, dtype=torch.int32, device="cuda")
+    dg.dg_conv2d_lut(dg.dg_build_lut(lw, la), Wp, Xp, desc, out=out)
+    assert np.array_equal(out.cpu().numpy(), oracle.conv2d(c.Wc, c.Ac, lw, la, stride=(1, 1), pad=(1, 1)))
