@@ -19,8 +19,9 @@ latency, not the kernel.)
 `roofline` (headline) and every `sweep` row price the kernel's EFFECTIVE work -- 2*M*N*K table operations (one
 lookup and one add per product) and the algorithmic bytes -- against the ceiling that binds the shape:
 t_roof = max(bytes / 8 TB/s, 2MNK / 5 POPS), frac = t_roof / t_kernel.  The int8 multiply-accumulates the matrix
-cores actually perform (4 per product when selecting with one-hot operands, 2 on the sparse instruction) are
-reported apart as `mfma_pipe_frac`: pipe utilisation, not a roofline fraction.
+cores actually perform (4 per product when selecting with one-hot operands, 2 on the sparse instruction; selecting by
+single bits 2 FP4 ones, counted as 1 for that instruction's twice as high peak) are reported apart as `mfma_pipe_frac`:
+pipe utilisation, not a roofline fraction.
 """
 from __future__ import annotations
 
@@ -249,7 +250,10 @@ def mfma_ops_factor(name):
     """int8 multiply-accumulates the matrix cores perform per effective operation: the one-hot kernel contracts over 4K
     (one operand byte per table column); on the sparse instruction, which skips the half of them that its index says
     are zero, over 2K (priced against the DENSE peak all the same); the decode-and-multiply comparison kernel over K;
-    table kernels on the VALU issue none."""
+    the kernel for tables that are two one-bit lookups over 2K on the FP4 instruction, which has twice the int8 peak, so
+    it counts as K here; table kernels on the VALU issue none."""
+    if name.startswith("onebit_") or name.startswith("codes_onebit_"):
+        return 1
     if name.startswith("onehot_mfma") or name.startswith("codes_onehot_mfma"):
         return 4
     if name.startswith("onehot_smfmac") or name.startswith("smfmac_"):
@@ -290,7 +294,8 @@ def roofline_object(w, ms, name):
             "frac": round(ach / INT8_MFMA_PEAK_TOPS, 5), **common,
             "note": "effective table operations (2MNK) against the dense int8 peak; selecting with one-hot operands "
                     "performs 4 (dense instruction) or 2 (sparse instruction) multiply-accumulates per product, so "
-                    "0.25 / 0.5 is the most a table kernel can reach on this ceiling"}
+                    "0.25 / 0.5 is the most such a kernel can reach on this ceiling, and 1 where the table is two one-bit lookups (2, "
+                    "on the FP4 instruction at twice the rate)"}
 
 
 def kernel_report(w, ms, name):

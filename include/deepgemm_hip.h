@@ -352,9 +352,7 @@ dg_status dg_conv2d_lut_requant(const dg_lut *lut, const void *Wp_dev, const voi
 dg_status dg_launch_empty(int64_t blocks, int32_t threads, void *hip_stream);
 
 /* Name of the kernel that AUTO would pick (or that `variant` maps to) for this GEMM / convolution
- * shape; static storage.  For reports only: it names AUTO's plan for the shape.  A "onehot_smfmac_<tile>" or "onehot_mfma_<tile>"
- * plan of AUTO's runs tables that are two one-bit lookups (2-bit activation levels 0, d, 2d, 3d) on the FP4 matrix instruction, in
- * tiles of its own, where there are many; the results are the same. */
+ * shape; static storage.  For reports only. */
 const char *dg_gemm_kernel_name(const dg_lut *lut, int64_t M, int64_t N, int64_t K,
                                 dg_kernel variant);
 const char *dg_conv_kernel_name(const dg_lut *lut, const dg_conv_desc *desc, dg_kernel variant);

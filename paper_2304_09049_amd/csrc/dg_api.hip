@@ -297,9 +297,10 @@ int64_t dg_conv_out_dim(int64_t in, int64_t k, int64_t stride, int64_t pad)
 
 namespace {
 
-enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Ragged, Staged2p, OneHotF32, Unsupported };
+enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Ragged, Staged2p, OneHotF32, OneBit, Unsupported };
 
-Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
+// The kernel for tables of any form; pick_kernel below looks at the table's.
+Pick pick_general(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
 {
     // binary32 tables run on their own matrix-core kernel and on the plain LDS kernel; 3- and 4-bit tables on the one-hot matrix-core kernel or the LDS kernel
     if (lut->dtype == DG_LUT_F32 && variant == DG_KERNEL_AUTO && dg_onehot_f32_preferred(lut, p)) return Pick::OneHotF32;
@@ -350,13 +351,17 @@ Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     return Pick::Unsupported;
 }
 
+// In place of AUTO's tiled one-hot kernels, tables that are two one-bit lookups run on a kernel of their own.
+Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
+{
+    const Pick pick = pick_general(lut, p, variant);
+    if (variant == DG_KERNEL_AUTO && (pick == Pick::Sparse || pick == Pick::OneHot) && dg_onebit_preferred(lut, p)) return Pick::OneBit;
+    return pick;
+}
+
 dg_status run(const dg_lut *lut, const DgProblem &p, dg_kernel variant, hipStream_t stream)
 {
-    const Pick pick = pick_kernel(lut, p, variant);
-    // (AUTO's plans on the one-hot kernels: tables of a narrower form run on a kernel of their own, whatever the plan's name says)
-    if (variant == DG_KERNEL_AUTO && (pick == Pick::Sparse || pick == Pick::OneHot) && dg_onebit_preferred(lut, p))
-        return dg_launch_onebit(lut, p, stream);
-    switch (pick) {
+    switch (pick_kernel(lut, p, variant)) {
     case Pick::Perm: return dg_launch_perm(lut, p, stream);
     case Pick::Lds: return dg_launch_lds(lut, p, stream);
     case Pick::LdsF32: return dg_launch_lds_f32(lut, p, stream);
@@ -373,6 +378,7 @@ dg_status run(const dg_lut *lut, const DgProblem &p, dg_kernel variant, hipStrea
     case Pick::SparseWs: return dg_launch_sparse_ws(lut, p, stream);
     case Pick::FewN: return dg_launch_fewn(lut, p, stream);
     case Pick::Ragged: return dg_launch_ragged(lut, p, false, stream);
+    case Pick::OneBit: return dg_launch_onebit(lut, p, stream);
     case Pick::Unsupported: break;
     }
     return dg_fail(DG_ERR_UNSUPPORTED,
@@ -399,6 +405,7 @@ const char *pick_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Pick::SparseWs: return "onehot_smfmac_ws_32xK";
     case Pick::FewN: return "onehot_smfmac_fewn_16";
     case Pick::Ragged: return dg_ragged_config_name(lut, p, false);
+    case Pick::OneBit: return dg_onebit_config_name(p);
     case Pick::Unsupported: break;
     }
     return "unsupported";
@@ -522,7 +529,7 @@ namespace {
 // the library's own choice for the problem (or the variant the caller names) has such a form: the one-hot split-K kernel,
 // the tiled kernels in their narrow tiles (dense, and sparse), the kernel for one or two columns, the stationary-weight
 // kernel, and the one for channel counts that are no multiple of 32.
-enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs, Ragged };
+enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs, Ragged, OneBit };
 
 // A 1x1 layer with a stride and no padding reads one input pixel in sh * sw: where the packing is not fused only those
 // are packed (2-bit codes in whole 16-code groups), and the layer then runs on them without a stride -- 56x56x256 -> 512
@@ -534,13 +541,14 @@ bool packs_strided_pixels(const dg_lut *lut, const DgProblem &p_codes)
            (int64_t)p_codes.N * (p_codes.Cin / 16) < ((int64_t)1 << 31);
 }
 
-Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel variant)
+// The fused form for tables of any kind; fuses_packing below looks at the table's.
+Fuse fuses_packing_general(const dg_lut *lut, const DgProblem &p_codes, dg_kernel variant)
 {
     // (the unpacked buffer's 16-byte alignment satisfies every kernel's test of the packed one)
     if ((uintptr_t)p_codes.Xp % 16 != 0 || lut->bits != 2) return Fuse::None;
     if ((variant == DG_KERNEL_AUTO || variant == DG_KERNEL_ONEHOT_MFMA) && dg_onehot_codes_supports(lut, p_codes) &&
         (variant == DG_KERNEL_ONEHOT_MFMA ||
-         (dg_onehot_codes_pays(p_codes) && pick_kernel(lut, p_codes, DG_KERNEL_AUTO) == Pick::OneHot)))
+         (dg_onehot_codes_pays(p_codes) && pick_general(lut, p_codes, DG_KERNEL_AUTO) == Pick::OneHot)))
         return Fuse::OneHot;
     // layers of a few microseconds on the tiled kernels: the narrow tiles pack per 64-row tile -- on the sparse instruction
     // where the output's channel axis is the contiguous one and the caller has not named the dense one's variant
@@ -548,29 +556,38 @@ Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel varian
         dg_onehot_codes_tiled_supports(lut, p_codes)) {
         const bool sparse = variant != DG_KERNEL_ONEHOT_MFMA && dg_onehot_codes_tiled_sparse(lut, p_codes);
         if ((sparse || variant != DG_KERNEL_ONEHOT_SMFMAC) && dg_onehot_codes_tiled_pays(lut, p_codes, sparse)) {
-            const Pick pick = pick_kernel(lut, p_codes, variant);
+            const Pick pick = pick_general(lut, p_codes, variant);
             if (pick == Pick::OneHot || pick == Pick::Sparse) return sparse ? Fuse::OneHotSparse : Fuse::OneHot;
         }
     }
     // (the few-columns kernel packs once per row block and pass of four columns, about 7 % more work for it: less than
     // a launch while the columns are few, which is where AUTO uses that kernel anyway)
     if ((variant == DG_KERNEL_SMALLN || (variant == DG_KERNEL_AUTO && p_codes.N <= 4)) &&
-        pick_kernel(lut, p_codes, variant) == Pick::SmallN)
+        pick_general(lut, p_codes, variant) == Pick::SmallN)
         return Fuse::SmallN;
     // the stationary-weight kernel stages and packs the codes of its pixel blocks itself
     if ((variant == DG_KERNEL_AUTO || variant == DG_KERNEL_ONEHOT_SMFMAC) && dg_sparse_ws_codes_supports(lut, p_codes) &&
-        pick_kernel(lut, p_codes, variant) == Pick::SparseWs)
+        pick_general(lut, p_codes, variant) == Pick::SparseWs)
         return Fuse::SparseWs;
     // channels that are no whole groups of 32 (a 1x1 layer with a stride keeps the kernel that packs only the pixels it reads)
     if (variant == DG_KERNEL_AUTO && dg_ragged_preferred(lut, p_codes, true) && !packs_strided_pixels(lut, p_codes) &&
-        pick_kernel(lut, p_codes, variant) == Pick::Ragged)
+        pick_general(lut, p_codes, variant) == Pick::Ragged)
         return Fuse::Ragged;
     // (one column: on packed activations the few-columns sparse-instruction kernel is the faster by 6 %, which is less
     // than the packing launch it would need here)
     if (variant == DG_KERNEL_AUTO && p_codes.N == 1 && p_codes.K >= 1024 && dg_smalln_supports(lut, p_codes) &&
-        pick_kernel(lut, p_codes, variant) == Pick::FewN)
+        pick_general(lut, p_codes, variant) == Pick::FewN)
         return Fuse::SmallN;
     return Fuse::None;
+}
+
+Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel variant)
+{
+    const Fuse fuse = fuses_packing_general(lut, p_codes, variant);
+    if (variant == DG_KERNEL_AUTO && (fuse == Fuse::OneHot || fuse == Fuse::OneHotSparse || fuse == Fuse::SparseWs) &&
+        dg_onebit_codes_preferred(lut, p_codes, fuse == Fuse::SparseWs))
+        return Fuse::OneBit;
+    return fuse;
 }
 
 DgProblem without_stride(const DgProblem &p)
@@ -585,16 +602,13 @@ dg_status run_codes(const char *name, const dg_lut *lut, DgProblem &p, const uin
                     void *work, size_t work_bytes, dg_kernel variant, void *hip_stream)
 {
     p.Xp = codes;
-    const Fuse fuse = fuses_packing(lut, p, variant);
-    if (variant == DG_KERNEL_AUTO && (fuse == Fuse::OneHot || fuse == Fuse::OneHotSparse || fuse == Fuse::SparseWs) &&
-        dg_onebit_codes_preferred(lut, p, fuse == Fuse::SparseWs))
-        return dg_launch_onebit_codes(lut, p, (hipStream_t)hip_stream);
-    switch (fuse) {
+    switch (fuses_packing(lut, p, variant)) {
     case Fuse::OneHot: return dg_launch_onehot_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::OneHotSparse: return dg_launch_onehot_codes(lut, p, (hipStream_t)hip_stream, true);
     case Fuse::SmallN: return dg_launch_smalln_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::SparseWs: return dg_launch_sparse_ws_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::Ragged: return dg_launch_ragged(lut, p, true, (hipStream_t)hip_stream);
+    case Fuse::OneBit: return dg_launch_onebit_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::None: break;
     }
     if (packs_strided_pixels(lut, p)) {
@@ -623,6 +637,7 @@ const char *codes_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Fuse::SmallN: return "codes_smalln";
     case Fuse::SparseWs: return "codes_onehot_smfmac_ws_32xK";
     case Fuse::Ragged: return dg_ragged_config_name(lut, p, true);
+    case Fuse::OneBit: return "codes_onebit_64x128";
     case Fuse::None: break;
     }
     if (packs_strided_pixels(lut, p)) return pick_name(lut, without_stride(p), variant);

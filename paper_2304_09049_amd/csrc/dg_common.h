@@ -163,6 +163,7 @@ bool dg_sparse_is_staged(const dg_lut *lut, const DgProblem &p);     // AUTO wou
 const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p);
 bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p);       // tables that are two one-bit lookups, on the FP4 instruction
 dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+const char *dg_onebit_config_name(const DgProblem &p);
 bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stationary);    // p.Xp: codes one per byte
 dg_status dg_launch_onebit_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes);      // taps of no whole 32-position groups; `codes`: p.Xp one per byte

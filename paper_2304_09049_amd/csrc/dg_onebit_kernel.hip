@@ -561,6 +561,14 @@ dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t st
     return dg_check_launch("onebit_kernel");
 }
 
+const char *dg_onebit_config_name(const DgProblem &p)
+{
+    const OneBitPlan q = onebit_plan(p);
+    if (q.wn == 4) return "onebit_64x512";
+    if (q.wn == 2) return p.N > q.columns * 256 ? "onebit_64x256_64x128" : "onebit_64x256";
+    return q.ks == 2 ? "onebit_64x128_k2" : "onebit_64x128";
+}
+
 // p.Xp: codes one per byte.  AUTO, where it would run a one-hot kernel that packs while loading: from 140 tiles of 64 x 128 up, of 60 such layers, us,
 // that kernel, this one (inputs changing from pass to pass): 56x56x64 -> 40 3x3 stride 2 at batch 25 (154 tiles) 10.8, 8.7; 112x112x64 -> 48 3x3 at
 // batch 7 (686) 17.1, 10.8; 14x14x192 -> 280 3x3 at batch 23 (180) 14.6, 13.5; below, 112x112x128 -> 64 3x3 (98) 8.3, 9.3; 28x28x320 -> 88 3x3 stride 2

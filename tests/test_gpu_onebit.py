@@ -10,7 +10,9 @@ from paper_2304_09049_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-TABLES = [((-2, -1, 0, 1), (0, 1, 2, 3)), ((12, -8, 3, -6), (0, 1, 2, 3)), ((-10, 5, 0, 15), (0, -2, -4, -6)), ((0, 0, 0, 0), (0, 1, 2, 3))]
+TABLES = [((-2, -1, 0, 1), (0, 1, 2, 3)), ((12, -8, 3, -6), (0, 1, 2, 3)), ((-10, 5, 0, 15), (0, -2, -4, -6)), ((0, 0, 0, 0), (0, 1, 2, 3)),
+          ((-100, 50, 0, 75), (0, 1, 2, 3))]                # (the last: entries down to -300, beyond int8)
+NAMES = {"1": "onebit_64x128", "2": "onebit_64x256", "4": "onebit_64x512", "12": "onebit_64x128_k2", "21": "onebit_64x256_64x128"}
 CONVS = [  # B, H, W, Cin, Cout, KH, KW, stride, pad: 1 to 25 taps, tiles and runs whole and not, taps outside on every side, padding without a window
     (1, 9, 11, 64, 36, 3, 3, (1, 1), (1, 1)), (2, 20, 13, 64, 132, 5, 5, (1, 1), (2, 2)), (1, 17, 19, 192, 64, 3, 2, (2, 1), (2, 0)),
     (3, 14, 14, 256, 200, 1, 1, (1, 1), (0, 0)), (2, 15, 14, 320, 68, 1, 1, (2, 2), (1, 1)), (1, 8, 40, 128, 100, 1, 4, (1, 3), (0, 3)),
@@ -26,6 +28,7 @@ def test_onebit_kernel(plan, monkeypatch):
         lut = dg.dg_build_lut(lw, la, dg.DG_LUT_I16)
         c = wl.small_conv(B, H, W, Cin, Cout, KH, KW, stride, pad, seed=H + Cin, scale=True)
         desc = dg.conv_desc(B, H, W, Cin, Cout, KH, KW, stride, pad)
+        assert dg.dg_conv_kernel_name(lut, desc) == NAMES[plan], i
         scale = torch.from_numpy(c.scale).cuda()
         Wp = dg.dg_pack_weights(torch.from_numpy(c.Wc).cuda(), Cout, KH * KW * Cin)
         Xp = dg.dg_pack_activations(torch.from_numpy(c.Ac).cuda(), B * H * W, Cin)
@@ -40,6 +43,7 @@ def test_onebit_kernel(plan, monkeypatch):
         lw, la = TABLES[i % len(TABLES)]
         lut = dg.dg_build_lut(lw, la, dg.DG_LUT_I16)
         g = wl.small_gemm(M, N, K, seed=M)
+        assert dg.dg_gemm_kernel_name(lut, M, N, K) == NAMES[plan], i
         Wp, Ap = dg.dg_pack_weights(torch.from_numpy(g.Wc).cuda(), M, K), dg.dg_pack_activations(torch.from_numpy(g.Ac).cuda(), N, K)
         scale = torch.from_numpy(np.random.default_rng(K).uniform(0.01, 0.1, M).astype(np.float32)).cuda()
         want = oracle.gemm(g.Wc, g.Ac, lw, la)
@@ -61,11 +65,11 @@ def test_onebit_kernel_on_unpacked_codes(monkeypatch):
                                                                            (16, 56, 56, 256, 72, 1, 1, (1, 1), (0, 0)), (8, 28, 28, 512, 96, 1, 1, (1, 1), (0, 0))]):
         if KH * KW * Cin > 3072:                            # (two kernels)
             continue
-        lw, la = TABLES[i % len(TABLES)]
+        lw, la = TABLES[i % (5 if i < 8 else 4)]            # (entries beyond int8 are packed while loading only by the split-K kernel)
         lut = dg.dg_build_lut(lw, la, dg.DG_LUT_I16)
         c = wl.small_conv(B, H, W, Cin, Cout, KH, KW, stride, pad, seed=H + Cin, scale=True)
         desc = dg.conv_desc(B, H, W, Cin, Cout, KH, KW, stride, pad)
-        assert dg.dg_conv_codes_kernel_name(lut, desc).startswith("codes_onehot"), i
+        assert dg.dg_conv_codes_kernel_name(lut, desc) == "codes_onebit_64x128", i
         scale = torch.from_numpy(c.scale).cuda()
         high = torch.randint(0, 64, (c.Ac.size,), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(i)) * 4
         X = torch.from_numpy(c.Ac).cuda().reshape(-1) + high
@@ -89,10 +93,13 @@ def test_tables_of_other_forms_stay_with_the_general_kernels(monkeypatch):
     Xp = dg.dg_pack_activations(torch.from_numpy(c.Ac).cuda(), B * H * W, Cin)
     for lw, la in (((-2, 5, 0, 1), (0, 1, 2, 3)), ((-2, -1, 0, 1), (1, 2, 3, 4)), ((-2, -1, 0, 1), (0, 1, 2, 4)), ((-2, -1, 0, 1), (0, 1, 3, 4)),
                    ((-2, -1, 0, 1), (0, 2, 1, 3)), ((-7, 7, 14, 1), (0, 1, 2, 3))):
-        got = dg.dg_conv2d_lut(dg.dg_build_lut(lw, la), Wp, Xp, desc).cpu().numpy()
+        lut = dg.dg_build_lut(lw, la)
+        assert not dg.dg_conv_kernel_name(lut, desc).startswith("onebit"), (lw, la)
+        got = dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy()
         assert np.array_equal(got, oracle.conv2d(c.Wc, c.Ac, lw, la, stride=(1, 1), pad=(1, 1))), (lw, la)
     lw, la = (-3, -1, 1, 3), (0, 1, 2, 3)
     lut = dg.dg_build_lut_entries([w * a for w in lw for a in la])
+    assert dg.dg_conv_kernel_name(lut, desc) == "onebit_64x128"
     assert np.array_equal(dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy(), oracle.conv2d(c.Wc, c.Ac, lw, la, stride=(1, 1), pad=(1, 1)))
 
 
@@ -112,7 +119,31 @@ def test_sums_to_the_end_of_the_range(monkeypatch):
     assert 2 ** 24 - 2 ** 10 <= np.abs(want).max() < 2 ** 24
     for plan in ("1", "12"):
         monkeypatch.setenv("DG_ONEBIT", plan)
+        assert dg.dg_gemm_kernel_name(lut, M, N, K) == NAMES[plan]
         assert np.array_equal(dg.dg_gemm_lut(lut, Wp, Ap, M, N, K).cpu().numpy(), want), plan
+
+
+AUTOS = [(1000, 2045, 512, "onebit_64x128"), (738, 360, 5568, "onebit_64x128_k2"), (1000, 8100, 1280, "onebit_64x256"),
+         (1024, 4220, 2304, "onebit_64x256_64x128"), (1000, 16301, 2112, "onebit_64x512")]
+
+
+@pytest.mark.parametrize("M,N,K,kernel", AUTOS)
+def test_autos_own_plans(M, N, K, kernel):
+    """Products of a size at which AUTO chooses each tile by itself: every sum, row- and column-major."""
+    lw, la = TABLES[1]
+    rng = np.random.default_rng(N)
+    Wc, Ac = rng.integers(0, 4, (M, K), dtype=np.uint8), rng.integers(0, 4, (N, K), dtype=np.uint8)
+    lut = dg.dg_build_lut(lw, la)
+    assert dg.dg_gemm_kernel_name(lut, M, N, K) == kernel
+    Wp, Ap = dg.dg_pack_weights(torch.from_numpy(Wc).cuda(), M, K), dg.dg_pack_activations(torch.from_numpy(Ac).cuda(), N, K)
+    # (sums of whole numbers below 36 K < 2^24: exact in binary32 in any order)
+    want = torch.from_numpy(np.asarray(lw, np.float32)[Wc]) @ torch.from_numpy(np.asarray(la, np.float32)[Ac]).T
+    want = want.to(torch.int32).numpy()
+    assert np.array_equal(want[:40, -40:], oracle.gemm(Wc[:40], Ac[-40:], lw, la))
+    assert np.array_equal(dg.dg_gemm_lut(lut, Wp, Ap, M, N, K).cpu().numpy(), want)
+    out = torch.zeros((N, M), dtype=torch.int32, device="cuda")
+    dg.dg_gemm_lut(lut, Wp, Ap, M, N, K, out=out, strides=(1, M))
+    assert np.array_equal(out.cpu().numpy().T, want)
 
 
 @pytest.mark.parametrize("codes", [False, True])
@@ -127,6 +158,8 @@ def test_padding_pixel_at_the_end_of_the_32_bit_offsets(codes, monkeypatch):
     desc = dg.conv_desc(1, 2, W, Cin, Cout, 1, 1, (3, W), (1, 0))           # rows -1 and 2 of two, column 0
     Wp = torch.zeros(Cout * Cin // 4, dtype=torch.uint8, device="cuda")
     X = torch.full((used,), 255, dtype=torch.uint8, device="cuda")
+    name = dg.dg_conv_codes_kernel_name if codes else dg.dg_conv_kernel_name
+    assert name(lut, desc) == ("codes_onebit_64x128" if codes else "onebit_64x128")
     if codes:
         got = dg.dg_conv2d_lut_codes(lut, Wp, X, desc, work=torch.empty(used // 4, dtype=torch.uint8, device="cuda"))
     else:
