@@ -436,7 +436,7 @@ bool takes(const dg_lut *lut, const DgProblem &p)
     if ((int64_t)p.K * 3 * largest >= 1 << 24) return false;           // (multiples of 1/4 below 2^22)
     if (p.Cin % 64 != 0 || p.KH * p.KW > 32 || (uintptr_t)p.Wp % 16 != 0 || (uintptr_t)p.Xp % 16 != 0) return false;
     if ((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * (p.Cin / 4) >= (int64_t)1 << 31) return false;      // (32-bit byte offsets)
-    return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 127) / 128) <= INT32_MAX;
+    return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 127) / 128) < 1 << 24;           // (a launch has fewer than 2^32 threads)
 }
 
 struct OneBitPlan {

@@ -68,6 +68,8 @@ def test_shapes():
     lut = dg.dg_build_lut((-2, -1, 0, 1), UNSIGNED)
     name = [dg.dg_conv_kernel_name(lut, dg.conv_desc(4, 64, 64, 128, 128, *k, (1, 1), (0, 0))) for k in ((4, 8), (3, 11))]
     assert name[0].startswith("onebit") and not name[1].startswith("onebit")
+    # 2^24 - 1 workgroups of 256 threads, and one more than a launch takes
+    assert gemm(2 ** 30 - 64, 1, 320) == "onebit_64x128" and gemm(2 ** 30 - 1, 1, 320) == "onehot_smfmac_64x32"
     # other variants are never replaced
     desc = dg.conv_desc(32, 56, 56, 256, 256, 3, 3, (1, 1), (1, 1))
     assert dg.dg_conv_kernel_name(lut, desc, "onehot_smfmac") == "onehot_smfmac_staged_32x224"
