@@ -159,7 +159,9 @@ bool dg_onehot_codes_tiled_pays(const dg_lut *lut, const DgProblem &p, bool spar
 bool dg_sparse_supports(const dg_lut *lut, const DgProblem &p);
 bool dg_sparse_preferred(const dg_lut *lut, const DgProblem &p);     // AUTO's choice between the two one-hot kernels
 dg_status dg_launch_sparse(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
-bool dg_sparse_is_staged(const dg_lut *lut, const DgProblem &p);     // AUTO would run it on the staged kernel
+// What AUTO's plan on the one-hot kernels is: K split over a workgroup, or tiles on the dense or the sparse instruction, from direct loads or staged.
+enum class DgOneHotForm { SplitK, Dense, Sparse, Staged, Staged32x128 };
+DgOneHotForm dg_onehot_auto_form(const dg_lut *lut, const DgProblem &p);
 const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p);
 bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p);       // tables that are two one-bit lookups, on the FP4 instruction
 dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream);

@@ -444,7 +444,14 @@ struct OneBitPlan {
     int64_t columns;         // of wide tiles, the pixel tiles; what is left takes narrow ones
 };
 
+// The output's rows are channels: a GEMM with n contiguous.
+bool rows_are_channels(const DgProblem &p) { return p.stride_cn == 1 && p.stride_cm != 1 && p.KH * p.KW == 1 && !p.Qp; }
+// (they are pixels, of 32-bit sums)
+bool rows_are_pixels(const DgProblem &p) { return !rows_are_channels(p) && !p.Qp; }
+
 int64_t tiles_of(const DgProblem &p, int wn) { return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 128 * wn - 1) / (128 * wn)); }
+
+bool large_output(const DgProblem &p) { return tiles_of(p, 1) >= 13 * (dg_simd_count() / 4); }
 
 // DG_ONEBIT: 0 never, 1, 2, 4 this kernel with WN so large, 12 with WN = 1 and KS = 2, 21 with WN = 2 and half of the pixels in narrow tiles, whatever the
 // size; -1 where it is not set, or to anything else.
@@ -468,10 +475,12 @@ OneBitPlan onebit_plan(const DgProblem &p)
     // A tile twice (four times) as wide costs 1.82 (3.55) times as much per run on a busy compute unit, so the plan is the one that
     // leaves the busiest the least: 112x112x128 -> 128 3x3 at batch 10 (1960, 980, 490 tiles) 24.2, 22.7, 25.0 us; 56x56x128 -> 112 3x3 at batch 26
     // (1274, 638) 16.7, 18.1; 56x56x256 -> 112 3x3 at batch 28 (1372, 686) 28.3, 25.2.  Few runs do not pay for a wide tile's longer end:
-    // 6648 x 2359 x 832 22.1, 25.2; the widest wants nine: 1986 x 7254 x 6272 83.7, 78.3, 74.9, 8192-cube 402, 367, 356, 112x112x128 -> 120 3x3 at
-    // batch 25 60.2, 54.7, 59.4.  Rounds of wide tiles that would leave compute units idle in the last one end in narrow tiles: 56x56x256 -> 256
-    // 3x3 at batch 16 (784 tiles on 256 compute units) 35.1, as 768 and 32 narrow ones 31.1; 112x112x128 -> 112 3x3 at batch 18 42.4, 39.4; 3200 x 6400 x
-    // 2304 42.9, 40.4.  Not the widest: the first as 256 of 512 pixels and 544 narrow ones was 3 us longer than that.
+    // 6648 x 2359 x 832 22.1, 25.2, but on large outputs (8192 x 8192 x 320 by rows 58.0, 51.3; 224x224x64 -> 64 3x3 at batch 16 re-quantising 48.5, 47.2), if
+    // they are not short rows, pixel by pixel, after one or two runs: 1000 x 200000 x 192 174, 255; 2048 x 16384 x 192 27.1, 34.0, x 384 28.9, 36.9.
+    // The widest wants nine: 1986 x 7254 x 6272 83.7, 78.3, 74.9, 8192-cube 402, 367, 356, 112x112x128 -> 120 3x3 at batch 25 60.2, 54.7,
+    // 59.4.  Rounds of wide tiles that would leave compute units idle in the last one end in narrow tiles: 56x56x256 -> 256 3x3 at batch 16
+    // (784 tiles on 256 compute units) 35.1, as 768 and 32 narrow ones 31.1; 112x112x128 -> 112 3x3 at batch 18 42.4, 39.4; 3200 x 6400 x 2304
+    // 42.9, 40.4.  Not the widest: the first as 256 of 512 pixels and 544 narrow ones was 3 us longer than that.
     if (t1 <= units) return OneBitPlan{1, runs >= 8 ? 2 : 1, columns(1)};
     OneBitPlan q = {1, 1, columns(1)};
     double best = (double)((t1 + units - 1) / units);
@@ -485,7 +494,7 @@ OneBitPlan onebit_plan(const DgProblem &p)
             if (mixed < best) best = mixed, q = OneBitPlan{wn, 1, whole};
         }
     };
-    if (t1 > 2 * units && (runs >= 5 || t1 >= 13 * units)) {
+    if (t1 > 2 * units && (runs >= 5 || (large_output(p) && !(runs <= 2 && rows_are_pixels(p) && p.M < 4000)))) {
         consider(2, 1.82);
         if (runs >= 9) consider(4, 3.55);
     }
@@ -494,20 +503,36 @@ OneBitPlan onebit_plan(const DgProblem &p)
 
 }   // namespace
 
-// AUTO takes such tables here where the tiles are many enough, instead of to the one-hot kernels.  Of 210 layers and
-// GEMMs of 1.5 to 200 GOP those with 130 tiles of 64 x 128 and more were all shorter here, by 38 % on average; with fewer, long K is walked by too
-// few wavefronts: 28x28x256 -> 64 3x3 at batch 8 (98 tiles, 9 runs) 8.3 against 7.9, 14x14x256 -> 744 3x3 at batch 7 (132) 11.4 against 9.2,
-// 7x7x1152 -> 1680 3x3 at batch 10 (108 tiles, 41 runs) 18.5 against 20.8, and short K is level: 28x28x128 -> 128 3x3 at batch 8 (98, 5 runs) 6.1 against
-// 6.2, re-quantising between other layers 0.4 us longer here; the direct-load kernels from 35: 738 x 360 x 5568 (36) 15.3 against 12.2.
+// AUTO takes such tables here where the tiles are many and full enough.  In us on packed codes, the one-hot kernels and this one:
+//  - from 130 tiles of 64 x 128 in place of the staged kernel: 14x14x256 -> 744 3x3 at batch 7 (132 tiles) 11.4, 9.2.  With fewer, long K is walked by
+//    too few wavefronts, 7x7x1152 -> 1680 3x3 at batch 10 (108 tiles, 41 runs) 18.5, 20.8, and short K is level, 28x28x128 -> 128 3x3 at batch
+//    8 (98, 5 runs) 6.1, 6.2, re-quantising between other layers 0.4 longer here; some between are shorter here and not taken, 28x28x256 -> 64 3x3
+//    at batch 8 (98, 9 runs) 8.3, 7.9, 134 x 4171 x 4480 (99) 15.3, 11.3: the line counts tiles, not time.
+//  - from 35 in place of direct loads: 738 x 360 x 5568 (36) 15.3, 12.2; 28x28x320 -> 512 3x3 (56) 8.9, 8.9; from 60 in place of the split-K kernel, which
+//    makes one round of long K there: 28x28x512 -> 144 3x3 at batch 2 (39) 7.6, 10.7, 1416 x 135 x 6912 (46) 12.1, 13.5, but 80 x 4112 x 2880 (66) 9.7, 8.1,
+//    85 x 4336 x 5184 (68) 17.5, 11.6 (entries beyond int8 from 35: 2240 x 65 x 5568 13.0, 12.0).
+//  - from 1.5e9 operations: smaller products were not measured.
+//  - from 65 columns, half of the tile: 4096 x 64 x 5568 (64) 9.3, 12.0, x 65 columns 15.1, 12.1; 8192 x 32 x 8192 (128) 11.4, 15.9; 11008 x 64 x 4096 (172) 9.9,
+//    10.2, x 65 13.9, 10.4.  (Entries beyond int8 cost the others twice as much: 8192 x 32 x 8192 13.8, 15.7, but 11008 x 32 x 4096 13.8, 9.9.)
+//  - from 33 rows, half of the tile, in place of staged tiles of 32 x 128: 56x56x128 -> 28 3x3 at batch 32 12.0, 13.0, -> 36 17.8, 14.5; 56x56x384 -> 16 at
+//    batch 16 13.0, 14.6.  The other tiles are behind there too: 112x112x64 -> 16 3x3 at batch 16 26.4, 14.5, 32 x 30000 x 2048 10.2, 7.2 -- but for direct
+//    loads of one or two runs where the output's rows are channels: 32 x 262144 x 320 11.1, 12.0 (x 448 13.7, 12.8), 24 x 262144 x 192 9.1, 10.7.
+//  - not with one run of K and long rows, pixel by pixel, of a large output: 4096 x 20480 x 192 60.1, 65.2 (1000 x 100000 x 192 113, 89).
 bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p)
 {
     const int forced = onebit_override();
     const int64_t t1 = tiles_of(p, 1);
-    if (forced >= 0 ? forced == 0 : t1 < 35 || 2.0 * (double)p.M * (double)p.N * (double)p.K < 1.5e9) return false;       // (smaller ones: not measured ahead)
+    if (forced >= 0 ? forced == 0 : t1 < 35 || 2.0 * (double)p.M * (double)p.N * (double)p.K < 1.5e9) return false;
     if (!takes(lut, p)) return false;
     if (forced > 0) return true;
     if (dg_override("DG_ONEHOT_PLAN") || dg_override("DG_ONEHOT_WAVES")) return false;
-    return t1 >= 130 || !dg_sparse_is_staged(lut, p);
+    const DgOneHotForm other = dg_onehot_auto_form(lut, p);
+    const bool int8 = lut->min_entry >= -128 && lut->max_entry <= 127;
+    if (p.N <= 64 && (int8 || t1 < 130)) return false;
+    if (p.M <= 32 && (other == DgOneHotForm::Staged32x128 || (other == DgOneHotForm::Sparse && p.K <= 320 && rows_are_channels(p)))) return false;
+    if (p.M >= 4000 && p.K <= 256 && int8 && rows_are_pixels(p) && large_output(p)) return false;
+    if (other == DgOneHotForm::SplitK && int8) return t1 >= 60;
+    return t1 >= 130 || other < DgOneHotForm::Staged;
 }
 
 namespace {
@@ -543,8 +568,7 @@ dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t st
     OneBitArgs a;
     fill(lut, p, q, &a);
     const dim3 grid(a.wide + (unsigned)((((int64_t)p.M + 63) / 64) * a.tiles_n[1]));
-    const bool taps = p.KH * p.KW > 1;
-    const bool rows_m = p.stride_cn == 1 && p.stride_cm != 1 && !taps && !p.Qp;      // (the output's rows are channels: a GEMM with n contiguous)
+    const bool taps = p.KH * p.KW > 1, rows_m = rows_are_channels(p);
 #define DG_ONEBIT_FORM(WN, KS, TAPS, TR) hipLaunchKernelGGL((onebit_kernel<WN, KS, TAPS, TR>), grid, dim3(256 * KS), 0, stream, a)
 #define DG_ONEBIT(WN, KS) \
     do { \
@@ -573,12 +597,13 @@ const char *dg_onebit_config_name(const DgProblem &p)
 // that kernel, this one (inputs changing from pass to pass): 56x56x64 -> 40 3x3 stride 2 at batch 25 (154 tiles) 10.8, 8.7; 112x112x64 -> 48 3x3 at
 // batch 7 (686) 17.1, 10.8; 14x14x192 -> 280 3x3 at batch 23 (180) 14.6, 13.5; below, 112x112x128 -> 64 3x3 (98) 8.3, 9.3; 28x28x320 -> 88 3x3 stride 2
 // at batch 31 (96) 15.2, 17.9.  Not in place of the one with stationary weights, whose loads run ahead of its stores: 56x56x256 -> 64 at
-// batch 32 8.6, 8.2 with the input in L2, but 9.4, 10.4 from the last-level cache.
+// batch 32 8.6, 8.2 with the input in L2, but 9.4, 10.4 from the last-level cache.  Nor for 64 columns or fewer, half of the tile: 9000 x 17 x 192 (141
+// tiles) 3.9, 5.6, 9000 x 32 x 1024 6.5, 7.9, 12000 x 64 x 576 6.2, 6.6, x 65 8.6, 6.6.
 // DG_ONEBIT_CODES: 0 never, 1 wherever a kernel packs while loading.
 bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stationary)
 {
     const char *f = dg_override("DG_ONEBIT_CODES");
-    if (f ? atoi(f) == 0 : stationary || tiles_of(p, 1) < 140) return false;
+    if (f ? atoi(f) == 0 : stationary || tiles_of(p, 1) < 140 || p.N <= 64) return false;
     if (!f && (dg_override("DG_ONEHOT_PLAN") || dg_override("DG_ONEHOT_WAVES") || dg_override("DG_ONEHOT_CODES_TILED"))) return false;
     if (!takes(lut, p) || p.stride_cm != 1 || p.Qp) return false;
     return (int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * p.Cin < (int64_t)1 << 31;                   // (32-bit byte offsets)

@@ -349,9 +349,14 @@ bool dg_sparse_preferred(const dg_lut *lut, const DgProblem &p)
            tile_count(t, 2, 1) > dg_simd_count();
 }
 
-bool dg_sparse_is_staged(const dg_lut *lut, const DgProblem &p)
+DgOneHotForm dg_onehot_auto_form(const dg_lut *lut, const DgProblem &p)
 {
-    return dg_sparse_supports(lut, p) && sparse_plan(lut, sparse_problem(p)).staged;
+    const bool sparse = dg_sparse_preferred(lut, p);
+    const Plan q = sparse ? sparse_plan(lut, sparse_problem(p)) : plan_for(lut, p, TABLE);
+    if (q.split) return DgOneHotForm::SplitK;
+    if (!sparse) return DgOneHotForm::Dense;
+    if (!q.staged) return DgOneHotForm::Sparse;
+    return q.wm == 1 && q.wn == 4 ? DgOneHotForm::Staged32x128 : DgOneHotForm::Staged;
 }
 
 bool dg_sparse_supports(const dg_lut *lut, const DgProblem &p)

@@ -5,6 +5,7 @@ import pytest
 from paper_2304_09049_amd import binding as dg
 
 UNSIGNED = (0, 1, 2, 3)
+WIDE = (-100, 50, 0, 75)          # entries beyond int8, which cost the other kernels twice as much
 
 
 @pytest.fixture(autouse=True)
@@ -27,12 +28,38 @@ def test_sizes():
     # 129 and 130 tiles of 64 x 128 in place of the staged kernel, 34 and 35 of the direct loads
     assert conv(1, 129, 128, 128, 64, 3)[0] == "onehot_smfmac_staged_32x64" and conv(1, 130, 128, 128, 64, 3)[0] == "onebit_64x128"
     assert gemm(34 * 64, 128, 5568) == "onehot_mfma_64x32_k4" and gemm(35 * 64, 128, 5568) == "onebit_64x128_k2"
+    # 46 and 66 of the split-K kernel (35 with entries beyond int8)
+    assert conv(2, 28, 28, 512, 144, 3)[0] == gemm(450, 530, 4608) == "onehot_mfma_splitk_s12" and gemm(80, 4112, 2880) == "onebit_64x128_k2"
+    assert gemm(1416, 135, 6912) == "onehot_mfma_splitk_s10" and gemm(2240, 65, 5568, lw=WIDE) == "onebit_64x128_k2"
     # 1.5e9 operations
     assert not gemm(1100, 256, 2624).startswith("onebit") and gemm(1100, 256, 2752) == "onebit_64x128_k2"
     # 139 and 140 tiles from unpacked codes
     assert conv(1, 139, 128, 64, 48, 3)[1] == "codes_onehot_smfmac_64x32" and conv(1, 140, 128, 64, 48, 3)[1] == "codes_onebit_64x128"
     # layers of the stationary-weight kernel stay there
     assert conv(32, 56, 56, 256, 64, 1) == ("onehot_smfmac_ws_32xK", "codes_onehot_smfmac_ws_32xK")
+
+
+def test_half_empty_tiles():
+    """64 columns or fewer and 32 rows or fewer leave half of a tile empty."""
+    assert gemm(4096, 64, 5568) == "onehot_mfma_splitk_s8" and gemm(4096, 65, 5568) == "onebit_64x128_k2"
+    assert gemm(11008, 64, 4096) == "onehot_smfmac_staged_32x64_k4" and gemm(11008, 65, 4096) == "onebit_64x128_k2"
+    assert gemm(11008, 32, 4096, lw=WIDE) == "onebit_64x128_k2" and gemm(4096, 64, 5568, lw=WIDE) == "onehot_mfma_2p_splitk_s8"
+    assert conv(1, 8, 8, 576, 12000, 1)[1] == "codes_onehot_smfmac_64x32_k4" and conv(1, 5, 13, 576, 12000, 1)[1] == "codes_onebit_64x128"
+    # 32 rows: not in place of staged tiles of that height, but of others
+    assert conv(32, 56, 56, 128, 32, 3)[0] == "onehot_smfmac_staged_32x128" and conv(32, 56, 56, 128, 36, 3)[0] == "onebit_64x256"
+    assert conv(16, 56, 56, 384, 16, 3)[0] == "onehot_smfmac_staged_32x128_k2" and conv(16, 112, 112, 64, 16, 3)[0] == "onebit_64x128"
+    assert gemm(32, 262144, 320) == "onehot_smfmac_64x32"
+    assert gemm(32, 262144, 448) == "onebit_64x128" and gemm(33, 262144, 320).startswith("onebit")
+
+
+def test_large_outputs_of_short_sums():
+    # pixels' rows: narrow tiles for one or two runs, wide ones for three; none of 4000 sums and more for one
+    assert conv(1, 400, 250, 192, 1000, 1)[0] == conv(1, 400, 250, 384, 1000, 1)[0] == "onebit_64x128"
+    assert conv(1, 400, 250, 576, 1000, 1)[0] == "onebit_64x256_64x128"
+    assert conv(1, 160, 128, 192, 4096, 1)[0] == "onehot_smfmac_64x64" and conv(1, 160, 128, 320, 4096, 1)[0] == "onebit_64x256"
+    assert conv(1, 32, 128, 192, 4096, 1)[0] == "onebit_64x128"
+    # channels' rows: wide
+    assert gemm(4096, 20480, 192) == gemm(1024, 65536, 192) == "onebit_64x256"
 
 
 @pytest.mark.parametrize("M,N,K,kernel", [
@@ -69,7 +96,7 @@ def test_shapes():
     name = [dg.dg_conv_kernel_name(lut, dg.conv_desc(4, 64, 64, 128, 128, *k, (1, 1), (0, 0))) for k in ((4, 8), (3, 11))]
     assert name[0].startswith("onebit") and not name[1].startswith("onebit")
     # 2^24 - 1 workgroups of 256 threads, and one more than a launch takes
-    assert gemm(2 ** 30 - 64, 1, 320) == "onebit_64x128" and gemm(2 ** 30 - 1, 1, 320) == "onehot_smfmac_64x32"
+    assert gemm(2 ** 30 - 64, 1, 320, lw=WIDE) == "onebit_64x128" and gemm(2 ** 30 - 1, 1, 320, lw=WIDE).startswith("onehot_mfma_2p_")
     # other variants are never replaced
     desc = dg.conv_desc(32, 56, 56, 256, 256, 3, 3, (1, 1), (1, 1))
     assert dg.dg_conv_kernel_name(lut, desc, "onehot_smfmac") == "onehot_smfmac_staged_32x224"
