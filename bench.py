@@ -10,13 +10,14 @@ of the same work is reported beside it.  The table and the packed weights are bu
 region (the paper packs weights offline, Sec. 5.2).  Steps are replayed from a HIP graph so that the host's
 launch cost does not cap a microsecond-scale kernel.
 
-Prints ONE JSON line.  `value` = 2*M*N*K / time per step, in GOPS, for the headline workload: the ResNet50-style
+Prints ONE JSON line on stdout; the sweep of every workload and kernel and the other tables of measurements, ten times
+as long, are one JSON line on stderr.  `value` = 2*M*N*K / time per step, in GOPS, for the headline workload: the ResNet50-style
 1x1 bottleneck convolution at batch 32 (56x56x256 -> 64, M=64 N=100352 K=256), the largest ResNet-shaped layer of
 the benchmark set.  (The ResNet18-style 3x3 layer at batch 1 -- 0.23 GOP, a 3.5 us kernel of which 1.6 us is the
-launch -- and the 64x196x576 GEMM are in `sweep` with their launch floors: their roofline fraction measures launch
+launch -- and the 64x196x576 GEMM are in the sweep with their launch floors: their roofline fraction measures launch
 latency, not the kernel.)
 
-`roofline` (headline) and every `sweep` row price the kernel's EFFECTIVE work -- 2*M*N*K table operations (one
+`roofline` (headline) and every row of the sweep price the kernel's EFFECTIVE work -- 2*M*N*K table operations (one
 lookup and one add per product) and the algorithmic bytes -- against the ceiling that binds the shape:
 t_roof = max(bytes / 8 TB/s, 2MNK / 5 POPS), frac = t_roof / t_kernel.  The int8 multiply-accumulates the matrix
 cores actually perform (4 per product when selecting with one-hot operands, 2 on the sparse instruction; selecting by
@@ -76,7 +77,7 @@ def parse_args():
     ap.add_argument("--workload", default=None, help="name in workloads.CONFIGS (default: the headline conv)")
     ap.add_argument("--variant", default="auto", help="auto | perm | lds | mfma_i8 | smalln | lut65k | onehot_mfma | onehot_smfmac")
     ap.add_argument("--no-graph", action="store_true", help="launch every step from the host instead of a HIP graph")
-    ap.add_argument("--no-sweep", action="store_true", help="skip the per-workload kernel sweep")
+    ap.add_argument("--no-sweep", action="store_true", help="skip the per-workload kernel sweep (a JSON line on stderr)")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
     ap.add_argument("--table-values", action="store_true",
                     help="also time the workload's kernel (AUTO and the comparison) with other tables of the same shape: "
@@ -614,6 +615,7 @@ def main():
                                            "ratio": round(ms_uniform / ms_kernel, 4)}
         del ru
 
+    details = {}
     if not args.no_sweep:
         sweep = []
         for wname, ww in wl.CONFIGS.items():
@@ -651,16 +653,18 @@ def main():
                 except Exception as e:                      # report, never hide
                     sweep.append({"workload": wname, "variant": variant, "error": str(e)})
             del rr
-        line["sweep"] = sweep
-        line["stage_kernels"] = stage_kernels(torch, wl.CONFIGS["resnet50_conv1x1_b32"])
-        line["wide_codes"] = wide_code_kernels(torch, wl.CONFIGS["vgg16_conv3x3_b16"], use_graph)
-        line["fused_layers"] = fused_layers(torch, ["resnet18_conv3x3_b1", "resnet50_conv1x1_b32", "vgg16_conv3x3_b16"],
-                                            use_graph)
+        details["sweep"] = sweep
+        details["stage_kernels"] = stage_kernels(torch, wl.CONFIGS["resnet50_conv1x1_b32"])
+        details["wide_codes"] = wide_code_kernels(torch, wl.CONFIGS["vgg16_conv3x3_b16"], use_graph)
+        details["fused_layers"] = fused_layers(torch, ["resnet18_conv3x3_b1", "resnet50_conv1x1_b32", "vgg16_conv3x3_b16"],
+                                               use_graph)
 
     if args.table_values:
         line["table_values"] = table_values(torch, r, use_graph)
     if not args.no_cpu:
         line["cpu_baseline"] = cpu_baseline(w)
+    if details:
+        print(json.dumps(details), file=sys.stderr, flush=True)
     print(json.dumps(line))
 
 
