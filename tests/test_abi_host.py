@@ -216,7 +216,8 @@ def test_two_plane_sharing_rule():
 
 def test_kernel_names_need_no_gpu():
     # the plan functions are host code: small layers split K, large ones get a wave tile, wide entries two planes
-    lut = dg.dg_build_lut((-2, -1, 0, 1), (0, 1, 2, 3))
+    # (a table of the general form; those that are two one-bit lookups have names of their own, test_onebit_rules.py)
+    lut = dg.dg_build_lut((-2, 5, 0, 1), (0, 1, 2, 3))
     assert dg.dg_gemm_kernel_name(lut, 64, 196, 576).startswith("onehot_mfma_splitk_s")
     # large layers: the sparse instruction, operands staged through LDS where the taps are whole 32-byte runs
     assert dg.dg_gemm_kernel_name(lut, 8192, 8192, 8192) == "onehot_smfmac_staged_64x128"
