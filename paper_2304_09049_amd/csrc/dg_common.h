@@ -60,7 +60,9 @@ struct DgProblem {
 // one, through L2 together.  Same kernels, us, streamed and through the caches: 5942 x 6830 x 320 (direct-load tiles) 108, 51; 3648 x 7425 x 256
 // (stationary weights) 52.8, 29.7; 1986 x 7254 x 1280 (staged) 56.5, 42.2; 28x28x512 -> 264 at batch 32 15.5, 14.1; 28x28x128 -> 104 3x3 at batch
 // 16, 4-bit, 12.6, 12.0; 1000 x 1001 x 2048 8.1, 8.0; and one-bit tables (dg_onebit_kernel.hip) 3569 x 7478 x 704 55, 28.  Whole pieces: 56x56x256 -> 64 at
-// batch 32 8.6, 9.9; one-bit tables 112x112x64 -> 96 3x3 at batch 12 20.4, 22.5.
+// batch 32 8.6, 9.9; one-bit tables 112x112x64 -> 96 3x3 at batch 12 20.4, 22.5.  Of 400 drawn layers and products with such rows, 0.1 to 400 MB, two were more than 2 % longer
+// through the caches (112x112x64 -> 24 at batch 21, stationary weights, 7.8, 8.3; one-bit tables 7079 x 1548 x 2112 29.1, 31.3); two planes 15x15x448 -> 1000 3x3
+// at batch 14 56.4, 56.6.
 inline int32_t dg_output_cached(const DgProblem &p)
 {
     if (p.Qp) return 0;                                     // (packed codes, bytes)

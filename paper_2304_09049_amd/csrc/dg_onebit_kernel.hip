@@ -1,6 +1,8 @@
 // 2-bit tables that are two ONE-BIT lookups, on the FP4 matrix instruction.  Where
 //
-//   T[w][0] = 0,  T[w][2] = 2 T[w][1],  T[w][3] = T[w][1] + T[w][2]       (evenly spaced activation levels from zero, any weight levels)
+//   T[w][0] = 0,  T[w][2] = 2 T[w][1],  T[w][3] = T[w][1] + T[w][2]       (evenly spaced activation levels from zero)
+//
+// and the entries T[w][1], over a common factor, are among 0, 1, 2, 3, 4, 6, 8, 12 and their negatives (find_numbers; not -2, 5, 0, 1),
 //
 // a position adds the entry T[w][1] if bit 0 of its activation code is set, and the entry T[w][2] if bit 1 is.  As a contraction that is
 // two places of the reduction per position, the entries on one side and single bits on the other, where the one-hot form of any table
@@ -11,7 +13,7 @@
 // the low bit at the bottom of a 4-bit place is 0.5, the high bit next to it is 1, of even codes as loaded, of odd ones after a shift by
 // two -- five vector instructions for the operands of two instructions.  Weight code w is the number N[w] = T[w][1] / (2 f), the same for
 // both bits, f the entries' common factor.  All products and sums are multiples of 1/4 below 2^22, hence exact in binary32 in any order
-// (the host checks; find_numbers), and 4 f times the sum is the integer result.
+// (the host checks; takes), and 4 f times the sum is the integer result.
 //
 // A workgroup's four wavefronts share 64 channels, each with 32 WN pixels of its own.  A run is 256 positions of K, 64 bytes of a row: four
 // neighbouring lanes fetch a row's, the pixels' straight to LDS (dg_lds_dma.h), one run ahead.  A 16-byte segment lies in one filter tap
@@ -593,12 +595,14 @@ const char *dg_onebit_config_name(const DgProblem &p)
     return q.ks == 2 ? "onebit_64x128_k2" : "onebit_64x128";
 }
 
-// p.Xp: codes one per byte.  AUTO, where it would run a one-hot kernel that packs while loading: from 140 tiles of 64 x 128 up, of 60 such layers, us,
-// that kernel, this one (inputs changing from pass to pass): 56x56x64 -> 40 3x3 stride 2 at batch 25 (154 tiles) 10.8, 8.7; 112x112x64 -> 48 3x3 at
-// batch 7 (686) 17.1, 10.8; 14x14x192 -> 280 3x3 at batch 23 (180) 14.6, 13.5; below, 112x112x128 -> 64 3x3 (98) 8.3, 9.3; 28x28x320 -> 88 3x3 stride 2
-// at batch 31 (96) 15.2, 17.9.  Not in place of the one with stationary weights, whose loads run ahead of its stores: 56x56x256 -> 64 at
-// batch 32 8.6, 8.2 with the input in L2, but 9.4, 10.4 from the last-level cache.  Nor for 64 columns or fewer, half of the tile: 9000 x 17 x 192 (141
-// tiles) 3.9, 5.6, 9000 x 32 x 1024 6.5, 7.9, 12000 x 64 x 576 6.2, 6.6, x 65 8.6, 6.6.
+// p.Xp: codes one per byte.  AUTO, where it would run a one-hot kernel that packs while loading: from 140 tiles of 64 x 128 up, us, that kernel, this one
+// (inputs changing from pass to pass): 56x56x64 -> 40 3x3 stride 2 at batch 25 (154 tiles) 10.8, 8.7; 112x112x64 -> 48 3x3 at batch 7 (686) 17.1, 10.8;
+// 14x14x192 -> 280 3x3 at batch 23 (180) 14.6, 13.5; of 290 such calls one layer behind, 56x56x192 -> 64 at batch 32 10.5, 10.8; below, 112x112x128 -> 64
+// 3x3 (98) 8.3, 9.3; 28x28x320 -> 88 3x3 stride 2 at batch 31 (96) 15.2, 17.9.  Not for 64 columns or fewer, half of the tile: 9000 x 17 x 192 (141)
+// 3.9, 5.6, 9000 x 32 x 1024 6.5, 7.9, 12000 x 64 x 576 6.2, 6.6, x 65 8.6, 6.6.
+// Nor in place of the kernel with stationary weights, whose loads run ahead of its stores.  It is behind that on 56x56x256 -> 64 at batch 32, 8.6, 8.2 with the
+// input in L2, but 9.4, 10.4 from the last-level cache, on 56x56x128 -> 40 at batch 16 6.1, 7.3, 56x56x256 -> 64 at batch 8 5.5, 5.8; of 17 such
+// layers 13 are shorter here, 28x28x256 -> 256 at batch 16 7.0, 6.1, 56x56x256 -> 200 at batch 16 20.5, 18.1: a rule between them is not made yet.
 // DG_ONEBIT_CODES: 0 never, 1 wherever a kernel packs while loading.
 bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stationary)
 {
