@@ -251,9 +251,9 @@ def mfma_ops_factor(name):
     """int8 multiply-accumulates the matrix cores perform per effective operation: the one-hot kernel contracts over 4K
     (one operand byte per table column); on the sparse instruction, which skips the half of them that its index says
     are zero, over 2K (priced against the DENSE peak all the same); the decode-and-multiply comparison kernel over K;
-    the kernel for tables that are two one-bit lookups over 2K on the FP4 instruction, which has twice the int8 peak, so
-    it counts as K here; table kernels on the VALU issue none."""
-    if name.startswith("onebit_") or name.startswith("codes_onebit_"):
+    the kernels for tables that are two one-bit lookups, and for products of levels, over 2K on the FP4 / FP6 instruction, which has
+    twice the int8 peak, so they count as K here; table kernels on the VALU issue none."""
+    if name.startswith(("onebit_", "codes_onebit_", "twopower_")):
         return 1
     if name.startswith("onehot_mfma") or name.startswith("codes_onehot_mfma"):
         return 4

@@ -163,11 +163,15 @@ bool dg_sparse_preferred(const dg_lut *lut, const DgProblem &p);     // AUTO's c
 dg_status dg_launch_sparse(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 // What AUTO's plan on the one-hot kernels is: K split over a workgroup, or tiles on the dense or the sparse instruction, from direct loads or staged.
 enum class DgOneHotForm { SplitK, Dense, Sparse, Staged, Staged32x128 };
-DgOneHotForm dg_onehot_auto_form(const dg_lut *lut, const DgProblem &p);
+// *busiest: what its tiles give the busiest SIMD, in blocks of 32 x 32 by thousands of positions.
+DgOneHotForm dg_onehot_auto_form(const dg_lut *lut, const DgProblem &p, double *busiest = nullptr);
 const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p);
 bool dg_onebit_preferred(const dg_lut *lut, const DgProblem &p);       // tables that are two one-bit lookups, on the FP4 instruction
 dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 const char *dg_onebit_config_name(const DgProblem &p);
+bool dg_twopower_preferred(const dg_lut *lut, const DgProblem &p);     // products of levels, on the FP6 / FP4 instruction
+dg_status dg_launch_twopower(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+const char *dg_twopower_config_name(const DgProblem &p);
 bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stationary);    // p.Xp: codes one per byte
 dg_status dg_launch_onebit_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes);      // taps of no whole 32-position groups; `codes`: p.Xp one per byte

@@ -349,10 +349,15 @@ bool dg_sparse_preferred(const dg_lut *lut, const DgProblem &p)
            tile_count(t, 2, 1) > dg_simd_count();
 }
 
-DgOneHotForm dg_onehot_auto_form(const dg_lut *lut, const DgProblem &p)
+DgOneHotForm dg_onehot_auto_form(const dg_lut *lut, const DgProblem &p, double *busiest)
 {
     const bool sparse = dg_sparse_preferred(lut, p);
-    const Plan q = sparse ? sparse_plan(lut, sparse_problem(p)) : plan_for(lut, p, TABLE);
+    const DgProblem t = sparse ? sparse_problem(p) : p;
+    const Plan q = sparse ? sparse_plan(lut, t) : plan_for(lut, p, TABLE);
+    if (busiest) {
+        const int64_t places = dg_simd_count() / q.skw, tiles = tile_count(t, q.wm, q.wn);
+        *busiest = (double)((tiles + places - 1) / places) / q.skw * q.wm * q.wn * 1e-3 * p.K;
+    }
     if (q.split) return DgOneHotForm::SplitK;
     if (!sparse) return DgOneHotForm::Dense;
     if (!q.staged) return DgOneHotForm::Sparse;
