@@ -221,6 +221,7 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *   DG_ONEBIT        "0": AUTO never takes tables that are two one-bit lookups to the FP4 instruction; "1", "2", "4": whatever the size, in
  *                    tiles of 64 x 128, 256 or 512, "12": 64 x 128 with K shared by two; "21": 64 x 256 for half of the pixels, 64 x 128 for the rest;
  *                    any other value counts as not set
+ *   DG_PLANES        "0": AUTO never reads codes bit by bit on the int8 instruction, "2", "4": whatever the size, in tiles of 64 x 64 or 64 x 128
  *   DG_TWOPOWER      "0": AUTO never takes products of levels to the FP6 / FP4 instruction; "1", "2", "4": whatever the size, in tiles of 64 x 128,
  *                    128 x 256 or 128 x 512, "12": 64 x 128 with K shared by two; any other value counts as not set
  *   DG_ONEBIT_CODES  "0": AUTO never takes them there from unpacked codes, "1": wherever a kernel packs while loading
@@ -292,9 +293,11 @@ dg_status dg_conv2d_lut(const dg_lut *lut, const void *Wp_dev, const void *Xp_de
  * where the output's channel axis is contiguous unless ONEHOT_MFMA is named -- up to about 2 * 10^9 table operations,
  * more where there is much to pack or Cin % 128 != 0); the layers of the stationary-weight
  * kernel (K = 64, 128, 256 without a filter window; AUTO or ONEHOT_SMFMAC); and the few-columns kernel (AUTO or
- * SMALLN); and layers with Cin % 32 != 0, Cin >= 16 and little enough to pack over (AUTO).  Every other layer is packed into
+ * SMALLN); and layers with Cin % 32 != 0, Cin >= 16 and little enough to pack over (AUTO).  Every other layer asks for
  * Xp_work_dev (device, work_bytes >= dg_packed_bytes_bits(B*H*W, Cin, bits), else DG_ERR_BUFFER; DG_ERR_NULL if it
- * is needed and NULL) by the packing kernel and then run as dg_conv2d_lut would run it, on the same stream (of a
+ * is needed and NULL), is packed into it by the packing kernel and then run as dg_conv2d_lut would run it, on the same stream (but AUTO
+ * reads the codes as they are, and leaves the buffer alone, on layers of a few microseconds with 3- and 4-bit codes and evenly
+ * spaced levels, and with 2-bit tables of products beyond int8 whose activation level 0 is 0, where Cin % 64 == 0; of a
  * 1x1 layer with a stride and no padding only the pixels it reads are packed, [B][OH][OW][Cin/4] at the start of the
  * buffer, and the layer runs on those without the stride).
  * Outputs, scale, variant and the other errors as dg_conv2d_lut; the results are identical to dg_pack_activations

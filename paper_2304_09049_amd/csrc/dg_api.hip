@@ -125,6 +125,7 @@ dg_status dg_build_lut_bits(int32_t bits, const int8_t *levels_w, const int8_t *
         }
     t.max_abs = t.max_entry > -t.min_entry ? t.max_entry : -t.min_entry;
     if (bits != 2) dg_find_two_lookups(&t);
+    dg_find_bit_sums(&t);
     dg_lut *p = new (std::nothrow) dg_lut(t);
     if (!p) return dg_fail(DG_ERR_BUFFER, "dg_build_lut: out of host memory");
     *out = p;
@@ -163,6 +164,7 @@ dg_status dg_build_lut_entries(const int16_t entries[16], dg_lut_dtype entry, dg
         if (v > t.max_entry) t.max_entry = v;
     }
     t.max_abs = t.max_entry > -t.min_entry ? t.max_entry : -t.min_entry;
+    dg_find_bit_sums(&t);
     dg_lut *p = new (std::nothrow) dg_lut(t);
     if (!p) return dg_fail(DG_ERR_BUFFER, "dg_build_lut_entries: out of host memory");
     *out = p;
@@ -532,7 +534,7 @@ namespace {
 // the library's own choice for the problem (or the variant the caller names) has such a form: the one-hot split-K kernel,
 // the tiled kernels in their narrow tiles (dense, and sparse), the kernel for one or two columns, the stationary-weight
 // kernel, and the one for channel counts that are no multiple of 32.
-enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs, Ragged, OneBit };
+enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs, Ragged, OneBit, Planes };
 
 // A 1x1 layer with a stride and no padding reads one input pixel in sh * sw: where the packing is not fused only those
 // are packed (2-bit codes in whole 16-code groups), and the layer then runs on them without a stride -- 56x56x256 -> 512
@@ -590,6 +592,8 @@ Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel varian
     if (variant == DG_KERNEL_AUTO && (fuse == Fuse::OneHot || fuse == Fuse::OneHotSparse || fuse == Fuse::SparseWs) &&
         dg_onebit_codes_preferred(lut, p_codes, fuse == Fuse::SparseWs))
         return Fuse::OneBit;
+    if (variant == DG_KERNEL_AUTO && fuse == Fuse::None && !packs_strided_pixels(lut, p_codes) && dg_planes_codes_preferred(lut, p_codes))
+        return Fuse::Planes;
     return fuse;
 }
 
@@ -605,13 +609,20 @@ dg_status run_codes(const char *name, const dg_lut *lut, DgProblem &p, const uin
                     void *work, size_t work_bytes, dg_kernel variant, void *hip_stream)
 {
     p.Xp = codes;
-    switch (fuses_packing(lut, p, variant)) {
+    const Fuse fuse = fuses_packing(lut, p, variant);
+    if (fuse == Fuse::Planes) {                             // (such layers ask for a work buffer all the same)
+        if (!work) return dg_fail(DG_ERR_NULL, "%s: NULL buffer", name);
+        const size_t need = dg_packed_bytes_bits(rows, row_codes, lut->bits);
+        if (work_bytes < need) return dg_fail(DG_ERR_BUFFER, "%s: packed buffer has %zu bytes, %zu needed", name, work_bytes, need);
+    }
+    switch (fuse) {
     case Fuse::OneHot: return dg_launch_onehot_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::OneHotSparse: return dg_launch_onehot_codes(lut, p, (hipStream_t)hip_stream, true);
     case Fuse::SmallN: return dg_launch_smalln_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::SparseWs: return dg_launch_sparse_ws_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::Ragged: return dg_launch_ragged(lut, p, true, (hipStream_t)hip_stream);
     case Fuse::OneBit: return dg_launch_onebit_codes(lut, p, (hipStream_t)hip_stream);
+    case Fuse::Planes: return dg_launch_planes_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::None: break;
     }
     if (packs_strided_pixels(lut, p)) {
@@ -641,6 +652,7 @@ const char *codes_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Fuse::SparseWs: return "codes_onehot_smfmac_ws_32xK";
     case Fuse::Ragged: return dg_ragged_config_name(lut, p, true);
     case Fuse::OneBit: return "codes_onebit_64x128";
+    case Fuse::Planes: return dg_planes_codes_config_name(lut, p);
     case Fuse::None: break;
     }
     if (packs_strided_pixels(lut, p)) return pick_name(lut, without_stride(p), variant);

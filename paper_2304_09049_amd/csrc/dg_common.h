@@ -15,6 +15,14 @@ struct DgTwoLookups {
     int32_t lo, hi;              // range of all their entries
 };
 
+// A table whose entries are sums of what the activation code's bits add, as dg_planes_kernel.hip takes it.
+struct DgBitSums {
+    bool sums;
+    uint32_t bytes;              // 2-bit codes: byte w, u[w]
+    int32_t low, high, both;     // 2-bit codes: what the sums of its three planes count for; others: T[w][1] = low w + high
+    int32_t most;                // the largest number on the weights' side times the largest on the other
+};
+
 // The opaque table object: levels, the 16 products, and what the kernels need to know about them.
 struct dg_lut {
     int32_t bits;        // code width: 2 (the paper's kernels), 3 or 4 (Sec. 3.3); 2^bits levels per side
@@ -28,6 +36,7 @@ struct dg_lut {
     int32_t max_entry;   // largest product
     int32_t max_abs;     // max |product|
     DgTwoLookups two[2]; // of the table, and of the transposed one (found when the table is built)
+    DgBitSums bit_sums;  // (found when the table is built)
 };
 
 // 16 table entries passed to kernels by value (no device allocation is needed for a table).
@@ -172,6 +181,15 @@ const char *dg_onebit_config_name(const DgProblem &p);
 bool dg_twopower_preferred(const dg_lut *lut, const DgProblem &p);     // products of levels, on the FP6 / FP4 instruction
 dg_status dg_launch_twopower(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 const char *dg_twopower_config_name(const DgProblem &p);
+// A 2-bit table as factor * u[w] * v[a], u and v whole numbers without a common factor each; false if it is no such product.
+bool dg_find_levels(const dg_lut *lut, int (&u)[4], int (&v)[4], int *factor);
+void dg_find_bit_sums(dg_lut *lut);
+bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p);    // p.Xp: codes one per byte, by their bits on the int8 instruction
+// About how long the packing kernel and AUTO's kernel on its output take, us: 3- and 4-bit codes as two lookups, 2-bit tables with entries beyond
+// int8; 0 where that was not measured.
+double dg_onehot_packed_time(const dg_lut *lut, const DgProblem &p);
+dg_status dg_launch_planes_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+const char *dg_planes_codes_config_name(const dg_lut *lut, const DgProblem &p);
 bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stationary);    // p.Xp: codes one per byte
 dg_status dg_launch_onebit_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes);      // taps of no whole 32-position groups; `codes`: p.Xp one per byte

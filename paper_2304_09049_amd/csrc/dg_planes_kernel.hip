@@ -1,0 +1,373 @@
+// Layers from unpacked codes by the codes' BITS, on the int8 matrix instruction, for tables whose entries are sums of what single bits add:
+//
+//   3- and 4-bit codes, T[w][a] = a T[w][1] (evenly spaced activation levels from zero): bit b of the code adds T[w][1] 2^b
+//   2-bit codes, T[w][a] = f u[w] v[a] with v[0] = 0 and entries beyond int8: the low bit adds f u[w] v[1], the high bit f u[w] v[2], and
+//   both together f u[w] (v[3] - v[1] - v[2]), three sums per output, each of the u[w] whose bits are set, put together at the end
+//
+// A code per byte is the operand as it is: masked with 0x01010101 << b it holds bit b's 0 or 2^b, one vector instruction per four codes
+// and bit.  The other operand is a byte per weight code, T[w][1] or u[w].  Three or four products per position on the int8 instruction, 32
+// positions of it in 32 cycles, are as many cycles as (3-bit codes and entries beyond int8: three quarters of) what the packed codes take on the
+// sparse instruction as two lookups or in two planes; every product is by 0 or a power of two.  What is saved is the launch of the
+// packing kernel, the rows of tables read per position, and their fill.
+//
+// Eight wavefronts: 64 channels, PXW blocks of 32 pixels, K in KS = 8 / PXW shares.  The wavefronts of a share take its runs of 128 positions
+// together, as in dg_onebit_kernel.hip: pixels' pieces straight to LDS, one run ahead, each lane working out its own piece's filter tap
+// and reading zeros outside the image (code 0 adds nothing); the channels' bytes made once for the share's wavefronts, one barrier a run.
+#include "dg_lds_dma.h"
+#include "dg_onehot_kernel.h"
+
+#include <cstdlib>
+#include <cstring>
+
+namespace {
+
+using namespace dgoh;
+
+struct PlanesArgs {
+    DgProblem p;
+    uint32_t bytes;          // 2-bit codes: byte w, u[w]
+    int32_t low, high, both; // 2-bit codes: what the three sums count for; others: T[w][1] = low w + high
+    FastDiv div_ow, div_oh, div_kw, div_cpt, div_band, div_last;      // (div_cpt: by the 16-position pieces of a filter tap)
+    int32_t tiles_n, band_log2;
+    uint32_t band_tiles, x_bytes;
+};
+
+// Where the rows of bytes of pixels n, n + 8, n + 16 and n + 24 begin, and which of their taps lie outside the image (bit t, tap t): all, beyond the
+// last pixel.
+__device__ __forceinline__ void place_pixels(const PlanesArgs &a, int n, uint32_t (&off0)[4], uint32_t (&outside)[4])
+{
+    const DgProblem &p = a.p;
+    uint32_t columns[4];
+    int h0[4], h1[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const Column c = make_column(p, a.div_ow, a.div_oh, n + 8 * i, p.Cin, 0);
+        const int c0 = max(0, -c.iw0), c1 = min(p.KW, p.W - c.iw0);
+        h0[i] = -c.ih0, h1[i] = c.ok ? p.H - c.ih0 : 0;
+        off0[i] = (uint32_t)c.off0;
+        columns[i] = c1 > c0 ? (~0u >> (32 - (c1 - c0))) << c0 : 0u;
+        outside[i] = ~0u;
+    }
+    for (int kh = 0; kh < p.KH; ++kh)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) outside[i] &= ~(kh >= h0[i] && kh < h1[i] ? columns[i] << (kh * p.KW) : 0u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm("" : "+v"(off0[i]));    // (kept, not worked out again for each load)
+}
+
+template <int BITS, int PXW>
+__global__ void __launch_bounds__(512, 2)
+planes_kernel(PlanesArgs a)
+{
+    constexpr int KS = 8 / PXW, SUMS = BITS == 2 ? 3 : 1;
+    constexpr int WEIGHTS = 8192, PIXELS = 4096;            // bytes of a run: a share's weights, a wavefront's pixels
+    constexpr int SHARE = 2 * WEIGHTS + 2 * PXW * PIXELS;
+    constexpr int UNITS = 4 / PXW, WORDS = BITS == 2 ? 2 : 4;          // quarters of a row's run that a thread expands, their packed words
+    __shared__ uint4 s_mem[KS * SHARE / 16];
+    __shared__ int32_t s_codes[BITS == 2 ? 4 : 256];        // [share][wavefront][pixel]: sums of codes
+    const DgProblem &p = a.p;
+    dg_fetch_arguments<sizeof(a)>();
+    const int lane = threadIdx.x & 63, all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 31, h = lane >> 5;
+    const int wave = all % PXW, ks = all / PXW;
+    int m_tile, n_tile;                                     // numbered in bands of 2^band_log2 pixel tiles, as in dg_sparse_staged_kernel.h
+    {
+        const uint32_t t = xcd_contiguous(blockIdx.x, gridDim.x), band = fdiv(t, a.div_band), t_in = t - band * a.band_tiles;
+        const int first = (int)band << a.band_log2, width = min(1 << a.band_log2, a.tiles_n - first);
+        m_tile = (int)(width == 1 << a.band_log2 ? t_in >> a.band_log2 : fdiv(t_in, a.div_last));
+        n_tile = first + (int)t_in - m_tile * width;
+    }
+    const int m0 = m_tile * 64, n0 = (n_tile * PXW + wave) * 32;
+    // this share's runs g0 ... g1 - 1 of K; the shares walk equally many, past their ends as zeros
+    const int all_runs = (p.K + 127) / 128, g0 = all_runs * ks / KS, g1 = all_runs * (ks + 1) / KS, runs = (all_runs + KS - 1) / KS;
+    const int pieces = min(p.K / 16, 8 * g1);
+    char *const mem = (char *)s_mem + ks * SHARE;
+
+    // ---- weights: quarter q of a run's positions of a row is a thread's unit (rows beyond M, bytes past the last row: zeros; past the end of K:
+    // the next row's, which meet pixels of zero)
+    constexpr int RUN_BYTES = BITS == 2 ? 32 : 64;
+    const uint32_t row_bytes = (uint32_t)p.K / (BITS == 2 ? 4 : 2);
+    const __amdgpu_buffer_rsrc_t w_buffer =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(p.Wp + (int64_t)m0 * row_bytes), 0, (int)(min(p.M - m0, 64) * row_bytes), 0x00020000);
+    const int w_row = (threadIdx.x % (64 * PXW)) >> 2, quarter = threadIdx.x & 3;
+    const uint32_t w_ld = w_row * row_bytes + quarter * (RUN_BYTES / 4);
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    struct Raw {
+        uint32_t v[UNITS][WORDS];
+    };
+    auto load_weights = [&](Raw &raw, int g) {
+#pragma unroll
+        for (int i = 0; i < UNITS; ++i) {
+            const uint32_t at = w_ld + i * (16 * PXW) * row_bytes + g * RUN_BYTES;
+            if constexpr (BITS == 2) {
+                const v2i t = (v2i)__builtin_amdgcn_raw_buffer_load_b64(w_buffer, at, 0, 0);
+                raw.v[i][0] = (uint32_t)t[0], raw.v[i][1] = (uint32_t)t[1];
+            } else {
+                const v4i t = (v4i)__builtin_amdgcn_raw_buffer_load_b128(w_buffer, at, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) raw.v[i][j] = (uint32_t)t[j];
+            }
+        }
+    };
+    // step i's bytes of rows 32 b ... as [i][b][lane], lane (r, half) with positions 64 half + 16 i ... of the run; lanes exchanged so that a
+    // thread's neighbours, which write the other quarters, are on other banks
+    auto expand = [&](const Raw &raw, uint32_t buf) {
+#pragma unroll
+        for (int i = 0; i < UNITS; ++i) {
+            const int row = w_row + i * (16 * PXW);
+            char *const to = mem + buf + ((2 * (quarter & 1)) * 2 + (row >> 5)) * 1024 + ((quarter >> 1) * 32 + ((row & 31) ^ (2 * quarter))) * 16;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {                   // 16 positions each
+                v4i o;
+                if constexpr (BITS == 2) {
+                    const uint32_t w = raw.v[i][s];
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {           // (four codes of a byte, one to a byte)
+                        const uint32_t pairs = (((w >> (8 * d)) & 255u) * 0x1001u) & 0x000F000Fu;
+                        o[d] = (int)__builtin_amdgcn_perm(0u, a.bytes, (pairs << 6 | pairs) & 0x03030303u);
+                    }
+                } else {
+#pragma unroll
+                    for (int d = 0; d < 2; ++d) {
+                        const uint32_t w = raw.v[i][2 * s + d], even = w & 0x0F0F0F0Fu, odd = (w >> 4) & 0x0F0F0F0Fu;
+                        o[2 * d] = (int)__builtin_amdgcn_perm(odd, even, 0x05010400u), o[2 * d + 1] = (int)__builtin_amdgcn_perm(odd, even, 0x07030602u);
+                    }
+                }
+                *(v4i *)(to + s * 2048) = o;
+            }
+        }
+    };
+
+    Raw raw;
+    load_weights(raw, g0);                                  // (before the pixels' places are worked out)
+
+    // ---- pixels: lane l of a load fetches piece (l % 8) ^ (row % 8) of row l / 8 of eight
+    const v4i x_buffer = dg_buffer(p.Xp, a.x_bytes);
+    const int l_row = lane >> 3, l_piece = (lane & 7) ^ l_row;
+    uint32_t off0[4], outside[4];
+    place_pixels(a, n0 + l_row, off0, outside);
+    const uint32_t x_lds = dg_lds_address(mem) + 2 * WEIGHTS + wave * 2 * PIXELS;
+    auto fetch = [&](int g, int odd) {
+        const uint32_t dst = x_lds + odd * PIXELS;
+        const int c = 8 * g + l_piece;
+        const uint32_t dead = c < pieces ? 0u : 0x80000000u;
+        const int tap = (int)fdiv((uint32_t)c, a.div_cpt), kh = (int)fdiv((uint32_t)tap, a.div_kw), kw = tap - kh * p.KW;
+        const uint32_t tap_off = (uint32_t)((kh * p.W + kw) * p.Cin + (c - tap * (p.Cin >> 4)) * 16);
+        dg_for<4>([&](auto i) {
+            const uint32_t out = (outside[i] << ((31 - tap) & 31)) | dead;
+            dg_load16_to_lds<i * 1024>(x_buffer, (off0[i] + tap_off) | (out & 0x80000000u), dst);
+        });
+    };
+
+    fetch(g0, 0);
+    expand(raw, 0);
+    load_weights(raw, g0 + 1);
+    float sc_cols[2];
+    dg_mfma_column_scales<2, true>(p, m0, lane, sc_cols);
+    v16i acc[2][SUMS];
+#pragma unroll
+    for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+        for (int k = 0; k < SUMS; ++k)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[bm][k][e] = 0;
+
+    int codes_sum = 0;                                      // BITS > 2: of the codes that this lane has multiplied
+    const char *const x_from = mem + 2 * WEIGHTS + wave * 2 * PIXELS + r * 128;
+    for (int i = 0; i < runs; ++i) {
+        const int odd = i & 1, g = g0 + i;
+        dg_wait_for_loads<0>();                             // (this run's pixels, the next one's weights)
+#pragma unroll
+        for (int j = 0; j < UNITS; ++j)
+#pragma unroll
+            for (int k = 0; k < WORDS; ++k) asm volatile("" : "+v"(raw.v[j][k]));
+        const Raw next = raw;
+        __syncthreads();
+        fetch(g + 1, odd ^ 1);
+        load_weights(raw, g + 2);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const v4i x = *(const v4i *)(x_from + odd * PIXELS + ((4 * h + s) ^ (r & 7)) * 16);
+            v4i w[2];
+#pragma unroll
+            for (int bm = 0; bm < 2; ++bm)
+                w[bm] = *(const v4i *)(mem + odd * WEIGHTS + (2 * s + bm) * 1024 + (h * 32 + (r ^ (2 * (2 * h + (s >> 1))))) * 16);
+#pragma unroll
+            for (int d = 0; d < (BITS == 2 ? 0 : 4); ++d)
+                codes_sum = (int)__builtin_amdgcn_udot4((uint32_t)x[d] & ((1u << BITS) - 1) * 0x01010101u, 0x01010101u, (uint32_t)codes_sum, false);
+#pragma unroll
+            for (int k = 0; k < (BITS == 2 ? 3 : BITS); ++k) {
+                v4i plane;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const uint32_t c = (uint32_t)x[d];
+                    plane[d] = (int)(BITS == 2 && k == 2 ? c & (c >> 1) & 0x01010101u : c & (0x01010101u << k));
+                }
+#pragma unroll
+                for (int bm = 0; bm < 2; ++bm)
+                    acc[bm][SUMS == 3 ? k : 0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(plane, w[bm], acc[bm][SUMS == 3 ? k : 0], 0, 0, 0);
+            }
+            if (s == 1) expand(next, (odd ^ 1) * WEIGHTS);
+        }
+    }
+    dg_wait_for_loads();                                    // (fetches past the end: their LDS writes end before the wavefront does)
+
+    if constexpr (BITS == 2) {                              // (sums below 2^23, what they count for below 2^17: the host checks)
+#pragma unroll
+        for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                acc[bm][0][e] = __mul24(acc[bm][0][e], a.low) + __mul24(acc[bm][1][e] >> 1, a.high) + __mul24(acc[bm][2][e], a.both);
+    }
+    if constexpr (BITS != 2) {
+        codes_sum += __shfl_xor(codes_sum, 32);
+        if (h == 0) s_codes[all * 32 + r] = codes_sum;
+    }
+    // [share][wavefront][block][group of four sums][lane]; then each wavefront adds up and stores 1 / KS of its pixels' two blocks
+    __syncthreads();
+    int4 *const mine = (int4 *)s_mem + all * 512 + lane;
+#pragma unroll
+    for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const v16i &t = acc[bm][0];
+            mine[(4 * bm + q) * 64] = make_int4(t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]);
+        }
+    __syncthreads();
+    constexpr int NQ = 8 / KS;
+    const int first = ks * NQ, bm = first >> 2, q0 = first & 3;
+    const int4 *const from = (const int4 *)s_mem + wave * 512 + first * 64 + lane;
+    dg_v4i sums[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        sums[q] = (dg_v4i){0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const int4 t = from[k * (PXW * 512) + q * 64];
+            sums[q][0] += t.x, sums[q][1] += t.y, sums[q][2] += t.z, sums[q][3] += t.w;
+        }
+        if constexpr (BITS != 2) {
+            dg_v4i codes = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < KS; ++k) codes += *(const dg_v4i *)(s_codes + (k * PXW + wave) * 32 + 8 * (q0 + q) + 4 * h);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sums[q][e] = __mul24(sums[q][e], a.low) + __mul24(codes[e], a.high);
+        }
+    }
+    dg_mfma_store_quads<NQ>(p, sums, q0, m0 + bm * 32, n0, lane, bm ? sc_cols[1] : sc_cols[0]);
+}
+
+int64_t tiles_of(const DgProblem &p, int pxw) { return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 32 * pxw - 1) / (32 * pxw)); }
+
+// DG_PLANES: 0 never, 2, 4 this kernel with so many pixel blocks whatever the size; -1 where it is not set, or to anything else.
+int planes_override()
+{
+    const char *f = dg_override("DG_PLANES");
+    if (f && (strcmp(f, "0") == 0 || strcmp(f, "2") == 0 || strcmp(f, "4") == 0)) return f[0] - '0';
+    return -1;
+}
+
+// us, fitted to 222 layers (2 to 3 % off on average): once, a round of workgroups (one to a compute unit), a run of one, an MB of output.
+double cost(const DgProblem &p, int bits, int pxw)
+{
+    static const double fits[3][2][4] = {{{1.6, 3.2, 1.28, 0.165}, {2.0, 2.7, 1.06, 0.18}},
+                                         {{1.7, 2.5, 1.23, 0.138}, {1.9, 2.4, 1.10, 0.139}},
+                                         {{1.7, 2.45, 1.41, 0.153}, {2.0, 2.2, 1.29, 0.153}}};
+    const double *const f = fits[bits - 2][pxw == 4];
+    const int64_t units = dg_simd_count() / 4, rounds = (tiles_of(p, pxw) + units - 1) / units, shares = 8 / pxw;
+    const double runs = (double)((((int64_t)p.K + 127) / 128 + shares - 1) / shares);
+    return f[0] + (double)rounds * (f[1] + f[2] * runs) + f[3] * 4e-6 * (double)p.M * (double)p.N;
+}
+
+int pixel_blocks(const DgProblem &p, int bits)
+{
+    const int forced = planes_override();
+    return forced > 0 ? forced : (cost(p, bits, 2) < cost(p, bits, 4) ? 2 : 4);
+}
+
+bool takes(const dg_lut *lut, const DgProblem &p)
+{
+    if (!lut->bit_sums.sums || p.stride_cm != 1 || p.Qp) return false;
+    if ((int64_t)p.K * lut->bit_sums.most >= 1 << 23) return false;    // (24-bit products)
+    if (p.Cin % 64 != 0 || p.KH * p.KW > 32 || (uintptr_t)p.Wp % 16 != 0 || (uintptr_t)p.Xp % 16 != 0) return false;
+    if ((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * p.Cin >= (int64_t)1 << 31) return false;               // (32-bit byte offsets)
+    return tiles_of(p, 2) < 1 << 22;                                                                               // (a launch has fewer than 2^32 threads)
+}
+
+}   // namespace
+
+// (once per table)
+void dg_find_bit_sums(dg_lut *lut)
+{
+    DgBitSums &n = lut->bit_sums;
+    memset(&n, 0, sizeof(n));
+    if (lut->bits == 2) {
+        int v[4], u[4], factor;
+        if (!dg_find_levels(lut, u, v, &factor) || v[0] != 0) return;
+        n.low = factor * v[1], n.high = factor * v[2], n.both = factor * (v[3] - v[1] - v[2]);
+        for (int w = 0; w < 4; ++w) {
+            if (u[w] < -128 || u[w] > 127) return;
+            n.bytes |= (uint32_t)(uint8_t)u[w] << (8 * w);
+            if (abs(u[w]) > n.most) n.most = abs(u[w]);
+        }
+    } else {
+        const int codes = 1 << lut->bits;
+        n.high = lut->entry[1], n.low = lut->entry[codes + 1] - n.high, n.most = (codes - 1) * (codes - 1);
+        for (int w = 0; w < codes; ++w)
+            for (int c = 0; c < codes; ++c)
+                if (lut->entry[codes * w + c] != c * (n.high + n.low * w)) return;
+    }
+    n.sums = true;
+}
+
+// AUTO, where a layer would be packed first: 3- and 4-bit codes that run as two lookups, 2-bit tables with entries beyond int8.  From codes, us, the two
+// kernels and this one (graph replays): 28x28x128 -> 128 3x3 at batch 8, 4-bit 10.1, 8.8, 3-bit 10.1, 8.2; 28x28x256 -> 256 3x3 at batch 8, entries
+// beyond int8 18.4, 15.4; 112x112x128 -> 112 3x3 stride 2 at batch 5, 3-bit 16.2, 10.4.  It is behind with many rounds of tiles, whose codes are read
+// again for every 64 channels (112x112x64 -> 112 3x3 at batch 4, 4-bit 19.9, 29.9; with more than four rounds the fit is not asked:
+// 116x116x64 -> 104 3x3 at batch 13, beyond int8, 72, 79), and on long K with few tiles (14x14x384 -> 360 3x3 at batch 2, beyond int8, 10.1, 14.2).
+// Of 222 drawn layers the fitted times send 78 here, 1.23 times as fast on average, none slower.
+bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
+{
+    const int forced = planes_override();
+    if (forced >= 0 ? forced == 0 : dg_override("DG_ONEHOT_PLAN") || dg_override("DG_ONEHOT_WAVES") || dg_override("DG_NIBBLES") ||
+                                     dg_override("DG_STAGED_2P") || dg_override("DG_STAGED_2P_PLAN"))
+        return false;
+    if (!takes(lut, p)) return false;
+    if (forced > 0) return true;
+    if (tiles_of(p, 4) > dg_simd_count()) return false;
+    const double here = cost(p, lut->bits, pixel_blocks(p, lut->bits)), there = dg_onehot_packed_time(lut, p);
+    return here < 0.94 * there && !dg_onebit_preferred(lut, p);
+}
+
+dg_status dg_launch_planes_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
+{
+    PlanesArgs a;
+    const DgBitSums &n = lut->bit_sums;
+    a.bytes = n.bytes, a.low = n.low, a.high = n.high, a.both = n.both;
+    a.p = p;
+    const int pxw = pixel_blocks(p, lut->bits), tiles_m = (p.M + 63) / 64;
+    a.div_ow = make_div((uint32_t)p.OW), a.div_oh = make_div((uint32_t)p.OH), a.div_kw = make_div((uint32_t)p.KW);
+    a.div_cpt = make_div((uint32_t)(p.Cin / 16));
+    a.tiles_n = (p.N + 32 * pxw - 1) / (32 * pxw);
+    a.band_log2 = 2;
+    a.band_tiles = (uint32_t)tiles_m << a.band_log2;
+    a.div_band = make_div(a.band_tiles);
+    const int last = a.tiles_n & ((1 << a.band_log2) - 1);
+    a.div_last = make_div((uint32_t)(last ? last : 1));
+    a.x_bytes = (uint32_t)((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * p.Cin);
+    const dim3 grid((unsigned)(tiles_m * a.tiles_n));
+#define DG_PLANES(BITS) \
+    do { \
+        if (pxw == 4) hipLaunchKernelGGL((planes_kernel<BITS, 4>), grid, dim3(512), 0, stream, a); \
+        else hipLaunchKernelGGL((planes_kernel<BITS, 2>), grid, dim3(512), 0, stream, a); \
+    } while (0)
+    if (lut->bits == 2) DG_PLANES(2);
+    else if (lut->bits == 3) DG_PLANES(3);
+    else DG_PLANES(4);
+#undef DG_PLANES
+    return dg_check_launch("planes_kernel");
+}
+
+const char *dg_planes_codes_config_name(const dg_lut *lut, const DgProblem &p)
+{
+    return pixel_blocks(p, lut->bits) == 4 ? "codes_planes_64x128_k2" : "codes_planes_64x64_k4";
+}

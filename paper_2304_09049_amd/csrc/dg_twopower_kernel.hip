@@ -296,8 +296,9 @@ twopower_kernel(TwoPowerArgs a)
         }
 }
 
-// The table as factor * u[w] * v[a], u and v whole numbers without a common factor each; false if it is no such product.
-bool find_levels(const dg_lut *lut, int (&u)[4], int (&v)[4], int *factor)
+}   // namespace
+
+bool dg_find_levels(const dg_lut *lut, int (&u)[4], int (&v)[4], int *factor)
 {
     if (lut->bits != 2 || lut->dtype == DG_LUT_F32) return false;
     const int16_t *row = nullptr;
@@ -327,6 +328,8 @@ bool find_levels(const dg_lut *lut, int (&u)[4], int (&v)[4], int *factor)
     return true;
 }
 
+namespace {
+
 // An FP6 (E2M3) number that is v eighths, or -1.
 int fp6(int v)
 {
@@ -345,7 +348,7 @@ struct Numbers {
 bool find_numbers(const dg_lut *lut, Numbers *n)
 {
     int u[4], v[4], most_u = 0, most_v = 0;
-    if (!find_levels(lut, u, v, &n->factor)) return false;
+    if (!dg_find_levels(lut, u, v, &n->factor)) return false;
     memset(n->bytes, 0, sizeof(n->bytes));
     n->powers = 0;
     for (int w = 0; w < 4; ++w) {
