@@ -299,7 +299,7 @@ int64_t dg_conv_out_dim(int64_t in, int64_t k, int64_t stride, int64_t pad)
 
 namespace {
 
-enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Ragged, Staged2p, OneHotF32, OneBit, TwoPower, Unsupported };
+enum class Pick { Perm, Lds, LdsF32, Mfma, SmallN, Lut65k, OneHot, Sparse, Nibble, Sparse4, Sparse2p, SparseWs, FewN, Ragged, Staged2p, OneHotF32, OneBit, TwoPower, Planes, Unsupported };
 
 // The kernel for tables of any form; pick_kernel below looks at the table's.
 Pick pick_general(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
@@ -359,6 +359,8 @@ Pick pick_kernel(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     const Pick pick = pick_general(lut, p, variant);
     if (variant == DG_KERNEL_AUTO && (pick == Pick::Sparse || pick == Pick::OneHot) && dg_onebit_preferred(lut, p)) return Pick::OneBit;
     if (variant == DG_KERNEL_AUTO && (pick == Pick::Sparse || pick == Pick::OneHot) && dg_twopower_preferred(lut, p)) return Pick::TwoPower;
+    if (variant == DG_KERNEL_AUTO && (pick == Pick::Staged2p || pick == Pick::Sparse2p || pick == Pick::OneHot) && dg_planes_preferred(lut, p))
+        return Pick::Planes;
     return pick;
 }
 
@@ -383,6 +385,7 @@ dg_status run(const dg_lut *lut, const DgProblem &p, dg_kernel variant, hipStrea
     case Pick::Ragged: return dg_launch_ragged(lut, p, false, stream);
     case Pick::OneBit: return dg_launch_onebit(lut, p, stream);
     case Pick::TwoPower: return dg_launch_twopower(lut, p, stream);
+    case Pick::Planes: return dg_launch_planes(lut, p, stream);
     case Pick::Unsupported: break;
     }
     return dg_fail(DG_ERR_UNSUPPORTED,
@@ -411,6 +414,7 @@ const char *pick_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Pick::Ragged: return dg_ragged_config_name(lut, p, false);
     case Pick::OneBit: return dg_onebit_config_name(p);
     case Pick::TwoPower: return dg_twopower_config_name(p);
+    case Pick::Planes: return "planes_64x128";
     case Pick::Unsupported: break;
     }
     return "unsupported";

@@ -185,11 +185,14 @@ const char *dg_twopower_config_name(const DgProblem &p);
 bool dg_find_levels(const dg_lut *lut, int (&u)[4], int (&v)[4], int *factor);
 void dg_find_bit_sums(dg_lut *lut);
 bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p);    // p.Xp: codes one per byte, by their bits on the int8 instruction
-// About how long the packing kernel and AUTO's kernel on its output take, us: 3- and 4-bit codes as two lookups, 2-bit tables with entries beyond
-// int8; 0 where that was not measured.
-double dg_onehot_packed_time(const dg_lut *lut, const DgProblem &p);
 dg_status dg_launch_planes_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 const char *dg_planes_codes_config_name(const dg_lut *lut, const DgProblem &p);
+bool dg_planes_preferred(const dg_lut *lut, const DgProblem &p);          // the same on packed 2-bit codes
+dg_status dg_launch_planes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
+// About how long AUTO's kernels take, us: 3- and 4-bit codes as two lookups, from `codes` MB of unpacked codes, packing included; 2-bit tables with
+// entries beyond int8, on packed codes.  0 where that was not measured.
+double dg_onehot_nibble_time(const dg_lut *lut, const DgProblem &p, double codes);
+double dg_onehot_two_plane_time(const dg_lut *lut, const DgProblem &p);
 bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stationary);    // p.Xp: codes one per byte
 dg_status dg_launch_onebit_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes);      // taps of no whole 32-position groups; `codes`: p.Xp one per byte

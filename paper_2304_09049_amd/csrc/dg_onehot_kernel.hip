@@ -993,36 +993,46 @@ dg_status dg_launch_staged2p(const dg_lut *lut, const DgProblem &p0, hipStream_t
     return dg_check_launch("smfmac_staged_kernel");
 }
 
-// Fitted to 222 layers of 0.02 to 60 GOP from codes (4 to 9 % off on average), in blocks of 32 x 32 by thousands of positions (of twice as many for 3- and 4-bit
-// codes) on the busiest SIMD or compute unit, MB of output and of codes.
-double dg_onehot_packed_time(const dg_lut *lut, const DgProblem &p)
+namespace {
+
+// What a plan's tiles give the busiest SIMD, and one block a workgroup the busiest compute unit, in blocks of 32 x 32 by thousands of positions.
+double tiles_on_simd(const DgProblem &p, const Plan &q, int wm)
 {
-    const bool nibble = lut->bits != 2;
-    const DgProblem n = nibble ? nibble_problem(p) : p;
+    const int64_t places = dg_simd_count() / q.skw, tiles = tile_count(p, wm, q.wn);
+    return (double)((tiles + places - 1) / places) / q.skw * wm * q.wn * 1e-3 * p.K;
+}
+double blocks_on_unit(const DgProblem &p)
+{
     const int64_t units = dg_simd_count() / 4;
+    return (double)((tile_count(p, 1, 1) + units - 1) / units) * 1e-3 * p.K;
+}
+
+}   // namespace
+
+// Fitted to 132 layers of 0.02 to 30 GOP (4 to 8 % off on average).
+double dg_onehot_nibble_time(const dg_lut *lut, const DgProblem &p, double codes)
+{
+    if (sparse_transposes(p) || !dg_nibble_preferred(lut, p)) return 0.0;
+    const DgProblem n = nibble_problem(p);
     const double thousands = 1e-3 * n.K, out = 4e-6 * (double)p.M * p.N;
-    const double codes = 1e-6 * (double)(p.N / ((int64_t)p.OH * p.OW)) * p.H * p.W * p.Cin;
-    auto tiles_on_simd = [&](const Plan &q, int wm) {
-        const int64_t places = 4 * units / q.skw, tiles = tile_count(n, wm, q.wn);
-        return (double)((tiles + places - 1) / places) / q.skw * wm * q.wn * thousands;
-    };
-    const double on_unit = (double)((tile_count(n, 1, 1) + units - 1) / units) * thousands;
-    if (sparse_transposes(p)) return 0.0;
-    if (nibble) {
-        if (!dg_nibble_preferred(lut, p)) return 0.0;
-        if (dg_sparse_ws_preferred(two_bit_view(), n)) return 4.5 + 0.56 * on_unit + 0.113 * out + 0.287 * codes + 1.96 * thousands;
-        const Plan q = sparse_plan(two_bit_view(), n);
-        if (q.split) return 4.7 + 0.86 * on_unit + 0.81 * out + 0.044 * codes;
-        return q.staged ? 5.8 + 1.31 * tiles_on_simd(q, q.wm) + 0.174 * out + 0.26 * codes + 0.37 * thousands : 0.0;
-    }
-    if (fits_int8(lut)) return 0.0;
-    if (dg_staged2p_preferred(lut, p))
-        return 6.3 + 2.19 * tiles_on_simd(staged2p_plan(n), 1) + 0.308 * out + 0.125 * codes + 0.34 * thousands;
+    if (dg_sparse_ws_preferred(two_bit_view(), n)) return 4.5 + 0.56 * blocks_on_unit(n) + 0.113 * out + 0.287 * codes + 1.96 * thousands;
+    const Plan q = sparse_plan(two_bit_view(), n);
+    if (q.split) return 4.7 + 0.86 * blocks_on_unit(n) + 0.81 * out + 0.044 * codes;
+    return q.staged ? 5.8 + 1.31 * tiles_on_simd(n, q, q.wm) + 0.174 * out + 0.26 * codes + 0.37 * thousands : 0.0;
+}
+
+// Fitted to 240 layers of 0.15 to 90 GOP (6 to 12 % off on average).
+double dg_onehot_two_plane_time(const dg_lut *lut, const DgProblem &p)
+{
+    if (sparse_transposes(p) || lut->bits != 2 || fits_int8(lut)) return 0.0;
+    const double out = 4e-6 * (double)p.M * p.N;
+    if (dg_staged2p_preferred(lut, p)) return 4.9 + 2.53 * tiles_on_simd(p, staged2p_plan(p), 1) + 0.13 * out;
     Plan q;
-    if (dg_sparse2p_preferred(lut, p)) q.wn = 4, q.skw = 1;
-    else q = plan_for(lut, p, TABLE);
-    if (q.split) return 4.6 + 1.38 * on_unit + out + 0.032 * codes;
-    return 4.6 + 2.78 * tiles_on_simd(q, 1) + 0.235 * out + 0.053 * codes + 5.06 * thousands;
+    if (dg_sparse2p_preferred(lut, p)) q.wn = 4, q.skw = 1, q.split = false;
+    else if (dg_onehot_supports(lut, p)) q = plan_for(lut, p, TABLE);
+    else return 0.0;
+    if (q.split) return 2.8 + 1.48 * blocks_on_unit(p) + 0.56 * out;
+    return 2.8 + 2.81 * tiles_on_simd(p, q, 1) + 0.2 * out + 5.2e-3 * p.K;
 }
 
 bool dg_decode_supports(const dg_lut *lut, const DgProblem &p)

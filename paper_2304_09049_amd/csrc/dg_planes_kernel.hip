@@ -1,4 +1,5 @@
-// Layers from unpacked codes by the codes' BITS, on the int8 matrix instruction, for tables whose entries are sums of what single bits add:
+// Layers by the codes' BITS, on the int8 matrix instruction, from unpacked codes (planes_packed_kernel: packed 2-bit ones), for tables whose entries
+// are sums of what single bits add:
 //
 //   3- and 4-bit codes, T[w][a] = a T[w][1] (evenly spaced activation levels from zero): bit b of the code adds T[w][1] 2^b
 //   2-bit codes, T[w][a] = f u[w] v[a] with v[0] = 0 and entries beyond int8: the low bit adds f u[w] v[1], the high bit f u[w] v[2], and
@@ -256,6 +257,115 @@ planes_kernel(PlanesArgs a)
     dg_mfma_store_quads<NQ>(p, sums, q0, m0 + bm * 32, n0, lane, bm ? sc_cols[1] : sc_cols[0]);
 }
 
+// 2-bit codes that are packed already, for larger layers: four wavefronts, 64 channels and 32 pixels each, K in runs of 128 positions.  A lane's
+// half of a run is four words, the bits of whose codes are 20 vector instructions per 16 codes and three planes: 5 beside each matrix instruction, three
+// wavefronts to a SIMD.  Three matrix instructions per 32 positions and block where two planes on the sparse one take four, and no rows of a
+// table: 56x56x256 -> 256 3x3 at batch 16 94 -> 70 us, 2646 instructions on every SIMD at 26 ns (20 with random bytes in registers and nothing else).
+__global__ void __launch_bounds__(256, 3)
+planes_packed_kernel(PlanesArgs a)
+{
+    constexpr int WEIGHTS = 8192, PIXELS = 1024;            // bytes of a run: the weights, a wavefront's pixels
+    __shared__ uint4 s_mem[(2 * WEIGHTS + 8 * PIXELS) / 16];
+    const DgProblem &p = a.p;
+    dg_fetch_arguments<sizeof(a)>();
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 31, h = lane >> 5;
+    int m_tile, n_tile;
+    {
+        const uint32_t t = xcd_contiguous(blockIdx.x, gridDim.x), band = fdiv(t, a.div_band), t_in = t - band * a.band_tiles;
+        const int first = (int)band << a.band_log2, width = min(1 << a.band_log2, a.tiles_n - first);
+        m_tile = (int)(width == 1 << a.band_log2 ? t_in >> a.band_log2 : fdiv(t_in, a.div_last));
+        n_tile = first + (int)t_in - m_tile * width;
+    }
+    const int m0 = m_tile * 64, n0 = (n_tile * 4 + wave) * 32;
+    const int runs = (p.K + 127) / 128, pieces = p.K / 64;  // (a piece: 64 positions, a lane's 16 bytes)
+    char *const mem = (char *)s_mem;
+
+    // ---- weights, as above
+    const uint32_t row_bytes = (uint32_t)p.K / 4;
+    const __amdgpu_buffer_rsrc_t w_buffer =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(p.Wp + (int64_t)m0 * row_bytes), 0, (int)(min(p.M - m0, 64) * row_bytes), 0x00020000);
+    const int w_row = threadIdx.x >> 2, quarter = threadIdx.x & 3;
+    const uint32_t w_ld = w_row * row_bytes + quarter * 8;
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    auto load_weights = [&](int g) { return (v2i)__builtin_amdgcn_raw_buffer_load_b64(w_buffer, w_ld + g * 32, 0, 0); };
+    char *const w_to = mem + ((2 * (quarter & 1)) * 2 + (w_row >> 5)) * 1024 + ((quarter >> 1) * 32 + ((w_row & 31) ^ (2 * quarter))) * 16;
+    auto expand = [&](const v2i &raw, int s, uint32_t buf) {
+        v4i o;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) o[d] = (int)__builtin_amdgcn_perm(0u, a.bytes, ((uint32_t)raw[s] >> (2 * d)) & 0x03030303u);
+        *(v4i *)(w_to + buf + s * 2048) = o;
+    };
+
+    // ---- pixels: lane l of the load fetches piece l % 2 of row l / 2
+    const v4i x_buffer = dg_buffer(p.Xp, a.x_bytes);
+    uint32_t off0, outside;
+    {
+        const Column c = make_column(p, a.div_ow, a.div_oh, n0 + (lane >> 1), p.Cin / 4, 0);
+        const int h0 = -c.ih0, h1 = c.ok ? p.H - c.ih0 : 0, c0 = max(0, -c.iw0), c1 = min(p.KW, p.W - c.iw0);
+        const uint32_t columns = c1 > c0 ? (~0u >> (32 - (c1 - c0))) << c0 : 0u;
+        off0 = (uint32_t)c.off0, outside = ~0u;
+        for (int kh = 0; kh < p.KH; ++kh) outside &= ~(kh >= h0 && kh < h1 ? columns << (kh * p.KW) : 0u);
+        asm("" : "+v"(off0));
+    }
+    const uint32_t x_lds = dg_lds_address(mem) + 2 * WEIGHTS + wave * 2 * PIXELS;
+    auto fetch = [&](int g, int odd) {
+        const int c = 2 * g + (lane & 1);
+        const int tap = (int)fdiv((uint32_t)c, a.div_cpt), kh = (int)fdiv((uint32_t)tap, a.div_kw), kw = tap - kh * p.KW;
+        const uint32_t tap_off = (uint32_t)((kh * p.W + kw) * (p.Cin >> 2) + (c - tap * (p.Cin >> 6)) * 16);
+        const uint32_t out = (outside << ((31 - tap) & 31)) | (c < pieces ? 0u : 0x80000000u);
+        dg_load16_to_lds<0>(x_buffer, (off0 + tap_off) | (out & 0x80000000u), x_lds + odd * PIXELS);
+    };
+
+    v2i raw = load_weights(0);
+    fetch(0, 0);
+    expand(raw, 0, 0), expand(raw, 1, 0);
+    raw = load_weights(1);
+    float sc_cols[2];
+    dg_mfma_column_scales<2, true>(p, m0, lane, sc_cols);
+    v16i acc[2][3];
+#pragma unroll
+    for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[bm][k][e] = 0;
+    for (int g = 0; g < runs; ++g) {
+        const int odd = g & 1;
+        dg_wait_for_loads<0>();                             // (this run's pixels, the next one's weights)
+        asm volatile("" : "+v"(raw));
+        const v2i next = raw;
+        __syncthreads();
+        const v4i x = *(const v4i *)(mem + 2 * WEIGHTS + wave * 2 * PIXELS + odd * PIXELS + (2 * r + h) * 16);
+        fetch(g + 1, odd ^ 1);
+        raw = load_weights(g + 2);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            v4i w[2];
+#pragma unroll
+            for (int bm = 0; bm < 2; ++bm)
+                w[bm] = *(const v4i *)(mem + odd * WEIGHTS + (2 * s + bm) * 1024 + (h * 32 + (r ^ (2 * (2 * h + (s >> 1))))) * 16);
+            const uint32_t c = (uint32_t)x[s], both = c & (c >> 1);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                v4i plane;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) plane[d] = (int)(((k == 2 ? both : c) >> (2 * d)) & (k == 1 ? 0x02020202u : 0x01010101u));
+#pragma unroll
+                for (int bm = 0; bm < 2; ++bm) acc[bm][k] = __builtin_amdgcn_mfma_i32_32x32x32_i8(plane, w[bm], acc[bm][k], 0, 0, 0);
+            }
+            if (s & 1) expand(next, s >> 1, (odd ^ 1) * WEIGHTS);
+        }
+    }
+    dg_wait_for_loads();                                    // (fetches past the end: their LDS writes end before the wavefront does)
+#pragma unroll
+    for (int bm = 0; bm < 2; ++bm) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            acc[bm][0][e] = __mul24(acc[bm][0][e], a.low) + __mul24(acc[bm][1][e] >> 1, a.high) + __mul24(acc[bm][2][e], a.both);
+        dg_mfma_store_block<true, true, DG_OUT_BY_PROBLEM>(p, acc[bm][0], m0 + bm * 32, n0, lane, sc_cols[bm]);
+    }
+}
+
 int64_t tiles_of(const DgProblem &p, int pxw) { return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 32 * pxw - 1) / (32 * pxw)); }
 
 // DG_PLANES: 0 never, 2, 4 this kernel with so many pixel blocks whatever the size; -1 where it is not set, or to anything else.
@@ -295,6 +405,22 @@ bool takes(const dg_lut *lut, const DgProblem &p)
 
 }   // namespace
 
+// The kernel on packed codes, us, fitted to 240 layers of 0.15 to 90 GOP (6 % off on average): once, a run of one, two or more workgroups of a compute
+// unit, a workgroup, an MB of output.
+static double packed_cost(const DgProblem &p)
+{
+    const int64_t units = dg_simd_count() / 4, n = (tiles_of(p, 4) + units - 1) / units;
+    const double runs = (double)(((int64_t)p.K + 127) / 128), per_run = n == 1 ? 0.611 : (n == 2 ? 0.439 : 0.465);
+    return 3.3 + (double)n * (0.575 + per_run * runs) + 0.065 * 4e-6 * (double)p.M * (double)p.N;
+}
+
+static bool other_overrides()
+{
+    for (const char *name : {"DG_ONEHOT_PLAN", "DG_ONEHOT_WAVES", "DG_NIBBLES", "DG_STAGED_2P", "DG_STAGED_2P_PLAN"})
+        if (dg_override(name)) return true;
+    return false;
+}
+
 // (once per table)
 void dg_find_bit_sums(dg_lut *lut)
 {
@@ -328,33 +454,73 @@ void dg_find_bit_sums(dg_lut *lut)
 bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
 {
     const int forced = planes_override();
-    if (forced >= 0 ? forced == 0 : dg_override("DG_ONEHOT_PLAN") || dg_override("DG_ONEHOT_WAVES") || dg_override("DG_NIBBLES") ||
-                                     dg_override("DG_STAGED_2P") || dg_override("DG_STAGED_2P_PLAN"))
-        return false;
+    if (forced >= 0 ? forced == 0 : other_overrides()) return false;
     if (!takes(lut, p)) return false;
     if (forced > 0) return true;
     if (tiles_of(p, 4) > dg_simd_count()) return false;
-    const double here = cost(p, lut->bits, pixel_blocks(p, lut->bits)), there = dg_onehot_packed_time(lut, p);
-    return here < 0.94 * there && !dg_onebit_preferred(lut, p);
+    const double codes = 1e-6 * (double)(p.N / ((int64_t)p.OH * p.OW)) * p.H * p.W * p.Cin;
+    double there;
+    if (lut->bits != 2) {
+        there = dg_onehot_nibble_time(lut, p, codes);
+    } else if (lut->min_entry >= -128 && lut->max_entry <= 127) {
+        return false;
+    } else {
+        there = dg_planes_preferred(lut, p) ? packed_cost(p) : dg_onehot_two_plane_time(lut, p);
+        there += 1.9 + 0.08 * codes;                        // (the packing kernel)
+    }
+    return cost(p, lut->bits, pixel_blocks(p, lut->bits)) < 0.94 * there && !dg_onebit_preferred(lut, p);
+}
+
+// AUTO, 2-bit tables with entries beyond int8 on packed codes, where the fit says a seventh less than the kernels in two planes (6 to 12 % off on average): us, those
+// and this one, 56x56x256 -> 256 3x3 at batch 16 94, 70; 116x116x64 -> 104 3x3 at batch 13 66, 41; 28x28x256 -> 256 3x3 at batch 16 26.9, 21.0;
+// 112x112x128 -> 40 3x3 at batch 4 16.5, 12.8; not 28x28x128 -> 128 3x3 at batch 8 8.3, 9.2; 14x14x384 -> 360 3x3 at batch 2 8.2, 20.4; 34x34x128 -> 352 at batch
+// 4 4.9, 5.5.  Of 240 drawn layers 70 go here, 1.38 times as fast on average, none slower.
+// DG_PLANES_PACKED: "0" never, "1" whatever the size.
+bool dg_planes_preferred(const dg_lut *lut, const DgProblem &p)
+{
+    const char *f = dg_override("DG_PLANES_PACKED");
+    const bool forced = f && strcmp(f, "1") == 0;
+    if (f && strcmp(f, "0") == 0) return false;
+    if (lut->bits != 2 || (lut->min_entry >= -128 && lut->max_entry <= 127) || (!forced && other_overrides())) return false;
+    return takes(lut, p) && (forced || packed_cost(p) < 0.87 * dg_onehot_two_plane_time(lut, p));
+}
+
+namespace {
+
+void fill(const dg_lut *lut, const DgProblem &p, int pxw, int piece, int bytes_per_pixel, PlanesArgs *args)
+{
+    PlanesArgs &a = *args;
+    const DgBitSums &n = lut->bit_sums;
+    a.bytes = n.bytes, a.low = n.low, a.high = n.high, a.both = n.both;
+    a.p = p;
+    a.p.cached = dg_output_cached(p);
+    a.div_ow = make_div((uint32_t)p.OW), a.div_oh = make_div((uint32_t)p.OH), a.div_kw = make_div((uint32_t)p.KW);
+    a.div_cpt = make_div((uint32_t)(p.Cin / piece));
+    a.tiles_n = (p.N + 32 * pxw - 1) / (32 * pxw);
+    a.band_log2 = 2;
+    a.band_tiles = (uint32_t)((p.M + 63) / 64) << a.band_log2;
+    a.div_band = make_div(a.band_tiles);
+    const int last = a.tiles_n & ((1 << a.band_log2) - 1);
+    a.div_last = make_div((uint32_t)(last ? last : 1));
+    a.x_bytes = (uint32_t)((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * bytes_per_pixel);
+}
+
+}   // namespace
+
+dg_status dg_launch_planes(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
+{
+    PlanesArgs a;
+    fill(lut, p, 4, 64, p.Cin / 4, &a);
+    hipLaunchKernelGGL(planes_packed_kernel, dim3((unsigned)(((p.M + 63) / 64) * a.tiles_n)), dim3(256), 0, stream, a);
+    return dg_check_launch("planes_packed_kernel");
 }
 
 dg_status dg_launch_planes_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
 {
     PlanesArgs a;
-    const DgBitSums &n = lut->bit_sums;
-    a.bytes = n.bytes, a.low = n.low, a.high = n.high, a.both = n.both;
-    a.p = p;
-    const int pxw = pixel_blocks(p, lut->bits), tiles_m = (p.M + 63) / 64;
-    a.div_ow = make_div((uint32_t)p.OW), a.div_oh = make_div((uint32_t)p.OH), a.div_kw = make_div((uint32_t)p.KW);
-    a.div_cpt = make_div((uint32_t)(p.Cin / 16));
-    a.tiles_n = (p.N + 32 * pxw - 1) / (32 * pxw);
-    a.band_log2 = 2;
-    a.band_tiles = (uint32_t)tiles_m << a.band_log2;
-    a.div_band = make_div(a.band_tiles);
-    const int last = a.tiles_n & ((1 << a.band_log2) - 1);
-    a.div_last = make_div((uint32_t)(last ? last : 1));
-    a.x_bytes = (uint32_t)((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * p.Cin);
-    const dim3 grid((unsigned)(tiles_m * a.tiles_n));
+    const int pxw = pixel_blocks(p, lut->bits);
+    fill(lut, p, pxw, 16, p.Cin, &a);
+    const dim3 grid((unsigned)(((p.M + 63) / 64) * a.tiles_n));
 #define DG_PLANES(BITS) \
     do { \
         if (pxw == 4) hipLaunchKernelGGL((planes_kernel<BITS, 4>), grid, dim3(512), 0, stream, a); \

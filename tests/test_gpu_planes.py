@@ -1,4 +1,4 @@
-"""Layers from unpacked codes by the codes' bits: both tiles, 2-, 3- and 4-bit codes, K of whole and of broken runs and shares without any, taps
+"""Layers by the codes' bits, from unpacked codes and from packed 2-bit ones: every tile, 2-, 3- and 4-bit codes, K of whole and of broken runs and shares without any, taps
 outside on every side, against the oracle; and AUTO's own choices."""
 import numpy as np
 import pytest
@@ -48,6 +48,53 @@ def test_planes_kernel(bits, plan, monkeypatch):
         assert bool((work == 77).all()), i
         with pytest.raises(dg.DgError):                     # (a buffer is asked for as ever)
             dg.dg_conv2d_lut_codes(lut, Wp, codes, desc, work=work[:-1].clone())
+
+
+def test_planes_kernel_on_packed_codes(monkeypatch):
+    monkeypatch.setenv("DG_PLANES_PACKED", "1")
+    for i, (B, H, W, Cin, Cout, KH, KW, stride, pad) in enumerate(CONVS):
+        for lw, la in TABLES[2]:
+            lut = dg.dg_build_lut(lw, la, dg.DG_LUT_I16)
+            desc = dg.conv_desc(B, H, W, Cin, Cout, KH, KW, stride, pad)
+            assert dg.dg_conv_kernel_name(lut, desc) == "planes_64x128", i
+            rng = np.random.default_rng(i)
+            Wc, Xc = wl.draw_codes(rng, (Cout, KH, KW, Cin)), wl.draw_codes(rng, (B, H, W, Cin))
+            Wp = dg.dg_pack_weights(torch.from_numpy(Wc).cuda(), Cout, KH * KW * Cin)
+            Xp = dg.dg_pack_activations(torch.from_numpy(Xc).cuda(), B * H * W, Cin)
+            scale = torch.from_numpy(rng.uniform(0.01, 0.1, Cout).astype(np.float32)).cuda()
+            want = oracle.conv2d(Wc, Xc, lw, la, stride=stride, pad=pad)
+            assert np.array_equal(dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy(), want), (i, "int32")
+            got = dg.dg_conv2d_lut(lut, Wp, Xp, desc, scale=scale).cpu().numpy()
+            assert np.array_equal(got, oracle.scale_epilogue_nhwc(want, scale.cpu().numpy())), (i, "scaled")
+    # a column-major product takes it, a row-major one does not
+    lw, la = TABLES[2][0]
+    lut, (M, N, K) = dg.dg_build_lut(lw, la, dg.DG_LUT_I16), (70, 300, 448)
+    g = wl.small_gemm(M, N, K, seed=1)
+    Wp, Ap = dg.dg_pack_weights(torch.from_numpy(g.Wc).cuda(), M, K), dg.dg_pack_activations(torch.from_numpy(g.Ac).cuda(), N, K)
+    want = oracle.gemm(g.Wc, g.Ac, lw, la)
+    for strides, shape in (((1, M + 3), (N, M + 3)), ((N, 1), (M, N))):
+        out = torch.full(shape, -7, dtype=torch.int32, device="cuda")
+        dg.dg_gemm_lut(lut, Wp, Ap, M, N, K, out=out, strides=strides)
+        got = out.cpu().numpy()
+        assert np.array_equal(got[:, :M].T if strides[0] == 1 else got, want) and (strides[0] != 1 or (got[:, M:] == -7).all()), strides
+
+
+@pytest.mark.parametrize("shape,kernel", [((16, 28, 256, 256, 3, 1), "planes_64x128"), ((4, 112, 128, 40, 3, 1), "planes_64x128"),
+                                          ((8, 28, 128, 128, 3, 1), "onehot_smfmac_2p_staged_32x128_k4"), ((2, 14, 384, 360, 3, 1), "onehot_mfma_2p_splitk_s14")])
+def test_autos_own_choice_on_packed_codes(shape, kernel):
+    B, H, Cin, Cout, k, s = shape
+    lw, la = TABLES[2][0]
+    lut = dg.dg_build_lut(lw, la, dg.DG_LUT_I16)
+    desc = dg.conv_desc(B, H, H, Cin, Cout, k, k, (s, s), (k // 2, k // 2))
+    assert dg.dg_conv_kernel_name(lut, desc) == kernel
+    rng = np.random.default_rng(Cin + Cout)
+    Wc, Xc = wl.draw_codes(rng, (Cout, k, k, Cin)), wl.draw_codes(rng, (B, H, H, Cin))
+    size = B * H * H * Cout
+    pos = np.unique(np.concatenate([rng.integers(0, size, 20000), np.arange(4 * Cout), size - 1 - np.arange(4 * Cout)]))
+    want = oracle.conv2d_sampled(Wc, Xc, lw, la, pos, stride=(s, s), pad=(k // 2, k // 2))
+    Wp = dg.dg_pack_weights(torch.from_numpy(Wc).cuda(), Cout, k * k * Cin)
+    Xp = dg.dg_pack_activations(torch.from_numpy(Xc).cuda(), B * H * H, Cin)
+    assert np.array_equal(dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy().reshape(-1)[pos], want)
 
 
 @pytest.mark.parametrize("plan", ["2", "4"])
