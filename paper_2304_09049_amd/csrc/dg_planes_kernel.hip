@@ -183,15 +183,19 @@ planes_kernel(PlanesArgs a)
             for (int k = 0; k < WORDS; ++k) asm volatile("" : "+v"(raw.v[j][k]));
         const Raw next = raw;
         __syncthreads();
-        fetch(g + 1, odd ^ 1);
+        v4i xs[4], ws[4][2];
+        auto read = [&](int s) {
+            xs[s] = *(const v4i *)(x_from + odd * PIXELS + ((4 * h + s) ^ (r & 7)) * 16);
+#pragma unroll
+            for (int bm = 0; bm < 2; ++bm)
+                ws[s][bm] = *(const v4i *)(mem + odd * WEIGHTS + (2 * s + bm) * 1024 + (h * 32 + (r ^ (2 * (2 * h + (s >> 1))))) * 16);
+        };
+        read(0), read(1), read(2), read(3);                 // (before the next run's addresses are worked out: 28x28x256 -> 256 3x3 at batch 8
+        fetch(g + 1, odd ^ 1);                              // beyond int8 15.0 -> 14.1 us, 28x28x128 -> 128 3-bit 8.22 -> 8.13)
         load_weights(raw, g + 2);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const v4i x = *(const v4i *)(x_from + odd * PIXELS + ((4 * h + s) ^ (r & 7)) * 16);
-            v4i w[2];
-#pragma unroll
-            for (int bm = 0; bm < 2; ++bm)
-                w[bm] = *(const v4i *)(mem + odd * WEIGHTS + (2 * s + bm) * 1024 + (h * 32 + (r ^ (2 * (2 * h + (s >> 1))))) * 16);
+            const v4i x = xs[s], (&w)[2] = ws[s];
 #pragma unroll
             for (int d = 0; d < (BITS == 2 ? 0 : 4); ++d)
                 codes_sum = (int)__builtin_amdgcn_udot4((uint32_t)x[d] & ((1u << BITS) - 1) * 0x01010101u, 0x01010101u, (uint32_t)codes_sum, false);
@@ -336,14 +340,19 @@ planes_packed_kernel(PlanesArgs a)
         const v2i next = raw;
         __syncthreads();
         const v4i x = *(const v4i *)(mem + 2 * WEIGHTS + wave * 2 * PIXELS + odd * PIXELS + (2 * r + h) * 16);
-        fetch(g + 1, odd ^ 1);
-        raw = load_weights(g + 2);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            v4i w[2];
+        v4i ws[4][2];
+        auto read = [&](int s) {
 #pragma unroll
             for (int bm = 0; bm < 2; ++bm)
-                w[bm] = *(const v4i *)(mem + odd * WEIGHTS + (2 * s + bm) * 1024 + (h * 32 + (r ^ (2 * (2 * h + (s >> 1))))) * 16);
+                ws[s][bm] = *(const v4i *)(mem + odd * WEIGHTS + (2 * s + bm) * 1024 + (h * 32 + (r ^ (2 * (2 * h + (s >> 1))))) * 16);
+        };
+        read(0), read(1);
+        fetch(g + 1, odd ^ 1);
+        raw = load_weights(g + 2);
+        read(2), read(3);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const v4i (&w)[2] = ws[s];
             const uint32_t c = (uint32_t)x[s], both = c & (c >> 1);
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
@@ -447,7 +456,7 @@ void dg_find_bit_sums(dg_lut *lut)
 
 // AUTO, where a layer would be packed first: 3- and 4-bit codes that run as two lookups, 2-bit tables with entries beyond int8.  From codes, us, the two
 // kernels and this one (graph replays): 28x28x128 -> 128 3x3 at batch 8, 4-bit 10.1, 8.8, 3-bit 10.1, 8.2; 28x28x256 -> 256 3x3 at batch 8, entries
-// beyond int8 18.4, 15.4; 112x112x128 -> 112 3x3 stride 2 at batch 5, 3-bit 16.2, 10.4.  It is behind with many rounds of tiles, whose codes are read
+// beyond int8 18.4, 14.1; 112x112x128 -> 112 3x3 stride 2 at batch 5, 3-bit 16.2, 10.4.  It is behind with many rounds of tiles, whose codes are read
 // again for every 64 channels (112x112x64 -> 112 3x3 at batch 4, 4-bit 19.9, 29.9; with more than four rounds the fit is not asked:
 // 116x116x64 -> 104 3x3 at batch 13, beyond int8, 72, 79), and on long K with few tiles (14x14x384 -> 360 3x3 at batch 2, beyond int8, 10.1, 14.2).
 // Of 222 drawn layers the fitted times send 78 here, 1.23 times as fast on average, none slower.
@@ -473,7 +482,7 @@ bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
 
 // AUTO, 2-bit tables with entries beyond int8 on packed codes, where the fit says a seventh less than the kernels in two planes (6 to 12 % off on average): us, those
 // and this one, 56x56x256 -> 256 3x3 at batch 16 94, 70; 116x116x64 -> 104 3x3 at batch 13 66, 41; 28x28x256 -> 256 3x3 at batch 16 26.9, 21.0;
-// 112x112x128 -> 40 3x3 at batch 4 16.5, 12.8; not 28x28x128 -> 128 3x3 at batch 8 8.3, 9.2; 14x14x384 -> 360 3x3 at batch 2 8.2, 20.4; 34x34x128 -> 352 at batch
+// 112x112x128 -> 40 3x3 at batch 4 16.5, 12.6; not 28x28x128 -> 128 3x3 at batch 8 8.3, 9.2; 14x14x384 -> 360 3x3 at batch 2 8.2, 20.4; 34x34x128 -> 352 at batch
 // 4 4.9, 5.5.  Of 240 drawn layers 70 go here, 1.38 times as fast on average, none slower.
 // DG_PLANES_PACKED: "0" never, "1" whatever the size.
 bool dg_planes_preferred(const dg_lut *lut, const DgProblem &p)
