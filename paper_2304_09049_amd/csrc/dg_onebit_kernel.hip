@@ -25,7 +25,7 @@
 // random operands take 18.4 at 1.77 GHz, constant ones 13.5 at 2.4), by the start, the end and lone wavefronts' issue slots on those of a few
 // microseconds: a run of the 64 x 128 tile takes 0.5 us then.  The staged sparse kernel, this one (packed codes, graph replays, us):
 //   8192-cube 648, 356          56x56x256 -> 256 3x3 at batch 16 47.1, 30.6          28x28x512 -> 512 3x3 at batch 16 46.1, 29.9
-//   28x28x128 -> 128 3x3 at batch 32 12.2, 8.6          28x28x256 -> 256 3x3 at batch 8 10.9, 8.4          3569 x 7478 x 704 81.5, 28.3
+//   28x28x128 -> 128 3x3 at batch 32 12.2, 8.5          28x28x256 -> 256 3x3 at batch 8 10.9, 7.9          3569 x 7478 x 704 81.5, 28.3
 // (the last by its stores too: dg_output_cached).
 #include "dg_lds_dma.h"
 #include "dg_onehot_kernel.h"
@@ -225,12 +225,12 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
         asm volatile("" : "+v"(raw));
         const v4i next = raw;
         __syncthreads();
+        Words t[2];
+        read(t[0], odd, 0);                                 // (before the next run's addresses are worked out, which take longer: 28x28x256 -> 256
+        read(t[1], odd, 1);                                 // 3x3 at batch 8 8.2 -> 7.9 us, 28x28x128 -> 128 3x3 at batch 32 8.6 -> 8.5)
         fetch(g + 1, odd ^ 1);
         raw = load_weights(g + 2);
         const uint32_t to = (odd ^ 1) * WEIGHTS;
-        Words t[2];
-        read(t[0], odd, 0);
-        read(t[1], odd, 1);
         multiply(t[0]);
         read(t[0], odd, 2);
         expand_half(next, 0, to);
