@@ -225,7 +225,8 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *   DG_PLANES_PACKED "0": AUTO never does so on packed 2-bit codes (entries beyond int8), "1": whatever the size
  *   DG_TWOPOWER      "0": AUTO never takes products of levels to the FP6 / FP4 instruction; "1", "2", "4": whatever the size, in tiles of 64 x 128,
  *                    128 x 256 or 128 x 512, "12": 64 x 128 with K shared by two; any other value counts as not set
- *   DG_ONEBIT_CODES  "0": AUTO never takes them there from unpacked codes, "1": wherever a kernel packs while loading
+ *   DG_ONEBIT_CODES  "0": AUTO never takes them there from unpacked codes, "1": wherever a kernel packs while loading, "2": also wherever that
+ *                    kernel would be run on packed codes
  *   DG_PERM_PLAN     index of the permute kernel's tile shape
  */
 typedef enum {
@@ -298,7 +299,8 @@ dg_status dg_conv2d_lut(const dg_lut *lut, const void *Wp_dev, const void *Xp_de
  * Xp_work_dev (device, work_bytes >= dg_packed_bytes_bits(B*H*W, Cin, bits), else DG_ERR_BUFFER; DG_ERR_NULL if it
  * is needed and NULL), is packed into it by the packing kernel and then run as dg_conv2d_lut would run it, on the same stream (but AUTO
  * reads the codes as they are, and leaves the buffer alone, on layers of a few microseconds with 3- and 4-bit codes and evenly
- * spaced levels, and with 2-bit tables of products beyond int8 whose activation level 0 is 0, where Cin % 64 == 0; of a
+ * spaced levels, with 2-bit tables of products beyond int8 whose activation level 0 is 0, and of two one-bit lookups where few
+ * taps and channels read a pixel, where Cin % 64 == 0; of a
  * 1x1 layer with a stride and no padding only the pixels it reads are packed, [B][OH][OW][Cin/4] at the start of the
  * buffer, and the layer runs on those without the stride).
  * Outputs, scale, variant and the other errors as dg_conv2d_lut; the results are identical to dg_pack_activations

@@ -538,7 +538,7 @@ namespace {
 // the library's own choice for the problem (or the variant the caller names) has such a form: the one-hot split-K kernel,
 // the tiled kernels in their narrow tiles (dense, and sparse), the kernel for one or two columns, the stationary-weight
 // kernel, and the one for channel counts that are no multiple of 32.
-enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs, Ragged, OneBit, Planes };
+enum class Fuse { None, OneHot, OneHotSparse, SmallN, SparseWs, Ragged, OneBit, OneBitWork, Planes };
 
 // A 1x1 layer with a stride and no padding reads one input pixel in sh * sw: where the packing is not fused only those
 // are packed (2-bit codes in whole 16-code groups), and the layer then runs on them without a stride -- 56x56x256 -> 512
@@ -598,6 +598,9 @@ Fuse fuses_packing(const dg_lut *lut, const DgProblem &p_codes, dg_kernel varian
         return Fuse::OneBit;
     if (variant == DG_KERNEL_AUTO && fuse == Fuse::None && !packs_strided_pixels(lut, p_codes) && dg_planes_codes_preferred(lut, p_codes))
         return Fuse::Planes;
+    if (variant == DG_KERNEL_AUTO && fuse == Fuse::None && !packs_strided_pixels(lut, p_codes) && dg_onebit_codes_spare_packing(lut, p_codes) &&
+        pick_kernel(lut, p_codes, variant) == Pick::OneBit)
+        return Fuse::OneBitWork;
     return fuse;
 }
 
@@ -614,7 +617,7 @@ dg_status run_codes(const char *name, const dg_lut *lut, DgProblem &p, const uin
 {
     p.Xp = codes;
     const Fuse fuse = fuses_packing(lut, p, variant);
-    if (fuse == Fuse::Planes) {                             // (such layers ask for a work buffer all the same)
+    if (fuse == Fuse::Planes || fuse == Fuse::OneBitWork) {  // (such layers ask for a work buffer all the same)
         if (!work) return dg_fail(DG_ERR_NULL, "%s: NULL buffer", name);
         const size_t need = dg_packed_bytes_bits(rows, row_codes, lut->bits);
         if (work_bytes < need) return dg_fail(DG_ERR_BUFFER, "%s: packed buffer has %zu bytes, %zu needed", name, work_bytes, need);
@@ -625,7 +628,8 @@ dg_status run_codes(const char *name, const dg_lut *lut, DgProblem &p, const uin
     case Fuse::SmallN: return dg_launch_smalln_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::SparseWs: return dg_launch_sparse_ws_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::Ragged: return dg_launch_ragged(lut, p, true, (hipStream_t)hip_stream);
-    case Fuse::OneBit: return dg_launch_onebit_codes(lut, p, (hipStream_t)hip_stream);
+    case Fuse::OneBit:
+    case Fuse::OneBitWork: return dg_launch_onebit_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::Planes: return dg_launch_planes_codes(lut, p, (hipStream_t)hip_stream);
     case Fuse::None: break;
     }
@@ -655,7 +659,8 @@ const char *codes_name(const dg_lut *lut, const DgProblem &p, dg_kernel variant)
     case Fuse::SmallN: return "codes_smalln";
     case Fuse::SparseWs: return "codes_onehot_smfmac_ws_32xK";
     case Fuse::Ragged: return dg_ragged_config_name(lut, p, true);
-    case Fuse::OneBit: return "codes_onebit_64x128";
+    case Fuse::OneBit:
+    case Fuse::OneBitWork: return "codes_onebit_64x128";
     case Fuse::Planes: return dg_planes_codes_config_name(lut, p);
     case Fuse::None: break;
     }

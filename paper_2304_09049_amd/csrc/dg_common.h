@@ -194,6 +194,7 @@ dg_status dg_launch_planes(const dg_lut *lut, const DgProblem &p, hipStream_t st
 double dg_onehot_nibble_time(const dg_lut *lut, const DgProblem &p, double codes);
 double dg_onehot_two_plane_time(const dg_lut *lut, const DgProblem &p);
 bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stationary);    // p.Xp: codes one per byte
+bool dg_onebit_codes_spare_packing(const dg_lut *lut, const DgProblem &p);                 // in place of packing first, where AUTO then runs the one-bit kernel
 dg_status dg_launch_onebit_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 bool dg_ragged_preferred(const dg_lut *lut, const DgProblem &p, bool codes);      // taps of no whole 32-position groups; `codes`: p.Xp one per byte
 const char *dg_ragged_config_name(const dg_lut *lut, const DgProblem &p, bool codes);

@@ -179,3 +179,27 @@ def test_override_values_that_are_none(value, monkeypatch):
     out = torch.full((2, 20, 13, 132), 1 << 30, dtype=torch.int32, device="cuda")
     dg.dg_conv2d_lut(dg.dg_build_lut(lw, la), Wp, Xp, desc, out=out)
     assert np.array_equal(out.cpu().numpy(), oracle.conv2d(c.Wc, c.Ac, lw, la, stride=(1, 1), pad=(1, 1)))
+
+
+@pytest.mark.parametrize("layer", [(1, 300, 128, 128, 128, 3, 2), (14, 113, 109, 128, 60, 3, 2), (39, 28, 28, 384, 232, 1, 1), (3, 57, 55, 128, 132, 5, 1)])
+def test_codes_in_place_of_packing(layer, monkeypatch):
+    """Layers that are not packed first: the work buffer is asked for and left alone, higher bits of a code count for nothing."""
+    B, H, W, Cin, Cout, k, s = layer
+    if k == 5:
+        monkeypatch.setenv("DG_ONEBIT_CODES", "2")          # (a layer that is packed first otherwise)
+    lw, la = (-2, -1, 0, 1), (0, 1, 2, 3)
+    lut, desc = dg.dg_build_lut(lw, la), dg.conv_desc(B, H, W, Cin, Cout, k, k, (s, s), (k // 2, k // 2))
+    OH, OW = ((x + 2 * (k // 2) - k) // s + 1 for x in (H, W))
+    rng = np.random.default_rng(H + Cout)
+    Wc, Xc = wl.draw_codes(rng, (Cout, k, k, Cin)), wl.draw_codes(rng, (B, H, W, Cin))
+    Wp, X = dg.dg_pack_weights(torch.from_numpy(Wc).cuda(), Cout, k * k * Cin), torch.from_numpy(Xc + 4 * (Xc ^ 1)).cuda()
+    work = torch.full((B * H * W * Cin // 4,), 77, dtype=torch.uint8, device="cuda")
+    size = B * OH * OW * Cout
+    pos = np.unique(np.concatenate([rng.integers(0, size, 20000), np.arange(4 * Cout), size - 1 - np.arange(4 * Cout)]))
+    want = oracle.conv2d_sampled(Wc, Xc, lw, la, pos, stride=(s, s), pad=(k // 2, k // 2))
+    assert dg.dg_conv_codes_kernel_name(lut, desc) == "codes_onebit_64x128"
+    got = dg.dg_conv2d_lut_codes(lut, Wp, X, desc, work=work).cpu().numpy().reshape(-1)
+    assert np.array_equal(got[pos], want) and bool((work == 77).all())
+    if k != 5:
+        with pytest.raises(dg.DgError, match="needed"):
+            dg.dg_conv2d_lut_codes(lut, Wp, X, desc, work=work[:-16])

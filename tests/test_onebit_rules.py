@@ -102,3 +102,11 @@ def test_shapes():
     assert dg.dg_conv_kernel_name(lut, desc, "onehot_smfmac") == "onehot_smfmac_staged_32x224"
     assert dg.dg_conv_kernel_name(lut, desc, "onehot_mfma").startswith("onehot_mfma_")
     assert not dg.dg_conv_codes_kernel_name(lut, dg.conv_desc(1, 140, 128, 64, 48, 3, 3, (1, 1), (1, 1)), "onehot_smfmac").startswith("codes_onebit")
+
+
+def test_codes_in_place_of_packing():
+    # 150 tiles, five readings of a pixel's codes, 1152 positions; K that two halves of a workgroup share; a 1x1 layer whose pixels are packed sparsely
+    assert conv(1, 300, 128, 128, 128, 3, 2)[1] == "codes_onebit_64x128" and conv(1, 296, 128, 128, 128, 3, 2)[1] == "onebit_64x128"
+    assert conv(1, 300, 256, 128, 128, 3, 2)[1] == "codes_onebit_64x128" and conv(1, 300, 256, 128, 132, 3, 2)[1] == "onebit_64x128"
+    assert conv(1, 400, 512, 1152, 64, 1)[1] == "codes_onebit_64x128" and conv(1, 400, 512, 1216, 64, 1)[1] == "onebit_64x256_64x128"
+    assert conv(6, 54, 64, 256, 88, 3, 2)[1] == "onebit_64x128_k2" and conv(16, 56, 56, 256, 256, 3)[1] == "onebit_64x256_64x128"
