@@ -300,7 +300,7 @@ dg_status dg_conv2d_lut(const dg_lut *lut, const void *Wp_dev, const void *Xp_de
  * is needed and NULL), is packed into it by the packing kernel and then run as dg_conv2d_lut would run it, on the same stream (but AUTO
  * reads the codes as they are, and leaves the buffer alone, on layers of a few microseconds with 3- and 4-bit codes and evenly
  * spaced levels, with 2-bit tables of products beyond int8 whose activation level 0 is 0, and of two one-bit lookups where few
- * taps and channels read a pixel, where Cin % 64 == 0; of a
+ * taps and channels read a pixel, where Cin % 64 == 0 and the output does not overlap the codes; of a
  * 1x1 layer with a stride and no padding only the pixels it reads are packed, [B][OH][OW][Cin/4] at the start of the
  * buffer, and the layer runs on those without the stride).
  * Outputs, scale, variant and the other errors as dg_conv2d_lut; the results are identical to dg_pack_activations

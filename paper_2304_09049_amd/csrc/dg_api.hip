@@ -611,16 +611,27 @@ DgProblem without_stride(const DgProblem &p)
     return c;
 }
 
+// Whether the output's memory meets the `bytes` of the codes.  A layer that is packed first has read its codes before its first result is stored, so
+// a caller may let the results take their place.
+bool output_meets_codes(const DgProblem &p, const uint8_t *codes, int64_t bytes)
+{
+    const int64_t along_m = (p.M - 1) * p.stride_cm, along_n = (p.N - 1) * p.stride_cn;
+    const int64_t first = (along_m < 0 ? along_m : 0) + (along_n < 0 ? along_n : 0), last = (along_m > 0 ? along_m : 0) + (along_n > 0 ? along_n : 0);
+    const uintptr_t out = p.scale ? (uintptr_t)p.Cf : (uintptr_t)p.C, at = (uintptr_t)codes;
+    return out + 4 * first < at + bytes && at < out + 4 * (last + 1);
+}
+
 // Launch the fused form, or pack into the work buffer and run the problem as the two-call path would.
 dg_status run_codes(const char *name, const dg_lut *lut, DgProblem &p, const uint8_t *codes, int64_t rows, int64_t row_codes,
                     void *work, size_t work_bytes, dg_kernel variant, void *hip_stream)
 {
     p.Xp = codes;
-    const Fuse fuse = fuses_packing(lut, p, variant);
+    Fuse fuse = fuses_packing(lut, p, variant);
     if (fuse == Fuse::Planes || fuse == Fuse::OneBitWork) {  // (such layers ask for a work buffer all the same)
         if (!work) return dg_fail(DG_ERR_NULL, "%s: NULL buffer", name);
         const size_t need = dg_packed_bytes_bits(rows, row_codes, lut->bits);
         if (work_bytes < need) return dg_fail(DG_ERR_BUFFER, "%s: packed buffer has %zu bytes, %zu needed", name, work_bytes, need);
+        if (output_meets_codes(p, codes, rows * row_codes)) fuse = Fuse::None;
     }
     switch (fuse) {
     case Fuse::OneHot: return dg_launch_onehot_codes(lut, p, (hipStream_t)hip_stream);

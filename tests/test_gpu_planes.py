@@ -148,3 +148,26 @@ def test_tables_of_other_forms_are_packed_first(monkeypatch):
     for i, lut in enumerate(tables):
         assert not dg.dg_conv_codes_kernel_name(lut, desc).startswith("codes_planes"), i
     assert dg.dg_conv_codes_kernel_name(dg.dg_build_lut_bits(4, list(range(-8, 8)), list(range(16))), desc, "onehot_mfma").startswith("onehot_mfma")
+
+
+@pytest.mark.parametrize("bits,shape,table", [(4, (3, 28, 128, 128, 3, 1), None), (3, (4, 28, 128, 96, 3, 1), None), (2, (6, 28, 384, 64, 3, 1), None),
+                                              (2, (32, 56, 192, 96, 1, 1), ((-2, -1, 0, 1), (0, 1, 2, 3)))])
+@pytest.mark.parametrize("ahead", [0, 4096])
+def test_results_in_the_codes_place(bits, shape, table, ahead):
+    """Layers that ask for a work buffer have read their codes before they store: results over the codes, and over their last bytes alone, are the same."""
+    B, H, Cin, Cout, k, s = shape
+    lw, la = (list(x) for x in table or TABLES[bits][0])
+    lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I16)
+    desc = dg.conv_desc(B, H, H, Cin, Cout, k, k, (s, s), (k // 2, k // 2))
+    assert dg.dg_conv_codes_kernel_name(lut, desc).startswith("codes_planes" if table is None else "codes_onebit")
+    rng = np.random.default_rng(Cout)
+    Wc, Xc = wl.draw_codes(rng, (Cout, k, k, Cin), nlev=1 << bits), wl.draw_codes(rng, (B, H, H, Cin), nlev=1 << bits)
+    want = oracle.conv2d(Wc, Xc, lw, la, stride=(s, s), pad=(k // 2, k // 2))
+    Wp = dg.dg_pack_codes_bits(torch.from_numpy(Wc).cuda(), Cout, k * k * Cin, bits)
+    work = torch.empty(dg.dg_packed_bytes_bits(B * H * H, Cin, bits), dtype=torch.uint8, device="cuda")
+    start = Xc.size - ahead if ahead else 0                 # of the results
+    memory = torch.zeros(max(Xc.size, start + 4 * want.size), dtype=torch.uint8, device="cuda")
+    codes, out = memory[: Xc.size].view(Xc.shape), memory[start : start + 4 * want.size].view(torch.int32).view(want.shape)
+    codes.copy_(torch.from_numpy(Xc))
+    dg.dg_conv2d_lut_codes(lut, Wp, codes, desc, work=work, out=out)
+    assert np.array_equal(out.cpu().numpy(), want)
