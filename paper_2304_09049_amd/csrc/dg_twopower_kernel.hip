@@ -76,6 +76,10 @@ twopower_kernel(TwoPowerArgs a)
     constexpr int PIXELS = WN * 2048, LOADS = 2 * WN;
     constexpr int SEGMENTS = 2 * BM / WAVES;                // 16-byte pieces of weights a thread expands per run
     static_assert(SEGMENTS * WAVES == 2 * BM, "whole pieces");
+    // A block's place in LDS as an offset of the step's one address.  Put in with the lane, the compiler keeps an address per block, and the tile of
+    // 128 x 256 reloads two from scratch in each run, whose waits are for the next run's loads as well: 4873 x 7116 x 4672 column-major 195 -> 176 us,
+    // 3992 x 1839 x 2944 37.5 -> 32.2, row-major level.  (The others have the registers; 2275 x 903 x 4544 by rows is 4 % longer so.)
+    constexpr bool ONE_BASE = BM == 4 && WAVES == 4;
     __shared__ uint4 s_mem[KS * SHARE / 16];
     const DgProblem &p = a.p;
     dg_fetch_arguments<sizeof(a)>();
@@ -185,8 +189,11 @@ twopower_kernel(TwoPowerArgs a)
         for (int bn = 0; bn < WN; ++bn) t.x[bn] = *(const uint2 *)(x + bn * 2048);
 #pragma unroll
         for (int bm = 0; bm < BM; ++bm) {
-            const v4i lo = *(const v4i *)(w + ((s * BM + bm) * 64 + (lane ^ (2 * s))) * 16);
-            const v2i hi = *(const v2i *)(w + WIDE + ((s * BM + bm) * 64 + (lane ^ (4 * s))) * 8);
+            const int block = (s * BM + bm) * 64;
+            const char *w16 = w + (block + (lane ^ (2 * s))) * 16, *w8 = w + WIDE + (block + (lane ^ (4 * s))) * 8;
+            if constexpr (ONE_BASE) w16 = w + (lane ^ (2 * s)) * 16 + block * 16, w8 = w + WIDE + (lane ^ (4 * s)) * 8 + block * 8;
+            const v4i lo = *(const v4i *)w16;
+            const v2i hi = *(const v2i *)w8;
             t.w[bm] = (i32x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], 0, 0};
         }
     };

@@ -1,19 +1,24 @@
-"""Kernels' machine code, compiled here: what the staged kernel's loads rely on, the registers that its narrow tiles may take, and how the kernel
-for ragged channel counts reads its table."""
+"""Kernels' machine code, compiled here: what the staged kernel's loads rely on, the registers that its narrow tiles may take, how the kernel
+for ragged channel counts reads its table, and that no main loop of the kernel for products of levels reloads from scratch."""
 import os
 import re
 import subprocess
 
 import pytest
 
-from paper_2304_09049_amd.build import HIPCC_FLAGS
+from paper_2304_09049_amd.build import CSRC, HIPCC_FLAGS
 
 
 def compile_forms(tmp_path, forms, *flags, header="dg_sparse_staged_kernel.h", kernel="smfmac_staged_kernel", arguments="Args"):
     """The listing of a kernel's instantiations (the staged kernel's: <WM, WN, SKW, TURNS, HALF, NIB, TWO, SHORT>)."""
-    source, listing = tmp_path / "forms.hip", tmp_path / "forms.s"
+    source = tmp_path / "forms.hip"
     source.write_text(f'#include "{header}"\n' +
                       "".join(f"template __global__ void dgoh::{kernel}<{f}>(dgoh::{arguments});\n" for f in forms))
+    return compile_listing(tmp_path, source, *flags)
+
+
+def compile_listing(tmp_path, source, *flags):
+    listing = tmp_path / "forms.s"
     common = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *common, *flags, "--cuda-device-only", "-S", str(source), "-o", str(listing)],
                    check=True, stderr=subprocess.DEVNULL)
@@ -75,3 +80,16 @@ def test_ragged_wavefronts_eight_to_a_simd(ragged_listing):
         if wm == wn == "1":
             assert scalars <= 80 and vectors <= (64 if ch == "1" else 512), (name, scalars, vectors)
         assert code.count("vmcnt(") <= 16, (name, code.count("vmcnt("))
+
+
+def test_twopower_loops_keep_their_registers(tmp_path):
+    """The tiles of 128 channels take all 256 registers.  A reload from scratch in the main loop waits for every load before it: for the next run's
+    pixels and weights, which are to arrive while this run is multiplied."""
+    text = compile_listing(tmp_path, os.path.join(CSRC, "dg_twopower_kernel.hip"))
+    kernels = re.findall(r"^(\S*twopower_kernelILi\d\S+):(.*?)^\.Lfunc_end", text, re.M | re.S)
+    assert len(kernels) == 4 * 2
+    for name, code in kernels:
+        loops = [body for _, body in re.findall(r"^(\.LBB\d+_\d+):[^\n]*Inner Loop(.*?)s_cbranch_\w+ \1$", code, re.M | re.S)]
+        mains = [body for body in loops if "s_barrier" in body and body.count("v_mfma") >= 16]
+        assert len(mains) == 1, name
+        assert "scratch_" not in mains[0], name
