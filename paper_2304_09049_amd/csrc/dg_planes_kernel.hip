@@ -385,12 +385,13 @@ int planes_override()
     return -1;
 }
 
-// us, fitted to 222 layers (2 to 3 % off on average): once, a round of workgroups (one to a compute unit), a run of one, an MB of output.
+// us: once, a round of workgroups (one to a compute unit), a run of one, an MB of output.  Fitted to 222 layers for 2-bit codes, to 700 whichever kernel is the
+// shorter for 3- and 4-bit ones (3 to 4 % off on average, 19 % at most).
 double cost(const DgProblem &p, int bits, int pxw)
 {
     static const double fits[3][2][4] = {{{1.6, 3.2, 1.28, 0.165}, {2.0, 2.7, 1.06, 0.18}},
-                                         {{1.7, 2.5, 1.23, 0.138}, {1.9, 2.4, 1.10, 0.139}},
-                                         {{1.7, 2.45, 1.41, 0.153}, {2.0, 2.2, 1.29, 0.153}}};
+                                         {{1.97, 2.28, 1.22, 0.24}, {2.17, 2.22, 1.04, 0.21}},
+                                         {{2.04, 2.15, 1.39, 0.25}, {2.32, 2.04, 1.25, 0.22}}};
     const double *const f = fits[bits - 2][pxw == 4];
     const int64_t units = dg_simd_count() / 4, rounds = (tiles_of(p, pxw) + units - 1) / units, shares = 8 / pxw;
     const double runs = (double)((((int64_t)p.K + 127) / 128 + shares - 1) / shares);
@@ -458,8 +459,10 @@ void dg_find_bit_sums(dg_lut *lut)
 // kernels and this one (graph replays): 28x28x128 -> 128 3x3 at batch 8, 4-bit 10.1, 8.8, 3-bit 10.1, 8.2; 28x28x256 -> 256 3x3 at batch 8, entries
 // beyond int8 18.4, 14.1; 112x112x128 -> 112 3x3 stride 2 at batch 5, 3-bit 16.2, 10.4.  It is behind with many rounds of tiles, whose codes are read
 // again for every 64 channels (112x112x64 -> 112 3x3 at batch 4, 4-bit 19.9, 29.9; with more than four rounds the fit is not asked:
-// 116x116x64 -> 104 3x3 at batch 13, beyond int8, 72, 79), and on long K with few tiles (14x14x384 -> 360 3x3 at batch 2, beyond int8, 10.1, 14.2).
-// Of 222 drawn layers the fitted times send 78 here, 1.23 times as fast on average, none slower.
+// 116x116x64 -> 104 3x3 at batch 13, beyond int8, 72, 79), on long K with few tiles (14x14x384 -> 360 3x3 at batch 2, beyond int8, 10.1, 14.2), and with 3-
+// and 4-bit codes where the split-K kernel has few blocks to a compute unit and a share here one run (315 x 128 -> 1564, 4-bit, 5.8, 6.7; 36x36x64 -> 352
+// stride 2 at batch 17, 4-bit, 8.2, 10.0; 734 x 64 -> 424, 3-bit, 6.1, 6.3): the fit has to say an eighth less there.  Of the 1400 layers of 3- and 4-bit codes
+// to which it was fitted, inputs changing from pass to pass, it sends 277 here, 1.29 times as fast on average, none longer.
 bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
 {
     const int forced = planes_override();
@@ -477,7 +480,8 @@ bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
         there = dg_planes_preferred(lut, p) ? packed_cost(p) : dg_onehot_two_plane_time(lut, p);
         there += 1.9 + 0.08 * codes;                        // (the packing kernel)
     }
-    return cost(p, lut->bits, pixel_blocks(p, lut->bits)) < 0.94 * there && !dg_onebit_preferred(lut, p);
+    const double margin = lut->bits == 2 ? 0.94 : (p.K <= 256 ? 0.88 : 0.92);
+    return cost(p, lut->bits, pixel_blocks(p, lut->bits)) < margin * there && !dg_onebit_preferred(lut, p);
 }
 
 // AUTO, 2-bit tables with entries beyond int8 on packed codes, where the fit says a seventh less than the kernels in two planes (6 to 12 % off on average): us, those
