@@ -615,11 +615,14 @@ bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stati
 
 // The same in place of the packing kernel and this one on packed codes.  A tile of 64 x 128 reads a pixel's codes once per filter tap and 64 channels, four
 // times the bytes of packed ones: where that is five times or less (1x1 layers of up to 320 channels, 3x3 ones of stride 2 and up to 128) the spared
-// launch and pass are more.  us, both kernels, this one (input in L2; then changing from pass to pass): 56x56x192 -> 192 at batch 23 17.7, 13.2; 19.5,
-// 14.0; 28x28x512 -> 208 at batch 32 12.2, 9.5; 13.6, 10.9; 112x112x128 -> 96 3x3 stride 2 at batch 14 16.5, 14.1; 18.1, 14.6; 56x56x128 -> 120 3x3 stride 2 at
-// batch 15 (184 tiles) 11.8, 10.2; 13.0, 11.9.  Not 56x56x128 -> 64 3x3 at batch 12 (nine times) 9.3, 9.7; nor with fewer tiles (12 at stride 2, 148,
-// 9.1, 9.4), with more than 1152 positions (56x56x256 -> 96 3x3 stride 2 at batch 23 16.2, 18.5) or K that two halves of a workgroup
-// share (54x64x256 -> 88 3x3 stride 2 at batch 6 10.3, 14.3).  Of 108 such layers 1.19 times as fast on average; input changing, six were 2 to 7 % longer.
+// launch and pass are more.  us, both kernels, this one, inputs changing from pass to pass: 28x28x512 -> 208 at batch 32 13.6, 10.9; 112x112x128 -> 96 3x3
+// stride 2 at batch 14 18.1, 14.6; 56x56x128 -> 120 3x3 stride 2 at batch 15 (184 tiles) 13.0, 11.9.  Not 56x56x128 -> 64 3x3 at batch 12 (nine times) 9.3, 9.7;
+// nor with fewer tiles (12 at stride 2, 148, 9.1, 9.4), with more than 1152 positions (56x56x256 -> 96 3x3 stride 2 at batch 23 16.2, 18.5) or K that two
+// halves of a workgroup share (54x64x256 -> 88 3x3 stride 2 at batch 6 10.3, 14.3).
+// Nor where several tiles of channels read the codes in many rounds of tiles, which wide tiles of packed codes make fewer of and whose codes fall out of the
+// caches: two such tiles of channels read them up to six rounds, more up to four (56x56x512 -> 296 at batch 10, 1225 tiles, 18.5, 20.8; 112x112x384 -> 260 at
+// batch 14, 6860, 62, 86; 112x112x576 -> 112 at batch 19, 3724, 59, 65; one tile of channels is ahead whatever the rounds).  Of 852 layers within
+// the other lines 319 are within these, 1.35 times as fast on average, none longer; 84 of the others were 2 to 39 % longer.
 // DG_ONEBIT_CODES: 2 wherever this kernel would be run on packed codes.
 bool dg_onebit_codes_spare_packing(const dg_lut *lut, const DgProblem &p)
 {
@@ -627,8 +630,9 @@ bool dg_onebit_codes_spare_packing(const dg_lut *lut, const DgProblem &p)
     const bool forced = f && strcmp(f, "2") == 0;
     if (!takes(lut, p) || p.stride_cm != 1 || p.Qp || (int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * p.Cin >= (int64_t)1 << 31) return false;
     if (f || onebit_override() >= 0) return forced;
-    return tiles_of(p, 1) >= 150 && p.K <= 1152 && onebit_plan(p).ks == 1 &&
-           (int64_t)p.KH * p.KW * (((int64_t)p.M + 63) / 64) <= 5 * (int64_t)p.sh * p.sw;
+    const int64_t t1 = tiles_of(p, 1), tm = ((int64_t)p.M + 63) / 64, units = dg_simd_count() / 4, reads = p.KH * p.KW * tm, strides = (int64_t)p.sh * p.sw;
+    if (t1 < 150 || p.K > 1152 || onebit_plan(p).ks != 1 || reads > 5 * strides) return false;
+    return tm == 1 || t1 <= (reads <= 2 * strides ? 6 : 4) * units;
 }
 
 dg_status dg_launch_onebit_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream)

@@ -151,7 +151,7 @@ def test_tables_of_other_forms_are_packed_first(monkeypatch):
 
 
 @pytest.mark.parametrize("bits,shape,table", [(4, (3, 28, 128, 128, 3, 1), None), (3, (4, 28, 128, 96, 3, 1), None), (2, (6, 28, 384, 64, 3, 1), None),
-                                              (2, (32, 56, 192, 96, 1, 1), ((-2, -1, 0, 1), (0, 1, 2, 3)))])
+                                              (2, (14, 112, 128, 96, 3, 2), ((-2, -1, 0, 1), (0, 1, 2, 3)))])
 @pytest.mark.parametrize("ahead", [0, 4096])
 def test_results_in_the_codes_place(bits, shape, table, ahead):
     """Layers that ask for a work buffer have read their codes before they store: results over the codes, and over their last bytes alone, are the same."""
