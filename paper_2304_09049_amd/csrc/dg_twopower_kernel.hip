@@ -23,6 +23,7 @@
 #include "dg_lds_dma.h"
 #include "dg_onehot_kernel.h"
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <numeric>
@@ -391,7 +392,9 @@ struct TwoPowerPlan {
 };
 
 // What they cost was fitted to 308 products of 1.2 to 120 GOP, us (5 % off on average): of the four the one that this says is shortest is 0.6 % behind the
-// shortest measured on average, 16 % at most.
+// shortest measured on average, 16 % at most.  The fit has no short K with outputs beyond 150 MB: there 128 x 256 stores in bursts (us, one-hot kernels, 64 x 128,
+// 128 x 256; column-major outputs, inputs changing: 3889 x 20227 x 384 107, 80, 135; 6977 x 7871 x 384 85, 60, 97; 5159 x 9628 x 576 93, 64, 95) and is behind 64 x 128
+// below K = 640: of 27 such products that is 20 % shorter on average, 41 % at most, one 2 % longer; at 640 and 768 the two are level.
 const TwoPowerPlan PLANS[] = {
     {2, 1, 4, 1, "twopower_64x128", 0.809, 0.647, 0.0, 0.108, 3.9},
     {2, 1, 4, 2, "twopower_64x128_k2", 0.641, 0.611, 0.3, 0.179, 3.75},
@@ -404,6 +407,8 @@ int64_t tiles_of(const DgProblem &p, const TwoPowerPlan &q)
     const int rows = 32 * q.bm, cols = 32 * q.wn * q.waves;
     return (((int64_t)p.M + rows - 1) / rows) * (((int64_t)p.N + cols - 1) / cols);
 }
+
+bool suits(const DgProblem &p, const TwoPowerPlan &q) { return q.bm == 2 || q.waves == 8 || p.K >= 640; }
 
 double cost(const DgProblem &p, const TwoPowerPlan &q)
 {
@@ -431,8 +436,16 @@ const TwoPowerPlan &twopower_plan(const DgProblem &p)
     }
     const TwoPowerPlan *best = PLANS;
     for (const TwoPowerPlan &q : PLANS)
-        if (cost(p, q) < cost(p, *best)) best = &q;
+        if (suits(p, q) && cost(p, q) < cost(p, *best)) best = &q;
     return *best;
+}
+
+// (whichever tile: where 64 x 128 is taken in place of a wider one, it is the shorter)
+double least_cost(const DgProblem &p)
+{
+    double least = cost(p, PLANS[0]);
+    for (const TwoPowerPlan &q : PLANS) least = std::min(least, cost(p, q));
+    return least;
 }
 
 bool takes(const dg_lut *lut, const DgProblem &p)
@@ -475,7 +488,7 @@ bool dg_twopower_preferred(const dg_lut *lut, const DgProblem &p)
     double there = 4.4 + 1.09 * busiest + 0.211 * gop + 0.124 * megabytes;                                       // staged
     if (other == DgOneHotForm::Sparse) there = 6.2 + 1.0 * gop + 0.103 * megabytes + 0.96 * thousands;           // direct loads
     else if (other == DgOneHotForm::Dense) there = 3.2 + 2.37 * busiest + 0.12 * gop + 0.348 * megabytes + 0.5 * thousands;
-    return cost(p, twopower_plan(p)) < 0.85 * there;
+    return least_cost(p) < 0.85 * there;
 }
 
 dg_status dg_launch_twopower(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
