@@ -126,6 +126,7 @@ dg_status dg_build_lut_bits(int32_t bits, const int8_t *levels_w, const int8_t *
     t.max_abs = t.max_entry > -t.min_entry ? t.max_entry : -t.min_entry;
     if (bits != 2) dg_find_two_lookups(&t);
     dg_find_bit_sums(&t);
+    dg_find_two_powers(&t);
     dg_lut *p = new (std::nothrow) dg_lut(t);
     if (!p) return dg_fail(DG_ERR_BUFFER, "dg_build_lut: out of host memory");
     *out = p;
@@ -165,6 +166,7 @@ dg_status dg_build_lut_entries(const int16_t entries[16], dg_lut_dtype entry, dg
     }
     t.max_abs = t.max_entry > -t.min_entry ? t.max_entry : -t.min_entry;
     dg_find_bit_sums(&t);
+    dg_find_two_powers(&t);
     dg_lut *p = new (std::nothrow) dg_lut(t);
     if (!p) return dg_fail(DG_ERR_BUFFER, "dg_build_lut_entries: out of host memory");
     *out = p;

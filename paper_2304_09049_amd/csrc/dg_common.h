@@ -23,6 +23,14 @@ struct DgBitSums {
     int32_t most;                // the largest number on the weights' side times the largest on the other
 };
 
+// A 2-bit table that is a product of levels which dg_twopower_kernel.hip takes.
+struct DgTwoPowers {
+    bool levels;
+    uint32_t bytes[6];           // of four FP6 numbers' three bytes: code w's share in byte w
+    uint32_t powers;             // byte a: the two signed powers of activation code a, as FP4
+    int32_t factor, reach;       // reach: the largest magnitude that a position adds, over the factor, its two powers taken apart
+};
+
 // The opaque table object: levels, the 16 products, and what the kernels need to know about them.
 struct dg_lut {
     int32_t bits;        // code width: 2 (the paper's kernels), 3 or 4 (Sec. 3.3); 2^bits levels per side
@@ -37,6 +45,7 @@ struct dg_lut {
     int32_t max_abs;     // max |product|
     DgTwoLookups two[2]; // of the table, and of the transposed one (found when the table is built)
     DgBitSums bit_sums;  // (found when the table is built)
+    DgTwoPowers two_powers;      // (the same)
 };
 
 // 16 table entries passed to kernels by value (no device allocation is needed for a table).
@@ -184,6 +193,7 @@ const char *dg_twopower_config_name(const DgProblem &p);
 // A 2-bit table as factor * u[w] * v[a], u and v whole numbers without a common factor each; false if it is no such product.
 bool dg_find_levels(const dg_lut *lut, int (&u)[4], int (&v)[4], int *factor);
 void dg_find_bit_sums(dg_lut *lut);
+void dg_find_two_powers(dg_lut *lut);
 bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p);    // p.Xp: codes one per byte, by their bits on the int8 instruction
 dg_status dg_launch_planes_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream);
 const char *dg_planes_codes_config_name(const dg_lut *lut, const DgProblem &p);

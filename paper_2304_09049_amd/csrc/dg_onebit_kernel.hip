@@ -626,13 +626,16 @@ bool dg_onebit_codes_preferred(const dg_lut *lut, const DgProblem &p, bool stati
 // DG_ONEBIT_CODES: 2 wherever this kernel would be run on packed codes.
 bool dg_onebit_codes_spare_packing(const dg_lut *lut, const DgProblem &p)
 {
+    if (lut->bits != 2 || p.stride_cm != 1 || p.Qp) return false;
     const char *f = dg_override("DG_ONEBIT_CODES");
-    const bool forced = f && strcmp(f, "2") == 0;
-    if (!takes(lut, p) || p.stride_cm != 1 || p.Qp || (int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * p.Cin >= (int64_t)1 << 31) return false;
-    if (f || onebit_override() >= 0) return forced;
-    const int64_t t1 = tiles_of(p, 1), tm = ((int64_t)p.M + 63) / 64, units = dg_simd_count() / 4, reads = p.KH * p.KW * tm, strides = (int64_t)p.sh * p.sw;
-    if (t1 < 150 || p.K > 1152 || onebit_plan(p).ks != 1 || reads > 5 * strides) return false;
-    return tm == 1 || t1 <= (reads <= 2 * strides ? 6 : 4) * units;
+    if (f || onebit_override() >= 0) {
+        if (!f || strcmp(f, "2") != 0) return false;
+    } else {
+        if (p.K > 1152) return false;
+        const int64_t t1 = tiles_of(p, 1), tm = ((int64_t)p.M + 63) / 64, units = dg_simd_count() / 4, reads = p.KH * p.KW * tm, strides = (int64_t)p.sh * p.sw;
+        if (t1 < 150 || reads > 5 * strides || (tm > 1 && t1 > (reads <= 2 * strides ? 6 : 4) * units) || onebit_plan(p).ks != 1) return false;
+    }
+    return takes(lut, p) && (int64_t)(p.N / (p.OH * p.OW)) * p.H * p.W * p.Cin < (int64_t)1 << 31;
 }
 
 dg_status dg_launch_onebit_codes(const dg_lut *lut, const DgProblem &p, hipStream_t stream)

@@ -192,18 +192,24 @@ Plan plan_for(const dg_lut *lut, const DgProblem &p, Mode mode, int tile = 0)
     return e.plan;
 }
 
-}   // namespace
-
-bool dg_onehot_supports(const dg_lut *lut, const DgProblem &p)
+// (*plan: that of such a problem)
+bool onehot_takes(const dg_lut *lut, const DgProblem &p, Plan *plan)
 {
     if (lut->dtype == DG_LUT_F32) return false;
     // MFMA operands are int8: wider entries take two planes, T = 256 * hi + lo (2-bit codes only, hi within int8)
     if (!fits_int8(lut) && (lut->bits != 2 || lut->max_entry > 127 * 256 + 127)) return false;
     if (p.Cin % (8 * per_byte(lut)) != 0) return false;                // a lane half reads whole words of one tap
     if (!offsets_fit(p, per_byte(lut))) return false;
-    const Plan q = plan_for(lut, p, TABLE);
-    if ((uintptr_t)p.Wp % (4 * q.ch) != 0 || (uintptr_t)p.Xp % (4 * q.ch) != 0) return false;
-    return true;
+    *plan = plan_for(lut, p, TABLE);
+    return (uintptr_t)p.Wp % (4 * plan->ch) == 0 && (uintptr_t)p.Xp % (4 * plan->ch) == 0;
+}
+
+}   // namespace
+
+bool dg_onehot_supports(const dg_lut *lut, const DgProblem &p)
+{
+    Plan q;
+    return onehot_takes(lut, p, &q);
 }
 
 namespace {
@@ -364,16 +370,26 @@ DgOneHotForm dg_onehot_auto_form(const dg_lut *lut, const DgProblem &p, double *
     return q.wm == 1 && q.wn == 4 ? DgOneHotForm::Staged32x128 : DgOneHotForm::Staged;
 }
 
-bool dg_sparse_supports(const dg_lut *lut, const DgProblem &p)
+namespace {
+
+// (*plan: that of such a problem as the sparse kernel runs it)
+bool sparse_takes(const dg_lut *lut, const DgProblem &p, Plan *plan)
 {
     if (lut->dtype == DG_LUT_F32 || lut->bits != 2 || !fits_int8(lut)) return false;
     if (p.Cin % 32 != 0) return false;                                 // a lane half reads whole words of one tap
     if (sparse_transposes(p) && !sparse_can_transpose(p)) return false;
     const DgProblem t = sparse_problem(p);
     if (!offsets_fit(t, 4)) return false;
-    const Plan q = sparse_plan(lut, t);
-    if ((uintptr_t)t.Wp % (4 * q.ch) != 0 || (uintptr_t)t.Xp % (4 * q.ch) != 0) return false;
-    return true;
+    *plan = sparse_plan(lut, t);
+    return (uintptr_t)t.Wp % (4 * plan->ch) == 0 && (uintptr_t)t.Xp % (4 * plan->ch) == 0;
+}
+
+}   // namespace
+
+bool dg_sparse_supports(const dg_lut *lut, const DgProblem &p)
+{
+    Plan q;
+    return sparse_takes(lut, p, &q);
 }
 
 const char *dg_sparse_config_name(const dg_lut *lut, const DgProblem &p)
@@ -748,14 +764,20 @@ void dg_find_two_lookups(dg_lut *lut)
 }
 
 // DG_NIBBLES: 0 never; 1 also while DG_ONEHOT_PLAN is set, which then forces the shape of the kernel (tests, A/B measurement).
-bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p)
+static bool nibble_takes(const dg_lut *lut, const DgProblem &p, Plan *plan)
 {
     if ((lut->bits != 3 && lut->bits != 4) || !lut->two[sparse_transposes(p)].splits) return false;
     const char *e = dg_override("DG_NIBBLES");
     if (e ? atoi(e) == 0 : dg_override("DG_ONEHOT_PLAN") != nullptr) return false;
     if (p.Cin % 16 != 0 || p.K >= (1 << 29)) return false;
     // (every sum of the split table is a sum of T, whose range the API has checked; partial sums wrap and wrap back)
-    return dg_sparse_supports(two_bit_view(), nibble_problem(p));
+    return sparse_takes(two_bit_view(), nibble_problem(p), plan);
+}
+
+bool dg_nibble_preferred(const dg_lut *lut, const DgProblem &p)
+{
+    Plan q;
+    return nibble_takes(lut, p, &q);
 }
 
 const char *dg_nibble_config_name(const dg_lut *, const DgProblem &p)
@@ -961,14 +983,20 @@ Plan staged2p_plan(const DgProblem &t)
 
 }   // namespace
 
-bool dg_staged2p_preferred(const dg_lut *lut, const DgProblem &p)
+static bool staged2p_takes(const dg_lut *lut, const DgProblem &p, Plan *plan)
 {
     if (!dg_sparse2p_supports(lut, p) || dg_override("DG_ONEHOT_PLAN") != nullptr) return false;
     if (const char *e = dg_override("DG_STAGED_2P")) if (atoi(e) == 0) return false;
     const DgProblem t = sparse_problem(p);
     if (t.M >= (1 << 30) || !offsets_fit(t, 4)) return false;
-    const Plan q = staged2p_plan(t);
-    return q.staged && tile_count(t, 1, q.wn) <= INT32_MAX;
+    *plan = staged2p_plan(t);
+    return plan->staged && tile_count(t, 1, plan->wn) <= INT32_MAX;
+}
+
+bool dg_staged2p_preferred(const dg_lut *lut, const DgProblem &p)
+{
+    Plan q;
+    return staged2p_takes(lut, p, &q);
 }
 
 const char *dg_staged2p_config_name(const dg_lut *, const DgProblem &p)
@@ -1012,11 +1040,11 @@ double blocks_on_unit(const DgProblem &p)
 // Fitted to 132 layers of 0.02 to 30 GOP, split K to 900 more (4 to 6 % off on average, split K 23 % at most).
 double dg_onehot_nibble_time(const dg_lut *lut, const DgProblem &p, double codes)
 {
-    if (sparse_transposes(p) || !dg_nibble_preferred(lut, p)) return 0.0;
+    Plan q;
+    if (sparse_transposes(p) || !nibble_takes(lut, p, &q)) return 0.0;
     const DgProblem n = nibble_problem(p);
     const double thousands = 1e-3 * n.K, out = 4e-6 * (double)p.M * p.N;
     if (dg_sparse_ws_preferred(two_bit_view(), n)) return 4.5 + 0.56 * blocks_on_unit(n) + 0.113 * out + 0.287 * codes + 1.96 * thousands;
-    const Plan q = sparse_plan(two_bit_view(), n);
     if (q.split) return 4.93 + 0.85 * blocks_on_unit(n) + 0.48 * out + 0.36 * codes;
     return q.staged ? 5.8 + 1.31 * tiles_on_simd(n, q, q.wm) + 0.174 * out + 0.26 * codes + 0.37 * thousands : 0.0;
 }
@@ -1026,11 +1054,10 @@ double dg_onehot_two_plane_time(const dg_lut *lut, const DgProblem &p)
 {
     if (sparse_transposes(p) || lut->bits != 2 || fits_int8(lut)) return 0.0;
     const double out = 4e-6 * (double)p.M * p.N;
-    if (dg_staged2p_preferred(lut, p)) return 4.9 + 2.53 * tiles_on_simd(p, staged2p_plan(p), 1) + 0.13 * out;
     Plan q;
+    if (staged2p_takes(lut, p, &q)) return 4.9 + 2.53 * tiles_on_simd(p, q, 1) + 0.13 * out;
     if (dg_sparse2p_preferred(lut, p)) q.wn = 4, q.skw = 1, q.split = false;
-    else if (dg_onehot_supports(lut, p)) q = plan_for(lut, p, TABLE);
-    else return 0.0;
+    else if (!onehot_takes(lut, p, &q)) return 0.0;
     if (q.split) return 2.8 + 1.48 * blocks_on_unit(p) + 0.56 * out;
     return 2.8 + 2.81 * tiles_on_simd(p, q, 1) + 0.2 * out + 5.2e-3 * p.K;
 }

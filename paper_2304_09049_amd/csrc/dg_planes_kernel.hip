@@ -17,6 +17,7 @@
 #include "dg_lds_dma.h"
 #include "dg_onehot_kernel.h"
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 
@@ -375,7 +376,11 @@ planes_packed_kernel(PlanesArgs a)
     }
 }
 
-int64_t tiles_of(const DgProblem &p, int pxw) { return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 32 * pxw - 1) / (32 * pxw)); }
+template <int PXW>
+int64_t tiles_of(const DgProblem &p) { return (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 32 * PXW - 1) / (32 * PXW)); }
+
+// Codes of the activations.
+int64_t codes_of(const DgProblem &p) { return (int64_t)(p.N / (p.OH * p.OW)) * p.H * p.W * p.Cin; }
 
 // DG_PLANES: 0 never, 2, 4 this kernel with so many pixel blocks whatever the size; -1 where it is not set, or to anything else.
 int planes_override()
@@ -387,30 +392,32 @@ int planes_override()
 
 // us: once, a round of workgroups (one to a compute unit), a run of one, an MB of output.  Fitted to 222 layers for 2-bit codes, to 700 whichever kernel is the
 // shorter for 3- and 4-bit ones (3 to 4 % off on average, 19 % at most).
-double cost(const DgProblem &p, int bits, int pxw)
+template <int PXW>
+double cost(const DgProblem &p, int bits)
 {
     static const double fits[3][2][4] = {{{1.6, 3.2, 1.28, 0.165}, {2.0, 2.7, 1.06, 0.18}},
                                          {{1.97, 2.28, 1.22, 0.24}, {2.17, 2.22, 1.04, 0.21}},
                                          {{2.04, 2.15, 1.39, 0.25}, {2.32, 2.04, 1.25, 0.22}}};
-    const double *const f = fits[bits - 2][pxw == 4];
-    const int64_t units = dg_simd_count() / 4, rounds = (tiles_of(p, pxw) + units - 1) / units, shares = 8 / pxw;
-    const double runs = (double)((((int64_t)p.K + 127) / 128 + shares - 1) / shares);
+    const double *const f = fits[bits - 2][PXW == 4];
+    const int64_t units = dg_simd_count() / 4, rounds = (tiles_of<PXW>(p) + units - 1) / units;
+    const int runs = ((p.K + 127) / 128 + 8 / PXW - 1) / (8 / PXW);
     return f[0] + (double)rounds * (f[1] + f[2] * runs) + f[3] * 4e-6 * (double)p.M * (double)p.N;
 }
 
 int pixel_blocks(const DgProblem &p, int bits)
 {
     const int forced = planes_override();
-    return forced > 0 ? forced : (cost(p, bits, 2) < cost(p, bits, 4) ? 2 : 4);
+    return forced > 0 ? forced : (cost<2>(p, bits) < cost<4>(p, bits) ? 2 : 4);
 }
 
+// (what most calls fail by first)
 bool takes(const dg_lut *lut, const DgProblem &p)
 {
-    if (!lut->bit_sums.sums || p.stride_cm != 1 || p.Qp) return false;
+    if (!lut->bit_sums.sums || p.stride_cm != 1 || p.Cin % 64 != 0 || p.Qp) return false;
+    if (p.KH * p.KW > 32 || (uintptr_t)p.Wp % 16 != 0 || (uintptr_t)p.Xp % 16 != 0) return false;
     if ((int64_t)p.K * lut->bit_sums.most >= 1 << 23) return false;    // (24-bit products)
-    if (p.Cin % 64 != 0 || p.KH * p.KW > 32 || (uintptr_t)p.Wp % 16 != 0 || (uintptr_t)p.Xp % 16 != 0) return false;
-    if ((int64_t)p.N / ((int64_t)p.OH * p.OW) * p.H * p.W * p.Cin >= (int64_t)1 << 31) return false;               // (32-bit byte offsets)
-    return tiles_of(p, 2) < 1 << 22;                                                                               // (a launch has fewer than 2^32 threads)
+    if (codes_of(p) >= (int64_t)1 << 31) return false;                 // (32-bit byte offsets)
+    return tiles_of<2>(p) < 1 << 22;                                   // (a launch has fewer than 2^32 threads)
 }
 
 }   // namespace
@@ -419,13 +426,18 @@ bool takes(const dg_lut *lut, const DgProblem &p)
 // unit, a workgroup, an MB of output.
 static double packed_cost(const DgProblem &p)
 {
-    const int64_t units = dg_simd_count() / 4, n = (tiles_of(p, 4) + units - 1) / units;
+    const int64_t units = dg_simd_count() / 4, n = (tiles_of<4>(p) + units - 1) / units;
     const double runs = (double)(((int64_t)p.K + 127) / 128), per_run = n == 1 ? 0.611 : (n == 2 ? 0.439 : 0.465);
     return 3.3 + (double)n * (0.575 + per_run * runs) + 0.065 * 4e-6 * (double)p.M * (double)p.N;
 }
 
+static bool packed_pays(const DgProblem &p, double two_planes) { return packed_cost(p) < 0.87 * two_planes; }
+
+static bool beyond_int8(const dg_lut *lut) { return lut->min_entry < -128 || lut->max_entry > 127; }
+
 static bool other_overrides()
 {
+    if (!dg_overrides_enabled()) return false;
     for (const char *name : {"DG_ONEHOT_PLAN", "DG_ONEHOT_WAVES", "DG_NIBBLES", "DG_STAGED_2P", "DG_STAGED_2P_PLAN"})
         if (dg_override(name)) return true;
     return false;
@@ -465,23 +477,17 @@ void dg_find_bit_sums(dg_lut *lut)
 // to which it was fitted, inputs changing from pass to pass, it sends 277 here, 1.29 times as fast on average, none longer.
 bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
 {
-    const int forced = planes_override();
-    if (forced >= 0 ? forced == 0 : other_overrides()) return false;
     if (!takes(lut, p)) return false;
-    if (forced > 0) return true;
-    if (tiles_of(p, 4) > dg_simd_count()) return false;
-    const double codes = 1e-6 * (double)(p.N / ((int64_t)p.OH * p.OW)) * p.H * p.W * p.Cin;
-    double there;
-    if (lut->bits != 2) {
-        there = dg_onehot_nibble_time(lut, p, codes);
-    } else if (lut->min_entry >= -128 && lut->max_entry <= 127) {
-        return false;
-    } else {
-        there = dg_planes_preferred(lut, p) ? packed_cost(p) : dg_onehot_two_plane_time(lut, p);
-        there += 1.9 + 0.08 * codes;                        // (the packing kernel)
-    }
-    const double margin = lut->bits == 2 ? 0.94 : (p.K <= 256 ? 0.88 : 0.92);
-    return cost(p, lut->bits, pixel_blocks(p, lut->bits)) < margin * there && !dg_onebit_preferred(lut, p);
+    const int forced = planes_override();
+    if (forced >= 0) return forced > 0;
+    if (tiles_of<4>(p) > dg_simd_count() || other_overrides()) return false;
+    const double here = std::min(cost<2>(p, lut->bits), cost<4>(p, lut->bits)), codes = 1e-6 * (double)codes_of(p);
+    if (lut->bits != 2) return here < (p.K <= 256 ? 0.88 : 0.92) * dg_onehot_nibble_time(lut, p, codes);
+    if (!beyond_int8(lut)) return false;
+    const double packing = 1.9 + 0.08 * codes, two_planes = dg_onehot_two_plane_time(lut, p);
+    if (here >= 0.94 * (two_planes + packing)) return false;
+    if (packed_pays(p, two_planes) && here >= 0.94 * (packed_cost(p) + packing)) return false;
+    return !dg_onebit_preferred(lut, p);
 }
 
 // AUTO, 2-bit tables with entries beyond int8 on packed codes, where the fit says a seventh less than the kernels in two planes (6 to 12 % off on average): us, those
@@ -491,11 +497,11 @@ bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
 // DG_PLANES_PACKED: "0" never, "1" whatever the size.
 bool dg_planes_preferred(const dg_lut *lut, const DgProblem &p)
 {
+    if (lut->bits != 2 || !beyond_int8(lut) || !takes(lut, p)) return false;
     const char *f = dg_override("DG_PLANES_PACKED");
-    const bool forced = f && strcmp(f, "1") == 0;
     if (f && strcmp(f, "0") == 0) return false;
-    if (lut->bits != 2 || (lut->min_entry >= -128 && lut->max_entry <= 127) || (!forced && other_overrides())) return false;
-    return takes(lut, p) && (forced || packed_cost(p) < 0.87 * dg_onehot_two_plane_time(lut, p));
+    if (f && strcmp(f, "1") == 0) return true;
+    return !other_overrides() && packed_pays(p, dg_onehot_two_plane_time(lut, p));
 }
 
 namespace {

@@ -348,20 +348,25 @@ int fp6(int v)
     return -1;
 }
 
-struct Numbers {
-    uint32_t bytes[6], powers;
-    int32_t factor, reach;   // the largest magnitude that a position adds, over the factor, its two powers taken apart
-};
+}   // namespace
 
-bool find_numbers(const dg_lut *lut, Numbers *n)
+// (once per table: on each choice of a kernel, it was 0.1 us of the call)
+void dg_find_two_powers(dg_lut *lut)
 {
+    DgTwoPowers *const n = &lut->two_powers;
     int u[4], v[4], most_u = 0, most_v = 0;
-    if (!dg_find_levels(lut, u, v, &n->factor)) return false;
-    memset(n->bytes, 0, sizeof(n->bytes));
-    n->powers = 0;
+    memset(n, 0, sizeof(*n));
+    if (!dg_find_levels(lut, u, v, &n->factor)) return;
+    // (activation levels evenly spaced from zero are left to the other kernels: dg_twopower_preferred)
+    bool spaced = true;
+    for (int w = 0; w < 4; ++w) {
+        const int16_t *t = lut->entry + 4 * w;
+        spaced = spaced && t[0] == 0 && t[2] == 2 * t[1] && t[3] == 3 * t[1];
+    }
+    if (spaced) return;
     for (int w = 0; w < 4; ++w) {
         const int f = fp6(u[w]);
-        if (f < 0) return false;
+        if (f < 0) return;
         const int parts[6] = {f, (f & 3) << 6, f >> 2, (f & 15) << 4, f >> 4, f << 2};
         for (int i = 0; i < 6; ++i) n->bytes[i] |= (uint32_t)parts[i] << (8 * w);
         if (abs(u[w]) > most_u) most_u = abs(u[w]);
@@ -375,13 +380,15 @@ bool find_numbers(const dg_lut *lut, Numbers *n)
                     best = abs(power[i]) + abs(power[j]);
                     byte = code[i] | code[j] << 4;
                 }
-        if (best == 100) return false;
+        if (best == 100) return;
         n->powers |= (uint32_t)byte << (8 * a);
         if (best > most_v) most_v = best;
     }
     n->reach = most_u * most_v;
-    return true;
+    n->levels = true;
 }
+
+namespace {
 
 struct TwoPowerPlan {
     int bm, wn, waves, ks;
@@ -450,11 +457,11 @@ double least_cost(const DgProblem &p)
 
 bool takes(const dg_lut *lut, const DgProblem &p)
 {
+    if (!lut->two_powers.levels) return false;
     if (p.KH * p.KW != 1 || p.sh != 1 || p.sw != 1 || p.ph || p.pw || p.Cin % 64 || p.Qp) return false;
     if ((uintptr_t)p.Wp % 16 || (uintptr_t)p.Xp % 16 || (int64_t)p.N * (p.K / 4) >= (int64_t)1 << 31) return false;      // (32-bit byte offsets)
     if (tiles_of(p, PLANS[0]) >= 1 << 22) return false;                // (a launch has fewer than 2^32 threads)
-    Numbers n;
-    return find_numbers(lut, &n) && (int64_t)p.K * n.reach < 1 << 24;  // (multiples of 1/16 below 2^20)
+    return (int64_t)p.K * lut->two_powers.reach < 1 << 24;             // (multiples of 1/16 below 2^20)
 }
 
 }   // namespace
@@ -468,17 +475,10 @@ bool takes(const dg_lut *lut, const DgProblem &p)
 // tests/test_abi_host.py).
 bool dg_twopower_preferred(const dg_lut *lut, const DgProblem &p)
 {
-    if (lut->bits != 2 || lut->dtype == DG_LUT_F32) return false;
+    if (!takes(lut, p)) return false;
     const char *forced = twopower_override();
     const double gop = 2e-9 * (double)p.M * (double)p.N * (double)p.K;
     if (forced ? strcmp(forced, "0") == 0 : gop < 1.5 || dg_override("DG_ONEHOT_PLAN") || dg_override("DG_ONEHOT_WAVES")) return false;
-    if (!takes(lut, p)) return false;
-    bool spaced = true;
-    for (int w = 0; w < 4; ++w) {
-        const int16_t *t = lut->entry + 4 * w;
-        spaced = spaced && t[0] == 0 && t[2] == 2 * t[1] && t[3] == 3 * t[1];
-    }
-    if (spaced) return false;
     if (forced) return true;
     if (lut->min_entry < -128 || lut->max_entry > 127) return false;
     double busiest;
@@ -494,8 +494,7 @@ bool dg_twopower_preferred(const dg_lut *lut, const DgProblem &p)
 dg_status dg_launch_twopower(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
 {
     TwoPowerArgs a;
-    Numbers n;
-    find_numbers(lut, &n);
+    const DgTwoPowers &n = lut->two_powers;
     memcpy(a.bytes, n.bytes, sizeof(a.bytes));
     a.powers = n.powers, a.factor = n.factor;
     a.p = p;
