@@ -19,35 +19,79 @@ CONVS = [  # B, H, W, Cin, Cout, KH, KW, stride, pad
     (1, 9, 11, 64, 36, 3, 3, (1, 1), (1, 1)), (2, 20, 13, 64, 132, 5, 5, (1, 1), (2, 2)), (1, 17, 19, 192, 64, 3, 2, (2, 1), (2, 0)),
     (3, 14, 14, 256, 200, 1, 1, (1, 1), (0, 0)), (2, 15, 14, 320, 68, 1, 1, (2, 2), (1, 1)), (1, 8, 40, 128, 100, 1, 4, (1, 3), (0, 3)),
     (1, 6, 28, 576, 4, 3, 3, (1, 1), (1, 1)), (2, 3, 3, 64, 64, 3, 3, (1, 1), (2, 2)), (1, 12, 12, 64, 65, 1, 1, (1, 1), (0, 0))]
+# how many times as many images the 2-bit layers have: smaller ones pack while loading, whatever DG_PLANES says
+TIMES = (96, 6, 48, 4, 48, 48, 1, 256, 1)
+
+
+def run_layer(bits, plan, layer, lw, la, seed):
+    B, H, W, Cin, Cout, KH, KW, stride, pad = layer
+    lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I16)
+    desc = dg.conv_desc(B, H, W, Cin, Cout, KH, KW, stride, pad)
+    assert dg.dg_conv_codes_kernel_name(lut, desc) == NAMES[plan], layer
+    rng = np.random.default_rng(seed)
+    Wc, Xc = wl.draw_codes(rng, (Cout, KH, KW, Cin), nlev=1 << bits), wl.draw_codes(rng, (B, H, W, Cin), nlev=1 << bits)
+    high = rng.integers(0, 256 >> bits, Xc.shape, dtype=np.uint8) << bits                      # (counts for nothing)
+    codes = torch.from_numpy(Xc | high).cuda()
+    Wp = dg.dg_pack_codes_bits(torch.from_numpy(Wc).cuda(), Cout, KH * KW * Cin, bits)
+    scale = torch.from_numpy(rng.uniform(0.01, 0.1, Cout).astype(np.float32)).cuda()
+    work = torch.full((dg.dg_packed_bytes_bits(B * H * W, Cin, bits),), 77, dtype=torch.uint8, device="cuda")
+    want = oracle.conv2d(Wc, Xc, lw, la, stride=stride, pad=pad)
+    assert np.array_equal(dg.dg_conv2d_lut_codes(lut, Wp, codes, desc, work=work).cpu().numpy(), want), (layer, "int32")
+    got = dg.dg_conv2d_lut_codes(lut, Wp, codes, desc, work=work, scale=scale).cpu().numpy()
+    assert np.array_equal(got, oracle.scale_epilogue_nhwc(want, scale.cpu().numpy())), (layer, "scaled")
+    assert bool((work == 77).all()), layer
+    with pytest.raises(dg.DgError):                         # (a buffer is asked for as ever)
+        dg.dg_conv2d_lut_codes(lut, Wp, codes, desc, work=work[:-1].clone())
 
 
 @pytest.mark.parametrize("plan", ["2", "4"])
 @pytest.mark.parametrize("bits", [2, 3, 4])
 def test_planes_kernel(bits, plan, monkeypatch):
     monkeypatch.setenv("DG_PLANES", plan)
-    for i, (B, H, W, Cin, Cout, KH, KW, stride, pad) in enumerate(CONVS):
+    for i, layer in enumerate(CONVS):
         lw, la = (list(x) for x in TABLES[bits][i % 3])
-        lut = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I16)
-        desc = dg.conv_desc(B, H, W, Cin, Cout, KH, KW, stride, pad)
-        name = dg.dg_conv_codes_kernel_name(lut, desc)
-        if bits == 2 and name != NAMES[plan]:               # (1x1 layers with a stride pack the pixels they read, the smallest ones pack while loading)
-            assert name.startswith(("codes_onehot_mfma_2p", "onehot_mfma_2p")), (i, name)
-            continue
-        assert name == NAMES[plan], i
-        rng = np.random.default_rng(100 * bits + i)
-        Wc, Xc = wl.draw_codes(rng, (Cout, KH, KW, Cin), nlev=1 << bits), wl.draw_codes(rng, (B, H, W, Cin), nlev=1 << bits)
-        high = rng.integers(0, 256 >> bits, Xc.shape, dtype=np.uint8) << bits                  # (counts for nothing)
-        codes = torch.from_numpy(Xc | high).cuda()
-        Wp = dg.dg_pack_codes_bits(torch.from_numpy(Wc).cuda(), Cout, KH * KW * Cin, bits)
-        scale = torch.from_numpy(rng.uniform(0.01, 0.1, Cout).astype(np.float32)).cuda()
-        work = torch.full((dg.dg_packed_bytes_bits(B * H * W, Cin, bits),), 77, dtype=torch.uint8, device="cuda")
-        want = oracle.conv2d(Wc, Xc, lw, la, stride=stride, pad=pad)
-        assert np.array_equal(dg.dg_conv2d_lut_codes(lut, Wp, codes, desc, work=work).cpu().numpy(), want), (i, "int32")
-        got = dg.dg_conv2d_lut_codes(lut, Wp, codes, desc, work=work, scale=scale).cpu().numpy()
-        assert np.array_equal(got, oracle.scale_epilogue_nhwc(want, scale.cpu().numpy())), (i, "scaled")
-        assert bool((work == 77).all()), i
-        with pytest.raises(dg.DgError):                     # (a buffer is asked for as ever)
-            dg.dg_conv2d_lut_codes(lut, Wp, codes, desc, work=work[:-1].clone())
+        run_layer(bits, plan, (layer[0] * TIMES[i],) + layer[1:] if bits == 2 else layer, lw, la, 100 * bits + i)
+
+
+@pytest.mark.parametrize("plan", ["2", "4"])
+def test_every_two_bit_table(plan, monkeypatch):
+    """Three sums to an output, each counting for another part of the table: odd images, and an output width that is no whole tile."""
+    monkeypatch.setenv("DG_PLANES", plan)
+    for i, (lw, la) in enumerate(TABLES[2]):
+        run_layer(2, plan, (12, 14, 14, 256, 200, 1, 1, (1, 1), (0, 0)), list(lw), list(la), i)
+        run_layer(2, plan, (96, 9, 11, 64, 36, 3, 3, (1, 1), (1, 1)), list(lw), list(la), i)
+
+
+LIMITS = {2: ((127, -128, 5, 0), (0, -128, 127, 1), 65472), 3: (range(21, -11, -4), range(0, 24, 3), 171136), 4: (range(-120, 120, 15), range(0, 112, 7), 37248)}
+
+
+@pytest.mark.parametrize("bits,kernel", [(2, "2"), (2, "4"), (2, "packed"), (3, "2"), (3, "4"), (4, "2"), (4, "4")])
+def test_sums_to_the_end_of_the_range(bits, kernel, monkeypatch):
+    """The longest K that is taken, a bit's sum just below 2^23 in magnitude (2-bit: 128 K, 3-bit: 7 * 7 K, 4-bit: 15 * 15 K), the multiplications of whose
+    24 bits would lose the next one's: rows and columns that climb to the largest codes."""
+    lw, la, K = (list(LIMITS[bits][0]), list(LIMITS[bits][1]), LIMITS[bits][2])
+    top = (1 << bits) - 1
+    monkeypatch.setenv("DG_PLANES_PACKED" if kernel == "packed" else "DG_PLANES", "1" if kernel == "packed" else kernel)
+    M, N = 68, 130 if bits != 2 or kernel == "packed" else 1030
+    lut, desc = dg.dg_build_lut_bits(bits, lw, la, dg.DG_LUT_I16), dg.conv_desc(1, N, 1, K, M, 1, 1, (1, 1), (0, 0))
+    name = dg.dg_conv_kernel_name(lut, desc) if kernel == "packed" else dg.dg_conv_codes_kernel_name(lut, desc)
+    assert name == ("planes_64x128" if kernel == "packed" else NAMES[kernel])
+    rng = np.random.default_rng(bits)
+    Wc, Xc = rng.integers(0, top + 1, (M, K), dtype=np.uint8), rng.integers(0, top + 1, (N, K), dtype=np.uint8)
+    for m in range(M):                                      # 2-bit: the codes whose level is the largest and the smallest
+        Wc[m, : K * (m + 1) // M] = (m % 2 if bits == 2 else top)
+    for n in range(0, N, 2):
+        Xc[n, : K * (n + 2) // N] = 1 + n // 2 % 3 if bits == 2 else top
+    Wc[-2:], Xc[N // 2 : N // 2 + 3] = ([[0], [1]] if bits == 2 else top), (np.arange(1, 4)[:, None] if bits == 2 else top)
+    want = np.rint(np.asarray(lw, np.float64)[Wc] @ np.asarray(la, np.float64)[Xc].T).astype(np.int64).T             # (below 2^53: exact)
+    assert np.abs(want).max() < 1 << 31
+    Wp, X = dg.dg_pack_codes_bits(torch.from_numpy(Wc).cuda(), M, K, bits), torch.from_numpy(Xc).cuda()
+    if kernel == "packed":
+        got = dg.dg_conv2d_lut(lut, Wp, dg.dg_pack_codes_bits(X, N, K, bits), desc)
+    else:
+        work = torch.empty(dg.dg_packed_bytes_bits(N, K, bits), dtype=torch.uint8, device="cuda")
+        got = dg.dg_conv2d_lut_codes(lut, Wp, X.view(1, N, 1, K), desc, work=work)
+    assert np.array_equal(got.cpu().numpy().reshape(N, M), want)
 
 
 def test_planes_kernel_on_packed_codes(monkeypatch):
@@ -117,7 +161,8 @@ def test_matrix_products(plan, monkeypatch):
 
 
 @pytest.mark.parametrize("bits,shape,kernel", [(4, (8, 28, 128, 128, 3, 1), "codes_planes_64x64_k4"), (3, (8, 28, 128, 128, 3, 1), "codes_planes_64x64_k4"),
-                                               (2, (8, 28, 256, 256, 3, 1), "codes_planes_64x128_k2"), (3, (5, 112, 128, 112, 3, 2), "codes_planes_64x128_k2"),
+                                               (2, (8, 28, 256, 256, 3, 1), "codes_planes_64x128_k2"), (2, (3, 28, 256, 256, 3, 1), "codes_planes_64x64_k4"),
+                                               (3, (5, 112, 128, 112, 3, 2), "codes_planes_64x128_k2"),
                                                (4, (4, 112, 64, 112, 3, 1), "onehot_smfmac_4as2_staged_32x128"),
                                                (2, (2, 14, 384, 360, 3, 1), "onehot_mfma_2p_splitk_s14")])
 def test_autos_own_choice(bits, shape, kernel):

@@ -68,3 +68,9 @@ def test_the_end_of_the_range():
 def test_override_values(value, monkeypatch):
     monkeypatch.setenv("DG_TWOPOWER", value)
     assert gemm(*BIG).startswith("onehot_" if value == "0" else "twopower_128x512")
+
+
+def test_offsets_of_31_bits(monkeypatch):
+    """2^31 bytes of packed codes."""
+    monkeypatch.setenv("DG_TWOPOWER", "1")
+    assert gemm(64, 26843545, 320) == "twopower_64x128" and not gemm(64, 26843546, 320).startswith("twopower")
