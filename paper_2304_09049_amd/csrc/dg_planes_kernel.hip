@@ -66,7 +66,7 @@ planes_kernel(PlanesArgs a)
     constexpr int SHARE = 2 * WEIGHTS + 2 * PXW * PIXELS;
     constexpr int UNITS = 4 / PXW, WORDS = BITS == 2 ? 2 : 4;          // quarters of a row's run that a thread expands, their packed words
     __shared__ uint4 s_mem[KS * SHARE / 16];
-    __shared__ int32_t s_codes[BITS == 2 ? 4 : 256];        // [share][wavefront][pixel]: sums of codes
+    __shared__ alignas(16) int32_t s_codes[BITS == 2 ? 4 : 256];       // [share][wavefront][pixel]: sums of codes
     const DgProblem &p = a.p;
     dg_fetch_arguments<sizeof(a)>();
     const int lane = threadIdx.x & 63, all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 31, h = lane >> 5;
@@ -217,7 +217,7 @@ planes_kernel(PlanesArgs a)
     }
     dg_wait_for_loads();                                    // (fetches past the end: their LDS writes end before the wavefront does)
 
-    if constexpr (BITS == 2) {                              // (sums below 2^23, what they count for below 2^17: the host checks)
+    if constexpr (BITS == 2) {                              // (sums below 2^23: takes; what they count for below 2^17, three entries of 16 bits)
 #pragma unroll
         for (int bm = 0; bm < 2; ++bm)
 #pragma unroll
