@@ -431,7 +431,12 @@ static double packed_cost(const DgProblem &p)
     return 3.3 + (double)n * (0.575 + per_run * runs) + 0.065 * 4e-6 * (double)p.M * (double)p.N;
 }
 
-static bool packed_pays(const DgProblem &p, double two_planes) { return packed_cost(p) < 0.87 * two_planes; }
+// (K = 64 is half of a run, and beyond 64 MB its output's stores are all: us, two planes and this one, 56x56x64 -> 1480 stride 2 at batch 26 27.0, 27.9; 28x27x64 ->
+// 1968 at batch 23 34.9, 35.9; with less 56x56x64 -> 804 at batch 4 14.8, 12.7; of 27 such layers 4 % shorter on average, seven up to 3 % longer, all of those with more)
+static bool packed_pays(const DgProblem &p, double two_planes)
+{
+    return packed_cost(p) < 0.87 * two_planes && (p.K > 64 || 4e-6 * (double)p.M * (double)p.N <= 64.0);
+}
 
 static bool beyond_int8(const dg_lut *lut) { return lut->min_entry < -128 || lut->max_entry > 127; }
 

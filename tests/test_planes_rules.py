@@ -38,6 +38,14 @@ def test_layers_by_their_bits(bits, layer, kernel):
 WIDE = ((127, -128, 5, 0), (0, -128, 127, 1))
 
 
+def test_large_outputs_of_half_runs_stay_in_two_planes():
+    lut = dg.dg_build_lut(*WIDE, dg.DG_LUT_I16)
+    name = lambda B, H, W, Cin, Cout, s: dg.dg_conv_kernel_name(lut, dg.conv_desc(B, H, W, Cin, Cout, 1, 1, (s, s), (0, 0)))
+    for layer in ((26, 56, 56, 64, 1480, 2), (23, 28, 27, 64, 1968, 1), (3, 112, 112, 64, 652, 1)):          # up to 3 % longer by their bits
+        assert name(*layer).startswith("onehot_mfma_2p_"), layer
+    assert name(4, 56, 56, 64, 804, 1) == name(26, 56, 56, 128, 1480, 2) == "planes_64x128"
+
+
 @pytest.mark.parametrize("bits,K", [(2, 65472), (3, 171136), (4, 37248)])
 def test_the_end_of_the_range(bits, K, monkeypatch):
     """The largest K times the largest of a bit's products below 2^23: 128 (2-bit codes), 7 * 7 and 15 * 15."""
