@@ -25,7 +25,7 @@
 // random operands take 18.4 at 1.77 GHz, constant ones 13.5 at 2.4), by the start, the end and lone wavefronts' issue slots on those of a few
 // microseconds: a run of the 64 x 128 tile takes 0.5 us then.  The staged sparse kernel, this one (packed codes, graph replays, us):
 //   8192-cube 648, 356          56x56x256 -> 256 3x3 at batch 16 47.1, 30.6          28x28x512 -> 512 3x3 at batch 16 46.1, 29.9
-//   28x28x128 -> 128 3x3 at batch 32 12.2, 8.5          28x28x256 -> 256 3x3 at batch 8 10.9, 7.9          3569 x 7478 x 704 81.5, 28.3
+//   28x28x128 -> 128 3x3 at batch 32 12.2, 8.6          28x28x256 -> 256 3x3 at batch 8 10.9, 7.9          3569 x 7478 x 704 81.5, 28.3
 // (the last by its stores too: dg_output_cached).
 #include "dg_lds_dma.h"
 #include "dg_onehot_kernel.h"
@@ -98,7 +98,9 @@ __device__ __forceinline__ void place_pixel(const OneBitArgs &a, int n, int byte
 //
 // KS = 2: eight wavefronts, two to a tile, each with half of K; their sums meet in LDS.  TAPS: a filter window.  TR: channels on the
 // matrix instruction's columns (dg_mfma_tile.h).
-template <int WN, int KS, bool TAPS, bool TR>
+// FIRST: a run's words are read from LDS before the next run's loads start, whose addresses are vector instructions in which the matrix pipe would wait.
+// The loads then start later, which is the longer where they come from beyond the L2 caches or are the only thing to wait for (reads_first).
+template <int WN, int KS, bool TAPS, bool TR, bool FIRST>
 __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, uint32_t block, uint32_t blocks, int part)
 {
     constexpr int WEIGHTS = 8192;                           // bytes of a run's weight operands: 64 rows, 256 positions
@@ -226,10 +228,10 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
         const v4i next = raw;
         __syncthreads();
         Words t[2];
-        read(t[0], odd, 0);                                 // (before the next run's addresses are worked out, which take longer: 28x28x256 -> 256
-        read(t[1], odd, 1);                                 // 3x3 at batch 8 8.2 -> 7.9 us, 28x28x128 -> 128 3x3 at batch 32 8.6 -> 8.5)
+        if constexpr (FIRST) read(t[0], odd, 0), read(t[1], odd, 1);
         fetch(g + 1, odd ^ 1);
         raw = load_weights(g + 2);
+        if constexpr (!FIRST) read(t[0], odd, 0), read(t[1], odd, 1);
         const uint32_t to = (odd ^ 1) * WEIGHTS;
         multiply(t[0]);
         read(t[0], odd, 2);
@@ -274,14 +276,14 @@ __device__ __forceinline__ void onebit_tile(const OneBitArgs &a, uint4 *s_mem, u
 }
 
 // WN = 2: the last workgroups may take narrow tiles (onebit_plan).
-template <int WN, int KS, bool TAPS, bool TR>
+template <int WN, int KS, bool TAPS, bool TR, bool FIRST = (WN > 1 || !TR)>
 __global__ void __launch_bounds__(256 * KS, 2)
 onebit_kernel(OneBitArgs a)
 {
     __shared__ uint4 s_mem[KS * (16384 + WN * 16384) / 16];
     dg_fetch_arguments<sizeof(a)>();
-    if (WN == 2 && blockIdx.x >= a.wide) onebit_tile<1, 1, TAPS, TR>(a, s_mem, blockIdx.x - a.wide, gridDim.x - a.wide, 1);
-    else onebit_tile<WN, KS, TAPS, TR>(a, s_mem, blockIdx.x, WN == 2 ? a.wide : gridDim.x, 0);
+    if (WN == 2 && blockIdx.x >= a.wide) onebit_tile<1, 1, TAPS, TR, !TR>(a, s_mem, blockIdx.x - a.wide, gridDim.x - a.wide, 1);
+    else onebit_tile<WN, KS, TAPS, TR, FIRST>(a, s_mem, blockIdx.x, WN == 2 ? a.wide : gridDim.x, 0);
 }
 
 // The same from activations that are still one code per byte (p.Xp = those bytes): 64 channels x 4 x 32 pixels, runs of 128 positions.  Nothing is
@@ -564,6 +566,19 @@ void fill(const dg_lut *lut, const DgProblem &p, const OneBitPlan &q, OneBitArgs
 
 }   // namespace
 
+// Which forms read a run's words first (FIRST), us, loads first and words first, inputs changing (780 calls, each form's mean in brackets):
+//  - wide tiles, a little (0.992)
+//  - 64 x 128: where the output's rows are channels (0.993); else the loads go first, 1201 x 7199 x 384 column-major 12.8, 13.9, 14x16x448 -> 1120 5x5 at
+//    batch 9 37.1, 38.5 (1.007)
+//  - with K shared by two: where there is a filter window, 28x28x256 -> 256 3x3 at batch 8 8.2, 7.9 (0.964); without one the loads are all that a run waits
+//    for, 729 x 486 x 7488 15.9, 17.5 (1.029).  Nor with more weights and activations than an XCD's L2 cache holds: of 400 such layers the 298 with less than
+//    4 MB are 0.961, one 4 % longer; those from 7 MB 1.034, 28x28x2496 -> 896 5x5 at batch 2 100, 117.
+static bool reads_first(const DgProblem &p)
+{
+    const int64_t codes = (int64_t)p.M * p.K + (int64_t)(p.N / (p.OH * p.OW)) * p.H * p.W * p.Cin;
+    return codes <= (int64_t)1 << 24;
+}
+
 dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t stream)
 {
     const OneBitPlan q = onebit_plan(p);
@@ -571,17 +586,20 @@ dg_status dg_launch_onebit(const dg_lut *lut, const DgProblem &p, hipStream_t st
     fill(lut, p, q, &a);
     const dim3 grid(a.wide + (unsigned)((((int64_t)p.M + 63) / 64) * a.tiles_n[1]));
     const bool taps = p.KH * p.KW > 1, rows_m = rows_are_channels(p);
-#define DG_ONEBIT_FORM(WN, KS, TAPS, TR) hipLaunchKernelGGL((onebit_kernel<WN, KS, TAPS, TR>), grid, dim3(256 * KS), 0, stream, a)
-#define DG_ONEBIT(WN, KS) \
+#define DG_ONEBIT_FORM(WN, KS, ...) hipLaunchKernelGGL((onebit_kernel<WN, KS, __VA_ARGS__>), grid, dim3(256 * KS), 0, stream, a)
+#define DG_ONEBIT(WN) \
     do { \
-        if (rows_m) DG_ONEBIT_FORM(WN, KS, false, false); \
-        else if (taps) DG_ONEBIT_FORM(WN, KS, true, true); \
-        else DG_ONEBIT_FORM(WN, KS, false, true); \
+        if (rows_m) DG_ONEBIT_FORM(WN, 1, false, false); \
+        else if (taps) DG_ONEBIT_FORM(WN, 1, true, true); \
+        else DG_ONEBIT_FORM(WN, 1, false, true); \
     } while (0)
-    if (q.wn == 4) DG_ONEBIT(4, 1);
-    else if (q.wn == 2) DG_ONEBIT(2, 1);
-    else if (q.ks == 2) DG_ONEBIT(1, 2);
-    else DG_ONEBIT(1, 1);
+    if (q.wn == 4) DG_ONEBIT(4);
+    else if (q.wn == 2) DG_ONEBIT(2);
+    else if (q.ks == 1) DG_ONEBIT(1);
+    else if (rows_m) DG_ONEBIT_FORM(1, 2, false, false, false);
+    else if (!taps) DG_ONEBIT_FORM(1, 2, false, true, false);
+    else if (reads_first(p)) DG_ONEBIT_FORM(1, 2, true, true, true);
+    else DG_ONEBIT_FORM(1, 2, true, true, false);
 #undef DG_ONEBIT
 #undef DG_ONEBIT_FORM
     return dg_check_launch("onebit_kernel");

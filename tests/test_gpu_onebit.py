@@ -146,6 +146,28 @@ def test_autos_own_plans(M, N, K, kernel):
     assert np.array_equal(out.cpu().numpy().T, want)
 
 
+@pytest.mark.parametrize("B", [20, 21])
+def test_window_and_shared_k_on_both_sides_of_the_caches(B, monkeypatch):
+    """Weights and activations of 2^24 codes, from which on another form runs: sampled sums, re-quantised ones of the same pixels."""
+    H, Cin, Cout, k = 56, 256, 68, 3
+    assert (B * H * H * Cin + Cout * k * k * Cin > 1 << 24) == (B == 21)
+    monkeypatch.setenv("DG_ONEBIT", "12")
+    lw, la = TABLES[1]
+    lut, desc = dg.dg_build_lut(lw, la, dg.DG_LUT_I16), dg.conv_desc(B, H, H, Cin, Cout, k, k, (1, 1), (1, 1))
+    assert dg.dg_conv_kernel_name(lut, desc) == NAMES["12"]
+    rng = np.random.default_rng(B)
+    Wc, Xc = wl.draw_codes(rng, (Cout, k, k, Cin)), wl.draw_codes(rng, (B, H, H, Cin))
+    size = B * H * H * Cout
+    pos = np.unique(np.concatenate([rng.integers(0, size, 20000), np.arange(4 * Cout), size - 1 - np.arange(4 * Cout)]))
+    want = oracle.conv2d_sampled(Wc, Xc, lw, la, pos, stride=(1, 1), pad=(1, 1))
+    Wp, Xp = dg.dg_pack_weights(torch.from_numpy(Wc).cuda(), Cout, k * k * Cin), dg.dg_pack_activations(torch.from_numpy(Xc).cuda(), B * H * H, Cin)
+    assert np.array_equal(dg.dg_conv2d_lut(lut, Wp, Xp, desc).cpu().numpy().reshape(-1)[pos], want)
+    scale = rng.uniform(0.001, 0.01, Cout).astype(np.float32)
+    got = dg.dg_conv2d_lut_requant(lut, Wp, Xp, desc, torch.from_numpy(scale).cuda(), 1.5, 0.5, 0).cpu().numpy().reshape(-1)
+    codes = np.clip(np.rint(np.float32(1.5) * (want.astype(np.float32) * scale[pos % Cout]) + np.float32(0.5)), 0, 3).astype(np.uint8)
+    assert np.array_equal(got[pos // 4] >> (2 * (pos % 4)) & 3, codes)
+
+
 @pytest.mark.parametrize("codes", [False, True])
 def test_padding_pixel_at_the_end_of_the_32_bit_offsets(codes, monkeypatch):
     """A padded 1x1 layer whose pixels below the image would lie just under byte 2^31: every output is padding, hence zero, wherever in the

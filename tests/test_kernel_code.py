@@ -93,3 +93,20 @@ def test_twopower_loops_keep_their_registers(tmp_path):
         mains = [body for body in loops if "s_barrier" in body and body.count("v_mfma") >= 16]
         assert len(mains) == 1, name
         assert "scratch_" not in mains[0], name
+
+
+def test_onebit_loops_start_their_loads_as_measured(tmp_path):
+    """The next run's loads start before this run's words are read from LDS where a run waits for nothing else: narrow tiles whose outputs' rows are
+    pixels, and K shared by two without a window or beyond the caches.  In the other forms the loads' addresses would hold up the matrix instructions."""
+    text = compile_listing(tmp_path, os.path.join(CSRC, "dg_onebit_kernel.hip"))
+    kernels = re.findall(r"^\S*onebit_kernelILi(\d)ELi(\d)ELb(\d)ELb(\d)ELb(\d)E\S*:(.*?)^\.Lfunc_end", text, re.M | re.S)
+    assert len(kernels) == 3 * 3 + 4
+    for wn, ks, taps, tr, first, code in kernels:
+        loops = [body for _, body in re.findall(r"^(\.LBB\d+_\d+):[^\n]*Inner Loop(.*?)s_cbranch_\w+ \1$", code, re.M | re.S)]
+        mains = [body[body.index("s_barrier"):] for body in loops if "s_barrier" in body and body.count("v_mfma") >= 16]
+        assert len(mains) == (2 if wn == "2" else 1)
+        for body in mains:
+            narrow = body.count("v_mfma") == 16
+            reads_first = body.index("ds_read") < body.index("buffer_load")
+            want = not narrow or (first == "1" and taps == "1" if ks == "2" else tr == "0")
+            assert reads_first == want, (wn, ks, taps, tr, first, body.count("v_mfma"))
