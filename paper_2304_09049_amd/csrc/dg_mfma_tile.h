@@ -154,7 +154,8 @@ __device__ __forceinline__ void dg_mfma_store_block(const DgProblem &p, const dg
 }
 
 // Store NQ groups of four registers of a block, the first one group q0 (TR layout; a partial last block of channels as with EDGE_COLUMNS
-// above; always past the caches: shared tiles belong to layers of a few microseconds, whose outputs gain 4 % at most the other way).
+// above; always past the caches, whatever dg_output_cached says: shared tiles belong to layers of a few microseconds, whose outputs gain 4 % at most the other
+// way; the kernel by the codes' bits has up to four rounds of tiles, 32 MB, for which the other way was not measured).
 template <int NQ>
 __device__ __forceinline__ void dg_mfma_store_quads(const DgProblem &p, const dg_v4i (&acc)[NQ], int q0, int mb, int nb, int lane, float sc)
 {

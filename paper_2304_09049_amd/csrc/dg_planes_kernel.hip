@@ -479,7 +479,8 @@ void dg_find_bit_sums(dg_lut *lut)
 // 116x116x64 -> 104 3x3 at batch 13, beyond int8, 72, 79), on long K with few tiles (14x14x384 -> 360 3x3 at batch 2, beyond int8, 10.1, 14.2), and with 3-
 // and 4-bit codes where the split-K kernel has few blocks to a compute unit and a share here one run (315 x 128 -> 1564, 4-bit, 5.8, 6.7; 36x36x64 -> 352
 // stride 2 at batch 17, 4-bit, 8.2, 10.0; 734 x 64 -> 424, 3-bit, 6.1, 6.3): the fit has to say an eighth less there.  Of the 1400 layers of 3- and 4-bit codes
-// to which it was fitted, inputs changing from pass to pass, it sends 277 here, 1.29 times as fast on average, none longer.
+// to which it was fitted, inputs changing from pass to pass, it sends 277 here, 1.29 times as fast on average, none longer; of 920 others that it sends here, 1.28
+// times on average, one is 6 % longer (56x65x128 -> 552 stride 2, 3-bit, 6.0, 6.4); of 602 of entries beyond int8, 1.37 times, none.
 bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
 {
     if (!takes(lut, p)) return false;
@@ -498,7 +499,8 @@ bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
 // AUTO, 2-bit tables with entries beyond int8 on packed codes, where the fit says a seventh less than the kernels in two planes (6 to 12 % off on average): us, those
 // and this one, 56x56x256 -> 256 3x3 at batch 16 94, 70; 116x116x64 -> 104 3x3 at batch 13 66, 41; 28x28x256 -> 256 3x3 at batch 16 26.9, 21.0;
 // 112x112x128 -> 40 3x3 at batch 4 16.5, 12.6; not 28x28x128 -> 128 3x3 at batch 8 8.3, 9.2; 14x14x384 -> 360 3x3 at batch 2 8.2, 20.4; 34x34x128 -> 352 at batch
-// 4 4.9, 5.5.  Of 240 drawn layers 70 go here, 1.38 times as fast on average, none slower.
+// 4 4.9, 5.5.  Of the 240 layers to which it was fitted 70 go here, 1.38 times as fast on average, none slower; 230 others that it sent here were 1.41 times as fast,
+// two of them 3 % longer, with K = 64 (packed_pays).
 // DG_PLANES_PACKED: "0" never, "1" whatever the size.
 bool dg_planes_preferred(const dg_lut *lut, const DgProblem &p)
 {

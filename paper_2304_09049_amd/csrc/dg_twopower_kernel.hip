@@ -13,11 +13,12 @@
 // activation's 19.  So the tiles are as large as the registers allow: up to 128 channels x 512 pixels to a workgroup of eight
 // wavefronts, which share the channels' numbers (made once a run of 256 positions, 16 codes of a row a thread and word, and handed over in LDS) and have 64
 // pixels each, whose packed words lie in LDS and whose powers are made where they are used, for four blocks of channels.  That is 7
-// vector instructions per matrix instruction.  Bound by the chip's power: 25.9 ns per instruction and SIMD in the
-// steady state, 23.6 with neither operand made, 20.2 with such operands in registers and nothing else (17.2 for single bits by FP4 levels), and
-// by the output, which a lone workgroup of a compute unit stores with its matrix pipe idle, 10 us a round of the largest tiles.  In the
-// narrow tiles the vector unit is the bound: 18 instructions beside each matrix instruction, 77 cycles for its 32.
-// Measured, us, the sparse kernels and this one (packed codes, graph replays):
+// vector instructions per matrix instruction.  On the 8192-cube, 420 to 460 us on a settled clock, an instruction and SIMD takes
+// 25.9 to 28.1 ns: the pipe is busy for 0.58 of the cycles, at 1.99 GHz; a wavefront waits for 28 % of its own and has an instruction ready that is not issued
+// for 34 %: two wavefronts to a SIMD do not fill it.  Power comes next: such operands in registers and nothing else take 19.2 (single bits by FP4
+// levels 16.4, zeros 13.6), the loop with neither operand made 23.6.  The output, which a lone workgroup of a compute unit stores with its matrix pipe idle, is
+// 10 us a round of the largest tiles.  In the narrow tiles the vector unit is the bound: 18 instructions beside each matrix instruction, 77 cycles for its 32.
+// Measured, us, the sparse kernels and this one (packed codes, graph replays; both on one card):
 //   8192-cube 725, 454          4096-cube 97, 63          4873 x 7116 x 4672 387, 176          6481 x 5352 x 1472 131, 67
 //   1305 x 1621 x 1856 20.8, 14.1          656 x 6500 x 896 17.6, 11.4          1900 x 1877 x 960 16.7, 11.0
 #include "dg_lds_dma.h"
@@ -468,7 +469,8 @@ bool takes(const dg_lut *lut, const DgProblem &p)
 
 // AUTO takes such tables here where the shortest plan is clearly shorter than the one-hot kernels would be, whose times were fitted to the same
 // 308 products (us; 6 to 8 % off on average).  Of those 111 are, all of them rightly, 1.45 times as fast on average; without the margin two more would be
-// up to 9 % behind (6509 x 160 x 2688 10.7, 11.8).  Left to the others: fewer than 1.5e9 operations (384 x 1742 x 896 6.3, 7.1), products that split K
+// up to 9 % behind (6509 x 160 x 2688 10.7, 11.8).  Of 1049 that were in no fit and that it sends here, 1.43 times on average, one is 2 % longer (175 x 34340 x
+// 6144 73.8, 75.4).  Left to the others: fewer than 1.5e9 operations (384 x 1742 x 896 6.3, 7.1), products that split K
 // over a workgroup (304 x 561 x 4224 7.1, 14.4), long K with few tiles (4607 x 200 x 7040 15.4, 22.4; 8192 x 256 x 8192 25.5, 26.7), K = 64, 128,
 // 256 and 512 where the stationary-weight kernel runs, and tables whose activation levels are evenly spaced from zero (dg_onebit_kernel.hip
 // takes most; those whose weight levels FP4 has not would be shorter here, and AUTO is held to the one-hot kernels for them:
