@@ -1037,15 +1037,16 @@ double blocks_on_unit(const DgProblem &p)
 
 }   // namespace
 
-// Fitted to 132 layers of 0.02 to 30 GOP, split K to 900 more (4 to 6 % off on average, split K 23 % at most).
+// Staged tiles fitted to 132 layers of 0.02 to 30 GOP (6 % off on average), split K to 900 more (2 and 3 %, 20 % at most), stationary weights to 132 more (4 %).
 double dg_onehot_nibble_time(const dg_lut *lut, const DgProblem &p, double codes)
 {
     Plan q;
     if (sparse_transposes(p) || !nibble_takes(lut, p, &q)) return 0.0;
     const DgProblem n = nibble_problem(p);
     const double thousands = 1e-3 * n.K, out = 4e-6 * (double)p.M * p.N;
-    if (dg_sparse_ws_preferred(two_bit_view(), n)) return 4.5 + 0.56 * blocks_on_unit(n) + 0.113 * out + 0.287 * codes + 1.96 * thousands;
-    if (q.split) return 4.93 + 0.85 * blocks_on_unit(n) + 0.48 * out + 0.36 * codes;
+    if (dg_sparse_ws_preferred(two_bit_view(), n)) return 4.6 + 0.688 * blocks_on_unit(n) + 0.11 * out + 0.361 * codes + 2.34 * thousands;
+    if (q.split && p.K <= 256) return 4.24 + 1.46 * blocks_on_unit(n) + 0.194 * out + 0.317 * codes + 75.3 / p.K;      // (fewer wavefronts, the shorter K is)
+    if (q.split) return 4.86 + 0.854 * blocks_on_unit(n) + 0.65 * out + 0.382 * codes;
     return q.staged ? 5.8 + 1.31 * tiles_on_simd(n, q, q.wm) + 0.174 * out + 0.26 * codes + 0.37 * thousands : 0.0;
 }
 

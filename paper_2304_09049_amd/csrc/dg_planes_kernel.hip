@@ -478,9 +478,9 @@ void dg_find_bit_sums(dg_lut *lut)
 // again for every 64 channels (112x112x64 -> 112 3x3 at batch 4, 4-bit 19.9, 29.9; with more than four rounds the fit is not asked:
 // 116x116x64 -> 104 3x3 at batch 13, beyond int8, 72, 79), on long K with few tiles (14x14x384 -> 360 3x3 at batch 2, beyond int8, 10.1, 14.2), and with 3-
 // and 4-bit codes where the split-K kernel has few blocks to a compute unit and a share here one run (315 x 128 -> 1564, 4-bit, 5.8, 6.7; 36x36x64 -> 352
-// stride 2 at batch 17, 4-bit, 8.2, 10.0; 734 x 64 -> 424, 3-bit, 6.1, 6.3): the fit has to say an eighth less there.  Of the 1400 layers of 3- and 4-bit codes
-// to which it was fitted, inputs changing from pass to pass, it sends 277 here, 1.29 times as fast on average, none longer; of 920 others that it sends here, 1.28
-// times on average, one is 6 % longer (56x65x128 -> 552 stride 2, 3-bit, 6.0, 6.4); of 602 of entries beyond int8, 1.37 times, none.
+// stride 2 at batch 17, 4-bit, 8.2, 10.0; 715 x 384 -> 252, 4-bit, 5.7, 6.0): the fit has to say more there.  Of the 1400 layers of 3- and 4-bit codes to which it was
+// fitted, inputs changing from pass to pass, it sends 305 here, 1.28 times as fast on average, none longer; of 1427 others that it sends here, 1.27 times on
+// average, two are 3 % longer; of 602 of entries beyond int8, 1.37 times, none.
 bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
 {
     if (!takes(lut, p)) return false;
@@ -488,7 +488,10 @@ bool dg_planes_codes_preferred(const dg_lut *lut, const DgProblem &p)
     if (forced >= 0) return forced > 0;
     if (tiles_of<4>(p) > dg_simd_count() || other_overrides()) return false;
     const double here = std::min(cost<2>(p, lut->bits), cost<4>(p, lut->bits)), codes = 1e-6 * (double)codes_of(p);
-    if (lut->bits != 2) return here < (p.K <= 256 ? 0.88 : 0.92) * dg_onehot_nibble_time(lut, p, codes);
+    if (lut->bits != 2) {
+        const double margin = p.K > 512 ? 0.95 : (p.K > 256 || p.sh * p.sw == 1 ? 0.92 : 0.88);
+        return here < margin * dg_onehot_nibble_time(lut, p, codes);
+    }
     if (!beyond_int8(lut)) return false;
     const double packing = 1.9 + 0.08 * codes, two_planes = dg_onehot_two_plane_time(lut, p);
     if (here >= 0.94 * (two_planes + packing)) return false;

@@ -21,7 +21,7 @@ def names(bits, B, H, W, Cin, Cout, k, s=1):
 
 @pytest.mark.parametrize("bits,layer", [(4, (315, 1, 1, 128, 1564, 1)), (3, (341, 1, 1, 128, 744, 1)), (4, (17, 36, 36, 64, 352, 1, 2)), (3, (19, 28, 28, 64, 544, 1, 2)),
                                         (4, (727, 1, 1, 128, 516, 1)), (4, (1855, 1, 1, 192, 140, 1)), (3, (729, 1, 1, 256, 324, 1)), (4, (286, 1, 1, 256, 1628, 1)),
-                                        (4, (8, 28, 28, 64, 780, 1, 2)), (3, (734, 1, 1, 64, 424, 1))])
+                                        (4, (8, 28, 28, 64, 780, 1, 2)), (3, (734, 1, 1, 64, 424, 1)), (4, (715, 1, 1, 384, 252, 1)), (3, (15, 7, 7, 320, 844, 1, 2))])
 def test_short_sums_of_few_blocks_are_packed_first(bits, layer):
     """Layers that measured 3 to 25 % longer by the codes' bits."""
     packed, codes = names(bits, *layer)
@@ -29,7 +29,8 @@ def test_short_sums_of_few_blocks_are_packed_first(bits, layer):
 
 
 @pytest.mark.parametrize("bits,layer,kernel", [(4, (8, 28, 28, 128, 128, 3), "codes_planes_64x64_k4"), (3, (8, 28, 28, 128, 128, 3), "codes_planes_64x64_k4"),
-                                               (3, (5, 112, 112, 128, 112, 3, 2), "codes_planes_64x128_k2")])
+                                               (3, (5, 112, 112, 128, 112, 3, 2), "codes_planes_64x128_k2"), (4, (8, 56, 56, 128, 48, 1), "codes_planes_64x128_k2"),
+                                               (3, (5, 56, 56, 64, 24, 1), "codes_planes_64x128_k2")])
 def test_layers_by_their_bits(bits, layer, kernel):
     packed, codes = names(bits, *layer)
     assert packed.startswith("onehot_smfmac_4as2_") and codes == kernel
