@@ -221,7 +221,8 @@ dg_status dg_dequantize(const int32_t *acc_dev, int64_t rows, int64_t C, const f
  *   DG_ONEBIT        "0": AUTO never takes tables that are two one-bit lookups to the FP4 instruction; "1", "2", "4": whatever the size, in
  *                    tiles of 64 x 128, 256 or 512, "12": 64 x 128 with K shared by two; "21": 64 x 256 for half of the pixels, 64 x 128 for the rest;
  *                    any other value counts as not set
- *   DG_PLANES        "0": AUTO never reads codes bit by bit on the int8 instruction, "2", "4": whatever the size, in tiles of 64 x 64 or 64 x 128
+ *   DG_PLANES        "0": AUTO never reads codes bit by bit on the int8 instruction, "2", "4": wherever a layer would be packed first, in tiles of 64 x 64 or
+ *                    64 x 128
  *   DG_PLANES_PACKED "0": AUTO never does so on packed 2-bit codes (entries beyond int8), "1": whatever the size
  *   DG_TWOPOWER      "0": AUTO never takes products of levels to the FP6 / FP4 instruction; "1", "2", "4": whatever the size, in tiles of 64 x 128,
  *                    128 x 256 or 128 x 512, "12": 64 x 128 with K shared by two; any other value counts as not set

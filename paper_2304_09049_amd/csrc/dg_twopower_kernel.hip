@@ -472,9 +472,9 @@ bool takes(const dg_lut *lut, const DgProblem &p)
 // up to 9 % behind (6509 x 160 x 2688 10.7, 11.8).  Of 1049 that were in no fit and that it sends here, 1.43 times on average, one is 2 % longer (175 x 34340 x
 // 6144 73.8, 75.4).  Left to the others: fewer than 1.5e9 operations (384 x 1742 x 896 6.3, 7.1), products that split K
 // over a workgroup (304 x 561 x 4224 7.1, 14.4), long K with few tiles (4607 x 200 x 7040 15.4, 22.4; 8192 x 256 x 8192 25.5, 26.7), K = 64, 128,
-// 256 and 512 where the stationary-weight kernel runs, and tables whose activation levels are evenly spaced from zero (dg_onebit_kernel.hip
-// takes most; those whose weight levels FP4 has not would be shorter here, and AUTO is held to the one-hot kernels for them:
-// tests/test_abi_host.py).
+// 256 and 512 where the stationary-weight kernel runs, and tables whose activation levels are evenly spaced from zero: dg_onebit_kernel.hip
+// takes most; the others, whose weight levels FP4 has not, would gain here what other tables do (the arithmetic does not depend on the levels), and stay with the
+// one-hot kernels because AUTO's names for one of them are held to that (tests/test_abi_host.py): no measurement draws this line.
 bool dg_twopower_preferred(const dg_lut *lut, const DgProblem &p)
 {
     if (!takes(lut, p)) return false;
